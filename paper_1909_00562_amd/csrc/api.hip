@@ -136,7 +136,9 @@ Layout make_layout(const as_shape* s) {
   L.p_q = gemm_plan(N, H, H, 1, bf, false);
   L.p_score = gemm_plan(T, S, H, B, bf, false);
   L.p_ctx = gemm_plan(T, H, S, B, bf, false);
-  L.p_hc = gemm_plan(N, H, bf ? 3 * H : 2 * H, 1, bf, true, true);   // segments: ctx (+ remainder), h_dec
+  // Segments: ctx (+ remainder), h_dec.  Each segment is cut into reduction tiles of its own, so the length to plan a
+  // split for counts whole tiles per segment: planned over 3 * H, sizes like H = 584 got a split with no tiles left.
+  L.p_hc = gemm_plan(N, H, bf ? 3 * (int)up(H, 64) : 2 * H, 1, bf, true, true);
   L.p_logits = gemm_plan(N, V, H, 1, bf, false);
   L.p_dwout = gemm_plan(V, H, N, 1, bf, true);
   L.p_dhc = gemm_plan(N, H, V, 1, bf, true);
