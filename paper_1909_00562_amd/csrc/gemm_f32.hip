@@ -1,6 +1,6 @@
 // fp32 matrix products for the AS_F32 path (fp32 operands, products summed in
-// fp64 so that each output is rounded once; plain FMA arithmetic, LDS tiled),
-// the split-K combine kernel shared with the bf16 path, and the tile planner.
+// fp64 so that each output is rounded once; fp64 matrix cores, LDS tiled), the
+// split-K combine kernel shared with the bf16 path, and the tile planner.
 #include "common.h"
 #include "gemm.h"
 
@@ -9,7 +9,7 @@ namespace asx {
 struct GemmDevF {
   const float* A[kMaxSeg];
   const float* B[kMaxSeg];
-  int64_t sam[kMaxSeg], sak[kMaxSeg], sbn[kMaxSeg], sbk[kMaxSeg];  // element strides of A(m,k), B(n,k)
+  int64_t lda[kMaxSeg], ldb[kMaxSeg];
   int64_t sA[kMaxSeg], sB[kMaxSeg];
   int K[kMaxSeg];
   int M, N;
@@ -27,7 +27,7 @@ struct GemmDevF {
   int splits;
   float* partial;
   int kper;
-  int a_kc, b_kc;
+  int tiles_n;
   const int32_t* M_dev;   // device-side row count / reduction length (or null), clamped to M / K[0]
   const int32_t* K_dev;
 };
@@ -38,98 +38,278 @@ __device__ __forceinline__ int dev_bound_f(const int32_t* count, int bound) {
   return v < 0 ? 0 : (v < bound ? v : bound);
 }
 
-constexpr int FT = 64;   // block tile edge
-constexpr int FK = 16;   // reduction slice
+// ---- fp32 products on the fp64 matrix cores ------------------------------------------
+// v_mfma_f64_16x16x4_f64: lane l holds A[l % 16][l / 16] and B[l / 16][l % 16] as doubles; accumulator register r of
+// lane l is row 4 * r + l / 16, column l % 16.  Operands stay float in memory and in LDS (half the bytes) and are
+// widened after the fragment read, which is exact; products and sums are fp64 as in scalar code, so an output is
+// rounded once.  Which four reduction indices meet in one instruction is free as long as both operands agree: lane
+// group q = l / 16 takes k = 4 q + j for instruction j, so a lane's four values are one 16-byte LDS read.
+//
+// Block: 256 threads as 2 x 2 waves, reduction tiles of FK, two LDS stages.  The next PF tiles are on their way in
+// registers (PF = 4 at 32 x 32, where a tile is short against a load's latency and the registers are there; 2 at 64 x 64).
+// LDS rows are padded to FLD floats: 16 rows at one k then start in 16 different groups of 4 banks.
+//
+// Large products are bound by the fp64 matrix rate: 61 TFLOP/s at 4096^3 (the vendor's fp64 product reaches 62 on the
+// same part; the scalar fp64 form this replaced ran at 17).  Small ones are bound by the steps of one wave: 64 matrix
+// cycles x 8, 16 conversions and a barrier per tile of a 32 x 32 block.  64 x 2048 x 512 in 4 splits: 55 -> 9.4 us.
+constexpr int FK = 32;
+constexpr int FLD = FK + 4;
 
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
+
+// ROWS x FK tiles of one operand: global -> registers -> LDS [row][k].  KC: the reduction index is contiguous (a thread
+// takes 4 consecutive k of a row); else a thread takes 4 consecutive rows of one k and scatters them.  Nothing branches
+// (with branches around the loads the compiler waits for every load in flight at each of them): reduction indices
+// outside the operand are read from `safe`, an address inside it, and stored as zero; rows outside are read from row 0
+// and stay as they are, they only reach elements of C that are not stored.
+// VEC: 16-byte loads; the host has checked that a group of four is all inside or all outside the operand.
+template <int ROWS, bool KC, bool VEC>
+struct F32Loader {
+  static constexpr int NV = ROWS * FK / 4 / 256;
+  const float* ptr[NV];
+  int last[NV];   // !KC, scalar loads: rows behind the first of the four that are inside
+  static __device__ __forceinline__ int row_of(int tid, int j) {
+    return KC ? (tid >> 3) + 32 * j : (tid & 7) * 4 + 32 * j;
+  }
+  static __device__ __forceinline__ int k_of(int tid) { return KC ? (tid & 7) * 4 : tid >> 3; }
+  // X: element (0, k0) of the rows; rows_left >= 1 of them are inside the operand
+  __device__ __forceinline__ void init(const float* X, int64_t ld, int rows_left, int tid) {
+    const int k = k_of(tid);
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      const int row = row_of(tid, j) < rows_left ? row_of(tid, j) : 0;
+      ptr[j] = KC ? X + (int64_t)row * ld + k : X + (int64_t)k * ld + row;
+      last[j] = rows_left - 1 - row;
+    }
+  }
+  __device__ __forceinline__ void load(f32x4_t (&r)[NV], const float* safe, int k_left, int64_t step, int tid) {
+    const int k = k_of(tid);
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      if constexpr (VEC) {
+        r[j] = *reinterpret_cast<const f32x4_t*>(k < k_left ? ptr[j] : safe);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float* q = ptr[j] + (KC || e <= last[j] ? e : last[j]);
+          r[j][e] = *(k + (KC ? e : 0) < k_left ? q : safe);
+        }
+      }
+      ptr[j] += step;
+    }
+  }
+  static __device__ __forceinline__ void store(const f32x4_t (&r)[NV], float* lds, int k_left, int tid) {
+    const int k = k_of(tid);
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      const int row = row_of(tid, j);
+      f32x4_t v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = k + (KC && !VEC ? e : 0) < k_left ? r[j][e] : 0.f;
+      if constexpr (KC) {
+        *reinterpret_cast<f32x4_t*>(lds + row * FLD + k) = v;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) lds[(row + e) * FLD + k] = v[e];
+      }
+    }
+  }
+};
+
+template <int BM, int BN, int PF, bool AKC, bool BKC, bool AVEC, bool BVEC>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmDevF p) {
-  __shared__ float As[FK][FT + 4];
-  __shared__ float Bs[FK][FT + 4];
-  const int tid = threadIdx.x;
-  const int tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.y * FT, n0 = blockIdx.x * FT;
+  static_assert(PF % 2 == 0, "a step's LDS stage is its slot's parity");
+  constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 16, TN = WN / 16;
+  constexpr int STAGE = (BM + BN) * FLD;   // floats
+  __shared__ __align__(16) float smem[2 * STAGE];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = (wave >> 1) * WM, wn = (wave & 1) * WN;
+
+  // consecutive blocks go round-robin to the 8 XCDs: each XCD gets a contiguous run of tiles, walked in groups of 8
+  // tile rows, so that co-resident blocks share operand panels in its L2
   const int Mv = dev_bound_f(p.M_dev, p.M);
   const int K0 = dev_bound_f(p.K_dev, p.K[0]);
-  if (m0 >= Mv) return;   // the whole block, before any barrier
+  const int tiles_m = (Mv + BM - 1) / BM, nt = tiles_m * p.tiles_n;   // the grid was sized for p.M
+  int pid = blockIdx.x;
+  if (pid >= nt) return;   // the whole block, before any barrier
+  {
+    const int xcd = pid & 7, idx = pid >> 3, per = nt >> 3, rem = nt & 7;
+    pid = xcd * per + (xcd < rem ? xcd : rem) + idx;
+  }
+  const int gid = pid / (8 * p.tiles_n), first_m = gid * 8;
+  const int gm = tiles_m - first_m < 8 ? tiles_m - first_m : 8;
+  const int in_g = pid - gid * 8 * p.tiles_n;
+  const int m0 = (first_m + in_g % gm) * BM, n0 = (in_g / gm) * BN;
   const int kper = p.K_dev ? (((K0 + FK - 1) / FK + p.splits - 1) / p.splits) * FK : p.kper;
   const int z = blockIdx.z;
   const int batch = z / p.splits, split = z - batch * p.splits;
 
-  double acc[4][4];
+  f64x4_t acc[TM][TN];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.0;
 
-  for (int seg = 0; seg < kMaxSeg; ++seg) {
-    if (p.K[seg] <= 0) continue;
-    int kbeg = 0, kend = seg == 0 ? K0 : p.K[seg];
-    if (p.splits > 1) {
-      kbeg = split * kper;
-      kend = kbeg + kper < kend ? kbeg + kper : kend;
+  // cursor over the reduction tiles of all segments (a split covers part of segment 0, the only one then)
+  int seg = 0, k_left = K0;
+  const float* cA = p.A[0] + (int64_t)batch * p.sA[0] + (AKC ? (int64_t)m0 * p.lda[0] : m0);
+  const float* cB = p.B[0] + (int64_t)batch * p.sB[0] + (BKC ? (int64_t)n0 * p.ldb[0] : n0);
+  if (p.splits > 1) {
+    const int kbeg = split * kper;
+    k_left = K0 - kbeg < kper ? K0 - kbeg : kper;
+    cA += AKC ? kbeg : (int64_t)kbeg * p.lda[0];
+    cB += BKC ? kbeg : (int64_t)kbeg * p.ldb[0];
+  }
+  int nk = k_left > 0 ? (k_left + FK - 1) / FK : 0, last_seg = 0;   // tiles of this block, last segment in use
+  if (p.splits <= 1) {
+#pragma unroll
+    for (int s = 1; s < kMaxSeg; ++s)
+      if (p.K[s] > 0) {
+        nk += (p.K[s] + FK - 1) / FK;
+        last_seg = s;
+      }
+  }
+  // tiles on their way: slot t % PF of the registers holds tile t + 1 at the top of step t
+  using LA = F32Loader<BM, AKC, AVEC>;
+  using LB = F32Loader<BN, BKC, BVEC>;
+  LA la;
+  LB lb;
+  f32x4_t ra[PF][LA::NV], rb[PF][LB::NV];
+  int kin[PF];
+  la.init(cA, p.lda[0], Mv - m0, tid);
+  lb.init(cB, p.ldb[0], p.N - n0, tid);
+  const float *safeA = p.A[0], *safeB = p.B[0];
+  // The tile under the cursor into registers.  Past the last tile the loads are issued all the same (of `safe`): the
+  // number in flight is then the same on every path, and the wait before a store to LDS covers just the tile it stores.
+  auto fetch = [&](int slot) {
+    if (k_left <= 0 && seg < last_seg) {   // on to the next segment
+      do { ++seg; } while (p.K[seg] <= 0);
+      k_left = p.K[seg];
+      la.init(p.A[seg] + (int64_t)batch * p.sA[seg] + (AKC ? (int64_t)m0 * p.lda[seg] : m0), p.lda[seg], Mv - m0, tid);
+      lb.init(p.B[seg] + (int64_t)batch * p.sB[seg] + (BKC ? (int64_t)n0 * p.ldb[seg] : n0), p.ldb[seg], p.N - n0, tid);
     }
-    const float* A = p.A[seg] + (int64_t)batch * p.sA[seg];
-    const float* B = p.B[seg] + (int64_t)batch * p.sB[seg];
-    for (int k0 = kbeg; k0 < kend; k0 += FK) {
+    kin[slot] = k_left;
+    la.load(ra[slot], safeA, k_left, AKC ? FK : (int64_t)FK * p.lda[seg], tid);
+    lb.load(rb[slot], safeB, k_left, BKC ? FK : (int64_t)FK * p.ldb[seg], tid);
+    k_left -= FK;
+  };
+  auto put = [&](int slot, int st) {   // registers -> LDS stage st
+    LA::store(ra[slot], smem + st * STAGE, kin[slot], tid);
+    LB::store(rb[slot], smem + st * STAGE + BM * FLD, kin[slot], tid);
+  };
+  auto compute = [&](int st) {
+    const float* as = smem + st * STAGE;
+    const float* bs = as + BM * FLD;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int idx = tid + 256 * j;
-        int m, k;
-        if (p.a_kc) { k = idx & 15; m = idx >> 4; } else { m = idx & 63; k = idx >> 6; }
-        const int gm = m0 + m, gk = k0 + k;
-        As[k][m] = (gm < Mv && gk < kend) ? A[(int64_t)gm * p.sam[seg] + (int64_t)gk * p.sak[seg]] : 0.f;
-        int n;
-        if (p.b_kc) { k = idx & 15; n = idx >> 4; } else { n = idx & 63; k = idx >> 6; }
-        const int gn = n0 + n;
-        const int gk2 = k0 + k;
-        Bs[k][n] = (gn < p.N && gk2 < kend) ? B[(int64_t)gn * p.sbn[seg] + (int64_t)gk2 * p.sbk[seg]] : 0.f;
+    for (int ks = 0; ks < FK / 16; ++ks) {
+      f32x4_t af[TM], bf[TN];
+      const int kof = ks * 16 + (lane >> 4) * 4;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+        af[i] = *reinterpret_cast<const f32x4_t*>(as + (wm + i * 16 + (lane & 15)) * FLD + kof);
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        bf[j] = *reinterpret_cast<const f32x4_t*>(bs + (wn + j * 16 + (lane & 15)) * FLD + kof);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        double b[TN];
+#pragma unroll
+        for (int j = 0; j < TN; ++j) b[j] = (double)bf[j][e];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          const double a = (double)af[i][e];
+#pragma unroll
+          for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b[j], acc[i][j], 0, 0, 0);
+        }
       }
-      __syncthreads();
+    }
+  };
+
+  fetch(PF - 1);
 #pragma unroll
-      for (int k = 0; k < FK; ++k) {
-        float a[4], b[4];
+  for (int u = 0; u + 1 < PF; ++u) fetch(u);
+  put(PF - 1, 0);
+  fetch(PF - 1);
+  __syncthreads();
+  int t = 0;
+  for (; t + PF <= nk; t += PF) {   // no exit inside: it would meet the loop's other paths with other counts in flight
 #pragma unroll
-        for (int i = 0; i < 4; ++i) a[i] = As[k][ty * 4 + i];
+    for (int u = 0; u < PF; ++u) {
+      put(u, (u + 1) & 1);
+      fetch(u);
+      compute(u & 1);
+      __syncthreads();        // tile t + u has been read everywhere, the next one is in place
+    }
+  }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) b[j] = Bs[k][tx * 4 + j];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[i][j] = fma((double)a[i], (double)b[j], acc[i][j]);
-      }
+  for (int u = 0; u + 1 < PF; ++u) {
+    if (t + u < nk) {
+      put(u, (u + 1) & 1);
+      compute(u & 1);
       __syncthreads();
     }
   }
 
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = m0 + ty * 4 + i;
-    if (row >= Mv) continue;
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int col = n0 + tx * 4 + j;
-      if (col >= p.N) continue;
-      double v = acc[i][j];
-      if (p.splits > 1) {
-        p.partial[((int64_t)z * p.M + row) * p.N + col] = (float)v;
-        continue;
+    for (int r = 0; r < 4; ++r) {
+      const int row = m0 + wm + i * 16 + 4 * r + (lane >> 4);
+      if (row >= Mv) continue;
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int col = n0 + wn + j * 16 + (lane & 15);
+        if (col >= p.N) continue;
+        double v = acc[i][j][r];
+        if (p.splits > 1) {
+          p.partial[((int64_t)z * p.M + row) * p.N + col] = (float)v;
+          continue;
+        }
+        if (p.bias) v += (double)p.bias[col];
+        if (p.act_tanh) v = tanh(v);
+        double dact = 1.0 - v * v;
+        if (p.drop_thr) {
+          const double s = (double)dropout_mult((uint64_t)row * p.N + col, p.drop_seed, p.drop_thr, p.drop_scale);
+          v *= s;
+          dact *= s;
+        }
+        if (p.gate) v *= (double)p.gate[(int64_t)row * p.ldg + col];
+        const int64_t ci = (int64_t)batch * p.sC + (int64_t)row * p.ldc + col;
+        if (p.accumulate) v += (double)p.C[ci];
+        const float vf = (float)v;
+        p.C[ci] = vf;
+        if (p.C_lo) p.C_lo[ci] = (float)(v - (double)vf);
+        if (p.C_dact) p.C_dact[ci] = (float)dact;
       }
-      if (p.bias) v += (double)p.bias[col];
-      if (p.act_tanh) v = tanh(v);
-      double dact = 1.0 - v * v;
-      if (p.drop_thr) {
-        const double s = (double)dropout_mult((uint64_t)row * p.N + col, p.drop_seed, p.drop_thr, p.drop_scale);
-        v *= s;
-        dact *= s;
-      }
-      if (p.gate) v *= (double)p.gate[(int64_t)row * p.ldg + col];
-      const int64_t ci = (int64_t)batch * p.sC + (int64_t)row * p.ldc + col;
-      if (p.accumulate) v += (double)p.C[ci];
-      const float vf = (float)v;
-      p.C[ci] = vf;
-      if (p.C_lo) p.C_lo[ci] = (float)(v - (double)vf);
-      if (p.C_dact) p.C_dact[ci] = (float)dact;
     }
-  }
+}
+
+// Block tile edge (64 or 32) for nz products of M x N.  With four blocks and more on every compute unit the 64 x 64 tile
+// is the faster one (4096^3: 2.25 ms = 61 TFLOP/s against 2.43 ms with 32 x 32); below that there are too few waves to
+// cover the loads, and the four times as many blocks of 32 x 32 win by far: 1286 x 512 x 16000 0.70 -> 0.53 ms,
+// 64 x 2048 x 512 28 -> 11 us.  (128 x 64 was never the fastest: 2.43 ms at 4096^3.)
+static int f32_tile(int M, int N, int nz) {
+  return (int64_t)((M + 63) / 64) * ((N + 63) / 64) * nz >= 1024 ? 64 : 32;
+}
+
+template <int BM, int BN, int PF, bool AKC, bool BKC>
+static hipError_t launch_f32_tile(GemmDevF& d, int batch, bool avec, bool bvec, hipStream_t st) {
+  d.tiles_n = (d.N + BN - 1) / BN;
+  dim3 grid((d.M + BM - 1) / BM * d.tiles_n, 1, batch * d.splits);
+#define ASX_F32(AV, BV) hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, PF, AKC, BKC, AV, BV>), grid, dim3(256), 0, st, d)
+  if (avec && bvec) ASX_F32(true, true);
+  else if (avec) ASX_F32(true, false);
+  else if (bvec) ASX_F32(false, true);
+  else ASX_F32(false, false);
+#undef ASX_F32
+  return hipGetLastError();
+}
+template <bool AKC, bool BKC>
+static hipError_t launch_f32_oriented(GemmDevF& d, int batch, bool avec, bool bvec, hipStream_t st) {
+  return f32_tile(d.M, d.N, batch * d.splits) == 64 ? launch_f32_tile<64, 64, 2, AKC, BKC>(d, batch, avec, bvec, st)
+                                                    : launch_f32_tile<32, 32, 4, AKC, BKC>(d, batch, avec, bvec, st);
 }
 
 hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t st) {
@@ -138,16 +318,24 @@ hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t st) {
   if (g.splits > 1 && (g.C_dact || g.drop_thr)) return hipErrorInvalidValue;
   if (g.drop_thr && g.batch != 1) return hipErrorInvalidValue;
   GemmDevF d;
+  bool avec = true, bvec = true;
   for (int s = 0; s < kMaxSeg; ++s) {
     d.A[s] = reinterpret_cast<const float*>(g.A[s]);
     d.B[s] = reinterpret_cast<const float*>(g.B[s]);
-    d.sam[s] = g.a_kc ? g.lda[s] : 1;
-    d.sak[s] = g.a_kc ? 1 : g.lda[s];
-    d.sbn[s] = g.b_kc ? g.ldb[s] : 1;
-    d.sbk[s] = g.b_kc ? 1 : g.ldb[s];
+    d.lda[s] = g.lda[s];
+    d.ldb[s] = g.ldb[s];
     d.sA[s] = g.sA[s];
     d.sB[s] = g.sB[s];
     d.K[s] = g.K[s];
+    if (g.K[s] > 0) {
+      // 16-byte loads: groups of four start aligned and do not straddle the operand's edge (a reduction length or row
+      // count read on the device counts rows, which are the other index of the operands that use it)
+      auto vec_ok = [&](const void* X, int64_t ld, int64_t stride, bool kc, int rows) {
+        return !((ld | stride | (kc ? g.K[s] : rows)) & 3) && !(reinterpret_cast<uintptr_t>(X) & 15);
+      };
+      avec = avec && vec_ok(g.A[s], g.lda[s], g.sA[s], g.a_kc, g.M) && !(g.a_kc && g.K_dev) && !(!g.a_kc && g.M_dev);
+      bvec = bvec && vec_ok(g.B[s], g.ldb[s], g.sB[s], g.b_kc, g.N) && !(g.b_kc && g.K_dev);
+    }
   }
   d.M = g.M;
   d.N = g.N;
@@ -166,8 +354,6 @@ hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t st) {
   d.accumulate = g.accumulate;
   d.splits = g.splits;
   d.partial = g.partial;
-  d.a_kc = g.a_kc;
-  d.b_kc = g.b_kc;
   if (g.M_dev && g.batch != 1) return hipErrorInvalidValue;
   if (g.K_dev && g.K[1] != 0) return hipErrorInvalidValue;
   d.M_dev = g.M_dev;
@@ -175,9 +361,10 @@ hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t st) {
   const int ktiles = (g.K[0] + FK - 1) / FK;
   d.kper = ((ktiles + g.splits - 1) / g.splits) * FK;
   if (g.splits > 1 && (int64_t)d.kper * (g.splits - 1) >= g.K[0]) return hipErrorInvalidValue;
-  dim3 grid((g.N + FT - 1) / FT, (g.M + FT - 1) / FT, g.batch * g.splits);
-  hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, st, d);
-  return hipGetLastError();
+  if (g.a_kc && g.b_kc) return launch_f32_oriented<true, true>(d, g.batch, avec, bvec, st);
+  if (g.a_kc && !g.b_kc) return launch_f32_oriented<true, false>(d, g.batch, avec, bvec, st);
+  if (!g.a_kc && !g.b_kc) return launch_f32_oriented<false, false>(d, g.batch, avec, bvec, st);
+  return hipErrorInvalidValue;  // (A strided, B contiguous) is not used by the path
 }
 
 // ---- split-K combine: C = epilogue(sum_s partial[b*splits+s]) in fixed order --
@@ -277,12 +464,14 @@ GemmPlan gemm_plan(int M, int N, int K, int batch, bool bf16, bool allow_split, 
   pl.splits = 1;
   if (!bf16) {
     if (multi_segment) allow_split = false;
-    // fp32 path: plain 64x64 tiles; split only to fill the machine
-    const int64_t tiles = (int64_t)((M + FT - 1) / FT) * ((N + FT - 1) / FT) * batch;
-    if (allow_split && tiles < 384) {
+    // fp32 path: split while there are fewer than ten 32 x 32 blocks per compute unit, down to four reduction tiles
+    // per split.  Measured (1 / 2 / 4 / 8 splits): 1286 x 512 x 16000 531 / 507 / 453 / 431 us, 512 x 512 x 1920
+    // 35 / 32 / 31 / 33 us, 64 x 512 x 2048 36 / 23 / 16 / 13 us; 16000 x 512 x 1286 (8000 blocks) only loses.
+    const int64_t tiles = (int64_t)((M + 31) / 32) * ((N + 31) / 32) * batch;
+    if (allow_split) {
       const int ktiles = (K + FK - 1) / FK;
-      int64_t want = (768 + tiles - 1) / tiles;
-      const int64_t cap = ktiles / 16;
+      int64_t want = 2560 / tiles;
+      const int64_t cap = ktiles / 4;
       if (want > cap) want = cap;
       if (want > 32) want = 32;
       if (want > 1) {

@@ -22,3 +22,12 @@ def test_h_c_split_with_ragged_segments(shape):
     sizes for which 3 * ceil(H / 64) and ceil(3 * H / 64) differ enough to leave a split without tiles."""
     T, S, B, H, V = shape
     _parity(make_custom(T=T, S=S, B=B, H=H, V=V, seed=H, dtype="bf16", min_len=1, pad_prob=0.1))
+
+
+@pytest.mark.parametrize("skip", [False, True])
+@pytest.mark.parametrize("shape", [(20, 5, 13, 60, 16003),     # 64 x 64 tiles of logits and dW_out, ragged in every direction
+                                   (3, 33, 11, 121, 999),      # rows that are not 16-byte aligned: scalar loads
+                                   (31, 7, 3, 132, 2051)])     # split reductions with a remainder
+def test_f32_products_at_tile_edges(shape, skip):
+    T, S, B, H, V = shape
+    _parity(make_custom(T=T, S=S, B=B, H=H, V=V, seed=V, dtype="f32", min_len=1, pad_prob=0.3), skip)
