@@ -1,0 +1,97 @@
+// Kernels of the stacked LSTM (lstm_wave.hip), as the entry points in lstm.hip drive them.
+//
+// One launch advances every layer that has work: layer l handles step t = d - l of wavefront d (forward; backward the
+// mirror image), so L layers x T steps take T + L - 1 launches.  A layer-step is one product over two segments, the
+// layer's own state and what it gets from its neighbour, and the cell.
+//
+// Operands are kept as FRAGMENT TILES: 16 rows x kKStep reduction indices = 64 lanes x 16 bytes = 1 KiB, in the order
+// in which a wave's lanes hold them for the matrix instruction (lane l: row l % 16, the l / 16-th group of kVec
+// consecutive reduction indices), laid out [reduction step][tile].  Reduction steps are padded with zeros.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace asx {
+
+constexpr int kLsMaxLayers = 16;
+constexpr int64_t kLsTile = 1024;   // bytes of a fragment tile
+
+template <typename TE> struct LsGeom;
+template <> struct LsGeom<uint16_t> { static constexpr int kVec = 8, kKStep = 32; };   // bf16
+template <> struct LsGeom<float> { static constexpr int kVec = 4, kKStep = 16; };
+
+// forward gate rows: 16 hidden units are 4 tiles of 16 rows; padded to whole groups of 32 units
+inline int ls_gate_tiles(int H) { return (H + 31) / 32 * 8; }
+// backward unit rows, padded to whole groups of 64 units
+inline int ls_unit_tiles(int H) { return (H + 63) / 64 * 4; }
+inline int ls_batch_tiles(int B) { return (B + 15) / 16; }
+template <typename TE> inline int ls_ksteps(int K) { return (K + LsGeom<TE>::kKStep - 1) / LsGeom<TE>::kKStep; }
+// reduction index of (gate, unit) in the backward products: gate * ls_gate_stride + unit
+template <typename TE> __host__ __device__ inline int ls_gate_stride(int H) {
+  return (H + LsGeom<TE>::kVec - 1) / LsGeom<TE>::kVec * LsGeom<TE>::kVec;
+}
+
+// Addresses in bytes or typed pointers; strides in elements of the pointer's type (bytes for char*).
+struct LsFwd {
+  // weights of layer l: fragment tiles made by launch_ls_prep_fwd, or the caller's rows (w_rows)
+  const void *W_hh[kLsMaxLayers], *W_ih[kLsMaxLayers];
+  const void* bias[kLsMaxLayers];
+  const char *xF, *zeros;          // input of layer 0 as tiles, one block of x_stride bytes per step; zeroed tiles
+  int64_t x_stride;
+  char *hF_hi, *hF_lo;             // [L][2 slots][h_stride bytes]: h_{t-1} in slot t & 1 (lo: bf16 storage only)
+  char *oF_hi, *oF_lo;             // [L - 1][2 slots][h_stride bytes]: output of step t (what layer l + 1 reads), slot t & 1
+  int64_t h_stride;
+  float *gates, *cs;               // [L][T,B,4H] i, f, g, o; [L][T+1,B,H] cell states
+  void *hE, *out;                  // [L][T+1,B,H] states, [L - 1][T,B,H] outputs, storage type
+  void* y;                         // [T,B,H] output of the top layer
+  float *hf, *cT;                  // [L][B,H] running h (ends as the final state); final c (or null)
+  const int32_t* lengths;
+  int T, B, I, H, L;
+  int w_rows;
+  uint32_t drop_thr;               // dropout on the outputs below the top layer; 0: none
+  float drop_scale;
+  uint64_t drop_seed;
+};
+
+struct LsBwd {
+  const char *WT_hh[kLsMaxLayers], *WT_up[kLsMaxLayers];   // tiles of W_hh[l]^T and of W_ih[l + 1]^T
+  const float *gates, *cs, *dy, *dhT, *dcT;                // dhT, dcT [L][B,H] may be null
+  float* dcs;                                              // [L][B,H] running gradient w.r.t. c (ends as dc0)
+  float* dh0;                                              // [L][B,H] or null
+  void* dG;                                                // [L][T,B,4H] gate gradients, storage type
+  char* dGF;                                               // [L][2 slots][g_stride bytes]: the same as tiles, slot t & 1
+  int64_t g_stride;
+  float* dbacc;                                            // [L][batch tiles][4H]: column sums of the gate gradients
+  const int32_t* lengths;
+  int T, B, H, L;
+  uint32_t drop_thr;
+  float drop_scale;
+  uint64_t drop_seed;
+};
+
+// Before the first wavefront: states of step 0 (h0, c0 may be null = zeros), x and, unless p.w_rows, the weights as
+// tiles (W_hh, W_ih: the caller's rows; p.W_*: where the tiles go).
+struct LsPrepFwd {
+  const void *W_hh[kLsMaxLayers], *W_ih[kLsMaxLayers];
+  const void* x;
+  const float *h0, *c0;
+};
+template <typename TE> hipError_t launch_ls_prep_fwd(const LsFwd& p, const LsPrepFwd& q, hipStream_t st);
+// tiles of the transposed weights into p.WT_*
+struct LsPrepBwd {
+  const void *W_hh[kLsMaxLayers], *W_ih[kLsMaxLayers];
+};
+template <typename TE> hipError_t launch_ls_prep_bwd(const LsBwd& p, const LsPrepBwd& q, hipStream_t st);
+// wavefront d = 0 .. T + L - 2
+template <typename TE> hipError_t launch_ls_wave_fwd(const LsFwd& p, int d, hipStream_t st);
+// wavefront d = 0 .. T + L - 2 + (dh0 != null)
+template <typename TE> hipError_t launch_ls_wave_bwd(const LsBwd& p, int d, hipStream_t st);
+// db[l][col] = sum over batch tiles of dbacc
+struct LsBiasOut {
+  float* db[kLsMaxLayers];
+};
+hipError_t launch_ls_bias_reduce(const float* dbacc, const LsBiasOut& o, int L, int nct, int cols, hipStream_t st);
+// Whether forward wavefronts read the caller's weight rows instead of tiles made from them.
+template <typename TE> bool ls_reads_weight_rows(int T, int I, int H, int L);
+
+}  // namespace asx

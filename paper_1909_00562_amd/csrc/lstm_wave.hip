@@ -1,0 +1,771 @@
+// The stacked LSTM on the matrix cores (gfx950): one launch per WAVEFRONT of layer-steps.
+//
+// Layer l can take step t as soon as it has its own state of step t - 1 and the output of layer l - 1 at step t.  All
+// layer-steps (l, d - l) are therefore independent and go into one launch; the input product is folded into the
+// step as a second segment of the reduction, so that nothing else has to run between two launches.
+//
+// A wavefront is a skinny product (B columns, typically 128) on the critical path, bound by the way from the caches to
+// the registers and by what any launch costs, not by the matrix cores:
+//   * no LDS staging: a wave loads matrix fragments straight into registers, 1 KiB per load from contiguous memory
+//     (fragment tiles, lstm_wave.h), with the next PF reduction steps in flight;
+//   * the reduction is split over the four waves of a block (wave w takes steps w, w + 4, ...), so no byte is loaded
+//     twice by a block; the partial tiles meet in LDS and are added in wave order.  Every block shape adds in the same
+//     order: results do not depend on the shape chosen, nor on how many sentences share the batch;
+//   * the WEIGHT rows are the rows of the matrix instruction and the sentences its columns.  A lane then holds four
+//     rows for its sentence: forward the four gates of one unit (and over four tiles those of four consecutive units),
+//     backward four consecutive units.  The whole cell is lane-local and its memory accesses are vectors.
+//   * bf16 storage: h enters as a (value, rounding remainder) pair that shares the weight fragment, without which
+//     rounding compounds over steps and layers.  Gate gradients enter the backward products as plain bf16.
+//   * fp32 storage: fp64 matrix instructions on operands widened after the load, as in gemm_f32.hip.
+#include "common.h"
+#include "lstm_wave.h"
+
+namespace asx {
+
+typedef uint32_t ls_u32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t ls_u32x2_t __attribute__((ext_vector_type(2)));
+typedef double ls_f64x4_t __attribute__((ext_vector_type(4)));
+
+constexpr int LS_KS = 4;   // waves per block = ways a reduction is split
+
+// Matrix instruction of one fragment pair.  Row of the tile that register r of a lane in group q = lane / 16 holds:
+// 4 q + r (bf16) or 4 r + q (fp64).
+template <typename TE> struct LsMma;
+template <> struct LsMma<uint16_t> {
+  typedef f32x4_t acc_t;
+  typedef float sum_t;
+  static constexpr bool kPair = true;
+  static __device__ __forceinline__ void mma(acc_t& acc, ls_u32x4_t a, ls_u32x4_t b) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), acc,
+                                                  0, 0, 0);
+  }
+  // tile row that lane group q holds in register r
+  static __host__ __device__ __forceinline__ int q_of_row(int rho) { return rho >> 2; }
+  static __host__ __device__ __forceinline__ int r_of_row(int rho) { return rho & 3; }
+};
+template <> struct LsMma<float> {
+  typedef ls_f64x4_t acc_t;
+  typedef double sum_t;
+  static constexpr bool kPair = false;
+  static __device__ __forceinline__ void mma(acc_t& acc, ls_u32x4_t a, ls_u32x4_t b) {
+    const f32x4_t af = __builtin_bit_cast(f32x4_t, a), bf = __builtin_bit_cast(f32x4_t, b);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)af[e], (double)bf[e], acc, 0, 0, 0);
+  }
+  static __host__ __device__ __forceinline__ int q_of_row(int rho) { return rho & 3; }
+  static __host__ __device__ __forceinline__ int r_of_row(int rho) { return rho >> 2; }
+};
+
+__device__ __forceinline__ float ls_sigmoid(float a) { return 1.f / (1.f + expf(-a)); }
+__device__ __forceinline__ int ls_len(const int32_t* lengths, int b, int T) {
+  const int n = lengths[b];
+  return n < 0 ? 0 : (n > T ? T : n);
+}
+
+// Four consecutive elements, of which n are inside; vec: H % 4 == 0, all four are inside and aligned
+__device__ __forceinline__ f32x4_t ls_ld4(const float* p, int n, bool vec) {
+  if (vec) return *reinterpret_cast<const f32x4_t*>(p);
+  f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (e < n) v[e] = p[e];
+  return v;
+}
+__device__ __forceinline__ f32x4_t ls_ld4(const uint16_t* p, int, bool) {
+  const ls_u32x2_t w = *reinterpret_cast<const ls_u32x2_t*>(p);
+  const f32x4_t v = {lo_bf16(w[0]), hi_bf16(w[0]), lo_bf16(w[1]), hi_bf16(w[1])};
+  return v;
+}
+__device__ __forceinline__ void ls_st4(float* p, const f32x4_t& v, int n, bool vec) {
+  if (vec) {
+    *reinterpret_cast<f32x4_t*>(p) = v;
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (e < n) p[e] = v[e];
+}
+__device__ __forceinline__ void ls_st4(uint16_t* p, const f32x4_t& v, int, bool) {
+  const ls_u32x2_t w = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+  *reinterpret_cast<ls_u32x2_t*>(p) = w;
+}
+template <typename TE> __device__ __forceinline__ f32x4_t ls_rest(const f32x4_t& v) {
+  f32x4_t r;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) r[e] = v[e] - round_elem<TE>(v[e]);
+  return r;
+}
+// multipliers of the four elements from flat index i on (vec: i % 4 == 0)
+__device__ __forceinline__ f32x4_t ls_drop4(uint64_t i, uint64_t seed, uint32_t thr, float scale, bool vec) {
+  f32x4_t m;
+  if (vec) {
+    uint32_t w[4];
+    dropout_words4(i >> 2, seed, w);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m[e] = w[e] >= thr ? scale : 0.f;
+  } else {
+#pragma unroll 1
+    for (int e = 0; e < 4; ++e) {
+      const float x = dropout_mult(i + e, seed, thr, scale);
+      m[0] = e == 0 ? x : m[0]; m[1] = e == 1 ? x : m[1]; m[2] = e == 2 ? x : m[2]; m[3] = e == 3 ? x : m[3];
+    }
+  }
+  return m;
+}
+// offset (elements) of reduction index k, k % 4 == 0, of column b in fragment tiles of nct column tiles
+template <typename TE> __device__ __forceinline__ int64_t ls_tile_off(int k, int b, int nct) {
+  constexpr int V = LsGeom<TE>::kVec, K = LsGeom<TE>::kKStep;
+  return (((int64_t)(k / K) * nct + (b >> 4)) * 64 + (k % K) / V * 16 + (b & 15)) * V + k % V;
+}
+
+// Blocks of a wavefront: nslices (layer, row block) slices of the weights x nbt batch blocks.  Consecutive blocks go
+// round-robin to the 8 XCDs; the batch blocks of a slice go to one XCD, whose L2 then fetches the slice once.
+__device__ __forceinline__ bool ls_block_of(int nslices, int nbt, int& slice, int& bt) {
+  const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
+  const int s = idx / nbt;
+  slice = s * 8 + xcd;
+  bt = idx - s * nbt;
+  return slice < nslices;
+}
+static inline unsigned ls_grid(int64_t nslices, int64_t nbt) { return (unsigned)((nslices + 7) / 8 * 8 * nbt); }
+
+// The reduction of one wave over its steps of a list of nsteps: PF slots of fragments in flight.  load(slot, s) must be
+// free of branches and valid for every s in [0, nsteps); past the wave's last step the last one is loaded again, so
+// that the number of loads in flight is the same on every path and a wait covers just the fragments it needs.
+template <int PF, typename Load, typename Mul>
+__device__ __forceinline__ void ls_reduce(int nsteps, int wave, Load load, Mul mul) {
+  const int n = nsteps > wave ? (nsteps - wave + LS_KS - 1) / LS_KS : 0;
+  auto at = [&](int i) { const int s = wave + i * LS_KS; return s < nsteps ? s : nsteps - 1; };
+#pragma unroll
+  for (int u = 0; u < PF; ++u) load(u, at(u));
+  int i = 0;
+  for (; i + PF <= n; i += PF) {
+#pragma unroll
+    for (int u = 0; u < PF; ++u) {
+      mul(u, at(i + u));
+      load(u, at(i + u + PF));
+    }
+  }
+#pragma unroll
+  for (int u = 0; u + 1 < PF; ++u)
+    if (i + u < n) mul(u, at(i + u));
+}
+
+// ---- forward ---------------------------------------------------------------------
+// Block: 16 * NI gate rows (4 * NI hidden units) x 16 * NJ sentences.  Tile 4 g + ii of a block, row rho: unit
+// u0 + 16 g + 4 q + ii, gate r, (q, r) = the lane group and register that hold row rho.  ROWS: weights are read as the
+// caller's rows (64 bytes of a row per load), each used once by the call.
+template <typename TE, int NI, int NJ, int PF, bool ROWS>
+__global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d, int l_lo, int n_layers) {
+  typedef LsMma<TE> M;
+  typedef typename M::acc_t acc_t;
+  constexpr int NG = NI / 4, V = LsGeom<TE>::kVec, KST = LsGeom<TE>::kKStep;
+  static_assert(NI % 4 == 0, "four tiles hold the gates of four consecutive units per lane");
+  __shared__ acc_t red[LS_KS * NI * NJ * 64];   // [wave][i][j][lane]
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int q = lane >> 4, c = lane & 15;
+  const int H = p.H, B = p.B, nct = (B + 15) >> 4;
+  const int nut = (H + 4 * NI - 1) / (4 * NI), nbt = (B + 16 * NJ - 1) / (16 * NJ);
+  int slice, bt;
+  if (!ls_block_of(n_layers * nut, nbt, slice, bt)) return;
+  const int l = l_lo + slice / nut, u0 = (slice % nut) * 4 * NI, b0 = bt * 16 * NJ;
+  const int t = d - l;
+  const int Kin = l == 0 ? p.I : H;
+  const bool vec = (H & 3) == 0;
+  const int64_t BH = (int64_t)B * H;
+
+  // what the cells need from memory is requested ahead of the product
+  constexpr int NTASK = (NG * NJ + LS_KS - 1) / LS_KS;   // (g, j) pairs, dealt out to the waves
+  f32x4_t cp[NTASK], bias[NTASK][4];
+  const float* c_prev = p.cs + ((int64_t)l * (p.T + 1) + t) * BH;
+  const TE* bl = reinterpret_cast<const TE*>(p.bias[l]);
+#pragma unroll
+  for (int k = 0; k < NTASK; ++k) {
+    const int task = wave + k * LS_KS, g = task / NJ, j = task % NJ;
+    const int b = b0 + 16 * j + c, unit0 = u0 + 16 * g + 4 * q;
+    if (task < NG * NJ && b < B && unit0 < H) {
+      cp[k] = ls_ld4(c_prev + (int64_t)b * H + unit0, H - unit0, vec);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) bias[k][e] = ls_ld4(bl + (int64_t)e * H + unit0, H - unit0, vec);
+    }
+  }
+
+  acc_t acc[NI][NJ];
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0;
+
+  // segments: own state, then the input (x is exact in the storage type: its remainder is read from zeroed tiles)
+  const int n0 = (H + KST - 1) / KST, n1 = (Kin + KST - 1) / KST;
+  const int64_t cstep = (int64_t)nct * kLsTile;
+  const char* h_hi = p.hF_hi + (2 * l + (t & 1)) * p.h_stride;
+  const char* h_lo = M::kPair ? p.hF_lo + (2 * l + (t & 1)) * p.h_stride : nullptr;
+  const char* i_hi = l == 0 ? p.xF + t * p.x_stride : p.oF_hi + (2 * (l - 1) + (t & 1)) * p.h_stride;
+  const char* i_lo = !M::kPair ? nullptr : l == 0 ? p.zeros : p.oF_lo + (2 * (l - 1) + (t & 1)) * p.h_stride;
+  const int64_t lstep1 = l == 0 ? 0 : cstep;
+  int64_t ctoff[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int ct = (b0 >> 4) + j;
+    ctoff[j] = (ct < nct ? ct : nct - 1) * kLsTile;   // columns past the batch repeat the last tile; not stored
+  }
+  const int64_t wstep = (int64_t)((H + 31) / 32 * 8) * kLsTile;   // ls_gate_tiles
+  const char* w0 = reinterpret_cast<const char*>(p.W_hh[l]) + (ROWS ? 0 : u0 / 4 * kLsTile);
+  const char* w1 = reinterpret_cast<const char*>(p.W_ih[l]) + (ROWS ? 0 : u0 / 4 * kLsTile);
+  int wrow[NI];
+  if constexpr (ROWS) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int unit = u0 + 16 * (i / 4) + 4 * M::q_of_row(c) + (i & 3);
+      wrow[i] = M::r_of_row(c) * H + (unit < H ? unit : H - 1);   // rows past the layer repeat the last unit; not stored
+    }
+  }
+  ls_u32x4_t wf[PF][NI], hf[PF][NJ], lf[PF][M::kPair ? NJ : 1];
+  auto load = [&](int slot, int s) {
+    const bool in = s >= n0;
+    const int k = in ? s - n0 : s;
+    if constexpr (ROWS) {
+      const int K = in ? Kin : H, kk = k * KST + q * V;
+      const char* wb = (in ? w1 : w0) + (int64_t)(kk < K ? kk : 0) * sizeof(TE);
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+        wf[slot][i] = *reinterpret_cast<const ls_u32x4_t*>(wb + (int64_t)wrow[i] * K * sizeof(TE));
+    } else {
+      const char* wb = (in ? w1 : w0) + k * wstep + lane * 16;
+#pragma unroll
+      for (int i = 0; i < NI; ++i) wf[slot][i] = *reinterpret_cast<const ls_u32x4_t*>(wb + i * kLsTile);
+    }
+    const char* hb = (in ? i_hi : h_hi) + k * cstep + lane * 16;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) hf[slot][j] = *reinterpret_cast<const ls_u32x4_t*>(hb + ctoff[j]);
+    if constexpr (M::kPair) {
+      const char* lb = (in ? i_lo + k * lstep1 : h_lo + k * cstep) + lane * 16;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) lf[slot][j] = *reinterpret_cast<const ls_u32x4_t*>(lb + ctoff[j]);
+    }
+  };
+  auto mul = [&](int slot, int s) {
+    if constexpr (ROWS) {   // chunks past a row's end were read from its start
+      const int K = s >= n0 ? Kin : H, kk = (s >= n0 ? s - n0 : s) * KST + q * V;
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) wf[slot][i][e] = kk < K ? wf[slot][i][e] : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) M::mma(acc[i][j], wf[slot][i], hf[slot][j]);
+    if constexpr (M::kPair) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) M::mma(acc[i][j], wf[slot][i], lf[slot][j]);
+    }
+  };
+  ls_reduce<PF>(n0 + n1, wave, load, mul);
+
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) red[((wave * NI + i) * NJ + j) * 64 + lane] = acc[i][j];
+  __syncthreads();
+
+  const bool last = t + 1 == p.T;
+#pragma unroll
+  for (int k = 0; k < NTASK; ++k) {
+    const int task = wave + k * LS_KS, g = task / NJ, j = task % NJ;
+    const int b = b0 + 16 * j + c, unit0 = u0 + 16 * g + 4 * q;
+    if (task >= NG * NJ || b >= B || unit0 >= H) continue;
+    const int n = H - unit0;
+    f32x4_t gi, gf, gg, go, cn, hn;
+#pragma unroll
+    for (int ii = 0; ii < 4; ++ii) {
+      acc_t v = red[((4 * g + ii) * NJ + j) * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < LS_KS; ++w) v += red[((w * NI + 4 * g + ii) * NJ + j) * 64 + lane];
+      float a[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[e] = (float)(v[e] + (typename M::sum_t)bias[k][e][ii]);
+      gi[ii] = ls_sigmoid(a[0]);
+      gf[ii] = ls_sigmoid(a[1]);
+      gg[ii] = tanhf(a[2]);
+      go[ii] = ls_sigmoid(a[3]);
+      cn[ii] = gf[ii] * cp[k][ii] + gi[ii] * gg[ii];
+      hn[ii] = go[ii] * tanhf(cn[ii]);
+    }
+    const int64_t idx = (int64_t)b * H + unit0;
+    float* G = p.gates + ((int64_t)l * p.T + t) * 4 * BH + (int64_t)b * 4 * H + unit0;
+    ls_st4(G, gi, n, vec);
+    ls_st4(G + H, gf, n, vec);
+    ls_st4(G + 2 * (int64_t)H, gg, n, vec);
+    ls_st4(G + 3 * (int64_t)H, go, n, vec);
+    const bool valid = t < ls_len(p.lengths, b, p.T);
+    const int64_t foff = ls_tile_off<TE>(unit0, b, nct);
+    TE* hFn_hi = reinterpret_cast<TE*>(p.hF_hi + (2 * l + ((t + 1) & 1)) * p.h_stride) + foff;
+    TE* hFn_lo = reinterpret_cast<TE*>(p.hF_lo + (2 * l + ((t + 1) & 1)) * p.h_stride) + foff;
+    if (!vec) {   // units past H: reduction padding of the next step, kept zero
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (e >= n) hn[e] = 0.f;
+    }
+    f32x4_t o = {0.f, 0.f, 0.f, 0.f}, hv;
+    if (valid) {   // what the next layer reads
+      o = hn;
+      if (p.drop_thr && l + 1 < p.L) {
+        const f32x4_t m = ls_drop4(((uint64_t)l * p.T + t) * (uint64_t)BH + (uint64_t)idx, p.drop_seed, p.drop_thr,
+                                   p.drop_scale, vec);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = m[e] != 0.f ? o[e] * m[e] : 0.f;
+      }
+      hv = hn;
+      ls_st4(p.hf + l * BH + idx, hn, n, vec);
+      ls_st4(hFn_hi, hn, 4, true);
+      if constexpr (M::kPair) ls_st4(hFn_lo, ls_rest<TE>(hn), 4, true);
+    } else {       // padded step: the state passes through, the output is 0
+      cn = cp[k];
+      hv = ls_ld4(reinterpret_cast<const TE*>(h_hi) + foff, 4, true);
+      ls_st4(hFn_hi, hv, 4, true);
+      if constexpr (M::kPair) ls_st4(hFn_lo, ls_ld4(reinterpret_cast<const TE*>(h_lo) + foff, 4, true), 4, true);
+    }
+    ls_st4(p.cs + ((int64_t)l * (p.T + 1) + t + 1) * BH + idx, cn, n, vec);
+    if (last && p.cT) ls_st4(p.cT + l * BH + idx, cn, n, vec);
+    ls_st4(reinterpret_cast<TE*>(p.hE) + ((int64_t)l * (p.T + 1) + t + 1) * BH + idx, hv, n, vec);
+    if (l + 1 < p.L) {
+      ls_st4(reinterpret_cast<TE*>(p.out) + ((int64_t)l * p.T + t) * BH + idx, o, n, vec);
+      const int64_t slot = (2 * l + (t & 1)) * p.h_stride;
+      ls_st4(reinterpret_cast<TE*>(p.oF_hi + slot) + foff, o, 4, true);
+      if constexpr (M::kPair) ls_st4(reinterpret_cast<TE*>(p.oF_lo + slot) + foff, ls_rest<TE>(o), 4, true);
+    } else {
+      ls_st4(reinterpret_cast<TE*>(p.y) + (int64_t)t * BH + idx, o, n, vec);
+    }
+  }
+}
+
+// ---- backward --------------------------------------------------------------------
+// Block: 16 * NI hidden units x 16 * NJ sentences of layer l at step t.  Two sums per output, over the 4H gate rows:
+// da_{t+1} W_hh of the layer itself (the gradient through its own state) and da_t W_ih of the layer above (the gradient
+// of its output; the top layer reads the caller's dy).  The gradient w.r.t. h_t is the former where step t + 1 was a
+// word of the sentence, else what came in for the final state (sentences are right-padded, so the steps of a sentence
+// are a prefix).  t = -1: the first sum alone, written out as the gradient of the initial state.
+template <typename TE, int NI, int NJ, int PF>
+__global__ __launch_bounds__(64 * LS_KS) void ls_wave_bwd_kernel(LsBwd p, int d, int l_lo, int n_layers) {
+  typedef LsMma<TE> M;
+  typedef typename M::acc_t acc_t;
+  constexpr int KST = LsGeom<TE>::kKStep;
+  __shared__ acc_t red[2 * LS_KS * NI * NJ * 64];   // [sum][wave][i][j][lane]
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int q = lane >> 4, c = lane & 15;
+  const int H = p.H, B = p.B, nct = (B + 15) >> 4;
+  const int nut = (H + 16 * NI - 1) / (16 * NI), nbt = (B + 16 * NJ - 1) / (16 * NJ);
+  int slice, bt;
+  if (!ls_block_of(n_layers * nut, nbt, slice, bt)) return;
+  const int l = l_lo + slice / nut, u0 = (slice % nut) * 16 * NI, b0 = bt * 16 * NJ;
+  const int t = p.T - 1 - (d - (p.L - 1 - l));
+  const bool vec = (H & 3) == 0, top = l + 1 == p.L;
+  const int64_t BH = (int64_t)B * H;
+
+  // the inputs of the cell derivative are requested ahead of the products
+  constexpr int NTASK = (NI * NJ + LS_KS - 1) / LS_KS;
+  f32x4_t gi[NTASK], gf[NTASK], gg[NTASK], go[NTASK], cp[NTASK], cn[NTASK], dy[NTASK], dcs[NTASK], carried[NTASK];
+  int len[NTASK];
+#pragma unroll
+  for (int k = 0; k < NTASK; ++k) {
+    const int task = wave + k * LS_KS, i = task / NJ, j = task % NJ;
+    const int b = b0 + 16 * j + c, unit0 = u0 + 16 * i + 4 * q;
+    const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+    len[k] = 0;
+    carried[k] = dcs[k] = dy[k] = zero;
+    if (task >= NI * NJ || b >= B || unit0 >= H) continue;
+    const int n = H - unit0;
+    const int64_t idx = (int64_t)b * H + unit0;
+    len[k] = ls_len(p.lengths, b, p.T);
+    if (p.dhT) carried[k] = ls_ld4(p.dhT + l * BH + idx, n, vec);
+    if (t >= 0) {
+      const float* dc_in = t + 1 < p.T ? p.dcs : p.dcT;
+      if (dc_in) dcs[k] = ls_ld4(dc_in + l * BH + idx, n, vec);
+    }
+    if (t >= 0 && t < len[k]) {
+      const float* G = p.gates + ((int64_t)l * p.T + t) * 4 * BH + (int64_t)b * 4 * H + unit0;
+      gi[k] = ls_ld4(G, n, vec);
+      gf[k] = ls_ld4(G + H, n, vec);
+      gg[k] = ls_ld4(G + 2 * (int64_t)H, n, vec);
+      go[k] = ls_ld4(G + 3 * (int64_t)H, n, vec);
+      const float* cs = p.cs + ((int64_t)l * (p.T + 1) + t) * BH + idx;
+      cp[k] = ls_ld4(cs, n, vec);
+      cn[k] = ls_ld4(cs + BH, n, vec);
+      if (top) dy[k] = ls_ld4(p.dy + (int64_t)t * BH + idx, n, vec);
+    }
+  }
+
+  acc_t acc[2][NI][NJ];   // own state, output
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[s][i][j][r] = 0;
+
+  const int ng = 4 * ls_gate_stride<TE>(H) / KST;
+  const int n0 = t + 1 < p.T ? ng : 0, n1 = !top && t >= 0 ? ng : 0;
+  if (n0 + n1 > 0) {
+    const int64_t cstep = (int64_t)nct * kLsTile, wstep = (int64_t)((H + 63) / 64 * 4) * kLsTile;   // ls_unit_tiles
+    const char* w0 = p.WT_hh[l] + u0 / 16 * kLsTile;
+    const char* w1 = p.WT_up[l] + u0 / 16 * kLsTile;
+    const char* g0 = p.dGF + (2 * l + ((t + 1) & 1)) * p.g_stride;
+    const char* g1 = p.dGF + (2 * (l + 1) + (t & 1)) * p.g_stride;
+    int64_t ctoff[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int ct = (b0 >> 4) + j;
+      ctoff[j] = (ct < nct ? ct : nct - 1) * kLsTile;
+    }
+    ls_u32x4_t wf[PF][NI], df[PF][NJ];
+    auto load = [&](int slot, int s) {
+      const bool in = s >= n0;
+      const int k = in ? s - n0 : s;
+      const char* wb = (in ? w1 : w0) + k * wstep + lane * 16;
+#pragma unroll
+      for (int i = 0; i < NI; ++i) wf[slot][i] = *reinterpret_cast<const ls_u32x4_t*>(wb + i * kLsTile);
+      const char* gb = (in ? g1 : g0) + k * cstep + lane * 16;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) df[slot][j] = *reinterpret_cast<const ls_u32x4_t*>(gb + ctoff[j]);
+    };
+    auto mul = [&](int slot, int s) {
+      if (s < n0) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) M::mma(acc[0][i][j], wf[slot][i], df[slot][j]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) M::mma(acc[1][i][j], wf[slot][i], df[slot][j]);
+      }
+    };
+    ls_reduce<PF>(n0 + n1, wave, load, mul);
+  }
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) red[(((s * LS_KS + wave) * NI + i) * NJ + j) * 64 + lane] = acc[s][i][j];
+  __syncthreads();
+
+  const int GS = ls_gate_stride<TE>(H);
+#pragma unroll
+  for (int k = 0; k < NTASK; ++k) {
+    const int task = wave + k * LS_KS, i = task / NJ, j = task % NJ;
+    const int b = b0 + 16 * j + c, unit0 = u0 + 16 * i + 4 * q;
+    if (task >= NI * NJ || unit0 >= H) continue;   // lanes past the batch stay for the column sums
+    const int n = H - unit0;
+    const int64_t idx = (int64_t)b * H + unit0;
+    f32x4_t sum[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      acc_t v = red[((s * LS_KS * NI + i) * NJ + j) * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < LS_KS; ++w) v += red[(((s * LS_KS + w) * NI + i) * NJ + j) * 64 + lane];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sum[s][e] = (float)v[e];
+    }
+    f32x4_t dh;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) dh[e] = t + 1 < len[k] ? sum[0][e] : carried[k][e];
+    if (t < 0) {
+      if (b < B) ls_st4(p.dh0 + l * BH + idx, dh, n, vec);
+      continue;
+    }
+    f32x4_t da[4];
+    const bool cell = b < B && t < len[k];
+    if (cell) {
+      if (!top) {
+        dy[k] = sum[1];
+        if (p.drop_thr) {   // back through the mask the forward step put on this layer's output
+          const f32x4_t m = ls_drop4(((uint64_t)l * p.T + t) * (uint64_t)BH + (uint64_t)idx, p.drop_seed, p.drop_thr,
+                                     p.drop_scale, vec);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dy[k][e] = m[e] != 0.f ? dy[k][e] * m[e] : 0.f;
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float dd = dy[k][e] + dh[e];
+        const float tc = tanhf(cn[k][e]);
+        const float dc = dcs[k][e] + dd * go[k][e] * (1.f - tc * tc);
+        da[0][e] = dc * gg[k][e] * gi[k][e] * (1.f - gi[k][e]);
+        da[1][e] = dc * cp[k][e] * gf[k][e] * (1.f - gf[k][e]);
+        da[2][e] = dc * gi[k][e] * (1.f - gg[k][e] * gg[k][e]);
+        da[3][e] = dd * tc * go[k][e] * (1.f - go[k][e]);
+        dcs[k][e] = dc * gf[k][e];
+      }
+      if (!vec) {   // units past H: reduction padding of the products that read these, kept zero
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (e >= n) da[0][e] = da[1][e] = da[2][e] = da[3][e] = 0.f;
+      }
+    } else {
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) da[g][e] = 0.f;
+    }
+    if (b < B) {
+      ls_st4(p.dcs + l * BH + idx, dcs[k], n, vec);
+      TE* dG = reinterpret_cast<TE*>(p.dG) + ((int64_t)l * p.T + t) * 4 * BH + (int64_t)b * 4 * H + unit0;
+      TE* dGF = reinterpret_cast<TE*>(p.dGF + (2 * l + (t & 1)) * p.g_stride);
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        ls_st4(dG + (int64_t)g * H, da[g], n, vec);
+        ls_st4(dGF + ls_tile_off<TE>(g * GS + unit0, b, nct), da[g], 4, true);
+      }
+    }
+    // bias gradient: sums over the tile's sentences, added up over the steps in an accumulator of the tile's own
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float v = da[g][e];
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 16);
+        da[g][e] = v;
+      }
+    if (c < 4 && (b0 >> 4) + j < nct) {
+      const f32x4_t mine = c == 0 ? da[0] : c == 1 ? da[1] : c == 2 ? da[2] : da[3];
+      float* acc_p = p.dbacc + ((int64_t)l * nct + (b0 >> 4) + j) * 4 * H + (int64_t)c * H + unit0;
+      f32x4_t old = {0.f, 0.f, 0.f, 0.f};
+      if (t + 1 < p.T) old = ls_ld4(acc_p, n, vec);
+      ls_st4(acc_p, old + mine, n, vec);
+    }
+  }
+}
+
+// ---- operands as tiles -------------------------------------------------------------
+template <typename TE>
+__device__ __forceinline__ void ls_copy_chunk(char* dst, const TE* src, int n) {
+  constexpr int V = LsGeom<TE>::kVec;
+  if (n >= V && (reinterpret_cast<uintptr_t>(src) & 15) == 0) {
+    *reinterpret_cast<ls_u32x4_t*>(dst) = *reinterpret_cast<const ls_u32x4_t*>(src);
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < V; ++e) reinterpret_cast<TE*>(dst)[e] = e < n ? src[e] : (TE)0;
+}
+
+// Jobs (blockIdx.y): 0 .. L-1 states of a layer, L the input x, then (unless w_rows) W_hh and W_ih of each layer.
+template <typename TE>
+__global__ __launch_bounds__(256) void ls_prep_fwd_kernel(LsFwd p, LsPrepFwd s) {
+  typedef LsMma<TE> M;
+  constexpr int V = LsGeom<TE>::kVec, KST = LsGeom<TE>::kKStep;
+  const int job = blockIdx.y, H = p.H, B = p.B, L = p.L, nct = (B + 15) >> 4;
+  const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x, stride = (int64_t)gridDim.x * 256;
+  const int64_t BH = (int64_t)B * H;
+  if (job < L) {
+    const int l = job;
+    const int64_t n = (int64_t)((H + KST - 1) / KST) * nct * 64;
+    TE* hE = reinterpret_cast<TE*>(p.hE) + (int64_t)l * (p.T + 1) * BH;
+    float* cs = p.cs + (int64_t)l * (p.T + 1) * BH;
+    for (int64_t i = first; i < n; i += stride) {
+      const int lane = (int)(i & 63), k = (int)((i >> 6) / nct) * KST + (lane >> 4) * V;
+      const int64_t tile = i >> 6;
+      const int b = (int)(tile % nct) * 16 + (lane & 15);
+      TE hi[V], lo[V];
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        const bool in = b < B && k + e < H;
+        const int64_t idx = (int64_t)l * BH + (int64_t)(in ? b : 0) * H + (in ? k + e : 0);
+        const float h = in && s.h0 ? s.h0[idx] : 0.f;
+        st_elem<TE>(hi, e, h);
+        st_elem<TE>(lo, e, h - round_elem<TE>(h));
+        if (in) {
+          const float c = s.c0 ? s.c0[idx] : 0.f;
+          p.hf[idx] = h;
+          cs[idx - (int64_t)l * BH] = c;
+          st_elem<TE>(hE, idx - (int64_t)l * BH, h);
+        }
+      }
+      auto put = [&](char* base, const TE (&v)[V]) {
+#pragma unroll
+        for (int e = 0; e < V; ++e) reinterpret_cast<TE*>(base + i * 16)[e] = v[e];
+      };
+      put(p.hF_hi + 2 * l * p.h_stride, hi);
+      if constexpr (M::kPair) put(p.hF_lo + 2 * l * p.h_stride, lo);
+      if (k >= H) {   // reduction padding: zero in every slot
+        const TE z[V] = {};
+        put(p.hF_hi + (2 * l + 1) * p.h_stride, z);
+        if constexpr (M::kPair) put(p.hF_lo + (2 * l + 1) * p.h_stride, z);
+        if (l + 1 < L)
+          for (int sl = 0; sl < 2; ++sl) {
+            put(p.oF_hi + (2 * l + sl) * p.h_stride, z);
+            if constexpr (M::kPair) put(p.oF_lo + (2 * l + sl) * p.h_stride, z);
+          }
+      }
+    }
+  } else if (job == L) {
+    const int nks = (p.I + KST - 1) / KST;
+    const int64_t per = (int64_t)nks * nct * 64, n = per * p.T;
+    const TE* x = reinterpret_cast<const TE*>(s.x);
+    for (int64_t i = first; i < n; i += stride) {
+      const int t = (int)(i / per);
+      const int64_t r = i - t * per, tile = r >> 6;
+      const int lane = (int)(r & 63), k = (int)(tile / nct) * KST + (lane >> 4) * V;
+      const int b = (int)(tile % nct) * 16 + (lane & 15);
+      const bool in = b < B && k < p.I;
+      ls_copy_chunk<TE>(const_cast<char*>(p.xF) + t * p.x_stride + r * 16,
+                        x + ((int64_t)t * B + (in ? b : 0)) * p.I + (in ? k : 0), in ? p.I - k : 0);
+    }
+    if (M::kPair)
+      for (int64_t i = first; i < (int64_t)nct * 64; i += stride)
+        *reinterpret_cast<ls_u32x4_t*>(const_cast<char*>(p.zeros) + i * 16) = ls_u32x4_t{0u, 0u, 0u, 0u};
+  } else {
+    const int l = (job - L - 1) >> 1;
+    const bool hh = ((job - L - 1) & 1) == 0;
+    const int K = hh || l > 0 ? H : p.I, ntw = (H + 31) / 32 * 8;
+    const TE* W = reinterpret_cast<const TE*>(hh ? s.W_hh[l] : s.W_ih[l]);
+    char* dst = reinterpret_cast<char*>(const_cast<void*>(hh ? p.W_hh[l] : p.W_ih[l]));
+    const int64_t n = (int64_t)((K + KST - 1) / KST) * ntw * 64;
+    for (int64_t i = first; i < n; i += stride) {
+      const int64_t tile = i >> 6;
+      const int lane = (int)(i & 63), k = (int)(tile / ntw) * KST + (lane >> 4) * V, rt = (int)(tile % ntw);
+      const int unit = 16 * (rt >> 2) + 4 * M::q_of_row(lane & 15) + (rt & 3), gate = M::r_of_row(lane & 15);
+      const bool in = unit < H && k < K;
+      ls_copy_chunk<TE>(dst + i * 16, W + ((int64_t)gate * H + (in ? unit : 0)) * K + (in ? k : 0), in ? K - k : 0);
+    }
+  }
+}
+
+// Jobs (blockIdx.y): W_hh^T of each layer, then W_ih[l + 1]^T.  Tile row rho of tile i: unit 16 i + 4 q + r.
+template <typename TE>
+__global__ __launch_bounds__(256) void ls_prep_bwd_kernel(LsBwd p, LsPrepBwd s) {
+  typedef LsMma<TE> M;
+  constexpr int V = LsGeom<TE>::kVec, KST = LsGeom<TE>::kKStep;
+  const int job = blockIdx.y, H = p.H, L = p.L;
+  const int l = job < L ? job : job - L;
+  const TE* W = reinterpret_cast<const TE*>(job < L ? s.W_hh[l] : s.W_ih[l + 1]);
+  char* dst = const_cast<char*>(job < L ? p.WT_hh[l] : p.WT_up[l]);
+  const int GS = ls_gate_stride<TE>(H), ntu = (H + 63) / 64 * 4;
+  const int64_t n = (int64_t)(4 * GS / KST) * ntu * 64;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const int64_t tile = i >> 6;
+    const int lane = (int)(i & 63), rho = lane & 15, k = (int)(tile / ntu) * KST + (lane >> 4) * V;
+    const int unit = 16 * (int)(tile % ntu) + 4 * M::q_of_row(rho) + M::r_of_row(rho);
+    const int gate = k / GS, u = k - gate * GS;   // GS % V == 0: a chunk lies inside one gate
+    TE v[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e)
+      v[e] = unit < H && u + e < H ? W[((int64_t)gate * H + u + e) * H + unit] : (TE)0;
+#pragma unroll
+    for (int e = 0; e < V; ++e) reinterpret_cast<TE*>(dst + i * 16)[e] = v[e];
+  }
+}
+
+__global__ __launch_bounds__(256) void ls_bias_reduce_kernel(const float* __restrict__ dbacc, LsBiasOut o, int nct,
+                                                             int cols) {
+  const int col = blockIdx.x * 256 + threadIdx.x, l = blockIdx.y;
+  if (col >= cols) return;
+  const float* a = dbacc + (int64_t)l * nct * cols + col;
+  float s = 0.f;
+#pragma unroll 8
+  for (int ct = 0; ct < nct; ++ct) s += a[(int64_t)ct * cols];
+  o.db[l][col] = s;
+}
+
+// ---- launches ----------------------------------------------------------------------
+template <typename TE> bool ls_reads_weight_rows(int T, int I, int H, int) {
+  return T == 1 && I % LsGeom<TE>::kVec == 0 && H % LsGeom<TE>::kVec == 0;
+}
+
+template <typename TE> hipError_t launch_ls_prep_fwd(const LsFwd& p, const LsPrepFwd& q, hipStream_t st) {
+  constexpr int KST = LsGeom<TE>::kKStep;
+  const int64_t nct = ls_batch_tiles(p.B);
+  int64_t n = ls_ksteps<TE>(p.H) * nct * 64;   // largest job, in chunks
+  const int64_t nx = (int64_t)ls_ksteps<TE>(p.I) * nct * 64 * p.T;
+  if (nx > n) n = nx;
+  if (!p.w_rows) {
+    const int64_t nw = (int64_t)((p.I > p.H ? p.I : p.H) + KST - 1) / KST * ls_gate_tiles(p.H) * 64;
+    if (nw > n) n = nw;
+  }
+  int64_t gx = (n + 255) / 256;
+  if (gx > 1024) gx = 1024;
+  const int jobs = p.L + 1 + (p.w_rows ? 0 : 2 * p.L);
+  hipLaunchKernelGGL(ls_prep_fwd_kernel<TE>, dim3((unsigned)gx, jobs), dim3(256), 0, st, p, q);
+  return hipGetLastError();
+}
+template <typename TE> hipError_t launch_ls_prep_bwd(const LsBwd& p, const LsPrepBwd& q, hipStream_t st) {
+  const int64_t n = (int64_t)(4 * ls_gate_stride<TE>(p.H) / LsGeom<TE>::kKStep) * ls_unit_tiles(p.H) * 64;
+  int64_t gx = (n + 255) / 256;
+  if (gx > 1024) gx = 1024;
+  hipLaunchKernelGGL(ls_prep_bwd_kernel<TE>, dim3((unsigned)gx, 2 * p.L - 1), dim3(256), 0, st, p, q);
+  return hipGetLastError();
+}
+hipError_t launch_ls_bias_reduce(const float* dbacc, const LsBiasOut& o, int L, int nct, int cols, hipStream_t st) {
+  hipLaunchKernelGGL(ls_bias_reduce_kernel, dim3((cols + 255) / 256, L), dim3(256), 0, st, dbacc, o, nct, cols);
+  return hipGetLastError();
+}
+
+template <typename TE, int NI, int NJ, int PF>
+static hipError_t ls_fwd_shape(const LsFwd& p, int d, int l_lo, int nl, hipStream_t st) {
+  const unsigned grid = ls_grid((int64_t)nl * ((p.H + 4 * NI - 1) / (4 * NI)), (p.B + 16 * NJ - 1) / (16 * NJ));
+  if (p.w_rows)
+    hipLaunchKernelGGL((ls_wave_fwd_kernel<TE, NI, NJ, PF, true>), dim3(grid), dim3(64 * LS_KS), 0, st, p, d, l_lo, nl);
+  else
+    hipLaunchKernelGGL((ls_wave_fwd_kernel<TE, NI, NJ, PF, false>), dim3(grid), dim3(64 * LS_KS), 0, st, p, d, l_lo, nl);
+  return hipGetLastError();
+}
+template <typename TE, int NI, int NJ, int PF>
+static hipError_t ls_bwd_shape(const LsBwd& p, int d, int l_lo, int nl, hipStream_t st) {
+  const unsigned grid = ls_grid((int64_t)nl * ((p.H + 16 * NI - 1) / (16 * NI)), (p.B + 16 * NJ - 1) / (16 * NJ));
+  hipLaunchKernelGGL((ls_wave_bwd_kernel<TE, NI, NJ, PF>), dim3(grid), dim3(64 * LS_KS), 0, st, p, d, l_lo, nl);
+  return hipGetLastError();
+}
+
+template <typename TE> hipError_t launch_ls_wave_fwd(const LsFwd& p, int d, hipStream_t st) {
+  const int l_lo = d - p.T + 1 > 0 ? d - p.T + 1 : 0, l_hi = d < p.L - 1 ? d : p.L - 1;   // 0 <= d - l < T
+  const int nl = l_hi - l_lo + 1;
+  if (nl < 1) return hipErrorInvalidValue;
+  const int64_t b64 = (p.B + 63) / 64, b32 = (p.B + 31) / 32;
+  if constexpr (LsMma<TE>::kPair) {
+    if (nl * ((p.H + 31) / 32) * b64 >= 192) return ls_fwd_shape<TE, 8, 4, 3>(p, d, l_lo, nl, st);
+    if (nl * ((p.H + 15) / 16) * b32 >= 192) return ls_fwd_shape<TE, 4, 2, 4>(p, d, l_lo, nl, st);
+    return ls_fwd_shape<TE, 4, 1, 4>(p, d, l_lo, nl, st);
+  } else {
+    if (nl * ((p.H + 15) / 16) * b32 >= 512) return ls_fwd_shape<TE, 4, 2, 4>(p, d, l_lo, nl, st);
+    return ls_fwd_shape<TE, 4, 1, 4>(p, d, l_lo, nl, st);
+  }
+}
+
+template <typename TE> hipError_t launch_ls_wave_bwd(const LsBwd& p, int d, hipStream_t st) {
+  const int dl = p.L - 1;                              // layer l takes step T - 1 - (d - (dl - l))
+  const int tail = p.dh0 ? p.T : p.T - 1;              // largest d - (dl - l)
+  const int l_hi = dl - (d - tail > 0 ? d - tail : 0), l_lo = dl - (d < dl ? d : dl);
+  const int nl = l_hi - l_lo + 1;
+  if (nl < 1) return hipErrorInvalidValue;
+  const int64_t b32 = (p.B + 31) / 32;
+  if constexpr (LsMma<TE>::kPair) {
+    if (nl * ((p.H + 63) / 64) * b32 >= 192) return ls_bwd_shape<TE, 4, 2, 4>(p, d, l_lo, nl, st);
+    if (nl * ((p.H + 31) / 32) * b32 >= 192) return ls_bwd_shape<TE, 2, 2, 4>(p, d, l_lo, nl, st);
+    return ls_bwd_shape<TE, 1, 2, 4>(p, d, l_lo, nl, st);
+  } else {
+    if (nl * ((p.H + 15) / 16) * b32 >= 512) return ls_bwd_shape<TE, 1, 2, 4>(p, d, l_lo, nl, st);
+    return ls_bwd_shape<TE, 1, 1, 4>(p, d, l_lo, nl, st);
+  }
+}
+
+#define ASX_LS(TE)                                                                                  \
+  template bool ls_reads_weight_rows<TE>(int, int, int, int);                                       \
+  template hipError_t launch_ls_prep_fwd<TE>(const LsFwd&, const LsPrepFwd&, hipStream_t);          \
+  template hipError_t launch_ls_prep_bwd<TE>(const LsBwd&, const LsPrepBwd&, hipStream_t);          \
+  template hipError_t launch_ls_wave_fwd<TE>(const LsFwd&, int, hipStream_t);                       \
+  template hipError_t launch_ls_wave_bwd<TE>(const LsBwd&, int, hipStream_t);
+ASX_LS(uint16_t)
+ASX_LS(float)
+#undef ASX_LS
+
+}  // namespace asx
