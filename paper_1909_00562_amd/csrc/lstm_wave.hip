@@ -34,6 +34,7 @@ template <typename TE> struct LsMma;
 template <> struct LsMma<uint16_t> {
   typedef f32x4_t acc_t;
   typedef float sum_t;
+  typedef ls_u32x2_t raw4_t;
   static constexpr bool kPair = true;
   static __device__ __forceinline__ void mma(acc_t& acc, ls_u32x4_t a, ls_u32x4_t b) {
     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), acc,
@@ -46,6 +47,7 @@ template <> struct LsMma<uint16_t> {
 template <> struct LsMma<float> {
   typedef ls_f64x4_t acc_t;
   typedef double sum_t;
+  typedef f32x4_t raw4_t;
   static constexpr bool kPair = false;
   static __device__ __forceinline__ void mma(acc_t& acc, ls_u32x4_t a, ls_u32x4_t b) {
     const f32x4_t af = __builtin_bit_cast(f32x4_t, a), bf = __builtin_bit_cast(f32x4_t, b);
@@ -62,30 +64,38 @@ __device__ __forceinline__ int ls_len(const int32_t* lengths, int b, int T) {
   return n < 0 ? 0 : (n > T ? T : n);
 }
 
-// Four consecutive elements, of which n are inside; vec: H % 4 == 0, all four are inside and aligned
-__device__ __forceinline__ f32x4_t ls_ld4(const float* p, int n, bool vec) {
-  if (vec) return *reinterpret_cast<const f32x4_t*>(p);
-  f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+// Four consecutive elements, of which n are inside.  VEC (H % 4 == 0): all four are, and aligned.
+template <bool VEC> __device__ __forceinline__ f32x4_t ls_ld4(const float* p, int n) {
+  if constexpr (VEC) {
+    return *reinterpret_cast<const f32x4_t*>(p);
+  } else {
+    f32x4_t v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int e = 0; e < 4; ++e)
-    if (e < n) v[e] = p[e];
-  return v;
+    for (int e = 0; e < 4; ++e)
+      if (e < n) v[e] = p[e];
+    return v;
+  }
 }
-__device__ __forceinline__ f32x4_t ls_ld4(const uint16_t* p, int, bool) {
-  const ls_u32x2_t w = *reinterpret_cast<const ls_u32x2_t*>(p);
+template <bool VEC> __device__ __forceinline__ void ls_st4(float* p, const f32x4_t& v, int n) {
+  if constexpr (VEC) {
+    *reinterpret_cast<f32x4_t*>(p) = v;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (e < n) p[e] = v[e];
+  }
+}
+// bf16 storage implies VEC (H % 8 == 0); raw: four elements as loaded
+template <bool VEC> __device__ __forceinline__ ls_u32x2_t ls_ldraw4(const uint16_t* p, int) {
+  return *reinterpret_cast<const ls_u32x2_t*>(p);
+}
+template <bool VEC> __device__ __forceinline__ f32x4_t ls_ldraw4(const float* p, int n) { return ls_ld4<VEC>(p, n); }
+__device__ __forceinline__ f32x4_t ls_widen4(const f32x4_t& v) { return v; }
+__device__ __forceinline__ f32x4_t ls_widen4(const ls_u32x2_t& w) {
   const f32x4_t v = {lo_bf16(w[0]), hi_bf16(w[0]), lo_bf16(w[1]), hi_bf16(w[1])};
   return v;
 }
-__device__ __forceinline__ void ls_st4(float* p, const f32x4_t& v, int n, bool vec) {
-  if (vec) {
-    *reinterpret_cast<f32x4_t*>(p) = v;
-    return;
-  }
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
-    if (e < n) p[e] = v[e];
-}
-__device__ __forceinline__ void ls_st4(uint16_t* p, const f32x4_t& v, int, bool) {
+template <bool VEC> __device__ __forceinline__ void ls_st4(uint16_t* p, const f32x4_t& v, int) {
   const ls_u32x2_t w = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
   *reinterpret_cast<ls_u32x2_t*>(p) = w;
 }
@@ -95,10 +105,10 @@ template <typename TE> __device__ __forceinline__ f32x4_t ls_rest(const f32x4_t&
   for (int e = 0; e < 4; ++e) r[e] = v[e] - round_elem<TE>(v[e]);
   return r;
 }
-// multipliers of the four elements from flat index i on (vec: i % 4 == 0)
-__device__ __forceinline__ f32x4_t ls_drop4(uint64_t i, uint64_t seed, uint32_t thr, float scale, bool vec) {
+// multipliers of the four elements from flat index i on (VEC: i % 4 == 0)
+template <bool VEC> __device__ __forceinline__ f32x4_t ls_drop4(uint64_t i, uint64_t seed, uint32_t thr, float scale) {
   f32x4_t m;
-  if (vec) {
+  if constexpr (VEC) {
     uint32_t w[4];
     dropout_words4(i >> 2, seed, w);
 #pragma unroll
@@ -118,32 +128,60 @@ template <typename TE> __device__ __forceinline__ int64_t ls_tile_off(int k, int
   return (((int64_t)(k / K) * nct + (b >> 4)) * 64 + (k % K) / V * 16 + (b & 15)) * V + k % V;
 }
 
+// 16 bytes per lane from a wave-uniform address and an unsigned lane offset: the form that needs no 64-bit address
+// arithmetic and no address registers per load
+__device__ __forceinline__ ls_u32x4_t ls_frag(const char* base, uint32_t lane16) {
+  return *reinterpret_cast<const ls_u32x4_t*>(base + lane16);
+}
+
 // Blocks of a wavefront: nslices (layer, row block) slices of the weights x nbt batch blocks.  Consecutive blocks go
-// round-robin to the 8 XCDs; the batch blocks of a slice go to one XCD, whose L2 then fetches the slice once.
+// round-robin to the 8 XCDs.  An XCD gets a contiguous run of slices with all their batch blocks: its L2 fetches a
+// slice of the weights once, and the state of few layers only.
 __device__ __forceinline__ bool ls_block_of(int nslices, int nbt, int& slice, int& bt) {
-  const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
+  const int per = (nslices + 7) >> 3, xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
   const int s = idx / nbt;
-  slice = s * 8 + xcd;
+  slice = xcd * per + s;
   bt = idx - s * nbt;
   return slice < nslices;
 }
 static inline unsigned ls_grid(int64_t nslices, int64_t nbt) { return (unsigned)((nslices + 7) / 8 * 8 * nbt); }
 
-// The reduction of one wave over its steps of a list of nsteps: PF slots of fragments in flight.  load(slot, s) must be
-// free of branches and valid for every s in [0, nsteps); past the wave's last step the last one is loaded again, so
-// that the number of loads in flight is the same on every path and a wait covers just the fragments it needs.
-template <int PF, typename Load, typename Mul>
-__device__ __forceinline__ void ls_reduce(int nsteps, int wave, Load load, Mul mul) {
-  const int n = nsteps > wave ? (nsteps - wave + LS_KS - 1) / LS_KS : 0;
-  auto at = [&](int i) { const int s = wave + i * LS_KS; return s < nsteps ? s : nsteps - 1; };
+// steps w, w + LS_KS, ... of a list of nsteps
+__device__ __forceinline__ int ls_own_steps(int nsteps, int wave) {
+  return nsteps > wave ? (nsteps - wave + LS_KS - 1) / LS_KS : 0;
+}
+
+// schedule of a region: load v of NL after (v + 1) / NL of its NM matrix instructions
+template <int v, int NL, int NM> __device__ __forceinline__ void ls_spread() {
+  if constexpr (v < NL) {
+    constexpr int nm = (v + 1) * NM / NL - v * NM / NL;
+    if constexpr (nm > 0) __builtin_amdgcn_sched_group_barrier(0x008, nm, 0);
+    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    ls_spread<v + 1, NL, NM>();
+  }
+}
+
+// A wave's n reduction steps, slot i % PF of the fragment registers holding step i.  load(slot, i) must be free of
+// branches and valid for 0 <= i < n; past the last step it is called with the last one again, so that the number of
+// loads in flight is the same on every path and a wait covers just the fragments it needs.
+// The NL loads of a step are spread over the NM matrix instructions of an earlier one.  Issued in one run they hold the
+// wave at the address unit while its matrix pipe idles: forward wavefronts of 4 layers x 1024 units x 128 sentences
+// then took the sum of their load and matrix times.
+template <int PF, int NL, int NM, typename Load, typename Mul>
+__device__ __forceinline__ void ls_reduce(int n, Load load, Mul mul) {
+  if (n <= 0) return;
+  auto at = [&](int i) { return i < n ? i : n - 1; };
 #pragma unroll
-  for (int u = 0; u < PF; ++u) load(u, at(u));
+  for (int u = 0; u + 1 < PF; ++u) load(u, at(u));
+  __builtin_amdgcn_sched_barrier(0);
   int i = 0;
   for (; i + PF <= n; i += PF) {
 #pragma unroll
     for (int u = 0; u < PF; ++u) {
       mul(u, at(i + u));
-      load(u, at(i + u + PF));
+      load((u + PF - 1) % PF, at(i + u + PF - 1));
+      ls_spread<0, NL, NM>();
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
 #pragma unroll
@@ -155,15 +193,17 @@ __device__ __forceinline__ void ls_reduce(int nsteps, int wave, Load load, Mul m
 // Block: 16 * NI gate rows (4 * NI hidden units) x 16 * NJ sentences.  Tile 4 g + ii of a block, row rho: unit
 // u0 + 16 g + 4 q + ii, gate r, (q, r) = the lane group and register that hold row rho.  ROWS: weights are read as the
 // caller's rows (64 bytes of a row per load), each used once by the call.
-template <typename TE, int NI, int NJ, int PF, bool ROWS>
+template <typename TE, int NI, int NJ, int PF, bool ROWS, bool VEC>
 __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d, int l_lo, int n_layers) {
   typedef LsMma<TE> M;
   typedef typename M::acc_t acc_t;
   constexpr int NG = NI / 4, V = LsGeom<TE>::kVec, KST = LsGeom<TE>::kKStep;
   static_assert(NI % 4 == 0, "four tiles hold the gates of four consecutive units per lane");
   __shared__ acc_t red[LS_KS * NI * NJ * 64];   // [wave][i][j][lane]
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int q = lane >> 4, c = lane & 15;
+  const uint32_t lane16 = lane * 16u;
   const int H = p.H, B = p.B, nct = (B + 15) >> 4;
   const int nut = (H + 4 * NI - 1) / (4 * NI), nbt = (B + 16 * NJ - 1) / (16 * NJ);
   int slice, bt;
@@ -171,23 +211,23 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
   const int l = l_lo + slice / nut, u0 = (slice % nut) * 4 * NI, b0 = bt * 16 * NJ;
   const int t = d - l;
   const int Kin = l == 0 ? p.I : H;
-  const bool vec = (H & 3) == 0;
   const int64_t BH = (int64_t)B * H;
 
   // what the cells need from memory is requested ahead of the product
   constexpr int NTASK = (NG * NJ + LS_KS - 1) / LS_KS;   // (g, j) pairs, dealt out to the waves
-  f32x4_t cp[NTASK], bias[NTASK][4];
+  // (lanes and tasks without a cell read the last one: no branch around a load that is to stay in flight)
+  f32x4_t cp[NTASK];
+  typename M::raw4_t bias[NTASK][4];
   const float* c_prev = p.cs + ((int64_t)l * (p.T + 1) + t) * BH;
   const TE* bl = reinterpret_cast<const TE*>(p.bias[l]);
 #pragma unroll
   for (int k = 0; k < NTASK; ++k) {
     const int task = wave + k * LS_KS, g = task / NJ, j = task % NJ;
     const int b = b0 + 16 * j + c, unit0 = u0 + 16 * g + 4 * q;
-    if (task < NG * NJ && b < B && unit0 < H) {
-      cp[k] = ls_ld4(c_prev + (int64_t)b * H + unit0, H - unit0, vec);
+    const int bs = b < B ? b : B - 1, us = unit0 < H ? unit0 : (H - 1) & ~3;
+    cp[k] = ls_ld4<VEC>(c_prev + (int64_t)bs * H + us, H - us);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) bias[k][e] = ls_ld4(bl + (int64_t)e * H + unit0, H - unit0, vec);
-    }
+    for (int e = 0; e < 4; ++e) bias[k][e] = ls_ldraw4<VEC>(bl + (int64_t)e * H + us, H - us);
   }
 
   acc_t acc[NI][NJ];
@@ -212,9 +252,8 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
     const int ct = (b0 >> 4) + j;
     ctoff[j] = (ct < nct ? ct : nct - 1) * kLsTile;   // columns past the batch repeat the last tile; not stored
   }
-  const int64_t wstep = (int64_t)((H + 31) / 32 * 8) * kLsTile;   // ls_gate_tiles
-  const char* w0 = reinterpret_cast<const char*>(p.W_hh[l]) + (ROWS ? 0 : u0 / 4 * kLsTile);
-  const char* w1 = reinterpret_cast<const char*>(p.W_ih[l]) + (ROWS ? 0 : u0 / 4 * kLsTile);
+  const char* w0 = reinterpret_cast<const char*>(p.W_hh[l]) + (ROWS ? 0 : (int64_t)(u0 / 16) * n0 * 4 * kLsTile);
+  const char* w1 = reinterpret_cast<const char*>(p.W_ih[l]) + (ROWS ? 0 : (int64_t)(u0 / 16) * n1 * 4 * kLsTile);
   int wrow[NI];
   if constexpr (ROWS) {
 #pragma unroll
@@ -224,7 +263,8 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
     }
   }
   ls_u32x4_t wf[PF][NI], hf[PF][NJ], lf[PF][M::kPair ? NJ : 1];
-  auto load = [&](int slot, int s) {
+  auto load = [&](int slot, int step) {
+    const int s = wave + step * LS_KS;
     const bool in = s >= n0;
     const int k = in ? s - n0 : s;
     if constexpr (ROWS) {
@@ -234,20 +274,23 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
       for (int i = 0; i < NI; ++i)
         wf[slot][i] = *reinterpret_cast<const ls_u32x4_t*>(wb + (int64_t)wrow[i] * K * sizeof(TE));
     } else {
-      const char* wb = (in ? w1 : w0) + k * wstep + lane * 16;
+      const char* wb = (in ? w1 : w0) + k * (4 * kLsTile);
+      const int64_t group = (int64_t)(in ? n1 : n0) * (4 * kLsTile);
 #pragma unroll
-      for (int i = 0; i < NI; ++i) wf[slot][i] = *reinterpret_cast<const ls_u32x4_t*>(wb + i * kLsTile);
+      for (int i = 0; i < NI; ++i)
+        wf[slot][i] = ls_frag(wb + (i / 4) * group + (i % 4) * kLsTile, lane16);
     }
-    const char* hb = (in ? i_hi : h_hi) + k * cstep + lane * 16;
+    const char* hb = (in ? i_hi : h_hi) + k * cstep;
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) hf[slot][j] = *reinterpret_cast<const ls_u32x4_t*>(hb + ctoff[j]);
+    for (int j = 0; j < NJ; ++j) hf[slot][j] = ls_frag(hb + ctoff[j], lane16);
     if constexpr (M::kPair) {
-      const char* lb = (in ? i_lo + k * lstep1 : h_lo + k * cstep) + lane * 16;
+      const char* lb = in ? i_lo + k * lstep1 : h_lo + k * cstep;
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) lf[slot][j] = *reinterpret_cast<const ls_u32x4_t*>(lb + ctoff[j]);
+      for (int j = 0; j < NJ; ++j) lf[slot][j] = ls_frag(lb + ctoff[j], lane16);
     }
   };
-  auto mul = [&](int slot, int s) {
+  auto mul = [&](int slot, int step) {
+    const int s = wave + step * LS_KS;
     if constexpr (ROWS) {   // chunks past a row's end were read from its start
       const int K = s >= n0 ? Kin : H, kk = (s >= n0 ? s - n0 : s) * KST + q * V;
 #pragma unroll
@@ -266,7 +309,8 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
         for (int j = 0; j < NJ; ++j) M::mma(acc[i][j], wf[slot][i], lf[slot][j]);
     }
   };
-  ls_reduce<PF>(n0 + n1, wave, load, mul);
+  constexpr int NP = M::kPair ? 2 : 1, NM = M::kPair ? 2 * NI * NJ : 4 * NI * NJ;
+  ls_reduce<PF, NI + NP * NJ, NM>(ls_own_steps(n0 + n1, wave), load, mul);
 
 #pragma unroll
   for (int i = 0; i < NI; ++i)
@@ -281,7 +325,9 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
     const int b = b0 + 16 * j + c, unit0 = u0 + 16 * g + 4 * q;
     if (task >= NG * NJ || b >= B || unit0 >= H) continue;
     const int n = H - unit0;
-    f32x4_t gi, gf, gg, go, cn, hn;
+    f32x4_t gi, gf, gg, go, cn, hn, bias4[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) bias4[e] = ls_widen4(bias[k][e]);
 #pragma unroll
     for (int ii = 0; ii < 4; ++ii) {
       acc_t v = red[((4 * g + ii) * NJ + j) * 64 + lane];
@@ -289,7 +335,7 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
       for (int w = 1; w < LS_KS; ++w) v += red[((w * NI + 4 * g + ii) * NJ + j) * 64 + lane];
       float a[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) a[e] = (float)(v[e] + (typename M::sum_t)bias[k][e][ii]);
+      for (int e = 0; e < 4; ++e) a[e] = (float)(v[e] + (typename M::sum_t)bias4[e][ii]);
       gi[ii] = ls_sigmoid(a[0]);
       gf[ii] = ls_sigmoid(a[1]);
       gg[ii] = tanhf(a[2]);
@@ -299,15 +345,15 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
     }
     const int64_t idx = (int64_t)b * H + unit0;
     float* G = p.gates + ((int64_t)l * p.T + t) * 4 * BH + (int64_t)b * 4 * H + unit0;
-    ls_st4(G, gi, n, vec);
-    ls_st4(G + H, gf, n, vec);
-    ls_st4(G + 2 * (int64_t)H, gg, n, vec);
-    ls_st4(G + 3 * (int64_t)H, go, n, vec);
+    ls_st4<VEC>(G, gi, n);
+    ls_st4<VEC>(G + H, gf, n);
+    ls_st4<VEC>(G + 2 * (int64_t)H, gg, n);
+    ls_st4<VEC>(G + 3 * (int64_t)H, go, n);
     const bool valid = t < ls_len(p.lengths, b, p.T);
     const int64_t foff = ls_tile_off<TE>(unit0, b, nct);
     TE* hFn_hi = reinterpret_cast<TE*>(p.hF_hi + (2 * l + ((t + 1) & 1)) * p.h_stride) + foff;
     TE* hFn_lo = reinterpret_cast<TE*>(p.hF_lo + (2 * l + ((t + 1) & 1)) * p.h_stride) + foff;
-    if (!vec) {   // units past H: reduction padding of the next step, kept zero
+    if constexpr (!VEC) {   // units past H: reduction padding of the next step, kept zero
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         if (e >= n) hn[e] = 0.f;
@@ -316,31 +362,31 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
     if (valid) {   // what the next layer reads
       o = hn;
       if (p.drop_thr && l + 1 < p.L) {
-        const f32x4_t m = ls_drop4(((uint64_t)l * p.T + t) * (uint64_t)BH + (uint64_t)idx, p.drop_seed, p.drop_thr,
-                                   p.drop_scale, vec);
+        const f32x4_t m = ls_drop4<VEC>(((uint64_t)l * p.T + t) * (uint64_t)BH + (uint64_t)idx, p.drop_seed, p.drop_thr,
+                                   p.drop_scale);
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = m[e] != 0.f ? o[e] * m[e] : 0.f;
       }
       hv = hn;
-      ls_st4(p.hf + l * BH + idx, hn, n, vec);
-      ls_st4(hFn_hi, hn, 4, true);
-      if constexpr (M::kPair) ls_st4(hFn_lo, ls_rest<TE>(hn), 4, true);
+      ls_st4<VEC>(p.hf + l * BH + idx, hn, n);
+      ls_st4<true>(hFn_hi, hn, 4);
+      if constexpr (M::kPair) ls_st4<true>(hFn_lo, ls_rest<TE>(hn), 4);
     } else {       // padded step: the state passes through, the output is 0
       cn = cp[k];
-      hv = ls_ld4(reinterpret_cast<const TE*>(h_hi) + foff, 4, true);
-      ls_st4(hFn_hi, hv, 4, true);
-      if constexpr (M::kPair) ls_st4(hFn_lo, ls_ld4(reinterpret_cast<const TE*>(h_lo) + foff, 4, true), 4, true);
+      hv = ls_widen4(ls_ldraw4<true>(reinterpret_cast<const TE*>(h_hi) + foff, 4));
+      ls_st4<true>(hFn_hi, hv, 4);
+      if constexpr (M::kPair) ls_st4<true>(hFn_lo, ls_widen4(ls_ldraw4<true>(reinterpret_cast<const TE*>(h_lo) + foff, 4)), 4);
     }
-    ls_st4(p.cs + ((int64_t)l * (p.T + 1) + t + 1) * BH + idx, cn, n, vec);
-    if (last && p.cT) ls_st4(p.cT + l * BH + idx, cn, n, vec);
-    ls_st4(reinterpret_cast<TE*>(p.hE) + ((int64_t)l * (p.T + 1) + t + 1) * BH + idx, hv, n, vec);
+    ls_st4<VEC>(p.cs + ((int64_t)l * (p.T + 1) + t + 1) * BH + idx, cn, n);
+    if (last && p.cT) ls_st4<VEC>(p.cT + l * BH + idx, cn, n);
+    ls_st4<VEC>(reinterpret_cast<TE*>(p.hE) + ((int64_t)l * (p.T + 1) + t + 1) * BH + idx, hv, n);
     if (l + 1 < p.L) {
-      ls_st4(reinterpret_cast<TE*>(p.out) + ((int64_t)l * p.T + t) * BH + idx, o, n, vec);
+      ls_st4<VEC>(reinterpret_cast<TE*>(p.out) + ((int64_t)l * p.T + t) * BH + idx, o, n);
       const int64_t slot = (2 * l + (t & 1)) * p.h_stride;
-      ls_st4(reinterpret_cast<TE*>(p.oF_hi + slot) + foff, o, 4, true);
-      if constexpr (M::kPair) ls_st4(reinterpret_cast<TE*>(p.oF_lo + slot) + foff, ls_rest<TE>(o), 4, true);
+      ls_st4<true>(reinterpret_cast<TE*>(p.oF_hi + slot) + foff, o, 4);
+      if constexpr (M::kPair) ls_st4<true>(reinterpret_cast<TE*>(p.oF_lo + slot) + foff, ls_rest<TE>(o), 4);
     } else {
-      ls_st4(reinterpret_cast<TE*>(p.y) + (int64_t)t * BH + idx, o, n, vec);
+      ls_st4<VEC>(reinterpret_cast<TE*>(p.y) + (int64_t)t * BH + idx, o, n);
     }
   }
 }
@@ -351,54 +397,55 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
 // of its output; the top layer reads the caller's dy).  The gradient w.r.t. h_t is the former where step t + 1 was a
 // word of the sentence, else what came in for the final state (sentences are right-padded, so the steps of a sentence
 // are a prefix).  t = -1: the first sum alone, written out as the gradient of the initial state.
-template <typename TE, int NI, int NJ, int PF>
+template <typename TE, int NI, int NJ, int PF, bool VEC>
 __global__ __launch_bounds__(64 * LS_KS) void ls_wave_bwd_kernel(LsBwd p, int d, int l_lo, int n_layers) {
   typedef LsMma<TE> M;
   typedef typename M::acc_t acc_t;
   constexpr int KST = LsGeom<TE>::kKStep;
+  static_assert(PF % 2 == 0, "a slot belongs to one of the two sums");
   __shared__ acc_t red[2 * LS_KS * NI * NJ * 64];   // [sum][wave][i][j][lane]
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int q = lane >> 4, c = lane & 15;
+  const uint32_t lane16 = lane * 16u;
   const int H = p.H, B = p.B, nct = (B + 15) >> 4;
   const int nut = (H + 16 * NI - 1) / (16 * NI), nbt = (B + 16 * NJ - 1) / (16 * NJ);
   int slice, bt;
   if (!ls_block_of(n_layers * nut, nbt, slice, bt)) return;
   const int l = l_lo + slice / nut, u0 = (slice % nut) * 16 * NI, b0 = bt * 16 * NJ;
   const int t = p.T - 1 - (d - (p.L - 1 - l));
-  const bool vec = (H & 3) == 0, top = l + 1 == p.L;
+  const bool top = l + 1 == p.L;
   const int64_t BH = (int64_t)B * H;
 
   // the inputs of the cell derivative are requested ahead of the products
   constexpr int NTASK = (NI * NJ + LS_KS - 1) / LS_KS;
+  // (lanes and tasks without a cell read the last one, and what is absent is read from cs: no branch around a load
+  // that is to stay in flight)
   f32x4_t gi[NTASK], gf[NTASK], gg[NTASK], go[NTASK], cp[NTASK], cn[NTASK], dy[NTASK], dcs[NTASK], carried[NTASK];
   int len[NTASK];
+  const int tc0 = t < 0 ? 0 : t;
+  const float* cs_t = p.cs + ((int64_t)l * (p.T + 1) + tc0) * BH;
+  const float* dc_in = t + 1 < p.T ? p.dcs : p.dcT;
+  const float* dc_src = dc_in ? dc_in + l * BH : cs_t;
+  const float* dh_src = p.dhT ? p.dhT + l * BH : cs_t;
+  const float* dy_src = top ? p.dy + (int64_t)tc0 * BH : cs_t;
 #pragma unroll
   for (int k = 0; k < NTASK; ++k) {
     const int task = wave + k * LS_KS, i = task / NJ, j = task % NJ;
     const int b = b0 + 16 * j + c, unit0 = u0 + 16 * i + 4 * q;
-    const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
-    len[k] = 0;
-    carried[k] = dcs[k] = dy[k] = zero;
-    if (task >= NI * NJ || b >= B || unit0 >= H) continue;
-    const int n = H - unit0;
-    const int64_t idx = (int64_t)b * H + unit0;
-    len[k] = ls_len(p.lengths, b, p.T);
-    if (p.dhT) carried[k] = ls_ld4(p.dhT + l * BH + idx, n, vec);
-    if (t >= 0) {
-      const float* dc_in = t + 1 < p.T ? p.dcs : p.dcT;
-      if (dc_in) dcs[k] = ls_ld4(dc_in + l * BH + idx, n, vec);
-    }
-    if (t >= 0 && t < len[k]) {
-      const float* G = p.gates + ((int64_t)l * p.T + t) * 4 * BH + (int64_t)b * 4 * H + unit0;
-      gi[k] = ls_ld4(G, n, vec);
-      gf[k] = ls_ld4(G + H, n, vec);
-      gg[k] = ls_ld4(G + 2 * (int64_t)H, n, vec);
-      go[k] = ls_ld4(G + 3 * (int64_t)H, n, vec);
-      const float* cs = p.cs + ((int64_t)l * (p.T + 1) + t) * BH + idx;
-      cp[k] = ls_ld4(cs, n, vec);
-      cn[k] = ls_ld4(cs + BH, n, vec);
-      if (top) dy[k] = ls_ld4(p.dy + (int64_t)t * BH + idx, n, vec);
-    }
+    const int bs = b < B ? b : B - 1, us = unit0 < H ? unit0 : (H - 1) & ~3, n = H - us;
+    const int64_t idx = (int64_t)bs * H + us;
+    const float* G = p.gates + ((int64_t)l * p.T + tc0) * 4 * BH + (int64_t)bs * 4 * H + us;
+    len[k] = p.lengths[bs];
+    gi[k] = ls_ld4<VEC>(G, n);
+    gf[k] = ls_ld4<VEC>(G + H, n);
+    gg[k] = ls_ld4<VEC>(G + 2 * (int64_t)H, n);
+    go[k] = ls_ld4<VEC>(G + 3 * (int64_t)H, n);
+    cp[k] = ls_ld4<VEC>(cs_t + idx, n);
+    cn[k] = ls_ld4<VEC>(cs_t + BH + idx, n);
+    dy[k] = ls_ld4<VEC>(dy_src + idx, n);
+    dcs[k] = ls_ld4<VEC>(dc_src + idx, n);
+    carried[k] = ls_ld4<VEC>(dh_src + idx, n);
   }
 
   acc_t acc[2][NI][NJ];   // own state, output
@@ -414,9 +461,9 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_bwd_kernel(LsBwd p, int d,
   const int ng = 4 * ls_gate_stride<TE>(H) / KST;
   const int n0 = t + 1 < p.T ? ng : 0, n1 = !top && t >= 0 ? ng : 0;
   if (n0 + n1 > 0) {
-    const int64_t cstep = (int64_t)nct * kLsTile, wstep = (int64_t)((H + 63) / 64 * 4) * kLsTile;   // ls_unit_tiles
-    const char* w0 = p.WT_hh[l] + u0 / 16 * kLsTile;
-    const char* w1 = p.WT_up[l] + u0 / 16 * kLsTile;
+    const int64_t cstep = (int64_t)nct * kLsTile, wrow = ng * kLsTile;
+    const char* w0 = p.WT_hh[l] + u0 / 16 * wrow;
+    const char* w1 = p.WT_up[l] + u0 / 16 * wrow;
     const char* g0 = p.dGF + (2 * l + ((t + 1) & 1)) * p.g_stride;
     const char* g1 = p.dGF + (2 * (l + 1) + (t & 1)) * p.g_stride;
     int64_t ctoff[NJ];
@@ -426,30 +473,42 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_bwd_kernel(LsBwd p, int d,
       ctoff[j] = (ct < nct ? ct : nct - 1) * kLsTile;
     }
     ls_u32x4_t wf[PF][NI], df[PF][NJ];
-    auto load = [&](int slot, int s) {
-      const bool in = s >= n0;
-      const int k = in ? s - n0 : s;
-      const char* wb = (in ? w1 : w0) + k * wstep + lane * 16;
+    auto fetch = [&](int slot, bool in, int k) {
+      const char* wb = (in ? w1 : w0) + k * kLsTile;
 #pragma unroll
-      for (int i = 0; i < NI; ++i) wf[slot][i] = *reinterpret_cast<const ls_u32x4_t*>(wb + i * kLsTile);
-      const char* gb = (in ? g1 : g0) + k * cstep + lane * 16;
+      for (int i = 0; i < NI; ++i) wf[slot][i] = ls_frag(wb + i * wrow, lane16);
+      const char* gb = (in ? g1 : g0) + k * cstep;
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) df[slot][j] = *reinterpret_cast<const ls_u32x4_t*>(gb + ctoff[j]);
+      for (int j = 0; j < NJ; ++j) df[slot][j] = ls_frag(gb + ctoff[j], lane16);
     };
-    auto mul = [&](int slot, int s) {
-      if (s < n0) {
+    auto add = [&](int slot, int sum) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) M::mma(acc[sum][i][j], wf[slot][i], df[slot][j]);
+    };
+    // Both sums: their steps alternate, so that the slot says which sum a step belongs to (PF is even).
+    constexpr int NL = NI + NJ, NM = M::kPair ? NI * NJ : 4 * NI * NJ;
+    const int own = ls_own_steps(ng, wave);
+    if (n0 > 0 && n1 > 0) {
+      ls_reduce<PF, NL, NM>(
+          2 * own, [&](int slot, int i) { fetch(slot, (i & 1) != 0, wave + (i >> 1) * LS_KS); },
+          [&](int slot, int) { add(slot, slot & 1); });
+    } else {
+      const bool in = n0 == 0;
+      ls_reduce<PF, NL, NM>(
+          own, [&](int slot, int i) { fetch(slot, in, wave + i * LS_KS); }, [&](int slot, int) { add(slot, 0); });
+      if (in) {
 #pragma unroll
         for (int i = 0; i < NI; ++i)
 #pragma unroll
-          for (int j = 0; j < NJ; ++j) M::mma(acc[0][i][j], wf[slot][i], df[slot][j]);
-      } else {
+          for (int j = 0; j < NJ; ++j) {
+            acc[1][i][j] = acc[0][i][j];
 #pragma unroll
-        for (int i = 0; i < NI; ++i)
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) M::mma(acc[1][i][j], wf[slot][i], df[slot][j]);
+            for (int r = 0; r < 4; ++r) acc[0][i][j][r] = 0;
+          }
       }
-    };
-    ls_reduce<PF>(n0 + n1, wave, load, mul);
+    }
   }
 #pragma unroll
   for (int s = 0; s < 2; ++s)
@@ -476,11 +535,17 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_bwd_kernel(LsBwd p, int d,
 #pragma unroll
       for (int e = 0; e < 4; ++e) sum[s][e] = (float)v[e];
     }
+    len[k] = len[k] < 0 ? 0 : (len[k] > p.T ? p.T : len[k]);
     f32x4_t dh;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (!dc_in) dcs[k][e] = 0.f;
+      if (!p.dhT) carried[k][e] = 0.f;
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) dh[e] = t + 1 < len[k] ? sum[0][e] : carried[k][e];
     if (t < 0) {
-      if (b < B) ls_st4(p.dh0 + l * BH + idx, dh, n, vec);
+      if (b < B) ls_st4<VEC>(p.dh0 + l * BH + idx, dh, n);
       continue;
     }
     f32x4_t da[4];
@@ -489,8 +554,8 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_bwd_kernel(LsBwd p, int d,
       if (!top) {
         dy[k] = sum[1];
         if (p.drop_thr) {   // back through the mask the forward step put on this layer's output
-          const f32x4_t m = ls_drop4(((uint64_t)l * p.T + t) * (uint64_t)BH + (uint64_t)idx, p.drop_seed, p.drop_thr,
-                                     p.drop_scale, vec);
+          const f32x4_t m = ls_drop4<VEC>(((uint64_t)l * p.T + t) * (uint64_t)BH + (uint64_t)idx, p.drop_seed, p.drop_thr,
+                                     p.drop_scale);
 #pragma unroll
           for (int e = 0; e < 4; ++e) dy[k][e] = m[e] != 0.f ? dy[k][e] * m[e] : 0.f;
         }
@@ -506,7 +571,7 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_bwd_kernel(LsBwd p, int d,
         da[3][e] = dd * tc * go[k][e] * (1.f - go[k][e]);
         dcs[k][e] = dc * gf[k][e];
       }
-      if (!vec) {   // units past H: reduction padding of the products that read these, kept zero
+      if constexpr (!VEC) {   // units past H: reduction padding of the products that read these, kept zero
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           if (e >= n) da[0][e] = da[1][e] = da[2][e] = da[3][e] = 0.f;
@@ -518,13 +583,13 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_bwd_kernel(LsBwd p, int d,
         for (int e = 0; e < 4; ++e) da[g][e] = 0.f;
     }
     if (b < B) {
-      ls_st4(p.dcs + l * BH + idx, dcs[k], n, vec);
+      ls_st4<VEC>(p.dcs + l * BH + idx, dcs[k], n);
       TE* dG = reinterpret_cast<TE*>(p.dG) + ((int64_t)l * p.T + t) * 4 * BH + (int64_t)b * 4 * H + unit0;
       TE* dGF = reinterpret_cast<TE*>(p.dGF + (2 * l + (t & 1)) * p.g_stride);
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        ls_st4(dG + (int64_t)g * H, da[g], n, vec);
-        ls_st4(dGF + ls_tile_off<TE>(g * GS + unit0, b, nct), da[g], 4, true);
+        ls_st4<VEC>(dG + (int64_t)g * H, da[g], n);
+        ls_st4<true>(dGF + ls_tile_off<TE>(g * GS + unit0, b, nct), da[g], 4);
       }
     }
     // bias gradient: sums over the tile's sentences, added up over the steps in an accumulator of the tile's own
@@ -541,8 +606,8 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_bwd_kernel(LsBwd p, int d,
       const f32x4_t mine = c == 0 ? da[0] : c == 1 ? da[1] : c == 2 ? da[2] : da[3];
       float* acc_p = p.dbacc + ((int64_t)l * nct + (b0 >> 4) + j) * 4 * H + (int64_t)c * H + unit0;
       f32x4_t old = {0.f, 0.f, 0.f, 0.f};
-      if (t + 1 < p.T) old = ls_ld4(acc_p, n, vec);
-      ls_st4(acc_p, old + mine, n, vec);
+      if (t + 1 < p.T) old = ls_ld4<VEC>(acc_p, n);
+      ls_st4<VEC>(acc_p, old + mine, n);
     }
   }
 }
@@ -630,11 +695,13 @@ __global__ __launch_bounds__(256) void ls_prep_fwd_kernel(LsFwd p, LsPrepFwd s) 
     const int K = hh || l > 0 ? H : p.I, ntw = (H + 31) / 32 * 8;
     const TE* W = reinterpret_cast<const TE*>(hh ? s.W_hh[l] : s.W_ih[l]);
     char* dst = reinterpret_cast<char*>(const_cast<void*>(hh ? p.W_hh[l] : p.W_ih[l]));
-    const int64_t n = (int64_t)((K + KST - 1) / KST) * ntw * 64;
+    const int nks = (K + KST - 1) / KST;
+    const int64_t n = (int64_t)nks * ntw * 64;
     for (int64_t i = first; i < n; i += stride) {
       const int64_t tile = i >> 6;
-      const int lane = (int)(i & 63), k = (int)(tile / ntw) * KST + (lane >> 4) * V, rt = (int)(tile % ntw);
-      const int unit = 16 * (rt >> 2) + 4 * M::q_of_row(lane & 15) + (rt & 3), gate = M::r_of_row(lane & 15);
+      const int lane = (int)(i & 63), k = (int)((tile >> 2) % nks) * KST + (lane >> 4) * V;
+      const int ug = (int)((tile >> 2) / nks), ii = (int)(tile & 3);
+      const int unit = 16 * ug + 4 * M::q_of_row(lane & 15) + ii, gate = M::r_of_row(lane & 15);
       const bool in = unit < H && k < K;
       ls_copy_chunk<TE>(dst + i * 16, W + ((int64_t)gate * H + (in ? unit : 0)) * K + (in ? k : 0), in ? K - k : 0);
     }
@@ -651,11 +718,12 @@ __global__ __launch_bounds__(256) void ls_prep_bwd_kernel(LsBwd p, LsPrepBwd s) 
   const TE* W = reinterpret_cast<const TE*>(job < L ? s.W_hh[l] : s.W_ih[l + 1]);
   char* dst = const_cast<char*>(job < L ? p.WT_hh[l] : p.WT_up[l]);
   const int GS = ls_gate_stride<TE>(H), ntu = (H + 63) / 64 * 4;
-  const int64_t n = (int64_t)(4 * GS / KST) * ntu * 64;
+  const int nks = 4 * GS / KST;
+  const int64_t n = (int64_t)nks * ntu * 64;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
     const int64_t tile = i >> 6;
-    const int lane = (int)(i & 63), rho = lane & 15, k = (int)(tile / ntu) * KST + (lane >> 4) * V;
-    const int unit = 16 * (int)(tile % ntu) + 4 * M::q_of_row(rho) + M::r_of_row(rho);
+    const int lane = (int)(i & 63), rho = lane & 15, k = (int)(tile % nks) * KST + (lane >> 4) * V;
+    const int unit = 16 * (int)(tile / nks) + 4 * M::q_of_row(rho) + M::r_of_row(rho);
     const int gate = k / GS, u = k - gate * GS;   // GS % V == 0: a chunk lies inside one gate
     TE v[V];
 #pragma unroll
@@ -713,16 +781,22 @@ hipError_t launch_ls_bias_reduce(const float* dbacc, const LsBiasOut& o, int L, 
 template <typename TE, int NI, int NJ, int PF>
 static hipError_t ls_fwd_shape(const LsFwd& p, int d, int l_lo, int nl, hipStream_t st) {
   const unsigned grid = ls_grid((int64_t)nl * ((p.H + 4 * NI - 1) / (4 * NI)), (p.B + 16 * NJ - 1) / (16 * NJ));
-  if (p.w_rows)
-    hipLaunchKernelGGL((ls_wave_fwd_kernel<TE, NI, NJ, PF, true>), dim3(grid), dim3(64 * LS_KS), 0, st, p, d, l_lo, nl);
-  else
-    hipLaunchKernelGGL((ls_wave_fwd_kernel<TE, NI, NJ, PF, false>), dim3(grid), dim3(64 * LS_KS), 0, st, p, d, l_lo, nl);
+#define ASX_FWD(ROWS, VEC) \
+  hipLaunchKernelGGL((ls_wave_fwd_kernel<TE, NI, NJ, PF, ROWS, VEC>), dim3(grid), dim3(64 * LS_KS), 0, st, p, d, l_lo, nl)
+  if (p.w_rows) ASX_FWD(true, true);   // widths are multiples of 4
+  else if (LsMma<TE>::kPair || p.H % 4 == 0) ASX_FWD(false, true);
+  else ASX_FWD(false, LsMma<TE>::kPair);
+#undef ASX_FWD
   return hipGetLastError();
 }
 template <typename TE, int NI, int NJ, int PF>
 static hipError_t ls_bwd_shape(const LsBwd& p, int d, int l_lo, int nl, hipStream_t st) {
   const unsigned grid = ls_grid((int64_t)nl * ((p.H + 16 * NI - 1) / (16 * NI)), (p.B + 16 * NJ - 1) / (16 * NJ));
-  hipLaunchKernelGGL((ls_wave_bwd_kernel<TE, NI, NJ, PF>), dim3(grid), dim3(64 * LS_KS), 0, st, p, d, l_lo, nl);
+  if (LsMma<TE>::kPair || p.H % 4 == 0)
+    hipLaunchKernelGGL((ls_wave_bwd_kernel<TE, NI, NJ, PF, true>), dim3(grid), dim3(64 * LS_KS), 0, st, p, d, l_lo, nl);
+  else
+    hipLaunchKernelGGL((ls_wave_bwd_kernel<TE, NI, NJ, PF, LsMma<TE>::kPair>), dim3(grid), dim3(64 * LS_KS), 0, st, p, d,
+                       l_lo, nl);
   return hipGetLastError();
 }
 
