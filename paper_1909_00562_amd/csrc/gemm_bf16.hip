@@ -28,86 +28,11 @@
 // global stores are 8/16-byte vectors along rows.
 #include "common.h"
 #include "gemm.h"
+#include "gemm_dev.h"
 
 #include <type_traits>
 
 namespace asx {
-
-struct GemmDev {
-  const uint16_t* A[kMaxSeg];
-  const uint16_t* B[kMaxSeg];
-  int64_t lda[kMaxSeg], ldb[kMaxSeg], sA[kMaxSeg], sB[kMaxSeg];
-  int K[kMaxSeg];
-  int M, N;
-  void* C;
-  uint16_t* C_lo;
-  float* C_dact;
-  int64_t ldc, sC;
-  const uint16_t* bias;
-  const float* gate;
-  int64_t ldg;
-  int act_tanh, accumulate;
-  uint32_t drop_thr;
-  float drop_scale;
-  uint64_t drop_seed;
-  int splits;
-  float* partial;
-  int tiles_m, tiles_n;
-  int group;   // tile rows per group of the persistent kernel's tile walk
-  int kper;    // reduction elements per split, multiple of 64
-  int vec_ok;  // rows of C (and C_lo, C_dact, gate) allow 8/16-byte vector access
-  const int32_t* M_dev;   // device-side row count (or null): min(*M_dev, M) rows are valid
-  const int32_t* K_dev;   // device-side reduction length of segment 0 (or null)
-  int nz;                 // batch * splits
-  int dyn_split;          // splits is the bound of a split chosen in the kernel from the row count (pp kernel)
-};
-
-// size made by an earlier kernel of the stream, clamped to the bound the launch was sized for
-__device__ __forceinline__ int dev_bound(const int32_t* count, int bound) {
-  if (!count) return bound;
-  const int v = *count;
-  return v < 0 ? 0 : (v < bound ? v : bound);
-}
-
-constexpr int BK = 64;                  // reduction elements per LDS tile row
-constexpr int ROWB = BK * 2;            // bytes per LDS tile row
-constexpr uint32_t kOob = 0x80000000u;  // offset outside every buffer resource below
-
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) void lds_void_t;
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base) {
-  // raw buffer, 2 GiB range: offsets >= 2^31 (kOob) read as zero
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x7fffffff, 0x00020000);
-}
-
-// ---- reduction-contiguous operand: HBM -> LDS, no registers ----------------------
-// The tile's ROWS rows are split into groups of 8 rows (1 KiB of LDS); one wave-wide
-// 16-byte load fills one group.  Per-lane byte offsets relative to element
-// (row0, k0) are computed once per kernel; rows beyond the operand get kOob.
-template <int ROWS, int NW>
-struct DirectLoader {
-  static constexpr int NL = ROWS / 8 / NW;   // loads per wave and tile
-  uint32_t voff[NL];
-  int chunk8;                                // first reduction element of this lane's chunk
-  __device__ __forceinline__ void init(int64_t ld, int rows_left, int wave, int lane) {
-    static_assert(NW % 2 == 0, "swizzle below assumes the parity of the row group is the wave's");
-    const int rl = lane >> 3;                        // row inside the group
-    const int chunk = (lane & 7) ^ rl ^ (wave & 1);  // logical 16-byte chunk that belongs in LDS slot `lane`
-    chunk8 = chunk * 8;
-#pragma unroll
-    for (int j = 0; j < NL; ++j) {
-      const int r = (wave + NW * j) * 8 + rl;
-      voff[j] = r < rows_left ? (uint32_t)(((int64_t)r * ld + chunk * 8) * 2) : kOob;
-    }
-  }
-  // X points at element (row0, k0); k_left = reduction elements left from k0
-  __device__ __forceinline__ void load(int j, const __amdgpu_buffer_rsrc_t& rs, int k_left, unsigned char* lds_tile,
-                                       int wave) const {
-    const uint32_t off = chunk8 < k_left ? voff[j] : kOob;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(lds_tile + (wave + NW * j) * 1024), 16, off, 0, 0, 0);
-  }
-};
 
 // ---- strided-reduction operand: HBM -> registers -> transposed into LDS --------------
 // Thread t owns rows (t/16)*8 .. +7 (contiguous index) x reduction rows (t%16)*4 .. +3.
@@ -164,7 +89,6 @@ __device__ __forceinline__ bf16x8_t frag_read(const unsigned char* base, int row
 // row), so the global accesses are row-contiguous.  row0 / col0: first row / column
 // of this wave's tile in C.
 // `region` is this wave's private LDS slice: CH rows of EP_LD floats (CH = 32 or 16).
-typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 
 // Accumulators of one round (CH rows of the wave tile) -> the wave's staging slice.
 // MI16 = false: 32x32 MFMA tiles (register r of lane l: row 8*(r/4) + 4*(l/32) + r%4, column l%32).
@@ -661,8 +585,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_kernel(GemmDev p) {
 constexpr int PTILE = 256 * BK * 2;   // bytes of one operand tile
 constexpr int PSTAGE = 2 * PTILE;
 
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
 
 // wave-wide direct loads of one operand tile: 32 loads of 1 KiB per tile, NL = 32 / NW per wave
 template <bool KC, int NW = 8>
@@ -732,7 +654,7 @@ __device__ __forceinline__ bf16x8_t pp_frag_at(const unsigned char* tile, uint32
     union { s16x4_t h[2]; bf16x8_t v; } u;
 #pragma unroll
     for (int q = 0; q < 2; ++q)
-      u.h[q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+      u.h[q] = lds_read_tr(
           (lds_s16x4_t*)(lds_void_t*)(tile + base + kk * 8192 + q * 2048));
     return u.v;
   }
@@ -764,7 +686,7 @@ __device__ __forceinline__ bf16x8_t pp16_frag_at(const unsigned char* tile, uint
     union { s16x4_t h[2]; bf16x8_t v; } u;
 #pragma unroll
     for (int q = 0; q < 2; ++q)
-      u.h[q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+      u.h[q] = lds_read_tr(
           (lds_s16x4_t*)(lds_void_t*)(tile + base + ks * 16384 + q * 2048));
     return u.v;
   }

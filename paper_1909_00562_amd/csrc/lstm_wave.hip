@@ -19,6 +19,7 @@
 //   * fp32 storage: fp64 matrix instructions on operands widened after the load, as in gemm_f32.hip.
 #include "common.h"
 #include "lstm_wave.h"
+#include "wave_pipe.h"
 
 namespace asx {
 
@@ -146,49 +147,6 @@ __device__ __forceinline__ bool ls_block_of(int nslices, int nbt, int& slice, in
 }
 static inline unsigned ls_grid(int64_t nslices, int64_t nbt) { return (unsigned)((nslices + 7) / 8 * 8 * nbt); }
 
-// steps w, w + LS_KS, ... of a list of nsteps
-__device__ __forceinline__ int ls_own_steps(int nsteps, int wave) {
-  return nsteps > wave ? (nsteps - wave + LS_KS - 1) / LS_KS : 0;
-}
-
-// schedule of a region: load v of NL after (v + 1) / NL of its NM matrix instructions
-template <int v, int NL, int NM> __device__ __forceinline__ void ls_spread() {
-  if constexpr (v < NL) {
-    constexpr int nm = (v + 1) * NM / NL - v * NM / NL;
-    if constexpr (nm > 0) __builtin_amdgcn_sched_group_barrier(0x008, nm, 0);
-    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-    ls_spread<v + 1, NL, NM>();
-  }
-}
-
-// A wave's n reduction steps, slot i % PF of the fragment registers holding step i.  load(slot, i) must be free of
-// branches and valid for 0 <= i < n; past the last step it is called with the last one again, so that the number of
-// loads in flight is the same on every path and a wait covers just the fragments it needs.
-// The NL loads of a step are spread over the NM matrix instructions of an earlier one.  Issued in one run they hold the
-// wave at the address unit while its matrix pipe idles: forward wavefronts of 4 layers x 1024 units x 128 sentences
-// then took the sum of their load and matrix times.
-template <int PF, int NL, int NM, typename Load, typename Mul>
-__device__ __forceinline__ void ls_reduce(int n, Load load, Mul mul) {
-  if (n <= 0) return;
-  auto at = [&](int i) { return i < n ? i : n - 1; };
-#pragma unroll
-  for (int u = 0; u + 1 < PF; ++u) load(u, at(u));
-  __builtin_amdgcn_sched_barrier(0);
-  int i = 0;
-  for (; i + PF <= n; i += PF) {
-#pragma unroll
-    for (int u = 0; u < PF; ++u) {
-      mul(u, at(i + u));
-      load((u + PF - 1) % PF, at(i + u + PF - 1));
-      ls_spread<0, NL, NM>();
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-#pragma unroll
-  for (int u = 0; u + 1 < PF; ++u)
-    if (i + u < n) mul(u, at(i + u));
-}
-
 // ---- forward ---------------------------------------------------------------------
 // Block: 16 * NI gate rows (4 * NI hidden units) x 16 * NJ sentences.  Tile 4 g + ii of a block, row rho: unit
 // u0 + 16 g + 4 q + ii, gate r, (q, r) = the lane group and register that hold row rho.  ROWS: weights are read as the
@@ -310,7 +268,7 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
     }
   };
   constexpr int NP = M::kPair ? 2 : 1, NM = M::kPair ? 2 * NI * NJ : 4 * NI * NJ;
-  ls_reduce<PF, NI + NP * NJ, NM>(ls_own_steps(n0 + n1, wave), load, mul);
+  wave_reduce<PF, NI + NP * NJ, NM>(own_steps<LS_KS>(n0 + n1, wave), load, mul);
 
 #pragma unroll
   for (int i = 0; i < NI; ++i)
@@ -489,14 +447,14 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_bwd_kernel(LsBwd p, int d,
     };
     // Both sums: their steps alternate, so that the slot says which sum a step belongs to (PF is even).
     constexpr int NL = NI + NJ, NM = M::kPair ? NI * NJ : 4 * NI * NJ;
-    const int own = ls_own_steps(ng, wave);
+    const int own = own_steps<LS_KS>(ng, wave);
     if (n0 > 0 && n1 > 0) {
-      ls_reduce<PF, NL, NM>(
+      wave_reduce<PF, NL, NM>(
           2 * own, [&](int slot, int i) { fetch(slot, (i & 1) != 0, wave + (i >> 1) * LS_KS); },
           [&](int slot, int) { add(slot, slot & 1); });
     } else {
       const bool in = n0 == 0;
-      ls_reduce<PF, NL, NM>(
+      wave_reduce<PF, NL, NM>(
           own, [&](int slot, int i) { fetch(slot, in, wave + i * LS_KS); }, [&](int slot, int) { add(slot, 0); });
       if (in) {
 #pragma unroll
