@@ -133,26 +133,26 @@ Layout make_layout(const as_shape* s) {
   L.rb = xent_rows_per_block(N, V, bf);
   L.nrb = (N + L.rb - 1) / L.rb;
 
-  L.p_q = gemm_plan(N, H, H, 1, bf, false);
-  L.p_score = gemm_plan(T, S, H, B, bf, false);
-  L.p_ctx = gemm_plan(T, H, S, B, bf, false);
+  L.p_q = gemm_plan(kFormNN, N, H, H, 1, bf, false);
+  L.p_score = gemm_plan(kFormNT, T, S, H, B, bf, false);
+  L.p_ctx = gemm_plan(kFormNN, T, H, S, B, bf, false);
   // Segments: ctx (+ remainder), h_dec.  Each segment is cut into reduction tiles of its own, so the length to plan a
   // split for counts whole tiles per segment: planned over 3 * H, sizes like H = 584 got a split with no tiles left.
-  L.p_hc = gemm_plan(N, H, bf ? 3 * (int)up(H, 64) : 2 * H, 1, bf, true, true);
-  L.p_logits = gemm_plan(N, V, H, 1, bf, false);
-  L.p_dwout = gemm_plan(V, H, N, 1, bf, true);
-  L.p_dhc = gemm_plan(N, H, V, 1, bf, true);
+  L.p_hc = gemm_plan(kFormNT, N, H, bf ? 3 * (int)up(H, 64) : 2 * H, 1, bf, true, true);
+  L.p_logits = gemm_plan(kFormNT, N, V, H, 1, bf, false);
+  L.p_dwout = gemm_plan(kFormTN, V, H, N, 1, bf, true);
+  L.p_dhc = gemm_plan(kFormNN, N, H, V, 1, bf, true);
   // Few, long work items (N/256 x H/256 tiles, reduction over V): once the padding rows are gone the item count
   // no longer fills whole rounds of the grid, so the kernel splits the reduction to fit the count it reads.
-  L.dhc_dyn = s->skip_pad_rows != 0 && bf && L.p_dhc.big_tile;
+  L.dhc_dyn = s->skip_pad_rows != 0 && bf && L.p_dhc.tile == kTile256;
   if (L.dhc_dyn && L.p_dhc.splits < 8) L.p_dhc.splits = 8;
-  L.p_dwc = gemm_plan(H, H, N, 2, bf, true);          // both halves of dW_c in one launch
-  L.p_dch = gemm_plan(N, H, H, 1, bf, false);
-  L.p_dalpha = gemm_plan(T, S, H, B, bf, false);
-  L.p_dq = gemm_plan(T, H, S, B, bf, false);
-  L.p_ds = gemm_plan(S, H, T, B, bf, false);
-  L.p_dwa = gemm_plan(H, H, N, 1, bf, true);
-  L.p_dh = gemm_plan(N, H, H, 1, bf, false);
+  L.p_dwc = gemm_plan(kFormTN, H, H, N, 2, bf, true);          // both halves of dW_c in one launch
+  L.p_dch = gemm_plan(kFormNN, N, H, H, 1, bf, false);
+  L.p_dalpha = gemm_plan(kFormNT, T, S, H, B, bf, false);
+  L.p_dq = gemm_plan(kFormNN, T, H, S, B, bf, false);
+  L.p_ds = gemm_plan(kFormTN, S, H, T, B, bf, false);
+  L.p_dwa = gemm_plan(kFormTN, H, H, N, 1, bf, true);
+  L.p_dh = gemm_plan(kFormNT, N, H, H, 1, bf, false);
   size_t pb = 0;
   auto mx = [&](size_t v) { if (v > pb) pb = v; };
   mx(gemm_partial_bytes(N, H, 1, L.p_hc.splits));
@@ -294,7 +294,7 @@ static as_status fwd_from_ctx(const as_shape* s, const Layout& L, char* w, const
       g.drop_scale = 1.f / (1.f - s->dropout_p);
       g.drop_seed = s->dropout_seed;
     }
-    AS_TRY(AS_STAGE_GEMM_HC, launch_gemm(g, bf, L.p_hc.big_tile, st));
+    AS_TRY(AS_STAGE_GEMM_HC, launch_gemm(g, bf, L.p_hc.tile, st));
   }
   // Padding rows drop out of Eq. 5-6 here: the rows of h_c (and of its saved derivative) whose target is a
   // word are gathered into a dense block, and everything over the vocabulary runs on that block alone.
@@ -316,7 +316,7 @@ static as_status fwd_from_ctx(const as_shape* s, const Layout& L, char* w, const
     g.M = N; g.N = V; g.bias = b_out;
     g.M_dev = n_act;
     g.C = w + L.logits; g.ldc = L.ldV; g.c_bf16 = bf;
-    AS_TRY(AS_STAGE_GEMM_LOGITS, launch_gemm(g, bf, L.p_logits.big_tile, st));
+    AS_TRY(AS_STAGE_GEMM_LOGITS, launch_gemm(g, bf, L.p_logits.tile, st));
   }
   AS_TRY(AS_STAGE_XENT_STATS,                                          // Eq. 5-6
          launch_xent_stats(w + L.logits, L.ldV, bf, N, V, targets, s->pad_id, reinterpret_cast<float*>(w + L.lse),
@@ -426,7 +426,7 @@ static as_status fwd_impl(const as_shape* s, const void* h_dec, const void* h_en
     g.M = N; g.N = H;
     g.C = w + L.q; g.ldc = H; g.c_bf16 = bf;
     g.C_lo = w + L.q_lo;
-    AS_TRY(AS_STAGE_GEMM_Q, launch_gemm(g, bf, L.p_q.big_tile, st));
+    AS_TRY(AS_STAGE_GEMM_Q, launch_gemm(g, bf, L.p_q.tile, st));
   }
   if (bf && attn_fwd_fused_supported(S, H)) {
     // Eq. 2 (second half), 1 and 3 in one kernel per (sentence, 32 decoder steps): the scores stay on chip
@@ -441,7 +441,7 @@ static as_status fwd_impl(const as_shape* s, const void* h_dec, const void* h_en
       g.a_kc = true; g.b_kc = true;
       g.M = T; g.N = S; g.batch = B;
       g.C = w + L.scores; g.ldc = S; g.sC = (int64_t)T * S; g.c_bf16 = false;
-      AS_TRY(AS_STAGE_ATTN_SCORE, launch_gemm(g, bf, L.p_score.big_tile, st));
+      AS_TRY(AS_STAGE_ATTN_SCORE, launch_gemm(g, bf, L.p_score.tile, st));
     }
     AS_TRY(AS_STAGE_ATTN_SOFTMAX,                                        // Eq. 1
            launch_attn_softmax_rows(reinterpret_cast<const float*>(w + L.scores), src_len, B, T, S,
@@ -455,7 +455,7 @@ static as_status fwd_impl(const as_shape* s, const void* h_dec, const void* h_en
       g.M = T; g.N = H; g.batch = B;
       g.C = w + L.ctx; g.ldc = BH; g.sC = H; g.c_bf16 = bf;
       g.C_lo = w + L.ctx_lo;
-      AS_TRY(AS_STAGE_ATTN_CTX, launch_gemm(g, bf, L.p_ctx.big_tile, st));
+      AS_TRY(AS_STAGE_ATTN_CTX, launch_gemm(g, bf, L.p_ctx.tile, st));
     }
   }
   return fwd_from_ctx(s, L, w, hd, wc, W_out, b_out, targets, loss_sum, n_tok, tok_loss, argmax, tgt_mask, st);
@@ -503,7 +503,7 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
     g.K_dev = n_act;     // compacted: the reduction runs over the non-pad rows only
     g.C = dW_out; g.ldc = H; g.c_bf16 = false;
     g.splits = L.p_dwout.splits; g.partial = partial;
-    AS_TRY(AS_STAGE_GEMM_DWOUT, launch_gemm(g, bf, L.p_dwout.big_tile, st));
+    AS_TRY(AS_STAGE_GEMM_DWOUT, launch_gemm(g, bf, L.p_dwout.tile, st));
   }
   {  // dz = (dlogits W_out) * (1 - h_c^2), the factor saved by the forward pass
     GemmArgs g;
@@ -516,7 +516,7 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
     g.M_dev = n_act;
     g.dyn_split = L.dhc_dyn;
     g.splits = L.p_dhc.splits; g.partial = partial;
-    AS_TRY(AS_STAGE_GEMM_DHC, launch_gemm(g, bf, L.p_dhc.big_tile, st));
+    AS_TRY(AS_STAGE_GEMM_DHC, launch_gemm(g, bf, L.p_dhc.tile, st));
   }
   if (L.compact)   // dz back to its time-major rows, zeros at the padding rows: the rest of the pass is per sentence
     AS_TRY(AS_STAGE_COMPACT, launch_scatter_rows(reinterpret_cast<const int32_t*>(w + L.row_pos), N, w + L.dz_c,
@@ -531,7 +531,7 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
     g.M = H; g.N = H; g.batch = 2;
     g.C = dW_c; g.ldc = 2 * H; g.sC = H; g.c_bf16 = false;
     g.splits = L.p_dwc.splits; g.partial = partial;
-    AS_TRY(AS_STAGE_GEMM_DWC, launch_gemm(g, bf, L.p_dwc.big_tile, st));
+    AS_TRY(AS_STAGE_GEMM_DWC, launch_gemm(g, bf, L.p_dwc.tile, st));
   }
   {  // dC = dz W_c[:, :H]
     GemmArgs g;
@@ -541,7 +541,7 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
     g.M = N; g.N = H;
     g.C = w + L.dC; g.ldc = H; g.c_bf16 = bf;
     g.C_lo = w + L.dC_lo;
-    AS_TRY(AS_STAGE_GEMM_DCH, launch_gemm(g, bf, L.p_dch.big_tile, st));
+    AS_TRY(AS_STAGE_GEMM_DCH, launch_gemm(g, bf, L.p_dch.tile, st));
   }
   {  // dH1 = dz W_c[:, H:]  -> d_h_dec
     GemmArgs g;
@@ -549,7 +549,7 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
     g.a_kc = true; g.b_kc = false;
     g.M = N; g.N = H;
     g.C = d_h_dec; g.ldc = H; g.c_bf16 = false;
-    AS_TRY(AS_STAGE_GEMM_DCH, launch_gemm(g, bf, L.p_dch.big_tile, st));
+    AS_TRY(AS_STAGE_GEMM_DCH, launch_gemm(g, bf, L.p_dch.tile, st));
   }
   if (bf && attn_fwd_fused_supported(S, H)) {
     // dalpha, the softmax Jacobian and dQ in one kernel per (sentence, 32 decoder steps): dalpha stays on chip
@@ -565,7 +565,7 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
       g.a_kc = true; g.b_kc = true;
       g.M = T; g.N = S; g.batch = B;
       g.C = w + L.dalpha; g.ldc = S; g.sC = (int64_t)T * S; g.c_bf16 = false;
-      AS_TRY(AS_STAGE_ATTN_BWD, launch_gemm(g, bf, L.p_dalpha.big_tile, st));
+      AS_TRY(AS_STAGE_ATTN_BWD, launch_gemm(g, bf, L.p_dalpha.tile, st));
     }
     AS_TRY(AS_STAGE_ATTN_SOFTMAX_BWD,
            launch_attn_softmax_rows_bwd(reinterpret_cast<const float*>(w + L.alpha32),
@@ -578,7 +578,7 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
       g.a_kc = true; g.b_kc = false;
       g.M = T; g.N = H; g.batch = B;
       g.C = w + L.dQ; g.ldc = BH; g.sC = H; g.c_bf16 = bf;
-      AS_TRY(AS_STAGE_ATTN_BWD, launch_gemm(g, bf, L.p_dq.big_tile, st));
+      AS_TRY(AS_STAGE_ATTN_BWD, launch_gemm(g, bf, L.p_dq.tile, st));
     }
   }
   {  // d_h_enc_b = alpha_b^T dC_b + dscore_b^T Q_b  (rows s >= src_len[b]: alpha = dscore = 0)
@@ -594,7 +594,7 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
     g.a_kc = false; g.b_kc = false;
     g.M = S; g.N = H; g.batch = B;
     g.C = d_h_enc; g.ldc = BH; g.sC = H; g.c_bf16 = false;
-    AS_TRY(AS_STAGE_ATTN_BWD, launch_gemm(g, bf, L.p_ds.big_tile, st));
+    AS_TRY(AS_STAGE_ATTN_BWD, launch_gemm(g, bf, L.p_ds.tile, st));
   }
   {  // dW_a = h_dec^T dQ
     GemmArgs g;
@@ -603,7 +603,7 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
     g.M = H; g.N = H;
     g.C = dW_a; g.ldc = H; g.c_bf16 = false;
     g.splits = L.p_dwa.splits; g.partial = partial;
-    AS_TRY(AS_STAGE_GEMM_DWA, launch_gemm(g, bf, L.p_dwa.big_tile, st));
+    AS_TRY(AS_STAGE_GEMM_DWA, launch_gemm(g, bf, L.p_dwa.tile, st));
   }
   {  // d_h_dec += dQ W_a^T
     GemmArgs g;
@@ -611,7 +611,7 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
     g.a_kc = true; g.b_kc = true;
     g.M = N; g.N = H;
     g.C = d_h_dec; g.ldc = H; g.c_bf16 = false; g.accumulate = 1;
-    AS_TRY(AS_STAGE_GEMM_DH, launch_gemm(g, bf, L.p_dh.big_tile, st));
+    AS_TRY(AS_STAGE_GEMM_DH, launch_gemm(g, bf, L.p_dh.tile, st));
   }
   return AS_OK;
 }
@@ -631,7 +631,7 @@ StepLayout make_step_layout(const as_shape* s) {
   sl.L = make_layout(&s1);
   sl.kprime = sl.L.total;
   sl.total = sl.kprime + up((size_t)s->S * s->B * s->H * sizeof(float), kAlign);
-  sl.p_kp = gemm_plan(s->S * s->B, s->H, s->H, 1, s->dtype == AS_BF16, false);
+  sl.p_kp = gemm_plan(kFormNT, s->S * s->B, s->H, s->H, 1, s->dtype == AS_BF16, false);
   return sl;
 }
 bool step_shape_ok(const as_shape* s, as_shape* s1) {
@@ -669,7 +669,7 @@ as_status attn_softmax_step_prepare(const as_shape* shape, const void* h_enc, co
   g.a_kc = true; g.b_kc = true;
   g.M = s1.S * s1.B; g.N = H;
   g.C = w + sl.kprime; g.ldc = H; g.c_bf16 = false;
-  AS_TRY(AS_STAGE_GEMM_Q, launch_gemm(g, bf, sl.p_kp.big_tile, st));
+  AS_TRY(AS_STAGE_GEMM_Q, launch_gemm(g, bf, sl.p_kp.tile, st));
   return AS_OK;
 }
 

@@ -100,19 +100,21 @@ __host__ __device__ inline int pp_dyn_splits(int tiles, int ktiles, int smax, in
 }
 
 // Tile plan shared by workspace sizing and launching.
+enum GemmTile { kTile128 = 0, kTile256 = 1, kTile64 = 2 };   // bf16: block tile edge, i.e. the kernel
+enum GemmForm { kFormNT, kFormNN, kFormTN };                 // (a_kc, b_kc) = (1, 1), (1, 0), (0, 0)
 struct GemmPlan {
-  int big_tile;   // bf16: 1 = 256x256 block tile, 0 = 128x128
+  GemmTile tile;
   int splits;
 };
-// multi_segment: the reduction runs over several operand segments; only the 128x128 kernel can split those
-GemmPlan gemm_plan(int M, int N, int K, int batch, bool bf16, bool allow_split, bool multi_segment = false);
+// multi_segment: the reduction runs over several operand segments; the 256x256 kernels cannot split those
+GemmPlan gemm_plan(GemmForm form, int M, int N, int K, int batch, bool bf16, bool allow_split, bool multi_segment = false);
 inline size_t gemm_partial_bytes(int M, int N, int batch, int splits) {
   return splits > 1 ? (size_t)splits * batch * M * N * sizeof(float) : 0;
 }
 
 // Enqueue; return hipSuccess or the launch error.  `in_bf16` selects the kernel family.
-hipError_t launch_gemm(const GemmArgs& g, bool in_bf16, int big_tile, hipStream_t st);
-hipError_t launch_gemm_bf16(const GemmArgs& g, int big_tile, hipStream_t st);
+hipError_t launch_gemm(const GemmArgs& g, bool in_bf16, GemmTile tile, hipStream_t st);
+hipError_t launch_gemm_bf16(const GemmArgs& g, GemmTile tile, hipStream_t st);
 hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t st);
 // partial[batch*splits][M][N] -> C with the epilogue of g
 hipError_t launch_splitk_combine(const GemmArgs& g, bool in_bf16, hipStream_t st);

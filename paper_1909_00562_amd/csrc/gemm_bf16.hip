@@ -1,6 +1,6 @@
 // bf16 x bf16 -> fp32 matrix products on the CDNA4 matrix cores (gfx950).
 //
-// Three kernels, one operand description (GemmDev: up to six reduction segments, three
+// Three kernels here and the 64x64 one of gemm_small.hip, one operand description (GemmDev: up to six reduction segments, three
 // operand orientations: both reduction-contiguous; B stored [K,N]; A and B stored [K,*]):
 //   * gemm_bf16_pp_kernel: 256x256x64 block tile, 8 waves in two staggered groups, two
 //     LDS stages, persistent (one block per compute unit walks an XCD-partitioned list
@@ -1256,7 +1256,8 @@ static hipError_t launch_tile(const GemmArgs& g, const GemmDev& d, hipStream_t s
 
 static bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
-hipError_t launch_gemm_bf16(const GemmArgs& g, int big_tile, hipStream_t st) {
+hipError_t launch_gemm_bf16(const GemmArgs& g, GemmTile tile, hipStream_t st) {
+  const bool big_tile = tile == kTile256;
   if (g.M < 1 || g.N < 1 || g.batch < 1 || g.splits < 1) return hipErrorInvalidValue;
   // split-K: the combine step applies the epilogue; the persistent kernel splits a single segment only
   if (g.splits > 1 && (g.partial == nullptr || (big_tile && g.K[1] != 0))) return hipErrorInvalidValue;
@@ -1311,7 +1312,7 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, int big_tile, hipStream_t st) {
              (!g.C_dact || al16(g.C_dact)) && (!g.gate || (al16(g.gate) && (g.ldg & 3) == 0)) &&
              (g.N & 3) == 0 &&                                            // a 4-column group is all in or all out
              g.ldc < (1 << 21) && g.ldg < (1 << 21) && g.N < (1 << 21);   // 32-bit byte offsets inside a 128-row window
-  const int bm = big_tile ? 256 : 128;
+  const int bm = tile == kTile256 ? 256 : tile == kTile128 ? 128 : 64;
   d.tiles_m = (g.M + bm - 1) / bm;
   d.tiles_n = (g.N + bm - 1) / bm;
   // many column tiles: 8 rows x 4 columns of co-resident tiles per XCD share 12 operand panels; few column
@@ -1322,6 +1323,7 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, int big_tile, hipStream_t st) {
   d.kper = ((ktiles + g.splits - 1) / g.splits) * BK;
   if (g.splits > 1 && !g.dyn_split && (int64_t)(d.kper / BK) * (g.splits - 1) >= ktiles)
     return hipErrorInvalidValue;   // an empty split
+  if (tile == kTile64) return launch_gemm_bf16_small(d, g.a_kc, g.b_kc, g.c_bf16 && g.splits <= 1, st);
   // Both operands strided in the reduction index (the weight-gradient products): their global rows are
   // 512 contiguous bytes whatever the reduction width, so the ring variant's deeper prefetch is free
   // (measured +7 %); with a reduction-contiguous operand its 64-byte row segments cost more than they hide.

@@ -458,9 +458,32 @@ static double plan_cost(int M, int N, int K, int batch, int tile, int splits) {
   return t;
 }
 
-GemmPlan gemm_plan(int M, int N, int K, int batch, bool bf16, bool allow_split, bool multi_segment) {
+// Microseconds of the 128 x 128 kernel by what it measures at few tiles, where the model above is far off (it was made
+// for full rounds): per reduction tile 0.6 (NT) or 1.07 (a transposed operand) while a block has a compute unit to
+// itself, 1.07 / 1.55 with two.  128 x 1024 x 1024 NT 15.5, NN 22.7; 6400 x 1024 x 1024 NT 22.7, NN 29.5.
+static double plan_split_us(int M, int N, int batch, int splits) {
+  return splits > 1 ? 2.0 * splits * (double)M * N * batch * 4.0 / 4e6 + 8.0 : 0.0;
+}
+static double plan_us_128(GemmForm form, int M, int N, int ktiles, int batch, int splits) {
+  const int64_t blocks = (int64_t)((M + 127) / 128) * ((N + 127) / 128) * batch * splits;
+  const int64_t rounds = (blocks + 511) / 512;
+  const double tile = blocks <= 256 ? (form == kFormNT ? 0.6 : 1.07) : (form == kFormNT ? 1.07 : 1.55);
+  return rounds * (tile * ((ktiles + splits - 1) / splits) + 5.0) + plan_split_us(M, N, batch, splits);
+}
+// The 64 x 64 kernel: 0.26 us per reduction tile and compute unit however many blocks share it (its LDS traffic), one
+// more per block for prologue and write-out, 5.5 per launch; a split costs it 5 for the combine launch.  Measured against
+// this: 1920 x 512 x 1024 NN 10.6 (10.7), 128 x 1024 x 3072 NT 17.7 (19), 1024 x 1024 x 6400 TN 35 (33), 2257 x 1000 x
+// 1000 NN 22 (21), 6400 x 1024 x 3072 NT 90 (93; the 128 x 128 kernel takes 60).
+static double plan_us_64(int M, int N, int ktiles, int batch, int splits) {
+  const int64_t blocks = (int64_t)((M + 63) / 64) * ((N + 63) / 64) * batch * splits;
+  const int64_t rounds = (blocks + 255) / 256;
+  return rounds * (0.26 * ((ktiles + splits - 1) / splits) + 1.0) + 5.5 +
+         (splits > 1 ? plan_split_us(M, N, batch, splits) - 3.0 : 0.0);
+}
+
+GemmPlan gemm_plan(GemmForm form, int M, int N, int K, int batch, bool bf16, bool allow_split, bool multi_segment) {
   GemmPlan pl;
-  pl.big_tile = 0;
+  pl.tile = kTile128;
   pl.splits = 1;
   if (!bf16) {
     if (multi_segment) allow_split = false;
@@ -494,16 +517,34 @@ GemmPlan gemm_plan(int M, int N, int K, int batch, bool bf16, bool allow_split, 
       const double c = plan_cost(M, N, K, batch, tile, s);
       if (c < best) {
         best = c;
-        pl.big_tile = tile == 256;
+        pl.tile = tile == 256 ? kTile256 : kTile128;
         pl.splits = s;
       }
     }
   }
+  // 64 x 64 tiles where they are at least a tenth faster than the plan so far
+  const double old = pl.tile == kTile128 ? plan_us_128(form, M, N, ktiles, batch, pl.splits) : best * 1e6;
+  double best64 = 1e30;
+  int splits64 = 1;
+  const int smax = allow_split ? (ktiles / 4 < 32 ? (ktiles / 4 > 1 ? ktiles / 4 : 1) : 32) : 1;
+  for (int want = 1; want <= smax; ++want) {
+    const int per = (ktiles + want - 1) / want, s = (ktiles + per - 1) / per;
+    if (s != want) continue;
+    const double c = plan_us_64(M, N, ktiles, batch, s);
+    if (c < best64) {
+      best64 = c;
+      splits64 = s;
+    }
+  }
+  if (best64 < 0.9 * old) {
+    pl.tile = kTile64;
+    pl.splits = splits64;
+  }
   return pl;
 }
 
-hipError_t launch_gemm(const GemmArgs& g, bool in_bf16, int big_tile, hipStream_t st) {
-  hipError_t e = in_bf16 ? launch_gemm_bf16(g, big_tile, st) : launch_gemm_f32(g, st);
+hipError_t launch_gemm(const GemmArgs& g, bool in_bf16, GemmTile tile, hipStream_t st) {
+  hipError_t e = in_bf16 ? launch_gemm_bf16(g, tile, st) : launch_gemm_f32(g, st);
   if (e != hipSuccess) return e;
   if (g.splits > 1) e = launch_splitk_combine(g, in_bf16, st);
   return e;

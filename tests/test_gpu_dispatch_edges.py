@@ -31,3 +31,36 @@ def test_h_c_split_with_ragged_segments(shape):
 def test_f32_products_at_tile_edges(shape, skip):
     T, S, B, H, V = shape
     _parity(make_custom(T=T, S=S, B=B, H=H, V=V, seed=V, dtype="f32", min_len=1, pad_prob=0.3), skip)
+
+
+@pytest.mark.parametrize("skip", [False, True])
+@pytest.mark.parametrize("shape", [(1, 5, 65, 72, 321),        # one row and one column past a 64 x 64 tile, H of 9 vectors
+                                   (2, 33, 64, 136, 1000),     # whole row tiles, reductions of 2 and a bit tiles
+                                   # source barely over one tile.  (With a vocabulary as small as 67 the rounding of
+                                   # dlogits to bf16 leaves 59 elements of dW_out to the row-scale floor, in the
+                                   # 128 x 128 kernel just as many; the budget of 0.0022 was taken at larger ones.)
+                                   (9, 70, 7, 200, 643)])
+def test_bf16_products_in_64x64_tiles(shape, skip):
+    """Few output tiles: the 64 x 64 kernel in its three operand forms, with remainders in rows, columns and reduction."""
+    T, S, B, H, V = shape
+    _parity(make_custom(T=T, S=S, B=B, H=H, V=V, seed=H, dtype="bf16", min_len=1, pad_prob=0.2), skip)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(3, 1, 8, 8, 2),            # one sentence
+                                   (5, 33, 40, 200, 3),        # units and sentences past every block shape
+                                   (4, 65, 24, 1032, 2),       # enough blocks for the larger shapes, with remainders
+                                   # one step: the caller's weight rows, widths of whole vectors.  (c = f c0 + i g is
+                                   # rounded at 2^-24 of its terms, 6e-8: elements of y below 6e-4, about one in a
+                                   # thousand, need the row-scale floor; a tensor of 1275 admits one, this one four.)
+                                   (1, 65, 16, 72, 2)])
+def test_lstm_wavefronts_at_block_edges(shape, dtype):
+    import test_gpu_lstm as tl
+    from synth_inputs import make_lstm_inputs
+    T, B, I, H, L = shape
+    if dtype == "f32" and T > 1:
+        I, H = I + 1, H + 3     # widths that are no multiple of four
+    inp = make_lstm_inputs(T, B, I, H, L, seed=H, dtype=dtype)
+    f, g, _ = tl.run_gpu(inp)
+    fo, go = tl.run_oracle(inp)
+    tl.compare(inp, f, g, fo, go)
