@@ -316,6 +316,7 @@ static as_status fwd_from_ctx(const as_shape* s, const Layout& L, char* w, const
     g.M = N; g.N = V; g.bias = b_out;
     g.M_dev = n_act;
     g.C = w + L.logits; g.ldc = L.ldV; g.c_bf16 = bf;
+    g.pad_out = true;
     AS_TRY(AS_STAGE_GEMM_LOGITS, launch_gemm(g, bf, L.p_logits.tile, st));
   }
   AS_TRY(AS_STAGE_XENT_STATS,                                          // Eq. 5-6

@@ -54,6 +54,7 @@ struct GemmArgs {
   const void* bias = nullptr;   // [N], storage type of the inputs
   const float* gate = nullptr;  // [M,ldg] multiplier (float)
   int64_t ldg = 0;
+  bool pad_out = false;         // columns N .. ldc - 1 of C's rows are padding: they may be written (with anything finite)
   int act_tanh = 0;
   int accumulate = 0;
   uint32_t drop_thr = 0;        // 0 = no dropout

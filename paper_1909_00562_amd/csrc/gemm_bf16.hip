@@ -146,7 +146,7 @@ __device__ __forceinline__ void gemm_epilogue_vec(const GemmDev& p, int Mv, AccT
   const __amdgpu_buffer_rsrc_t rs_da = make_rsrc(p.C_dact ? p.C_dact + origin : nullptr);
   const float* gate0 = p.gate ? p.gate + (int64_t)row0 * p.ldg + col0 : nullptr;   // gate and old-C reads: plain loads
   const int rows_left = Mv - row0 - vrow;                        // valid rows of C from this lane's first row on
-  const bool col_in = col0 + vcol < p.N;                         // N % 4 == 0: a 4-column group is all in or all out
+  const bool col_in = col0 + vcol < p.n_out;                     // n_out % 4 == 0: a 4-column group is all in or all out
   const uint32_t lane_off = (uint32_t)(vrow * ld + vcol);        // elements, inside the wave tile's window
   const uint32_t lane_off_g = (uint32_t)(vrow * p.ldg + vcol);
   const uint32_t ld32 = (uint32_t)ld, ldg32 = (uint32_t)p.ldg;
@@ -155,7 +155,7 @@ __device__ __forceinline__ void gemm_epilogue_vec(const GemmDev& p, int Mv, AccT
   if (p.bias && fuse) {
 #pragma unroll
     for (int c = 0; c < 4; ++c)
-      if (col_in) bias4[c] = bf16_bits_to_f32(p.bias[col0 + vcol + c]);
+      if (col0 + vcol + c < p.N) bias4[c] = bf16_bits_to_f32(p.bias[col0 + vcol + c]);
   }
   const bool plain = !DROP && !p.act_tanh && !p.gate && !p.C_lo && !p.C_dact && !(fuse && p.accumulate);
   if (plain) {
@@ -1306,11 +1306,16 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, GemmTile tile, hipStream_t st) {
   // a split chosen in the kernel: persistent two-stage kernel, rows counted on the device, partial sums always
   if (g.dyn_split && (!big_tile || !g.M_dev || g.splits < 2 || (!g.a_kc && !g.b_kc))) return hipErrorInvalidValue;
   d.dyn_split = g.dyn_split ? 1 : 0;
+  // Rows with padding behind column N: the write-out may cover whole groups of four columns (the product is zero there,
+  // operand rows >= N read as zero).  2257 x 32003 x 1000 with its rows of 32008: 228 us element by element.
+  const bool padded = g.pad_out && g.splits == 1 && g.batch == 1 && !g.drop_thr && !g.gate && !g.accumulate && !g.C_lo &&
+                      !g.C_dact && ((g.N + 3) & ~3) <= g.ldc;
+  d.n_out = padded ? (g.N + 3) & ~3 : g.N;
   // vector epilogue: every row of C / C_lo / C_dact / gate starts 16-byte aligned
   // (ldc % 4 == 0 gives 8-byte alignment for bf16 rows, which their 8-byte stores need)
   d.vec_ok = ((g.ldc & 3) == 0) && ((g.sC & 3) == 0) && al16(g.C) && (!g.C_lo || al16(g.C_lo)) &&
              (!g.C_dact || al16(g.C_dact)) && (!g.gate || (al16(g.gate) && (g.ldg & 3) == 0)) &&
-             (g.N & 3) == 0 &&                                            // a 4-column group is all in or all out
+             (d.n_out & 3) == 0 &&                                        // a 4-column group is all in or all out
              g.ldc < (1 << 21) && g.ldg < (1 << 21) && g.N < (1 << 21);   // 32-bit byte offsets inside a 128-row window
   const int bm = tile == kTile256 ? 256 : tile == kTile128 ? 128 : 64;
   d.tiles_m = (g.M + bm - 1) / bm;

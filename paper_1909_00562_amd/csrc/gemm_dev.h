@@ -14,6 +14,7 @@ struct GemmDev {
   int64_t lda[kMaxSeg], ldb[kMaxSeg], sA[kMaxSeg], sB[kMaxSeg];
   int K[kMaxSeg];
   int M, N;
+  int n_out;   // columns the vector write-out covers: N, or N rounded up to 4 where C's rows have padding
   void* C;
   uint16_t* C_lo;
   float* C_dact;

@@ -65,7 +65,7 @@ template <bool KC> __device__ __forceinline__ bf16x8_t gs_frag(const unsigned ch
 __device__ __forceinline__ void gs_store4(const GemmDev& p, int out_bf16, int batch, int z, int row, int col,
                                           const f32x4_t& v) {
   const int nc = p.N - col < 4 ? p.N - col : 4;   // columns inside
-  const bool vec = p.vec_ok != 0;                 // then N % 4 == 0: all four are inside and aligned
+  const bool vec = p.vec_ok != 0;                 // all four are inside C's rows (or their padding) and aligned
   float x[4] = {v[0], v[1], v[2], v[3]};
   if (p.splits > 1) {
     float* dst = p.partial + ((int64_t)z * p.M + row) * p.N + col;
