@@ -495,7 +495,7 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
          launch_xent_dlogits(w + L.logits, L.ldV, bf, N, V, targets, s->pad_id,
                              reinterpret_cast<const float*>(w + L.lse), s->grad_scale,
                              reinterpret_cast<float*>(w + L.dbpart), rows, n_act, st));
-  AS_TRY(AS_STAGE_MISC, launch_db_reduce(reinterpret_cast<const float*>(w + L.dbpart), L.nrb, V, db_out, st));
+  AS_TRY(AS_STAGE_MISC, launch_db_reduce(reinterpret_cast<const float*>(w + L.dbpart), L.nrb, V, db_out, n_act, L.rb, st));
   {  // dW_out = dlogits^T h_c
     GemmArgs g;
     g.seg(w + L.logits, L.ldV, 0, L.compact ? w + L.hc_c : w + L.hc, H, 0, N);
