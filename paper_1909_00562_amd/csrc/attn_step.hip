@@ -1,117 +1,177 @@
-// Attention for ONE decoder step (T = 1), fused: scores (Eq. 2), masked softmax
-// (Eq. 1) and context vector (Eq. 3) of section 3.2 in one kernel, one workgroup
-// per sentence.  The encoder-side half of the score, K'[s,b,:] = W_a h_enc[s,b,:],
-// does not depend on the decoder step and is computed once per batch of sentences,
-// so a step costs one pass over K' (float) and one over h_enc:
-//   score[s] = h_t[b] . K'[s,b]      alpha = softmax_{s < src_len[b]}      ctx = sum_s alpha[s] h_enc[s,b]
-// Used by the per-step mode (decoding, scoring, the input-feeding variant of the
-// paper's section 4, where step t+1 needs the attentional state of step t).
+// Attention for ONE decoder step (T = 1), fused: scores (Eq. 2), masked softmax (Eq. 1) and context vector (Eq. 3) of
+// section 3.2 in one kernel, one workgroup per sentence, and the backward pass of the same.
+//   score[s] = query[b] . key[s,b]      alpha = softmax_{s < src_len[b]}      ctx = sum_s alpha[s] h_enc[s,b]
+// Per-step mode (decoding, scoring, the input-feeding variant of the paper's section 4, where step t+1 needs the
+// attentional state of step t): query h_t, key K'[s,b,:] = W_a h_enc[s,b,:] (float), computed once per batch of
+// sentences.  Training step with T = 1: query Q = h_dec W_a, key h_enc.  Backward: with query dC, the scores are dalpha;
+//   dscore = alpha (dalpha - alpha . dalpha)    dQ = sum_s dscore[s] h_enc[s,b]
+//   d_h_enc[s,b] = alpha[s] dC[b] + dscore[s] Q[b]
+// One row per sentence leaves nothing for matrix instructions; what counts is that the sentence's S x H block is
+// requested at once: 16 waves, four source positions per wave in flight (128 x 50 x 1024, bf16: the 32-step kernel of
+// attn_fused.hip, four waves and a tile ahead, takes 29 us forward and 26 backward).
 #include "common.h"
 #include "kernels.h"
 
 namespace asx {
 
-typedef uint32_t u32x4_raw __attribute__((ext_vector_type(4)));
-constexpr int kStepThreads = 512, kStepWaves = kStepThreads / 64;
+typedef uint32_t st_u32x4_t __attribute__((ext_vector_type(4)));
+constexpr int kStepThreads = 1024, kStepWaves = kStepThreads / 64;
+constexpr size_t kStepSmem = 150 * 1024;
 
-template <typename TE>
-__global__ __launch_bounds__(kStepThreads) void attn_step_kernel(const TE* __restrict__ h_t, const float* __restrict__ kprime,
-                                                       const TE* __restrict__ h_enc,
-                                                       const int32_t* __restrict__ src_len, int B, int S, int H,
-                                                       float* __restrict__ alpha, TE* __restrict__ ctx,
-                                                       TE* __restrict__ ctx_lo, uint8_t* __restrict__ attn_mask) {
-  extern __shared__ float sm[];          // h_t as float [H], scores / alpha [S], context partial sums [G][H]
+template <typename T> __device__ __forceinline__ void st_unpack(const st_u32x4_t& q, float (&f)[16 / sizeof(T)]) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const uint32_t w = q[v];
+    if constexpr (sizeof(T) == 2) {
+      f[2 * v] = lo_bf16(w);
+      f[2 * v + 1] = hi_bf16(w);
+    } else {
+      f[v] = __builtin_bit_cast(float, w);
+    }
+  }
+}
+
+struct AttnStep {
+  const void *query, *query_lo;   // [B,H] storage type: value, optional remainder
+  const void* key;                // [S,B,H] TK
+  const void* h_enc;              // [S,B,H] storage type
+  const int32_t* src_len;
+  int B, S, H;
+  int G;                          // groups of the context sum (0: element-wise form)
+  float* alpha;                   // [B,S]: written; BWD: read
+  void *ctx, *ctx_lo;             // [B,H] storage type: ctx and optional remainder; BWD: dQ
+  uint8_t* attn_mask;             // optional
+  const void *q, *q_lo;           // BWD: Q [B,H] as value and remainder
+  float* d_h_enc;                 // BWD: [S,B,H]
+};
+
+template <typename TK, typename TE, bool BWD>
+__global__ __launch_bounds__(kStepThreads) void attn_step_kernel(AttnStep p) {
+  extern __shared__ __align__(16) float sm[];   // query [H], row results [S], BWD: alpha [S], partial sums [G][H]
+  const int B = p.B, S = p.S, H = p.H;
   float* hs = sm;
   float* sc = sm + H;
+  float* al = sc + S;             // BWD only
+  float* part = BWD ? al + S : al;
   __shared__ float red[2 * kStepWaves];
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int L = src_len[b];
+  int L = p.src_len[b];
   L = L < 0 ? 0 : (L > S ? S : L);
-  for (int c = tid; c < H; c += kStepThreads) hs[c] = ld_elem<TE>(h_t, (int64_t)b * H + c);
+  const TE* query = reinterpret_cast<const TE*>(p.query) + (int64_t)b * H;
+  const TE* query_lo = reinterpret_cast<const TE*>(p.query_lo) + (int64_t)b * H;
+  for (int c = tid; c < H; c += kStepThreads)
+    hs[c] = ld_elem<TE>(query, c) + (p.query_lo ? ld_elem<TE>(query_lo, c) : 0.f);
+  if constexpr (BWD)
+    for (int s = tid; s < S; s += kStepThreads) al[s] = p.alpha[(int64_t)b * S + s];
   __syncthreads();
 
-  // scores: one wavefront per source position (two at a time, so that the loads of both are in flight),
-  // lanes across H
-  auto dot = [&](int s) {
-    const float* kp = kprime + ((int64_t)s * B + b) * H;
-    float acc = 0.f;
-    if ((H & 3) == 0) {
-      for (int c = lane * 4; c < H; c += 256) {
-        const f32x4_t k4 = *reinterpret_cast<const f32x4_t*>(kp + c);
-        const f32x4_t h4 = *reinterpret_cast<const f32x4_t*>(hs + c);
-        acc += k4[0] * h4[0] + k4[1] * h4[1] + k4[2] * h4[2] + k4[3] * h4[3];
+  // scores: one wavefront per source position, four positions at a time, lanes across H
+  constexpr int VK = 16 / (int)sizeof(TK), NU = 4;
+  const TK* key = reinterpret_cast<const TK*>(p.key) + (int64_t)b * H;
+  const int64_t BH = (int64_t)B * H;
+  for (int s0 = wave; s0 < L; s0 += NU * kStepWaves) {
+    float acc[NU];
+    const TK* row[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int s = s0 + u * kStepWaves;
+      acc[u] = 0.f;
+      row[u] = key + (s < L ? s : s0) * BH;   // past the end: the first position again, not stored
+    }
+    if (H % VK == 0) {
+#pragma unroll 2
+      for (int c = lane * VK; c < H; c += 64 * VK) {
+        st_u32x4_t k[NU];
+#pragma unroll
+        for (int u = 0; u < NU; ++u) k[u] = *reinterpret_cast<const st_u32x4_t*>(row[u] + c);
+        float h[VK];
+#pragma unroll
+        for (int v = 0; v < VK; v += 4) {
+          const f32x4_t h4 = *reinterpret_cast<const f32x4_t*>(hs + c + v);
+          h[v] = h4[0]; h[v + 1] = h4[1]; h[v + 2] = h4[2]; h[v + 3] = h4[3];
+        }
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+          float f[VK];
+          st_unpack<TK>(k[u], f);
+#pragma unroll
+          for (int v = 0; v < VK; ++v) acc[u] += f[v] * h[v];
+        }
       }
     } else {
-      for (int c = lane; c < H; c += 64) acc += kp[c] * hs[c];
+      for (int c = lane; c < H; c += 64)
+#pragma unroll
+        for (int u = 0; u < NU; ++u) acc[u] += ld_elem<TK>(row[u], c) * hs[c];
     }
-    return acc;
-  };
-  for (int s = wave; s < L; s += 2 * kStepWaves) {
-    const int s2 = s + kStepWaves;
-    float a0 = dot(s), a1 = s2 < L ? dot(s2) : 0.f;
-    a0 = wave_sum(a0);
-    a1 = wave_sum(a1);
-    if (lane == 0) {
-      sc[s] = a0;
-      if (s2 < L) sc[s2] = a1;
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const float a = wave_sum(acc[u]);
+      if (lane == 0 && s0 + u * kStepWaves < L) sc[s0 + u * kStepWaves] = a;
     }
   }
   __syncthreads();
 
-  // masked softmax over the L valid positions
-  float m = -INFINITY;
-  for (int s = tid; s < L; s += kStepThreads) m = fmaxf(m, sc[s]);
-  m = wave_max(m);
-  if (lane == 0) red[wave] = m;
-  __syncthreads();
-  m = red[0];
+  if constexpr (!BWD) {   // masked softmax over the L valid positions
+    float m = -INFINITY;
+    for (int s = tid; s < L; s += kStepThreads) m = fmaxf(m, sc[s]);
+    m = wave_max(m);
+    if (lane == 0) red[wave] = m;
+    __syncthreads();
+    m = red[0];
 #pragma unroll
-  for (int i = 1; i < kStepWaves; ++i) m = fmaxf(m, red[i]);
-  float sum = 0.f;
-  for (int s = tid; s < L; s += kStepThreads) sum += expf(sc[s] - m);
-  sum = wave_sum(sum);
-  if (lane == 0) red[kStepWaves + wave] = sum;
-  __syncthreads();
-  sum = 0.f;
+    for (int i = 1; i < kStepWaves; ++i) m = fmaxf(m, red[i]);
+    float sum = 0.f;
+    for (int s = tid; s < L; s += kStepThreads) sum += expf(sc[s] - m);
+    sum = wave_sum(sum);
+    if (lane == 0) red[kStepWaves + wave] = sum;
+    __syncthreads();
+    sum = 0.f;
 #pragma unroll
-  for (int i = 0; i < kStepWaves; ++i) sum += red[kStepWaves + i];
-  const float inv = L > 0 ? 1.f / sum : 0.f;
-  for (int s = tid; s < S; s += kStepThreads) {
-    const float a = s < L ? expf(sc[s] - m) * inv : 0.f;   // masked positions: exactly 0
-    alpha[(int64_t)b * S + s] = a;
-    if (attn_mask) attn_mask[(int64_t)b * S + s] = s < L ? 1 : 0;
+    for (int i = 0; i < kStepWaves; ++i) sum += red[kStepWaves + i];
+    const float inv = L > 0 ? 1.f / sum : 0.f;
+    for (int s = tid; s < S; s += kStepThreads) {   // a thread reads and writes its own positions only
+      const float a = s < L ? expf(sc[s] - m) * inv : 0.f;   // masked positions: exactly 0
+      p.alpha[(int64_t)b * S + s] = a;
+      if (p.attn_mask) p.attn_mask[(int64_t)b * S + s] = s < L ? 1 : 0;
+      sc[s] = a;
+    }
+  } else {                // softmax Jacobian
+    float dot = 0.f;
+    for (int s = tid; s < L; s += kStepThreads) dot += al[s] * sc[s];
+    dot = wave_sum(dot);
+    if (lane == 0) red[wave] = dot;
+    __syncthreads();
+    dot = 0.f;
+#pragma unroll
+    for (int i = 0; i < kStepWaves; ++i) dot += red[i];
+    for (int s = tid; s < S; s += kStepThreads) sc[s] = s < L ? al[s] * (sc[s] - dot) : 0.f;
   }
-  __syncthreads();                        // every thread has read sc[] (its max / sum passes) before it is overwritten
-  for (int s = tid; s < L; s += kStepThreads) sc[s] = expf(sc[s] - m) * inv;
   __syncthreads();
 
   // context: the threads form G groups; a group covers all of H with 16-byte vectors and takes every G-th
   // source position; the G partial sums are added in a fixed order
   constexpr int VEC = 16 / (int)sizeof(TE);
-  float* part = sc + S;                   // [G][H]
-  if (H % VEC == 0 && H / VEC <= kStepThreads) {
-    const int per = H / VEC;              // threads of one group
-    const int G = kStepThreads / per < 8 ? kStepThreads / per : 8;
+  const TE* h_enc = reinterpret_cast<const TE*>(p.h_enc) + (int64_t)b * H;
+  TE* ctx = reinterpret_cast<TE*>(p.ctx) + (int64_t)b * H;
+  TE* ctx_lo = reinterpret_cast<TE*>(p.ctx_lo) + (int64_t)b * H;
+  auto put = [&](int c, float v) {
+    st_elem<TE>(ctx, c, v);
+    if (p.ctx_lo) st_elem<TE>(ctx_lo, c, v - round_elem<TE>(v));
+  };
+  if (p.G > 0) {
+    const int per = H / VEC, G = p.G;     // threads of one group
     const int grp = tid / per, c = (tid - grp * per) * VEC;
     if (grp < G) {
       float acc[VEC];
 #pragma unroll
       for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
+#pragma unroll 8
       for (int s = grp; s < L; s += G) {
-        const TE* src = h_enc + ((int64_t)s * B + b) * H + c;
+        float f[VEC];
+        st_unpack<TE>(*reinterpret_cast<const st_u32x4_t*>(h_enc + s * BH + c), f);
         const float a = sc[s];
-        if constexpr (sizeof(TE) == 2) {
-          const u32x4_raw raw = *reinterpret_cast<const u32x4_raw*>(src);
 #pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            acc[2 * v] += a * lo_bf16(raw[v]);
-            acc[2 * v + 1] += a * hi_bf16(raw[v]);
-          }
-        } else {
-          const f32x4_t raw = *reinterpret_cast<const f32x4_t*>(src);
-#pragma unroll
-          for (int v = 0; v < 4; ++v) acc[v] += a * raw[v];
-        }
+        for (int v = 0; v < VEC; ++v) acc[v] += a * f[v];
       }
 #pragma unroll
       for (int v = 0; v < VEC; ++v) part[grp * H + c + v] = acc[v];
@@ -120,48 +180,109 @@ __global__ __launch_bounds__(kStepThreads) void attn_step_kernel(const TE* __res
     for (int cc = tid; cc < H; cc += kStepThreads) {
       float acc = 0.f;
       for (int g = 0; g < G; ++g) acc += part[g * H + cc];
-      st_elem<TE>(ctx, (int64_t)b * H + cc, acc);
-      if (ctx_lo) st_elem<TE>(ctx_lo, (int64_t)b * H + cc, acc - round_elem<TE>(acc));
+      put(cc, acc);
     }
   } else {
     for (int c = tid; c < H; c += kStepThreads) {
       float acc = 0.f;
-      for (int s = 0; s < L; ++s) acc += sc[s] * ld_elem<TE>(h_enc, ((int64_t)s * B + b) * H + c);
-      st_elem<TE>(ctx, (int64_t)b * H + c, acc);
-      if (ctx_lo) st_elem<TE>(ctx_lo, (int64_t)b * H + c, acc - round_elem<TE>(acc));
+      for (int s = 0; s < L; ++s) acc += sc[s] * ld_elem<TE>(h_enc, s * BH + c);
+      put(c, acc);
     }
   }
+  if constexpr (BWD) {   // gradient of the encoder states: the sentence's rows are written by its workgroup alone
+    const TE* q = reinterpret_cast<const TE*>(p.q) + (int64_t)b * H;
+    const TE* q_lo = reinterpret_cast<const TE*>(p.q_lo) + (int64_t)b * H;
+    float* out = p.d_h_enc + (int64_t)b * H;
+    const int per = H / 4;   // H % 8 == 0 (bf16 storage)
+    const int side = per < kStepThreads ? kStepThreads / per : 1;   // positions side by side
+    const int step = per < kStepThreads ? per : kStepThreads;
+    const int ss = tid / step;
+    for (int c4 = tid - ss * step; c4 < per && ss < side; c4 += step) {
+      const int c = c4 * 4;
+      const f32x4_t dc = *reinterpret_cast<const f32x4_t*>(hs + c);
+      f32x4_t qv;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) qv[e] = ld_elem<TE>(q, c + e) + ld_elem<TE>(q_lo, c + e);
+      for (int s = ss; s < S; s += side) {
+        const float a = al[s], d = sc[s];
+        f32x4_t o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = a * dc[e] + d * qv[e];
+        *reinterpret_cast<f32x4_t*>(out + s * BH + c) = o;
+      }
+    }
+  }
+}
+
+// groups of the context sum, by what the threads and the LDS allow
+static int step_groups(int S, int H, int vec, bool bwd, size_t& smem) {
+  int G = 0;
+  if (H % vec == 0 && H / vec <= kStepThreads) {
+    G = kStepThreads / (H / vec);
+    if (G > 8) G = 8;
+  }
+  const size_t base = ((size_t)H + (bwd ? 2 : 1) * (size_t)S) * sizeof(float);
+  while (G > 0 && base + (size_t)G * H * sizeof(float) > kStepSmem) --G;
+  smem = base + (size_t)G * H * sizeof(float);
+  return G;
+}
+
+template <typename TK, typename TE, bool BWD>
+static hipError_t launch_step(AttnStep p, hipStream_t st) {
+  size_t smem = 0;
+  p.G = step_groups(p.S, p.H, 16 / (int)sizeof(TE), BWD, smem);
+  if (smem > kStepSmem) return hipErrorInvalidValue;
+  auto k = attn_step_kernel<TK, TE, BWD>;
+  if (smem > 48 * 1024) {
+    const hipError_t e =
+        hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(k, dim3(p.B), dim3(kStepThreads), smem, st, p);
+  return hipGetLastError();
 }
 
 hipError_t launch_attn_step(const void* h_t, const float* kprime, const void* h_enc, const int32_t* src_len, int B,
                             int S, int H, float* alpha, void* ctx, void* ctx_lo, bool e_bf16, uint8_t* attn_mask,
                             hipStream_t st) {
-  // h_t, scores, partial contexts: G groups x H floats with G <= 8 and G * H <= threads * 8
-  const size_t part = (size_t)8 * H < (size_t)kStepThreads * 8 ? (size_t)8 * H : (size_t)kStepThreads * 8;
-  const size_t smem = ((size_t)H + S + part) * sizeof(float);
-  if (smem > 150 * 1024) return hipErrorInvalidValue;
-  if (e_bf16) {
-    auto k = attn_step_kernel<uint16_t>;
-    if (smem > 48 * 1024) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         (int)smem);
-      if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(k, dim3(B), dim3(kStepThreads), smem, st, reinterpret_cast<const uint16_t*>(h_t), kprime,
-                       reinterpret_cast<const uint16_t*>(h_enc), src_len, B, S, H, alpha,
-                       reinterpret_cast<uint16_t*>(ctx), reinterpret_cast<uint16_t*>(ctx_lo), attn_mask);
-  } else {
-    auto k = attn_step_kernel<float>;
-    if (smem > 48 * 1024) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         (int)smem);
-      if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(k, dim3(B), dim3(kStepThreads), smem, st, reinterpret_cast<const float*>(h_t), kprime,
-                       reinterpret_cast<const float*>(h_enc), src_len, B, S, H, alpha, reinterpret_cast<float*>(ctx),
-                       reinterpret_cast<float*>(ctx_lo), attn_mask);
-  }
-  return hipGetLastError();
+  AttnStep p{};
+  p.query = h_t;
+  p.key = kprime;
+  p.h_enc = h_enc;
+  p.src_len = src_len;
+  p.B = B; p.S = S; p.H = H;
+  p.alpha = alpha; p.ctx = ctx; p.ctx_lo = ctx_lo; p.attn_mask = attn_mask;
+  return e_bf16 ? launch_step<float, uint16_t, false>(p, st) : launch_step<float, float, false>(p, st);
+}
+
+bool attn_one_step_supported(int T, int S, int H) {
+  size_t smem = 0;
+  step_groups(S, H, 8, true, smem);
+  return T == 1 && H % 8 == 0 && smem <= kStepSmem;
+}
+hipError_t launch_attn_one_step_fwd(const void* q_hi, const void* q_lo, const void* h_enc, const int32_t* src_len, int B,
+                                    int S, int H, float* alpha, void* ctx, void* ctx_lo, uint8_t* attn_mask,
+                                    hipStream_t st) {
+  AttnStep p{};
+  p.query = q_hi; p.query_lo = q_lo;
+  p.key = p.h_enc = h_enc;
+  p.src_len = src_len;
+  p.B = B; p.S = S; p.H = H;
+  p.alpha = alpha; p.ctx = ctx; p.ctx_lo = ctx_lo; p.attn_mask = attn_mask;
+  return launch_step<uint16_t, uint16_t, false>(p, st);
+}
+hipError_t launch_attn_one_step_bwd(const void* dC_hi, const void* dC_lo, const void* h_enc, const int32_t* src_len,
+                                    int B, int S, int H, const float* alpha, const void* q_hi, const void* q_lo, void* dQ,
+                                    float* d_h_enc, hipStream_t st) {
+  AttnStep p{};
+  p.query = dC_hi; p.query_lo = dC_lo;
+  p.key = p.h_enc = h_enc;
+  p.src_len = src_len;
+  p.B = B; p.S = S; p.H = H;
+  p.alpha = const_cast<float*>(alpha);
+  p.ctx = dQ;
+  p.q = q_hi; p.q_lo = q_lo; p.d_h_enc = d_h_enc;
+  return launch_step<uint16_t, uint16_t, true>(p, st);
 }
 
 }  // namespace asx

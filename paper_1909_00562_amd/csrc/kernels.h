@@ -73,6 +73,16 @@ hipError_t launch_db_reduce(const float* db_partial, int nrb, int V, float* db_o
 hipError_t launch_attn_step(const void* h_t, const float* kprime, const void* h_enc, const int32_t* src_len, int B,
                             int S, int H, float* alpha, void* ctx, void* ctx_lo, bool e_bf16, uint8_t* attn_mask,
                             hipStream_t st);
+// The same for a training step with T = 1, bf16 storage: query Q = h_dec W_a [B,H] as value and remainder, key h_enc.
+// Backward: alpha as saved, dC [B,H] and Q as value and remainder -> dQ [B,H] and d_h_enc [S,B,H] (all of it).
+bool attn_one_step_supported(int T, int S, int H);
+hipError_t launch_attn_one_step_fwd(const void* q_hi, const void* q_lo, const void* h_enc, const int32_t* src_len, int B,
+                                    int S, int H, float* alpha, void* ctx, void* ctx_lo, uint8_t* attn_mask,
+                                    hipStream_t st);
+hipError_t launch_attn_one_step_bwd(const void* dC_hi, const void* dC_lo, const void* h_enc, const int32_t* src_len,
+                                    int B, int S, int H, const float* alpha, const void* q_hi, const void* q_lo, void* dQ,
+                                    float* d_h_enc, hipStream_t st);
+
 // Measurement aid: plain streams over `rows` chunks of `row_bytes` bytes (a multiple of 16).  kind 0: read-only with
 // the statistics kernel's load pattern, buf2 receives 4 words per row; kind 1: copy buf -> buf2 and kind 2:
 // in-place read-modify-write of buf, both with the dlogits kernel's grid and loads in flight.
