@@ -133,26 +133,26 @@ Layout make_layout(const as_shape* s) {
   L.rb = xent_rows_per_block(N, V, bf);
   L.nrb = (N + L.rb - 1) / L.rb;
 
-  L.p_q = gemm_plan(kFormNN, N, H, H, 1, bf, false);
-  L.p_score = gemm_plan(kFormNT, T, S, H, B, bf, false);
-  L.p_ctx = gemm_plan(kFormNN, T, H, S, B, bf, false);
+  L.p_q = gemm_plan(N, H, H, 1, bf, false);
+  L.p_score = gemm_plan(T, S, H, B, bf, false);
+  L.p_ctx = gemm_plan(T, H, S, B, bf, false);
   // Segments: ctx (+ remainder), h_dec.  Each segment is cut into reduction tiles of its own, so the length to plan a
   // split for counts whole tiles per segment: planned over 3 * H, sizes like H = 584 got a split with no tiles left.
-  L.p_hc = gemm_plan(kFormNT, N, H, bf ? 3 * (int)up(H, 64) : 2 * H, 1, bf, true, true);
-  L.p_logits = gemm_plan(kFormNT, N, V, H, 1, bf, false);
-  L.p_dwout = gemm_plan(kFormTN, V, H, N, 1, bf, true);
-  L.p_dhc = gemm_plan(kFormNN, N, H, V, 1, bf, true);
+  L.p_hc = gemm_plan(N, H, bf ? 3 * (int)up(H, 64) : 2 * H, 1, bf, true, true);
+  L.p_logits = gemm_plan(N, V, H, 1, bf, false);
+  L.p_dwout = gemm_plan(V, H, N, 1, bf, true);
+  L.p_dhc = gemm_plan(N, H, V, 1, bf, true);
   // Few, long work items (N/256 x H/256 tiles, reduction over V): once the padding rows are gone the item count
   // no longer fills whole rounds of the grid, so the kernel splits the reduction to fit the count it reads.
   L.dhc_dyn = s->skip_pad_rows != 0 && bf && L.p_dhc.tile == kTile256;
   if (L.dhc_dyn && L.p_dhc.splits < 8) L.p_dhc.splits = 8;
-  L.p_dwc = gemm_plan(kFormTN, H, H, N, 2, bf, true);          // both halves of dW_c in one launch
-  L.p_dch = gemm_plan(kFormNN, N, H, H, 1, bf, false);
-  L.p_dalpha = gemm_plan(kFormNT, T, S, H, B, bf, false);
-  L.p_dq = gemm_plan(kFormNN, T, H, S, B, bf, false);
-  L.p_ds = gemm_plan(kFormTN, S, H, T, B, bf, false);
-  L.p_dwa = gemm_plan(kFormTN, H, H, N, 1, bf, true);
-  L.p_dh = gemm_plan(kFormNT, N, H, H, 1, bf, false);
+  L.p_dwc = gemm_plan(H, H, N, 2, bf, true);          // both halves of dW_c in one launch
+  L.p_dch = gemm_plan(N, H, H, 1, bf, false);
+  L.p_dalpha = gemm_plan(T, S, H, B, bf, false);
+  L.p_dq = gemm_plan(T, H, S, B, bf, false);
+  L.p_ds = gemm_plan(S, H, T, B, bf, false);
+  L.p_dwa = gemm_plan(H, H, N, 1, bf, true);
+  L.p_dh = gemm_plan(N, H, H, 1, bf, false);
   size_t pb = 0;
   auto mx = [&](size_t v) { if (v > pb) pb = v; };
   mx(gemm_partial_bytes(N, H, 1, L.p_hc.splits));
@@ -643,7 +643,7 @@ StepLayout make_step_layout(const as_shape* s) {
   sl.L = make_layout(&s1);
   sl.kprime = sl.L.total;
   sl.total = sl.kprime + up((size_t)s->S * s->B * s->H * sizeof(float), kAlign);
-  sl.p_kp = gemm_plan(kFormNT, s->S * s->B, s->H, s->H, 1, s->dtype == AS_BF16, false);
+  sl.p_kp = gemm_plan(s->S * s->B, s->H, s->H, 1, s->dtype == AS_BF16, false);
   return sl;
 }
 bool step_shape_ok(const as_shape* s, as_shape* s1) {

@@ -102,13 +102,12 @@ __host__ __device__ inline int pp_dyn_splits(int tiles, int ktiles, int smax, in
 
 // Tile plan shared by workspace sizing and launching.
 enum GemmTile { kTile128 = 0, kTile256 = 1, kTile64 = 2 };   // bf16: block tile edge, i.e. the kernel
-enum GemmForm { kFormNT, kFormNN, kFormTN };                 // (a_kc, b_kc) = (1, 1), (1, 0), (0, 0)
 struct GemmPlan {
   GemmTile tile;
   int splits;
 };
 // multi_segment: the reduction runs over several operand segments; the 256x256 kernels cannot split those
-GemmPlan gemm_plan(GemmForm form, int M, int N, int K, int batch, bool bf16, bool allow_split, bool multi_segment = false);
+GemmPlan gemm_plan(int M, int N, int K, int batch, bool bf16, bool allow_split, bool multi_segment = false);
 inline size_t gemm_partial_bytes(int M, int N, int batch, int splits) {
   return splits > 1 ? (size_t)splits * batch * M * N * sizeof(float) : 0;
 }

@@ -34,53 +34,6 @@
 
 namespace asx {
 
-// ---- strided-reduction operand: HBM -> registers -> transposed into LDS --------------
-// Thread t owns rows (t/16)*8 .. +7 (contiguous index) x reduction rows (t%16)*4 .. +3.
-template <int ROWS, int NT>
-struct TransposeLoader {
-  static constexpr int NB = ROWS * 2 / NT;   // 4x8 blocks per thread
-  static constexpr int NL = NB * 4;          // 16-byte loads per thread and tile
-  uint32_t voff[NL];
-  u32x4_t r[NL];
-  int k4;
-  __device__ __forceinline__ void init(int64_t ld, int rows_left, int tid) {
-    const int kq = tid & 15, rb = tid >> 4;
-    k4 = kq * 4;
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      const int row = (rb + (NT / 16) * j) * 8;
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-        voff[j * 4 + kk] = row < rows_left ? (uint32_t)(((int64_t)(k4 + kk) * ld + row) * 2) : kOob;
-    }
-  }
-  // X points at element (k0, row0) of the operand stored [K, rows]
-  __device__ __forceinline__ void load(int l, const __amdgpu_buffer_rsrc_t& rs, int k_left) {
-    const uint32_t off = (k4 + (l & 3)) < k_left ? voff[l] : kOob;
-    r[l] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
-  }
-  __device__ __forceinline__ void store(unsigned char* lds_tile, int tid) const {
-    static_assert((NT / 16) % 2 == 0, "row-group parity must not depend on j");
-    const int kq = tid & 15, rb = tid >> 4;
-    const int chunk = (kq >> 1) ^ (rb & 1), half = kq & 1;
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int row = (rb + (NT / 16) * j) * 8 + e;
-        const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
-        const uint32_t lo = __builtin_amdgcn_perm(r[j * 4 + 1][e >> 1], r[j * 4 + 0][e >> 1], sel);
-        const uint32_t hi = __builtin_amdgcn_perm(r[j * 4 + 3][e >> 1], r[j * 4 + 2][e >> 1], sel);
-        *reinterpret_cast<uint2*>(lds_tile + row * ROWB + ((chunk ^ e) << 4) + half * 8) = make_uint2(lo, hi);
-      }
-    }
-  }
-};
-
-__device__ __forceinline__ bf16x8_t frag_read(const unsigned char* base, int row, int chunk) {
-  return *reinterpret_cast<const bf16x8_t*>(base + row * ROWB + ((chunk ^ (row & 7) ^ ((row >> 3) & 1)) << 4));
-}
-
 // ---- epilogue --------------------------------------------------------------------
 // MFMA 32x32 output: register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4,
 // column l%32 of its tile.  Each wave stages 32 rows x 64 columns at a time through
@@ -382,184 +335,6 @@ __device__ __forceinline__ void gemm_epilogue(const GemmDev& p, int Mv, AccT& ac
     __builtin_amdgcn_s_waitcnt(WAIT_LGKM_ONLY);  // LDS reads done before the next rows overwrite the slice
   }
 }
-
-template <int BM, int BN, int WGM, int WGN, bool AKC, bool BKC, bool OUT_BF16, bool VEC, bool DROP>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_kernel(GemmDev p) {
-  constexpr int NW = WGM * WGN, NT = 64 * NW;
-  constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32;
-  constexpr int STAGE = (BM + BN) * ROWB;
-  static_assert(WN == 64 && (WM == 64 || WM == 128), "epilogue assumes 64-column wave tiles");
-  static_assert(2 * STAGE >= NW * 16384, "epilogue needs 16 KiB of LDS per wave");
-  extern __shared__ __align__(1024) unsigned char smem[];
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: LDS bases of direct loads
-  const int wm = wave / WGN, wn = wave % WGN;
-
-  // --- block -> tile: consecutive blocks go round-robin to the 8 XCDs, so give
-  // each XCD a contiguous run of tiles, then walk tiles in groups of 8 tile
-  // rows so that co-resident blocks share operand panels in their XCD's L2.
-  const int nt = p.tiles_m * p.tiles_n;
-  int pid = blockIdx.x;
-  {
-    const int xcd = pid & 7, idx = pid >> 3;
-    const int per = nt >> 3, rem = nt & 7;
-    pid = xcd * per + (xcd < rem ? xcd : rem) + idx;
-  }
-  constexpr int GROUP = 8;
-  const int gsize = GROUP * p.tiles_n;
-  const int gid = pid / gsize;
-  const int first_m = gid * GROUP;
-  const int gm = (p.tiles_m - first_m) < GROUP ? (p.tiles_m - first_m) : GROUP;
-  const int in_g = pid - gid * gsize;
-  const int tile_m = first_m + in_g % gm, tile_n = in_g / gm;
-  const int m0 = tile_m * BM, n0 = tile_n * BN;
-  const int Mv = dev_bound(p.M_dev, p.M);   // valid rows: the grid was sized for p.M
-  const int K0 = dev_bound(p.K_dev, p.K[0]);
-  if (m0 >= Mv) return;                     // the whole block, before any barrier
-
-  const int z = blockIdx.z;
-  const int batch = z / p.splits, split = z - batch * p.splits;
-
-  // reduction tiles of this block: all of them, or (split-K) tiles [t0, t1) of the sequence that runs
-  // through the segments one after the other; the cursor below starts at tile t0
-  int nks[kMaxSeg];
-  int nk = 0;
-#pragma unroll
-  for (int s = 0; s < kMaxSeg; ++s) {
-    nks[s] = ((s == 0 ? K0 : p.K[s]) + BK - 1) / BK;
-    nk += nks[s];
-  }
-  int seg0 = 0, skip0 = 0;   // first segment of this block and reduction tiles skipped inside it
-  if (p.splits > 1) {
-    // a reduction length read on the device is split here (a split may then come out empty: it stores zeros)
-    const int tper = p.K_dev ? (nk + p.splits - 1) / p.splits : p.kper / BK;
-    const int t0 = split * tper;
-    const int t1 = t0 + tper < nk ? t0 + tper : nk;
-    nk = t1 > t0 ? t1 - t0 : 0;
-    skip0 = t0;
-    while (seg0 < kMaxSeg - 1 && skip0 >= nks[seg0]) {
-      skip0 -= nks[seg0];
-      ++seg0;
-    }
-  }
-  const int kbeg0 = skip0 * BK;
-
-  f32x16_t acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  // per-lane load offsets, fixed for the whole kernel (all segments share lda / ldb)
-  DirectLoader<BM, NW> dla;
-  DirectLoader<BN, NW> dlb;
-  TransposeLoader<BM, NT> tla;
-  TransposeLoader<BN, NT> tlb;
-  if constexpr (AKC) dla.init(p.lda[0], Mv - m0, wave, lane); else tla.init(p.lda[0], Mv - m0, tid);
-  if constexpr (BKC) dlb.init(p.ldb[0], p.N - n0, wave, lane); else tlb.init(p.ldb[0], p.N - n0, tid);
-  constexpr int NLA = AKC ? DirectLoader<BM, NW>::NL : TransposeLoader<BM, NT>::NL;
-  constexpr int NLB = BKC ? DirectLoader<BN, NW>::NL : TransposeLoader<BN, NT>::NL;
-  constexpr int NLT = NLA + NLB;
-
-  // cursor over the reduction tiles of all segments: operand pointers of the next tile to load
-  const int64_t stepA = AKC ? BK : (int64_t)BK * p.lda[0], stepB = BKC ? BK : (int64_t)BK * p.ldb[0];
-  const int64_t offA = AKC ? (int64_t)m0 * p.lda[0] : m0, offB = BKC ? (int64_t)n0 * p.ldb[0] : n0;
-  int cseg = seg0, ck_left = (seg0 == 0 ? K0 : p.K[seg0]) - kbeg0;
-  const uint16_t* cA = p.A[seg0] + (int64_t)batch * p.sA[seg0] + offA + (AKC ? kbeg0 : (int64_t)kbeg0 * p.lda[0]);
-  const uint16_t* cB = p.B[seg0] + (int64_t)batch * p.sB[seg0] + offB + (BKC ? kbeg0 : (int64_t)kbeg0 * p.ldb[0]);
-  auto advance = [&]() {
-    cA += stepA;
-    cB += stepB;
-    ck_left -= BK;
-    if (ck_left <= 0) {
-      do { ++cseg; } while (cseg < kMaxSeg && p.K[cseg] <= 0);
-      if (cseg < kMaxSeg) {
-        cA = p.A[cseg] + (int64_t)batch * p.sA[cseg] + offA;
-        cB = p.B[cseg] + (int64_t)batch * p.sB[cseg] + offB;
-        ck_left = p.K[cseg];
-      }
-    }
-  };
-  // loads [l0, l1) of the tile under the cursor into LDS stage `stage` (or registers)
-  auto issue = [&](int stage, int l0, int l1) {
-    const __amdgpu_buffer_rsrc_t rsa = make_rsrc(cA), rsb = make_rsrc(cB);
-    unsigned char* as = smem + stage * STAGE;
-    unsigned char* bs = as + BM * ROWB;
-#pragma unroll
-    for (int l = 0; l < NLT; ++l) {
-      if (l < l0 || l >= l1) continue;
-      if (l < NLA) {
-        if constexpr (AKC) dla.load(l, rsa, ck_left, as, wave); else tla.load(l, rsa, ck_left);
-      } else {
-        if constexpr (BKC) dlb.load(l - NLA, rsb, ck_left, bs, wave); else tlb.load(l - NLA, rsb, ck_left);
-      }
-    }
-  };
-  // transposed operands: registers -> LDS
-  auto commit = [&](int stage) {
-    unsigned char* as = smem + stage * STAGE;
-    unsigned char* bs = as + BM * ROWB;
-    if constexpr (!AKC) tla.store(as, tid);
-    if constexpr (!BKC) tlb.store(bs, tid);
-  };
-  auto read_frags = [&](bf16x8_t (&af)[TM], bf16x8_t (&bfr)[TN], int stage, int kk) {
-    const unsigned char* as = smem + stage * STAGE;
-    const unsigned char* bs = as + BM * ROWB;
-    const int chunk = kk * 2 + (lane >> 5);
-#pragma unroll
-    for (int i = 0; i < TM; ++i) af[i] = frag_read(as, wm * WM + i * 32 + (lane & 31), chunk);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) bfr[j] = frag_read(bs, wn * WN + j * 32 + (lane & 31), chunk);
-  };
-
-  if (nk > 0) {
-    issue(0, 0, NLT);
-    advance();
-    commit(0);
-  }
-  __builtin_amdgcn_s_waitcnt(0);  // this wave's direct loads have landed in LDS
-  __syncthreads();
-
-  // Software pipeline: the fragments of step kk+1 are read from LDS while the MFMAs
-  // of step kk run, also across the tile boundary; the next tile's global loads
-  // are spread over the first three steps.
-  bf16x8_t af[2][TM], bfr[2][TN];
-  if (nk > 0) read_frags(af[0], bfr[0], 0, 0);
-  constexpr int KSTEPS = BK / 16;
-  constexpr int LPART = (NLT + KSTEPS - 2) / (KSTEPS - 1);
-  for (int kt = 0; kt < nk; ++kt) {
-    const bool more = kt + 1 < nk;
-    const int cur = kt & 1, nxt = cur ^ 1;
-#pragma unroll
-    for (int kk = 0; kk < KSTEPS; ++kk) {
-      if (kk < KSTEPS - 1) {
-        if (more) issue(nxt, kk * LPART, (kk + 1) * LPART < NLT ? (kk + 1) * LPART : NLT);
-        read_frags(af[(kk + 1) & 1], bfr[(kk + 1) & 1], cur, kk + 1);
-      } else {
-        if (more) {
-          commit(nxt);
-          advance();
-        }
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        if (more) read_frags(af[(kk + 1) & 1], bfr[(kk + 1) & 1], nxt, 0);
-      }
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[kk & 1][i], bfr[kk & 1][j], acc[i][j], 0, 0, 0);
-    }
-  }
-  // (the last barrier above came after every wave's final fragment reads: LDS is free for the epilogue)
-
-  gemm_epilogue<TM, TN, OUT_BF16, VEC, DROP>(p, Mv, acc, smem + wave * 16384, lane, m0 + wm * WM, n0 + wn * WN, batch,
-                                             z);
-}
-
 
 // ---- 256x256 tile, 8 waves, two staggered wave groups ("ping-pong") ---------------
 // Reduction tiles of 64 elements, two LDS stages, every operand loaded HBM -> LDS
@@ -1179,22 +954,6 @@ static hipError_t launch_ring_oriented(const GemmArgs& g, const GemmDev& d, hipS
   return vec ? launch_ring<AKC, BKC, false, true>(d, g.batch, st) : launch_ring<AKC, BKC, false, false>(d, g.batch, st);
 }
 
-template <int BM, int BN, int WGM, int WGN, bool AKC, bool BKC, bool OUT_BF16, bool VEC, bool DROP = false>
-static hipError_t launch_one(const GemmDev& d, int batch, hipStream_t st) {
-  constexpr int smem = 2 * (BM + BN) * ROWB;
-  auto kfn = gemm_bf16_kernel<BM, BN, WGM, WGN, AKC, BKC, OUT_BF16, VEC, DROP>;
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
-  dim3 grid(d.tiles_m * d.tiles_n, 1, batch * d.splits);
-  hipLaunchKernelGGL(kfn, grid, dim3(64 * WGM * WGN), smem, st, d);
-  return hipGetLastError();
-}
-
 template <bool AKC, bool BKC, bool OUT_BF16, bool VEC, bool DROP = false>
 static hipError_t launch_pp(const GemmDev& d, int batch, hipStream_t st) {
   constexpr int smem = PP_SMEM;
@@ -1214,44 +973,20 @@ static hipError_t launch_pp(const GemmDev& d, int batch, hipStream_t st) {
 }
 
 // operand orientations x output type x epilogue form -> kernel instance
-template <bool BIG, bool AKC, bool BKC>
+template <bool AKC, bool BKC>
 static hipError_t launch_oriented(const GemmArgs& g, const GemmDev& d, hipStream_t st) {
   const bool obf = g.c_bf16 && g.splits <= 1;
   const bool vec = d.vec_ok != 0;
   if (d.drop_thr) {   // dropout variants exist for the one product that uses them (both operands reduction-contiguous)
     if constexpr (AKC && BKC) {
-      if constexpr (BIG) {
-        if (obf) return vec ? launch_pp<true, true, true, true, true>(d, g.batch, st) : launch_pp<true, true, true, false, true>(d, g.batch, st);
-        return vec ? launch_pp<true, true, false, true, true>(d, g.batch, st) : launch_pp<true, true, false, false, true>(d, g.batch, st);
-      } else {
-        if (obf)
-          return vec ? launch_one<128, 128, 2, 2, true, true, true, true, true>(d, g.batch, st)
-                     : launch_one<128, 128, 2, 2, true, true, true, false, true>(d, g.batch, st);
-        return vec ? launch_one<128, 128, 2, 2, true, true, false, true, true>(d, g.batch, st)
-                   : launch_one<128, 128, 2, 2, true, true, false, false, true>(d, g.batch, st);
-      }
+      if (obf) return vec ? launch_pp<true, true, true, true, true>(d, g.batch, st) : launch_pp<true, true, true, false, true>(d, g.batch, st);
+      return vec ? launch_pp<true, true, false, true, true>(d, g.batch, st) : launch_pp<true, true, false, false, true>(d, g.batch, st);
     } else {
       return hipErrorInvalidValue;
     }
   }
-  if constexpr (BIG) {
-    if (obf) return vec ? launch_pp<AKC, BKC, true, true>(d, g.batch, st) : launch_pp<AKC, BKC, true, false>(d, g.batch, st);
-    return vec ? launch_pp<AKC, BKC, false, true>(d, g.batch, st) : launch_pp<AKC, BKC, false, false>(d, g.batch, st);
-  } else {
-    if (obf)
-      return vec ? launch_one<128, 128, 2, 2, AKC, BKC, true, true>(d, g.batch, st)
-                 : launch_one<128, 128, 2, 2, AKC, BKC, true, false>(d, g.batch, st);
-    return vec ? launch_one<128, 128, 2, 2, AKC, BKC, false, true>(d, g.batch, st)
-               : launch_one<128, 128, 2, 2, AKC, BKC, false, false>(d, g.batch, st);
-  }
-}
-
-template <bool BIG>
-static hipError_t launch_tile(const GemmArgs& g, const GemmDev& d, hipStream_t st) {
-  if (g.a_kc && g.b_kc) return launch_oriented<BIG, true, true>(g, d, st);
-  if (g.a_kc && !g.b_kc) return launch_oriented<BIG, true, false>(g, d, st);
-  if (!g.a_kc && !g.b_kc) return launch_oriented<BIG, false, false>(g, d, st);
-  return hipErrorInvalidValue;  // (A strided, B contiguous) is not used by the path
+  if (obf) return vec ? launch_pp<AKC, BKC, true, true>(d, g.batch, st) : launch_pp<AKC, BKC, true, false>(d, g.batch, st);
+  return vec ? launch_pp<AKC, BKC, false, true>(d, g.batch, st) : launch_pp<AKC, BKC, false, false>(d, g.batch, st);
 }
 
 static bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -1328,12 +1063,14 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, GemmTile tile, hipStream_t st) {
   d.kper = ((ktiles + g.splits - 1) / g.splits) * BK;
   if (g.splits > 1 && !g.dyn_split && (int64_t)(d.kper / BK) * (g.splits - 1) >= ktiles)
     return hipErrorInvalidValue;   // an empty split
-  if (tile == kTile64) return launch_gemm_bf16_small(d, g.a_kc, g.b_kc, g.c_bf16 && g.splits <= 1, st);
+  if (tile != kTile256) return launch_gemm_bf16_tile(d, tile, g.a_kc, g.b_kc, g.c_bf16 && g.splits <= 1, st);
   // Both operands strided in the reduction index (the weight-gradient products): their global rows are
   // 512 contiguous bytes whatever the reduction width, so the ring variant's deeper prefetch is free
   // (measured +7 %); with a reduction-contiguous operand its 64-byte row segments cost more than they hide.
-  if (big_tile && !g.a_kc && !g.b_kc && !d.drop_thr) return launch_ring_oriented<false, false>(g, d, st);
-  return big_tile ? launch_tile<true>(g, d, st) : launch_tile<false>(g, d, st);
+  if (!g.a_kc && !g.b_kc && !d.drop_thr) return launch_ring_oriented<false, false>(g, d, st);
+  if (g.a_kc && g.b_kc) return launch_oriented<true, true>(g, d, st);
+  if (g.a_kc && !g.b_kc) return launch_oriented<true, false>(g, d, st);
+  return hipErrorInvalidValue;  // (A strided, B contiguous) is not used by the path
 }
 
 }  // namespace asx

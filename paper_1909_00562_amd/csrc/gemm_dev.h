@@ -95,7 +95,7 @@ struct DirectLoader {
   }
 };
 
-// the 64 x 64 kernel (gemm_small.hip); d as launch_gemm_bf16 has filled it in
-hipError_t launch_gemm_bf16_small(const GemmDev& d, bool a_kc, bool b_kc, bool out_bf16, hipStream_t st);
+// the 64 x 64 and 128 x 128 kernel (gemm_tile.hip); d as launch_gemm_bf16 has filled it in
+hipError_t launch_gemm_bf16_tile(const GemmDev& d, GemmTile tile, bool a_kc, bool b_kc, bool out_bf16, hipStream_t st);
 
 }  // namespace asx

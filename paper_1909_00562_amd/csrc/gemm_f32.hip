@@ -440,7 +440,7 @@ hipError_t launch_splitk_combine(const GemmArgs& g, bool in_bf16, hipStream_t st
 }
 
 // ---- planner ----------------------------------------------------------------
-// Cost model (seconds) used to pick the block tile and the reduction split of a bf16
+// Cost model (seconds) used to pick 256x256 tiles, or smaller ones, and the reduction split of a bf16
 // product on a 256-CU part: blocks run in rounds of `slots` (one 256x256 block or
 // two 128x128 blocks per CU); a round costs the block's flops at the per-CU rate
 // the kernel sustains plus a fixed prologue/epilogue; a split adds the round trip
@@ -458,30 +458,30 @@ static double plan_cost(int M, int N, int K, int batch, int tile, int splits) {
   return t;
 }
 
-// Microseconds of the 128 x 128 kernel by what it measures at few tiles, where the model above is far off (it was made
-// for full rounds): per reduction tile 0.6 (NT) or 1.07 (a transposed operand) while a block has a compute unit to
-// itself, 1.07 / 1.55 with two.  128 x 1024 x 1024 NT 15.5, NN 22.7; 6400 x 1024 x 1024 NT 22.7, NN 29.5.
+// Microseconds of the kernels of gemm_tile.hip, from what they measure.  A split adds the round trip of its partial sums
+// and a launch.
 static double plan_split_us(int M, int N, int batch, int splits) {
-  return splits > 1 ? 2.0 * splits * (double)M * N * batch * 4.0 / 4e6 + 8.0 : 0.0;
+  return splits > 1 ? 2.0 * splits * (double)M * N * batch * 4.0 / 4e6 + 6.0 : 0.0;
 }
-static double plan_us_128(GemmForm form, int M, int N, int ktiles, int batch, int splits) {
-  const int64_t blocks = (int64_t)((M + 127) / 128) * ((N + 127) / 128) * batch * splits;
-  const int64_t rounds = (blocks + 511) / 512;
-  const double tile = blocks <= 256 ? (form == kFormNT ? 0.6 : 1.07) : (form == kFormNT ? 1.07 : 1.55);
-  return rounds * (tile * ((ktiles + splits - 1) / splits) + 5.0) + plan_split_us(M, N, batch, splits);
-}
-// The 64 x 64 kernel: 0.26 us per reduction tile and compute unit however many blocks share it (its LDS traffic), one
-// more per block for prologue and write-out, 5.5 per launch; a split costs it 5 for the combine launch.  Measured against
-// this: 1920 x 512 x 1024 NN 10.6 (10.7), 128 x 1024 x 3072 NT 17.7 (19), 1024 x 1024 x 6400 TN 35 (33), 2257 x 1000 x
-// 1000 NN 22 (21), 6400 x 1024 x 3072 NT 90 (93; the 128 x 128 kernel takes 60).
+// 64 x 64: 0.26 us per reduction tile and compute unit however many blocks share it, 0.8 per block.  (1920 x 512 x 1024 NN
+// 9.7 measured, 10.0 by this; 128 x 1024 x 3072 NT 17, 18.3; 2257 x 1000 x 1000 NN 20.6, 20.1; 1024 x 1024 x 6400 TN 34.7,
+// 31.8; 6400 x 1024 x 3072 NT 90, 98.)
 static double plan_us_64(int M, int N, int ktiles, int batch, int splits) {
   const int64_t blocks = (int64_t)((M + 63) / 64) * ((N + 63) / 64) * batch * splits;
-  const int64_t rounds = (blocks + 255) / 256;
-  return rounds * (0.26 * ((ktiles + splits - 1) / splits) + 1.0) + 5.5 +
-         (splits > 1 ? plan_split_us(M, N, batch, splits) - 3.0 : 0.0);
+  return (double)((blocks + 255) / 256) * (0.26 * ((ktiles + splits - 1) / splits) + 0.8) + 5.0 +
+         plan_split_us(M, N, batch, splits);
+}
+// 128 x 128: 0.7 us per reduction tile with a compute unit to itself, 1.05 with two blocks on one.  (2257 x 1000 x 1000 NN
+// 18.6, 18.2; 6400 x 1024 x 1024 NN 24.9, 25.3, NT 24.0, 25.3; x 2048 NN 41.3, 42.1; 16000 x 512 x 1286 TN 31.5, 30.5;
+// 1286 x 16000 x 512 NT 44.6, 39.7, the 256 x 256 kernel 41.)
+static double plan_us_128(int M, int N, int ktiles, int batch, int splits) {
+  const int64_t blocks = (int64_t)((M + 127) / 128) * ((N + 127) / 128) * batch * splits;
+  const int k = (ktiles + splits - 1) / splits;
+  const double t = blocks <= 256 ? 0.7 * k + 1.5 : (double)((blocks + 511) / 512) * (1.05 * k + 3.0);
+  return t + 5.5 + plan_split_us(M, N, batch, splits);
 }
 
-GemmPlan gemm_plan(GemmForm form, int M, int N, int K, int batch, bool bf16, bool allow_split, bool multi_segment) {
+GemmPlan gemm_plan(int M, int N, int K, int batch, bool bf16, bool allow_split, bool multi_segment) {
   GemmPlan pl;
   pl.tile = kTile128;
   pl.splits = 1;
@@ -522,23 +522,26 @@ GemmPlan gemm_plan(GemmForm form, int M, int N, int K, int batch, bool bf16, boo
       }
     }
   }
-  // 64 x 64 tiles where they are at least a tenth faster than the plan so far
-  const double old = pl.tile == kTile128 ? plan_us_128(form, M, N, ktiles, batch, pl.splits) : best * 1e6;
-  double best64 = 1e30;
-  int splits64 = 1;
+  // Which of the two shapes of gemm_tile.hip, if not 256 x 256.  With more than a round of 256 x 256 tiles that kernel
+  // stays: it writes a tile while the next one is on its way, which the models leave out (2257 x 32003 x 1000: 174 us, 231
+  // with 128 x 128, 184 by the model).
+  double now = 1e30;
+  if (pl.tile == kTile256) {
+    if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) * batch * pl.splits > 256) return pl;
+    now = 0.9 * best * 1e6;
+  }
   const int smax = allow_split ? (ktiles / 4 < 32 ? (ktiles / 4 > 1 ? ktiles / 4 : 1) : 32) : 1;
   for (int want = 1; want <= smax; ++want) {
     const int per = (ktiles + want - 1) / want, s = (ktiles + per - 1) / per;
     if (s != want) continue;
-    const double c = plan_us_64(M, N, ktiles, batch, s);
-    if (c < best64) {
-      best64 = c;
-      splits64 = s;
+    for (int tile = 64; tile <= 128; tile += 64) {
+      const double c = tile == 64 ? plan_us_64(M, N, ktiles, batch, s) : plan_us_128(M, N, ktiles, batch, s);
+      if (c < now) {
+        now = c;
+        pl.tile = tile == 64 ? kTile64 : kTile128;
+        pl.splits = s;
+      }
     }
-  }
-  if (best64 < 0.9 * old) {
-    pl.tile = kTile64;
-    pl.splits = splits64;
   }
   return pl;
 }

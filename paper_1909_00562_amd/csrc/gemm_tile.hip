@@ -1,0 +1,352 @@
+// bf16 products that do not fill the 256 x 256 kernels (gfx950): square block tiles of 64 or 128, an NST-stage LDS ring.
+//
+// 64 x 64 tiles, four stages: a product of a hundred rows and a thousand columns is 8 tiles of 128 x 128, each of which
+// walks the whole reduction on one compute unit while the others idle; there are four times as many blocks with a
+// quarter of the work per reduction tile.  0.26 us per 64 reduction elements and compute unit, its LDS traffic (16 KiB in,
+// 32 KiB out), however many blocks share it.
+// 128 x 128 tiles: 0.7 us per 64 reduction elements with a compute unit to itself (four stages), 1.05 for two blocks that
+// share one (two stages each: 64 KiB of LDS per block); LDS traffic again, 32 KiB in and 64 KiB out, before the matrix
+// cores.  Rates and the choice between the shapes: gemm_plan.
+// Loads go HBM -> LDS directly in every orientation, NST - 1 tiles ahead, one barrier per tile, no branch and the same
+// number of loads in flight at every wait (past the last tile they read out of range, i.e. zeros).  (The form this
+// replaced transposed strided operands in registers: 6400 x 1024 x 2048 NN 56 us against 41, 16000 x 512 x 1286 TN
+// 51 against 31; NT 60 against 55 at 6400 x 1024 x 3072, 22.6 against 24.0 at a third of that.)
+//   * reduction-contiguous operand: LDS [rows][64 k] as in gemm_bf16.hip;
+//   * strided operand: LDS [64 k][columns] as in memory, fragments by transposing reads.  A 16-lane group reads four
+//     k-rows x 32 bytes; the 32-byte segments of a row are XOR-swizzled so that the four land in different banks.
+#include "common.h"
+#include "gemm.h"
+#include "gemm_dev.h"
+
+#include <type_traits>
+
+namespace asx {
+
+// 64 k-rows x COLS columns of a strided operand, 1 KiB per wave-wide load
+template <int COLS> struct StridedLoader {
+  static constexpr int RPL = 512 / COLS, NL = COLS / 32;   // k-rows per load, loads per wave
+  uint32_t voff[NL];
+  int k;
+  // 32-byte segments of k-row k are stored at segment ^ swizzle(k)
+  static __device__ __forceinline__ int swizzle(int k) { return COLS == 64 ? (k >> 1) & 3 : k & 3; }
+  __device__ __forceinline__ void init(int64_t ld, int cols_left, int wave, int lane) {
+    constexpr int CPR = COLS / 8;   // 16-byte chunks of a row
+    k = RPL * wave + lane / CPR;
+    const int pc = lane % CPR, seg = (pc >> 1) ^ swizzle(lane / CPR);   // (4 RPL j and RPL wave are multiples of 4)
+    const int col = (seg * 2 + (pc & 1)) * 8;
+#pragma unroll
+    for (int j = 0; j < NL; ++j)
+      voff[j] = col < cols_left ? (uint32_t)(((int64_t)(k + 4 * RPL * j) * ld + col) * 2) : kOob;
+  }
+  __device__ __forceinline__ void load(int j, const __amdgpu_buffer_rsrc_t& rs, int k_left, unsigned char* lds_tile,
+                                       int wave) const {
+    const uint32_t off = k + 4 * RPL * j < k_left ? voff[j] : kOob;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(lds_tile + (wave + 4 * j) * 1024), 16, off, 0, 0, 0);
+  }
+};
+
+// Fragment of the 16x16x32 instruction: 16 rows (columns) from row0 on x 32 reduction elements, step ks of the tile.
+template <bool KC, int COLS> __device__ __forceinline__ uint32_t gs_frag_base(int row0, int lane) {
+  if constexpr (KC) {
+    const int row = row0 + (lane & 15);
+    return (uint32_t)(row * ROWB + (((lane >> 4) ^ (row & 7) ^ ((row >> 3) & 1)) << 4));
+  } else {
+    const int k = (lane >> 4) * 8 + ((lane & 15) >> 2);   // this lane presents four columns of k-rows k and k + 4
+    const int cb = (row0 + (lane & 3) * 4) * 2;
+    return (uint32_t)(k * COLS * 2 + (((cb >> 5) ^ StridedLoader<COLS>::swizzle(k)) << 5) + (cb & 31));
+  }
+}
+template <bool KC, int COLS> __device__ __forceinline__ bf16x8_t gs_frag(const unsigned char* tile, uint32_t base, int ks) {
+  if constexpr (KC) {
+    return *reinterpret_cast<const bf16x8_t*>(tile + (base ^ (uint32_t)(ks << 6)));
+  } else {
+    constexpr uint32_t flip = COLS == 64 ? 64u : 0u;      // k-row k + 4 has another swizzle in 128-byte rows
+    union { s16x4_t h[2]; bf16x8_t v; } u;
+    u.h[0] = lds_read_tr((lds_s16x4_t*)(lds_void_t*)(tile + base + ks * COLS * 64));
+    u.h[1] = lds_read_tr((lds_s16x4_t*)(lds_void_t*)(tile + (base ^ flip) + ks * COLS * 64 + COLS * 8));
+    return u.v;
+  }
+}
+
+// Epilogue of four consecutive columns of a row, in whole vectors
+__device__ __forceinline__ void gs_finish4(const GemmDev& p, int out_bf16, int batch, int row, int col, f32x4_t v,
+                                           const f32x4_t& bias4) {
+  const int64_t ci = (int64_t)batch * p.sC + (int64_t)row * p.ldc + col;
+  v += bias4;
+  if (p.act_tanh) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = tanhf(v[e]);
+  }
+  f32x4_t dact = 1.f - v * v;
+  if (p.drop_thr) {
+    uint32_t w[4];
+    dropout_words4(((uint64_t)row * p.N + col) >> 2, p.drop_seed, w);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float m = w[e] >= p.drop_thr ? p.drop_scale : 0.f;
+      v[e] *= m;
+      dact[e] *= m;
+    }
+  }
+  if (p.gate) v *= *reinterpret_cast<const f32x4_t*>(p.gate + (int64_t)row * p.ldg + col);
+  if (p.C_dact) *reinterpret_cast<f32x4_t*>(p.C_dact + ci) = dact;
+  if (out_bf16) {
+    uint32_t hb[4];
+    float lo[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      hb[e] = f32_to_bf16_bits(v[e]);
+      lo[e] = v[e] - bf16_bits_to_f32(hb[e]);
+    }
+    const u32x2_t o = {hb[0] | (hb[1] << 16), hb[2] | (hb[3] << 16)};
+    *reinterpret_cast<u32x2_t*>(reinterpret_cast<uint16_t*>(p.C) + ci) = o;
+    if (p.C_lo) {
+      const u32x2_t ol = {pack_bf16(lo[0], lo[1]), pack_bf16(lo[2], lo[3])};
+      *reinterpret_cast<u32x2_t*>(p.C_lo + ci) = ol;
+    }
+  } else {
+    float* C = reinterpret_cast<float*>(p.C) + ci;
+    if (p.accumulate) v += *reinterpret_cast<const f32x4_t*>(C);
+    *reinterpret_cast<f32x4_t*>(C) = v;
+  }
+}
+// The same element by element: nc columns inside, nothing aligned
+__device__ __forceinline__ void gs_finish_ragged(const GemmDev& p, int out_bf16, int batch, int z, int row, int col,
+                                                 const f32x4_t& v) {
+  const int nc = p.N - col < 4 ? p.N - col : 4;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if (e >= nc) continue;
+    float x = v[e];
+    if (p.splits > 1) {
+      p.partial[((int64_t)z * p.M + row) * p.N + col + e] = x;
+      continue;
+    }
+    if (p.bias) x += bf16_bits_to_f32(p.bias[col + e]);
+    if (p.act_tanh) x = tanhf(x);
+    float dact = 1.f - x * x;
+    if (p.drop_thr) {
+      const float m = dropout_mult((uint64_t)row * p.N + col + e, p.drop_seed, p.drop_thr, p.drop_scale);
+      x *= m;
+      dact *= m;
+    }
+    if (p.gate) x *= p.gate[(int64_t)row * p.ldg + col + e];
+    const int64_t ci = (int64_t)batch * p.sC + (int64_t)row * p.ldc + col + e;
+    if (p.C_dact) p.C_dact[ci] = dact;
+    if (out_bf16) {
+      const uint32_t hb = f32_to_bf16_bits(x);
+      reinterpret_cast<uint16_t*>(p.C)[ci] = (uint16_t)hb;
+      if (p.C_lo) p.C_lo[ci] = (uint16_t)f32_to_bf16_bits(x - bf16_bits_to_f32(hb));
+    } else {
+      float* C = reinterpret_cast<float*>(p.C);
+      C[ci] = p.accumulate ? x + C[ci] : x;
+    }
+  }
+}
+
+template <int TW, bool AKC, bool BKC, int NST>
+__global__ __launch_bounds__(256) void gemm_bf16_tile_kernel(GemmDev p, int out_bf16) {
+  constexpr int BM = 32 * TW, TILE = BM * ROWB, STAGE = 2 * TILE;   // square block tile; bytes of an operand tile, a stage
+  constexpr int NL = TW, LD = BM + 4;                               // loads per wave, operand and tile; staging row (floats)
+  static_assert((NST & (NST - 1)) == 0 && NST * STAGE >= 64 * LD * 4, "ring of a power of two; write-out staging");
+  extern __shared__ __align__(1024) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = (wave >> 1) * 16 * TW, wn = (wave & 1) * 16 * TW;
+  const int Mv = dev_bound(p.M_dev, p.M), K0 = dev_bound(p.K_dev, p.K[0]);
+  const int tiles_m = (Mv + BM - 1) / BM, nt = tiles_m * p.tiles_n;   // the grid was sized for p.M
+  int pid = blockIdx.x;
+  if (pid >= nt) return;                                          // the whole block, before any barrier
+  {  // each XCD gets a contiguous run of tiles, walked in groups of 8 tile rows
+    const int xcd = pid & 7, idx = pid >> 3, per = nt >> 3, rem = nt & 7;
+    pid = xcd * per + (xcd < rem ? xcd : rem) + idx;
+  }
+  const int gid = pid / (8 * p.tiles_n), first_m = gid * 8;
+  const int gm = tiles_m - first_m < 8 ? tiles_m - first_m : 8;
+  const int in_g = pid - gid * 8 * p.tiles_n;
+  const int m0 = (first_m + in_g % gm) * BM, n0 = (in_g / gm) * BM;
+  const int z = blockIdx.z, batch = z / p.splits, split = z - batch * p.splits;
+
+  // reduction tiles of this block: [t0, t1) of the sequence that runs through the segments one after the other
+  int nk = 0, seg = 0, skip = 0;
+#pragma unroll
+  for (int s = 0; s < kMaxSeg; ++s) nk += ((s == 0 ? K0 : p.K[s]) + BK - 1) / BK;
+  if (p.splits > 1) {
+    const int per = p.K_dev ? (nk + p.splits - 1) / p.splits : p.kper / BK;
+    skip = split * per;
+    nk = nk - skip < per ? nk - skip : per;
+    for (int left = (K0 + BK - 1) / BK; seg < kMaxSeg - 1 && skip >= left; left = (p.K[seg] + BK - 1) / BK) {
+      skip -= left;
+      ++seg;
+    }
+  }
+  typename std::conditional<AKC, DirectLoader<BM, 4>, StridedLoader<BM>>::type la;
+  typename std::conditional<BKC, DirectLoader<BM, 4>, StridedLoader<BM>>::type lb;
+  la.init(p.lda[0], Mv - m0, wave, lane);
+  lb.init(p.ldb[0], p.N - n0, wave, lane);
+  const int64_t stepA = AKC ? BK : BK * p.lda[0], stepB = BKC ? BK : BK * p.ldb[0];
+  const int64_t offA = AKC ? (int64_t)m0 * p.lda[0] : m0, offB = BKC ? (int64_t)n0 * p.ldb[0] : n0;
+  int k_left = (seg == 0 ? K0 : p.K[seg]) - skip * BK;
+  const uint16_t* cA = p.A[seg] + (int64_t)batch * p.sA[seg] + offA + skip * stepA;
+  const uint16_t* cB = p.B[seg] + (int64_t)batch * p.sB[seg] + offB + skip * stepB;
+  auto issue = [&](int stage) {   // the tile under the cursor
+    if (k_left <= 0) {            // on to the next segment, if there is one
+      do { ++seg; } while (seg < kMaxSeg && p.K[seg] <= 0);
+      if (seg < kMaxSeg) {
+        cA = p.A[seg] + (int64_t)batch * p.sA[seg] + offA;
+        cB = p.B[seg] + (int64_t)batch * p.sB[seg] + offB;
+        k_left = p.K[seg];
+      } else {
+        seg = kMaxSeg - 1;        // all loads below are out of range
+      }
+    }
+    const __amdgpu_buffer_rsrc_t ra = make_rsrc(cA), rb = make_rsrc(cB);
+    unsigned char* as = smem + stage * STAGE;
+#pragma unroll
+    for (int j = 0; j < NL; ++j) la.load(j, ra, k_left, as, wave);
+#pragma unroll
+    for (int j = 0; j < NL; ++j) lb.load(j, rb, k_left, as + TILE, wave);
+    cA += stepA;
+    cB += stepB;
+    k_left -= BK;
+  };
+  uint32_t fa[TW], fb[TW];
+#pragma unroll
+  for (int i = 0; i < TW; ++i) {
+    fa[i] = gs_frag_base<AKC, BM>(wm + 16 * i, lane);
+    fb[i] = gs_frag_base<BKC, BM>(wn + 16 * i, lane);
+  }
+  f32x4_t acc[TW][TW];
+#pragma unroll
+  for (int i = 0; i < TW; ++i)
+#pragma unroll
+    for (int j = 0; j < TW; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+
+  // s_waitcnt vmcnt: 2 NL loads per wave and tile, the oldest tile has landed
+  constexpr int kFly = 2 * NL * (NST - 2), kWaitOldest = (kFly & 15) | ((kFly >> 4) << 14) | 0x0f70;
+  for (int t = 0; t < NST - 1; ++t) issue(t);
+  for (int t = 0; t < nk; ++t) {
+    __builtin_amdgcn_s_waitcnt(kWaitOldest);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();   // tile t is in LDS, and every wave is done with tile t - 1, whose stage is refilled
+    __builtin_amdgcn_sched_barrier(0);
+    issue((t + NST - 1) & (NST - 1));
+    const unsigned char* as = smem + (t & (NST - 1)) * STAGE;
+    bf16x8_t a[2][TW], b[2][TW];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < TW; ++i) {
+        a[ks][i] = gs_frag<AKC, BM>(as, fa[i], ks);
+        b[ks][i] = gs_frag<BKC, BM>(as + TILE, fb[i], ks);
+      }
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < TW; ++i)
+#pragma unroll
+        for (int j = 0; j < TW; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks][i], b[ks][j], acc[i][j], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+
+  // write-out through LDS, rows of 64 columns; the loads past the last tile have to land before their stages are reused
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  float* stage = reinterpret_cast<float*>(smem);
+  const int q = lane >> 4, c = lane & 15;
+  constexpr int VPR = BM / 4;                 // groups of four columns per row
+  const int col = n0 + (tid % VPR) * 4;
+  const bool fuse = p.splits <= 1;
+  const bool plain = p.vec_ok && (!fuse || (!p.act_tanh && !p.drop_thr && !p.gate && !p.C_lo && !p.C_dact));
+  f32x4_t bias4 = {0.f, 0.f, 0.f, 0.f};
+  if (fuse && p.bias)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (col + e < p.N) bias4[e] = bf16_bits_to_f32(p.bias[col + e]);
+  constexpr int RP = 256 / VPR, RU = 4;       // rows per sweep of the block, sweeps whose reads go together
+#pragma unroll 1
+  for (int half = 0; half < BM / 64; ++half) {   // 64 rows at a time
+    if (wm / 64 == half) {
+#pragma unroll
+      for (int i = 0; i < TW; ++i)
+#pragma unroll
+        for (int j = 0; j < TW; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) stage[(wm % 64 + 16 * i + 4 * q + r) * LD + wn + 16 * j + c] = acc[i][j][r];
+    }
+    __syncthreads();
+    const int left = Mv - m0 - half * 64 < 64 ? Mv - m0 - half * 64 : 64;   // rows inside (may be none)
+    if (plain) {   // bias and accumulation only: nothing tested per row but the bounds
+#pragma unroll
+      for (int r0 = 0; r0 < 64; r0 += RU * RP) {
+        f32x4_t v[RU];
+#pragma unroll
+        for (int u = 0; u < RU; ++u)
+          v[u] = *reinterpret_cast<const f32x4_t*>(stage + (r0 + u * RP + tid / VPR) * LD + (tid % VPR) * 4);
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+          const int r = r0 + u * RP + tid / VPR, row = m0 + half * 64 + r;
+          if (r >= left || col >= p.N) continue;
+          if (!fuse) {
+            *reinterpret_cast<f32x4_t*>(p.partial + ((int64_t)z * p.M + row) * p.N + col) = v[u];
+            continue;
+          }
+          const int64_t ci = (int64_t)batch * p.sC + (int64_t)row * p.ldc + col;
+          v[u] += bias4;
+          if (out_bf16) {
+            const u32x2_t o = {pack_bf16(v[u][0], v[u][1]), pack_bf16(v[u][2], v[u][3])};
+            *reinterpret_cast<u32x2_t*>(reinterpret_cast<uint16_t*>(p.C) + ci) = o;
+          } else {
+            float* C = reinterpret_cast<float*>(p.C) + ci;
+            if (p.accumulate) v[u] += *reinterpret_cast<const f32x4_t*>(C);
+            *reinterpret_cast<f32x4_t*>(C) = v[u];
+          }
+        }
+      }
+    } else if (col < p.N) {
+#pragma unroll 1
+      for (int r0 = tid / VPR; r0 < left; r0 += RP) {
+        const int row = m0 + half * 64 + r0;
+        const f32x4_t v = *reinterpret_cast<const f32x4_t*>(stage + r0 * LD + (tid % VPR) * 4);
+        if (p.vec_ok) gs_finish4(p, out_bf16, batch, row, col, v, bias4);
+        else gs_finish_ragged(p, out_bf16, batch, z, row, col, v);
+      }
+    }
+    if (half + 1 < BM / 64) __syncthreads();
+  }
+}
+
+template <int TW, bool AKC, bool BKC, int NST>
+static hipError_t launch_tile_shape(const GemmDev& d, int out_bf16, hipStream_t st) {
+  constexpr int BM = 32 * TW, smem = NST * 2 * BM * ROWB;
+  auto kfn = gemm_bf16_tile_kernel<TW, AKC, BKC, NST>;
+  static bool attr_set = false;
+  if (!attr_set) {
+    const hipError_t e =
+        hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  const dim3 grid((d.M + BM - 1) / BM * d.tiles_n, 1, d.nz);
+  hipLaunchKernelGGL(kfn, grid, dim3(256), smem, st, d, out_bf16);
+  return hipGetLastError();
+}
+
+template <bool AKC, bool BKC>
+static hipError_t launch_tile_form(const GemmDev& d, GemmTile tile, int out_bf16, hipStream_t st) {
+  if (tile == kTile64) return launch_tile_shape<2, AKC, BKC, 4>(d, out_bf16, st);
+  // 128 KiB of LDS where no compute unit gets a second block anyway
+  if ((int64_t)d.tiles_m * d.tiles_n * d.nz <= 256) return launch_tile_shape<4, AKC, BKC, 4>(d, out_bf16, st);
+  return launch_tile_shape<4, AKC, BKC, 2>(d, out_bf16, st);
+}
+hipError_t launch_gemm_bf16_tile(const GemmDev& d, GemmTile tile, bool a_kc, bool b_kc, bool out_bf16, hipStream_t st) {
+  if (a_kc && b_kc) return launch_tile_form<true, true>(d, tile, out_bf16, st);
+  if (a_kc && !b_kc) return launch_tile_form<true, false>(d, tile, out_bf16, st);
+  if (!a_kc && !b_kc) return launch_tile_form<false, false>(d, tile, out_bf16, st);
+  return hipErrorInvalidValue;  // (A strided, B contiguous) is not used by the path
+}
+
+}  // namespace asx

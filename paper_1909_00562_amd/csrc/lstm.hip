@@ -101,19 +101,19 @@ LsLayout make_ls_layout(const ls_shape* s) {
   auto mx = [&](size_t v) { if (v > pb) pb = v; };
   for (int l = 0; l < NL; ++l) {
     const int Il = l == 0 ? I : H;
-    L.p_dwi.push_back(gemm_plan(kFormTN, 4 * H, Il, TB, 1, bf, true));
+    L.p_dwi.push_back(gemm_plan(4 * H, Il, TB, 1, bf, true));
     mx(gemm_partial_bytes(4 * H, Il, 1, L.p_dwi.back().splits));
   }
   // The reduction split of the gradient of x is a function of the widths alone: with a split chosen from the row
   // count, a sentence's gradients would depend (in the last fp32 bit) on how many sentences share its batch.
-  L.p_dx = gemm_plan(kFormNN, TB, I, 4 * H, 1, bf, false);
+  L.p_dx = gemm_plan(TB, I, 4 * H, 1, bf, false);
   if (bf) {
     const int ktiles = (4 * H + 63) / 64, want = I >= 1024 ? 2 : 4;
     L.p_dx.splits = ktiles / 8 < 1 ? 1 : (ktiles / 8 < want ? ktiles / 8 : want);
     L.p_dx.tile = kTile256;
   }
   mx(gemm_partial_bytes(TB, I, 1, L.p_dx.splits));
-  L.p_dwh = gemm_plan(kFormTN, 4 * H, H, TB, 1, bf, true);
+  L.p_dwh = gemm_plan(4 * H, H, TB, 1, bf, true);
   mx(gemm_partial_bytes(4 * H, H, 1, L.p_dwh.splits));
   L.gates = take((size_t)NL * TB * 4 * H * 4);
   L.cs = take((size_t)NL * (T + 1) * L.BH * 4);
