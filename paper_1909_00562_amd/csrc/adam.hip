@@ -1,7 +1,8 @@
 // Fused Adam update of one parameter tensor (paper section 4.2, "Parameter
 // settings"; Kingma and Ba, Algorithm 1).  One streaming pass: per element 16
 // bytes read (gradient, both moments, master weight), 12 written back and the
-// 2- or 4-byte copy in the storage type of the forward pass; HBM-bound.
+// 2- or 4-byte copy in the storage type of the forward pass; HBM-bound.  Nothing but
+// that copy is read again soon: the other streams go past the caches (195 -> 175 us at 32.8M elements).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -24,16 +25,17 @@ __global__ __launch_bounds__(256) void adam_step_kernel(size_t n4, size_t n, con
   };
   const size_t stride = (size_t)gridDim.x * 256;
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += stride) {
-    const f32x4_t g4 = reinterpret_cast<const f32x4_t*>(grad)[i];
-    f32x4_t m4 = reinterpret_cast<f32x4_t*>(m)[i], v4 = reinterpret_cast<f32x4_t*>(v)[i];
-    f32x4_t w4 = reinterpret_cast<f32x4_t*>(master)[i];
+    const f32x4_t g4 = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(grad) + i);
+    f32x4_t m4 = __builtin_nontemporal_load(reinterpret_cast<f32x4_t*>(m) + i);
+    f32x4_t v4 = __builtin_nontemporal_load(reinterpret_cast<f32x4_t*>(v) + i);
+    f32x4_t w4 = __builtin_nontemporal_load(reinterpret_cast<f32x4_t*>(master) + i);
     float mm[4] = {m4[0], m4[1], m4[2], m4[3]}, vv[4] = {v4[0], v4[1], v4[2], v4[3]};
     float w[4] = {w4[0], w4[1], w4[2], w4[3]};
 #pragma unroll
     for (int c = 0; c < 4; ++c) upd(g4[c], mm[c], vv[c], w[c]);
-    reinterpret_cast<f32x4_t*>(m)[i] = f32x4_t{mm[0], mm[1], mm[2], mm[3]};
-    reinterpret_cast<f32x4_t*>(v)[i] = f32x4_t{vv[0], vv[1], vv[2], vv[3]};
-    reinterpret_cast<f32x4_t*>(master)[i] = f32x4_t{w[0], w[1], w[2], w[3]};
+    __builtin_nontemporal_store(f32x4_t{mm[0], mm[1], mm[2], mm[3]}, reinterpret_cast<f32x4_t*>(m) + i);
+    __builtin_nontemporal_store(f32x4_t{vv[0], vv[1], vv[2], vv[3]}, reinterpret_cast<f32x4_t*>(v) + i);
+    __builtin_nontemporal_store(f32x4_t{w[0], w[1], w[2], w[3]}, reinterpret_cast<f32x4_t*>(master) + i);
     if constexpr (HAS_OUT) {
       if constexpr (OUT_BF16)
         reinterpret_cast<uint2*>(wout)[i] = make_uint2(pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3]));
@@ -61,7 +63,9 @@ hipError_t launch_adam_step(size_t n, const float* grad, float* master, float* m
                             float inv_bc2, hipStream_t st) {
   const size_t n4 = n / 4;
   size_t blocks = (n4 + 255) / 256;
-  if (blocks > 256 * 16) blocks = 256 * 16;   // 16 resident blocks per CU, grid-stride beyond
+  // One vector per thread: blocks that come and go keep the streams in step, a grid-stride loop of resident blocks drifts
+  // apart.  32.8M elements: 16 blocks per compute unit 195 us, 64 of them 162, one vector each 157 (983 MB, 6.3 TB/s).
+  if (blocks > (size_t)1 << 20) blocks = (size_t)1 << 20;
   if (blocks < 1) blocks = 1;
   dim3 grid((unsigned)blocks), blk(256);
 #define ASX_ADAM(BF, HO) \
