@@ -461,7 +461,7 @@ static double plan_cost(int M, int N, int K, int batch, int tile, int splits) {
 // Microseconds of the kernels of gemm_tile.hip, from what they measure.  A split adds the round trip of its partial sums
 // and a launch.
 static double plan_split_us(int M, int N, int batch, int splits) {
-  return splits > 1 ? 2.0 * splits * (double)M * N * batch * 4.0 / 4e6 + 6.0 : 0.0;
+  return splits > 1 ? 2.0 * splits * (double)M * N * batch * 4.0 / 4e6 + 4.5 : 0.0;
 }
 // 64 x 64: 0.26 us per reduction tile and compute unit however many blocks share it, 0.8 per block.  (1920 x 512 x 1024 NN
 // 9.7 measured, 10.0 by this; 128 x 1024 x 3072 NT 17, 18.3; 2257 x 1000 x 1000 NN 20.6, 20.1; 1024 x 1024 x 6400 TN 34.7,
