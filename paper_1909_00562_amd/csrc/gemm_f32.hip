@@ -487,14 +487,14 @@ GemmPlan gemm_plan(int M, int N, int K, int batch, bool bf16, bool allow_split, 
   pl.splits = 1;
   if (!bf16) {
     if (multi_segment) allow_split = false;
-    // fp32 path: split while there are fewer than ten 32 x 32 blocks per compute unit, down to four reduction tiles
-    // per split.  Measured (1 / 2 / 4 / 8 splits): 1286 x 512 x 16000 531 / 507 / 453 / 431 us, 512 x 512 x 1920
+    // fp32 path: split while there are fewer than ten 32 x 32 blocks per compute unit, down to eight reduction tiles
+    // per split (a split's sums are rounded to fp32: no more of them than the speed is worth).  Measured (1 / 2 / 4 / 8 splits): 1286 x 512 x 16000 531 / 507 / 453 / 431 us, 512 x 512 x 1920
     // 35 / 32 / 31 / 33 us, 64 x 512 x 2048 36 / 23 / 16 / 13 us; 16000 x 512 x 1286 (8000 blocks) only loses.
     const int64_t tiles = (int64_t)((M + 31) / 32) * ((N + 31) / 32) * batch;
     if (allow_split) {
       const int ktiles = (K + FK - 1) / FK;
       int64_t want = 2560 / tiles;
-      const int64_t cap = ktiles / 4;
+      const int64_t cap = ktiles / 8;
       if (want > cap) want = cap;
       if (want > 32) want = 32;
       if (want > 1) {
