@@ -429,12 +429,8 @@ static as_status fwd_impl(const as_shape* s, const void* h_dec, const void* h_en
     g.C_lo = w + L.q_lo;
     AS_TRY(AS_STAGE_GEMM_Q, launch_gemm(g, bf, L.p_q.tile, st));
   }
-  const bool one_step = bf && attn_one_step_supported(T, S, H);   // the backward pass decides alike
-  if (one_step) {
-    AS_TRY(AS_STAGE_ATTN_SCORE,
-           launch_attn_one_step_fwd(w + L.q, w + L.q_lo, he, src_len, B, S, H, reinterpret_cast<float*>(w + L.alpha32),
-                                    w + L.ctx, w + L.ctx_lo, attn_mask, st));
-  } else if (bf && attn_fwd_fused_supported(S, H)) {
+  // (T = 1 too: a step by itself gives the same bits as in a batch of steps, which the row sums of attn_step.hip would not)
+  if (bf && attn_fwd_fused_supported(S, H)) {
     // Eq. 2 (second half), 1 and 3 in one kernel per (sentence, 32 decoder steps): the scores stay on chip
     AS_TRY(AS_STAGE_ATTN_SCORE,
            launch_attn_fwd_fused(w + L.q, w + L.q_lo, he, src_len, B, T, S, H, reinterpret_cast<float*>(w + L.alpha32),
@@ -557,7 +553,7 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
     g.C = d_h_dec; g.ldc = H; g.c_bf16 = false;
     AS_TRY(AS_STAGE_GEMM_DCH, launch_gemm(g, bf, L.p_dch.tile, st));
   }
-  const bool one_step = bf && attn_one_step_supported(T, S, H);
+  const bool one_step = bf && attn_one_step_bwd_supported(T, S, H);
   if (one_step) {
     AS_TRY(AS_STAGE_ATTN_BWD,
            launch_attn_one_step_bwd(w + L.dC, w + L.dC_lo, he, src_len, B, S, H,

@@ -3,12 +3,13 @@
 //   score[s] = query[b] . key[s,b]      alpha = softmax_{s < src_len[b]}      ctx = sum_s alpha[s] h_enc[s,b]
 // Per-step mode (decoding, scoring, the input-feeding variant of the paper's section 4, where step t+1 needs the
 // attentional state of step t): query h_t, key K'[s,b,:] = W_a h_enc[s,b,:] (float), computed once per batch of
-// sentences.  Training step with T = 1: query Q = h_dec W_a, key h_enc.  Backward: with query dC, the scores are dalpha;
+// sentences.  Backward of a training step with T = 1: with query dC and key h_enc the scores are dalpha;
 //   dscore = alpha (dalpha - alpha . dalpha)    dQ = sum_s dscore[s] h_enc[s,b]
 //   d_h_enc[s,b] = alpha[s] dC[b] + dscore[s] Q[b]
 // One row per sentence leaves nothing for matrix instructions; what counts is that the sentence's S x H block is
-// requested at once: 16 waves, four source positions per wave in flight (128 x 50 x 1024, bf16: the 32-step kernel of
-// attn_fused.hip, four waves and a tile ahead, takes 29 us forward and 26 backward).
+// requested at once: 16 waves, four source positions per wave in flight.  128 x 50 x 1024, bf16: per-step mode 11 us (19 with
+// eight waves and two positions); backward 14 us, where the 32-step kernel of attn_fused.hip, four waves and a tile ahead,
+// takes 26 and d_h_enc as a batched product of rank one 25.
 #include "common.h"
 #include "kernels.h"
 
@@ -255,21 +256,10 @@ hipError_t launch_attn_step(const void* h_t, const float* kprime, const void* h_
   return e_bf16 ? launch_step<float, uint16_t, false>(p, st) : launch_step<float, float, false>(p, st);
 }
 
-bool attn_one_step_supported(int T, int S, int H) {
+bool attn_one_step_bwd_supported(int T, int S, int H) {
   size_t smem = 0;
   step_groups(S, H, 8, true, smem);
   return T == 1 && H % 8 == 0 && smem <= kStepSmem;
-}
-hipError_t launch_attn_one_step_fwd(const void* q_hi, const void* q_lo, const void* h_enc, const int32_t* src_len, int B,
-                                    int S, int H, float* alpha, void* ctx, void* ctx_lo, uint8_t* attn_mask,
-                                    hipStream_t st) {
-  AttnStep p{};
-  p.query = q_hi; p.query_lo = q_lo;
-  p.key = p.h_enc = h_enc;
-  p.src_len = src_len;
-  p.B = B; p.S = S; p.H = H;
-  p.alpha = alpha; p.ctx = ctx; p.ctx_lo = ctx_lo; p.attn_mask = attn_mask;
-  return launch_step<uint16_t, uint16_t, false>(p, st);
 }
 hipError_t launch_attn_one_step_bwd(const void* dC_hi, const void* dC_lo, const void* h_enc, const int32_t* src_len,
                                     int B, int S, int H, const float* alpha, const void* q_hi, const void* q_lo, void* dQ,

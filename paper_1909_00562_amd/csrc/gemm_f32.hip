@@ -440,11 +440,11 @@ hipError_t launch_splitk_combine(const GemmArgs& g, bool in_bf16, hipStream_t st
 }
 
 // ---- planner ----------------------------------------------------------------
-// Cost model (seconds) used to pick 256x256 tiles, or smaller ones, and the reduction split of a bf16
-// product on a 256-CU part: blocks run in rounds of `slots` (one 256x256 block or
-// two 128x128 blocks per CU); a round costs the block's flops at the per-CU rate
-// the kernel sustains plus a fixed prologue/epilogue; a split adds the round trip
-// of its fp32 partial sums through HBM and one more launch.
+// Cost model (seconds) that decides whether a bf16 product gets 256x256 tiles, and its reduction split then, on a
+// 256-CU part: blocks run in rounds of `slots` (one 256x256 block or two 128x128 blocks per CU); a round costs the
+// block's flops at the per-CU rate the kernel sustains plus a fixed prologue/epilogue; a split adds the round trip
+// of its fp32 partial sums through HBM and one more launch.  The 128x128 rate is that of an earlier kernel: with the
+// present one's it would draw products with several rounds of 256x256 tiles away from the kernel that is faster there.
 static double plan_cost(int M, int N, int K, int batch, int tile, int splits) {
   const double cus = 256.0;
   const double rate = tile == 256 ? 3.9e12 : 1.35e12;      // flop/s of one resident block

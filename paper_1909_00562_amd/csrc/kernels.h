@@ -73,12 +73,9 @@ hipError_t launch_db_reduce(const float* db_partial, int nrb, int V, float* db_o
 hipError_t launch_attn_step(const void* h_t, const float* kprime, const void* h_enc, const int32_t* src_len, int B,
                             int S, int H, float* alpha, void* ctx, void* ctx_lo, bool e_bf16, uint8_t* attn_mask,
                             hipStream_t st);
-// The same for a training step with T = 1, bf16 storage: query Q = h_dec W_a [B,H] as value and remainder, key h_enc.
-// Backward: alpha as saved, dC [B,H] and Q as value and remainder -> dQ [B,H] and d_h_enc [S,B,H] (all of it).
-bool attn_one_step_supported(int T, int S, int H);
-hipError_t launch_attn_one_step_fwd(const void* q_hi, const void* q_lo, const void* h_enc, const int32_t* src_len, int B,
-                                    int S, int H, float* alpha, void* ctx, void* ctx_lo, uint8_t* attn_mask,
-                                    hipStream_t st);
+// Backward pass of attention for a training step with T = 1, bf16 storage: alpha as saved by the forward pass, dC [B,H] and
+// Q = h_dec W_a [B,H] as value and remainder -> dQ [B,H] and d_h_enc [S,B,H] (all of it).
+bool attn_one_step_bwd_supported(int T, int S, int H);
 hipError_t launch_attn_one_step_bwd(const void* dC_hi, const void* dC_lo, const void* h_enc, const int32_t* src_len,
                                     int B, int S, int H, const float* alpha, const void* q_hi, const void* q_lo, void* dQ,
                                     float* d_h_enc, hipStream_t st);
