@@ -267,10 +267,14 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
 #pragma unroll
       for (int j = 0; j < NJ; ++j) M::mma(acc[i][j], wf[slot][i], hf[slot][j]);
     if constexpr (M::kPair) {
+      const uint32_t keep = l == 0 && s >= n0 ? 0u : ~0u;   // x has no remainder: 0 * 0 also where a weight is not finite
 #pragma unroll
-      for (int i = 0; i < NI; ++i)
+      for (int i = 0; i < NI; ++i) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) wf[slot][i][e] &= keep;
 #pragma unroll
         for (int j = 0; j < NJ; ++j) M::mma(acc[i][j], wf[slot][i], lf[slot][j]);
+      }
     }
   };
   constexpr int NP = M::kPair ? 2 : 1, NM = M::kPair ? 2 * NI * NJ : 4 * NI * NJ;

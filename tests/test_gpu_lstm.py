@@ -227,3 +227,20 @@ def test_lstm_dropout_paper_size_sixteen_sentences():
     f, g, _ = run_gpu(inp)
     fo, go = run_oracle(inp)
     compare(inp, f, g, fo, go)
+
+
+@pytest.mark.parametrize("T", [1, 3])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_infinite_input_weight_saturates_its_gate(dtype, T):
+    """The input x is exact in the storage type: an infinite weight of layer 0 makes a pre-activation +-inf, which the
+    cell maps to a saturated gate, and never 0 * inf.  Every output stays finite and equal to the oracle's."""
+    inp = make_lstm_inputs(T, 5, 24, 40, 2, seed=91, dtype=dtype)
+    assert np.all(inp.x != 0)
+    for gate, unit, k, sign in ((0, 3, 2, 1), (1, 17, 9, -1), (2, 39, 23, 1), (3, 0, 0, -1)):
+        inp.W_ih[0][gate * 40 + unit, k] = sign * np.inf
+    f, _, _ = run_gpu(inp)
+    with np.errstate(over="ignore"):
+        fo = lo.forward(inp.x, inp.lengths, inp.W_ih, inp.W_hh, inp.b, inp.h0, inp.c0)
+    for key in ("y", "hT", "cT"):
+        assert np.isfinite(fo[key]).all()
+        pu.assert_close(f[key], fo[key], dtype, key)
