@@ -308,7 +308,8 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
       gf[ii] = ls_sigmoid(a[1]);
       gg[ii] = tanhf(a[2]);
       go[ii] = ls_sigmoid(a[3]);
-      cn[ii] = gf[ii] * cp[k][ii] + gi[ii] * gg[ii];
+      // (which product is rounded by itself is not left to the compiler: block shapes would differ)
+      cn[ii] = __builtin_fmaf(gf[ii], cp[k][ii], gi[ii] * gg[ii]);
       hn[ii] = go[ii] * tanhf(cn[ii]);
     }
     const int64_t idx = (int64_t)b * H + unit0;
