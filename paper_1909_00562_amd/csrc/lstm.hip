@@ -3,11 +3,11 @@
 // points, workspace and schedule.
 //
 // The layer-steps of one wavefront (layer l at step d - l) run as one launch, input
-// product, recurrent product and cell together (lstm_wave.hip).  Backward walks the
-// wavefronts the other way; the weight gradients and the gradient of x are then
-// large products over all steps at once.  Right-padded sentences keep their state at
-// steps t >= lengths[b]; their gate gradients are zero rows, so the large products
-// need no masking.
+// product, recurrent product and cell together (lstm_wave.hip; a wide x has its product
+// over all steps ahead of them).  Backward walks the wavefronts the other way; the weight
+// gradients and the gradient of x are then large products over all steps at once.
+// Right-padded sentences keep their state at steps t >= lengths[b]; their gate gradients
+// are zero rows, so the large products need no masking.
 #include "../../include/lstm_stack.h"
 
 #include <vector>
@@ -33,7 +33,8 @@ struct LsLayout {
   size_t xF, zeros, hF[2], oF[2], dGF;    // fragment tiles; [0] value, [1] remainder (bf16 storage)
   std::vector<size_t> Wf_hh, Wf_ih, Wb_hh, Wb_up;   // weights as tiles, per layer: forward and backward share the space
   std::vector<GemmPlan> p_dwi;
-  GemmPlan p_dwh, p_dx;
+  GemmPlan p_dwh, p_dx, p_gx;
+  bool x_apart;   // the input product of layer 0 ahead of the wavefronts
 };
 
 bool ls_shape_ok(const ls_shape* s) {
@@ -58,7 +59,8 @@ void ls_tile_sizes(const ls_shape* s, LsLayout& L, size_t& off) {
   const size_t nct = ls_batch_tiles(s->B);
   const int copies = sizeof(TE) == 2 ? 2 : 1;
   const size_t gk = 4 * (size_t)ls_gate_stride<TE>(H) / LsGeom<TE>::kKStep;
-  L.x_stride = (int64_t)(ls_ksteps<TE>(I) * nct * kLsTile);
+  L.x_apart = ls_input_apart<TE>(T, s->B, I, H, NL);
+  L.x_stride = L.x_apart ? 0 : (int64_t)(ls_ksteps<TE>(I) * nct * kLsTile);
   L.h_stride = (int64_t)(ls_ksteps<TE>(H) * nct * kLsTile);
   L.g_stride = (int64_t)(gk * nct * kLsTile);
   L.xF = take((size_t)L.x_stride * T);
@@ -72,7 +74,7 @@ void ls_tile_sizes(const ls_shape* s, LsLayout& L, size_t& off) {
   const size_t w0 = off;
   for (int l = 0; l < NL; ++l) {
     L.Wf_hh.push_back(take((size_t)ls_ksteps<TE>(H) * ls_gate_tiles(H) * kLsTile));
-    L.Wf_ih.push_back(take((size_t)ls_ksteps<TE>(l == 0 ? I : H) * ls_gate_tiles(H) * kLsTile));
+    L.Wf_ih.push_back(take((size_t)ls_ksteps<TE>(l > 0 ? H : L.x_apart ? 0 : I) * ls_gate_tiles(H) * kLsTile));
   }
   const size_t end = off;
   off = w0;
@@ -114,6 +116,7 @@ LsLayout make_ls_layout(const ls_shape* s) {
   }
   mx(gemm_partial_bytes(TB, I, 1, L.p_dx.splits));
   L.p_dwh = gemm_plan(4 * H, H, TB, 1, bf, true);
+  L.p_gx = gemm_plan(TB, 4 * H, I, 1, bf, false);
   mx(gemm_partial_bytes(4 * H, H, 1, L.p_dwh.splits));
   L.gates = take((size_t)NL * TB * 4 * H * 4);
   L.cs = take((size_t)NL * (T + 1) * L.BH * 4);
@@ -169,6 +172,7 @@ as_status ls_fwd(const ls_shape* s, const LsLayout& L, const char* x, const int3
   LsFwd f{};
   LsPrepFwd q{};
   f.T = s->T; f.B = s->B; f.I = s->I; f.H = s->H; f.L = s->L;
+  f.x_apart = L.x_apart;
   f.w_rows = ls_reads_weight_rows<TE>(s->T, s->I, s->H, s->L);
   for (int l = 0; l < s->L; ++l) {
     q.W_hh[l] = W_hh[l];
@@ -193,6 +197,14 @@ as_status ls_fwd(const ls_shape* s, const LsLayout& L, const char* x, const int3
   f.drop_scale = 1.f / (1.f - s->dropout_p);
   f.drop_seed = s->dropout_seed;
   LS_TRY(launch_ls_prep_fwd<TE>(f, q, st));
+  if (L.x_apart) {   // x W_ih^T + b of layer 0, all steps
+    GemmArgs g;
+    g.seg(x, s->I, 0, W_ih[0], s->I, 0, s->I);
+    g.a_kc = true; g.b_kc = true;
+    g.M = (int)L.TB; g.N = 4 * s->H; g.bias = b[0];
+    g.C = f.gates; g.ldc = 4 * s->H; g.c_bf16 = false;
+    LS_TRY(launch_gemm(g, sizeof(TE) == 2, L.p_gx.tile, st));
+  }
   for (int d = 0; d < s->T + s->L - 1; ++d) LS_TRY(launch_ls_wave_fwd<TE>(f, d, st));
   return AS_OK;
 }

@@ -48,6 +48,7 @@ struct LsFwd {
   const int32_t* lengths;
   int T, B, I, H, L;
   int w_rows;
+  int x_apart;                     // layer 0: gates hold x W_ih^T + b when a wavefront starts (x and W_ih are not read)
   uint32_t drop_thr;               // dropout on the outputs below the top layer; 0: none
   float drop_scale;
   uint64_t drop_seed;
@@ -91,6 +92,8 @@ struct LsBiasOut {
   float* db[kLsMaxLayers];
 };
 hipError_t launch_ls_bias_reduce(const float* dbacc, const LsBiasOut& o, int L, int nct, int cols, hipStream_t st);
+// Whether the input product of layer 0 is one product over all steps ahead of the wavefronts.
+template <typename TE> bool ls_input_apart(int T, int B, int I, int H, int L);
 // Whether forward wavefronts read the caller's weight rows instead of tiles made from them.
 template <typename TE> bool ls_reads_weight_rows(int T, int I, int H, int L);
 

@@ -2,7 +2,8 @@
 //
 // Layer l can take step t as soon as it has its own state of step t - 1 and the output of layer l - 1 at step t.  All
 // layer-steps (l, d - l) are therefore independent and go into one launch; the input product is folded into the
-// step as a second segment of the reduction, so that nothing else has to run between two launches.
+// step as a second segment of the reduction, so that nothing else has to run between two launches (layer 0: unless
+// ls_input_apart).
 //
 // A wavefront is a skinny product (B columns, typically 128) on the critical path, bound by the way from the caches to
 // the registers and by what any launch costs, not by the matrix cores:
@@ -156,8 +157,9 @@ static inline unsigned ls_grid(int64_t nslices, int64_t nbt) { return (unsigned)
 // ---- forward ---------------------------------------------------------------------
 // Block: 16 * NI gate rows (4 * NI hidden units) x 16 * NJ sentences.  Tile 4 g + ii of a block, row rho: unit
 // u0 + 16 g + 4 q + ii, gate r, (q, r) = the lane group and register that hold row rho.  ROWS: weights are read as the
-// caller's rows (64 bytes of a row per load), each used once by the call.
-template <typename TE, int NI, int NJ, int PF, bool ROWS, bool VEC>
+// caller's rows (64 bytes of a row per load), each used once by the call.  APART: layer 0 finds the input product and the
+// bias in the gates' place.
+template <typename TE, int NI, int NJ, int PF, bool ROWS, bool VEC, bool APART>
 __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d, int l_lo, int n_layers) {
   typedef LsMma<TE> M;
   typedef typename M::acc_t acc_t;
@@ -202,8 +204,14 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[i][j][r] = 0;
 
-  // segments: own state, then the input (x is exact in the storage type: its remainder is read from zeroed tiles)
-  const int n0 = (H + KST - 1) / KST, n1 = (Kin + KST - 1) / KST;
+  // Segments: own state, then the input.  x is exact in the storage type, it has no remainder.  The widest block reduces
+  // the two segments of layer 0 one after the other, the second without remainders (one loop for both spilled 32
+  // registers: lstm_paper sizes 3.60 -> 3.53 ms).  In the smaller ones the refill between two loops costs more (a step by
+  // itself 147 -> 148 us for four layers): they read zeroed tiles as the remainder and clear the weight ahead of the
+  // product, because 0 * inf would be NaN.
+  constexpr bool TWO = M::kPair && !APART && NI * NJ >= 32;
+  const bool apart = APART && l == 0;
+  const int n0 = (H + KST - 1) / KST, n1 = apart ? 0 : (Kin + KST - 1) / KST;
   const int64_t cstep = (int64_t)nct * kLsTile;
   const char* h_hi = p.hF_hi + (2 * l + (t & 1)) * p.h_stride;
   const char* h_lo = M::kPair ? p.hF_lo + (2 * l + (t & 1)) * p.h_stride : nullptr;
@@ -227,7 +235,7 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
     }
   }
   ls_u32x4_t wf[PF][NI], hf[PF][NJ], lf[PF][M::kPair ? NJ : 1];
-  auto load = [&](int slot, int step) {
+  auto load = [&](int slot, int step, bool rest = true) {   // rest: the remainders too
     const int s = wave + step * LS_KS;
     const bool in = s >= n0;
     const int k = in ? s - n0 : s;
@@ -247,13 +255,13 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
     const char* hb = (in ? i_hi : h_hi) + k * cstep;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) hf[slot][j] = ls_frag(hb + ctoff[j], lane16);
-    if constexpr (M::kPair) {
+    if (M::kPair && rest) {
       const char* lb = in ? i_lo + k * lstep1 : h_lo + k * cstep;
 #pragma unroll
       for (int j = 0; j < NJ; ++j) lf[slot][j] = ls_frag(lb + ctoff[j], lane16);
     }
   };
-  auto mul = [&](int slot, int step) {
+  auto mul = [&](int slot, int step, bool rest = true) {
     const int s = wave + step * LS_KS;
     if constexpr (ROWS) {   // chunks past a row's end were read from its start
       const int K = s >= n0 ? Kin : H, kk = (s >= n0 ? s - n0 : s) * KST + q * V;
@@ -266,8 +274,8 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
     for (int i = 0; i < NI; ++i)
 #pragma unroll
       for (int j = 0; j < NJ; ++j) M::mma(acc[i][j], wf[slot][i], hf[slot][j]);
-    if constexpr (M::kPair) {
-      const uint32_t keep = l == 0 && s >= n0 ? 0u : ~0u;   // x has no remainder: 0 * 0 also where a weight is not finite
+    if (M::kPair && rest) {
+      const uint32_t keep = !TWO && !APART && l == 0 && s >= n0 ? 0u : ~0u;
 #pragma unroll
       for (int i = 0; i < NI; ++i) {
 #pragma unroll
@@ -278,7 +286,16 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
     }
   };
   constexpr int NP = M::kPair ? 2 : 1, NM = M::kPair ? 2 * NI * NJ : 4 * NI * NJ;
-  wave_reduce<PF, NI + NP * NJ, NM>(own_steps<LS_KS>(n0 + n1, wave), load, mul);
+  const int own = own_steps<LS_KS>(n0 + n1, wave);
+  if constexpr (TWO) {
+    const int own0 = l == 0 ? own_steps<LS_KS>(n0, wave) : own;
+    wave_reduce<PF, NI + NP * NJ, NM>(own0, load, mul);
+    wave_reduce<PF, NI + NJ, NM / 2>(
+        own - own0, [&](int slot, int i) { load(slot, own0 + i, false); },
+        [&](int slot, int i) { mul(slot, own0 + i, false); });
+  } else {
+    wave_reduce<PF, NI + NP * NJ, NM>(own, load, mul);
+  }
 
 #pragma unroll
   for (int i = 0; i < NI; ++i)
@@ -293,9 +310,15 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
     const int b = b0 + 16 * j + c, unit0 = u0 + 16 * g + 4 * q;
     if (task >= NG * NJ || b >= B || unit0 >= H) continue;
     const int n = H - unit0;
+    float* G = p.gates + ((int64_t)l * p.T + t) * 4 * BH + (int64_t)b * 4 * H + unit0;
     f32x4_t gi, gf, gg, go, cn, hn, bias4[4];
+    if (apart) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) bias4[e] = ls_widen4(bias[k][e]);
+      for (int e = 0; e < 4; ++e) bias4[e] = ls_ld4<VEC>(G + (int64_t)e * H, n);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) bias4[e] = ls_widen4(bias[k][e]);
+    }
 #pragma unroll
     for (int ii = 0; ii < 4; ++ii) {
       acc_t v = red[((4 * g + ii) * NJ + j) * 64 + lane];
@@ -313,7 +336,6 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
       hn[ii] = go[ii] * tanhf(cn[ii]);
     }
     const int64_t idx = (int64_t)b * H + unit0;
-    float* G = p.gates + ((int64_t)l * p.T + t) * 4 * BH + (int64_t)b * 4 * H + unit0;
     ls_st4<VEC>(G, gi, n);
     ls_st4<VEC>(G + H, gf, n);
     ls_st4<VEC>(G + 2 * (int64_t)H, gg, n);
@@ -643,6 +665,7 @@ __global__ __launch_bounds__(256) void ls_prep_fwd_kernel(LsFwd p, LsPrepFwd s) 
       }
     }
   } else if (job == L) {
+    if (p.x_apart) return;
     const int nks = (p.I + KST - 1) / KST;
     const int64_t per = (int64_t)nks * nct * 64, n = per * p.T;
     const TE* x = reinterpret_cast<const TE*>(s.x);
@@ -661,6 +684,7 @@ __global__ __launch_bounds__(256) void ls_prep_fwd_kernel(LsFwd p, LsPrepFwd s) 
   } else {
     const int l = (job - L - 1) >> 1;
     const bool hh = ((job - L - 1) & 1) == 0;
+    if (p.x_apart && l == 0 && !hh) return;
     const int K = hh || l > 0 ? H : p.I, ntw = (H + 31) / 32 * 8;
     const TE* W = reinterpret_cast<const TE*>(hh ? s.W_hh[l] : s.W_ih[l]);
     char* dst = reinterpret_cast<char*>(const_cast<void*>(hh ? p.W_hh[l] : p.W_ih[l]));
@@ -721,14 +745,29 @@ template <typename TE> bool ls_reads_weight_rows(int T, int I, int H, int) {
   return T == 1 && I % LsGeom<TE>::kVec == 0 && H % LsGeom<TE>::kVec == 0;
 }
 
+// Folded into the wavefronts, the input product of layer 0 lengthens a chain of T dependent launches by what I reduction
+// indices take (0.7 us a launch at I = 512); as one product ahead of them it costs a launch and the round trip of the gates.
+// With more than one layer a launch has reductions of 2 H in it anyway.  Forward, us, folded / apart, at T x B, I -> H:
+//   L = 1  50 x 16, 512 -> 64: 331 / 303, 1024 -> 256: 392 / 336, 4096 -> 256: 623 / 348, 512 -> 1024: 423 / 409,
+//          256 -> 128: 318 / 324; 50 x 128, 512 -> 512: 399 / 393, 512 -> 1024: 538 / 547, 1024 -> 1024: 600 / 565;
+//          10 x 512, 512 -> 256: 97 / 102, 1024 -> 512: 165 / 157; 3 x 128, 1024 -> 256: 33 / 36
+//   L = 2  50 x 128, 512 -> 256: 375 / 366, 512 -> 512: 482 / 490, 1024 -> 1024: 992 / 1046; 3 x 128, 2048 -> 512: 60 / 63
+//   L = 4  50 x 128, 512 -> 1024: 1620 / 1663, 1024 -> 512: 822 / 747
+// fp32 storage is always folded: the matrix instructions bound it, and a sum over both segments is rounded once.
+template <typename TE> bool ls_input_apart(int T, int B, int I, int H, int L) {
+  if (!LsMma<TE>::kPair || T == 1 || (int64_t)T * (I - 256) < 6000) return false;
+  return L > 1 ? I >= 2 * H : I >= H || (2 * I >= H && B <= 32);
+}
+
 template <typename TE> hipError_t launch_ls_prep_fwd(const LsFwd& p, const LsPrepFwd& q, hipStream_t st) {
   constexpr int KST = LsGeom<TE>::kKStep;
   const int64_t nct = ls_batch_tiles(p.B);
   int64_t n = ls_ksteps<TE>(p.H) * nct * 64;   // largest job, in chunks
-  const int64_t nx = (int64_t)ls_ksteps<TE>(p.I) * nct * 64 * p.T;
+  const int I = p.x_apart ? 0 : p.I;
+  const int64_t nx = (int64_t)ls_ksteps<TE>(I) * nct * 64 * p.T;
   if (nx > n) n = nx;
   if (!p.w_rows) {
-    const int64_t nw = (int64_t)((p.I > p.H ? p.I : p.H) + KST - 1) / KST * ls_gate_tiles(p.H) * 64;
+    const int64_t nw = (int64_t)((I > p.H ? I : p.H) + KST - 1) / KST * ls_gate_tiles(p.H) * 64;
     if (nw > n) n = nw;
   }
   int64_t gx = (n + 255) / 256;
@@ -752,11 +791,13 @@ hipError_t launch_ls_bias_reduce(const float* dbacc, const LsBiasOut& o, int L, 
 template <typename TE, int NI, int NJ, int PF>
 static hipError_t ls_fwd_shape(const LsFwd& p, int d, int l_lo, int nl, hipStream_t st) {
   const unsigned grid = ls_grid((int64_t)nl * ((p.H + 4 * NI - 1) / (4 * NI)), (p.B + 16 * NJ - 1) / (16 * NJ));
-#define ASX_FWD(ROWS, VEC) \
-  hipLaunchKernelGGL((ls_wave_fwd_kernel<TE, NI, NJ, PF, ROWS, VEC>), dim3(grid), dim3(64 * LS_KS), 0, st, p, d, l_lo, nl)
-  if (p.w_rows) ASX_FWD(true, true);   // widths are multiples of 4
-  else if (LsMma<TE>::kPair || p.H % 4 == 0) ASX_FWD(false, true);
-  else ASX_FWD(false, LsMma<TE>::kPair);
+#define ASX_FWD(ROWS, VEC, APART)                                                                                    \
+  hipLaunchKernelGGL((ls_wave_fwd_kernel<TE, NI, NJ, PF, ROWS, VEC, APART>), dim3(grid), dim3(64 * LS_KS), 0, st, p, \
+                     d, l_lo, nl)
+  if (p.w_rows) ASX_FWD(true, true, false);   // widths are multiples of 4
+  else if (LsMma<TE>::kPair && p.x_apart && l_lo == 0) ASX_FWD(false, true, LsMma<TE>::kPair);
+  else if (LsMma<TE>::kPair || p.H % 4 == 0) ASX_FWD(false, true, false);
+  else ASX_FWD(false, LsMma<TE>::kPair, false);
 #undef ASX_FWD
   return hipGetLastError();
 }
@@ -810,6 +851,7 @@ template <typename TE> hipError_t launch_ls_wave_bwd(const LsBwd& p, int d, hipS
 
 #define ASX_LS(TE)                                                                                  \
   template bool ls_reads_weight_rows<TE>(int, int, int, int);                                       \
+  template bool ls_input_apart<TE>(int, int, int, int, int);                                        \
   template hipError_t launch_ls_prep_fwd<TE>(const LsFwd&, const LsPrepFwd&, hipStream_t);          \
   template hipError_t launch_ls_prep_bwd<TE>(const LsBwd&, const LsPrepBwd&, hipStream_t);          \
   template hipError_t launch_ls_wave_fwd<TE>(const LsFwd&, int, hipStream_t);                       \

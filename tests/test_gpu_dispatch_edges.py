@@ -64,3 +64,17 @@ def test_lstm_wavefronts_at_block_edges(shape, dtype):
     f, g, _ = tl.run_gpu(inp)
     fo, go = tl.run_oracle(inp)
     tl.compare(inp, f, g, fo, go)
+
+
+@pytest.mark.parametrize("states", [True, False])
+@pytest.mark.parametrize("shape", [(16, 21, 648, 72, 1),       # a wide x: its product ahead of the wavefronts, ragged tiles
+                                   (8, 33, 1032, 40, 3),       # with layers above it
+                                   (24, 9, 512, 1024, 1)])     # narrower than the state, few sentences
+def test_lstm_wide_input(shape, states):
+    import test_gpu_lstm as tl
+    from synth_inputs import make_lstm_inputs
+    T, B, I, H, L = shape
+    inp = make_lstm_inputs(T, B, I, H, L, seed=I, dtype="bf16")
+    f, g, _ = tl.run_gpu(inp, use_states=states)
+    fo, go = tl.run_oracle(inp, use_states=states)
+    tl.compare(inp, f, g, fo, go)
