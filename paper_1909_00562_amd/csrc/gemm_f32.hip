@@ -481,22 +481,35 @@ static double plan_us_128(int M, int N, int ktiles, int batch, int splits) {
   return t + 5.5 + plan_split_us(M, N, batch, splits);
 }
 
+// A split's sum is rounded to fp32, an undivided one is fp64 to the end: at most one split per 256 reduction indices (by
+// sixteens), 32 in all, and 768 blocks of 64 x 64, however many more the compute units could take.
+static int f32_most_splits(int M, int N, int K, int batch) {
+  const int64_t tiles = (int64_t)((M + 63) / 64) * ((N + 63) / 64) * batch;
+  if (tiles >= 384) return 1;
+  const int slices = (K + 15) / 16;
+  int64_t most = (768 + tiles - 1) / tiles;
+  if (most > slices / 16) most = slices / 16;
+  if (most > 32) most = 32;
+  if (most <= 1) return 1;
+  const int per = (int)((slices + most - 1) / most);
+  return (slices + per - 1) / per;
+}
+
 GemmPlan gemm_plan(int M, int N, int K, int batch, bool bf16, bool allow_split, bool multi_segment) {
   GemmPlan pl;
   pl.tile = kTile128;
   pl.splits = 1;
   if (!bf16) {
     if (multi_segment) allow_split = false;
-    // fp32 path: split while there are fewer than ten 32 x 32 blocks per compute unit, down to eight reduction tiles
-    // per split (a split's sums are rounded to fp32: no more of them than the speed is worth).  Measured (1 / 2 / 4 / 8 splits): 1286 x 512 x 16000 531 / 507 / 453 / 431 us, 512 x 512 x 1920
-    // 35 / 32 / 31 / 33 us, 64 x 512 x 2048 36 / 23 / 16 / 13 us; 16000 x 512 x 1286 (8000 blocks) only loses.
+    // fp32 path: split while there are fewer than ten 32 x 32 blocks per compute unit.  Measured (1 / 2 / 4 / 8 splits):
+    // 1286 x 512 x 16000 531 / 507 / 453 / 431 us, 512 x 512 x 1920 35 / 32 / 31 / 33 us, 64 x 512 x 2048 36 / 23 / 16 /
+    // 13 us; 16000 x 512 x 1286 (8000 blocks) only loses.
     const int64_t tiles = (int64_t)((M + 31) / 32) * ((N + 31) / 32) * batch;
     if (allow_split) {
       const int ktiles = (K + FK - 1) / FK;
       int64_t want = 2560 / tiles;
-      const int64_t cap = ktiles / 8;
-      if (want > cap) want = cap;
-      if (want > 32) want = 32;
+      const int most = f32_most_splits(M, N, K, batch);
+      if (want > most) want = most;
       if (want > 1) {
         const int per = (int)((ktiles + want - 1) / want);
         pl.splits = (ktiles + per - 1) / per;

@@ -1,5 +1,6 @@
 """Host-side dispatch rules, without a GPU: which kernel a size goes to where both sides were measured."""
 import ctypes
+import random
 
 import pytest
 
@@ -27,3 +28,34 @@ def test_input_product_of_layer_0_where_it_was_faster(T, B, I, H, L, apart):
     """bf16: folded into the wavefronts or one product ahead of them, as measured at these sizes; fp32 always folded."""
     assert _rule("_ZN3asx14ls_input_apartItEEbiiiii", ctypes.c_bool, *[I32] * 5)(T, B, I, H, L) == apart
     assert not _rule("_ZN3asx14ls_input_apartIfEEbiiiii", ctypes.c_bool, *[I32] * 5)(T, B, I, H, L)
+
+
+def _plan(M, N, K, batch, bf16, allow_split=True, multi_segment=False):
+    """(tile, splits) of a product: tile 0 = 128 x 128, 1 = 256 x 256, 2 = 64 x 64 (bf16)."""
+    f = _rule("_ZN3asx9gemm_planEiiiibbb", ctypes.c_uint64, *[I32] * 4, *[ctypes.c_bool] * 3)
+    v = f(M, N, K, batch, bf16, allow_split, multi_segment)
+    return v & 0xffffffff, v >> 32
+
+
+def _f32_split_bound(M, N, K, batch):
+    tiles = -(-M // 64) * -(-N // 64) * batch
+    if tiles >= 384:
+        return 1
+    slices = -(-K // 16)
+    most = min(-(-768 // tiles), slices // 16, 32)
+    return 1 if most <= 1 else -(-slices // -(-slices // most))
+
+
+def test_f32_products_keep_their_sums_in_fp64():
+    """A split's partial sum is rounded to fp32, so no product gets more splits than the bound; none is left without
+    reduction tiles."""
+    rng = random.Random(7)
+    log = lambda lo, hi: int(round(lo * (hi / lo) ** rng.random()))
+    sizes = [(512, 512, 496, 1), (32, 64, 1000, 1), (16, 2048, 32000, 1), (30, 20000, 4096, 1), (1, 1, 1, 1)]
+    sizes += [(log(1, 8192), log(1, 8192), log(1, 65536), rng.choice((1, 1, 2))) for _ in range(20000)]
+    for s in sizes:
+        _, splits = _plan(*s, bf16=False)
+        assert 1 <= splits <= _f32_split_bound(*s), s
+        tiles = -(-s[2] // 32)
+        assert -(-tiles // splits) * (splits - 1) < tiles, s
+    assert _plan(512, 512, 496, 1, bf16=False)[1] == 1
