@@ -481,6 +481,17 @@ static double plan_us_128(int M, int N, int ktiles, int batch, int splits) {
   return t + 5.5 + plan_split_us(M, N, batch, splits);
 }
 
+// 256 x 256, a round of blocks or less: 0.9 to 1.6 us per reduction tile, the more compute units share the memory and the
+// power.  Its combine moves the partial sums at 5.7 TB/s, and 6.5 us at least.  (2048 x 2048 x 16384 TN in 4 splits 147
+// measured, 140 by this; two of them in 2 splits 255, 242; 6144 x 512 x 6400 TN in 5 65, 67; 4096 x 1024 x 6400 TN in 4 73,
+// 78: with 128 x 128 73 too, and less ahead of another product; 1280 x 1024 x 32000 NN in 12 100, 102; 3776 x 512 x 27403 NN
+// in 8 135, 120; 4096^3 TN 116, 110.  plan_cost puts the first two at 187 and 325.)
+static double plan_us_256(int M, int N, int ktiles, int batch, int splits) {
+  const int64_t blocks = (int64_t)((M + 255) / 256) * ((N + 255) / 256) * batch * splits;
+  const int k = (ktiles + splits - 1) / splits;
+  return (0.9 + 0.7 * (double)blocks / 256.0) * k + 7.5 + (splits > 1 ? 8.0 * splits * M * N * batch / 5.7e6 + 6.5 : 0.0);
+}
+
 // A split's sum is rounded to fp32, an undivided one is fp64 to the end: at most one split per 256 reduction indices (by
 // sixteens), 32 in all, and 768 blocks of 64 x 64, however many more the compute units could take.
 static int f32_most_splits(int M, int N, int K, int batch) {
@@ -535,13 +546,13 @@ GemmPlan gemm_plan(int M, int N, int K, int batch, bool bf16, bool allow_split, 
       }
     }
   }
-  // Which of the two shapes of gemm_tile.hip, if not 256 x 256.  With more than a round of 256 x 256 tiles that kernel
+  // Which of the two shapes of gemm_tile.hip, if they are faster than 256 x 256.  With more than a round of 256 x 256 tiles that kernel
   // stays: it writes a tile while the next one is on its way, which the models leave out (2257 x 32003 x 1000: 174 us, 231
   // with 128 x 128, 184 by the model).
   double now = 1e30;
   if (pl.tile == kTile256) {
     if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) * batch * pl.splits > 256) return pl;
-    now = 0.9 * best * 1e6;
+    now = plan_us_256(M, N, ktiles, batch, pl.splits);
   }
   const int smax = allow_split ? (ktiles / 4 < 32 ? (ktiles / 4 > 1 ? ktiles / 4 : 1) : 32) : 1;
   for (int want = 1; want <= smax; ++want) {

@@ -59,3 +59,15 @@ def test_f32_products_keep_their_sums_in_fp64():
         tiles = -(-s[2] // 32)
         assert -(-tiles // splits) * (splits - 1) < tiles, s
     assert _plan(512, 512, 496, 1, bf16=False)[1] == 1
+
+
+@pytest.mark.parametrize("M, N, K, batch, plan", [
+    (2048, 2048, 16384, 1, (1, 4)), (2048, 2048, 16384, 2, (1, 2)), (2048, 2048, 7680, 2, (1, 2)),
+    (1024, 1024, 12800, 2, (1, 8)), (4096, 1024, 12800, 1, (1, 4)), (6144, 512, 6400, 1, (1, 5)),
+    (1280, 1024, 32000, 1, (1, 12)), (3776, 512, 27403, 1, (1, 8)),
+    (4096, 1024, 6400, 1, (0, 1)), (8192, 512, 6400, 1, (0, 1)), (2048, 2048, 4096, 1, (0, 1)), (1024, 1024, 6400, 1, (2, 1)), (4096, 1024, 3200, 1, (0, 1)),
+    (1536, 1536, 2560, 1, (0, 1)), (16000, 512, 1286, 1, (0, 1)), (4096, 4096, 4096, 1, (1, 1))])
+def test_bf16_tile_that_was_the_faster_one(M, N, K, batch, plan):
+    """Weight-gradient products (and dlogits W_out) whose time was taken with every tile and split: 256 x 256 tiles above,
+    the smaller ones below."""
+    assert _plan(M, N, K, batch, bf16=True) == plan
