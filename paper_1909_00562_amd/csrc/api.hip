@@ -95,7 +95,7 @@ struct Layout {
   int64_t N, ldS, ldV;
   size_t e;  // bytes per stored element
   size_t q, scores, alpha32, alphaE, ctx, hc, logits, lse, tokloss;
-  size_t dz, dC, dalpha, dscoreE, dQ, dbpart, partial, total;
+  size_t partial_hc, dz, dC, dalpha, dscoreE, dQ, dbpart, partial, total;
   // rounding remainders (value - stored(value)) of operands made inside the attention core,
   // and the tanh derivative 1 - h_c^2 taken before h_c is rounded
   size_t q_lo, alphaE_lo, dC_lo, dscoreE_lo, dact, dz_lo, ctx_lo;
@@ -105,7 +105,6 @@ struct Layout {
   size_t row_pos, rows, n_act, hc_c, dact_c, dz_c, dz_lo_c;
   int rb, nrb;
   GemmPlan p_q, p_score, p_ctx, p_hc, p_logits, p_dwout, p_dhc, p_dwc, p_dch, p_dalpha, p_dq, p_ds, p_dwa, p_dh;
-  size_t partial_bytes;
 };
 
 bool shape_ok(const as_shape* s) {
@@ -153,14 +152,6 @@ Layout make_layout(const as_shape* s) {
   L.p_ds = gemm_plan(S, H, T, B, bf, false);
   L.p_dwa = gemm_plan(H, H, N, 1, bf, true);
   L.p_dh = gemm_plan(N, H, H, 1, bf, false);
-  size_t pb = 0;
-  auto mx = [&](size_t v) { if (v > pb) pb = v; };
-  mx(gemm_partial_bytes(N, H, 1, L.p_hc.splits));
-  mx(gemm_partial_bytes(V, H, 1, L.p_dwout.splits));
-  mx(gemm_partial_bytes(N, H, 1, L.p_dhc.splits));
-  mx(gemm_partial_bytes(H, H, 2, L.p_dwc.splits));
-  mx(gemm_partial_bytes(H, H, 1, L.p_dwa.splits));
-  L.partial_bytes = pb;
 
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -170,6 +161,7 @@ Layout make_layout(const as_shape* s) {
   };
   const size_t NH = (size_t)N * H;
   const size_t BTS = (size_t)B * T * S, BTSl = (size_t)B * T * L.ldS;
+  // what the forward pass leaves for views and for the backward pass
   L.q = take(NH * L.e);
   L.scores = take(BTS * 4);
   L.alpha32 = take(BTS * 4);
@@ -179,20 +171,10 @@ Layout make_layout(const as_shape* s) {
   L.logits = take((size_t)N * L.ldV * L.e);
   L.lse = take((size_t)N * 4);
   L.tokloss = take((size_t)N * 4);
-  L.dz = take(NH * L.e);
-  L.dC = take(NH * L.e);
-  L.dalpha = take(BTS * 4);
-  L.dscoreE = take(BTSl * L.e);
-  L.dQ = take(NH * L.e);
-  L.dbpart = take((size_t)L.nrb * V * 4);
-  L.partial = take(pb);
   L.q_lo = take(NH * L.e);
   L.alphaE_lo = take(BTSl * L.e);
-  L.dC_lo = take(NH * L.e);
-  L.dscoreE_lo = take(BTSl * L.e);
   L.dact = take(NH * 4);
   L.ctx_lo = take(NH * L.e);
-  L.dz_lo = take(NH * L.e);
   L.compact = s->skip_pad_rows != 0;
   L.row_pos = L.rows = L.n_act = L.hc_c = L.dact_c = L.dz_c = L.dz_lo_c = 0;
   if (L.compact) {
@@ -201,9 +183,37 @@ Layout make_layout(const as_shape* s) {
     L.n_act = take(16);
     L.hc_c = take(NH * L.e);
     L.dact_c = take(NH * 4);
+  }
+  // One area for three things that are never alive together: the partial sums of h_c (forward), the column sums of
+  // dlogits (first thing of the backward pass, reduced before anything else of it is written) and the rest of the
+  // backward pass.  (16384 x 128000 positions x words: the column sums alone are 262 MB.)
+  const size_t area = off;
+  L.partial_hc = take(gemm_partial_bytes(N, H, 1, L.p_hc.splits));
+  size_t end = off;
+  off = area;
+  L.dbpart = take((size_t)L.nrb * V * 4);
+  if (off > end) end = off;
+  off = area;
+  L.dz = take(NH * L.e);
+  L.dC = take(NH * L.e);
+  L.dalpha = take(BTS * 4);
+  L.dscoreE = take(BTSl * L.e);
+  L.dQ = take(NH * L.e);
+  L.dC_lo = take(NH * L.e);
+  L.dscoreE_lo = take(BTSl * L.e);
+  L.dz_lo = take(NH * L.e);
+  if (L.compact) {
     L.dz_c = take(NH * L.e);
     L.dz_lo_c = take(NH * L.e);
   }
+  size_t pb = 0;
+  auto mx = [&](size_t v) { if (v > pb) pb = v; };
+  mx(gemm_partial_bytes(V, H, 1, L.p_dwout.splits));
+  mx(gemm_partial_bytes(N, H, 1, L.p_dhc.splits));
+  mx(gemm_partial_bytes(H, H, 2, L.p_dwc.splits));
+  mx(gemm_partial_bytes(H, H, 1, L.p_dwa.splits));
+  L.partial = take(pb);
+  if (off < end) off = end;
   L.total = off;
   return L;
 }
@@ -288,7 +298,7 @@ static as_status fwd_from_ctx(const as_shape* s, const Layout& L, char* w, const
     g.M = N; g.N = H; g.act_tanh = 1;
     g.C = w + L.hc; g.ldc = H; g.c_bf16 = bf;
     g.C_dact = reinterpret_cast<float*>(w + L.dact);
-    g.splits = L.p_hc.splits; g.partial = reinterpret_cast<float*>(w + L.partial);
+    g.splits = L.p_hc.splits; g.partial = reinterpret_cast<float*>(w + L.partial_hc);
     if (s->dropout_p > 0.f) {   // section 4.2: dropout, here on the attentional state; the mask rides on dact into bwd
       g.drop_thr = (uint32_t)((double)s->dropout_p * 4294967296.0);   // floor: the product is exact in double
       g.drop_scale = 1.f / (1.f - s->dropout_p);

@@ -71,3 +71,20 @@ def test_bf16_tile_that_was_the_faster_one(M, N, K, batch, plan):
     """Weight-gradient products (and dlogits W_out) whose time was taken with every tile and split: 256 x 256 tiles above,
     the smaller ones below."""
     assert _plan(M, N, K, batch, bf16=True) == plan
+
+
+@pytest.mark.parametrize("T, S, B, H, V, dtype, skip", [
+    (5, 53, 103, 32, 27126, bd.AS_F32, 1), (11, 27, 45, 31, 28054, bd.AS_F32, 0), (10, 123, 55, 22, 25179, bd.AS_F32, 0),
+    (2, 39, 241, 2281, 197, bd.AS_F32, 1), (78, 29, 53, 92, 2017, bd.AS_F32, 0)])
+def test_static_scratch_holds_shapes_just_below_its_size(T, S, B, H, V, dtype, skip):
+    """attn_softmax_fwd_static takes a shape by the size of its whole workspace, so that must not grow with parts of the
+    backward pass that are never alive together."""
+    shape = bd.AsShape(T, S, B, H, V, 0, dtype, 1.0, 0.0, 0, skip)
+    assert bd.attn_softmax_workspace_bytes(shape) <= bd.AS_STATIC_SCRATCH_BYTES
+
+
+def test_workspace_of_the_largest_training_step():
+    """64 steps x 256 sentences, 2048 units, 128000 words: the column sums of dlogits (262 MB) and the partial sums share
+    their place."""
+    shape = bd.AsShape(64, 64, 256, 2048, 128000, 0, bd.AS_BF16, 1.0, 0.0, 0, 1)
+    assert bd.attn_softmax_workspace_bytes(shape) <= 6.45e9

@@ -78,3 +78,13 @@ def test_lstm_wide_input(shape, states):
     f, g, _ = tl.run_gpu(inp, use_states=states)
     fo, go = tl.run_oracle(inp, use_states=states)
     tl.compare(inp, f, g, fo, go)
+
+
+@pytest.mark.parametrize("skip", [False, True])
+def test_static_scratch_just_below_its_size(skip):
+    """The forward pass in the library's own scratch, nearly all of it used, and the passes that share one area of a
+    caller's workspace, against the oracle."""
+    import test_zz_no_alloc as na
+    inp = make_custom(T=5, S=53, B=103, H=32, V=27126, seed=5, dtype="f32", min_len=1, pad_prob=0.2)
+    na._run_pair(inp, skip)
+    _parity(inp, skip)
