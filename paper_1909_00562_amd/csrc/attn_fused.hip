@@ -26,6 +26,7 @@
 //   through the wave's LDS slice so that ctx / ctx_lo leave as 8-byte row vectors.
 #include "common.h"
 #include "kernels.h"
+#include "lds_limit.h"
 
 namespace asx {
 
@@ -328,16 +329,10 @@ static hipError_t launch_attn_fused(bool bwd, AttnFwdArgs p, hipStream_t st) {
   p.off_x = region0;
   p.off_a = region0 + regionx;
   const int smem = p.off_a + 2 * KB * 4096;
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_fwd_fused_kernel<false>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_fwd_fused_kernel<true>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static LdsLimit limit[2];
+  const hipError_t e = limit[bwd].raise(bwd ? reinterpret_cast<const void*>(attn_fwd_fused_kernel<true>)
+                                            : reinterpret_cast<const void*>(attn_fwd_fused_kernel<false>), 160 * 1024);
+  if (e != hipSuccess) return e;
   const dim3 grid(p.B, (p.T + AF_ROWS - 1) / AF_ROWS);
   if (bwd) hipLaunchKernelGGL(attn_fwd_fused_kernel<true>, grid, dim3(AF_THREADS), smem, st, p);
   else hipLaunchKernelGGL(attn_fwd_fused_kernel<false>, grid, dim3(AF_THREADS), smem, st, p);

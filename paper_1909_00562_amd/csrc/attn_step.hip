@@ -12,6 +12,7 @@
 // takes 26 and d_h_enc as a batched product of rank one 25.
 #include "common.h"
 #include "kernels.h"
+#include "lds_limit.h"
 
 namespace asx {
 
@@ -235,8 +236,8 @@ static hipError_t launch_step(AttnStep p, hipStream_t st) {
   if (smem > kStepSmem) return hipErrorInvalidValue;
   auto k = attn_step_kernel<TK, TE, BWD>;
   if (smem > 48 * 1024) {
-    const hipError_t e =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    static LdsLimit limit;
+    const hipError_t e = limit.raise(reinterpret_cast<const void*>(k), (int)kStepSmem);
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(k, dim3(p.B), dim3(kStepThreads), smem, st, p);

@@ -27,6 +27,7 @@
 #include "common.h"
 #include "gemm.h"
 #include "gemm_dev.h"
+#include "lds_limit.h"
 
 #include <type_traits>
 
@@ -932,13 +933,9 @@ template <bool AKC, bool BKC, bool OUT_BF16, bool VEC>
 static hipError_t launch_ring(const GemmDev& d, int batch, hipStream_t st) {
   constexpr int smem = RING_SMEM;
   auto kfn = gemm_bf16_ring_kernel<AKC, BKC, OUT_BF16, VEC, false>;
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static LdsLimit limit;
+  const hipError_t e = limit.raise(reinterpret_cast<const void*>(kfn), smem);
+  if (e != hipSuccess) return e;
   const int work_total = d.tiles_m * d.tiles_n * batch * d.splits;
   const int blocks = pp_grid_blocks(work_total);
   hipLaunchKernelGGL(kfn, dim3(blocks), dim3(512), smem, st, d, work_total);
@@ -956,13 +953,9 @@ template <bool AKC, bool BKC, bool OUT_BF16, bool VEC, bool DROP = false>
 static hipError_t launch_pp(const GemmDev& d, int batch, hipStream_t st) {
   constexpr int smem = PP_SMEM;
   auto kfn = gemm_bf16_pp_kernel<AKC, BKC, OUT_BF16, VEC, DROP, AKC && BKC>;
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kfn),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static LdsLimit limit;
+  const hipError_t e = limit.raise(reinterpret_cast<const void*>(kfn), smem);
+  if (e != hipSuccess) return e;
   // persistent: one block per CU (a multiple of the 8 XCDs), each walking its share of the work items
   const int work_total = d.tiles_m * d.tiles_n * batch * d.splits;
   const int blocks = pp_grid_blocks(work_total);

@@ -17,6 +17,7 @@
 #include "common.h"
 #include "gemm.h"
 #include "gemm_dev.h"
+#include "lds_limit.h"
 
 #include <type_traits>
 
@@ -323,13 +324,9 @@ template <int TW, bool AKC, bool BKC, int NST>
 static hipError_t launch_tile_shape(const GemmDev& d, int out_bf16, hipStream_t st) {
   constexpr int BM = 32 * TW, smem = NST * 2 * BM * ROWB;
   auto kfn = gemm_bf16_tile_kernel<TW, AKC, BKC, NST>;
-  static bool attr_set = false;
-  if (!attr_set) {
-    const hipError_t e =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static LdsLimit limit;
+  const hipError_t e = limit.raise(reinterpret_cast<const void*>(kfn), smem);
+  if (e != hipSuccess) return e;
   const dim3 grid((d.M + BM - 1) / BM * d.tiles_n, 1, d.nz);
   hipLaunchKernelGGL(kfn, grid, dim3(256), smem, st, d, out_bf16);
   return hipGetLastError();

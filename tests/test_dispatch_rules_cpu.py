@@ -1,6 +1,9 @@
 """Host-side dispatch rules, without a GPU: which kernel a size goes to where both sides were measured."""
 import ctypes
+import os
 import random
+import shutil
+import subprocess
 
 import pytest
 
@@ -88,3 +91,48 @@ def test_workspace_of_the_largest_training_step():
     their place."""
     shape = bd.AsShape(64, 64, 256, 2048, 128000, 0, bd.AS_BF16, 1.0, 0.0, 0, 1)
     assert bd.attn_softmax_workspace_bytes(shape) <= 6.45e9
+
+
+HIP_STUB = """
+#pragma once
+enum hipError_t { hipSuccess = 0, hipErrorUnknown = 1 };
+enum { hipFuncAttributeMaxDynamicSharedMemorySize = 8 };
+extern int device, calls, fail;
+inline hipError_t hipGetDevice(int* d) { *d = device; return hipSuccess; }
+inline hipError_t hipFuncSetAttribute(const void*, int, int) { ++calls; return fail ? hipErrorUnknown : hipSuccess; }
+"""
+LDS_LIMIT_MAIN = """
+#include "lds_limit.h"
+int device = 0, calls = 0, fail = 0;
+int main() {
+  asx::LdsLimit a, b;
+  auto expect = [](bool ok) { if (!ok) __builtin_trap(); };
+  expect(a.raise(0, 1) == hipSuccess && calls == 1);
+  expect(a.raise(0, 1) == hipSuccess && calls == 1);     // once per device
+  device = 1;
+  expect(a.raise(0, 1) == hipSuccess && calls == 2);     // another device of the same process
+  expect(b.raise(0, 1) == hipSuccess && calls == 3);     // another kernel
+  device = 2; fail = 1;
+  expect(a.raise(0, 1) == hipErrorUnknown && calls == 4);
+  fail = 0;
+  expect(a.raise(0, 1) == hipSuccess && calls == 5);     // a failure is not remembered
+  device = 70;
+  expect(a.raise(0, 1) == hipSuccess && a.raise(0, 1) == hipSuccess && calls == 7);
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="no host compiler")
+def test_lds_limit_is_raised_on_every_device(tmp_path):
+    """The limit of a kernel's dynamic LDS belongs to the device it is loaded on: host code against a stub of the runtime."""
+    csrc = os.path.join(os.path.dirname(bd.library_path()), "csrc")
+    (tmp_path / "hip").mkdir()
+    (tmp_path / "hip" / "hip_runtime.h").write_text(HIP_STUB)
+    (tmp_path / "main.cpp").write_text(LDS_LIMIT_MAIN)
+    exe = tmp_path / "main"
+    subprocess.run(["g++", "-std=c++17", f"-I{tmp_path}", f"-I{csrc}", str(tmp_path / "main.cpp"), "-o", str(exe)], check=True)
+    subprocess.run([str(exe)], check=True)
+    # and every launcher that needs more than 64 KiB goes through it
+    for name in os.listdir(csrc):
+        if name != "lds_limit.h":
+            assert "hipFuncSetAttribute" not in open(os.path.join(csrc, name)).read(), name
