@@ -31,10 +31,12 @@ struct LsLayout {
   size_t gates, cs, hE, out, dG;          // [L] (out: [L - 1]) blocks each
   size_t hf, dcs, dbacc, partial, total;
   size_t xF, zeros, hF[2], oF[2], dGF;    // fragment tiles; [0] value, [1] remainder (bf16 storage)
-  std::vector<size_t> Wf_hh, Wf_ih, Wb_hh, Wb_up;   // weights as tiles, per layer: forward and backward share the space
+  std::vector<size_t> Wf_hh, Wf_ih, Wb_hh, Wb_up;   // weights as tiles, per layer
   std::vector<GemmPlan> p_dwi;
   GemmPlan p_dwh, p_dx, p_gx;
   bool x_apart;   // the input product of layer 0 ahead of the wavefronts
+  bool w_rows;    // forward wavefronts read the caller's weight rows
+  int group;      // T = 1, backward: wavefronts whose weights are tiles at the same time
 };
 
 bool ls_shape_ok(const ls_shape* s) {
@@ -48,21 +50,22 @@ bool ls_shape_ok(const ls_shape* s) {
   return true;
 }
 
-template <typename TE>
-void ls_tile_sizes(const ls_shape* s, LsLayout& L, size_t& off) {
-  auto take = [&](size_t bytes) {
-    size_t o = off;
-    off += upl(bytes, kAlignL);
-    return o;
-  };
+// Weights of the backward pass as tiles.  With one step (T = 1) a weight is used by one wavefront alone, so that places for
+// a few wavefronts' (16 MiB of them, one wavefront's two at least) do for all layers: they are filled again in between.
+// (128 sentences, four layers of 1024 units: 46 MiB of workspace where tiles of all weights make it 86.)
+int ls_one_step_group(size_t weight) {
+  const size_t g = ((size_t)16 << 20) / (2 * weight);
+  return g < 1 ? 1 : (g < kLsMaxLayers ? (int)g : kLsMaxLayers);
+}
+
+template <typename TE, typename Take> void ls_fwd_tiles(const ls_shape* s, LsLayout& L, Take take) {
   const int T = s->T, I = s->I, H = s->H, NL = s->L;
   const size_t nct = ls_batch_tiles(s->B);
   const int copies = sizeof(TE) == 2 ? 2 : 1;
-  const size_t gk = 4 * (size_t)ls_gate_stride<TE>(H) / LsGeom<TE>::kKStep;
   L.x_apart = ls_input_apart<TE>(T, s->B, I, H, NL);
+  L.w_rows = ls_reads_weight_rows<TE>(T, I, H);
   L.x_stride = L.x_apart ? 0 : (int64_t)(ls_ksteps<TE>(I) * nct * kLsTile);
   L.h_stride = (int64_t)(ls_ksteps<TE>(H) * nct * kLsTile);
-  L.g_stride = (int64_t)(gk * nct * kLsTile);
   L.xF = take((size_t)L.x_stride * T);
   L.zeros = take(nct * kLsTile);
   for (int k = 0; k < copies; ++k) {
@@ -70,19 +73,24 @@ void ls_tile_sizes(const ls_shape* s, LsLayout& L, size_t& off) {
     L.oF[k] = take((size_t)L.h_stride * 2 * (NL - 1));
   }
   for (int k = copies; k < 2; ++k) L.hF[k] = L.oF[k] = 0;
+  for (int l = 0; l < NL; ++l) {
+    const size_t row = L.w_rows ? 0 : ls_gate_tiles(H) * kLsTile;
+    L.Wf_hh.push_back(take(ls_ksteps<TE>(H) * row));
+    L.Wf_ih.push_back(take(ls_ksteps<TE>(l > 0 ? H : L.x_apart ? 0 : I) * row));
+  }
+}
+template <typename TE, typename Take> void ls_bwd_tiles(const ls_shape* s, LsLayout& L, Take take) {
+  const int H = s->H, NL = s->L;
+  const size_t gk = 4 * (size_t)ls_gate_stride<TE>(H) / LsGeom<TE>::kKStep, weight = gk * ls_unit_tiles(H) * kLsTile;
+  L.g_stride = (int64_t)(gk * ls_batch_tiles(s->B) * kLsTile);
   L.dGF = take((size_t)L.g_stride * 2 * NL);
-  const size_t w0 = off;
-  for (int l = 0; l < NL; ++l) {
-    L.Wf_hh.push_back(take((size_t)ls_ksteps<TE>(H) * ls_gate_tiles(H) * kLsTile));
-    L.Wf_ih.push_back(take((size_t)ls_ksteps<TE>(l > 0 ? H : L.x_apart ? 0 : I) * ls_gate_tiles(H) * kLsTile));
+  L.group = s->T > 1 ? NL : ls_one_step_group(weight);
+  auto places = [&](int n) { return take((L.group < n ? L.group : n) * weight); };
+  const size_t hh = places(NL), up = places(NL - 1);
+  for (int l = 0; l < NL; ++l) {   // wavefront NL - l reads W_hh[l], the one before it W_ih[l + 1]
+    L.Wb_hh.push_back(hh + (NL - 1 - l) % L.group * weight);
+    L.Wb_up.push_back(l + 1 < NL ? up + (NL - 2 - l) % L.group * weight : 0);
   }
-  const size_t end = off;
-  off = w0;
-  for (int l = 0; l < NL; ++l) {
-    L.Wb_hh.push_back(take(gk * ls_unit_tiles(H) * kLsTile));
-    L.Wb_up.push_back(l + 1 < NL ? take(gk * ls_unit_tiles(H) * kLsTile) : 0);
-  }
-  if (off < end) off = end;
 }
 
 LsLayout make_ls_layout(const ls_shape* s) {
@@ -118,17 +126,25 @@ LsLayout make_ls_layout(const ls_shape* s) {
   L.p_dwh = gemm_plan(4 * H, H, TB, 1, bf, true);
   L.p_gx = gemm_plan(TB, 4 * H, I, 1, bf, false);
   mx(gemm_partial_bytes(4 * H, H, 1, L.p_dwh.splits));
+  // what the forward pass leaves for the backward pass
   L.gates = take((size_t)NL * TB * 4 * H * 4);
   L.cs = take((size_t)NL * (T + 1) * L.BH * 4);
   L.hE = take((size_t)NL * (T + 1) * L.BH * L.e);
   L.out = take((size_t)(NL - 1) * TB * H * L.e);
-  L.dG = take((size_t)NL * TB * 4 * H * L.e);
+  // one area for what only the forward and what only the backward pass needs
+  const size_t area = off;
   L.hf = take((size_t)NL * L.BH * 4);
+  if (bf) ls_fwd_tiles<uint16_t>(s, L, take);
+  else ls_fwd_tiles<float>(s, L, take);
+  const size_t end = off;
+  off = area;
+  L.dG = take((size_t)NL * TB * 4 * H * L.e);
   L.dcs = take((size_t)NL * L.BH * 4);
   L.dbacc = take((size_t)NL * ls_batch_tiles(B) * 4 * H * 4);
   L.partial = take(pb);
-  if (bf) ls_tile_sizes<uint16_t>(s, L, off);
-  else ls_tile_sizes<float>(s, L, off);
+  if (bf) ls_bwd_tiles<uint16_t>(s, L, take);
+  else ls_bwd_tiles<float>(s, L, take);
+  if (off < end) off = end;
   L.total = off;
   return L;
 }
@@ -173,7 +189,7 @@ as_status ls_fwd(const ls_shape* s, const LsLayout& L, const char* x, const int3
   LsPrepFwd q{};
   f.T = s->T; f.B = s->B; f.I = s->I; f.H = s->H; f.L = s->L;
   f.x_apart = L.x_apart;
-  f.w_rows = ls_reads_weight_rows<TE>(s->T, s->I, s->H, s->L);
+  f.w_rows = L.w_rows;
   for (int l = 0; l < s->L; ++l) {
     q.W_hh[l] = W_hh[l];
     q.W_ih[l] = W_ih[l];
@@ -222,8 +238,6 @@ as_status ls_bwd(const ls_shape* s, const LsLayout& L, const char* x, const int3
   LsPrepBwd q{};
   LsBiasOut o{};
   for (int l = 0; l < NL; ++l) {
-    q.W_hh[l] = W_hh[l];
-    q.W_ih[l] = W_ih[l];
     r.WT_hh[l] = w + L.Wb_hh[l];
     r.WT_up[l] = w + L.Wb_up[l];
     o.db[l] = db[l];
@@ -241,9 +255,24 @@ as_status ls_bwd(const ls_shape* s, const LsLayout& L, const char* x, const int3
   r.drop_thr = s->dropout_p > 0.f ? (uint32_t)((double)s->dropout_p * 4294967296.0) : 0u;
   r.drop_scale = 1.f / (1.f - s->dropout_p);
   r.drop_seed = s->dropout_seed;
-  LS_TRY(launch_ls_prep_bwd<TE>(r, q, st));
+  q.H = H;
+  if (T > 1) {
+    for (int l = 0; l < NL; ++l) q.add(W_hh[l], r.WT_hh[l]);
+    for (int l = 0; l + 1 < NL; ++l) q.add(W_ih[l + 1], r.WT_up[l]);
+    LS_TRY(launch_ls_prep_bwd<TE>(q, st));
+  }
   const int waves = T + NL - 1 + (dh0 ? 1 : 0);
-  for (int d = 0; d < waves; ++d) LS_TRY(launch_ls_wave_bwd<TE>(r, d, st));
+  for (int d = 0; d < waves; ++d) {
+    if (T == 1 && d > 0 && (d - 1) % L.group == 0) {   // wavefront e: layer NL - 1 - e, and the initial state of NL - e
+      q.n = 0;
+      for (int e = d; e < d + L.group && e < waves; ++e) {
+        if (e < NL) q.add(W_ih[NL - e], r.WT_up[NL - 1 - e]);
+        if (dh0) q.add(W_hh[NL - e], r.WT_hh[NL - e]);
+      }
+      LS_TRY(launch_ls_prep_bwd<TE>(q, st));
+    }
+    LS_TRY(launch_ls_wave_bwd<TE>(r, d, st));
+  }
   LS_TRY(launch_ls_bias_reduce(r.dbacc, o, NL, ls_batch_tiles(B), 4 * H, st));
   for (int l = 0; l < NL; ++l) {
     const int Il = l == 0 ? I : H;

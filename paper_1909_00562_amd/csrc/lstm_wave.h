@@ -78,11 +78,14 @@ struct LsPrepFwd {
   const float *h0, *c0;
 };
 template <typename TE> hipError_t launch_ls_prep_fwd(const LsFwd& p, const LsPrepFwd& q, hipStream_t st);
-// tiles of the transposed weights into p.WT_*
+// tiles of n transposed [4H,H] weights (W_hh[l], W_ih[l + 1]) into the places p.WT_* point to
 struct LsPrepBwd {
-  const void *W_hh[kLsMaxLayers], *W_ih[kLsMaxLayers];
+  const void* W[2 * kLsMaxLayers];
+  char* tiles[2 * kLsMaxLayers];
+  int n, H;
+  void add(const void* w, const char* t) { W[n] = w; tiles[n++] = const_cast<char*>(t); }
 };
-template <typename TE> hipError_t launch_ls_prep_bwd(const LsBwd& p, const LsPrepBwd& q, hipStream_t st);
+template <typename TE> hipError_t launch_ls_prep_bwd(const LsPrepBwd& q, hipStream_t st);
 // wavefront d = 0 .. T + L - 2
 template <typename TE> hipError_t launch_ls_wave_fwd(const LsFwd& p, int d, hipStream_t st);
 // wavefront d = 0 .. T + L - 2 + (dh0 != null)
@@ -95,6 +98,6 @@ hipError_t launch_ls_bias_reduce(const float* dbacc, const LsBiasOut& o, int L, 
 // Whether the input product of layer 0 is one product over all steps ahead of the wavefronts.
 template <typename TE> bool ls_input_apart(int T, int B, int I, int H, int L);
 // Whether forward wavefronts read the caller's weight rows instead of tiles made from them.
-template <typename TE> bool ls_reads_weight_rows(int T, int I, int H, int L);
+template <typename TE> bool ls_reads_weight_rows(int T, int I, int H);
 
 }  // namespace asx

@@ -701,15 +701,14 @@ __global__ __launch_bounds__(256) void ls_prep_fwd_kernel(LsFwd p, LsPrepFwd s) 
   }
 }
 
-// Jobs (blockIdx.y): W_hh^T of each layer, then W_ih[l + 1]^T.  Tile row rho of tile i: unit 16 i + 4 q + r.
+// blockIdx.y: the weight.  Tile row rho of tile i: unit 16 i + 4 q + r.
 template <typename TE>
-__global__ __launch_bounds__(256) void ls_prep_bwd_kernel(LsBwd p, LsPrepBwd s) {
+__global__ __launch_bounds__(256) void ls_prep_bwd_kernel(LsPrepBwd s) {
   typedef LsMma<TE> M;
   constexpr int V = LsGeom<TE>::kVec, KST = LsGeom<TE>::kKStep;
-  const int job = blockIdx.y, H = p.H, L = p.L;
-  const int l = job < L ? job : job - L;
-  const TE* W = reinterpret_cast<const TE*>(job < L ? s.W_hh[l] : s.W_ih[l + 1]);
-  char* dst = const_cast<char*>(job < L ? p.WT_hh[l] : p.WT_up[l]);
+  const int H = s.H;
+  const TE* W = reinterpret_cast<const TE*>(s.W[blockIdx.y]);
+  char* dst = s.tiles[blockIdx.y];
   const int GS = ls_gate_stride<TE>(H), ntu = (H + 63) / 64 * 4;
   const int nks = 4 * GS / KST;
   const int64_t n = (int64_t)nks * ntu * 64;
@@ -741,7 +740,7 @@ __global__ __launch_bounds__(256) void ls_bias_reduce_kernel(const float* __rest
 // ---- launches ----------------------------------------------------------------------
 // One step: making tiles (64 bytes moved per 16 used once) costs more than the rows' half-used lines do.  128 sentences, 1024
 // units: 17 us per layer from rows, 13 from tiles and 7 to make them.  From two steps on the tiles are read again.
-template <typename TE> bool ls_reads_weight_rows(int T, int I, int H, int) {
+template <typename TE> bool ls_reads_weight_rows(int T, int I, int H) {
   return T == 1 && I % LsGeom<TE>::kVec == 0 && H % LsGeom<TE>::kVec == 0;
 }
 
@@ -776,11 +775,12 @@ template <typename TE> hipError_t launch_ls_prep_fwd(const LsFwd& p, const LsPre
   hipLaunchKernelGGL(ls_prep_fwd_kernel<TE>, dim3((unsigned)gx, jobs), dim3(256), 0, st, p, q);
   return hipGetLastError();
 }
-template <typename TE> hipError_t launch_ls_prep_bwd(const LsBwd& p, const LsPrepBwd& q, hipStream_t st) {
-  const int64_t n = (int64_t)(4 * ls_gate_stride<TE>(p.H) / LsGeom<TE>::kKStep) * ls_unit_tiles(p.H) * 64;
+template <typename TE> hipError_t launch_ls_prep_bwd(const LsPrepBwd& q, hipStream_t st) {
+  if (q.n < 1) return hipSuccess;
+  const int64_t n = (int64_t)(4 * ls_gate_stride<TE>(q.H) / LsGeom<TE>::kKStep) * ls_unit_tiles(q.H) * 64;
   int64_t gx = (n + 255) / 256;
   if (gx > 1024) gx = 1024;
-  hipLaunchKernelGGL(ls_prep_bwd_kernel<TE>, dim3((unsigned)gx, 2 * p.L - 1), dim3(256), 0, st, p, q);
+  hipLaunchKernelGGL(ls_prep_bwd_kernel<TE>, dim3((unsigned)gx, q.n), dim3(256), 0, st, q);
   return hipGetLastError();
 }
 hipError_t launch_ls_bias_reduce(const float* dbacc, const LsBiasOut& o, int L, int nct, int cols, hipStream_t st) {
@@ -850,10 +850,10 @@ template <typename TE> hipError_t launch_ls_wave_bwd(const LsBwd& p, int d, hipS
 }
 
 #define ASX_LS(TE)                                                                                  \
-  template bool ls_reads_weight_rows<TE>(int, int, int, int);                                       \
+  template bool ls_reads_weight_rows<TE>(int, int, int);                                            \
   template bool ls_input_apart<TE>(int, int, int, int, int);                                        \
   template hipError_t launch_ls_prep_fwd<TE>(const LsFwd&, const LsPrepFwd&, hipStream_t);          \
-  template hipError_t launch_ls_prep_bwd<TE>(const LsBwd&, const LsPrepBwd&, hipStream_t);          \
+  template hipError_t launch_ls_prep_bwd<TE>(const LsPrepBwd&, hipStream_t);                        \
   template hipError_t launch_ls_wave_fwd<TE>(const LsFwd&, int, hipStream_t);                       \
   template hipError_t launch_ls_wave_bwd<TE>(const LsBwd&, int, hipStream_t);
 ASX_LS(uint16_t)
