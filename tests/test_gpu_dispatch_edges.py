@@ -46,10 +46,32 @@ def test_bf16_products_in_64x64_tiles(shape, skip):
     _parity(make_custom(T=T, S=S, B=B, H=H, V=V, seed=H, dtype="bf16", min_len=1, pad_prob=0.2), skip)
 
 
+def test_lstm_f32_largest_block_in_vectors():
+    """16 units x 32 sentences in fp32 with a hidden size of whole vectors (other sizes: test_lstm_wavefronts_at_block_edges)."""
+    import test_gpu_lstm as tl
+    from synth_inputs import make_lstm_inputs
+    inp = make_lstm_inputs(4, 65, 24, 1028, 4, seed=1028, dtype="f32")
+    f, g, _ = tl.run_gpu(inp)
+    fo, go = tl.run_oracle(inp)
+    tl.compare(inp, f, g, fo, go)
+
+
+@pytest.mark.parametrize("shape", [(70, 5, 200, 643),          # a second sweep over the source positions
+                                   (131, 3, 264, 997),         # more than the fused kernel takes forward
+                                   (1500, 2, 512, 777)])       # many sweeps
+def test_one_step_attention_backward(shape):
+    """T = 1, bf16: one workgroup per sentence, 64 source positions at a time."""
+    S, B, H, V = shape
+    _parity(make_custom(T=1, S=S, B=B, H=H, V=V, seed=S, dtype="bf16", min_len=1))
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shape", [(3, 1, 8, 8, 2),            # one sentence
                                    (5, 33, 40, 200, 3),        # units and sentences past every block shape
-                                   (4, 65, 24, 1032, 2),       # enough blocks for the larger shapes, with remainders
+                                   (4, 65, 24, 1032, 2),       # remainders in 16 units x 32 sentences forward
+                                   # 32 units x 64 sentences forward, 64 x 32 backward (fp32: 16 x 32 both ways): the
+                                   # largest blocks, from four (three) layers in one launch on, with remainders
+                                   (5, 65, 24, 1032, 4),
                                    # one step: the caller's weight rows, widths of whole vectors.  (c = f c0 + i g is
                                    # rounded at 2^-24 of its terms, 6e-8: elements of y below 6e-4, about one in a
                                    # thousand, need the row-scale floor; a tensor of 1275 admits one, this one four.)
@@ -70,7 +92,8 @@ def test_lstm_wavefronts_at_block_edges(shape, dtype):
 @pytest.mark.parametrize("states", [True, False])
 @pytest.mark.parametrize("shape", [(16, 21, 648, 72, 1),       # a wide x: its product ahead of the wavefronts, ragged tiles
                                    (8, 33, 1032, 40, 3),       # with layers above it
-                                   (24, 9, 512, 1024, 1)])     # narrower than the state, few sentences
+                                   (24, 9, 512, 1024, 1),      # narrower than the state, few sentences
+                                   (4, 65, 2064, 1032, 4)])    # in the largest block
 def test_lstm_wide_input(shape, states):
     import test_gpu_lstm as tl
     from synth_inputs import make_lstm_inputs
