@@ -206,9 +206,10 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
 
   // Segments: own state, then the input.  x is exact in the storage type, it has no remainder.  The widest block reduces
   // the two segments of layer 0 one after the other, the second without remainders (one loop for both spilled 32
-  // registers: lstm_paper sizes 3.60 -> 3.53 ms).  In the smaller ones the refill between two loops costs more (a step by
-  // itself 147 -> 148 us for four layers): they read zeroed tiles as the remainder and clear the weight ahead of the
-  // product, because 0 * inf would be NaN.
+  // registers: 4 x 1024 units x 128 sentences 1508 -> 1410 us).  In the smaller ones the refill between two loops costs
+  // more (a step by itself 147 -> 148 us for four layers): they load zeroed tiles as the remainder and branch around its
+  // product, a block of its own behind the one the loads are spread over (0 * inf would be NaN; the weight cleared by a
+  // mask instead, 50 x 128 x 512 units x 4 took 699 us, 681 so).
   constexpr bool TWO = M::kPair && !APART && NI * NJ >= 32;
   const bool apart = APART && l == 0;
   const int n0 = (H + KST - 1) / KST, n1 = apart ? 0 : (Kin + KST - 1) / KST;
@@ -275,14 +276,10 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
 #pragma unroll
       for (int j = 0; j < NJ; ++j) M::mma(acc[i][j], wf[slot][i], hf[slot][j]);
     if (M::kPair && rest) {
-      const uint32_t keep = !TWO && !APART && l == 0 && s >= n0 ? 0u : ~0u;
 #pragma unroll
-      for (int i = 0; i < NI; ++i) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) wf[slot][i][e] &= keep;
+      for (int i = 0; i < NI; ++i)
 #pragma unroll
         for (int j = 0; j < NJ; ++j) M::mma(acc[i][j], wf[slot][i], lf[slot][j]);
-      }
     }
   };
   constexpr int NP = M::kPair ? 2 : 1, NM = M::kPair ? 2 * NI * NJ : 4 * NI * NJ;
@@ -293,6 +290,16 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
     wave_reduce<PF, NI + NJ, NM / 2>(
         own - own0, [&](int slot, int i) { load(slot, own0 + i, false); },
         [&](int slot, int i) { mul(slot, own0 + i, false); });
+  } else if constexpr (M::kPair && !APART) {
+    wave_reduce<PF, NI + NP * NJ, NM / 2>(
+        own, load, [&](int slot, int i) { mul(slot, i, false); },
+        [&](int slot, int i) {
+          if (l == 0 && wave + i * LS_KS >= n0) return;
+#pragma unroll
+          for (int ii = 0; ii < NI; ++ii)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) M::mma(acc[ii][j], wf[slot][ii], lf[slot][j]);
+        });
   } else {
     wave_reduce<PF, NI + NP * NJ, NM>(own, load, mul);
   }

@@ -19,14 +19,19 @@ template <int v, int NL, int NM> __device__ __forceinline__ void spread_loads() 
   }
 }
 
+struct NoRest {
+  __device__ __forceinline__ void operator()(int, int) const {}
+};
+
 // A wave's n reduction steps, slot i % PF of the fragment registers holding step i.  load(slot, i) must be free of
 // branches and valid for 0 <= i < n; past the last step it is called with the last one again, so that the number of
 // loads in flight is the same on every path and a wait covers just the fragments it needs.
 // The NL loads of a step are spread over the NM matrix instructions of an earlier one.  Issued in one run they hold the
 // wave at the address unit while its matrix pipe idles: forward wavefronts of 4 layers x 1024 units x 128 sentences
 // then took the sum of their load and matrix times.
-template <int PF, int NL, int NM, typename Load, typename Mul>
-__device__ __forceinline__ void wave_reduce(int n, Load load, Mul mul) {
+// rest(slot, i): products of step i that may need a branch, behind the region that the loads are spread over.
+template <int PF, int NL, int NM, typename Load, typename Mul, typename Rest = NoRest>
+__device__ __forceinline__ void wave_reduce(int n, Load load, Mul mul, Rest rest = Rest()) {
   if (n <= 0) return;
   auto at = [&](int i) { return i < n ? i : n - 1; };
 #pragma unroll
@@ -40,11 +45,15 @@ __device__ __forceinline__ void wave_reduce(int n, Load load, Mul mul) {
       load((u + PF - 1) % PF, at(i + u + PF - 1));
       spread_loads<0, NL, NM>();
       __builtin_amdgcn_sched_barrier(0);
+      rest(u, at(i + u));
     }
   }
 #pragma unroll
   for (int u = 0; u + 1 < PF; ++u)
-    if (i + u < n) mul(u, at(i + u));
+    if (i + u < n) {
+      mul(u, at(i + u));
+      rest(u, at(i + u));
+    }
 }
 
 }  // namespace asx
