@@ -751,17 +751,22 @@ template <typename TE> bool ls_reads_weight_rows(int T, int I, int H) {
   return T == 1 && I % LsGeom<TE>::kVec == 0 && H % LsGeom<TE>::kVec == 0;
 }
 
+// Blocks of 32 units x 64 sentences in n layers, and whether they are enough for most compute units.
+static bool ls_widest_fwd(int n, int B, int H) { return (int64_t)n * ((H + 31) / 32) * ((B + 63) / 64) >= 192; }
+
 // Folded into the wavefronts, the input product of layer 0 lengthens a chain of T dependent launches by what I reduction
 // indices take (0.7 us a launch at I = 512); as one product ahead of them it costs a launch and the round trip of the gates.
-// With more than one layer a launch has reductions of 2 H in it anyway.  Forward, us, folded / apart, at T x B, I -> H:
-//   L = 1  50 x 16, 512 -> 64: 331 / 303, 1024 -> 256: 392 / 336, 4096 -> 256: 623 / 348, 512 -> 1024: 423 / 409,
-//          256 -> 128: 318 / 324; 50 x 128, 512 -> 512: 399 / 393, 512 -> 1024: 538 / 547, 1024 -> 1024: 600 / 565;
-//          10 x 512, 512 -> 256: 97 / 102, 1024 -> 512: 165 / 157; 3 x 128, 1024 -> 256: 33 / 36
-//   L = 2  50 x 128, 512 -> 256: 375 / 366, 512 -> 512: 482 / 490, 1024 -> 1024: 992 / 1046; 3 x 128, 2048 -> 512: 60 / 63
-//   L = 4  50 x 128, 512 -> 1024: 1620 / 1663, 1024 -> 512: 822 / 747
+// With more than one layer a launch has reductions of 2 H in it anyway, and the widest blocks do it at little more than the
+// product's own rate.  Forward, us, folded / apart, at T x B, I -> H:
+//   L = 1  50 x 16, 512 -> 64: 317 / 304, 1024 -> 256: 373 / 336, 4096 -> 256: 594 / 349, 512 -> 1024: 409 / 404,
+//          256 -> 128: 308 / 324; 50 x 128, 512 -> 512: 396 / 392, 512 -> 1024: 516 / 526, 1024 -> 1024: 568 / 546;
+//          10 x 512, 512 -> 256: 91 / 99, 2048 -> 512: 208 / 174, 2048 -> 1024: 296 / 325; 3 x 128, 1024 -> 256: 32 / 36
+//   L = 2  50 x 128, 512 -> 256: 363 / 363, 512 -> 512: 467 / 481, 1024 -> 1024: 968 / 1014; 20 x 256, 2048 -> 512: 406 / 317;
+//          10 x 512, 2048 -> 1024: 574 / 645; 3 x 128, 2048 -> 512: 59 / 61
+//   L = 4  50 x 128, 512 -> 1024: 1385 / 1521, 1024 -> 512: 783 / 727; 20 x 256, 1024 -> 512: 459 / 497
 // fp32 storage is always folded: the matrix instructions bound it, and a sum over both segments is rounded once.
 template <typename TE> bool ls_input_apart(int T, int B, int I, int H, int L) {
-  if (!LsMma<TE>::kPair || T == 1 || (int64_t)T * (I - 256) < 6000) return false;
+  if (!LsMma<TE>::kPair || T == 1 || (int64_t)T * (I - 256) < 6000 || ls_widest_fwd(L < T ? L : T, B, H)) return false;
   return L > 1 ? I >= 2 * H : I >= H || (2 * I >= H && B <= 32);
 }
 
@@ -798,11 +803,13 @@ hipError_t launch_ls_bias_reduce(const float* dbacc, const LsBiasOut& o, int L, 
 template <typename TE, int NI, int NJ, int PF>
 static hipError_t ls_fwd_shape(const LsFwd& p, int d, int l_lo, int nl, hipStream_t st) {
   const unsigned grid = ls_grid((int64_t)nl * ((p.H + 4 * NI - 1) / (4 * NI)), (p.B + 16 * NJ - 1) / (16 * NJ));
+  constexpr bool kApart = LsMma<TE>::kPair && NI * NJ < 32;
 #define ASX_FWD(ROWS, VEC, APART)                                                                                    \
   hipLaunchKernelGGL((ls_wave_fwd_kernel<TE, NI, NJ, PF, ROWS, VEC, APART>), dim3(grid), dim3(64 * LS_KS), 0, st, p, \
                      d, l_lo, nl)
+  if (p.x_apart && (p.w_rows || !kApart)) return hipErrorInvalidValue;   // (ls_input_apart excludes both)
   if (p.w_rows) ASX_FWD(true, true, false);   // widths are multiples of 4
-  else if (LsMma<TE>::kPair && p.x_apart && l_lo == 0) ASX_FWD(false, true, LsMma<TE>::kPair);
+  else if (kApart && p.x_apart && l_lo == 0) ASX_FWD(false, true, kApart);
   else if (LsMma<TE>::kPair || p.H % 4 == 0) ASX_FWD(false, true, false);
   else ASX_FWD(false, LsMma<TE>::kPair, false);
 #undef ASX_FWD
@@ -823,12 +830,12 @@ template <typename TE> hipError_t launch_ls_wave_fwd(const LsFwd& p, int d, hipS
   const int l_lo = d - p.T + 1 > 0 ? d - p.T + 1 : 0, l_hi = d < p.L - 1 ? d : p.L - 1;   // 0 <= d - l < T
   const int nl = l_hi - l_lo + 1;
   if (nl < 1) return hipErrorInvalidValue;
-  const int64_t b64 = (p.B + 63) / 64, b32 = (p.B + 31) / 32;
+  const int64_t b32 = (p.B + 31) / 32;
   // The largest block that still gives most compute units one: larger blocks load less per output (128 gate rows x 64
   // sentences: 512 bytes per reduction index for 8192 outputs).  1024 units x 128 sentences, 64 x 32 blocks against 128 x 64:
   // three layers 27.5 us (768 blocks) and 28.0 (192), four 34.0 (1024) and 29.4 (256).
   if constexpr (LsMma<TE>::kPair) {
-    if (nl * ((p.H + 31) / 32) * b64 >= 192) return ls_fwd_shape<TE, 8, 4, 3>(p, d, l_lo, nl, st);
+    if (ls_widest_fwd(nl, p.B, p.H)) return ls_fwd_shape<TE, 8, 4, 3>(p, d, l_lo, nl, st);   // (never with x_apart)
     if (nl * ((p.H + 15) / 16) * b32 >= 192) return ls_fwd_shape<TE, 4, 2, 4>(p, d, l_lo, nl, st);
     return ls_fwd_shape<TE, 4, 1, 4>(p, d, l_lo, nl, st);
   } else {

@@ -23,6 +23,8 @@ I32 = ctypes.c_int
     (50, 16, 512, 64, 1, True), (50, 16, 1024, 256, 1, True), (50, 16, 4096, 256, 1, True), (50, 16, 512, 1024, 1, True),
     (50, 128, 512, 512, 1, True), (50, 128, 1024, 1024, 1, True), (50, 128, 512, 256, 2, True),
     (50, 128, 1024, 512, 4, True), (50, 128, 4096, 1024, 2, True),
+    (10, 512, 2048, 512, 1, True), (20, 256, 2048, 512, 2, True),
+    (10, 512, 2048, 1024, 1, False), (10, 512, 2048, 1024, 2, False), (20, 256, 1024, 512, 4, False),
     (50, 16, 256, 128, 1, False), (50, 128, 512, 1024, 1, False), (10, 512, 512, 256, 1, False),
     (3, 128, 1024, 256, 1, False), (3, 128, 2048, 512, 2, False), (1, 128, 4096, 256, 1, False), (1, 128, 65536, 256, 1, False),
     (50, 128, 512, 512, 2, False),

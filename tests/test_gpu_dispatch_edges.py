@@ -93,7 +93,7 @@ def test_lstm_wavefronts_at_block_edges(shape, dtype):
 @pytest.mark.parametrize("shape", [(16, 21, 648, 72, 1),       # a wide x: its product ahead of the wavefronts, ragged tiles
                                    (8, 33, 1032, 40, 3),       # with layers above it
                                    (24, 9, 512, 1024, 1),      # narrower than the state, few sentences
-                                   (4, 65, 2064, 1032, 4)])    # in the largest block
+                                   (4, 65, 2064, 520, 2)])     # in 16 units x 32 sentences
 def test_lstm_wide_input(shape, states):
     import test_gpu_lstm as tl
     from synth_inputs import make_lstm_inputs
