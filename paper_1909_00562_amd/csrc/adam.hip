@@ -2,8 +2,9 @@
 // settings"; Kingma and Ba, Algorithm 1).  One streaming pass: per element 16
 // bytes read (gradient, both moments, master weight), 12 written back and the
 // 2- or 4-byte copy in the storage type of the forward pass; HBM-bound.  Nothing but
-// that copy is read again soon: where they do not fit there, the other streams go past the caches (195 -> 175 us at
-// 32.8M elements).
+// that copy is read again soon: the other streams go past the caches where they would not stay there.
+// 33.5M elements, bf16 copy, after other work: 200 us as a grid-stride loop through the caches, 191 with one vector
+// per thread, 184 past the caches too (5.5 TB/s); repeated on one tensor 199, 190, 156.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -75,12 +76,13 @@ hipError_t launch_adam_step(size_t n, const float* grad, float* master, float* m
   const size_t n4 = n / 4;
   size_t blocks = (n4 + 255) / 256;
   // One vector per thread: blocks that come and go keep the streams in step, a grid-stride loop of resident blocks drifts
-  // apart.  32.8M elements: 16 blocks per compute unit 195 us, 64 of them 162, one vector each 157 (983 MB, 6.3 TB/s).
+  // apart (32.8M elements past the caches: 16 blocks per compute unit 175 us, 64 of them 162, one vector each 157).
   if (blocks > (size_t)1 << 20) blocks = (size_t)1 << 20;
   if (blocks < 1) blocks = 1;
   dim3 grid((unsigned)blocks), blk(256);
-  // Past the caches only where a tensor's streams exceed the 256 MB memory-side cache: below, the next step finds them there
-  // (8.2M elements: 45 us through the caches, 50 past them).
+  // Past the caches only where a tensor's streams exceed the 256 MB memory-side cache: below, a next update that follows at
+  // once finds them there (8.2M elements: 45 us through the caches, 50 past them).  Above, it still finds some (12.6M: 54
+  // and 62 us, 18.9M: 88 and 92, 21M: 111 and 101), but after a training step's other work it does not (12.6M: 73 and 62).
   const bool nt = n * 28 > (size_t)256 << 20;
 #define ASX_ADAM(BF, HO) \
   if (nt) ASX_ADAM_NT(BF, HO, true); \

@@ -439,7 +439,9 @@ static as_status fwd_impl(const as_shape* s, const void* h_dec, const void* h_en
     g.C_lo = w + L.q_lo;
     AS_TRY(AS_STAGE_GEMM_Q, launch_gemm(g, bf, L.p_q.tile, st));
   }
-  // (T = 1 too: a step by itself gives the same bits as in a batch of steps, which the row sums of attn_step.hip would not)
+  // (T = 1 too: from the same Q, alpha and ctx of a step by itself are the same bits as in a batch of steps, which the row
+  // sums of attn_step.hip would not give.  Whole calls are where Q and h_c have the same plan at both row counts, as small
+  // models do; else h_c, split by the row count, adds in another order.)
   if (bf && attn_fwd_fused_supported(S, H)) {
     // Eq. 2 (second half), 1 and 3 in one kernel per (sentence, 32 decoder steps): the scores stay on chip
     AS_TRY(AS_STAGE_ATTN_SCORE,

@@ -546,9 +546,9 @@ GemmPlan gemm_plan(int M, int N, int K, int batch, bool bf16, bool allow_split, 
       }
     }
   }
-  // Which of the two shapes of gemm_tile.hip, if they are faster than 256 x 256.  With more than a round of 256 x 256 tiles that kernel
-  // stays: it writes a tile while the next one is on its way, which the models leave out (2257 x 32003 x 1000: 174 us, 231
-  // with 128 x 128, 184 by the model).
+  // Which of the two shapes of gemm_tile.hip, if they are faster than 256 x 256.  With more than a round of 256 x 256
+  // tiles that kernel stays: it writes a tile while the next one is on its way, which the models leave out
+  // (2257 x 32003 x 1000: 174 us, 231 with 128 x 128, 184 by the model).
   double now = 1e30;
   if (pl.tile == kTile256) {
     if ((int64_t)((M + 255) / 256) * ((N + 255) / 256) * batch * pl.splits > 256) return pl;

@@ -62,7 +62,7 @@ template <typename TE, typename Take> void ls_fwd_tiles(const ls_shape* s, LsLay
   const int T = s->T, I = s->I, H = s->H, NL = s->L;
   const size_t nct = ls_batch_tiles(s->B);
   const int copies = sizeof(TE) == 2 ? 2 : 1;
-  L.x_apart = ls_input_apart<TE>(T, s->B, I, H, NL);
+  L.x_apart = ls_input_apart<TE>(T, I, H, NL);
   L.w_rows = ls_reads_weight_rows<TE>(T, I, H);
   L.x_stride = L.x_apart ? 0 : (int64_t)(ls_ksteps<TE>(I) * nct * kLsTile);
   L.h_stride = (int64_t)(ls_ksteps<TE>(H) * nct * kLsTile);

@@ -96,7 +96,7 @@ struct LsBiasOut {
 };
 hipError_t launch_ls_bias_reduce(const float* dbacc, const LsBiasOut& o, int L, int nct, int cols, hipStream_t st);
 // Whether the input product of layer 0 is one product over all steps ahead of the wavefronts.
-template <typename TE> bool ls_input_apart(int T, int B, int I, int H, int L);
+template <typename TE> bool ls_input_apart(int T, int I, int H, int L);
 // Whether forward wavefronts read the caller's weight rows instead of tiles made from them.
 template <typename TE> bool ls_reads_weight_rows(int T, int I, int H);
 

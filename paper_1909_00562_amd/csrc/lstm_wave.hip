@@ -19,7 +19,7 @@
 //     rounding compounds over steps and layers.  Gate gradients enter the backward products as plain bf16.
 //   * fp32 storage: fp64 matrix instructions on operands widened after the load, as in gemm_f32.hip.
 //
-// 4 layers x 1024 units x 128 sentences, full wavefronts: 28.9 us forward, 28.8 backward, of which 12 are not the
+// 4 layers x 1024 units x 128 sentences, full wavefronts: 28 us forward, 28.8 backward, of which 12 are not the
 // reduction (launch, cells, 14 MB of stores); 64 MB of weights and 1 MB (forward) or 1.5 MB (backward) of fragments per
 // compute unit make the rest.  A launch per layer and step took 10.5 us each, 42 for what a wavefront does, and the input
 // products another 90 per layer.  Tried without gain: weights streamed past the caches (34.6 / 40.7 us), other tile orders
@@ -210,15 +210,16 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
   // more (a step by itself 147 -> 148 us for four layers): they load zeroed tiles as the remainder and branch around its
   // product, a block of its own behind the one the loads are spread over (0 * inf would be NaN; the weight cleared by a
   // mask instead, 50 x 128 x 512 units x 4 took 699 us, 681 so).
-  constexpr bool TWO = M::kPair && !APART && NI * NJ >= 32;
+  constexpr bool TWO = M::kPair && NI * NJ >= 32;
   const bool apart = APART && l == 0;
   const int n0 = (H + KST - 1) / KST, n1 = apart ? 0 : (Kin + KST - 1) / KST;
   const int64_t cstep = (int64_t)nct * kLsTile;
   const char* h_hi = p.hF_hi + (2 * l + (t & 1)) * p.h_stride;
   const char* h_lo = M::kPair ? p.hF_lo + (2 * l + (t & 1)) * p.h_stride : nullptr;
   const char* i_hi = l == 0 ? p.xF + t * p.x_stride : p.oF_hi + (2 * (l - 1) + (t & 1)) * p.h_stride;
-  const char* i_lo = !M::kPair ? nullptr : l == 0 ? p.zeros : p.oF_lo + (2 * (l - 1) + (t & 1)) * p.h_stride;
-  const int64_t lstep1 = l == 0 ? 0 : cstep;
+  const bool no_rest = !TWO && !APART && l == 0;   // the input's remainder: zeroed tiles
+  const char* i_lo = !M::kPair ? nullptr : no_rest ? p.zeros : p.oF_lo + (2 * (l - 1) + (t & 1)) * p.h_stride;
+  const int64_t lstep1 = no_rest ? 0 : cstep;
   int64_t ctoff[NJ];
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
@@ -751,23 +752,20 @@ template <typename TE> bool ls_reads_weight_rows(int T, int I, int H) {
   return T == 1 && I % LsGeom<TE>::kVec == 0 && H % LsGeom<TE>::kVec == 0;
 }
 
-// Blocks of 32 units x 64 sentences in n layers, and whether they are enough for most compute units.
-static bool ls_widest_fwd(int n, int B, int H) { return (int64_t)n * ((H + 31) / 32) * ((B + 63) / 64) >= 192; }
-
 // Folded into the wavefronts, the input product of layer 0 lengthens a chain of T dependent launches by what I reduction
 // indices take (0.7 us a launch at I = 512); as one product ahead of them it costs a launch and the round trip of the gates.
-// With more than one layer a launch has reductions of 2 H in it anyway, and the widest blocks do it at little more than the
-// product's own rate.  Forward, us, folded / apart, at T x B, I -> H:
+// With more than one layer a launch has reductions of 2 H in it anyway.  The number of sentences has no part in the rule: the
+// two ways add in different orders, and a sentence's result must not depend on its batch.  Forward, us, folded / apart, at
+// T x B, I -> H:
 //   L = 1  50 x 16, 512 -> 64: 317 / 304, 1024 -> 256: 373 / 336, 4096 -> 256: 594 / 349, 512 -> 1024: 409 / 404,
 //          256 -> 128: 308 / 324; 50 x 128, 512 -> 512: 396 / 392, 512 -> 1024: 516 / 526, 1024 -> 1024: 568 / 546;
-//          10 x 512, 512 -> 256: 91 / 99, 2048 -> 512: 208 / 174, 2048 -> 1024: 296 / 325; 3 x 128, 1024 -> 256: 32 / 36
-//   L = 2  50 x 128, 512 -> 256: 363 / 363, 512 -> 512: 467 / 481, 1024 -> 1024: 968 / 1014; 20 x 256, 2048 -> 512: 406 / 317;
-//          10 x 512, 2048 -> 1024: 574 / 645; 3 x 128, 2048 -> 512: 59 / 61
-//   L = 4  50 x 128, 512 -> 1024: 1385 / 1521, 1024 -> 512: 783 / 727; 20 x 256, 1024 -> 512: 459 / 497
+//          10 x 512, 512 -> 256: 91 / 99, 2048 -> 512: 208 / 174; 3 x 128, 1024 -> 256: 32 / 36
+//   L = 2  50 x 128, 512 -> 256: 363 / 363, 512 -> 512: 467 / 481, 1024 -> 1024: 968 / 1014; 20 x 256, 2048 -> 512: 406 /
+//          317; 3 x 128, 2048 -> 512: 59 / 61
+//   L = 4  50 x 128, 512 -> 1024: 1385 / 1521, 1024 -> 512: 783 / 727
 // fp32 storage is always folded: the matrix instructions bound it, and a sum over both segments is rounded once.
-template <typename TE> bool ls_input_apart(int T, int B, int I, int H, int L) {
-  if (!LsMma<TE>::kPair || T == 1 || (int64_t)T * (I - 256) < 6000 || ls_widest_fwd(L < T ? L : T, B, H)) return false;
-  return L > 1 ? I >= 2 * H : I >= H || (2 * I >= H && B <= 32);
+template <typename TE> bool ls_input_apart(int T, int I, int H, int L) {
+  return LsMma<TE>::kPair && T > 1 && (int64_t)T * (I - 256) >= 6000 && I >= (L > 1 ? 2 * H : H);
 }
 
 template <typename TE> hipError_t launch_ls_prep_fwd(const LsFwd& p, const LsPrepFwd& q, hipStream_t st) {
@@ -803,13 +801,12 @@ hipError_t launch_ls_bias_reduce(const float* dbacc, const LsBiasOut& o, int L, 
 template <typename TE, int NI, int NJ, int PF>
 static hipError_t ls_fwd_shape(const LsFwd& p, int d, int l_lo, int nl, hipStream_t st) {
   const unsigned grid = ls_grid((int64_t)nl * ((p.H + 4 * NI - 1) / (4 * NI)), (p.B + 16 * NJ - 1) / (16 * NJ));
-  constexpr bool kApart = LsMma<TE>::kPair && NI * NJ < 32;
 #define ASX_FWD(ROWS, VEC, APART)                                                                                    \
   hipLaunchKernelGGL((ls_wave_fwd_kernel<TE, NI, NJ, PF, ROWS, VEC, APART>), dim3(grid), dim3(64 * LS_KS), 0, st, p, \
                      d, l_lo, nl)
-  if (p.x_apart && (p.w_rows || !kApart)) return hipErrorInvalidValue;   // (ls_input_apart excludes both)
+  if (p.x_apart && p.w_rows) return hipErrorInvalidValue;   // (ls_input_apart: not with one step)
   if (p.w_rows) ASX_FWD(true, true, false);   // widths are multiples of 4
-  else if (kApart && p.x_apart && l_lo == 0) ASX_FWD(false, true, kApart);
+  else if (LsMma<TE>::kPair && p.x_apart && l_lo == 0) ASX_FWD(false, true, LsMma<TE>::kPair);
   else if (LsMma<TE>::kPair || p.H % 4 == 0) ASX_FWD(false, true, false);
   else ASX_FWD(false, LsMma<TE>::kPair, false);
 #undef ASX_FWD
@@ -830,12 +827,12 @@ template <typename TE> hipError_t launch_ls_wave_fwd(const LsFwd& p, int d, hipS
   const int l_lo = d - p.T + 1 > 0 ? d - p.T + 1 : 0, l_hi = d < p.L - 1 ? d : p.L - 1;   // 0 <= d - l < T
   const int nl = l_hi - l_lo + 1;
   if (nl < 1) return hipErrorInvalidValue;
-  const int64_t b32 = (p.B + 31) / 32;
+  const int64_t b64 = (p.B + 63) / 64, b32 = (p.B + 31) / 32;
   // The largest block that still gives most compute units one: larger blocks load less per output (128 gate rows x 64
   // sentences: 512 bytes per reduction index for 8192 outputs).  1024 units x 128 sentences, 64 x 32 blocks against 128 x 64:
   // three layers 27.5 us (768 blocks) and 28.0 (192), four 34.0 (1024) and 29.4 (256).
   if constexpr (LsMma<TE>::kPair) {
-    if (ls_widest_fwd(nl, p.B, p.H)) return ls_fwd_shape<TE, 8, 4, 3>(p, d, l_lo, nl, st);   // (never with x_apart)
+    if (nl * ((p.H + 31) / 32) * b64 >= 192) return ls_fwd_shape<TE, 8, 4, 3>(p, d, l_lo, nl, st);
     if (nl * ((p.H + 15) / 16) * b32 >= 192) return ls_fwd_shape<TE, 4, 2, 4>(p, d, l_lo, nl, st);
     return ls_fwd_shape<TE, 4, 1, 4>(p, d, l_lo, nl, st);
   } else {
@@ -865,7 +862,7 @@ template <typename TE> hipError_t launch_ls_wave_bwd(const LsBwd& p, int d, hipS
 
 #define ASX_LS(TE)                                                                                  \
   template bool ls_reads_weight_rows<TE>(int, int, int);                                            \
-  template bool ls_input_apart<TE>(int, int, int, int, int);                                        \
+  template bool ls_input_apart<TE>(int, int, int, int);                                             \
   template hipError_t launch_ls_prep_fwd<TE>(const LsFwd&, const LsPrepFwd&, hipStream_t);          \
   template hipError_t launch_ls_prep_bwd<TE>(const LsPrepBwd&, hipStream_t);                        \
   template hipError_t launch_ls_wave_fwd<TE>(const LsFwd&, int, hipStream_t);                       \

@@ -338,7 +338,9 @@ int xent_rows_per_block(int N, int V, bool e_bf16) {
   const int64_t strips = (ldV + 256 * vec - 1) / (256 * vec);
   // About 32768 blocks, of 16 rows and more: short-lived blocks keep to one neighbourhood of rows, long ones drift apart
   // (16384 x 128000, three quarters words, with the column sums' reduction: 252 rows 1285 us, 128 1243, 64 1227, 32
-  // 1206; 6400 x 32000: 28 rows 119 us, 16 118.5, 8 140).  Eight rows where 16 would leave fewer than 2048 blocks.
+  // 1206; 6400 x 32000: 28 rows 119 us, 16 118.5, 8 140).  Eight rows where 16 would leave fewer than 2048 blocks.  The
+  // blocks' column sums take V floats each (16384 x 128000: 262 MB at 32 rows, 33 at 252), where the partial sums of the
+  // products go afterwards.
   int64_t rb = ((int64_t)N * strips + 32767) / 32768;
   const int64_t least = (int64_t)N * strips >= 16 * 2048 ? 16 : 8;
   if (rb < least) rb = least;

@@ -92,8 +92,8 @@ def test_lstm_wavefronts_at_block_edges(shape, dtype):
 @pytest.mark.parametrize("states", [True, False])
 @pytest.mark.parametrize("shape", [(16, 21, 648, 72, 1),       # a wide x: its product ahead of the wavefronts, ragged tiles
                                    (8, 33, 1032, 40, 3),       # with layers above it
-                                   (24, 9, 512, 1024, 1),      # narrower than the state, few sentences
-                                   (4, 65, 2064, 520, 2)])     # in 16 units x 32 sentences
+                                   (4, 65, 2064, 520, 2),      # in 16 units x 32 sentences
+                                   (4, 65, 2064, 1032, 4)])    # in 32 units x 64 sentences
 def test_lstm_wide_input(shape, states):
     import test_gpu_lstm as tl
     from synth_inputs import make_lstm_inputs
@@ -112,3 +112,21 @@ def test_static_scratch_just_below_its_size(skip):
     inp = make_custom(T=5, S=53, B=103, H=32, V=27126, seed=5, dtype="f32", min_len=1, pad_prob=0.2)
     na._run_pair(inp, skip)
     _parity(inp, skip)
+
+
+def test_lstm_wide_input_does_not_see_its_batch():
+    """With the input product ahead of the wavefronts too, a sentence's outputs are the same bits in every batch: 130
+    sentences and 16 go to different tiles of that product and different blocks."""
+    import test_gpu_lstm as tl
+    from synth_inputs import make_lstm_inputs
+    inp = make_lstm_inputs(10, 130, 1032, 512, 2, seed=3, dtype="bf16")
+    f, _, _ = tl.run_gpu(inp)
+    part = make_lstm_inputs(10, 130, 1032, 512, 2, seed=3, dtype="bf16")
+    for k in ("x", "dy"):
+        setattr(part, k, np.ascontiguousarray(getattr(part, k)[:, 32:48]))
+    for k in ("h0", "c0", "dhT", "dcT"):
+        setattr(part, k, np.ascontiguousarray(getattr(part, k)[:, 32:48]))
+    part.lengths, part.B = part.lengths[32:48].copy(), 16
+    g, _, _ = tl.run_gpu(part)
+    assert np.array_equal(g["y"], f["y"][:, 32:48])
+    assert np.array_equal(g["hT"], f["hT"][:, 32:48]) and np.array_equal(g["cT"], f["cT"][:, 32:48])
