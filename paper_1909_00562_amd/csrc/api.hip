@@ -139,8 +139,9 @@ Layout make_layout(const as_shape* s) {
   // split for counts whole tiles per segment: planned over 3 * H, sizes like H = 584 got a split with no tiles left.
   L.p_hc = gemm_plan(N, H, bf ? 3 * (int)up(H, 64) : 2 * H, 1, bf, true, true);
   L.p_logits = gemm_plan(N, V, H, 1, bf, false);
-  L.p_dwout = gemm_plan(V, H, N, 1, bf, true);
-  L.p_dhc = gemm_plan(N, H, V, 1, bf, true);
+  const bool counted = s->skip_pad_rows != 0;
+  L.p_dwout = gemm_plan(V, H, N, 1, bf, true, false, counted);
+  L.p_dhc = gemm_plan(N, H, V, 1, bf, true, false, counted);
   // Few, long work items (N/256 x H/256 tiles, reduction over V): once the padding rows are gone the item count
   // no longer fills whole rounds of the grid, so the kernel splits the reduction to fit the count it reads.
   L.dhc_dyn = s->skip_pad_rows != 0 && bf && L.p_dhc.tile == kTile256;

@@ -107,7 +107,9 @@ struct GemmPlan {
   int splits;
 };
 // multi_segment: the reduction runs over several operand segments; the 256x256 kernels cannot split those
-GemmPlan gemm_plan(int M, int N, int K, int batch, bool bf16, bool allow_split, bool multi_segment = false);
+// counted: M or K is the bound of a size counted on the device (M_dev, K_dev), usually well above it
+GemmPlan gemm_plan(int M, int N, int K, int batch, bool bf16, bool allow_split, bool multi_segment = false,
+                   bool counted = false);
 inline size_t gemm_partial_bytes(int M, int N, int batch, int splits) {
   return splits > 1 ? (size_t)splits * batch * M * N * sizeof(float) : 0;
 }

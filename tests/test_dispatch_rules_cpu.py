@@ -33,10 +33,10 @@ def test_input_product_of_layer_0_where_it_was_faster(T, I, H, L, apart):
     assert not _rule("_ZN3asx14ls_input_apartIfEEbiiii", ctypes.c_bool, *[I32] * 4)(T, I, H, L)
 
 
-def _plan(M, N, K, batch, bf16, allow_split=True, multi_segment=False):
+def _plan(M, N, K, batch, bf16, allow_split=True, multi_segment=False, counted=False):
     """(tile, splits) of a product: tile 0 = 128 x 128, 1 = 256 x 256, 2 = 64 x 64 (bf16)."""
-    f = _rule("_ZN3asx9gemm_planEiiiibbb", ctypes.c_uint64, *[I32] * 4, *[ctypes.c_bool] * 3)
-    v = f(M, N, K, batch, bf16, allow_split, multi_segment)
+    f = _rule("_ZN3asx9gemm_planEiiiibbbb", ctypes.c_uint64, *[I32] * 4, *[ctypes.c_bool] * 4)
+    v = f(M, N, K, batch, bf16, allow_split, multi_segment, counted)
     return v & 0xffffffff, v >> 32
 
 
@@ -74,6 +74,13 @@ def test_bf16_tile_that_was_the_faster_one(M, N, K, batch, plan):
     """Weight-gradient products (and dlogits W_out) whose time was taken with every tile and split: 256 x 256 tiles above,
     the smaller ones below."""
     assert _plan(M, N, K, batch, bf16=True) == plan
+
+
+@pytest.mark.parametrize("M, N, K, plan", [(800, 1024, 32000, (0, 9)), (8192, 512, 8000, (0, 1)), (8000, 512, 8192, (0, 2)),
+                                           (128000, 2048, 16384, (1, 1)), (6400, 1024, 32000, (1, 5))])
+def test_bf16_tile_where_the_device_counts_the_size(M, N, K, plan):
+    """Row compaction: the sizes are bounds, about half of which is there; smaller tiles win earlier."""
+    assert _plan(M, N, K, 1, bf16=True, counted=True) == plan
 
 
 @pytest.mark.parametrize("T, S, B, H, V, dtype, skip", [
