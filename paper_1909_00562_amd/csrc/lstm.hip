@@ -51,10 +51,11 @@ bool ls_shape_ok(const ls_shape* s) {
 }
 
 // Weights of the backward pass as tiles.  With one step (T = 1) a weight is used by one wavefront alone, so that places for
-// a few wavefronts' (16 MiB of them, one wavefront's two at least) do for all layers: they are filled again in between.
-// (128 sentences, four layers of 1024 units: 46 MiB of workspace where tiles of all weights make it 86.)
+// a few wavefronts' (32 MiB of them, one wavefront's two at least) do for all layers: they are filled again in between.
+// (Four layers of 1024 units, 128 sentences: 62 MiB of workspace where tiles of all weights make it 86.  Places for one
+// wavefront alone, 46 MiB: forward and backward with one sentence 242 us, 224 with two.)
 int ls_one_step_group(size_t weight) {
-  const size_t g = ((size_t)16 << 20) / (2 * weight);
+  const size_t g = ((size_t)32 << 20) / (2 * weight);
   return g < 1 ? 1 : (g < kLsMaxLayers ? (int)g : kLsMaxLayers);
 }
 

@@ -76,7 +76,7 @@ def test_one_step_attention_backward(shape):
                                    # rounded at 2^-24 of its terms, 6e-8: elements of y below 6e-4, about one in a
                                    # thousand, need the row-scale floor; a tensor of 1275 admits one, this one four.)
                                    (1, 65, 16, 72, 2),
-                                   (1, 9, 24, 40, 5)])          # one step: tiles of two weights at a time
+                                   (1, 9, 24, 1032, 4)])        # one step, tiles of one wavefront's weights at a time
 def test_lstm_wavefronts_at_block_edges(shape, dtype):
     import test_gpu_lstm as tl
     from synth_inputs import make_lstm_inputs
