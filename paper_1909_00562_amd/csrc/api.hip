@@ -101,6 +101,7 @@ struct Layout {
   size_t q_lo, alphaE_lo, dC_lo, dscoreE_lo, dact, dz_lo, ctx_lo;
   // row compaction (skip_pad_rows): position <-> compacted row, the count, and the gathered / to-be-scattered blocks
   bool compact;
+  bool dz_scatter;   // compacted rows of dz go back to their places in a pass of their own (a split product's combine does it)
   bool dhc_dyn;   // the product with W_out in the backward pass picks its reduction split on the device
   size_t row_pos, rows, n_act, hc_c, dact_c, dz_c, dz_lo_c;
   int rb, nrb;
@@ -146,6 +147,7 @@ Layout make_layout(const as_shape* s) {
   // no longer fills whole rounds of the grid, so the kernel splits the reduction to fit the count it reads.
   L.dhc_dyn = s->skip_pad_rows != 0 && bf && L.p_dhc.tile == kTile256;
   if (L.dhc_dyn && L.p_dhc.splits < 8) L.p_dhc.splits = 8;
+  L.dz_scatter = s->skip_pad_rows != 0 && L.p_dhc.splits == 1;
   L.p_dwc = gemm_plan(H, H, N, 2, bf, true);          // both halves of dW_c in one launch
   L.p_dch = gemm_plan(N, H, H, 1, bf, false);
   L.p_dalpha = gemm_plan(T, S, H, B, bf, false);
@@ -203,7 +205,7 @@ Layout make_layout(const as_shape* s) {
   L.dC_lo = take(NH * L.e);
   L.dscoreE_lo = take(BTSl * L.e);
   L.dz_lo = take(NH * L.e);
-  if (L.compact) {
+  if (L.dz_scatter) {
     L.dz_c = take(NH * L.e);
     L.dz_lo_c = take(NH * L.e);
   }
@@ -526,14 +528,15 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
     g.a_kc = true; g.b_kc = false;
     g.M = N; g.N = H;
     g.gate = reinterpret_cast<const float*>(w + (L.compact ? L.dact_c : L.dact)); g.ldg = H;
-    g.C = w + (L.compact ? L.dz_c : L.dz); g.ldc = H; g.c_bf16 = bf;
-    g.C_lo = w + (L.compact ? L.dz_lo_c : L.dz_lo);
+    g.C = w + (L.dz_scatter ? L.dz_c : L.dz); g.ldc = H; g.c_bf16 = bf;
+    g.C_lo = w + (L.dz_scatter ? L.dz_lo_c : L.dz_lo);
+    if (L.compact && !L.dz_scatter) g.row_pos = reinterpret_cast<const int32_t*>(w + L.row_pos);
     g.M_dev = n_act;
     g.dyn_split = L.dhc_dyn;
     g.splits = L.p_dhc.splits; g.partial = partial;
     AS_TRY(AS_STAGE_GEMM_DHC, launch_gemm(g, bf, L.p_dhc.tile, st));
   }
-  if (L.compact)   // dz back to its time-major rows, zeros at the padding rows: the rest of the pass is per sentence
+  if (L.dz_scatter)   // dz back to its time-major rows, zeros at the padding rows: the rest of the pass is per sentence
     AS_TRY(AS_STAGE_COMPACT, launch_scatter_rows(reinterpret_cast<const int32_t*>(w + L.row_pos), N, w + L.dz_c,
                                                  w + L.dz, w + L.dz_lo_c, w + L.dz_lo, (int64_t)H * L.e, st));
   {  // dW_c = dz^T [ctx ; h_dec]: the two halves as one launch of two products that share dz; the second operand

@@ -74,6 +74,9 @@ struct GemmArgs {
   // split of the reduction from the row count it reads (pp_dyn_splits below), so that the shrunken work list
   // still fills whole rounds of the grid, and the combine step, which always runs, picks the same.
   bool dyn_split = false;
+  // Split products only, applied by the combine step: row n < M of C (and C_lo) is the product's row row_pos[n], zeros where
+  // that is negative (row compaction undone on the way out).  The gate's rows are the product's.
+  const int32_t* row_pos = nullptr;
 };
 
 // Blocks of a persistent launch (one per compute unit, a multiple of the 8 XCDs).

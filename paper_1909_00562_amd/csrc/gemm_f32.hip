@@ -1,6 +1,8 @@
 // fp32 matrix products for the AS_F32 path (fp32 operands, products summed in
 // fp64 so that each output is rounded once; fp64 matrix cores, LDS tiled), the
 // split-K combine kernel shared with the bf16 path, and the tile planner.
+#include <type_traits>
+
 #include "common.h"
 #include "gemm.h"
 
@@ -368,74 +370,192 @@ hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t st) {
 }
 
 // ---- split-K combine: C = epilogue(sum_s partial[b*splits+s]) in fixed order --
-template <typename TIn, bool OUT_BF16>
-__global__ __launch_bounds__(256) void splitk_combine_kernel(const float* __restrict__ partial, int splits,
-                                                            int M, int N, void* C, void* C_lo, int64_t ldc,
-                                                            int64_t sC, const TIn* bias, const float* gate,
-                                                            int64_t ldg, int act_tanh, int accumulate,
-                                                            float* C_dact, uint32_t drop_thr, float drop_scale,
-                                                            uint64_t drop_seed, const int32_t* M_dev,
-                                                            int dyn_ktiles, int dyn_blocks) {
-  const int64_t mn = (int64_t)M * N;      // extent of one partial
-  const int Mv = dev_bound_f(M_dev, M);
-  const int64_t mn_valid = (int64_t)Mv * N;   // rows the product wrote
-  if (dyn_ktiles > 0)   // the product chose its split from the row count: the same choice here
-    splits = pp_dyn_splits(((Mv + 255) / 256) * ((N + 255) / 256), dyn_ktiles, splits, dyn_blocks);
+struct CombineDev {
+  const float* partial;
+  int splits, M, N;
+  void *C, *C_lo;
+  float* C_dact;
+  int64_t ldc, sC;
+  const void* bias;
+  const float* gate;
+  int64_t ldg;
+  int act_tanh, accumulate;
+  uint32_t drop_thr;
+  float drop_scale;
+  uint64_t drop_seed;
+  const int32_t* M_dev;
+  const int32_t* row_pos;   // row n of C is row row_pos[n] of the product, zeros where that is negative
+  int dyn_ktiles, dyn_blocks;
+};
+
+// Bound by memory: splits x 4 bytes read per element, 4 to 12 more for the gate and the outputs.  V columns per thread, the
+// gate and up to four splits requested together, 16-byte accesses throughout.  12145 of 16384 rows x 2048, two splits, gate
+// and remainder, back to their rows: 148 us (2.9 TB/s; an element at a time, and the rows in a pass of their own, 207 + 39);
+// 4287 of 6400 x 1024, three splits: 26.6 us (56 + 9).  One split after the other instead of together: 238 and 46.
+template <typename TIn, bool OUT_BF16, int V>
+__global__ __launch_bounds__(256) void splitk_combine_kernel(CombineDev p) {
+  constexpr int Q = V > 4 ? 4 : V;            // columns of a vector access
+  typedef float vec_t __attribute__((ext_vector_type(Q)));
+  const int64_t mn = (int64_t)p.M * p.N;      // extent of one partial
+  const int Mv = dev_bound_f(p.M_dev, p.M);
+  int splits = p.splits;
+  if (p.dyn_ktiles > 0)   // the product chose its split from the row count: the same choice here
+    splits = pp_dyn_splits(((Mv + 255) / 256) * ((p.N + 255) / 256), p.dyn_ktiles, splits, p.dyn_blocks);
   const int batch = blockIdx.y;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < mn_valid; i += (int64_t)gridDim.x * 256) {
-    const int row = (int)(i / N), col = (int)(i - (int64_t)row * N);
-    const float* P = partial + (int64_t)batch * splits * mn + i;
-    float v = 0.f;
-    for (int s = 0; s < splits; ++s) v += P[(int64_t)s * mn];
-    if (bias) v += ld_elem<TIn>(bias, col);
-    if (act_tanh) v = tanhf(v);
-    float dact = 1.f - v * v;
-    if (drop_thr) {
-      const float sc = dropout_mult((uint64_t)i, drop_seed, drop_thr, drop_scale);   // i = row * N + col
-      v *= sc;
-      dact *= sc;
+  const int64_t total = (int64_t)(p.row_pos ? p.M : Mv) * (p.N / V);   // groups of V columns
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
+    int row;
+    if constexpr (V > 1) row = (int)((uint32_t)i / (uint32_t)(p.N / V));   // (the launcher has checked the range)
+    else row = (int)(i / p.N);
+    const int col = (int)(i - (int64_t)row * (p.N / V)) * V;
+    const int src = p.row_pos ? p.row_pos[row] : row;   // rows >= Mv were not written
+    const int64_t ci = (int64_t)batch * p.sC + (int64_t)row * p.ldc + col;
+    auto get = [&](const float* from, float (&x)[V]) {
+#pragma unroll
+      for (int k = 0; k < V / Q; ++k) {
+        const vec_t o = *reinterpret_cast<const vec_t*>(from + k * Q);
+#pragma unroll
+        for (int e = 0; e < Q; ++e) x[k * Q + e] = o[e];
+      }
+    };
+    float v[V], dact[V], gate[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) v[e] = dact[e] = 0.f;
+    if (src >= 0 && src < Mv) {
+      const float* P = p.partial + (int64_t)batch * splits * mn + (int64_t)src * p.N + col;
+      if (p.gate) get(p.gate + (int64_t)src * p.ldg + col, gate);   // ahead of the sums: in flight with them
+      auto add = [&](auto count, const float* from) {               // `count` splits, requested together
+        constexpr int S = decltype(count)::value;
+        float x[S][V];
+#pragma unroll
+        for (int u = 0; u < S; ++u) get(from + (int64_t)u * mn, x[u]);
+#pragma unroll
+        for (int u = 0; u < S; ++u)
+#pragma unroll
+          for (int e = 0; e < V; ++e) v[e] += x[u][e];
+      };
+      int s = 0;
+      for (; s + 4 <= splits; s += 4) add(std::integral_constant<int, 4>{}, P + (int64_t)s * mn);
+      if ((splits - s) == 3) add(std::integral_constant<int, 3>{}, P + (int64_t)s * mn);
+      else if ((splits - s) == 2) add(std::integral_constant<int, 2>{}, P + (int64_t)s * mn);
+      else if ((splits - s) == 1) add(std::integral_constant<int, 1>{}, P + (int64_t)s * mn);
+      if (p.bias)
+#pragma unroll
+        for (int e = 0; e < V; ++e) v[e] += ld_elem<TIn>(reinterpret_cast<const TIn*>(p.bias), col + e);
+      if (p.act_tanh)
+#pragma unroll
+        for (int e = 0; e < V; ++e) v[e] = tanhf(v[e]);
+#pragma unroll
+      for (int e = 0; e < V; ++e) dact[e] = 1.f - v[e] * v[e];
+      if (p.drop_thr) {
+        const uint64_t flat = (uint64_t)row * p.N + col;
+        if constexpr (V >= 4) {   // N % 4 == 0: whole blocks of the generator
+#pragma unroll
+          for (int k = 0; k < V / 4; ++k) {
+            uint32_t w[4];
+            dropout_words4((flat >> 2) + k, p.drop_seed, w);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const float sc = w[e] >= p.drop_thr ? p.drop_scale : 0.f;
+              v[4 * k + e] *= sc;
+              dact[4 * k + e] *= sc;
+            }
+          }
+        } else {
+          const float sc = dropout_mult(flat, p.drop_seed, p.drop_thr, p.drop_scale);
+          v[0] *= sc;
+          dact[0] *= sc;
+        }
+      }
+      if (p.gate)
+#pragma unroll
+        for (int e = 0; e < V; ++e) v[e] *= gate[e];
     }
-    if (gate) v *= gate[(int64_t)row * ldg + col];
-    const int64_t ci = (int64_t)batch * sC + (int64_t)row * ldc + col;
-    if (C_dact) C_dact[ci] = dact;
+    auto put = [&](void* dst, const float (&x)[V]) {   // floats
+#pragma unroll
+      for (int k = 0; k < V / Q; ++k) {
+        vec_t o;
+#pragma unroll
+        for (int e = 0; e < Q; ++e) o[e] = x[k * Q + e];
+        *reinterpret_cast<vec_t*>(reinterpret_cast<float*>(dst) + ci + k * Q) = o;
+      }
+    };
+    if (p.C_dact) put(p.C_dact, dact);
     if constexpr (OUT_BF16) {
-      const uint32_t hi = f32_to_bf16_bits(v);
-      reinterpret_cast<uint16_t*>(C)[ci] = (uint16_t)hi;
-      if (C_lo) reinterpret_cast<uint16_t*>(C_lo)[ci] = (uint16_t)f32_to_bf16_bits(v - bf16_bits_to_f32(hi));
+      uint32_t hi[V], lo[V];
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        hi[e] = f32_to_bf16_bits(v[e]);
+        lo[e] = f32_to_bf16_bits(v[e] - bf16_bits_to_f32(hi[e]));
+      }
+      auto put16 = [&](void* dst, const uint32_t (&x)[V]) {
+        uint16_t* d = reinterpret_cast<uint16_t*>(dst) + ci;
+        static_assert(V == 8, "16-byte stores");
+        *reinterpret_cast<uint4*>(d) = make_uint4(x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16), x[6] | (x[7] << 16));
+      };
+      put16(p.C, hi);
+      if (p.C_lo) put16(p.C_lo, lo);
     } else {
-      float* Cf = reinterpret_cast<float*>(C);
-      if (accumulate) v += Cf[ci];
-      Cf[ci] = v;
-      if (C_lo) reinterpret_cast<float*>(C_lo)[ci] = 0.f;   // partial sums were already rounded to fp32
+      if (p.accumulate) {
+        float x[V];
+        get(reinterpret_cast<const float*>(p.C) + ci, x);
+#pragma unroll
+        for (int e = 0; e < V; ++e) v[e] += x[e];
+      }
+      put(p.C, v);
+      if (p.C_lo) {   // partial sums were already rounded to fp32
+        const float z[V] = {};
+        put(p.C_lo, z);
+      }
     }
   }
 }
 
 hipError_t launch_splitk_combine(const GemmArgs& g, bool in_bf16, hipStream_t st) {
-  const int64_t mn = (int64_t)g.M * g.N;
+  if (g.row_pos && (g.batch != 1 || g.accumulate || g.drop_thr || g.C_dact)) return hipErrorInvalidValue;
+  CombineDev d;
+  d.partial = g.partial;
+  d.splits = g.splits;
+  d.M = g.M;
+  d.N = g.N;
+  d.C = g.C;
+  d.C_lo = g.C_lo;
+  d.C_dact = g.C_dact;
+  d.ldc = g.ldc;
+  d.sC = g.sC;
+  d.bias = g.bias;
+  d.gate = g.gate;
+  d.ldg = g.ldg;
+  d.act_tanh = g.act_tanh;
+  d.accumulate = g.accumulate;
+  d.drop_thr = g.drop_thr;
+  d.drop_scale = g.drop_scale;
+  d.drop_seed = g.drop_seed;
+  d.M_dev = g.M_dev;
+  d.row_pos = g.row_pos;
   // a split chosen by the persistent kernel (dyn_split): its reduction tiles and its grid, as that launch had them
-  const int dyn_ktiles = g.dyn_split ? (g.K[0] + 63) / 64 : 0;
-  const int dyn_blocks = g.dyn_split ? pp_grid_blocks(((g.M + 255) / 256) * ((g.N + 255) / 256) * g.splits) : 0;
-  int blocks = (int)((mn + 255) / 256);
-  if (blocks > 8192) blocks = 8192;
-  dim3 grid(blocks, g.batch);
+  d.dyn_ktiles = g.dyn_split ? (g.K[0] + 63) / 64 : 0;
+  d.dyn_blocks = g.dyn_split ? pp_grid_blocks(((g.M + 255) / 256) * ((g.N + 255) / 256) * g.splits) : 0;
+  // groups of V columns: every row of what is read and written starts on a whole vector, and the group's index fits 32 bits
+  // for the division.  bf16 widths are multiples of 8.
+  const int V = g.c_bf16 ? 8 : 4;
+  auto al = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
+  const bool vec = g.N % V == 0 && g.ldc % V == 0 && g.sC % V == 0 && al(g.partial) && al(g.C) && al(g.C_lo) && al(g.C_dact) &&
+                   (!g.gate || (g.ldg % 4 == 0 && al(g.gate))) && (int64_t)g.M * g.N / V < (int64_t)1 << 32;
+  int64_t blocks = ((int64_t)g.M * g.N / (vec ? V : 1) + 255) / 256;
+  if (blocks > 1 << 17) blocks = 1 << 17;
+  const dim3 grid((unsigned)blocks, g.batch);
+#define ASX_COMBINE(TIN, BF, W) hipLaunchKernelGGL((splitk_combine_kernel<TIN, BF, W>), grid, dim3(256), 0, st, d)
   if (in_bf16) {
-    const uint16_t* bias = reinterpret_cast<const uint16_t*>(g.bias);
-    const float* gate = g.gate;
-    if (g.c_bf16)
-      hipLaunchKernelGGL((splitk_combine_kernel<uint16_t, true>), grid, dim3(256), 0, st, g.partial, g.splits,
-                         g.M, g.N, g.C, g.C_lo, g.ldc, g.sC, bias, gate, g.ldg, g.act_tanh, g.accumulate, g.C_dact,
-                         g.drop_thr, g.drop_scale, g.drop_seed, g.M_dev, dyn_ktiles, dyn_blocks);
-    else
-      hipLaunchKernelGGL((splitk_combine_kernel<uint16_t, false>), grid, dim3(256), 0, st, g.partial, g.splits,
-                         g.M, g.N, g.C, g.C_lo, g.ldc, g.sC, bias, gate, g.ldg, g.act_tanh, g.accumulate, g.C_dact,
-                         g.drop_thr, g.drop_scale, g.drop_seed, g.M_dev, dyn_ktiles, dyn_blocks);
+    if (!vec) return hipErrorInvalidValue;
+    if (g.c_bf16) ASX_COMBINE(uint16_t, true, 8);
+    else ASX_COMBINE(uint16_t, false, 4);
+  } else if (vec) {
+    ASX_COMBINE(float, false, 4);
   } else {
-    hipLaunchKernelGGL((splitk_combine_kernel<float, false>), grid, dim3(256), 0, st, g.partial, g.splits, g.M,
-                       g.N, g.C, g.C_lo, g.ldc, g.sC, reinterpret_cast<const float*>(g.bias),
-                       g.gate, g.ldg, g.act_tanh, g.accumulate, g.C_dact, g.drop_thr, g.drop_scale, g.drop_seed,
-                       g.M_dev, dyn_ktiles, dyn_blocks);
+    ASX_COMBINE(float, false, 1);
   }
+#undef ASX_COMBINE
   return hipGetLastError();
 }
 
@@ -573,6 +693,7 @@ GemmPlan gemm_plan(int M, int N, int K, int batch, bool bf16, bool allow_split, 
 }
 
 hipError_t launch_gemm(const GemmArgs& g, bool in_bf16, GemmTile tile, hipStream_t st) {
+  if (g.row_pos && g.splits <= 1) return hipErrorInvalidValue;
   hipError_t e = in_bf16 ? launch_gemm_bf16(g, tile, st) : launch_gemm_f32(g, st);
   if (e != hipSuccess) return e;
   if (g.splits > 1) e = launch_splitk_combine(g, in_bf16, st);

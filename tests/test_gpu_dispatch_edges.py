@@ -46,6 +46,14 @@ def test_bf16_products_in_64x64_tiles(shape, skip):
     _parity(make_custom(T=T, S=S, B=B, H=H, V=V, seed=H, dtype="bf16", min_len=1, pad_prob=0.2), skip)
 
 
+@pytest.mark.parametrize("dtype, H", [("bf16", 72), ("bf16", 520), ("f32", 68), ("f32", 67)])   # f32, 67: no whole vectors
+@pytest.mark.parametrize("pad_prob", [0.0, 0.3, 0.97])         # all rows, some, a row or two of 35
+def test_split_dz_goes_straight_to_its_rows(dtype, H, pad_prob):
+    """Few rows, a long vocabulary: dlogits W_out is a split product, whose combine step also undoes the row compaction."""
+    inp = make_custom(T=5, S=6, B=7, H=H, V=4099, seed=H, dtype=dtype, min_len=1, pad_prob=pad_prob)
+    _parity(inp, skip=True)
+
+
 def test_lstm_f32_largest_block_in_vectors():
     """16 units x 32 sentences in fp32 with a hidden size of whole vectors (other sizes: test_lstm_wavefronts_at_block_edges)."""
     import test_gpu_lstm as tl
