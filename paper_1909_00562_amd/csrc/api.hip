@@ -446,7 +446,7 @@ static as_status fwd_impl(const as_shape* s, const void* h_dec, const void* h_en
   // sums of attn_step.hip would not give.  Whole calls are where Q and h_c have the same plan at both row counts, as small
   // models do; else h_c, split by the row count, adds in another order.)
   if (bf && attn_fwd_fused_supported(S, H)) {
-    // Eq. 2 (second half), 1 and 3 in one kernel per (sentence, 32 decoder steps): the scores stay on chip
+    // Eq. 2 (second half), 1 and 3 in one kernel per (sentence, 16 or 32 decoder steps): the scores stay on chip
     AS_TRY(AS_STAGE_ATTN_SCORE,
            launch_attn_fwd_fused(w + L.q, w + L.q_lo, he, src_len, B, T, S, H, reinterpret_cast<float*>(w + L.alpha32),
                                  w + L.alphaE, w + L.alphaE_lo, L.ldS, w + L.ctx, w + L.ctx_lo, attn_mask, st));
@@ -576,7 +576,7 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
                                     reinterpret_cast<const float*>(w + L.alpha32), w + L.q, w + L.q_lo, w + L.dQ,
                                     d_h_enc, st));
   } else if (bf && attn_fwd_fused_supported(S, H)) {
-    // dalpha, the softmax Jacobian and dQ in one kernel per (sentence, 32 decoder steps): dalpha stays on chip
+    // dalpha, the softmax Jacobian and dQ in one kernel per (sentence, 16 or 32 decoder steps): dalpha stays on chip
     AS_TRY(AS_STAGE_ATTN_BWD,
            launch_attn_bwd_fused(w + L.dC, w + L.dC_lo, he, src_len, B, T, S, H,
                                  reinterpret_cast<const float*>(w + L.alpha32), w + L.dscoreE, w + L.dscoreE_lo, L.ldS,

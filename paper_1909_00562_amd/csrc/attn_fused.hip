@@ -1,75 +1,47 @@
 // Fused attention for the batched path, bf16 storage (section 3.2, Eq. 1-3): one workgroup per
-// (sentence b, block of 32 decoder steps) computes
+// (sentence b, block of 16 or 32 decoder steps) computes
 //   score[t,s] = (q_hi + q_lo)[t,b,:] . h_enc[s,b,:]      (Eq. 2; q = h_dec W_a as value + rounding remainder)
 //   alpha[t,:] = softmax over s < src_len[b], exactly 0 elsewhere   (Eq. 1)
 //   ctx[t,b,:] = sum_s alpha[t,s] h_enc[s,b,:]             (Eq. 3; alpha enters as value + remainder)
-// without the scores ever leaving the compute unit.  It replaces three launches (batched score product,
-// softmax rows, batched context product) whose 128x128 tiles were mostly padding at T, S <= 80.
+// without the scores ever leaving the compute unit.
 // The same kernel with BWD = true is the first half of the attention backward pass, which has the same shape:
 //   dalpha[t,s] = (dC_hi + dC_lo)[t,b,:] . h_enc[s,b,:]
 //   dscore[t,:] = alpha[t,:] * (dalpha[t,:] - sum_s alpha[t,s] dalpha[t,s])      (softmax Jacobian)
 //   dQ[t,b,:]   = sum_s dscore[t,s] h_enc[s,b,:]
 // (dscore also leaves as bf16 value / remainder for the product that forms d_h_enc).
 //
-// The four waves of a workgroup run as private pipelines, with no workgroup barrier inside a phase: LDS operations
-// of one wave complete in order, so a wave can fill its own LDS slice and read fragments back without one.
-// Phase 1 (scores): the reduction over H is cut into tiles of 32; wave w takes tiles w, w+4, ...  For each it
-//   brings q_hi, q_lo (32 rows each) and the S encoder rows through its own LDS slice (rows of 32 reduction
-//   elements = 64 bytes, 16-byte chunks swizzled with (row >> 2) & 3), loaded into registers one tile ahead, and
-//   accumulates all score tiles (32 x 32 MFMA tiles, up to four) over its share of H.  The four partial sums
-//   meet in LDS in a fixed order.
-// Phase 2 (softmax): one wavefront per row, shuffle reductions; alpha goes to global memory (float, and the bf16
-//   value / remainder copies the backward pass reads) and to LDS as the row operand of phase 3.
-// Phase 3 (context): the reduction runs over source positions, so h_enc_b is the strided operand.  Wave w takes
-//   the 64-column chunks w, w+4, ... of H: [s][64 columns] as stored (rows padded to 160 bytes so that the four
-//   rows a transposing read touches fall on different banks), read with ds_read_b64_tr_b16.  Results are staged
-//   through the wave's LDS slice so that ctx / ctx_lo leave as 8-byte row vectors.
+// A few hundred KiB per workgroup: what counts is that they are requested early and by many waves, so eight waves share a
+// workgroup, none of them waits for another inside a phase, and phase 3's first operand is requested before phase 1.
+// Phase 1 (scores): matrix fragments straight from global memory into registers.  A wave takes pairs of 32-wide reduction
+//   steps (whole 128-byte lines of its rows), a pair ahead on its way; pairs w, w + 8, ... go to wave w, and the eight
+//   partial sums are added in wave order whatever T and B are.
+// Phase 2 (softmax): one wavefront per row, shuffle reductions, all rows of a wave at once; alpha goes to global memory
+//   (float, and the bf16 value / remainder copies the backward pass reads) and to LDS as the row operand of phase 3.
+// Phase 3 (context): the reduction runs over source positions, so h_enc_b is the strided operand: a wave brings its chunks
+//   of 64 columns (32 where S > 64) as stored into two LDS slots of its own, directly, and reads them transposing.
+// One workgroup per 32 decoder steps where that makes 192 of them, else per 16, so that more compute units have one
+// (us, 32 / 16 steps: 64 / 128 workgroups of S 30 H 512 10.2 / 7.5, 122 / 183 of S 43 H 1000 16.3 / 12.8, 256 / 512 of S 50
+// H 1024 20.8 / 24.4, 512 / 1024 of S 64 H 2048 104 / 129); S > 64: 16, by the LDS.  Four waves, two workgroups per compute
+// unit: 8.4, 13.8, 23.3, 107.  The kernel this replaced, four waves that brought both operands through LDS a tile ahead in
+// registers: 20.6, 32.8, 36.4, 104 forward and 17.3, -, 33.5, 108 backward (now 6.2, -, 18.1, 91); T 80 S 80 B 128 H 1024
+// 69 and 66, now 43 and 43; T 1 S 50 B 128 H 1024 29, now 9.5.
 #include "common.h"
 #include "kernels.h"
 #include "lds_limit.h"
+#include "gemm_dev.h"
 
 namespace asx {
 
 namespace {
 
-constexpr int AF_ROWS = 32;      // decoder steps per workgroup
-constexpr int AF_THREADS = 256;  // 4 waves
-
 typedef uint32_t af_u32x4_t __attribute__((ext_vector_type(4)));
-typedef uint32_t af_u32x2_t __attribute__((ext_vector_type(2)));
-typedef short af_s16x4_t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) af_s16x4_t af_lds_s16x4_t;
-typedef __attribute__((address_space(3))) void af_lds_void_t;
+typedef __attribute__((address_space(1))) void af_glb_void_t;
+
+constexpr int AF_NW = 8;   // waves of a workgroup
 
 // alpha operand blocks: rows of 64 elements (128 bytes), chunk c of row r at chunk c ^ (r & 7) ^ ((r >> 3) & 1)
 __device__ __forceinline__ uint32_t kc_off(int row, int chunk) {
   return (uint32_t)(row * 128 + ((chunk ^ (row & 7) ^ ((row >> 3) & 1)) << 4));
-}
-__device__ __forceinline__ bf16x8_t kc_frag(const unsigned char* tile, int row, int chunk) {
-  return *reinterpret_cast<const bf16x8_t*>(tile + kc_off(row, chunk));
-}
-// phase-1 slices: rows of 32 elements (64 bytes), chunk c (0..3) of row r at chunk c ^ ((r >> 2) & 3)
-__device__ __forceinline__ uint32_t k32_off(int row, int chunk) {
-  return (uint32_t)(row * 64 + ((chunk ^ ((row >> 2) & 3)) << 4));
-}
-__device__ __forceinline__ bf16x8_t k32_frag(const unsigned char* tile, int row, int chunk) {
-  return *reinterpret_cast<const bf16x8_t*>(tile + k32_off(row, chunk));
-}
-// phase-3 slices [k][64 columns], k-rows AF_RS bytes apart.  Transposing read: a 16-lane group presents four k-rows x
-// 16 columns, each lane receives four consecutive k of its own column (two reads, 4 k-rows apart, give 8).
-constexpr int AF_RS = 160;
-__device__ __forceinline__ uint32_t st_frag_base(int col0, int lane) {
-  const int col = col0 + ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
-  const int k0 = (lane >> 5) * 8 + ((lane & 15) >> 2);
-  return (uint32_t)(k0 * AF_RS + col * 2);
-}
-__device__ __forceinline__ bf16x8_t st_frag(const unsigned char* tile, uint32_t base, int kk) {
-  union { af_s16x4_t h[2]; bf16x8_t v; } u;
-#pragma unroll
-  for (int q = 0; q < 2; ++q)
-    u.h[q] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (af_lds_s16x4_t*)(af_lds_void_t*)(tile + base + kk * 16 * AF_RS + q * 4 * AF_RS));
-  return u.v;
 }
 
 struct AttnFwdArgs {
@@ -81,229 +53,284 @@ struct AttnFwdArgs {
   uint8_t* attn_mask;
   int T, S, B, H;
   int64_t ldS;
-  int SP;         // S rounded up to 32: score columns computed
-  int KS;         // S rounded up to 16: reduction length of the context product
-  int p1_bytes, p3_bytes;   // bytes of one wave's LDS slice in phase 1 / phase 3 (both live in region 0)
-  int off_x, off_a;         // LDS byte offsets of the score / staging region and of the alpha operand blocks
 };
 
-template <bool BWD>
-__global__ __launch_bounds__(AF_THREADS) void attn_fwd_fused_kernel(AttnFwdArgs p) {
+// LDS of a workgroup of 16 RT decoder steps x 16 ST source positions: a slot of NT x 16 columns of encoder states per wave;
+// the score partial sums, later a second slot per wave; the row results
+template <int RT, int ST> struct AttnLds {
+  static constexpr int kRows = 16 * RT, kSld = 16 * ST + 4;
+  static constexpr int kNT = ST <= 4 ? 4 : 2, kRB = kNT * 32;           // slot rows: bytes
+  static constexpr int kSlot = 16 * ST * kRB, kPart = kRows * kSld * 4;  // bytes per wave
+  static constexpr int kX = AF_NW * kSlot, kA = kX + AF_NW * (kPart > kSlot ? kPart : kSlot);
+  static constexpr int kBlk = kRows * 128, kKB = (16 * ST + 63) / 64;
+  static constexpr int kBytes = kA + 2 * kKB * kBlk;
+  static_assert(kBytes <= 160 * 1024, "LDS of a compute unit");
+};
+
+// 16-byte piece c of slot row k is kept at c ^ slot_swizzle(k): the four rows of a transposing read lie in different banks
+template <int NT> __device__ __forceinline__ int slot_swizzle(int k) { return NT == 4 ? (k & 2) << 1 : 0; }
+
+template <bool BWD, int RT, int ST>
+__global__ __launch_bounds__(64 * AF_NW) void attn_fused_kernel(AttnFwdArgs p) {
+  typedef AttnLds<RT, ST> Lds;
+  constexpr int NW = AF_NW, ROWS = Lds::kRows, SLD = Lds::kSld, KB = Lds::kKB, NT = Lds::kNT, RB = Lds::kRB;
   extern __shared__ __align__(1024) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int b = blockIdx.x, t0 = blockIdx.y * AF_ROWS;
-  const int T = p.T, S = p.S, B = p.B, H = p.H, SP = p.SP;
-  const int64_t BH = (int64_t)B * H;
+  const int c16 = lane & 15, q4 = lane >> 4;
+  const int b = blockIdx.x, t0 = blockIdx.y * ROWS;
+  const int T = p.T, S = p.S, H = p.H;
+  const int64_t BH = (int64_t)p.B * H;
   int L = p.src_len[b];
   L = L < 0 ? 0 : (L > S ? S : L);
-  const int SS = SP / 32;                           // score tiles of 32 columns (<= 4)
+  const int last = L > 0 ? L - 1 : 0;   // source rows past the sentence are read from its last word: their weights are 0
+  const uint16_t* he = p.h_enc + (int64_t)b * H;
 
-  // ---------------- phase 1: scores, each wave over its share of H -------------------------------
-  {
-    unsigned char* slice = smem + wave * p.p1_bytes;
-    const int nl = (64 + SP) / 16;                  // wave-wide 16-byte loads per tile (16 rows of 64 bytes each)
-    const int nkt = (H + 31) / 32;
-    af_u32x4_t regs[12];                            // nl <= 12 (S <= 128)
-    auto load_tile = [&](int kt) {
+  // ---------------- phase 3's first chunk of encoder states, requested first --------------------------------------
+  const int nk3 = (L + 31) >> 5, nch = (H + 16 * NT - 1) / (16 * NT);   // reduction steps of 32 source positions; chunks
+  auto load_chunk = [&](int c, unsigned char* slot) {
+    constexpr int CPR = RB / 16, RPL = 64 / CPR;   // 16-byte pieces of a row, rows per load
+    const int kr = lane / CPR, col = c * 16 * NT + ((lane % CPR) ^ slot_swizzle<NT>(kr)) * 8;
+    const uint16_t* src = he + (col < H ? col : 0);
+    for (int i = 0; i < 32 / RPL * nk3; ++i) {
+      const int k = i * RPL + kr;
+      __builtin_amdgcn_global_load_lds((af_glb_void_t*)(src + (k < L ? k : last) * BH), (lds_void_t*)(slot + i * 1024), 16, 0, 0);
+    }
+  };
+  if (wave < nch) load_chunk(wave, smem + wave * Lds::kSlot);
+  constexpr int RPW = ROWS / NW;        // rows of phase 2 per wave
+  float al[RPW][KB];                    // BWD: their weights
+  if constexpr (BWD) {
 #pragma unroll
-      for (int i = 0; i < 12; ++i) {
-        regs[i] = af_u32x4_t{0, 0, 0, 0};
-        if (i < nl) {
-          const int row = i * 16 + (lane >> 2), k = kt * 32 + (lane & 3) * 8;
-          const uint16_t* src = nullptr;
-          if (row < 32) {
-            if (t0 + row < T) src = p.q_hi + (int64_t)(t0 + row) * BH + (int64_t)b * H;
-          } else if (row < 64) {
-            if (t0 + row - 32 < T) src = p.q_lo + (int64_t)(t0 + row - 32) * BH + (int64_t)b * H;
-          } else if (row - 64 < S) {
-            src = p.h_enc + (int64_t)(row - 64) * BH + (int64_t)b * H;
-          }
-          if (src && k < H) regs[i] = *reinterpret_cast<const af_u32x4_t*>(src + k);
-        }
+    for (int r = 0; r < RPW; ++r)
+#pragma unroll
+      for (int h = 0; h < KB; ++h) {
+        const int t = t0 + wave * RPW + r, s = lane + 64 * h;
+        al[r][h] = p.alpha32[((int64_t)b * T + (t < T ? t : T - 1)) * S + (s < S ? s : 0)];
       }
-    };
-    f32x16_t sacc[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sacc[j][r] = 0.f;
-    if (wave < nkt) load_tile(wave);
-    for (int kt = wave; kt < nkt; kt += 4) {
-#pragma unroll
-      for (int i = 0; i < 12; ++i)
-        if (i < nl)
-          *reinterpret_cast<af_u32x4_t*>(slice + k32_off(i * 16 + (lane >> 2), lane & 3)) = regs[i];
-      if (kt + 4 < nkt) load_tile(kt + 4);          // in flight while this tile is multiplied
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
-        const int chunk = kk * 2 + (lane >> 5);
-        const bf16x8_t a_hi = k32_frag(slice, lane & 31, chunk);
-        const bf16x8_t a_lo = k32_frag(slice, 32 + (lane & 31), chunk);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (j < SS) {
-            const bf16x8_t bf = k32_frag(slice, 64 + j * 32 + (lane & 31), chunk);
-            sacc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_hi, bf, sacc[j], 0, 0, 0);
-            sacc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_lo, bf, sacc[j], 0, 0, 0);
-          }
-      }
-    }
-    // the four partial sums meet in two LDS buffers: waves 0, 1 store, then waves 2, 3 add (fixed order)
-    const int sld = SP + 8;                         // row stride: the two half-waves of a store hit different banks
-    float* buf = reinterpret_cast<float*>(smem + p.off_x) + (wave & 1) * (AF_ROWS * sld);
-    if (wave < 2) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (j < SS)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            buf[(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * sld + j * 32 + (lane & 31)] = sacc[j][r];
-    }
-    __syncthreads();
-    if (wave >= 2) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (j < SS)
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            buf[(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * sld + j * 32 + (lane & 31)] += sacc[j][r];
-    }
-    __syncthreads();
   }
 
-  // ---------------- phase 2: masked softmax rows --------------------------------------------------
-  const int KB = (p.KS + 63) / 64;                                  // 64-wide reduction blocks of the alpha operand
-  unsigned char* a_hi_blk = smem + p.off_a;                         // [KB][32 rows][64] value
-  unsigned char* a_lo_blk = a_hi_blk + KB * 4096;                   // same, rounding remainder
+  // ---------------- phase 1: scores -------------------------------------------------------------------------------
   {
-    const int sld = SP + 8;
-    const float* sc0 = reinterpret_cast<const float*>(smem + p.off_x);
-    const float* sc1 = sc0 + AF_ROWS * sld;
-    for (int rr = 0; rr < 8; ++rr) {
-      const int row = wave * 8 + rr, t = t0 + row;
-      const int s0 = lane, s1 = lane + 64;
-      float a0, a1;
-      if constexpr (!BWD) {
-        const float x0 = s0 < L ? sc0[row * sld + s0] + sc1[row * sld + s0] : -INFINITY;
-        const float x1 = s1 < L ? sc0[row * sld + s1] + sc1[row * sld + s1] : -INFINITY;
-        const float m = wave_max(fmaxf(x0, x1));
-        const float e0 = s0 < L ? expf(x0 - m) : 0.f, e1 = s1 < L ? expf(x1 - m) : 0.f;
-        const float sum = wave_sum(e0 + e1);
-        const float inv = L > 0 ? 1.f / sum : 0.f;
-        a0 = s0 < L ? e0 * inv : 0.f;             // masked positions: exactly 0
-        a1 = s1 < L ? e1 * inv : 0.f;
-      } else {
-        // softmax Jacobian; alpha is 0 at masked positions, so dscore is exactly 0 there
-        const bool v0 = s0 < S && t < T, v1 = s1 < S && t < T;
-        const float al0 = v0 ? p.alpha32[((int64_t)b * T + t) * S + s0] : 0.f;
-        const float al1 = v1 ? p.alpha32[((int64_t)b * T + t) * S + s1] : 0.f;
-        const float x0 = v0 ? sc0[row * sld + s0] + sc1[row * sld + s0] : 0.f;
-        const float x1 = v1 ? sc0[row * sld + s1] + sc1[row * sld + s1] : 0.f;
-        const float r = wave_sum(al0 * x0 + al1 * x1);
-        a0 = al0 * (x0 - r);
-        a1 = al1 * (x1 - r);
+    const uint16_t *qh[RT], *ql[RT], *hr[ST];
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+      const int t = t0 + 16 * r + c16;
+      const int64_t off = (int64_t)(t < T ? t : T - 1) * BH + (int64_t)b * H;
+      qh[r] = p.q_hi + off;
+      ql[r] = p.q_lo + off;
+    }
+#pragma unroll
+    for (int j = 0; j < ST; ++j) {
+      const int s = 16 * j + c16;
+      hr[j] = he + (s < L ? s : last) * BH;
+    }
+    f32x4_t acc[RT][ST];
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int j = 0; j < ST; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[r][j][e] = 0.f;
+    // Steps 2 i and 2 i + 1 of a pair go through register slots 0 and 1: a pair ahead is on its way.
+    af_u32x4_t fq[2][RT], fl[2][RT], fh[2][ST];
+    auto load = [&](int slot, int i) {  // half `slot` of the wave's i-th pair
+      const int k = (2 * (wave + i * NW) + slot) * 32 + q4 * 8, kk = k < H ? k : 0;
+#pragma unroll
+      for (int j = 0; j < ST; ++j) fh[slot][j] = *reinterpret_cast<const af_u32x4_t*>(hr[j] + kk);
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        fq[slot][r] = *reinterpret_cast<const af_u32x4_t*>(qh[r] + kk);
+        fl[slot][r] = *reinterpret_cast<const af_u32x4_t*>(ql[r] + kk);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto mul = [&](int slot, int i) {
+      const int k0 = (2 * (wave + i * NW) + slot) * 32;
+      if (k0 + 32 > H) {                // reduction indices past the end were read from the row's start
+        const bool in = k0 + q4 * 8 < H;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+#pragma unroll
+          for (int j = 0; j < ST; ++j) fh[slot][j][e] = in ? fh[slot][j][e] : 0u;
+#pragma unroll
+          for (int r = 0; r < RT; ++r) {
+            fq[slot][r][e] = in ? fq[slot][r][e] : 0u;
+            fl[slot][r][e] = in ? fl[slot][r][e] : 0u;
+          }
+        }
       }
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int s = h ? s1 : s0;
-        const float a = h ? a1 : a0;
-        const uint32_t hb = f32_to_bf16_bits(a);
-        const uint32_t lb = f32_to_bf16_bits(a - bf16_bits_to_f32(hb));
-        if (s < KB * 64) {                          // operand of phase 3 (zeros beyond the valid positions)
-          const uint32_t o = (uint32_t)((s >> 6) * 4096) + kc_off(row, (s & 63) >> 3) + (uint32_t)(s & 7) * 2;
-          *reinterpret_cast<uint16_t*>(a_hi_blk + o) = (uint16_t)hb;
-          *reinterpret_cast<uint16_t*>(a_lo_blk + o) = (uint16_t)lb;
+      for (int j = 0; j < ST; ++j) {
+        const bf16x8_t a = __builtin_bit_cast(bf16x8_t, fh[slot][j]);
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+          acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8_t, fq[slot][r]), acc[r][j], 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+          acc[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8_t, fl[slot][r]), acc[r][j], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    const int npair = (H + 63) / 64, n = npair > wave ? (npair - wave + NW - 1) / NW : 0;
+    if (n > 0) {
+      load(0, 0);
+      load(1, 0);
+      for (int i = 0; i + 1 < n; ++i) {
+        mul(0, i);
+        load(0, i + 1);
+        mul(1, i);
+        load(1, i + 1);
+      }
+      mul(0, n - 1);
+      mul(1, n - 1);
+    }
+    float* part = reinterpret_cast<float*>(smem + Lds::kX) + wave * (ROWS * SLD);
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int j = 0; j < ST; ++j)
+        *reinterpret_cast<f32x4_t*>(part + (16 * r + c16) * SLD + 16 * j + 4 * q4) = acc[r][j];
+  }
+  __syncthreads();
+
+  // ---------------- phase 2: masked softmax rows, or the softmax Jacobian ------------------------------------------
+  unsigned char* a_hi = smem + Lds::kA;             // [KB][rows][64] value
+  unsigned char* a_lo = a_hi + KB * Lds::kBlk;      // same, rounding remainder
+  {
+    const float* part = reinterpret_cast<const float*>(smem + Lds::kX);
+    float x[RPW][KB], a[RPW][KB];
+#pragma unroll
+    for (int r = 0; r < RPW; ++r)
+#pragma unroll
+      for (int h = 0; h < KB; ++h) {
+        const int s = lane + 64 * h;
+        const float* q = part + (wave * RPW + r) * SLD + (s < 16 * ST ? s : 0);
+        float v = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) v += q[w * (ROWS * SLD)];
+        x[r][h] = v;
+      }
+    if constexpr (!BWD) {
+#pragma unroll
+      for (int r = 0; r < RPW; ++r) {
+        float m = -INFINITY, sum = 0.f;
+#pragma unroll
+        for (int h = 0; h < KB; ++h) m = lane + 64 * h < L ? fmaxf(m, x[r][h]) : m;
+        m = wave_max(m);
+#pragma unroll
+        for (int h = 0; h < KB; ++h) {
+          a[r][h] = lane + 64 * h < L ? expf(x[r][h] - m) : 0.f;   // masked positions: exactly 0
+          sum += a[r][h];
         }
+        sum = wave_sum(sum);
+        const float inv = L > 0 ? 1.f / sum : 0.f;
+#pragma unroll
+        for (int h = 0; h < KB; ++h) a[r][h] *= inv;
+      }
+    } else {
+      // alpha is 0 at masked positions, so dscore is exactly 0 there
+#pragma unroll
+      for (int r = 0; r < RPW; ++r) {
+        float dot = 0.f;
+#pragma unroll
+        for (int h = 0; h < KB; ++h) {
+          const bool in = lane + 64 * h < L && t0 + wave * RPW + r < T;
+          al[r][h] = in ? al[r][h] : 0.f;
+          x[r][h] = in ? x[r][h] : 0.f;
+          dot += al[r][h] * x[r][h];
+        }
+        dot = wave_sum(dot);
+#pragma unroll
+        for (int h = 0; h < KB; ++h) a[r][h] = al[r][h] * (x[r][h] - dot);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < RPW; ++r)
+#pragma unroll
+      for (int h = 0; h < KB; ++h) {
+        const int row = wave * RPW + r, t = t0 + row, s = lane + 64 * h;
+        const uint32_t hb = f32_to_bf16_bits(a[r][h]);
+        const uint32_t lb = f32_to_bf16_bits(a[r][h] - bf16_bits_to_f32(hb));
+        const uint32_t o = (uint32_t)(h * Lds::kBlk) + kc_off(row, (s & 63) >> 3) + (uint32_t)(s & 7) * 2;
+        *reinterpret_cast<uint16_t*>(a_hi + o) = (uint16_t)hb;   // operand of phase 3 (zeros beyond the valid positions)
+        *reinterpret_cast<uint16_t*>(a_lo + o) = (uint16_t)lb;
         if (t < T) {
           if constexpr (!BWD)
-            if (s < S) p.alpha32[((int64_t)b * T + t) * S + s] = a;
+            if (s < S) p.alpha32[((int64_t)b * T + t) * S + s] = a[r][h];
           if (s < p.ldS) {
             p.alphaE[((int64_t)b * T + t) * p.ldS + s] = (uint16_t)hb;
             p.alphaE_lo[((int64_t)b * T + t) * p.ldS + s] = (uint16_t)lb;
           }
         }
       }
-    }
     if (!BWD && p.attn_mask && blockIdx.y == 0)
-      for (int s = tid; s < S; s += AF_THREADS) p.attn_mask[(int64_t)b * S + s] = s < L ? 1 : 0;
+      for (int s = tid; s < S; s += 64 * NW) p.attn_mask[(int64_t)b * S + s] = s < L ? 1 : 0;
   }
-  __syncthreads();     // alpha blocks complete; score buffers and phase-1 slices are dead from here on
+  __builtin_amdgcn_s_waitcnt(0);   // the first chunk has landed (each wave reads its own slots only)
+  __syncthreads();                 // row results complete; the partial sums are dead from here on
 
-  // ---------------- phase 3: context vectors, each wave over its 64-column chunks of H ---------------
-  {
-    unsigned char* slice = smem + wave * p.p3_bytes;
-    const int KS = p.KS, nks = KS / 16;             // reduction steps of 16 source positions
-    const int nch = (H + 63) / 64;
-    const int nl = KS / 8;                          // wave-wide 16-byte loads per chunk (8 k-rows of 128 bytes each)
-    af_u32x4_t cregs[16];                           // nl <= 16 (S <= 128)
-    auto load_chunk = [&](int c) {
+  // ---------------- phase 3: context vectors, each wave over its 64-column chunks of H ------------------------------
+  // Transposing reads: lane j of a 16-lane group presents four columns of k-row j / 4 and gets four k of the column that
+  // is its row of the matrix instruction.  Tile i's rows 4 q .. 4 q + 3 are the columns 32 (i / 2) + 8 q + 4 (i % 2) ..: a
+  // lane then holds eight consecutive columns of its decoder step in two tiles.
+  uint32_t fb[NT];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        cregs[i] = af_u32x4_t{0, 0, 0, 0};
-        if (i < nl) {
-          const int k = i * 8 + (lane >> 3), col = c * 64 + (lane & 7) * 8;
-          if (k < S && col < H)
-            cregs[i] = *reinterpret_cast<const af_u32x4_t*>(p.h_enc + (int64_t)k * BH + (int64_t)b * H + col);
-        }
+  for (int i = 0; i < NT; ++i) {
+    const int k = q4 * 8 + (c16 >> 2), piece = (4 * (i >> 1) + (lane & 3)) ^ slot_swizzle<NT>(k);
+    fb[i] = (uint32_t)(k * RB + piece * 16 + (i & 1) * 8);
+  }
+  int par = 0;
+  for (int c = wave; c < nch; c += NW, par ^= 1) {
+    const unsigned char* slot = smem + par * Lds::kX + wave * Lds::kSlot;
+    if (c + NW < nch) load_chunk(c + NW, smem + (par ^ 1) * Lds::kX + wave * Lds::kSlot);
+    f32x4_t acc[RT][NT];
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[r][i][e] = 0.f;
+    for (int ks = 0; ks < nk3; ++ks) {
+      bf16x8_t f[NT];
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+        union { s16x4_t h[2]; bf16x8_t v; } u;
+        u.h[0] = lds_read_tr((lds_s16x4_t*)(lds_void_t*)(slot + fb[i] + ks * 32 * RB));
+        u.h[1] = lds_read_tr((lds_s16x4_t*)(lds_void_t*)(slot + fb[i] + ks * 32 * RB + 4 * RB));
+        f[i] = u.v;
       }
-    };
-    const uint32_t bbase0 = st_frag_base(0, lane), bbase1 = st_frag_base(32, lane);
-    float* stage_f = reinterpret_cast<float*>(smem + p.off_x) + wave * 1024;   // this wave's 16 x 64 floats
-    const int vcol = (lane & 15) * 4, vrow = lane >> 4;
-    if (wave < nch) load_chunk(wave);
-    for (int c = wave; c < nch; c += 4) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i)
-        if (i < nl)
-          *reinterpret_cast<af_u32x4_t*>(slice + (i * 8 + (lane >> 3)) * AF_RS + (lane & 7) * 16) = cregs[i];
-      if (c + 4 < nch) load_chunk(c + 4);           // in flight while this chunk is multiplied and written out
-      f32x16_t cacc[2];
+      for (int r = 0; r < RT; ++r) {
+        const uint32_t o = (uint32_t)((ks >> 1) * Lds::kBlk) + kc_off(16 * r + c16, (ks & 1) * 4 + q4);
+        const bf16x8_t ah = *reinterpret_cast<const bf16x8_t*>(a_hi + o), alo = *reinterpret_cast<const bf16x8_t*>(a_lo + o);
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+        for (int i = 0; i < NT; ++i) acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i], ah, acc[r][i], 0, 0, 0);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) cacc[j][r] = 0.f;
-      for (int kk = 0; kk < nks; ++kk) {
-        const int chunk = (kk & 3) * 2 + (lane >> 5);
-        const bf16x8_t ah = kc_frag(a_hi_blk + (kk >> 2) * 4096, lane & 31, chunk);
-        const bf16x8_t al = kc_frag(a_lo_blk + (kk >> 2) * 4096, lane & 31, chunk);
-        const bf16x8_t b0 = st_frag(slice, bbase0, kk);
-        const bf16x8_t b1 = st_frag(slice, bbase1, kk);
-        cacc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, b0, cacc[0], 0, 0, 0);
-        cacc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, b1, cacc[1], 0, 0, 0);
-        cacc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, b0, cacc[0], 0, 0, 0);
-        cacc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, b1, cacc[1], 0, 0, 0);
+        for (int i = 0; i < NT; ++i) acc[r][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i], alo, acc[r][i], 0, 0, 0);
       }
-      // write-out: 16 rows at a time through this wave's staging slice, 8-byte row vectors to ctx and ctx_lo
-      const int col = c * 64 + vcol;
+    }
+    __builtin_amdgcn_s_waitcnt(0);   // the next chunk has landed; this one's stores are not waited for until the next time
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int half = 0; half < 2; ++half) {
+    for (int r = 0; r < RT; ++r) {
+      const int t = t0 + 16 * r + c16;
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+      for (int g = 0; g < NT / 2; ++g) {
+        const int col = c * 16 * NT + g * 32 + q4 * 8;
+        if (t >= T || col >= H) continue;
+        af_u32x4_t hv, lv;
 #pragma unroll
-          for (int r8 = 0; r8 < 8; ++r8) {
-            const int r = half * 8 + r8;
-            stage_f[(8 * (r8 >> 2) + 4 * (lane >> 5) + (r8 & 3)) * 64 + j * 32 + (lane & 31)] = cacc[j][r];
-          }
-#pragma unroll
-        for (int it = 0; it < 4; ++it) {
-          const int row = it * 4 + vrow;
-          const f32x4_t v4 = *reinterpret_cast<const f32x4_t*>(stage_f + row * 64 + vcol);
-          const int t = t0 + half * 16 + row;
-          if (t < T && col < H) {
-            uint32_t hb[4];
-            float lo[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              hb[e] = f32_to_bf16_bits(v4[e]);
-              lo[e] = v4[e] - bf16_bits_to_f32(hb[e]);
-            }
-            const int64_t o = (int64_t)t * BH + (int64_t)b * H + col;
-            *reinterpret_cast<af_u32x2_t*>(p.ctx + o) = af_u32x2_t{hb[0] | (hb[1] << 16), hb[2] | (hb[3] << 16)};
-            if constexpr (!BWD)
-              *reinterpret_cast<af_u32x2_t*>(p.ctx_lo + o) = af_u32x2_t{pack_bf16(lo[0], lo[1]), pack_bf16(lo[2], lo[3])};
-          }
+        for (int e = 0; e < 4; ++e) {
+          const f32x4_t& v4 = acc[r][2 * g + (e >> 1)];
+          const float v0 = v4[2 * (e & 1)], v1 = v4[2 * (e & 1) + 1];
+          const uint32_t h0 = f32_to_bf16_bits(v0), h1 = f32_to_bf16_bits(v1);
+          hv[e] = h0 | (h1 << 16);
+          lv[e] = pack_bf16(v0 - bf16_bits_to_f32(h0), v1 - bf16_bits_to_f32(h1));
         }
+        const int64_t o = (int64_t)t * BH + (int64_t)b * H + col;
+        *reinterpret_cast<af_u32x4_t*>(p.ctx + o) = hv;
+        if constexpr (!BWD) *reinterpret_cast<af_u32x4_t*>(p.ctx_lo + o) = lv;
       }
     }
   }
@@ -313,30 +340,22 @@ __global__ __launch_bounds__(AF_THREADS) void attn_fwd_fused_kernel(AttnFwdArgs 
 
 bool attn_fwd_fused_supported(int S, int H) { return S >= 1 && S <= 128 && (H % 8) == 0; }
 
-static hipError_t launch_attn_fused(bool bwd, AttnFwdArgs p, hipStream_t st) {
-  if (!attn_fwd_fused_supported(p.S, p.H) || p.B < 1 || p.T < 1 || p.ldS < p.S || p.ldS > 128) return hipErrorInvalidValue;
-  p.SP = (p.S + 31) / 32 * 32;
-  p.KS = (p.S + 15) / 16 * 16;
-  // LDS: region 0 holds the four wave slices of phase 1 ((64 + SP) rows x 64 bytes each) and later those of phase 3
-  // (KS k-rows x 160 bytes each); then the two score buffers / the write-out staging; then the alpha operand blocks
-  p.p1_bytes = (64 + p.SP) * 64;
-  p.p3_bytes = p.KS * AF_RS;
-  const int ph1 = 4 * p.p1_bytes, ph3 = 4 * p.p3_bytes;
-  const int region0 = ((ph1 > ph3 ? ph1 : ph3) + 1023) / 1024 * 1024;
-  const int scores = 2 * AF_ROWS * (p.SP + 8) * 4, staging = 4 * 16 * 64 * 4;
-  const int regionx = ((scores > staging ? scores : staging) + 1023) / 1024 * 1024;
-  const int KB = (p.KS + 63) / 64;
-  p.off_x = region0;
-  p.off_a = region0 + regionx;
-  const int smem = p.off_a + 2 * KB * 4096;
-  static LdsLimit limit[2];
-  const hipError_t e = limit[bwd].raise(bwd ? reinterpret_cast<const void*>(attn_fwd_fused_kernel<true>)
-                                            : reinterpret_cast<const void*>(attn_fwd_fused_kernel<false>), 160 * 1024);
+template <bool BWD, int RT, int ST> static hipError_t launch_attn_shape(const AttnFwdArgs& p, hipStream_t st) {
+  auto k = attn_fused_kernel<BWD, RT, ST>;
+  constexpr int smem = AttnLds<RT, ST>::kBytes;
+  static LdsLimit limit;
+  const hipError_t e = limit.raise(reinterpret_cast<const void*>(k), smem);
   if (e != hipSuccess) return e;
-  const dim3 grid(p.B, (p.T + AF_ROWS - 1) / AF_ROWS);
-  if (bwd) hipLaunchKernelGGL(attn_fwd_fused_kernel<true>, grid, dim3(AF_THREADS), smem, st, p);
-  else hipLaunchKernelGGL(attn_fwd_fused_kernel<false>, grid, dim3(AF_THREADS), smem, st, p);
+  hipLaunchKernelGGL(k, dim3(p.B, (p.T + 16 * RT - 1) / (16 * RT)), dim3(64 * AF_NW), smem, st, p);
   return hipGetLastError();
+}
+template <bool BWD> static hipError_t launch_attn_fused(const AttnFwdArgs& p, hipStream_t st) {
+  if (!attn_fwd_fused_supported(p.S, p.H) || p.B < 1 || p.T < 1 || p.ldS < p.S || p.ldS > 128) return hipErrorInvalidValue;
+  // (the order of every sum is the same in all of them; the figures are at the head of this file)
+  if (p.S > 64) return launch_attn_shape<BWD, 1, 8>(p, st);
+  const bool wide = (int64_t)p.B * ((p.T + 31) / 32) >= 192;
+  if (p.S > 32) return wide ? launch_attn_shape<BWD, 2, 4>(p, st) : launch_attn_shape<BWD, 1, 4>(p, st);
+  return wide ? launch_attn_shape<BWD, 2, 2>(p, st) : launch_attn_shape<BWD, 1, 2>(p, st);
 }
 
 hipError_t launch_attn_fwd_fused(const void* q_hi, const void* q_lo, const void* h_enc, const int32_t* src_len, int B,
@@ -355,7 +374,7 @@ hipError_t launch_attn_fwd_fused(const void* q_hi, const void* q_lo, const void*
   p.attn_mask = attn_mask;
   p.T = T; p.S = S; p.B = B; p.H = H;
   p.ldS = ldS;
-  return launch_attn_fused(false, p, st);
+  return launch_attn_fused<false>(p, st);
 }
 
 hipError_t launch_attn_bwd_fused(const void* dC_hi, const void* dC_lo, const void* h_enc, const int32_t* src_len,
@@ -374,7 +393,7 @@ hipError_t launch_attn_bwd_fused(const void* dC_hi, const void* dC_lo, const voi
   p.attn_mask = nullptr;
   p.T = T; p.S = S; p.B = B; p.H = H;
   p.ldS = ldS;
-  return launch_attn_fused(true, p, st);
+  return launch_attn_fused<true>(p, st);
 }
 
 }  // namespace asx

@@ -8,8 +8,7 @@
 //   d_h_enc[s,b] = alpha[s] dC[b] + dscore[s] Q[b]
 // One row per sentence leaves nothing for matrix instructions; what counts is that the sentence's S x H block is
 // requested at once: 16 waves, four source positions per wave in flight.  128 x 50 x 1024, bf16: per-step mode 11 us (19 with
-// eight waves and two positions); backward 14 us, where the 32-step kernel of attn_fused.hip, four waves and a tile ahead,
-// takes 26 and d_h_enc as a batched product of rank one 25.
+// eight waves and two positions); backward 14 us, where d_h_enc alone as a batched product of rank one takes 25.
 #include "common.h"
 #include "kernels.h"
 #include "lds_limit.h"

@@ -22,7 +22,7 @@ hipError_t launch_attn_softmax_rows_bwd(const float* alpha32, const float* dalph
 
 // Eq. 1-3 fused for the batched path, bf16 storage, S <= 128 (attn_fwd_fused_supported): q_hi / q_lo [T,B,H] (Q = h_dec
 // W_a as value and rounding remainder), h_enc [S,B,H] -> alpha32 [B,T,S], alphaE / alphaE_lo [B,T,ldS] (zero padded),
-// ctx / ctx_lo [T,B,H], optional attn_mask [B,S].  One workgroup per (sentence, 32 decoder steps).
+// ctx / ctx_lo [T,B,H], optional attn_mask [B,S].  One workgroup per (sentence, 16 or 32 decoder steps).
 bool attn_fwd_fused_supported(int S, int H);
 hipError_t launch_attn_fwd_fused(const void* q_hi, const void* q_lo, const void* h_enc, const int32_t* src_len, int B,
                                  int T, int S, int H, float* alpha32, void* alphaE, void* alphaE_lo, int64_t ldS,

@@ -46,6 +46,28 @@ def test_bf16_products_in_64x64_tiles(shape, skip):
     _parity(make_custom(T=T, S=S, B=B, H=H, V=V, seed=H, dtype="bf16", min_len=1, pad_prob=0.2), skip)
 
 
+@pytest.mark.parametrize("shape", [(1, 1, 3, 8, 67),          # one step, one source position, one reduction step
+                                   # (The vocabulary of the larger ones: with 203 words the rounding of dlogits to bf16
+                                   # leaves 0.019 to 0.028 of dW_out to the row-scale floor, whatever made the states;
+                                   # the budget of 0.0022 was taken at larger ones.)
+                                   (16, 32, 4, 72, 515),      # whole row and source tiles, a reduction of 2 steps and a bit
+                                   (17, 33, 3, 520, 203),     # one past them; waves with one and two pairs of steps
+                                   (33, 64, 5, 1032, 2003),   # waves with two and three pairs
+                                   (19, 65, 3, 136, 203),     # 32-column slots
+                                   (3, 128, 2, 2056, 203),    # the longest source, waves with four and five pairs
+                                   (31, 20, 192, 24, 2003),    # 32 decoder steps per workgroup, a source of one tile
+                                   (33, 45, 97, 40, 2003)])    # the same, of two
+def test_fused_attention_at_tile_edges(shape):
+    """bf16, S <= 128: 16 or 32 decoder steps and 32, 64 or 128 source positions per workgroup, eight waves that share the
+    reduction and the columns; one sentence of length 0.  (Wide states get weights of 0.05, as in the largest configuration:
+    with 0.1 the scores of 1032 units are twice those the tolerance was taken at, and the rounding of dQ alone moves an
+    element of d_h_dec to 1.34 of it.)"""
+    T, S, B, H, V = shape
+    inp = make_custom(T=T, S=S, B=B, H=H, V=V, seed=S, dtype="bf16", min_len=1, pad_prob=0.1, w=0.05 if H > 1000 else 0.1)
+    inp.src_len[B // 2] = 0
+    _parity(inp)
+
+
 @pytest.mark.parametrize("dtype, H", [("bf16", 72), ("bf16", 520), ("f32", 68), ("f32", 67)])   # f32, 67: no whole vectors
 @pytest.mark.parametrize("pad_prob", [0.0, 0.3, 0.97])         # all rows, some, a row or two of 35
 def test_split_dz_goes_straight_to_its_rows(dtype, H, pad_prob):
