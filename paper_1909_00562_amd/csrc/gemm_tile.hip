@@ -4,13 +4,17 @@
 // walks the whole reduction on one compute unit while the others idle; there are four times as many blocks with a
 // quarter of the work per reduction tile.  0.26 us per 64 reduction elements and compute unit, its LDS traffic (16 KiB in,
 // 32 KiB out), however many blocks share it.
-// 128 x 128 tiles: 0.7 us per 64 reduction elements with a compute unit to itself (four stages), 1.05 for two blocks that
-// share one (two stages each: 64 KiB of LDS per block); LDS traffic again, 32 KiB in and 64 KiB out, before the matrix
-// cores.  Rates and the choice between the shapes: gemm_plan.
-// Loads go HBM -> LDS directly in every orientation, NST - 1 tiles ahead, one barrier per tile, no branch and the same
-// number of loads in flight at every wait (past the last tile they read out of range, i.e. zeros).  (The form this
-// replaced transposed strided operands in registers: 6400 x 1024 x 2048 NN 56 us against 41, 16000 x 512 x 1286 TN
-// 51 against 31; NT 60 against 55 at 6400 x 1024 x 3072, 22.6 against 24.0 at a third of that.)
+// 128 x 128 tiles: 0.67 us per 64 reduction elements with a compute unit to itself (four stages), 1.0 for two blocks that
+// share one (two stages each: 64 KiB of LDS per block).  Rates and the choice between the shapes: gemm_plan.
+// Loads go HBM -> LDS directly in every orientation, NST tiles ahead, one barrier per tile, no branch and the same
+// number of loads in flight at every wait (past the last tile they read out of range, i.e. zeros).
+// What bounds it is the stream of loads: without fragment reads and matrix instructions a tile takes 0.57 us (32 KiB per
+// compute unit, 57 bytes a nanosecond), contiguous operands or a fifth stage change nothing, operands that all blocks share
+// 0.49.  The rest was the chain barrier -> fragment reads -> matrix instructions of a wave that has its SIMD to itself, so
+// the reads of half a tile now run between the matrix instructions of the half before: 4096 x 1024 x 6400 TN 73.5 -> 67.6 us,
+// 6400 x 1024 x 3072 NT 81 -> 73.7, 2257 x 1000 x 3000 NT 46.2 -> 42.3, 6400 x 1024 x 2048 NN 47.3 -> 44.4 (16000 x 512 x
+// 1286 TN 30.3 -> 32).  At most 256 registers per wave keep the accumulators out of the other register half, from which the
+// compiler copies them around every matrix instruction of this loop.
 //   * reduction-contiguous operand: LDS [rows][64 k] as in gemm_bf16.hip;
 //   * strided operand: LDS [64 k][columns] as in memory, fragments by transposing reads.  A 16-lane group reads four
 //     k-rows x 32 bytes; the 32-byte segments of a row are XOR-swizzled so that the four land in different banks.
@@ -146,7 +150,7 @@ __device__ __forceinline__ void gs_finish_ragged(const GemmDev& p, int out_bf16,
 }
 
 template <int TW, bool AKC, bool BKC, int NST>
-__global__ __launch_bounds__(256) void gemm_bf16_tile_kernel(GemmDev p, int out_bf16) {
+__global__ __launch_bounds__(256, 2) void gemm_bf16_tile_kernel(GemmDev p, int out_bf16) {
   constexpr int BM = 32 * TW, TILE = BM * ROWB, STAGE = 2 * TILE;   // square block tile; bytes of an operand tile, a stage
   constexpr int NL = TW, LD = BM + 4;                               // loads per wave, operand and tile; staging row (floats)
   static_assert((NST & (NST - 1)) == 0 && NST * STAGE >= 64 * LD * 4, "ring of a power of two; write-out staging");
@@ -225,31 +229,45 @@ __global__ __launch_bounds__(256) void gemm_bf16_tile_kernel(GemmDev p, int out_
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
 
-  // s_waitcnt vmcnt: 2 NL loads per wave and tile, the oldest tile has landed
-  constexpr int kFly = 2 * NL * (NST - 2), kWaitOldest = (kFly & 15) | ((kFly >> 4) << 14) | 0x0f70;
-  for (int t = 0; t < NST - 1; ++t) issue(t);
+  // Two sets of fragments, one per half (32 reduction elements) of a tile: the reads of a half run between the matrix
+  // instructions of the half before it.  s_waitcnt vmcnt: 2 NL loads per wave and tile, all but NST - 2 (ahead of the first
+  // barrier NST - 1) tiles have landed.
+  constexpr int kFly = 2 * NL * (NST - 2), kFly0 = 2 * NL * (NST - 1);
+  constexpr int kWaitNext = (kFly & 15) | ((kFly >> 4) << 14) | 0x0070, kWaitFirst = (kFly0 & 15) | ((kFly0 >> 4) << 14) | 0x0f70;
+  bf16x8_t a[2][TW], b[2][TW];
+  auto read = [&](int stage, int ks, int i) {
+    const unsigned char* as = smem + stage * STAGE;
+    b[ks][i] = gs_frag<BKC, BM>(as + TILE, fb[i], ks);
+    a[ks][i] = gs_frag<AKC, BM>(as, fa[i], ks);
+  };
+  auto mul = [&](int ks, int i) {
+#pragma unroll
+    for (int j = 0; j < TW; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks][i], b[ks][j], acc[i][j], 0, 0, 0);
+  };
+  for (int t = 0; t < NST; ++t) issue(t);
+  __builtin_amdgcn_s_waitcnt(kWaitFirst);
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < TW; ++i) read(0, 0, i);
   for (int t = 0; t < nk; ++t) {
-    __builtin_amdgcn_s_waitcnt(kWaitOldest);
+    const int cur = t & (NST - 1);
+#pragma unroll
+    for (int i = 0; i < TW; ++i) {
+      read(cur, 1, i);
+      mul(0, i);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __builtin_amdgcn_s_waitcnt(kWaitNext);   // own loads of tile t + 1 have landed, own reads of tile t are in registers
     __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_barrier();   // tile t is in LDS, and every wave is done with tile t - 1, whose stage is refilled
+    __builtin_amdgcn_s_barrier();            // tile t + 1 is in LDS, and every wave is done with tile t, whose stage is refilled
     __builtin_amdgcn_sched_barrier(0);
-    issue((t + NST - 1) & (NST - 1));
-    const unsigned char* as = smem + (t & (NST - 1)) * STAGE;
-    bf16x8_t a[2][TW], b[2][TW];
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
+    for (int i = 0; i < TW; ++i) read((t + 1) & (NST - 1), 0, i);
+    issue(cur);
 #pragma unroll
-      for (int i = 0; i < TW; ++i) {
-        a[ks][i] = gs_frag<AKC, BM>(as, fa[i], ks);
-        b[ks][i] = gs_frag<BKC, BM>(as + TILE, fb[i], ks);
-      }
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-      for (int i = 0; i < TW; ++i)
-#pragma unroll
-        for (int j = 0; j < TW; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks][i], b[ks][j], acc[i][j], 0, 0, 0);
+    for (int i = 0; i < TW; ++i) mul(1, i);
     __builtin_amdgcn_sched_barrier(0);
   }
 
