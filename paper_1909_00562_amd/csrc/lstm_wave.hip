@@ -19,9 +19,11 @@
 //     rounding compounds over steps and layers.  Gate gradients enter the backward products as plain bf16.
 //   * fp32 storage: fp64 matrix instructions on operands widened after the load, as in gemm_f32.hip.
 //
-// 4 layers x 1024 units x 128 sentences, full wavefronts: 28 us forward, 28.8 backward, of which 12 are not the
-// reduction (launch, cells, 14 MB of stores); 64 MB of weights and 1 MB (forward) or 1.5 MB (backward) of fragments per
-// compute unit make the rest.  A launch per layer and step took 10.5 us each, 42 for what a wavefront does, and the input
+// 4 layers x 1024 units x 128 sentences, full wavefronts: 25.1 us forward, 27.6 backward (27.3 and 28.9 before the cells
+// were shortened: functions above the kernels, dropout and the backward tanh while the first fragments are on their way,
+// column sums by rotations in registers, 16 MB of stores of which the gates go past the caches).  Forward, launch and first
+// loads 3.5, reduction 12.5 (weights that all come from the L2 save 1.6), cells the rest, 5 of it the stores.  64 MB of
+// weights and 1 MB (forward) or 1.5 MB (backward) of fragments per compute unit make the reduction.  A launch per layer and step took 10.5 us each, 42 for what a wavefront does, and the input
 // products another 90 per layer.  Tried without gain: weights streamed past the caches (34.6 / 40.7 us), other tile orders
 // of the weights, two to four slots (30.0 / 28.9 / 28.4), 64 x 64 and 64 x 32 forward blocks (33.5, 34.0).
 #include "common.h"
@@ -66,13 +68,74 @@ template <> struct LsMma<float> {
   static __host__ __device__ __forceinline__ int r_of_row(int rho) { return rho >> 2; }
 };
 
-__device__ __forceinline__ float ls_sigmoid(float a) { return 1.f / (1.f + expf(-a)); }
+// The cell's functions without branches or IEEE divisions: with one wave per SIMD nothing hides the vector instructions of
+// a cell (4 x 1024 units x 128 sentences, forward wavefronts: 2 us of 27 less than with expf, tanhf and divisions).  Largest /
+// mean error in units of the last place over 4 M arguments of N(0, s^2), here and with those: sigmoid s = 0.6 2.12 / 0.402 and
+// 2.12 / 0.401, s = 10 2.49 / 0.419 and 2.49 / 0.418; tanh s = 0.1 0.54 / 0.250 and 0.60 / 0.251, s = 0.6 1.48 / 0.265 and
+// 1.38 / 0.273, s = 10 1.36 / 0.167 and 1.34 / 0.169.
+// e^-a, |a| <= 128 or NaN
+__device__ __forceinline__ float ls_exp_neg(float a) {
+  constexpr float kLog2e = 1.44269504088896f, kLog2eLo = 1.925963033500e-8f;
+  const float n = __builtin_rintf(-a * kLog2e);
+  const float f = __builtin_fmaf(-a, kLog2eLo, __builtin_fmaf(-a, kLog2e, -n));
+  return __builtin_ldexpf(__builtin_amdgcn_exp2f(f), (int)n);
+}
+// 1 / d of a finite d >= 1: the instruction and a Newton step
+__device__ __forceinline__ float ls_rcp(float d) {
+  const float r = __builtin_amdgcn_rcpf(d);
+  return __builtin_fmaf(__builtin_fmaf(-d, r, 1.f), r, r);
+}
+__device__ __forceinline__ float ls_sigmoid(float a) {
+  constexpr float kMax = 87.33f;   // beyond it the result is 1 or less than the smallest normal number
+  const float b = __builtin_fabsf(a) > kMax ? __builtin_copysignf(kMax, a) : a;   // (NaN stays)
+  const float s = ls_rcp(1.f + ls_exp_neg(b));
+  return a < -kMax ? 0.f : s;
+}
+// |a| < 0.625: a + a^3 P(a^2), P the minimax polynomial of (tanh(a) / a - 1) / a^2 (relative error of the whole 1.5e-10 before
+// rounding); else 1 - 2 e^-2a / (1 + e^-2a)
+__device__ __forceinline__ float ls_tanh(float a) {
+  const float m = __builtin_fabsf(a), b = m > 20.f ? 20.f : m;
+  const float e = ls_exp_neg(b + b), t = __builtin_fmaf(-2.f * e, ls_rcp(1.f + e), 1.f);
+  const float u = a * a;
+  float q = __builtin_fmaf(u, 0x1.197b62p-9f, -0x1.0c213ep-7f);
+  q = __builtin_fmaf(u, q, 0x1.6394d8p-6f);
+  q = __builtin_fmaf(u, q, -0x1.b9ef7cp-5f);
+  q = __builtin_fmaf(u, q, 0x1.11106cp-3f);
+  q = __builtin_fmaf(u, q, -0x1.555554p-2f);
+  const float s = __builtin_fmaf(u * a, q, a);
+  return m < 0.625f ? s : __builtin_copysignf(t, a);
+}
+// sum over the 16 lanes of a row (lanes l, l ^ 8, then ^ 4, ^ 2, ^ 1: rotations add the same pairs), without the LDS pipe
+template <int N> __device__ __forceinline__ float ls_row_ror(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + N, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float ls_row_sum(float v) {
+  v += ls_row_ror<8>(v);
+  v += ls_row_ror<4>(v);
+  v += ls_row_ror<2>(v);
+  v += ls_row_ror<1>(v);
+  return v;
+}
 __device__ __forceinline__ int ls_len(const int32_t* lengths, int b, int T) {
   const int n = lengths[b];
   return n < 0 ? 0 : (n > T ? T : n);
 }
 
 // Four consecutive elements, of which n are inside.  VEC (H % 4 == 0): all four are, and aligned.
+// the same past the caches, for what no wavefront reads again
+template <bool VEC> __device__ __forceinline__ void ls_st4_away(float* p, const f32x4_t& v, int n) {
+  if constexpr (VEC) {
+    __builtin_nontemporal_store(v, reinterpret_cast<f32x4_t*>(p));
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (e < n) p[e] = v[e];
+  }
+}
+template <bool VEC> __device__ __forceinline__ void ls_st4_away(uint16_t* p, const f32x4_t& v, int) {
+  const ls_u32x2_t w = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+  __builtin_nontemporal_store(w, reinterpret_cast<ls_u32x2_t*>(p));
+}
 template <bool VEC> __device__ __forceinline__ f32x4_t ls_ld4(const float* p, int n) {
   if constexpr (VEC) {
     return *reinterpret_cast<const f32x4_t*>(p);
@@ -283,11 +346,23 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
         for (int j = 0; j < NJ; ++j) M::mma(acc[i][j], wf[slot][i], lf[slot][j]);
     }
   };
+  // while the first fragments are on their way: the dropout multipliers of the cells
+  const bool drop = p.drop_thr && l + 1 < p.L;
+  f32x4_t dm[NTASK];
+  auto masks = [&]() {
+    if (!drop) return;
+#pragma unroll
+    for (int k = 0; k < NTASK; ++k) {
+      const int task = wave + k * LS_KS, g = task / NJ, j = task % NJ;
+      dm[k] = ls_drop4<VEC>(((uint64_t)l * p.T + t) * (uint64_t)BH + (uint64_t)((int64_t)(b0 + 16 * j + c) * H) +
+                                (uint64_t)(u0 + 16 * g + 4 * q), p.drop_seed, p.drop_thr, p.drop_scale);
+    }
+  };
   constexpr int NP = M::kPair ? 2 : 1, NM = M::kPair ? 2 * NI * NJ : 4 * NI * NJ;
   const int own = own_steps<LS_KS>(n0 + n1, wave);
   if constexpr (TWO) {
     const int own0 = l == 0 ? own_steps<LS_KS>(n0, wave) : own;
-    wave_reduce<PF, NI + NP * NJ, NM>(own0, load, mul);
+    wave_reduce<PF, NI + NP * NJ, NM>(own0, load, mul, NoRest(), masks);
     wave_reduce<PF, NI + NJ, NM / 2>(
         own - own0, [&](int slot, int i) { load(slot, own0 + i, false); },
         [&](int slot, int i) { mul(slot, own0 + i, false); });
@@ -300,9 +375,10 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
           for (int ii = 0; ii < NI; ++ii)
 #pragma unroll
             for (int j = 0; j < NJ; ++j) M::mma(acc[ii][j], wf[slot][ii], lf[slot][j]);
-        });
+        },
+        masks);
   } else {
-    wave_reduce<PF, NI + NP * NJ, NM>(own, load, mul);
+    wave_reduce<PF, NI + NP * NJ, NM>(own, load, mul, NoRest(), masks);
   }
 
 #pragma unroll
@@ -337,18 +413,19 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
       for (int e = 0; e < 4; ++e) a[e] = (float)(v[e] + (typename M::sum_t)bias4[e][ii]);
       gi[ii] = ls_sigmoid(a[0]);
       gf[ii] = ls_sigmoid(a[1]);
-      gg[ii] = tanhf(a[2]);
+      gg[ii] = ls_tanh(a[2]);
       go[ii] = ls_sigmoid(a[3]);
       // (which product is rounded by itself is not left to the compiler: block shapes would differ)
       cn[ii] = __builtin_fmaf(gf[ii], cp[k][ii], gi[ii] * gg[ii]);
-      hn[ii] = go[ii] * tanhf(cn[ii]);
+      hn[ii] = go[ii] * ls_tanh(cn[ii]);
     }
     const int64_t idx = (int64_t)b * H + unit0;
-    ls_st4<VEC>(G, gi, n);
-    ls_st4<VEC>(G + H, gf, n);
-    ls_st4<VEC>(G + 2 * (int64_t)H, gg, n);
-    ls_st4<VEC>(G + 3 * (int64_t)H, go, n);
-    const bool valid = t < ls_len(p.lengths, b, p.T);
+    ls_st4_away<VEC>(G, gi, n);
+    ls_st4_away<VEC>(G + H, gf, n);
+    ls_st4_away<VEC>(G + 2 * (int64_t)H, gg, n);
+    ls_st4_away<VEC>(G + 3 * (int64_t)H, go, n);
+    const int len = ls_len(p.lengths, b, p.T);
+    const bool valid = t < len;
     const int64_t foff = ls_tile_off<TE>(unit0, b, nct);
     TE* hFn_hi = reinterpret_cast<TE*>(p.hF_hi + (2 * l + ((t + 1) & 1)) * p.h_stride) + foff;
     TE* hFn_lo = reinterpret_cast<TE*>(p.hF_lo + (2 * l + ((t + 1) & 1)) * p.h_stride) + foff;
@@ -360,14 +437,12 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
     f32x4_t o = {0.f, 0.f, 0.f, 0.f}, hv;
     if (valid) {   // what the next layer reads
       o = hn;
-      if (p.drop_thr && l + 1 < p.L) {
-        const f32x4_t m = ls_drop4<VEC>(((uint64_t)l * p.T + t) * (uint64_t)BH + (uint64_t)idx, p.drop_seed, p.drop_thr,
-                                   p.drop_scale);
+      if (drop) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = m[e] != 0.f ? o[e] * m[e] : 0.f;
+        for (int e = 0; e < 4; ++e) o[e] = dm[k][e] != 0.f ? o[e] * dm[k][e] : 0.f;
       }
       hv = hn;
-      ls_st4<VEC>(p.hf + l * BH + idx, hn, n);
+      if (t + 1 == len) ls_st4<VEC>(p.hf + l * BH + idx, hn, n);   // the final state
       ls_st4<true>(hFn_hi, hn, 4);
       if constexpr (M::kPair) ls_st4<true>(hFn_lo, ls_rest<TE>(hn), 4);
     } else {       // padded step: the state passes through, the output is 0
@@ -457,8 +532,24 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_bwd_kernel(LsBwd p, int d,
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[s][i][j][r] = 0;
 
+  // while the first fragments are on their way: tanh of the cell states, the dropout multipliers (back through the mask the
+  // forward step put on this layer's output)
+  const bool drop = p.drop_thr && !top;
+  f32x4_t tc[NTASK], dm[NTASK];
+  auto ahead = [&]() {
+#pragma unroll
+    for (int k = 0; k < NTASK; ++k) {
+      const int task = wave + k * LS_KS, i = task / NJ, j = task % NJ;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) tc[k][e] = ls_tanh(cn[k][e]);
+      if (drop)
+        dm[k] = ls_drop4<VEC>(((uint64_t)l * p.T + tc0) * (uint64_t)BH + (uint64_t)((int64_t)(b0 + 16 * j + c) * H) +
+                                  (uint64_t)(u0 + 16 * i + 4 * q), p.drop_seed, p.drop_thr, p.drop_scale);
+    }
+  };
   const int ng = 4 * ls_gate_stride<TE>(H) / KST;
   const int n0 = t + 1 < p.T ? ng : 0, n1 = !top && t >= 0 ? ng : 0;
+  if (n0 + n1 == 0) ahead();
   if (n0 + n1 > 0) {
     const int64_t cstep = (int64_t)nct * kLsTile, wrow = ng * kLsTile;
     const char* w0 = p.WT_hh[l] + u0 / 16 * wrow;
@@ -492,11 +583,12 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_bwd_kernel(LsBwd p, int d,
     if (n0 > 0 && n1 > 0) {
       wave_reduce<PF, NL, NM>(
           2 * own, [&](int slot, int i) { fetch(slot, (i & 1) != 0, wave + (i >> 1) * LS_KS); },
-          [&](int slot, int) { add(slot, slot & 1); });
+          [&](int slot, int) { add(slot, slot & 1); }, NoRest(), ahead);
     } else {
       const bool in = n0 == 0;
       wave_reduce<PF, NL, NM>(
-          own, [&](int slot, int i) { fetch(slot, in, wave + i * LS_KS); }, [&](int slot, int) { add(slot, 0); });
+          own, [&](int slot, int i) { fetch(slot, in, wave + i * LS_KS); }, [&](int slot, int) { add(slot, 0); }, NoRest(),
+          ahead);
       if (in) {
 #pragma unroll
         for (int i = 0; i < NI; ++i)
@@ -552,22 +644,19 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_bwd_kernel(LsBwd p, int d,
     if (cell) {
       if (!top) {
         dy[k] = sum[1];
-        if (p.drop_thr) {   // back through the mask the forward step put on this layer's output
-          const f32x4_t m = ls_drop4<VEC>(((uint64_t)l * p.T + t) * (uint64_t)BH + (uint64_t)idx, p.drop_seed, p.drop_thr,
-                                     p.drop_scale);
+        if (drop) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) dy[k][e] = m[e] != 0.f ? dy[k][e] * m[e] : 0.f;
+          for (int e = 0; e < 4; ++e) dy[k][e] = dm[k][e] != 0.f ? dy[k][e] * dm[k][e] : 0.f;
         }
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float dd = dy[k][e] + dh[e];
-        const float tc = tanhf(cn[k][e]);
-        const float dc = dcs[k][e] + dd * go[k][e] * (1.f - tc * tc);
+        const float dc = dcs[k][e] + dd * go[k][e] * (1.f - tc[k][e] * tc[k][e]);
         da[0][e] = dc * gg[k][e] * gi[k][e] * (1.f - gi[k][e]);
         da[1][e] = dc * cp[k][e] * gf[k][e] * (1.f - gf[k][e]);
         da[2][e] = dc * gi[k][e] * (1.f - gg[k][e] * gg[k][e]);
-        da[3][e] = dd * tc * go[k][e] * (1.f - go[k][e]);
+        da[3][e] = dd * tc[k][e] * go[k][e] * (1.f - go[k][e]);
         dcs[k][e] = dc * gf[k][e];
       }
       if constexpr (!VEC) {   // units past H: reduction padding of the products that read these, kept zero
@@ -596,10 +685,7 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_bwd_kernel(LsBwd p, int d,
     for (int g = 0; g < 4; ++g)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        float v = da[g][e];
-#pragma unroll
-        for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 16);
-        da[g][e] = v;
+        da[g][e] = ls_row_sum(da[g][e]);
       }
     if (c < 4 && (b0 >> 4) + j < nct) {
       const f32x4_t mine = c == 0 ? da[0] : c == 1 ? da[1] : c == 2 ? da[2] : da[3];
@@ -640,9 +726,29 @@ __global__ __launch_bounds__(256) void ls_prep_fwd_kernel(LsFwd p, LsPrepFwd s) 
       const int lane = (int)(i & 63), k = (int)((i >> 6) / nct) * KST + (lane >> 4) * V;
       const int64_t tile = i >> 6;
       const int b = (int)(tile % nct) * 16 + (lane & 15);
-      TE hi[V], lo[V];
+      alignas(16) TE hi[V], lo[V];
+      // a chunk of V units inside, its rows aligned: whole vectors (one step of 4 x 1024 units x 128 sentences: 8.6 -> 5.3 us)
+      const bool whole = H % V == 0 && b < B && k < H;
+      if (whole) {
+        const int64_t row = (int64_t)b * H + k, idx = (int64_t)l * BH + row;
+        f32x4_t h[V / 4], c[V / 4];
+#pragma unroll
+        for (int v = 0; v < V / 4; ++v) {
+          h[v] = s.h0 ? *reinterpret_cast<const f32x4_t*>(s.h0 + idx + 4 * v) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+          c[v] = s.c0 ? *reinterpret_cast<const f32x4_t*>(s.c0 + idx + 4 * v) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int v = 0; v < V / 4; ++v) {
+          ls_st4<true>(p.hf + idx + 4 * v, h[v], 4);
+          ls_st4<true>(cs + row + 4 * v, c[v], 4);
+          ls_st4<true>(hE + row + 4 * v, h[v], 4);
+          ls_st4<true>(hi + 4 * v, h[v], 4);
+          ls_st4<true>(lo + 4 * v, ls_rest<TE>(h[v]), 4);
+        }
+      }
 #pragma unroll
       for (int e = 0; e < V; ++e) {
+        if (whole) break;
         const bool in = b < B && k + e < H;
         const int64_t idx = (int64_t)l * BH + (int64_t)(in ? b : 0) * H + (in ? k + e : 0);
         const float h = in && s.h0 ? s.h0[idx] : 0.f;
@@ -656,13 +762,12 @@ __global__ __launch_bounds__(256) void ls_prep_fwd_kernel(LsFwd p, LsPrepFwd s) 
         }
       }
       auto put = [&](char* base, const TE (&v)[V]) {
-#pragma unroll
-        for (int e = 0; e < V; ++e) reinterpret_cast<TE*>(base + i * 16)[e] = v[e];
+        *reinterpret_cast<ls_u32x4_t*>(base + i * 16) = *reinterpret_cast<const ls_u32x4_t*>(v);
       };
       put(p.hF_hi + 2 * l * p.h_stride, hi);
       if constexpr (M::kPair) put(p.hF_lo + 2 * l * p.h_stride, lo);
       if (k >= H) {   // reduction padding: zero in every slot
-        const TE z[V] = {};
+        alignas(16) const TE z[V] = {};
         put(p.hF_hi + (2 * l + 1) * p.h_stride, z);
         if constexpr (M::kPair) put(p.hF_lo + (2 * l + 1) * p.h_stride, z);
         if (l + 1 < L)
@@ -798,11 +903,11 @@ hipError_t launch_ls_bias_reduce(const float* dbacc, const LsBiasOut& o, int L, 
   return hipGetLastError();
 }
 
-template <typename TE, int NI, int NJ, int PF>
+template <typename TE, int NI, int NJ, int PF, int PF_ROWS = PF>
 static hipError_t ls_fwd_shape(const LsFwd& p, int d, int l_lo, int nl, hipStream_t st) {
   const unsigned grid = ls_grid((int64_t)nl * ((p.H + 4 * NI - 1) / (4 * NI)), (p.B + 16 * NJ - 1) / (16 * NJ));
 #define ASX_FWD(ROWS, VEC, APART)                                                                                    \
-  hipLaunchKernelGGL((ls_wave_fwd_kernel<TE, NI, NJ, PF, ROWS, VEC, APART>), dim3(grid), dim3(64 * LS_KS), 0, st, p, \
+  hipLaunchKernelGGL((ls_wave_fwd_kernel<TE, NI, NJ, ROWS ? PF_ROWS : PF, ROWS, VEC, APART>), dim3(grid), dim3(64 * LS_KS), 0, st, p, \
                      d, l_lo, nl)
   if (p.x_apart && p.w_rows) return hipErrorInvalidValue;   // (ls_input_apart: not with one step)
   if (p.w_rows) ASX_FWD(true, true, false);   // widths are multiples of 4
@@ -828,13 +933,15 @@ template <typename TE> hipError_t launch_ls_wave_fwd(const LsFwd& p, int d, hipS
   const int nl = l_hi - l_lo + 1;
   if (nl < 1) return hipErrorInvalidValue;
   const int64_t b64 = (p.B + 63) / 64, b32 = (p.B + 31) / 32;
+  // The caller's rows come from memory, not from the caches: more steps in flight (one step, 4 x 1024 units x 128
+  // sentences, with the other changes to the cells: 72.1 us with four, 68.5 with six, 75.4 with eight).
   // The largest block that still gives most compute units one: larger blocks load less per output (128 gate rows x 64
   // sentences: 512 bytes per reduction index for 8192 outputs).  1024 units x 128 sentences, 64 x 32 blocks against 128 x 64:
   // three layers 27.5 us (768 blocks) and 28.0 (192), four 34.0 (1024) and 29.4 (256).
   if constexpr (LsMma<TE>::kPair) {
     if (nl * ((p.H + 31) / 32) * b64 >= 192) return ls_fwd_shape<TE, 8, 4, 3>(p, d, l_lo, nl, st);
-    if (nl * ((p.H + 15) / 16) * b32 >= 192) return ls_fwd_shape<TE, 4, 2, 4>(p, d, l_lo, nl, st);
-    return ls_fwd_shape<TE, 4, 1, 4>(p, d, l_lo, nl, st);
+    if (nl * ((p.H + 15) / 16) * b32 >= 192) return ls_fwd_shape<TE, 4, 2, 4, 6>(p, d, l_lo, nl, st);
+    return ls_fwd_shape<TE, 4, 1, 4, 6>(p, d, l_lo, nl, st);
   } else {
     if (nl * ((p.H + 15) / 16) * b32 >= 512) return ls_fwd_shape<TE, 4, 2, 4>(p, d, l_lo, nl, st);
     return ls_fwd_shape<TE, 4, 1, 4>(p, d, l_lo, nl, st);

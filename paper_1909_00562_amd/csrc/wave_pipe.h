@@ -22,6 +22,9 @@ template <int v, int NL, int NM> __device__ __forceinline__ void spread_loads() 
 struct NoRest {
   __device__ __forceinline__ void operator()(int, int) const {}
 };
+struct NoMeanwhile {
+  __device__ __forceinline__ void operator()() const {}
+};
 
 // A wave's n reduction steps, slot i % PF of the fragment registers holding step i.  load(slot, i) must be free of
 // branches and valid for 0 <= i < n; past the last step it is called with the last one again, so that the number of
@@ -30,12 +33,19 @@ struct NoRest {
 // wave at the address unit while its matrix pipe idles: forward wavefronts of 4 layers x 1024 units x 128 sentences
 // then took the sum of their load and matrix times.
 // rest(slot, i): products of step i that may need a branch, behind the region that the loads are spread over.
-template <int PF, int NL, int NM, typename Load, typename Mul, typename Rest = NoRest>
-__device__ __forceinline__ void wave_reduce(int n, Load load, Mul mul, Rest rest = Rest()) {
-  if (n <= 0) return;
+// meanwhile(): other work of the wave, done while the first loads are on their way.
+template <int PF, int NL, int NM, typename Load, typename Mul, typename Rest = NoRest, typename Meanwhile = NoMeanwhile>
+__device__ __forceinline__ void wave_reduce(int n, Load load, Mul mul, Rest rest = Rest(),
+                                            Meanwhile meanwhile = Meanwhile()) {
+  if (n <= 0) {
+    meanwhile();
+    return;
+  }
   auto at = [&](int i) { return i < n ? i : n - 1; };
 #pragma unroll
   for (int u = 0; u + 1 < PF; ++u) load(u, at(u));
+  __builtin_amdgcn_sched_barrier(0);
+  meanwhile();
   __builtin_amdgcn_sched_barrier(0);
   int i = 0;
   for (; i + PF <= n; i += PF) {
