@@ -31,6 +31,7 @@
 namespace asx {
 
 constexpr int kMaxSeg = 6;
+constexpr int kMaxApart = 16;   // batches whose results lie apart
 
 struct GemmArgs {
   const void* A[kMaxSeg] = {};
@@ -48,6 +49,7 @@ struct GemmArgs {
   int M = 0, N = 0;
   void* C = nullptr;
   int64_t ldc = 0, sC = 0;
+  void* const* C_of = nullptr;  // [batch] results of a batch that lie apart (C, sC unused; bf16 256x256 kernels, no split)
   bool c_bf16 = false;          // output storage: bf16 bits or float
   void* C_lo = nullptr;         // optional rounding remainder of C
   float* C_dact = nullptr;      // optional 1 - v^2 (float)

@@ -91,11 +91,12 @@ __device__ __forceinline__ void gemm_epilogue_vec(const GemmDev& p, int Mv, AccT
   const bool to_partial = p.splits > 1;
   const int64_t ld = to_partial ? (int64_t)p.N : p.ldc;
   const int64_t origin = to_partial ? ((int64_t)z * p.M + row0) * p.N + col0
-                                    : (int64_t)batch * p.sC + (int64_t)row0 * p.ldc + col0;
-  unsigned char* cbase = to_partial ? reinterpret_cast<unsigned char*>(p.partial) : reinterpret_cast<unsigned char*>(p.C);
+                                    : (int64_t)row0 * p.ldc + col0;
+  unsigned char* cbase = to_partial ? reinterpret_cast<unsigned char*>(p.partial) : c_base(p, batch, ES);
   const __amdgpu_buffer_rsrc_t rs_c = make_rsrc(cbase + origin * ES);
-  const __amdgpu_buffer_rsrc_t rs_lo = make_rsrc(p.C_lo ? p.C_lo + origin : nullptr);
-  const __amdgpu_buffer_rsrc_t rs_da = make_rsrc(p.C_dact ? p.C_dact + origin : nullptr);
+  const int64_t second = (int64_t)batch * p.sC + origin;
+  const __amdgpu_buffer_rsrc_t rs_lo = make_rsrc(p.C_lo ? p.C_lo + second : nullptr);
+  const __amdgpu_buffer_rsrc_t rs_da = make_rsrc(p.C_dact ? p.C_dact + second : nullptr);
   const float* gate0 = p.gate ? p.gate + (int64_t)row0 * p.ldg + col0 : nullptr;   // gate and old-C reads: plain loads
   const int rows_left = Mv - row0 - vrow;                        // valid rows of C from this lane's first row on
   const bool col_in = col0 + vcol < p.n_out;                     // n_out % 4 == 0: a 4-column group is all in or all out
@@ -290,7 +291,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmDev& p, int Mv, AccT& ac
         v[c] = x * gt[c];
       }
       if constexpr (OUT_BF16) {
-        uint16_t* C = reinterpret_cast<uint16_t*>(p.C) + ci;
+        uint16_t* C = reinterpret_cast<uint16_t*>(c_base(p, batch, 2)) + (int64_t)grow * p.ldc + gcol;
         uint32_t hb[4];
         float lo[4];
 #pragma unroll
@@ -316,7 +317,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmDev& p, int Mv, AccT& ac
             }
         }
       } else {
-        float* C = reinterpret_cast<float*>(p.C) + ci;
+        float* C = reinterpret_cast<float*>(c_base(p, batch, 4)) + (int64_t)grow * p.ldc + gcol;
         if (vec) {
           if (p.accumulate) {
             const f32x4_t o4 = *reinterpret_cast<const f32x4_t*>(C);
@@ -1014,6 +1015,12 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, GemmTile tile, hipStream_t st) {
   d.C_dact = g.C_dact;
   d.ldc = g.ldc;
   d.sC = g.sC;
+  if (g.C_of && (g.C || !big_tile || g.splits != 1 || g.batch > kMaxApart || g.C_lo || g.C_dact)) return hipErrorInvalidValue;
+  bool apart_al16 = true;
+  for (int b = 0; b < kMaxApart; ++b) {
+    d.C_of[b] = g.C_of && b < g.batch ? g.C_of[b] : nullptr;
+    apart_al16 = apart_al16 && al16(d.C_of[b]);
+  }
   d.bias = reinterpret_cast<const uint16_t*>(g.bias);
   d.gate = g.gate;
   d.ldg = g.ldg;
@@ -1039,7 +1046,7 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, GemmTile tile, hipStream_t st) {
   d.n_out = padded ? (g.N + 3) & ~3 : g.N;
   // vector epilogue: every row of C / C_lo / C_dact / gate starts 16-byte aligned
   // (ldc % 4 == 0 gives 8-byte alignment for bf16 rows, which their 8-byte stores need)
-  d.vec_ok = ((g.ldc & 3) == 0) && ((g.sC & 3) == 0) && al16(g.C) && (!g.C_lo || al16(g.C_lo)) &&
+  d.vec_ok = ((g.ldc & 3) == 0) && ((g.sC & 3) == 0) && al16(g.C) && apart_al16 && (!g.C_lo || al16(g.C_lo)) &&
              (!g.C_dact || al16(g.C_dact)) && (!g.gate || (al16(g.gate) && (g.ldg & 3) == 0)) &&
              (d.n_out & 3) == 0 &&                                        // a 4-column group is all in or all out
              g.ldc < (1 << 21) && g.ldg < (1 << 21) && g.N < (1 << 21);   // 32-bit byte offsets inside a 128-row window

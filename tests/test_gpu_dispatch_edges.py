@@ -119,6 +119,16 @@ def test_lstm_wavefronts_at_block_edges(shape, dtype):
     tl.compare(inp, f, g, fo, go)
 
 
+def test_lstm_weight_gradients_of_all_layers_at_once():
+    """dW_hh of five layers in one launch (180 tiles of 256 x 256, ragged in rows and columns), dW_ih one by one."""
+    import test_gpu_lstm as tl
+    from synth_inputs import make_lstm_inputs
+    inp = make_lstm_inputs(2, 3, 16, 712, 5, seed=712, dtype="bf16")
+    f, g, _ = tl.run_gpu(inp)
+    fo, go = tl.run_oracle(inp)
+    tl.compare(inp, f, g, fo, go)
+
+
 @pytest.mark.parametrize("states", [True, False])
 @pytest.mark.parametrize("shape", [(16, 21, 648, 72, 1),       # a wide x: its product ahead of the wavefronts, ragged tiles
                                    (8, 33, 1032, 40, 3),       # with layers above it
