@@ -106,7 +106,8 @@ __host__ __device__ inline int pp_dyn_splits(int tiles, int ktiles, int smax, in
 }
 
 // Tile plan shared by workspace sizing and launching.
-enum GemmTile { kTile128 = 0, kTile256 = 1, kTile64 = 2 };   // bf16: block tile edge, i.e. the kernel
+// bf16: block tile edge, i.e. the kernel; kTileFew: the kernel for few rows (gemm_tile.hip), never the planner's own choice
+enum GemmTile { kTile128 = 0, kTile256 = 1, kTile64 = 2, kTileFew = 3 };
 struct GemmPlan {
   GemmTile tile;
   int splits;

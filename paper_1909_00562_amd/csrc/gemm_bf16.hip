@@ -1061,6 +1061,10 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, GemmTile tile, hipStream_t st) {
   d.kper = ((ktiles + g.splits - 1) / g.splits) * BK;
   if (g.splits > 1 && !g.dyn_split && (int64_t)(d.kper / BK) * (g.splits - 1) >= ktiles)
     return hipErrorInvalidValue;   // an empty split
+  if (tile == kTileFew) {
+    if (!g.a_kc || !g.b_kc || d.nz != 1 || g.M_dev || g.K_dev || d.n_out != g.N) return hipErrorInvalidValue;
+    return launch_gemm_bf16_few(d, g.c_bf16, st);
+  }
   if (tile != kTile256) return launch_gemm_bf16_tile(d, tile, g.a_kc, g.b_kc, g.c_bf16 && g.splits <= 1, st);
   // Both operands strided in the reduction index (the weight-gradient products): their global rows are
   // 512 contiguous bytes whatever the reduction width, so the ring variant's deeper prefetch is free

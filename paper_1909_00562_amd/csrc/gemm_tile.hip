@@ -22,6 +22,7 @@
 #include "gemm.h"
 #include "gemm_dev.h"
 #include "lds_limit.h"
+#include "wave_pipe.h"
 
 #include <type_traits>
 
@@ -357,6 +358,105 @@ static hipError_t launch_tile_form(const GemmDev& d, GemmTile tile, int out_bf16
   if ((int64_t)d.tiles_m * d.tiles_n * d.nz <= 256) return launch_tile_shape<4, AKC, BKC, 4>(d, out_bf16, st);
   return launch_tile_shape<4, AKC, BKC, 2>(d, out_bf16, st);
 }
+// ---- few rows ----------------------------------------------------------------------
+// 16 columns x 16 NJ rows per block, the reduction split over its eight waves (wave w takes steps w, w + 8, ...), fragments
+// straight from the operands' rows into registers, PF - 1 lines ahead; the partial tiles meet in LDS and are added in wave
+// order, and the epilogue follows.  A hundred rows and a thousand columns are a few tiles of 64 x 64: those need a split over
+// blocks to fill the chip, and a split needs a second launch that reads the partial sums back.  What bounds this one is its
+// launch and one or two memory latencies: 16 x 512 x 1536 7.4 us, 10.6 split and combined.
+// The columns of B are the rows of the matrix instruction, so that a lane holds four consecutive columns of a row of C.
+constexpr int kFewWaves = 8;
+// (by value: a choice between variables that a lambda refers to would keep them in memory)
+__device__ __forceinline__ const uint16_t* few_pick(int seg, const uint16_t* a, const uint16_t* b, const uint16_t* c) {
+  return seg == 0 ? a : seg == 1 ? b : c;
+}
+template <int NJ>
+__global__ __launch_bounds__(64 * kFewWaves) void gemm_bf16_few_kernel(GemmDev p, int out_bf16, int nseg) {
+  constexpr int PF = 4;
+  __shared__ f32x4_t red[kFewWaves * NJ * 64];   // [wave][row tile][lane]
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int q = lane >> 4, c = lane & 15;
+  // an XCD gets a contiguous run of column blocks with all their row blocks: its L2 fetches a row of B once
+  const int nbm = (p.M + 16 * NJ - 1) / (16 * NJ), nbn = (p.N + 15) / 16, per = (nbn + 7) / 8;
+  const int idx = blockIdx.x >> 3, bn = (blockIdx.x & 7) * per + idx / nbm;
+  if (bn >= nbn) return;
+  const int n0 = bn * 16, m0 = (idx % nbm) * 16 * NJ, K = p.K[0], nk = (K + 63) / 64;
+  const int col = n0 + c < p.N ? n0 + c : p.N - 1;   // columns and rows outside repeat the last one; not stored
+  const int64_t boff = (int64_t)col * p.ldb[0];
+  int64_t aoff[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) aoff[j] = (int64_t)(m0 + 16 * j + c < p.M ? m0 + 16 * j + c : p.M - 1) * p.lda[0];
+  const uint16_t *A0 = p.A[0], *A1 = p.A[1], *A2 = p.A[2], *B0 = p.B[0], *B1 = p.B[1], *B2 = p.B[2];
+  f32x4_t acc[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  // A step is a whole 128-byte line of every row, two matrix instructions: lane group q takes bytes 32 q .. 32 q + 31.
+  u32x4_t bf[PF][2], af[PF][NJ][2];
+  auto segment = [&](int step) { return (wave + step * kFewWaves >= nk) + (wave + step * kFewWaves >= 2 * nk); };
+  auto first = [&](int step) { return (wave + step * kFewWaves - segment(step) * nk) * 64; };   // reduction index of a step
+  auto load = [&](int slot, int step) {
+    const int seg = segment(step), k0 = first(step);
+    const uint16_t *A = few_pick(seg, A0, A1, A2), *B = few_pick(seg, B0, B1, B2);
+    const int k = k0 + q * 16, ko[2] = {k < K ? k : k0, k + 8 < K ? k + 8 : k0};   // past the row's end: the line's start
+    // the two halves of a line one behind the other, while it is on its way
+#pragma unroll
+    for (int h = 0; h < 2; ++h) bf[slot][h] = *reinterpret_cast<const u32x4_t*>(B + boff + ko[h]);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) af[slot][j][h] = *reinterpret_cast<const u32x4_t*>(A + aoff[j] + ko[h]);
+  };
+  auto mul = [&](int slot, int step) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const bool in = first(step) + q * 16 + h * 8 < K;   // chunks past the end: both operands cleared (0 * inf)
+      u32x4_t b = bf[slot][h];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) b[e] = in ? b[e] : 0u;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        u32x4_t a = af[slot][j][h];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[e] = in ? a[e] : 0u;
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, b), __builtin_bit_cast(bf16x8_t, a),
+                                                         acc[j], 0, 0, 0);
+      }
+    }
+  };
+  wave_reduce<PF, 2 * (NJ + 1), 2 * NJ>(own_steps<kFewWaves>(nk * nseg, wave), load, mul);
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) red[(wave * NJ + j) * 64 + lane] = acc[j];
+  __syncthreads();
+  if (wave >= NJ) return;
+  f32x4_t v = red[wave * 64 + lane];
+#pragma unroll
+  for (int w = 1; w < kFewWaves; ++w) v += red[(w * NJ + wave) * 64 + lane];
+  const int row = m0 + 16 * wave + c, ccol = n0 + 4 * q;
+  if (row >= p.M || ccol >= p.N) return;
+  if (!p.vec_ok) {
+    gs_finish_ragged(p, out_bf16, 0, 0, row, ccol, v);
+    return;
+  }
+  f32x4_t bias4 = {0.f, 0.f, 0.f, 0.f};
+  if (p.bias)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) bias4[e] = bf16_bits_to_f32(p.bias[ccol + e]);
+  gs_finish4(p, out_bf16, 0, row, ccol, v, bias4);
+}
+hipError_t launch_gemm_bf16_few(const GemmDev& d, bool out_bf16, hipStream_t st) {
+  int nseg = 0;
+  while (nseg < kMaxSeg && d.K[nseg] > 0) ++nseg;
+  if (nseg < 1 || nseg > 3 || d.splits != 1) return hipErrorInvalidValue;
+  for (int s = 1; s < nseg; ++s)
+    if (d.K[s] != d.K[0]) return hipErrorInvalidValue;
+  const int nj = d.M > 16 ? 2 : 1;
+  const int64_t nbm = (d.M + 16 * nj - 1) / (16 * nj), per = ((d.N + 15) / 16 + 7) / 8;
+  const dim3 grid((unsigned)(8 * per * nbm));
+  if (nj == 2) hipLaunchKernelGGL(gemm_bf16_few_kernel<2>, grid, dim3(64 * kFewWaves), 0, st, d, (int)out_bf16, nseg);
+  else hipLaunchKernelGGL(gemm_bf16_few_kernel<1>, grid, dim3(64 * kFewWaves), 0, st, d, (int)out_bf16, nseg);
+  return hipGetLastError();
+}
+
 hipError_t launch_gemm_bf16_tile(const GemmDev& d, GemmTile tile, bool a_kc, bool b_kc, bool out_bf16, hipStream_t st) {
   if (a_kc && b_kc) return launch_tile_form<true, true>(d, tile, out_bf16, st);
   if (a_kc && !b_kc) return launch_tile_form<true, false>(d, tile, out_bf16, st);

@@ -88,6 +88,10 @@ __global__ __launch_bounds__(256) void xent_stats_kernel(const TE* __restrict__ 
   if (rows && n >= *n_act) return;
   const int pos = rows ? rows[n] : n;
   const TE* x = logits + (int64_t)n * ldV;
+  // the target and its logit are requested ahead of the row: behind it they are two memory latencies in a chain
+  const int y = targets[pos];
+  const bool nonpad = (y != pad_id) && (y >= 0) && (y < V);
+  const float ly = ld_elem<TE>(x, nonpad ? y : 0);
   RowStat st{-INFINITY, 0.f, 0x7fffffff};   // idx: column of the first element of the vector holding the first maximum
   // one group = UNR vectors of this thread, 256 * VEC columns apart; GUARD: the group may reach past the row
   auto group = [&](int v0, auto guard) {
@@ -178,9 +182,7 @@ __global__ __launch_bounds__(256) void xent_stats_kernel(const TE* __restrict__ 
       amax = r.idx + k;
     }
     const float l = r.m + logf(r.s);
-    const int y = targets[pos];
-    const bool nonpad = (y != pad_id) && (y >= 0) && (y < V);
-    const float loss = nonpad ? l - ld_elem<TE>(x, y) : 0.f;
+    const float loss = nonpad ? l - ly : 0.f;
     lse[n] = l;
     tok_loss_ws[n] = loss;
     if (tok_loss) tok_loss[pos] = loss;
@@ -212,11 +214,19 @@ __global__ __launch_bounds__(1024) void loss_reduce_kernel(const float* __restri
   sd[tid] = acc;
   sc[tid] = cnt;
   __syncthreads();
-  for (int o = 512; o > 0; o >>= 1) {
+  for (int o = 512; o >= 64; o >>= 1) {
     if (tid < o) { sd[tid] += sd[tid + o]; sc[tid] += sc[tid + o]; }
     __syncthreads();
   }
-  if (tid == 0) { *loss_sum = (float)sd[0]; *n_tok = sc[0]; }
+  if (tid >= 64) return;
+  acc = sd[tid];
+  cnt = sc[tid];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {   // the same tree inside one wave
+    acc += __shfl_down(acc, o, 64);
+    cnt += __shfl_down(cnt, o, 64);
+  }
+  if (tid == 0) { *loss_sum = (float)acc; *n_tok = cnt; }
 }
 
 // RU rows in flight per thread; NT: 1 = streaming loads, 2 = streaming stores, 3 = both.  Measured on

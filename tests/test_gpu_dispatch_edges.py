@@ -24,6 +24,18 @@ def test_h_c_split_with_ragged_segments(shape):
     _parity(make_custom(T=T, S=S, B=B, H=H, V=V, seed=H, dtype="bf16", min_len=1, pad_prob=0.1))
 
 
+@pytest.mark.parametrize("shape", [(1, 3, 1, 136, 2003),      # one row; a reduction that ends inside a line
+                                   (2, 4, 8, 264, 2003),      # 16 rows, the last of one block form
+                                   (1, 5, 17, 328, 2003),     # 17, the first of the other; columns past a block
+                                   (4, 6, 32, 512, 2003),     # the most rows and the longest reduction
+                                   (3, 6, 43, 504, 2003)])    # one row more: tiles
+def test_h_c_of_few_rows(shape):
+    T, S, B, H, V = shape
+    inp = make_custom(T=T, S=S, B=B, H=H, V=V, seed=H, dtype="bf16", min_len=1, pad_prob=0.1)
+    inp.dropout_p, inp.dropout_seed = 0.3, 11
+    _parity(inp)
+
+
 @pytest.mark.parametrize("skip", [False, True])
 @pytest.mark.parametrize("shape", [(20, 5, 13, 60, 16003),     # 64 x 64 tiles of logits and dW_out, ragged in every direction
                                    (3, 33, 11, 121, 999),      # rows that are not 16-byte aligned: scalar loads
@@ -114,6 +126,17 @@ def test_lstm_wavefronts_at_block_edges(shape, dtype):
     if dtype == "f32" and T > 1:
         I, H = I + 1, H + 3     # widths that are no multiple of four
     inp = make_lstm_inputs(T, B, I, H, L, seed=H, dtype=dtype)
+    f, g, _ = tl.run_gpu(inp)
+    fo, go = tl.run_oracle(inp)
+    tl.compare(inp, f, g, fo, go)
+
+
+@pytest.mark.parametrize("dtype, I, H", [("bf16", 72, 1032), ("f32", 36, 1028)])
+def test_lstm_one_step_in_the_largest_blocks(dtype, I, H):
+    """The caller's weight rows in 32 units x 64 sentences (fp32: 16 x 32), rows that end inside a line."""
+    import test_gpu_lstm as tl
+    from synth_inputs import make_lstm_inputs
+    inp = make_lstm_inputs(1, 385, I, H, 2, seed=H, dtype=dtype)
     f, g, _ = tl.run_gpu(inp)
     fo, go = tl.run_oracle(inp)
     tl.compare(inp, f, g, fo, go)
