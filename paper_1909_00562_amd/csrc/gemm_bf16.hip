@@ -1016,7 +1016,11 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, GemmTile tile, hipStream_t st) {
   d.ldc = g.ldc;
   d.sC = g.sC;
   if (g.C_of && (g.C || !big_tile || g.splits != 1 || g.batch > kMaxApart || g.C_lo || g.C_dact)) return hipErrorInvalidValue;
-  bool apart_al16 = true;
+  if (g.C_second && (g.batch != 2 || tile != kTile64 || !g.a_kc || g.b_kc || g.splits != 1 || !g.c_bf16 || g.sC || g.bias || g.act_tanh ||
+                     g.gate || g.drop_thr || g.accumulate || g.C_dact))
+    return hipErrorInvalidValue;
+  d.C_second = g.C_second;
+  bool apart_al16 = !g.C_second || al16(g.C_second);
   for (int b = 0; b < kMaxApart; ++b) {
     d.C_of[b] = g.C_of && b < g.batch ? g.C_of[b] : nullptr;
     apart_al16 = apart_al16 && al16(d.C_of[b]);
@@ -1050,6 +1054,7 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, GemmTile tile, hipStream_t st) {
              (!g.C_dact || al16(g.C_dact)) && (!g.gate || (al16(g.gate) && (g.ldg & 3) == 0)) &&
              (d.n_out & 3) == 0 &&                                        // a 4-column group is all in or all out
              g.ldc < (1 << 21) && g.ldg < (1 << 21) && g.N < (1 << 21);   // 32-bit byte offsets inside a 128-row window
+  if (g.C_second && !d.vec_ok) return hipErrorInvalidValue;
   const int bm = tile == kTile256 ? 256 : tile == kTile128 ? 128 : 64;
   d.tiles_m = (g.M + bm - 1) / bm;
   d.tiles_n = (g.N + bm - 1) / bm;

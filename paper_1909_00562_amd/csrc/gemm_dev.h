@@ -19,6 +19,7 @@ struct GemmDev {
   uint16_t* C_lo;
   float* C_dact;
   int64_t ldc, sC;
+  float* C_second;         // batch of two: where the product of segment 0 alone goes (or null)
   void* C_of[kMaxApart];   // results of a batch that lie apart (C is then null)
   const uint16_t* bias;
   const float* gate;

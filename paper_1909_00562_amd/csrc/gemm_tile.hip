@@ -172,11 +172,14 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_tile_kernel(GemmDev p, int o
   const int in_g = pid - gid * 8 * p.tiles_n;
   const int m0 = (first_m + in_g % gm) * BM, n0 = (in_g / gm) * BM;
   const int z = blockIdx.z, batch = z / p.splits, split = z - batch * p.splits;
+  constexpr bool kSecond = TW == 2 && AKC && !BKC;               // (compiled in where it is used)
+  const bool second = kSecond && p.C_second && batch == 1;       // segment 0 alone
+  const int nseg = second ? 1 : kMaxSeg;
 
   // reduction tiles of this block: [t0, t1) of the sequence that runs through the segments one after the other
   int nk = 0, seg = 0, skip = 0;
 #pragma unroll
-  for (int s = 0; s < kMaxSeg; ++s) nk += ((s == 0 ? K0 : p.K[s]) + BK - 1) / BK;
+  for (int s = 0; s < kMaxSeg; ++s) nk += s < nseg ? ((s == 0 ? K0 : p.K[s]) + BK - 1) / BK : 0;
   if (p.splits > 1) {
     const int per = p.K_dev ? (nk + p.splits - 1) / p.splits : p.kper / BK;
     skip = split * per;
@@ -197,13 +200,13 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_tile_kernel(GemmDev p, int o
   const uint16_t* cB = p.B[seg] + (int64_t)batch * p.sB[seg] + offB + skip * stepB;
   auto issue = [&](int stage) {   // the tile under the cursor
     if (k_left <= 0) {            // on to the next segment, if there is one
-      do { ++seg; } while (seg < kMaxSeg && p.K[seg] <= 0);
-      if (seg < kMaxSeg) {
+      do { ++seg; } while (seg < nseg && p.K[seg] <= 0);
+      if (seg < nseg) {
         cA = p.A[seg] + (int64_t)batch * p.sA[seg] + offA;
         cB = p.B[seg] + (int64_t)batch * p.sB[seg] + offB;
         k_left = p.K[seg];
       } else {
-        seg = kMaxSeg - 1;        // all loads below are out of range
+        seg = nseg - 1;           // all loads below are out of range
       }
     }
     const __amdgpu_buffer_rsrc_t ra = make_rsrc(cA), rb = make_rsrc(cB);
@@ -280,7 +283,8 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_tile_kernel(GemmDev p, int o
   constexpr int VPR = BM / 4;                 // groups of four columns per row
   const int col = n0 + (tid % VPR) * 4;
   const bool fuse = p.splits <= 1;
-  const bool plain = p.vec_ok && (!fuse || (!p.act_tanh && !p.drop_thr && !p.gate && !p.C_lo && !p.C_dact));
+  if (second) out_bf16 = 0;
+  const bool plain = p.vec_ok && (!fuse || second || (!p.act_tanh && !p.drop_thr && !p.gate && !p.C_lo && !p.C_dact));
   f32x4_t bias4 = {0.f, 0.f, 0.f, 0.f};
   if (fuse && p.bias)
 #pragma unroll
@@ -320,7 +324,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_tile_kernel(GemmDev p, int o
             const u32x2_t o = {pack_bf16(v[u][0], v[u][1]), pack_bf16(v[u][2], v[u][3])};
             *reinterpret_cast<u32x2_t*>(reinterpret_cast<uint16_t*>(p.C) + ci) = o;
           } else {
-            float* C = reinterpret_cast<float*>(p.C) + ci;
+            float* C = (second ? p.C_second : reinterpret_cast<float*>(p.C)) + ci;
             if (p.accumulate) v[u] += *reinterpret_cast<const f32x4_t*>(C);
             *reinterpret_cast<f32x4_t*>(C) = v[u];
           }

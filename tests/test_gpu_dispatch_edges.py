@@ -193,3 +193,12 @@ def test_lstm_wide_input_does_not_see_its_batch():
     g, _, _ = tl.run_gpu(part)
     assert np.array_equal(g["y"], f["y"][:, 32:48])
     assert np.array_equal(g["hT"], f["hT"][:, 32:48]) and np.array_equal(g["cT"], f["cT"][:, 32:48])
+
+
+@pytest.mark.parametrize("shape", [(1, 9, 3, 8, 643),          # one reduction tile, one row tile
+                                   (1, 7, 65, 136, 643),       # a row past a tile, a reduction of two tiles and a bit
+                                   (6, 20, 43, 520, 2003)])    # ragged in every direction
+def test_both_gradients_through_w_c_in_one_launch(shape):
+    """dC = dz W_c[:, :H] with dz as value and remainder (bf16 pair out), dz W_c[:, H:] of the value alone (float out)."""
+    T, S, B, H, V = shape
+    _parity(make_custom(T=T, S=S, B=B, H=H, V=V, seed=V + H, dtype="bf16", min_len=1, pad_prob=0.1))
