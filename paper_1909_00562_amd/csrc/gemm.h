@@ -49,7 +49,8 @@ struct GemmArgs {
   int M = 0, N = 0;
   void* C = nullptr;
   int64_t ldc = 0, sC = 0;
-  void* const* C_of = nullptr;  // [batch] results of a batch that lie apart (C, sC unused; bf16 256x256 kernels, no split)
+  void* const* C_of = nullptr;  // [batch] results of a batch that lie apart (C, sC unused; bf16 256x256 kernel of strided operands,
+                                // float results in whole vectors, no split)
   float* C_second = nullptr;    // batch of two: the second product is of segment 0 alone (its batch strides) and goes here, as
                                 // float with C's ldc and no epilogue (64x64 kernel, A contiguous, B strided, bf16 C, no split)
   bool c_bf16 = false;          // output storage: bf16 bits or float

@@ -79,7 +79,8 @@ __device__ __forceinline__ int stage_read_off(int it, int vrow, int vcol) {
 // loads) go through buffer resources that start at the wave tile's first element, so
 // the row part of an address is a scalar offset, the lane part one register, and rows
 // beyond M are dropped by pointing the lane offset outside the resource instead of branching.
-template <int TM, int TN, bool OUT_BF16, bool DROP, int CH, int EP_LD, bool MI16, typename AccT>
+// APART: the results of a batch lie apart (C_of).
+template <int TM, int TN, bool OUT_BF16, bool DROP, int CH, int EP_LD, bool MI16, bool APART, typename AccT>
 __device__ __forceinline__ void gemm_epilogue_vec(const GemmDev& p, int Mv, AccT& acc,
                                                   unsigned char* region, int lane, int row0, int col0, int batch,
                                                   int z) {
@@ -91,12 +92,13 @@ __device__ __forceinline__ void gemm_epilogue_vec(const GemmDev& p, int Mv, AccT
   const bool to_partial = p.splits > 1;
   const int64_t ld = to_partial ? (int64_t)p.N : p.ldc;
   const int64_t origin = to_partial ? ((int64_t)z * p.M + row0) * p.N + col0
-                                    : (int64_t)row0 * p.ldc + col0;
-  unsigned char* cbase = to_partial ? reinterpret_cast<unsigned char*>(p.partial) : c_base(p, batch, ES);
+                                    : (int64_t)batch * p.sC + (int64_t)row0 * p.ldc + col0;
+  unsigned char* cbase = APART        ? reinterpret_cast<unsigned char*>(p.C_of[batch])   // (no split, sC = 0)
+                         : to_partial ? reinterpret_cast<unsigned char*>(p.partial)
+                                      : reinterpret_cast<unsigned char*>(p.C);
   const __amdgpu_buffer_rsrc_t rs_c = make_rsrc(cbase + origin * ES);
-  const int64_t second = (int64_t)batch * p.sC + origin;
-  const __amdgpu_buffer_rsrc_t rs_lo = make_rsrc(p.C_lo ? p.C_lo + second : nullptr);
-  const __amdgpu_buffer_rsrc_t rs_da = make_rsrc(p.C_dact ? p.C_dact + second : nullptr);
+  const __amdgpu_buffer_rsrc_t rs_lo = make_rsrc(p.C_lo ? p.C_lo + origin : nullptr);
+  const __amdgpu_buffer_rsrc_t rs_da = make_rsrc(p.C_dact ? p.C_dact + origin : nullptr);
   const float* gate0 = p.gate ? p.gate + (int64_t)row0 * p.ldg + col0 : nullptr;   // gate and old-C reads: plain loads
   const int rows_left = Mv - row0 - vrow;                        // valid rows of C from this lane's first row on
   const bool col_in = col0 + vcol < p.n_out;                     // n_out % 4 == 0: a 4-column group is all in or all out
@@ -220,13 +222,13 @@ __device__ __forceinline__ void gemm_epilogue_vec(const GemmDev& p, int Mv, AccT
 }
 
 template <int TM, int TN, bool OUT_BF16, bool VEC, bool DROP, int CH = 32, int EP_LD = 72, bool MI16 = false,
-          typename AccT>
+          bool APART = false, typename AccT>
 __device__ __forceinline__ void gemm_epilogue(const GemmDev& p, int Mv, AccT& acc,
                                               unsigned char* region, int lane, int row0, int col0, int batch, int z) {
   static_assert(TN == (MI16 ? 4 : 2), "64-column wave tiles");
   static_assert(CH == 32 || CH == 16, "chunk of one or half an MFMA tile");
   if constexpr (VEC) {
-    gemm_epilogue_vec<TM, TN, OUT_BF16, DROP, CH, EP_LD, MI16>(p, Mv, acc, region, lane, row0, col0, batch, z);
+    gemm_epilogue_vec<TM, TN, OUT_BF16, DROP, CH, EP_LD, MI16, APART>(p, Mv, acc, region, lane, row0, col0, batch, z);
     return;
   }
   constexpr int WAIT_LGKM_ONLY = 0xC07F;   // leaves global loads in flight
@@ -291,7 +293,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmDev& p, int Mv, AccT& ac
         v[c] = x * gt[c];
       }
       if constexpr (OUT_BF16) {
-        uint16_t* C = reinterpret_cast<uint16_t*>(c_base(p, batch, 2)) + (int64_t)grow * p.ldc + gcol;
+        uint16_t* C = reinterpret_cast<uint16_t*>(p.C) + ci;
         uint32_t hb[4];
         float lo[4];
 #pragma unroll
@@ -317,7 +319,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmDev& p, int Mv, AccT& ac
             }
         }
       } else {
-        float* C = reinterpret_cast<float*>(c_base(p, batch, 4)) + (int64_t)grow * p.ldc + gcol;
+        float* C = reinterpret_cast<float*>(p.C) + ci;
         if (vec) {
           if (p.accumulate) {
             const f32x4_t o4 = *reinterpret_cast<const f32x4_t*>(C);
@@ -742,7 +744,7 @@ __device__ __forceinline__ uint32_t ring_frag_base(int row0, int lane) {
   }
 }
 
-template <bool AKC, bool BKC, bool OUT_BF16, bool VEC, bool DROP>
+template <bool AKC, bool BKC, bool OUT_BF16, bool VEC, bool DROP, bool APART>
 __global__ __launch_bounds__(512) void gemm_bf16_ring_kernel(GemmDev p, int work_total) {
   constexpr int BM = 256, BN = 256, WGN = 4;
   constexpr int WM = 128, WN = 64, TM = 4, TN = 2;
@@ -924,16 +926,16 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring_kernel(GemmDev p, int work
       }
     }
     // item done: write it out while the next item's first sub-tiles are already in flight
-    gemm_epilogue<TM, TN, OUT_BF16, VEC, DROP, 16, 64>(p, Mv, acc, smem + RING_EPI_OFF + wave * 4096, lane,
+    gemm_epilogue<TM, TN, OUT_BF16, VEC, DROP, 16, 64, false, APART>(p, Mv, acc, smem + RING_EPI_OFF + wave * 4096, lane,
                                                        it.m0 + wm * WM, it.n0 + wn * WN, it.batch, it.z);
     zero_acc();
   }
 }
 
-template <bool AKC, bool BKC, bool OUT_BF16, bool VEC>
+template <bool AKC, bool BKC, bool OUT_BF16, bool VEC, bool APART = false>
 static hipError_t launch_ring(const GemmDev& d, int batch, hipStream_t st) {
   constexpr int smem = RING_SMEM;
-  auto kfn = gemm_bf16_ring_kernel<AKC, BKC, OUT_BF16, VEC, false>;
+  auto kfn = gemm_bf16_ring_kernel<AKC, BKC, OUT_BF16, VEC, false, APART>;
   static LdsLimit limit;
   const hipError_t e = limit.raise(reinterpret_cast<const void*>(kfn), smem);
   if (e != hipSuccess) return e;
@@ -946,6 +948,8 @@ template <bool AKC, bool BKC>
 static hipError_t launch_ring_oriented(const GemmArgs& g, const GemmDev& d, hipStream_t st) {
   const bool obf = g.c_bf16 && g.splits <= 1;
   const bool vec = d.vec_ok != 0;
+  // (an instance of its own: with the choice made in the kernel all its products were 2 to 4 % slower)
+  if (g.C_of) return vec && !obf ? launch_ring<AKC, BKC, false, true, true>(d, g.batch, st) : hipErrorInvalidValue;
   if (obf) return vec ? launch_ring<AKC, BKC, true, true>(d, g.batch, st) : launch_ring<AKC, BKC, true, false>(d, g.batch, st);
   return vec ? launch_ring<AKC, BKC, false, true>(d, g.batch, st) : launch_ring<AKC, BKC, false, false>(d, g.batch, st);
 }
@@ -1015,7 +1019,7 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, GemmTile tile, hipStream_t st) {
   d.C_dact = g.C_dact;
   d.ldc = g.ldc;
   d.sC = g.sC;
-  if (g.C_of && (g.C || !big_tile || g.splits != 1 || g.batch > kMaxApart || g.C_lo || g.C_dact)) return hipErrorInvalidValue;
+  if (g.C_of && (g.C || g.sC || !big_tile || g.a_kc || g.b_kc || g.accumulate || g.splits != 1 || g.batch > kMaxApart || g.C_lo || g.C_dact)) return hipErrorInvalidValue;
   if (g.C_second && (g.batch != 2 || tile != kTile64 || !g.a_kc || g.b_kc || g.splits != 1 || !g.c_bf16 || g.sC || g.bias || g.act_tanh ||
                      g.gate || g.drop_thr || g.accumulate || g.C_dact))
     return hipErrorInvalidValue;

@@ -40,12 +40,6 @@ struct GemmDev {
   int dyn_split;          // splits is the bound of a split chosen in the kernel from the row count (pp kernel)
 };
 
-// first element of a batch's result, es bytes each
-__device__ __forceinline__ unsigned char* c_base(const GemmDev& p, int batch, int es) {
-  return p.C ? reinterpret_cast<unsigned char*>(p.C) + (int64_t)batch * p.sC * es
-             : reinterpret_cast<unsigned char*>(p.C_of[batch]);
-}
-
 // size made by an earlier kernel of the stream, clamped to the bound the launch was sized for
 __device__ __forceinline__ int dev_bound(const int32_t* count, int bound) {
   if (!count) return bound;

@@ -88,10 +88,6 @@ __global__ __launch_bounds__(256) void xent_stats_kernel(const TE* __restrict__ 
   if (rows && n >= *n_act) return;
   const int pos = rows ? rows[n] : n;
   const TE* x = logits + (int64_t)n * ldV;
-  // the target and its logit are requested ahead of the row: behind it they are two memory latencies in a chain
-  const int y = targets[pos];
-  const bool nonpad = (y != pad_id) && (y >= 0) && (y < V);
-  const float ly = ld_elem<TE>(x, nonpad ? y : 0);
   RowStat st{-INFINITY, 0.f, 0x7fffffff};   // idx: column of the first element of the vector holding the first maximum
   // one group = UNR vectors of this thread, 256 * VEC columns apart; GUARD: the group may reach past the row
   auto group = [&](int v0, auto guard) {
@@ -182,7 +178,9 @@ __global__ __launch_bounds__(256) void xent_stats_kernel(const TE* __restrict__ 
       amax = r.idx + k;
     }
     const float l = r.m + logf(r.s);
-    const float loss = nonpad ? l - ly : 0.f;
+    const int y = targets[pos];
+    const bool nonpad = (y != pad_id) && (y >= 0) && (y < V);
+    const float loss = nonpad ? l - ld_elem<TE>(x, y) : 0.f;
     lse[n] = l;
     tok_loss_ws[n] = loss;
     if (tok_loss) tok_loss[pos] = loss;
