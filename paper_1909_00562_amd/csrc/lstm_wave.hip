@@ -220,7 +220,10 @@ static inline unsigned ls_grid(int64_t nslices, int64_t nbt) { return (unsigned)
 // ---- forward ---------------------------------------------------------------------
 // Block: 16 * NI gate rows (4 * NI hidden units) x 16 * NJ sentences.  Tile 4 g + ii of a block, row rho: unit
 // u0 + 16 g + 4 q + ii, gate r, (q, r) = the lane group and register that hold row rho.  ROWS: weights are read as the
-// caller's rows (64 bytes of a row per load), each used once by the call.  APART: layer 0 finds the input product and the
+// caller's rows (64 bytes of a row per load), each used once by the call; steps of the reduction, their waves and the order
+// inside a step are those of the tiles, so that a step by itself gives the bits it has in a sequence (whole lines of a row
+// per step: 4 x 1024 units x 128 sentences 114.7 us for 116.9, 4 x 192 units x 116 sentences 75.5 for 73.8, and other bits).
+// APART: layer 0 finds the input product and the
 // bias in the gates' place.
 template <typename TE, int NI, int NJ, int PF, bool ROWS, bool VEC, bool APART>
 __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d, int l_lo, int n_layers) {
@@ -275,10 +278,7 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
   // mask instead, 50 x 128 x 512 units x 4 took 699 us, 681 so).
   constexpr bool TWO = M::kPair && NI * NJ >= 32;
   const bool apart = APART && l == 0;
-  // ROWS: a step is a whole 128-byte line of every weight row, two matrix instructions' worth (HS); lane group q takes bytes
-  // 32 q .. 32 q + 31 of it, the first 16 of them in the first instruction.
-  constexpr int HS = ROWS ? 2 : 1;
-  const int n0 = (H + HS * KST - 1) / (HS * KST), n1 = apart ? 0 : (Kin + HS * KST - 1) / (HS * KST);
+  const int n0 = (H + KST - 1) / KST, n1 = apart ? 0 : (Kin + KST - 1) / KST;
   const int64_t cstep = (int64_t)nct * kLsTile;
   const char* h_hi = p.hF_hi + (2 * l + (t & 1)) * p.h_stride;
   const char* h_lo = M::kPair ? p.hF_lo + (2 * l + (t & 1)) * p.h_stride : nullptr;
@@ -302,90 +302,53 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
       wrow[i] = M::r_of_row(c) * H + (unit < H ? unit : H - 1);   // rows past the layer repeat the last unit; not stored
     }
   }
-  ls_u32x4_t wf[PF][HS][NI], hf[PF][HS][NJ], lf[PF][HS][M::kPair ? NJ : 1];
+  ls_u32x4_t wf[PF][NI], hf[PF][NJ], lf[PF][M::kPair ? NJ : 1];
   auto load = [&](int slot, int step, bool rest = true) {   // rest: the remainders too
     const int s = wave + step * LS_KS;
     const bool in = s >= n0;
     const int k = in ? s - n0 : s;
     if constexpr (ROWS) {
-      const int K = in ? Kin : H;
-      const char* wb = (in ? w1 : w0) + (int64_t)k * (HS * 64);
-      const char* hb = (in ? i_hi : h_hi) + k * HS * cstep;
-      // (an input without remainder: anything inside)
-      const char* lb = !M::kPair ? nullptr : in ? (no_rest ? hb : i_lo + k * HS * cstep) : h_lo + k * HS * cstep;
-      uint32_t woff[HS], off[HS];
-#pragma unroll
-      for (int hs = 0; hs < HS; ++hs) {
-        const int ch = (k * HS * 4 + q * HS + hs) * V < K ? q * HS + hs : 0;   // past the row's end: the line's start
-        woff[hs] = ch * 16;
-        off[hs] = (uint32_t)(ch >> 2) * (uint32_t)cstep + (uint32_t)((ch & 3) * 256 + c * 16);
-      }
-      // the two halves of a line one behind the other, while it is on its way
+      const int K = in ? Kin : H, kk = k * KST + q * V;
+      const char* wb = (in ? w1 : w0) + (int64_t)(kk < K ? kk : 0) * sizeof(TE);
 #pragma unroll
       for (int i = 0; i < NI; ++i)
-#pragma unroll
-        for (int hs = 0; hs < HS; ++hs)
-          wf[slot][hs][i] = *reinterpret_cast<const ls_u32x4_t*>(wb + (int64_t)wrow[i] * K * sizeof(TE) + woff[hs]);
-#pragma unroll
-      for (int hs = 0; hs < HS; ++hs) {
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) hf[slot][hs][j] = ls_frag(hb + ctoff[j], off[hs]);
-        if (M::kPair && rest) {
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) lf[slot][hs][j] = ls_frag(lb + ctoff[j], off[hs]);
-        }
-      }
+        wf[slot][i] = *reinterpret_cast<const ls_u32x4_t*>(wb + (int64_t)wrow[i] * K * sizeof(TE));
     } else {
       const char* wb = (in ? w1 : w0) + k * (4 * kLsTile);
       const int64_t group = (int64_t)(in ? n1 : n0) * (4 * kLsTile);
 #pragma unroll
       for (int i = 0; i < NI; ++i)
-        wf[slot][0][i] = ls_frag(wb + (i / 4) * group + (i % 4) * kLsTile, lane16);
-      const char* hb = (in ? i_hi : h_hi) + k * cstep;
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) hf[slot][0][j] = ls_frag(hb + ctoff[j], lane16);
-      if (M::kPair && rest) {
-        const char* lb = in ? i_lo + k * lstep1 : h_lo + k * cstep;
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) lf[slot][0][j] = ls_frag(lb + ctoff[j], lane16);
-      }
+        wf[slot][i] = ls_frag(wb + (i / 4) * group + (i % 4) * kLsTile, lane16);
     }
-  };
-  auto mul_rest = [&](int slot) {
+    const char* hb = (in ? i_hi : h_hi) + k * cstep;
 #pragma unroll
-    for (int hs = 0; hs < HS; ++hs)
+    for (int j = 0; j < NJ; ++j) hf[slot][j] = ls_frag(hb + ctoff[j], lane16);
+    if (M::kPair && rest) {
+      const char* lb = in ? i_lo + k * lstep1 : h_lo + k * cstep;
 #pragma unroll
-      for (int i = 0; i < NI; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) M::mma(acc[i][j], wf[slot][hs][i], lf[slot][hs][j]);
+      for (int j = 0; j < NJ; ++j) lf[slot][j] = ls_frag(lb + ctoff[j], lane16);
+    }
   };
   auto mul = [&](int slot, int step, bool rest = true) {
     const int s = wave + step * LS_KS;
-    if constexpr (ROWS) {   // chunks past a row's end: both operands cleared
-      const int K = s >= n0 ? Kin : H;
-#pragma unroll
-      for (int hs = 0; hs < HS; ++hs) {
-        const bool ok = ((s >= n0 ? s - n0 : s) * HS * 4 + q * HS + hs) * V < K;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-#pragma unroll
-          for (int i = 0; i < NI; ++i) wf[slot][hs][i][e] = ok ? wf[slot][hs][i][e] : 0u;
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) {
-            hf[slot][hs][j][e] = ok ? hf[slot][hs][j][e] : 0u;
-            if (M::kPair && rest) lf[slot][hs][j][e] = ok ? lf[slot][hs][j][e] : 0u;
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int hs = 0; hs < HS; ++hs)
+    if constexpr (ROWS) {   // chunks past a row's end were read from its start
+      const int K = s >= n0 ? Kin : H, kk = (s >= n0 ? s - n0 : s) * KST + q * V;
 #pragma unroll
       for (int i = 0; i < NI; ++i)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) M::mma(acc[i][j], wf[slot][hs][i], hf[slot][hs][j]);
+        for (int e = 0; e < 4; ++e) wf[slot][i][e] = kk < K ? wf[slot][i][e] : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) M::mma(acc[i][j], wf[slot][i], hf[slot][j]);
     if constexpr (M::kPair) {   // (a plain condition cost the fp32 wavefronts 0.5 us in copies of accumulators)
-      if (rest) mul_rest(slot);
+      if (rest) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) M::mma(acc[i][j], wf[slot][i], lf[slot][j]);
+      }
     }
   };
   // while the first fragments are on their way: the dropout multipliers of the cells
@@ -400,24 +363,27 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
                                 (uint64_t)(u0 + 16 * g + 4 * q), p.drop_seed, p.drop_thr, p.drop_scale);
     }
   };
-  constexpr int NP = M::kPair ? 2 : 1, NM = HS * (M::kPair ? 2 * NI * NJ : 4 * NI * NJ);
+  constexpr int NP = M::kPair ? 2 : 1, NM = M::kPair ? 2 * NI * NJ : 4 * NI * NJ;
   const int own = own_steps<LS_KS>(n0 + n1, wave);
   if constexpr (TWO) {
     const int own0 = l == 0 ? own_steps<LS_KS>(n0, wave) : own;
-    wave_reduce<PF, HS * (NI + NP * NJ), NM>(own0, load, mul, NoRest(), masks);
-    wave_reduce<PF, HS * (NI + NJ), NM / 2>(
+    wave_reduce<PF, NI + NP * NJ, NM>(own0, load, mul, NoRest(), masks);
+    wave_reduce<PF, NI + NJ, NM / 2>(
         own - own0, [&](int slot, int i) { load(slot, own0 + i, false); },
         [&](int slot, int i) { mul(slot, own0 + i, false); });
   } else if constexpr (M::kPair && !APART) {
-    wave_reduce<PF, HS * (NI + NP * NJ), NM / 2>(
+    wave_reduce<PF, NI + NP * NJ, NM / 2>(
         own, load, [&](int slot, int i) { mul(slot, i, false); },
         [&](int slot, int i) {
           if (l == 0 && wave + i * LS_KS >= n0) return;
-          mul_rest(slot);
+#pragma unroll
+          for (int ii = 0; ii < NI; ++ii)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) M::mma(acc[ii][j], wf[slot][ii], lf[slot][j]);
         },
         masks);
   } else {
-    wave_reduce<PF, HS * (NI + NP * NJ), NM>(own, load, mul, NoRest(), masks);
+    wave_reduce<PF, NI + NP * NJ, NM>(own, load, mul, NoRest(), masks);
   }
 
 #pragma unroll
@@ -972,19 +938,18 @@ template <typename TE> hipError_t launch_ls_wave_fwd(const LsFwd& p, int d, hipS
   const int nl = l_hi - l_lo + 1;
   if (nl < 1) return hipErrorInvalidValue;
   const int64_t b64 = (p.B + 63) / 64, b32 = (p.B + 31) / 32;
-  // The caller's rows: whole lines two or three steps ahead.  A decoder step of 4 x 1024 units x 128 sentences with one / two /
-  // three lines ahead 120.9 / 114.7 / 122.2 us (half lines five ahead 116.9), of 512 units x 1 sentence 36.8 / 37.8 / 36.4
-  // (38.9).
+  // The caller's rows come from memory, not from the caches: more steps in flight (one step, 4 x 1024 units x 128
+  // sentences, with the other changes to the cells: 72.1 us with four, 68.5 with six, 75.4 with eight).
   // The largest block that still gives most compute units one: larger blocks load less per output (128 gate rows x 64
   // sentences: 512 bytes per reduction index for 8192 outputs).  1024 units x 128 sentences, 64 x 32 blocks against 128 x 64:
   // three layers 27.5 us (768 blocks) and 28.0 (192), four 34.0 (1024) and 29.4 (256).
   if constexpr (LsMma<TE>::kPair) {
-    if (nl * ((p.H + 31) / 32) * b64 >= 192) return ls_fwd_shape<TE, 8, 4, 3, 2>(p, d, l_lo, nl, st);
-    if (nl * ((p.H + 15) / 16) * b32 >= 192) return ls_fwd_shape<TE, 4, 2, 4, 3>(p, d, l_lo, nl, st);
-    return ls_fwd_shape<TE, 4, 1, 4, 4>(p, d, l_lo, nl, st);
+    if (nl * ((p.H + 31) / 32) * b64 >= 192) return ls_fwd_shape<TE, 8, 4, 3>(p, d, l_lo, nl, st);
+    if (nl * ((p.H + 15) / 16) * b32 >= 192) return ls_fwd_shape<TE, 4, 2, 4, 6>(p, d, l_lo, nl, st);
+    return ls_fwd_shape<TE, 4, 1, 4, 6>(p, d, l_lo, nl, st);
   } else {
-    if (nl * ((p.H + 15) / 16) * b32 >= 512) return ls_fwd_shape<TE, 4, 2, 4, 3>(p, d, l_lo, nl, st);
-    return ls_fwd_shape<TE, 4, 1, 4, 3>(p, d, l_lo, nl, st);
+    if (nl * ((p.H + 15) / 16) * b32 >= 512) return ls_fwd_shape<TE, 4, 2, 4>(p, d, l_lo, nl, st);
+    return ls_fwd_shape<TE, 4, 1, 4>(p, d, l_lo, nl, st);
   }
 }
 

@@ -112,6 +112,28 @@ def test_lstm_two_runs_are_bit_identical():
             assert np.array_equal(g1[k][l], g2[k][l]), (k, l)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(3, 7, 24, 40, 3),         # T, B, I, H, L: reductions of one and two steps
+                                   (3, 97, 72, 1032, 2),      # 16 units x 32 sentences at one step
+                                   (2, 385, 72, 1032, 1),     # 32 x 64
+                                   (4, 16, 256, 512, 2)])     # 16 x 16
+def test_lstm_one_step_at_a_time_gives_the_bits_of_the_sequence(shape, dtype):
+    """A decoder that advances the stack word by word from the states it got back follows the training pass exactly: one
+    step reads the caller's weight rows, several read tiles of them, and both add in the same order."""
+    T, B, I, H, L = shape
+    inp = make_lstm_inputs(T, B, I, H, L, seed=H + B, dtype=dtype)
+    inp.lengths[:] = T
+    f, _, _ = run_gpu(inp)
+    one = make_lstm_inputs(T, B, I, H, L, seed=H + B, dtype=dtype)
+    one.T, one.lengths = 1, np.ones_like(inp.lengths)
+    for t in range(T):
+        one.x, one.dy = inp.x[t:t + 1].copy(), inp.dy[t:t + 1].copy()
+        g, _, _ = run_gpu(one)
+        assert np.array_equal(g["y"][0], f["y"][t]), t
+        one.h0, one.c0 = g["hT"], g["cT"]
+    assert np.array_equal(one.h0, f["hT"]) and np.array_equal(one.c0, f["cT"])
+
+
 def test_lstm_paper_size_sixteen_sentences():
     """Table 2's model (embedding 512, hidden 1024, depth 4) at 50 steps, a batch of 16 sentences:
     everything, including the weight gradients, against the oracle."""
