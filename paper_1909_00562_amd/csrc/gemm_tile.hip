@@ -150,8 +150,8 @@ __device__ __forceinline__ void gs_finish_ragged(const GemmDev& p, int out_bf16,
   }
 }
 
-template <int TW, bool AKC, bool BKC, int NST>
-__global__ __launch_bounds__(256, 2) void gemm_bf16_tile_kernel(GemmDev p, int out_bf16) {
+template <int TW, bool AKC, bool BKC, int NST, bool LACED>
+__global__ __launch_bounds__(256, LACED ? 2 : 1) void gemm_bf16_tile_kernel(GemmDev p, int out_bf16) {
   constexpr int BM = 32 * TW, TILE = BM * ROWB, STAGE = 2 * TILE;   // square block tile; bytes of an operand tile, a stage
   constexpr int NL = TW, LD = BM + 4;                               // loads per wave, operand and tile; staging row (floats)
   static_assert((NST & (NST - 1)) == 0 && NST * STAGE >= 64 * LD * 4, "ring of a power of two; write-out staging");
@@ -233,11 +233,13 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_tile_kernel(GemmDev p, int o
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
 
-  // Two sets of fragments, one per half (32 reduction elements) of a tile: the reads of a half run between the matrix
-  // instructions of the half before it.  s_waitcnt vmcnt: 2 NL loads per wave and tile, all but NST - 2 (ahead of the first
-  // barrier NST - 1) tiles have landed.
+  // Two sets of fragments, one per half (32 reduction elements) of a tile.  LACED: the reads of a half run between the matrix
+  // instructions of the half before it; else all reads of a tile come first and the other blocks of the compute unit run
+  // meanwhile.  s_waitcnt vmcnt: 2 NL loads per wave and tile, all but NST - 2 (LACED, ahead of the first barrier: NST - 1)
+  // tiles have landed.  The sums are the same.
   constexpr int kFly = 2 * NL * (NST - 2), kFly0 = 2 * NL * (NST - 1);
-  constexpr int kWaitNext = (kFly & 15) | ((kFly >> 4) << 14) | 0x0070, kWaitFirst = (kFly0 & 15) | ((kFly0 >> 4) << 14) | 0x0f70;
+  constexpr int kWaitNext = (kFly & 15) | ((kFly >> 4) << 14) | 0x0070, kWaitOldest = kWaitNext | 0x0f00;
+  constexpr int kWaitFirst = (kFly0 & 15) | ((kFly0 >> 4) << 14) | 0x0f70;
   bf16x8_t a[2][TW], b[2][TW];
   auto read = [&](int stage, int ks, int i) {
     const unsigned char* as = smem + stage * STAGE;
@@ -248,31 +250,51 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_tile_kernel(GemmDev p, int o
 #pragma unroll
     for (int j = 0; j < TW; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks][i], b[ks][j], acc[i][j], 0, 0, 0);
   };
-  for (int t = 0; t < NST; ++t) issue(t);
-  __builtin_amdgcn_s_waitcnt(kWaitFirst);
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (LACED) {
+    for (int t = 0; t < NST; ++t) issue(t);
+    __builtin_amdgcn_s_waitcnt(kWaitFirst);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int i = 0; i < TW; ++i) read(0, 0, i);
-  for (int t = 0; t < nk; ++t) {
-    const int cur = t & (NST - 1);
+    for (int i = 0; i < TW; ++i) read(0, 0, i);
+    for (int t = 0; t < nk; ++t) {
+      const int cur = t & (NST - 1);
 #pragma unroll
-    for (int i = 0; i < TW; ++i) {
-      read(cur, 1, i);
-      mul(0, i);
+      for (int i = 0; i < TW; ++i) {
+        read(cur, 1, i);
+        mul(0, i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      __builtin_amdgcn_s_waitcnt(kWaitNext);   // own loads of tile t + 1 have landed, own reads of tile t are in registers
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_barrier();            // tile t + 1 is in LDS, and every wave is done with tile t, whose stage is refilled
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < TW; ++i) read((t + 1) & (NST - 1), 0, i);
+      issue(cur);
+#pragma unroll
+      for (int i = 0; i < TW; ++i) mul(1, i);
       __builtin_amdgcn_sched_barrier(0);
     }
-    __builtin_amdgcn_s_waitcnt(kWaitNext);   // own loads of tile t + 1 have landed, own reads of tile t are in registers
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_barrier();            // tile t + 1 is in LDS, and every wave is done with tile t, whose stage is refilled
-    __builtin_amdgcn_sched_barrier(0);
+  } else {
+    for (int t = 0; t < NST - 1; ++t) issue(t);
+    for (int t = 0; t < nk; ++t) {
+      __builtin_amdgcn_s_waitcnt(kWaitOldest);
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_barrier();            // tile t is in LDS, and every wave is done with tile t - 1, whose stage is refilled
+      __builtin_amdgcn_sched_barrier(0);
+      issue((t + NST - 1) & (NST - 1));
 #pragma unroll
-    for (int i = 0; i < TW; ++i) read((t + 1) & (NST - 1), 0, i);
-    issue(cur);
+      for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-    for (int i = 0; i < TW; ++i) mul(1, i);
-    __builtin_amdgcn_sched_barrier(0);
+        for (int i = 0; i < TW; ++i) read(t & (NST - 1), ks, i);
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int i = 0; i < TW; ++i) mul(ks, i);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
 
   // write-out through LDS, rows of 64 columns; the loads past the last tile have to land before their stages are reused
@@ -343,10 +365,10 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_tile_kernel(GemmDev p, int o
   }
 }
 
-template <int TW, bool AKC, bool BKC, int NST>
+template <int TW, bool AKC, bool BKC, int NST, bool LACED>
 static hipError_t launch_tile_shape(const GemmDev& d, int out_bf16, hipStream_t st) {
   constexpr int BM = 32 * TW, smem = NST * 2 * BM * ROWB;
-  auto kfn = gemm_bf16_tile_kernel<TW, AKC, BKC, NST>;
+  auto kfn = gemm_bf16_tile_kernel<TW, AKC, BKC, NST, LACED>;
   static LdsLimit limit;
   const hipError_t e = limit.raise(reinterpret_cast<const void*>(kfn), smem);
   if (e != hipSuccess) return e;
@@ -355,13 +377,38 @@ static hipError_t launch_tile_shape(const GemmDev& d, int out_bf16, hipStream_t 
   return hipGetLastError();
 }
 
+// A block by itself on its compute unit has nothing else to hide the fragment reads behind; with others beside it the lacing
+// holds the matrix instructions up where reads are transposing ones, and does not pay for itself in a short reduction.  us,
+// reads first / laced, 128 x 128 tiles (64 x 64 where it says so):
+//   up to 256 blocks: 4096 x 1024 x 6400 TN 64.6 / 59.0, 2257 x 1000 x 1000 NN 17.4 / 15.9; 64: 128 x 1024 x 3072 NT 16.7 / 14.4,
+//     1024 x 1024 x 6400 TN 31.4 / 31.3, 1920 x 512 x 1024 NN 9.2 / 9.3
+//   more, B contiguous: 6400 x 1024 x 3072 50.8 / 47.8, x 768 18.4 / 18.4, x 512 14.9 / 15.2; 600 x 8000 x 768 18.1 / 18.0, x 256
+//     10.5 / 11.5; 64: 6400 x 1024 x 3072 78.7 / 74.6, 4096 x 1024 x 256 11.1 / 11.4
+//   more, B strided, A contiguous: 6400 x 1024 x 2048 35.8 / 33.0, x 768 19.0 / 18.7, x 256 11.2 / 12.2, 3000 x 3000 x 640 26.5 /
+//     27.4; 64: 8192 x 1024 x 1024 38.3 / 40.3
+//   more, both strided: 16000 x 512 x 1286 26.6 / 27.8, 9000 x 640 x 3000 44.0 / 49.0, x 300 of 16000 x 512 13.8 / 14.5; 64: 2048 x
+//     2048 x 4096 58.2 / 62.4
+bool gemm_tile_laced(int edge, bool a_kc, bool b_kc, int64_t blocks, int ktiles) {
+  return blocks <= 256 || (ktiles >= 12 && (b_kc || (a_kc && edge == 128)));
+}
+
 template <bool AKC, bool BKC>
 static hipError_t launch_tile_form(const GemmDev& d, GemmTile tile, int out_bf16, hipStream_t st) {
-  if (tile == kTile64) return launch_tile_shape<2, AKC, BKC, 4>(d, out_bf16, st);
+  const int64_t blocks = (int64_t)d.tiles_m * d.tiles_n * d.nz;
+  int ktiles = 0;   // of a block
+  for (int s = 0; s < kMaxSeg; ++s) ktiles += (d.K[s] + BK - 1) / BK;
+  ktiles = (ktiles + d.splits - 1) / d.splits;
+  const bool laced = gemm_tile_laced(tile == kTile64 ? 64 : 128, AKC, BKC, blocks, ktiles);
+  if (tile == kTile64)
+    return laced ? launch_tile_shape<2, AKC, BKC, 4, true>(d, out_bf16, st) : launch_tile_shape<2, AKC, BKC, 4, false>(d, out_bf16, st);
   // 128 KiB of LDS where no compute unit gets a second block anyway
-  if ((int64_t)d.tiles_m * d.tiles_n * d.nz <= 256) return launch_tile_shape<4, AKC, BKC, 4>(d, out_bf16, st);
-  return launch_tile_shape<4, AKC, BKC, 2>(d, out_bf16, st);
+  if (blocks <= 256) return launch_tile_shape<4, AKC, BKC, 4, true>(d, out_bf16, st);
+  if constexpr (AKC) {
+    if (laced) return launch_tile_shape<4, AKC, BKC, 2, true>(d, out_bf16, st);
+  }
+  return launch_tile_shape<4, AKC, BKC, 2, false>(d, out_bf16, st);
 }
+
 // ---- few rows ----------------------------------------------------------------------
 // 16 columns x 16 NJ rows per block, the reduction split over its eight waves (wave w takes steps w, w + 8, ...), fragments
 // straight from the operands' rows into registers, PF - 1 lines ahead; the partial tiles meet in LDS and are added in wave
