@@ -150,7 +150,7 @@ __device__ __forceinline__ void gs_finish_ragged(const GemmDev& p, int out_bf16,
   }
 }
 
-template <int TW, bool AKC, bool BKC, int NST, bool LACED>
+template <int TW, bool AKC, bool BKC, int NST, bool LACED, bool SECOND>
 __global__ __launch_bounds__(256, LACED ? 2 : 1) void gemm_bf16_tile_kernel(GemmDev p, int out_bf16) {
   constexpr int BM = 32 * TW, TILE = BM * ROWB, STAGE = 2 * TILE;   // square block tile; bytes of an operand tile, a stage
   constexpr int NL = TW, LD = BM + 4;                               // loads per wave, operand and tile; staging row (floats)
@@ -172,8 +172,7 @@ __global__ __launch_bounds__(256, LACED ? 2 : 1) void gemm_bf16_tile_kernel(Gemm
   const int in_g = pid - gid * 8 * p.tiles_n;
   const int m0 = (first_m + in_g % gm) * BM, n0 = (in_g / gm) * BM;
   const int z = blockIdx.z, batch = z / p.splits, split = z - batch * p.splits;
-  constexpr bool kSecond = TW == 2 && AKC && !BKC;               // (compiled in where it is used)
-  const bool second = kSecond && p.C_second && batch == 1;       // segment 0 alone
+  const bool second = SECOND && batch == 1;                      // segment 0 alone, to C_second
   const int nseg = second ? 1 : kMaxSeg;
 
   // reduction tiles of this block: [t0, t1) of the sequence that runs through the segments one after the other
@@ -365,10 +364,10 @@ __global__ __launch_bounds__(256, LACED ? 2 : 1) void gemm_bf16_tile_kernel(Gemm
   }
 }
 
-template <int TW, bool AKC, bool BKC, int NST, bool LACED>
+template <int TW, bool AKC, bool BKC, int NST, bool LACED, bool SECOND = false>
 static hipError_t launch_tile_shape(const GemmDev& d, int out_bf16, hipStream_t st) {
   constexpr int BM = 32 * TW, smem = NST * 2 * BM * ROWB;
-  auto kfn = gemm_bf16_tile_kernel<TW, AKC, BKC, NST, LACED>;
+  auto kfn = gemm_bf16_tile_kernel<TW, AKC, BKC, NST, LACED, SECOND>;
   static LdsLimit limit;
   const hipError_t e = limit.raise(reinterpret_cast<const void*>(kfn), smem);
   if (e != hipSuccess) return e;
@@ -383,13 +382,14 @@ static hipError_t launch_tile_shape(const GemmDev& d, int out_bf16, hipStream_t 
 //   up to 256 blocks: 4096 x 1024 x 6400 TN 64.6 / 59.0, 2257 x 1000 x 1000 NN 17.4 / 15.9; 64: 128 x 1024 x 3072 NT 16.7 / 14.4,
 //     1024 x 1024 x 6400 TN 31.4 / 31.3, 1920 x 512 x 1024 NN 9.2 / 9.3
 //   more, B contiguous: 6400 x 1024 x 3072 50.8 / 47.8, x 768 18.4 / 18.4, x 512 14.9 / 15.2; 600 x 8000 x 768 18.1 / 18.0, x 256
-//     10.5 / 11.5; 64: 6400 x 1024 x 3072 78.7 / 74.6, 4096 x 1024 x 256 11.1 / 11.4
+//     10.5 / 11.5; 64: 6400 x 1024 x 3072 78.7 / 74.6, 1920 x 1024 x 1536 14.9 / 14.6, 2000 x 768 x 768 9.4 / 9.6
 //   more, B strided, A contiguous: 6400 x 1024 x 2048 35.8 / 33.0, x 768 19.0 / 18.7, x 256 11.2 / 12.2, 3000 x 3000 x 640 26.5 /
-//     27.4; 64: 8192 x 1024 x 1024 38.3 / 40.3
+//     27.4; 64: 1920 x 1024 x 2048 17.6 / 18.5
 //   more, both strided: 16000 x 512 x 1286 26.6 / 27.8, 9000 x 640 x 3000 44.0 / 49.0, x 300 of 16000 x 512 13.8 / 14.5; 64: 2048 x
-//     2048 x 4096 58.2 / 62.4
+//     768 x 1500 14.6 / 16.1
 bool gemm_tile_laced(int edge, bool a_kc, bool b_kc, int64_t blocks, int ktiles) {
-  return blocks <= 256 || (ktiles >= 12 && (b_kc || (a_kc && edge == 128)));
+  if (blocks <= 256) return true;
+  return edge == 128 ? a_kc && ktiles >= 12 : b_kc && ktiles >= 24;
 }
 
 template <bool AKC, bool BKC>
@@ -399,6 +399,13 @@ static hipError_t launch_tile_form(const GemmDev& d, GemmTile tile, int out_bf16
   for (int s = 0; s < kMaxSeg; ++s) ktiles += (d.K[s] + BK - 1) / BK;
   ktiles = (ktiles + d.splits - 1) / d.splits;
   const bool laced = gemm_tile_laced(tile == kTile64 ? 64 : 128, AKC, BKC, blocks, ktiles);
+  // (an instance of its own: with the choice made in the kernel its other products were 1 to 8 % slower.  launch_gemm_bf16:
+  // 64 x 64 only)
+  if constexpr (AKC && !BKC) {
+    if (d.C_second)
+      return laced ? launch_tile_shape<2, AKC, BKC, 4, true, true>(d, out_bf16, st)
+                   : launch_tile_shape<2, AKC, BKC, 4, false, true>(d, out_bf16, st);
+  }
   if (tile == kTile64)
     return laced ? launch_tile_shape<2, AKC, BKC, 4, true>(d, out_bf16, st) : launch_tile_shape<2, AKC, BKC, 4, false>(d, out_bf16, st);
   // 128 KiB of LDS where no compute unit gets a second block anyway

@@ -86,7 +86,7 @@ def test_bf16_tile_where_the_device_counts_the_size(M, N, K, plan):
 @pytest.mark.parametrize("edge, form, M, N, K, laced", [
     (128, "TN", 4096, 1024, 6400, True), (128, "NN", 2257, 1000, 1000, True), (64, "NT", 128, 1024, 3072, True),
     (64, "TN", 1024, 1024, 6400, True), (128, "NT", 6400, 1024, 3072, True), (64, "NT", 6400, 1024, 3072, True),
-    (128, "NN", 6400, 1024, 2048, True),
+    (64, "NT", 2000, 768, 768, False), (128, "NN", 6400, 1024, 2048, True),
     (128, "TN", 16000, 512, 1286, False), (128, "TN", 9000, 640, 3000, False), (128, "TN", 4096, 2048, 2048, False),
     (64, "TN", 2048, 2048, 4096, False), (64, "NN", 8192, 1024, 1024, False), (64, "NN", 6400, 1024, 1024, False),
     (128, "NT", 600, 8000, 256, False), (128, "NT", 600, 8000, 512, False), (128, "NN", 6400, 1024, 256, False),
