@@ -939,13 +939,16 @@ template <typename TE> hipError_t launch_ls_wave_fwd(const LsFwd& p, int d, hipS
   if (nl < 1) return hipErrorInvalidValue;
   const int64_t b64 = (p.B + 63) / 64, b32 = (p.B + 31) / 32;
   // The caller's rows come from memory, not from the caches: more steps in flight (one step, 4 x 1024 units x 128
-  // sentences, with the other changes to the cells: 72.1 us with four, 68.5 with six, 75.4 with eight).
+  // sentences, with the other changes to the cells: 72.1 us with four, 68.5 with six, 75.4 with eight).  Six take the
+  // registers of a second block, so not where compute units get one.
   // The largest block that still gives most compute units one: larger blocks load less per output (128 gate rows x 64
   // sentences: 512 bytes per reduction index for 8192 outputs).  1024 units x 128 sentences, 64 x 32 blocks against 128 x 64:
   // three layers 27.5 us (768 blocks) and 28.0 (192), four 34.0 (1024) and 29.4 (256).
   if constexpr (LsMma<TE>::kPair) {
     if (nl * ((p.H + 31) / 32) * b64 >= 192) return ls_fwd_shape<TE, 8, 4, 3>(p, d, l_lo, nl, st);
-    if (nl * ((p.H + 15) / 16) * b32 >= 192) return ls_fwd_shape<TE, 4, 2, 4, 6>(p, d, l_lo, nl, st);
+    const int64_t blocks = nl * ((p.H + 15) / 16) * b32;
+    if (blocks > 256) return ls_fwd_shape<TE, 4, 2, 4>(p, d, l_lo, nl, st);
+    if (blocks >= 192) return ls_fwd_shape<TE, 4, 2, 4, 6>(p, d, l_lo, nl, st);
     return ls_fwd_shape<TE, 4, 1, 4, 6>(p, d, l_lo, nl, st);
   } else {
     if (nl * ((p.H + 15) / 16) * b32 >= 512) return ls_fwd_shape<TE, 4, 2, 4>(p, d, l_lo, nl, st);

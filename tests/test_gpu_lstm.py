@@ -115,6 +115,7 @@ def test_lstm_two_runs_are_bit_identical():
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shape", [(3, 7, 24, 40, 3),         # T, B, I, H, L: reductions of one and two steps
                                    (3, 97, 72, 1032, 2),      # 16 units x 32 sentences at one step
+                                   (2, 225, 24, 648, 1),      # the same, more blocks than compute units
                                    (2, 385, 72, 1032, 1),     # 32 x 64
                                    (4, 16, 256, 512, 2)])     # 16 x 16
 def test_lstm_one_step_at_a_time_gives_the_bits_of_the_sequence(shape, dtype):
