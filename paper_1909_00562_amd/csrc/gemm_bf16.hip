@@ -79,11 +79,11 @@ __device__ __forceinline__ int stage_read_off(int it, int vrow, int vcol) {
 // loads) go through buffer resources that start at the wave tile's first element, so
 // the row part of an address is a scalar offset, the lane part one register, and rows
 // beyond M are dropped by pointing the lane offset outside the resource instead of branching.
-// APART: the results of a batch lie apart (C_of).
+// APART: the results of a batch lie apart, this one at C_apart.
 template <int TM, int TN, bool OUT_BF16, bool DROP, int CH, int EP_LD, bool MI16, bool APART, typename AccT>
 __device__ __forceinline__ void gemm_epilogue_vec(const GemmDev& p, int Mv, AccT& acc,
                                                   unsigned char* region, int lane, int row0, int col0, int batch,
-                                                  int z) {
+                                                  int z, void* C_apart) {
   constexpr int WAIT_LGKM_ONLY = 0xC07F;
   constexpr int ES = OUT_BF16 ? 2 : 4;
   float* stage_f = reinterpret_cast<float*>(region);
@@ -93,7 +93,7 @@ __device__ __forceinline__ void gemm_epilogue_vec(const GemmDev& p, int Mv, AccT
   const int64_t ld = to_partial ? (int64_t)p.N : p.ldc;
   const int64_t origin = to_partial ? ((int64_t)z * p.M + row0) * p.N + col0
                                     : (int64_t)batch * p.sC + (int64_t)row0 * p.ldc + col0;
-  unsigned char* cbase = APART        ? reinterpret_cast<unsigned char*>(p.C_of[batch])   // (no split, sC = 0)
+  unsigned char* cbase = APART        ? reinterpret_cast<unsigned char*>(C_apart)   // (no split, sC = 0)
                          : to_partial ? reinterpret_cast<unsigned char*>(p.partial)
                                       : reinterpret_cast<unsigned char*>(p.C);
   const __amdgpu_buffer_rsrc_t rs_c = make_rsrc(cbase + origin * ES);
@@ -224,11 +224,12 @@ __device__ __forceinline__ void gemm_epilogue_vec(const GemmDev& p, int Mv, AccT
 template <int TM, int TN, bool OUT_BF16, bool VEC, bool DROP, int CH = 32, int EP_LD = 72, bool MI16 = false,
           bool APART = false, typename AccT>
 __device__ __forceinline__ void gemm_epilogue(const GemmDev& p, int Mv, AccT& acc,
-                                              unsigned char* region, int lane, int row0, int col0, int batch, int z) {
+                                              unsigned char* region, int lane, int row0, int col0, int batch, int z,
+                                              void* C_apart = nullptr) {
   static_assert(TN == (MI16 ? 4 : 2), "64-column wave tiles");
   static_assert(CH == 32 || CH == 16, "chunk of one or half an MFMA tile");
   if constexpr (VEC) {
-    gemm_epilogue_vec<TM, TN, OUT_BF16, DROP, CH, EP_LD, MI16, APART>(p, Mv, acc, region, lane, row0, col0, batch, z);
+    gemm_epilogue_vec<TM, TN, OUT_BF16, DROP, CH, EP_LD, MI16, APART>(p, Mv, acc, region, lane, row0, col0, batch, z, C_apart);
     return;
   }
   constexpr int WAIT_LGKM_ONLY = 0xC07F;   // leaves global loads in flight
@@ -745,7 +746,8 @@ __device__ __forceinline__ uint32_t ring_frag_base(int row0, int lane) {
 }
 
 template <bool AKC, bool BKC, bool OUT_BF16, bool VEC, bool DROP, bool APART>
-__global__ __launch_bounds__(512) void gemm_bf16_ring_kernel(GemmDev p, int work_total) {
+__global__ __launch_bounds__(512) void gemm_bf16_ring_kernel(
+    GemmDev p, int work_total, typename std::conditional<APART, GemmApart, GemmNotApart>::type apart) {
   constexpr int BM = 256, BN = 256, WGN = 4;
   constexpr int WM = 128, WN = 64, TM = 4, TN = 2;
   extern __shared__ __align__(1024) unsigned char smem[];
@@ -926,22 +928,27 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring_kernel(GemmDev p, int work
       }
     }
     // item done: write it out while the next item's first sub-tiles are already in flight
+    void* C_apart = nullptr;
+    if constexpr (APART) C_apart = apart.C[it.batch];
     gemm_epilogue<TM, TN, OUT_BF16, VEC, DROP, 16, 64, false, APART>(p, Mv, acc, smem + RING_EPI_OFF + wave * 4096, lane,
-                                                       it.m0 + wm * WM, it.n0 + wn * WN, it.batch, it.z);
+                                                       it.m0 + wm * WM, it.n0 + wn * WN, it.batch, it.z, C_apart);
     zero_acc();
   }
 }
 
 template <bool AKC, bool BKC, bool OUT_BF16, bool VEC, bool APART = false>
-static hipError_t launch_ring(const GemmDev& d, int batch, hipStream_t st) {
+static hipError_t launch_ring(const GemmArgs& g, const GemmDev& d, hipStream_t st) {
   constexpr int smem = RING_SMEM;
   auto kfn = gemm_bf16_ring_kernel<AKC, BKC, OUT_BF16, VEC, false, APART>;
   static LdsLimit limit;
   const hipError_t e = limit.raise(reinterpret_cast<const void*>(kfn), smem);
   if (e != hipSuccess) return e;
-  const int work_total = d.tiles_m * d.tiles_n * batch * d.splits;
+  const int work_total = d.tiles_m * d.tiles_n * g.batch * d.splits;
   const int blocks = pp_grid_blocks(work_total);
-  hipLaunchKernelGGL(kfn, dim3(blocks), dim3(512), smem, st, d, work_total);
+  typename std::conditional<APART, GemmApart, GemmNotApart>::type apart{};
+  if constexpr (APART)
+    for (int b = 0; b < g.batch; ++b) apart.C[b] = g.C_of[b];   // (launch_gemm_bf16 has checked the count)
+  hipLaunchKernelGGL(kfn, dim3(blocks), dim3(512), smem, st, d, work_total, apart);
   return hipGetLastError();
 }
 template <bool AKC, bool BKC>
@@ -949,9 +956,9 @@ static hipError_t launch_ring_oriented(const GemmArgs& g, const GemmDev& d, hipS
   const bool obf = g.c_bf16 && g.splits <= 1;
   const bool vec = d.vec_ok != 0;
   // (an instance of its own: with the choice made in the kernel all its products were 2 to 4 % slower)
-  if (g.C_of) return vec && !obf ? launch_ring<AKC, BKC, false, true, true>(d, g.batch, st) : hipErrorInvalidValue;
-  if (obf) return vec ? launch_ring<AKC, BKC, true, true>(d, g.batch, st) : launch_ring<AKC, BKC, true, false>(d, g.batch, st);
-  return vec ? launch_ring<AKC, BKC, false, true>(d, g.batch, st) : launch_ring<AKC, BKC, false, false>(d, g.batch, st);
+  if (g.C_of) return vec && !obf ? launch_ring<AKC, BKC, false, true, true>(g, d, st) : hipErrorInvalidValue;
+  if (obf) return vec ? launch_ring<AKC, BKC, true, true>(g, d, st) : launch_ring<AKC, BKC, true, false>(g, d, st);
+  return vec ? launch_ring<AKC, BKC, false, true>(g, d, st) : launch_ring<AKC, BKC, false, false>(g, d, st);
 }
 
 template <bool AKC, bool BKC, bool OUT_BF16, bool VEC, bool DROP = false>
@@ -1025,10 +1032,7 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, GemmTile tile, hipStream_t st) {
     return hipErrorInvalidValue;
   d.C_second = g.C_second;
   bool apart_al16 = !g.C_second || al16(g.C_second);
-  for (int b = 0; b < kMaxApart; ++b) {
-    d.C_of[b] = g.C_of && b < g.batch ? g.C_of[b] : nullptr;
-    apart_al16 = apart_al16 && al16(d.C_of[b]);
-  }
+  for (int b = 0; g.C_of && b < g.batch; ++b) apart_al16 = apart_al16 && al16(g.C_of[b]);
   d.bias = reinterpret_cast<const uint16_t*>(g.bias);
   d.gate = g.gate;
   d.ldg = g.ldg;
