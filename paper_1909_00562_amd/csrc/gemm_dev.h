@@ -105,8 +105,8 @@ struct DirectLoader {
 
 // the 64 x 64 and 128 x 128 kernel (gemm_tile.hip); d as launch_gemm_bf16 has filled it in
 hipError_t launch_gemm_bf16_tile(const GemmDev& d, GemmTile tile, bool a_kc, bool b_kc, bool out_bf16, hipStream_t st);
-// whether that kernel's fragment reads run between its matrix instructions (ktiles: reduction tiles of a block)
-bool gemm_tile_laced(int edge, bool a_kc, bool b_kc, int64_t blocks, int ktiles);
+// whether that kernel's fragment reads run between its matrix instructions
+bool gemm_tile_laced(bool a_kc, int64_t blocks);
 // the kernel for few rows: both operands reduction-contiguous, up to three segments of the same length, no split, no batch
 hipError_t launch_gemm_bf16_few(const GemmDev& d, bool out_bf16, hipStream_t st);
 

@@ -250,14 +250,21 @@ __global__ __launch_bounds__(256, LACED ? 2 : 1) void gemm_bf16_tile_kernel(Gemm
     for (int j = 0; j < TW; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ks][i], b[ks][j], acc[i][j], 0, 0, 0);
   };
   if constexpr (LACED) {
-    for (int t = 0; t < NST; ++t) issue(t);
-    __builtin_amdgcn_s_waitcnt(kWaitFirst);
+    static_assert(NST == 2 || NST == 4, "the waits of the last tiles");
+    if (nk >= NST) {
+      for (int t = 0; t < NST; ++t) issue(t);
+      __builtin_amdgcn_s_waitcnt(kWaitFirst);
+    } else {
+      for (int t = 0; t < nk; ++t) issue(t);
+      __builtin_amdgcn_s_waitcnt(0x0f70);
+    }
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < TW; ++i) read(0, 0, i);
-    for (int t = 0; t < nk; ++t) {
+    int t = 0;
+    for (; t + NST < nk; ++t) {
       const int cur = t & (NST - 1);
 #pragma unroll
       for (int i = 0; i < TW; ++i) {
@@ -272,6 +279,30 @@ __global__ __launch_bounds__(256, LACED ? 2 : 1) void gemm_bf16_tile_kernel(Gemm
 #pragma unroll
       for (int i = 0; i < TW; ++i) read((t + 1) & (NST - 1), 0, i);
       issue(cur);
+#pragma unroll
+      for (int i = 0; i < TW; ++i) mul(1, i);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // The last NST tiles: nothing more to load.  (Loads past the end would be waited for before the write-out: 0.4 us, a tenth
+    // of a short product.)
+    for (; t < nk; ++t) {
+#pragma unroll
+      for (int i = 0; i < TW; ++i) {
+        read(t & (NST - 1), 1, i);
+        mul(0, i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (t + 1 < nk) {
+        const int behind = nk - 2 - t;         // tiles on their way after t + 1
+        if (NST > 2 && behind >= 2) __builtin_amdgcn_s_waitcnt(kWaitNext);
+        else if (NST > 2 && behind == 1) __builtin_amdgcn_s_waitcnt(((2 * NL) & 15) | (((2 * NL) >> 4) << 14) | 0x0070);
+        else __builtin_amdgcn_s_waitcnt(0x0070);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < TW; ++i) read((t + 1) & (NST - 1), 0, i);
+      }
 #pragma unroll
       for (int i = 0; i < TW; ++i) mul(1, i);
       __builtin_amdgcn_sched_barrier(0);
@@ -376,44 +407,32 @@ static hipError_t launch_tile_shape(const GemmDev& d, int out_bf16, hipStream_t 
   return hipGetLastError();
 }
 
-// A block by itself on its compute unit has nothing else to hide the fragment reads behind; with others beside it the lacing
-// holds the matrix instructions up where reads are transposing ones, and does not pay for itself in a short reduction.  us,
-// reads first / laced, 128 x 128 tiles (64 x 64 where it says so):
-//   up to 256 blocks: 4096 x 1024 x 6400 TN 64.6 / 59.0, 2257 x 1000 x 1000 NN 17.4 / 15.9; 64: 128 x 1024 x 3072 NT 16.7 / 14.4,
-//     1024 x 1024 x 6400 TN 31.4 / 31.3, 1920 x 512 x 1024 NN 9.2 / 9.3
-//   more, B contiguous: 6400 x 1024 x 3072 50.8 / 47.8, x 768 18.4 / 18.4, x 512 14.9 / 15.2; 600 x 8000 x 768 18.1 / 18.0, x 256
-//     10.5 / 11.5; 64: 6400 x 1024 x 3072 78.7 / 74.6, 1920 x 1024 x 1536 14.9 / 14.6, 2000 x 768 x 768 9.4 / 9.6
-//   more, B strided, A contiguous: 6400 x 1024 x 2048 35.8 / 33.0, x 768 19.0 / 18.7, x 256 11.2 / 12.2, 3000 x 3000 x 640 26.5 /
-//     27.4; 64: 1920 x 1024 x 2048 17.6 / 18.5
-//   more, both strided: 16000 x 512 x 1286 26.6 / 27.8, 9000 x 640 x 3000 44.0 / 49.0, x 300 of 16000 x 512 13.8 / 14.5; 64: 2048 x
-//     768 x 1500 14.6 / 16.1
-bool gemm_tile_laced(int edge, bool a_kc, bool b_kc, int64_t blocks, int ktiles) {
-  if (blocks <= 256) return true;
-  return edge == 128 ? a_kc && ktiles >= 12 : b_kc && ktiles >= 24;
-}
+// Reads first and laced, us, 128 x 128 tiles (64 x 64 where it says so): up to 256 blocks 1024 x 1024 x 6400 TN 62.6 / 53.8, 2257 x
+// 1000 x 1000 NN 20.8 / 18.0, 1920 x 1024 x 384 NT 13.2 / 12.2; 64: 128 x 1024 x 3072 NT 16.9 / 14.5, 1024 x 1024 x 6400 TN 31.3 /
+// 30.7.  More, A contiguous: 6400 x 1024 x 3072 NT 52.1 / 48.9, 600 x 8000 x 256 NT 13.8 / 13.4, 6400 x 1024 x 2048 NN 40.5 / 37.9, x
+// 256 15.0 / 14.1; 64: 6400 x 1024 x 1024 NT 33.7 / 30.6, 8192 x 1024 x 1024 NN 39.2 / 36.3.  More, both strided, where two blocks
+// share a compute unit's transposing reads: 16000 x 512 x 1286 28.0 / 29.1, 9000 x 640 x 3000 44.2 / 47.9, 4096 x 2048 x 2048 35.3 /
+// 36.2; 64: 2048 x 768 x 1500 13.8 / 14.5, 4096 x 1024 x 6400 84.8 / 91.1.
+bool gemm_tile_laced(bool a_kc, int64_t blocks) { return a_kc || blocks <= 256; }
 
 template <bool AKC, bool BKC>
 static hipError_t launch_tile_form(const GemmDev& d, GemmTile tile, int out_bf16, hipStream_t st) {
   const int64_t blocks = (int64_t)d.tiles_m * d.tiles_n * d.nz;
-  int ktiles = 0;   // of a block
-  for (int s = 0; s < kMaxSeg; ++s) ktiles += (d.K[s] + BK - 1) / BK;
-  ktiles = (ktiles + d.splits - 1) / d.splits;
-  const bool laced = gemm_tile_laced(tile == kTile64 ? 64 : 128, AKC, BKC, blocks, ktiles);
+  if constexpr (!AKC) {
+    if (!gemm_tile_laced(AKC, blocks))
+      return tile == kTile64 ? launch_tile_shape<2, AKC, BKC, 4, false>(d, out_bf16, st)
+                             : launch_tile_shape<4, AKC, BKC, 2, false>(d, out_bf16, st);
+  }
   // (an instance of its own: with the choice made in the kernel its other products were 1 to 8 % slower.  launch_gemm_bf16:
   // 64 x 64 only)
   if constexpr (AKC && !BKC) {
-    if (d.C_second)
-      return laced ? launch_tile_shape<2, AKC, BKC, 4, true, true>(d, out_bf16, st)
-                   : launch_tile_shape<2, AKC, BKC, 4, false, true>(d, out_bf16, st);
+    if (d.C_second) return launch_tile_shape<2, AKC, BKC, 4, true, true>(d, out_bf16, st);
   }
-  if (tile == kTile64)
-    return laced ? launch_tile_shape<2, AKC, BKC, 4, true>(d, out_bf16, st) : launch_tile_shape<2, AKC, BKC, 4, false>(d, out_bf16, st);
+  if (tile == kTile64) return launch_tile_shape<2, AKC, BKC, 4, true>(d, out_bf16, st);
   // 128 KiB of LDS where no compute unit gets a second block anyway
   if (blocks <= 256) return launch_tile_shape<4, AKC, BKC, 4, true>(d, out_bf16, st);
-  if constexpr (AKC) {
-    if (laced) return launch_tile_shape<4, AKC, BKC, 2, true>(d, out_bf16, st);
-  }
-  return launch_tile_shape<4, AKC, BKC, 2, false>(d, out_bf16, st);
+  if constexpr (AKC) return launch_tile_shape<4, AKC, BKC, 2, true>(d, out_bf16, st);
+  return hipErrorInvalidValue;   // (not reached)
 }
 
 // ---- few rows ----------------------------------------------------------------------

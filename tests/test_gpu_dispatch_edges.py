@@ -204,12 +204,13 @@ def test_both_gradients_through_w_c_in_one_launch(shape):
     _parity(make_custom(T=T, S=S, B=B, H=H, V=V, seed=V + H, dtype="bf16", min_len=1, pad_prob=0.1))
 
 
-@pytest.mark.parametrize("shape", [(6, 7, 55, 520, 3003),      # 64 x 64: logits, dW_out
-                                   (9, 5, 45, 520, 8011),      # 128 x 128: logits, dW_out
+@pytest.mark.parametrize("shape", [(6, 7, 55, 520, 3003),      # 64 x 64: logits, and dW_out with its fragments read first
+                                   (9, 5, 45, 520, 8011),      # 128 x 128: the same
                                    # (With 643 words 0.011 of dW_out need the row-scale floor, in the other loop as
                                    # many, 3630 elements; the budget of 0.0022 was taken at larger vocabularies.)
                                    (10, 6, 103, 520, 3003)])   # both gradients through W_c in one launch, 306 blocks
 def test_bf16_products_with_several_blocks_per_compute_unit(shape):
-    """More than 256 blocks and a short reduction or strided operands: the loop that reads a tile's fragments first."""
+    """More than 256 blocks of 64 x 64 or 128 x 128 tiles, reductions of fewer tiles than the ring has stages among them (the
+    attention products and dW_a of the last)."""
     T, S, B, H, V = shape
     _parity(make_custom(T=T, S=S, B=B, H=H, V=V, seed=V + H, dtype="bf16", min_len=1, pad_prob=0.1))
