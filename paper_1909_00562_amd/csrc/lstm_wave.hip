@@ -69,41 +69,40 @@ template <> struct LsMma<float> {
 };
 
 // The cell's functions without branches or IEEE divisions: with one wave per SIMD nothing hides the vector instructions of
-// a cell (4 x 1024 units x 128 sentences, forward wavefronts: 2 us of 27 less than with expf, tanhf and divisions).  Largest /
-// mean error in units of the last place over 4 M arguments of N(0, s^2), here and with those: sigmoid s = 0.6 2.12 / 0.402 and
-// 2.12 / 0.401, s = 10 2.49 / 0.419 and 2.49 / 0.418; tanh s = 0.1 0.54 / 0.250 and 0.60 / 0.251, s = 0.6 1.48 / 0.265 and
-// 1.38 / 0.273, s = 10 1.36 / 0.167 and 1.34 / 0.169.
-// e^-a, |a| <= 128 or NaN
+// a cell (4 x 1024 units x 128 sentences, forward wavefronts: 2 us of 27 less than with expf, tanhf and divisions).  Error in
+// units of the last place, over every float of a binade, here and with those: no binade of either function has a larger
+// maximum or mean.  Largest, sigmoid 1.72 and 2.20 (2.62 below -16; past -87 results less than the smallest normal number,
+// which 1 / (1 + expf) loses), tanh 1.03 and 1.41; mean over N(0, s^2), s = 0.1 / 1 / 10, sigmoid 0.266 / 0.280 / 0.283 and 0.458 /
+// 0.397 / 0.418, tanh 0.250 / 0.257 / 0.166 and 0.251 / 0.275 / 0.169.
+// e^-a, 0 <= a <= 104 or NaN
 __device__ __forceinline__ float ls_exp_neg(float a) {
   constexpr float kLog2e = 1.44269504088896f, kLog2eLo = 1.925963033500e-8f;
   const float n = __builtin_rintf(-a * kLog2e);
   const float f = __builtin_fmaf(-a, kLog2eLo, __builtin_fmaf(-a, kLog2e, -n));
   return __builtin_ldexpf(__builtin_amdgcn_exp2f(f), (int)n);
 }
-// 1 / d of a finite d >= 1: the instruction and a Newton step
-__device__ __forceinline__ float ls_rcp(float d) {
-  const float r = __builtin_amdgcn_rcpf(d);
-  return __builtin_fmaf(__builtin_fmaf(-d, r, 1.f), r, r);
+// x / (1 + e), 0 <= e <= 1: a Newton step from the reciprocal instruction whose remainder counts the rounding of 1 + e in
+__device__ __forceinline__ float ls_over_1p(float x, float e) {
+  const float d = 1.f + e, lo = e - (d - 1.f), r = __builtin_amdgcn_rcpf(d), q = x * r;
+  return __builtin_fmaf(__builtin_fmaf(-q, lo, __builtin_fmaf(-q, d, x)), r, q);
 }
 __device__ __forceinline__ float ls_sigmoid(float a) {
-  constexpr float kMax = 87.33f;   // beyond it the result is 1 or less than the smallest normal number
-  const float b = __builtin_fabsf(a) > kMax ? __builtin_copysignf(kMax, a) : a;   // (NaN stays)
-  const float s = ls_rcp(1.f + ls_exp_neg(b));
-  return a < -kMax ? 0.f : s;
+  const float m = __builtin_fabsf(a), e = ls_exp_neg(m > 104.f ? 104.f : m);   // (NaN stays; e^-104 rounds to 0)
+  return ls_over_1p(a < 0.f ? e : 1.f, e);
 }
-// |a| < 0.625: a + a^3 P(a^2), P the minimax polynomial of (tanh(a) / a - 1) / a^2 (relative error of the whole 1.5e-10 before
+// |a| < 0.625: a + a^3 P(a^2), P the minimax polynomial of (tanh(a) / a - 1) / a^2 (relative error of the whole 1.6e-10 before
 // rounding); else 1 - 2 e^-2a / (1 + e^-2a)
 __device__ __forceinline__ float ls_tanh(float a) {
   const float m = __builtin_fabsf(a), b = m > 20.f ? 20.f : m;
-  const float e = ls_exp_neg(b + b), t = __builtin_fmaf(-2.f * e, ls_rcp(1.f + e), 1.f);
+  const float e = ls_exp_neg(b + b), t = __builtin_fmaf(-2.f * e, ls_over_1p(1.f, e), 1.f);
   const float u = a * a;
-  float q = __builtin_fmaf(u, 0x1.197b62p-9f, -0x1.0c213ep-7f);
-  q = __builtin_fmaf(u, q, 0x1.6394d8p-6f);
-  q = __builtin_fmaf(u, q, -0x1.b9ef7cp-5f);
-  q = __builtin_fmaf(u, q, 0x1.11106cp-3f);
+  float q = __builtin_fmaf(u, 0x1.1ace3ep-9f, -0x1.0c895ep-7f);
+  q = __builtin_fmaf(u, q, 0x1.63ad18p-6f);
+  q = __builtin_fmaf(u, q, -0x1.b9f220p-5f);
+  q = __builtin_fmaf(u, q, 0x1.11107cp-3f);
   q = __builtin_fmaf(u, q, -0x1.555554p-2f);
-  const float s = __builtin_fmaf(u * a, q, a);
-  return m < 0.625f ? s : __builtin_copysignf(t, a);
+  const float s = __builtin_fmaf(u * m, q, m);
+  return __builtin_copysignf(m < 0.625f ? s : t, a);
 }
 // sum over the 16 lanes of a row (lanes l, l ^ 8, then ^ 4, ^ 2, ^ 1: rotations add the same pairs), without the LDS pipe
 template <int N> __device__ __forceinline__ float ls_row_ror(float v) {

@@ -112,6 +112,50 @@ def test_lstm_two_runs_are_bit_identical():
             assert np.array_equal(g1[k][l], g2[k][l]), (k, l)
 
 
+def _one_cell(a_o, c0):
+    """y of one fp32 step whose forget gate is 1, input gate 0 and cell input -1: sigmoid(a_o) tanh(c0), [B, H]."""
+    import torch
+    import paper_1909_00562_amd as lib
+    B, H = a_o.shape
+    W_ih, b = np.zeros((4 * H, H), np.float32), np.zeros(4 * H, np.float32)
+    W_ih[3 * H:] = np.eye(H, dtype=np.float32)          # the output gate's argument is x
+    b[:H], b[H:2 * H], b[2 * H:3 * H] = -200, 200, -200
+    d = lib.DeviceLstm(a_o[None], np.ones(B, np.int32), [W_ih], [np.zeros((4 * H, H), np.float32)], [b],
+                       np.zeros((1, B, H), np.float32), c0[None], dtype="f32")
+    d.fwd()
+    d.sync()
+    return _host(d.y)[0]
+
+
+@pytest.mark.parametrize("lo, hi", [(1e-3, 0.1), (0.1, 0.6), (0.6, 0.7), (0.7, 1.5), (1.5, 9.0), (9.0, 18.0), (18.0, 86.0),
+                                    (87.5, 103.0)])
+def test_cell_functions_are_accurate_to_the_last_place(lo, hi):
+    """Over every float the cell's sigmoid is off by 1.72 units of the last place at most and its tanh by 1.03 (1 / (1 + expf)
+    and tanhf: 2.6 and 1.41), down to the subnormal results of sigmoid."""
+    B, H = 256, 512
+    rng = np.random.default_rng(int(hi * 10))
+    a = rng.uniform(lo, hi, (B, H)).astype(np.float32)
+    a[::2] *= -1
+    ulp = lambda y, r: np.abs(y.astype(np.float64) - r) / np.spacing(np.abs(r).astype(np.float32)).astype(np.float64)
+    big = np.full((B, H), 100.0, np.float32)
+    sig = ulp(_one_cell(a, big), 1 / (1 + np.exp(-a.astype(np.float64))))
+    tanh = ulp(_one_cell(2 * big, a), np.tanh(a.astype(np.float64)))
+    assert sig.max() <= 1.72 and tanh.max() <= 1.04, (sig.max(), tanh.max())
+
+
+def test_cell_functions_at_special_arguments():
+    a = np.array([[0.0, -0.0, np.inf, -np.inf, np.nan, 1e38, -1e38, 1e-40, -1e-40, 104.5, -104.5, 88.0]], np.float32)
+    big = np.full_like(a, 100.0)
+    # (an infinite or NaN x meets the zeros of the other gates' weight rows, so sigmoid's come as finite ones)
+    f = np.where(np.isfinite(a), a, 0)
+    with np.errstate(over="ignore"):
+        assert np.array_equal(_one_cell(f, big), (1 / (1 + np.exp(-f.astype(np.float64)))).astype(np.float32))
+    y = _one_cell(2 * big, a)
+    assert np.array_equal(y, np.tanh(a), equal_nan=True)
+    number = ~np.isnan(a)
+    assert np.array_equal(np.signbit(y[number]), np.signbit(a[number]))
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shape", [(3, 7, 24, 40, 3),         # T, B, I, H, L: reductions of one and two steps
                                    (3, 97, 72, 1032, 2),      # 16 units x 32 sentences at one step
