@@ -111,11 +111,24 @@ LsLayout make_ls_layout(const ls_shape* s) {
   };
   size_t pb = 0;
   auto mx = [&](size_t v) { if (v > pb) pb = v; };
+  // Several layers' weight gradients together fill the compute units with tiles of 256 x 256, whose operands are read half
+  // as often as those of 128 x 128: where rounds of the compute units are two thirds full or more.  Four layers of 1024
+  // units, 6400 rows: 473 us as seven products, 330 so.  The number of rows has no part in it: from 1 to 65536 of them, 2 to 16
+  // layers of 704 to 2048 units, no pass was slower (forward and backward 16 x 1024, one row 955 -> 728 us; backward 3 x 1024,
+  // 65536 rows 15.7 -> 15.3 ms, two thirds of a round in 2 x 1216 units, 16384 rows, 3.49 -> 3.32).
+  auto batched = [&](int n) {
+    const int64_t tiles = (int64_t)((4 * H + 255) / 256) * ((H + 255) / 256) * n, rounds = (tiles + 255) / 256;
+    return bf && n > 1 && 3 * tiles >= 2 * 256 * rounds;
+  };
+  L.dwh_batched = batched(NL);
+  L.dwi_batched = batched(NL - 1);
   for (int l = 0; l < NL; ++l) {
     const int Il = l == 0 ? I : H;
     L.p_dwi.push_back(gemm_plan(4 * H, Il, TB, 1, bf, true));
-    mx(gemm_partial_bytes(4 * H, Il, 1, L.p_dwi.back().splits));
+    if (l == 0 || !L.dwi_batched) mx(gemm_partial_bytes(4 * H, Il, 1, L.p_dwi.back().splits));
   }
+  L.p_dwh = gemm_plan(4 * H, H, TB, 1, bf, true);
+  if (!L.dwh_batched) mx(gemm_partial_bytes(4 * H, H, 1, L.p_dwh.splits));
   // The reduction split of the gradient of x is a function of the widths alone: with a split chosen from the row
   // count, a sentence's gradients would depend (in the last fp32 bit) on how many sentences share its batch.
   L.p_dx = gemm_plan(TB, I, 4 * H, 1, bf, false);
@@ -125,18 +138,7 @@ LsLayout make_ls_layout(const ls_shape* s) {
     L.p_dx.tile = kTile256;
   }
   mx(gemm_partial_bytes(TB, I, 1, L.p_dx.splits));
-  L.p_dwh = gemm_plan(4 * H, H, TB, 1, bf, true);
   L.p_gx = gemm_plan(TB, 4 * H, I, 1, bf, false);
-  mx(gemm_partial_bytes(4 * H, H, 1, L.p_dwh.splits));
-  // Several layers' weight gradients together fill the compute units with tiles of 256 x 256, whose operands are read half
-  // as often as those of 128 x 128: where rounds of the compute units are two thirds full or more.  Four layers of 1024
-  // units, 6400 rows: 473 us as seven products, 330 so.
-  auto batched = [&](int n) {
-    const int64_t tiles = (int64_t)((4 * H + 255) / 256) * ((H + 255) / 256) * n, rounds = (tiles + 255) / 256;
-    return bf && n > 1 && 3 * tiles >= 2 * 256 * rounds;
-  };
-  L.dwh_batched = batched(NL);
-  L.dwi_batched = batched(NL - 1);
   // what the forward pass leaves for the backward pass
   L.gates = take((size_t)NL * TB * 4 * H * 4);
   L.cs = take((size_t)NL * (T + 1) * L.BH * 4);

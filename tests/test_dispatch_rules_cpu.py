@@ -120,6 +120,18 @@ def test_workspace_of_one_lstm_step():
     assert bd.load_library().lstm_stack_workspace_bytes(ctypes.byref(shape)) <= 64 << 20
 
 
+def test_lstm_workspace_has_no_partial_sums_for_products_that_are_not_split():
+    """12800 rows, four layers of 1024 units: alone each weight gradient would be split in four (67 MB of partial sums); in
+    one launch for all layers none is, and those of dx (64 wide, 13 MB) are the largest left."""
+    T, B, I, H, L = 100, 128, 64, 1024, 4
+    assert _plan(4 * H, H, T * B, 1, bf16=True)[1] == 4
+    shape = bd.LsShape(T, B, I, H, L, bd.AS_BF16, 0.0, 0)
+    dx = 4 * T * B * I * 4
+    gates_and_states = L * T * B * 4 * H * 4 + L * (T + 1) * B * H * (4 + 2) + (L - 1) * T * B * H * 2
+    backward = L * T * B * 4 * H * 2 + dx + 2 * L * 4 * H * B * 2 + (2 * L - 1) * 4 * H * H * 2   # dG, its tiles, the weights'
+    assert bd.load_library().lstm_stack_workspace_bytes(ctypes.byref(shape)) <= gates_and_states + backward + (8 << 20)
+
+
 HIP_STUB = """
 #pragma once
 enum hipError_t { hipSuccess = 0, hipErrorUnknown = 1 };
