@@ -137,13 +137,7 @@ Layout make_layout(const as_shape* s) {
   L.p_q = gemm_plan(N, H, H, 1, bf, false);
   L.p_score = gemm_plan(T, S, H, B, bf, false);
   L.p_ctx = gemm_plan(T, H, S, B, bf, false);
-  // Segments: ctx (+ remainder), h_dec.  Each segment is cut into reduction tiles of its own, so the length to plan a
-  // split for counts whole tiles per segment: planned over 3 * H, sizes like H = 584 got a split with no tiles left.
-  L.p_hc = gemm_plan(N, H, bf ? 3 * (int)up(H, 64) : 2 * H, 1, bf, true, true);
-  // Few rows whose tiles would need a split over blocks and a combine launch, and a reduction that is short for one block.
-  // A decoder step, split / few: 512 units, 1 sentence 41.7 / 38.9 us, 16 54.4 / 52.4, 40 45.8 / 45.0, 128 50.7 / 50.5; 1024
-  // units, 1 sentence 48.2 / 47.0, 40 51.6 / 54.4, 200 70.9 / 82.5.
-  if (bf && N <= 128 && H <= 512 && L.p_hc.splits > 1) L.p_hc = {kTileFew, 1};
+  L.p_hc = plan_hc(N, H, bf);
   L.p_logits = gemm_plan(N, V, H, 1, bf, false);
   const bool counted = s->skip_pad_rows != 0;
   L.p_dwout = gemm_plan(V, H, N, 1, bf, true, false, counted);
@@ -162,10 +156,7 @@ Layout make_layout(const as_shape* s) {
   L.p_dq = gemm_plan(T, H, S, B, bf, false);
   L.p_ds = gemm_plan(S, H, T, B, bf, false);
   L.p_dwa = gemm_plan(H, H, N, 1, bf, true);
-  L.p_dh = gemm_plan(N, H, H, 1, bf, false);
-  // As for h_c, and here without a split to save.  A training step of one decoder step, 64 x 64 tiles / few: 4 sentences x 256
-  // units 83.0 / 82.0 us, 4 x 1024 108.9 / 105.8, 40 x 512 95.1 / 94.8, 128 x 1024 124.0 / 122.0.
-  if (bf && N <= 128 && H <= 1024 && L.p_dh.tile == kTile64) L.p_dh = {kTileFew, 1};
+  L.p_dh = plan_dh(N, H, bf);
 
   size_t off = 0;
   auto take = [&](size_t bytes) {

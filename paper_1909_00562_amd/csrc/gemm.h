@@ -119,6 +119,9 @@ struct GemmPlan {
 // counted: M or K is the bound of a size counted on the device (M_dev, K_dev), usually well above it
 GemmPlan gemm_plan(int M, int N, int K, int batch, bool bf16, bool allow_split, bool multi_segment = false,
                    bool counted = false);
+// the two products that may go to the kernel for few rows
+GemmPlan plan_hc(int N, int H, bool bf16);
+GemmPlan plan_dh(int N, int H, bool bf16);
 inline size_t gemm_partial_bytes(int M, int N, int batch, int splits) {
   return splits > 1 ? (size_t)splits * batch * M * N * sizeof(float) : 0;
 }

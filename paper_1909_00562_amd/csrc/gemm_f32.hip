@@ -692,6 +692,26 @@ GemmPlan gemm_plan(int M, int N, int K, int batch, bool bf16, bool allow_split, 
   return pl;
 }
 
+// h_c = tanh(W_c [ctx ; h_dec]) of N rows.  Segments: ctx (+ remainder), h_dec.  Each is cut into reduction tiles of its own,
+// so the length to plan a split for counts whole tiles per segment: planned over 3 * H, sizes like H = 584 got a split with no
+// tiles left.
+// Few rows whose tiles would need a split over blocks and a combine launch, with a reduction that is short for one block: the
+// planner splits from 449 units on, up to 127 rows of 456 units and 113 of 512.  us, split and combined / few: 456 units, 1 row
+// 7.6 / 4.2, 113 8.7 / 5.6; 512, 1 7.6 / 4.5, 16 8.0 / 5.4, 40 8.4 / 6.8, 113 8.6 / 6.9; past the line 576, 16 8.3 / 6.7, 40 8.6 / 8.7,
+// 640, 40 8.7 / 10.5, 1024, 16 8.9 / 8.8, 40 9.3 / 11.8.  (Fewer units are not split, and stay with the tiles.)
+GemmPlan plan_hc(int N, int H, bool bf16) {
+  const GemmPlan p = gemm_plan(N, H, bf16 ? 3 * ((H + 63) / 64 * 64) : 2 * H, 1, bf16, true, true);
+  return bf16 && N <= 128 && H <= 512 && p.splits > 1 ? GemmPlan{kTileFew, 1} : p;
+}
+// d_h_dec += dQ W_a^T of N rows: as for h_c, and here without a split to save.  us, 64 x 64 tiles / few: 128 units, 1 row 4.1 /
+// 3.3, 128 rows 4.7 / 4.0; 256, 40 4.9 / 4.6; 512, 17 5.8 / 5.5, 40 6.0 / 6.5, 128 6.2 / 6.6; 640, 17 6.3 / 5.9, 40 6.4 / 6.7; 768, 40
+// 6.8 / 6.4, 128 7.0 / 6.5; 1024, 1 7.2 / 4.4, 128 7.8 / 6.5; 1280, 128 8.6 / 10.6.
+GemmPlan plan_dh(int N, int H, bool bf16) {
+  const GemmPlan p = gemm_plan(N, H, H, 1, bf16, false);
+  const bool few = bf16 && N <= 128 && H <= 1024 && (N <= 32 || H <= 256 || H >= 768);
+  return few && p.tile == kTile64 ? GemmPlan{kTileFew, 1} : p;
+}
+
 hipError_t launch_gemm(const GemmArgs& g, bool in_bf16, GemmTile tile, hipStream_t st) {
   if (g.row_pos && g.splits <= 1) return hipErrorInvalidValue;
   hipError_t e = in_bf16 ? launch_gemm_bf16(g, tile, st) : launch_gemm_f32(g, st);

@@ -40,6 +40,34 @@ def _plan(M, N, K, batch, bf16, allow_split=True, multi_segment=False, counted=F
     return v & 0xffffffff, v >> 32
 
 
+def _plan_of(which, N, H, bf16=True):
+    """The same for h_c ("hc") or the last product of d_h_dec ("dh") of N rows; tile 3 = the kernel for few rows."""
+    v = _rule(f"_ZN3asx7plan_{which}Eiib", ctypes.c_uint64, I32, I32, ctypes.c_bool)(N, H, bf16)
+    return v & 0xffffffff, v >> 32
+
+
+FEW_ROWS_HC = [(1, 456), (16, 472), (17, 504), (113, 512), (127, 456)]     # (rows, units), the edges of its rows among them
+
+
+@pytest.mark.parametrize("N, H", FEW_ROWS_HC)
+def test_h_c_of_few_rows_goes_to_the_kernel_for_few_rows(N, H):
+    assert _plan_of("hc", N, H) == (3, 1)
+    assert _plan_of("hc", N, H, bf16=False)[0] != 3
+
+
+@pytest.mark.parametrize("N, H", [(1, 448), (114, 512), (128, 456), (1, 520), (40, 576), (16, 1024)])
+def test_h_c_of_other_sizes_stays_with_the_tiles(N, H):
+    assert _plan_of("hc", N, H)[0] != 3
+
+
+@pytest.mark.parametrize("N, H, few", [
+    (1, 64, True), (128, 256, True), (32, 512, True), (17, 640, True), (128, 768, True), (1, 1024, True), (128, 1024, True),
+    (33, 512, False), (128, 512, False), (40, 640, False), (33, 264, False), (129, 1024, False), (1, 1032, False)])
+def test_d_h_dec_of_few_rows_where_the_kernel_for_few_rows_was_faster(N, H, few):
+    assert (_plan_of("dh", N, H)[0] == 3) == few
+    assert _plan_of("dh", N, H, bf16=False)[0] != 3
+
+
 def _f32_split_bound(M, N, K, batch):
     tiles = -(-M // 64) * -(-N // 64) * batch
     if tiles >= 384:

@@ -24,16 +24,36 @@ def test_h_c_split_with_ragged_segments(shape):
     _parity(make_custom(T=T, S=S, B=B, H=H, V=V, seed=H, dtype="bf16", min_len=1, pad_prob=0.1))
 
 
-@pytest.mark.parametrize("shape", [(1, 3, 1, 136, 2003),      # one row; a reduction that ends inside a line
-                                   (2, 4, 8, 264, 2003),      # 16 rows, the last of one block form
-                                   (1, 5, 17, 328, 2003),     # 17, the first of the other; columns past a block
-                                   (4, 6, 32, 512, 2003),     # the most rows and the longest reduction
-                                   (3, 6, 43, 504, 2003)])    # one row more: tiles
+@pytest.mark.parametrize("shape", [(1, 3, 1, 136, 2003), (2, 4, 8, 264, 2003), (1, 5, 17, 328, 2003), (4, 6, 32, 512, 2003),
+                                   (3, 6, 43, 504, 2003)])
 def test_h_c_of_few_rows(shape):
+    """1 to 129 rows that need no split: one 64 x 64 tile of rows to three, reductions that end inside a tile."""
     T, S, B, H, V = shape
     inp = make_custom(T=T, S=S, B=B, H=H, V=V, seed=H, dtype="bf16", min_len=1, pad_prob=0.1)
     inp.dropout_p, inp.dropout_seed = 0.3, 11
     _parity(inp)
+
+
+@pytest.mark.parametrize("shape", [(1, 3, 1, 456, 2003),      # one row; a reduction that ends inside a line
+                                   (2, 4, 8, 472, 2003),      # 16 rows, the last of one block form; columns past a block
+                                   (1, 5, 17, 504, 2003),     # 17, the first of the other
+                                   (1, 6, 113, 512, 2003),    # the most rows of the longest reduction
+                                   (1, 4, 127, 456, 2003),    # the most rows
+                                   (1, 4, 128, 456, 2003)])   # one more: tiles
+def test_h_c_by_the_kernel_for_few_rows(shape):
+    """The sizes of test_h_c_of_few_rows_goes_to_the_kernel_for_few_rows: three segments, tanh, dropout and the saved
+    derivative."""
+    T, S, B, H, V = shape
+    inp = make_custom(T=T, S=S, B=B, H=H, V=V, seed=H + B, dtype="bf16", min_len=1, pad_prob=0.1)
+    inp.dropout_p, inp.dropout_seed = 0.3, 11
+    _parity(inp)
+
+
+@pytest.mark.parametrize("shape", [(32, 512), (33, 264), (128, 256), (128, 776), (33, 1024)])   # rows, units
+def test_d_h_dec_of_few_rows(shape):
+    """dQ W_a^T added to d_h_dec by the kernel for few rows, and (33 x 264) by tiles."""
+    B, H = shape
+    _parity(make_custom(T=1, S=7, B=B, H=H, V=2003, seed=H + B, dtype="bf16", min_len=1))
 
 
 @pytest.mark.parametrize("skip", [False, True])
