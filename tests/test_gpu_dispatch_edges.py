@@ -56,6 +56,19 @@ def test_d_h_dec_of_few_rows(shape):
     _parity(make_custom(T=1, S=7, B=B, H=H, V=2003, seed=H + B, dtype="bf16", min_len=1))
 
 
+@pytest.mark.parametrize("shape", [(1, 97, 72, 1032, 2)])      # T, B, I, H, L: 260 blocks, 66 of the largest form
+def test_lstm_one_step_in_blocks_of_16_units_and_32_sentences(shape):
+    """The form a decoder step of the largest model takes, with ragged edges in units, sentences and input."""
+    import test_gpu_lstm as tl
+    from synth_inputs import make_lstm_inputs
+    T, B, I, H, L = shape
+    for units in (H, H - 8 * 33):                              # (768: 192 blocks, one per compute unit at most)
+        inp = make_lstm_inputs(T, B, I, units, L, seed=units, dtype="bf16")
+        f, g, _ = tl.run_gpu(inp)
+        fo, go = tl.run_oracle(inp)
+        tl.compare(inp, f, g, fo, go)
+
+
 @pytest.mark.parametrize("skip", [False, True])
 @pytest.mark.parametrize("shape", [(20, 5, 13, 60, 16003),     # 64 x 64 tiles of logits and dW_out, ragged in every direction
                                    (3, 33, 11, 121, 999),      # rows that are not 16-byte aligned: scalar loads
