@@ -37,7 +37,8 @@ namespace {
 typedef uint32_t af_u32x4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) void af_glb_void_t;
 
-constexpr int AF_NW = 8;   // waves of a workgroup
+constexpr int AF_NW = 8;        // waves of a workgroup
+constexpr int kGridY = 65535;   // a grid's limit in y
 
 // alpha operand blocks: rows of 64 elements (128 bytes), chunk c of row r at chunk c ^ (r & 7) ^ ((r >> 3) & 1)
 __device__ __forceinline__ uint32_t kc_off(int row, int chunk) {
@@ -53,6 +54,7 @@ struct AttnFwdArgs {
   uint8_t* attn_mask;
   int T, S, B, H;
   int64_t ldS;
+  int y0;                                // first block of decoder steps of this launch
 };
 
 // LDS of a workgroup of 16 RT decoder steps x 16 ST source positions: a slot of NT x 16 columns of encoder states per wave;
@@ -78,7 +80,7 @@ __global__ __launch_bounds__(64 * AF_NW) void attn_fused_kernel(AttnFwdArgs p) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c16 = lane & 15, q4 = lane >> 4;
-  const int b = blockIdx.x, t0 = blockIdx.y * ROWS;
+  const int b = blockIdx.x, t0 = (p.y0 + blockIdx.y) * ROWS;
   const int T = p.T, S = p.S, H = p.H;
   const int64_t BH = (int64_t)p.B * H;
   int L = p.src_len[b];
@@ -264,7 +266,7 @@ __global__ __launch_bounds__(64 * AF_NW) void attn_fused_kernel(AttnFwdArgs p) {
           }
         }
       }
-    if (!BWD && p.attn_mask && blockIdx.y == 0)
+    if (!BWD && p.attn_mask && t0 == 0)
       for (int s = tid; s < S; s += 64 * NW) p.attn_mask[(int64_t)b * S + s] = s < L ? 1 : 0;
   }
   __builtin_amdgcn_s_waitcnt(0);   // the first chunk has landed (each wave reads its own slots only)
@@ -340,14 +342,19 @@ __global__ __launch_bounds__(64 * AF_NW) void attn_fused_kernel(AttnFwdArgs p) {
 
 bool attn_fwd_fused_supported(int S, int H) { return S >= 1 && S <= 128 && (H % 8) == 0; }
 
-template <bool BWD, int RT, int ST> static hipError_t launch_attn_shape(const AttnFwdArgs& p, hipStream_t st) {
+template <bool BWD, int RT, int ST> static hipError_t launch_attn_shape(AttnFwdArgs p, hipStream_t st) {
   auto k = attn_fused_kernel<BWD, RT, ST>;
   constexpr int smem = AttnLds<RT, ST>::kBytes;
   static LdsLimit limit;
   const hipError_t e = limit.raise(reinterpret_cast<const void*>(k), smem);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k, dim3(p.B, (p.T + 16 * RT - 1) / (16 * RT)), dim3(64 * AF_NW), smem, st, p);
-  return hipGetLastError();
+  const int ny = (p.T + 16 * RT - 1) / (16 * RT);
+  for (p.y0 = 0; p.y0 < ny; p.y0 += kGridY) {   // (more than a million decoder steps: several launches)
+    hipLaunchKernelGGL(k, dim3(p.B, ny - p.y0 < kGridY ? ny - p.y0 : kGridY), dim3(64 * AF_NW), smem, st, p);
+    const hipError_t launched = hipGetLastError();
+    if (launched != hipSuccess) return launched;
+  }
+  return hipSuccess;
 }
 template <bool BWD> static hipError_t launch_attn_fused(const AttnFwdArgs& p, hipStream_t st) {
   if (!attn_fwd_fused_supported(p.S, p.H) || p.B < 1 || p.T < 1 || p.ldS < p.S || p.ldS > 128) return hipErrorInvalidValue;

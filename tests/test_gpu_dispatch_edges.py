@@ -113,6 +113,29 @@ def test_fused_attention_at_tile_edges(shape):
     _parity(inp)
 
 
+def test_fused_attention_of_more_steps_than_a_grid_has_blocks():
+    """S > 64 takes 16 decoder steps per workgroup: 16 * 65536 + 64 steps need more workgroups than a grid may have in one
+    direction.  Every step repeats the one 64 before it, so its results do too, bit for bit."""
+    import torch
+    import paper_1909_00562_amd as lib
+    from paper_1909_00562_amd import binding as bd
+    P = 64
+    T = 16 * 65536 + P
+    inp = make_custom(T=P, S=65, B=1, H=8, V=8, seed=1, dtype="bf16", min_len=1, pad_prob=0.1)
+    results = lambda db: [db.view(bd.AS_VIEW_ALPHA)[0], db.view(bd.AS_VIEW_CTX)[:, 0], db.d_h_dec[:, 0]]
+    few = lib.DeviceBatch(inp)
+    few.fwd(), few.bwd(), few.sync()
+    first = [v.float() for v in results(few)]
+    inp.h_dec, inp.targets = np.tile(inp.h_dec, (T // P, 1, 1)), np.tile(inp.targets, (T // P, 1))
+    inp.T = T
+    db = lib.DeviceBatch(inp)
+    db.fwd(), db.bwd(), db.sync()
+    for v, f in zip(results(db), first):
+        rows = v.reshape(T // P, P, -1)
+        assert torch.equal(rows, rows[:1].expand_as(rows))
+        assert torch.allclose(rows[0].float(), f, rtol=1e-2, atol=1e-3)
+
+
 @pytest.mark.parametrize("dtype, H", [("bf16", 72), ("bf16", 520), ("f32", 68), ("f32", 67)])   # f32, 67: no whole vectors
 @pytest.mark.parametrize("pad_prob", [0.0, 0.3, 0.97])         # all rows, some, a row or two of 35
 def test_split_dz_goes_straight_to_its_rows(dtype, H, pad_prob):
