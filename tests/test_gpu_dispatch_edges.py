@@ -113,6 +113,13 @@ def test_fused_attention_at_tile_edges(shape):
     _parity(inp)
 
 
+@pytest.mark.parametrize("shape", [(33, 64, 5, 1032, 2003), (3, 128, 2, 2056, 2003)])
+def test_fused_attention_of_wide_states_with_large_weights(shape):
+    """The same widths with the weights of the narrower ones, scores twice as large."""
+    T, S, B, H, V = shape
+    _parity(make_custom(T=T, S=S, B=B, H=H, V=V, seed=S, dtype="bf16", min_len=1, pad_prob=0.1, w=0.1))
+
+
 def test_fused_attention_of_more_steps_than_a_grid_has_blocks():
     """S > 64 takes 16 decoder steps per workgroup: 16 * 65536 + 64 steps need more workgroups than a grid may have in one
     direction.  Every step repeats the one 64 before it, so its results do too, bit for bit."""
