@@ -390,8 +390,9 @@ struct CombineDev {
 
 // Bound by memory: splits x 4 bytes read per element, 4 to 12 more for the gate and the outputs.  V columns per thread, the
 // gate and up to four splits requested together, 16-byte accesses throughout.  12145 of 16384 rows x 2048, two splits, gate
-// and remainder, back to their rows: 148 us (2.9 TB/s; an element at a time, and the rows in a pass of their own, 207 + 39);
-// 4287 of 6400 x 1024, three splits: 26.6 us (56 + 9).  One split after the other instead of together: 238 and 46.
+// and remainder, back to their rows: 148 us behind the product that has just written the partial sums (an element at a time,
+// and the rows in a pass of their own, 207 + 39), 102 with everything in memory (4.2 TB/s; a copy of as much 5.2); 4287 of 6400
+// x 1024, three splits: 26.6 us (56 + 9), 27.0 from memory.  One split after the other instead of together: 238 and 46.
 template <typename TIn, bool OUT_BF16, int V>
 __global__ __launch_bounds__(256) void splitk_combine_kernel(CombineDev p) {
   constexpr int Q = V > 4 ? 4 : V;            // columns of a vector access
@@ -584,16 +585,19 @@ static double plan_split_us(int M, int N, int batch, int splits) {
   return splits > 1 ? 2.0 * splits * (double)M * N * batch * 4.0 / 4e6 + 4.5 : 0.0;
 }
 // 64 x 64: 0.26 us per reduction tile and compute unit however many blocks share it, 0.8 per block.  (1920 x 512 x 1024 NN
-// 9.7 measured, 10.0 by this; 128 x 1024 x 3072 NT 17, 18.3; 2257 x 1000 x 1000 NN 20.6, 20.1; 1024 x 1024 x 6400 TN 34.7,
-// 31.8; 6400 x 1024 x 3072 NT 90, 98.)
+// 9.1 measured, 10.0 by this; 128 x 1024 x 3072 NT 14.5, 18.3; 2257 x 1000 x 1000 NN 19.3, 19.9; 1024 x 1024 x 6400 TN 30.8,
+// 31.8; 6400 x 1024 x 3072 NT 73.3, 98.)
 static double plan_us_64(int M, int N, int ktiles, int batch, int splits) {
   const int64_t blocks = (int64_t)((M + 63) / 64) * ((N + 63) / 64) * batch * splits;
   return (double)((blocks + 255) / 256) * (0.26 * ((ktiles + splits - 1) / splits) + 0.8) + 5.0 +
          plan_split_us(M, N, batch, splits);
 }
 // 128 x 128: 0.7 us per reduction tile with a compute unit to itself, 1.05 with two blocks on one.  (2257 x 1000 x 1000 NN
-// 18.6, 18.2; 6400 x 1024 x 1024 NN 24.9, 25.3, NT 24.0, 25.3; x 2048 NN 41.3, 42.1; 16000 x 512 x 1286 TN 31.5, 30.5;
-// 1286 x 16000 x 512 NT 44.6, 39.7, the 256 x 256 kernel 41.)
+// 18.1, 18.2; 6400 x 1024 x 1024 NN 23.5, 25.3, NT 22.8, 25.3; x 2048 NN 37.5, 42.1; 16000 x 512 x 1286 TN 28.0, 30.5; 1286 x
+// 16000 x 512 NT 39.3, 39.7, the 256 x 256 kernel 35.2.)  These are the rates of the loop that read a tile's fragments first;
+// the one that reads them between the matrix instructions takes 0.58 and 0.9.  They stand because the choices do: over 89
+// sizes of 16 to 16000 in every form, with every tile and ten splits timed, the plan is 0.5 % behind the best on average and
+// 9 % at most (48 x 376 x 8168 NN: 32 splits, 11.1 us, 16 10.2).
 static double plan_us_128(int M, int N, int ktiles, int batch, int splits) {
   const int64_t blocks = (int64_t)((M + 127) / 128) * ((N + 127) / 128) * batch * splits;
   const int k = (ktiles + splits - 1) / splits;

@@ -4,17 +4,19 @@
 // walks the whole reduction on one compute unit while the others idle; there are four times as many blocks with a
 // quarter of the work per reduction tile.  0.26 us per 64 reduction elements and compute unit, its LDS traffic (16 KiB in,
 // 32 KiB out), however many blocks share it.
-// 128 x 128 tiles: 0.67 us per 64 reduction elements with a compute unit to itself (four stages), 1.0 for two blocks that
-// share one (two stages each: 64 KiB of LDS per block).  Rates and the choice between the shapes: gemm_plan.
-// Loads go HBM -> LDS directly in every orientation, NST tiles ahead, one barrier per tile, no branch and the same
-// number of loads in flight at every wait (past the last tile they read out of range, i.e. zeros).
+// 128 x 128 tiles: 0.58 us per 64 reduction elements with a compute unit to itself (four stages; 0.5 where a quarter of the
+// units have one), 0.85 to 0.95 for two blocks that share one (two stages each: 64 KiB of LDS per block).  Rates and the
+// choice between the shapes: gemm_plan.
+// Loads go HBM -> LDS directly in every orientation, NST tiles ahead, one barrier per tile, no branch and the same number of
+// loads in flight at every wait; the last tiles have a loop without loads (LACED) or read out of range, i.e. zeros.
 // What bounds it is the stream of loads: without fragment reads and matrix instructions a tile takes 0.57 us (32 KiB per
 // compute unit, 57 bytes a nanosecond), contiguous operands or a fifth stage change nothing, operands that all blocks share
 // 0.49.  The rest was the chain barrier -> fragment reads -> matrix instructions of a wave that has its SIMD to itself, so
-// the reads of half a tile now run between the matrix instructions of the half before: 4096 x 1024 x 6400 TN 73.5 -> 67.6 us,
-// 6400 x 1024 x 3072 NT 81 -> 73.7, 2257 x 1000 x 3000 NT 46.2 -> 42.3, 6400 x 1024 x 2048 NN 47.3 -> 44.4 (16000 x 512 x
-// 1286 TN 30.3 -> 32).  At most 256 registers per wave keep the accumulators out of the other register half, from which the
-// compiler copies them around every matrix instruction of this loop.
+// the reads of half a tile run between the matrix instructions of the half before (gemm_tile_laced: where that is faster).
+// Without / with, and without loads past the end: 4096 x 1024 x 6400 TN 70.1 / 63.9 us, 1024 x 1024 x 6400 TN 62.0 / 54.0, 6400 x
+// 1024 x 3072 NT 53.5 / 49.9, 2257 x 1000 x 3000 NT 38.2 / 36.0, 6400 x 1024 x 2048 NN 40.9 / 38.7.  At most 256 registers per wave
+// keep the accumulators out of the other register half, from which the compiler copies them around every matrix instruction
+// of that loop.
 //   * reduction-contiguous operand: LDS [rows][64 k] as in gemm_bf16.hip;
 //   * strided operand: LDS [64 k][columns] as in memory, fragments by transposing reads.  A 16-lane group reads four
 //     k-rows x 32 bytes; the 32-byte segments of a row are XOR-swizzled so that the four land in different banks.

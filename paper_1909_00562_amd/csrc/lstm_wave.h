@@ -44,7 +44,7 @@ struct LsFwd {
   float *gates, *cs;               // [L][T,B,4H] i, f, g, o; [L][T+1,B,H] cell states
   void *hE, *out;                  // [L][T+1,B,H] states, [L - 1][T,B,H] outputs, storage type
   void* y;                         // [T,B,H] output of the top layer
-  float *hf, *cT;                  // [L][B,H] running h (ends as the final state); final c (or null)
+  float *hf, *cT;                  // [L][B,H] final h: h0 from the prepare launch, overwritten at a sentence's last step; final c (or null)
   const int32_t* lengths;
   int T, B, I, H, L;
   int w_rows;

@@ -23,8 +23,8 @@
 // were shortened: functions above the kernels, dropout and the backward tanh while the first fragments are on their way,
 // column sums by rotations in registers, 16 MB of stores of which the gates go past the caches).  Forward, launch and first
 // loads 3.5, reduction 12.5 (weights that all come from the L2 save 1.6), cells the rest, 5 of it the stores.  64 MB of
-// weights and 1 MB (forward) or 1.5 MB (backward) of fragments per compute unit make the reduction.  A launch per layer and step took 10.5 us each, 42 for what a wavefront does, and the input
-// products another 90 per layer.  Tried without gain: weights streamed past the caches (34.6 / 40.7 us), other tile orders
+// weights and 1 MB (forward) or 1.5 MB (backward) of fragments per compute unit make the reduction.  A launch per layer and
+// step took 10.5 us each, 42 for what a wavefront does, and the input products another 90 per layer.  Tried without gain: weights streamed past the caches (34.6 / 40.7 us), other tile orders
 // of the weights, two to four slots (30.0 / 28.9 / 28.4), 64 x 64 and 64 x 32 forward blocks (33.5, 34.0).
 #include "common.h"
 #include "lstm_wave.h"
@@ -121,20 +121,6 @@ __device__ __forceinline__ int ls_len(const int32_t* lengths, int b, int T) {
 }
 
 // Four consecutive elements, of which n are inside.  VEC (H % 4 == 0): all four are, and aligned.
-// the same past the caches, for what no wavefront reads again
-template <bool VEC> __device__ __forceinline__ void ls_st4_away(float* p, const f32x4_t& v, int n) {
-  if constexpr (VEC) {
-    __builtin_nontemporal_store(v, reinterpret_cast<f32x4_t*>(p));
-  } else {
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (e < n) p[e] = v[e];
-  }
-}
-template <bool VEC> __device__ __forceinline__ void ls_st4_away(uint16_t* p, const f32x4_t& v, int) {
-  const ls_u32x2_t w = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-  __builtin_nontemporal_store(w, reinterpret_cast<ls_u32x2_t*>(p));
-}
 template <bool VEC> __device__ __forceinline__ f32x4_t ls_ld4(const float* p, int n) {
   if constexpr (VEC) {
     return *reinterpret_cast<const f32x4_t*>(p);
@@ -149,6 +135,16 @@ template <bool VEC> __device__ __forceinline__ f32x4_t ls_ld4(const float* p, in
 template <bool VEC> __device__ __forceinline__ void ls_st4(float* p, const f32x4_t& v, int n) {
   if constexpr (VEC) {
     *reinterpret_cast<f32x4_t*>(p) = v;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (e < n) p[e] = v[e];
+  }
+}
+// the same past the caches, for what no wavefront reads again
+template <bool VEC> __device__ __forceinline__ void ls_st4_away(float* p, const f32x4_t& v, int n) {
+  if constexpr (VEC) {
+    __builtin_nontemporal_store(v, reinterpret_cast<f32x4_t*>(p));
   } else {
 #pragma unroll
     for (int e = 0; e < 4; ++e)
