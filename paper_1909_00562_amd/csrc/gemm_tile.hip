@@ -442,7 +442,7 @@ static hipError_t launch_tile_form(const GemmDev& d, GemmTile tile, int out_bf16
 // straight from the operands' rows into registers, PF - 1 lines ahead; the partial tiles meet in LDS and are added in wave
 // order, and the epilogue follows.  A hundred rows and a thousand columns are a few tiles of 64 x 64: those need a split over
 // blocks to fill the chip, and a split needs a second launch that reads the partial sums back.  What bounds this one is its
-// launch and one or two memory latencies: 16 x 512 x 1536 7.4 us, 10.6 split and combined.
+// launch and one or two memory latencies: 16 x 512 x 1536 5.4 us, 8.0 split and combined.
 // The columns of B are the rows of the matrix instruction, so that a lane holds four consecutive columns of a row of C.
 constexpr int kFewWaves = 8;
 // (by value: a choice between variables that a lambda refers to would keep them in memory)

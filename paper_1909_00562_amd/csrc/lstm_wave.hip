@@ -852,7 +852,7 @@ __global__ __launch_bounds__(256) void ls_bias_reduce_kernel(const float* __rest
 
 // ---- launches ----------------------------------------------------------------------
 // One step: making tiles (64 bytes moved per 16 used once) costs more than the rows' half-used lines do.  128 sentences, 1024
-// units: 17 us per layer from rows, 13 from tiles and 7 to make them.  From two steps on the tiles are read again.
+// units: 16 us per layer from rows, 13 from tiles and 7 to make them.  From two steps on the tiles are read again.
 template <typename TE> bool ls_reads_weight_rows(int T, int I, int H) {
   return T == 1 && I % LsGeom<TE>::kVec == 0 && H % LsGeom<TE>::kVec == 0;
 }
