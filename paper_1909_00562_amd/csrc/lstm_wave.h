@@ -99,5 +99,7 @@ hipError_t launch_ls_bias_reduce(const float* dbacc, const LsBiasOut& o, int L, 
 template <typename TE> bool ls_input_apart(int T, int I, int H, int L);
 // Whether forward wavefronts read the caller's weight rows instead of tiles made from them.
 template <typename TE> bool ls_reads_weight_rows(int T, int I, int H);
+// Reduction steps of those rows that a wave has in flight in the smaller blocks (bf16; K: input width of the layer).
+int ls_row_steps_in_flight(int K, int H);
 
 }  // namespace asx

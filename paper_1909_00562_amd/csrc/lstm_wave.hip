@@ -903,6 +903,18 @@ hipError_t launch_ls_bias_reduce(const float* dbacc, const LsBiasOut& o, int L, 
   return hipGetLastError();
 }
 
+// One step: how many steps of the weight rows, which come from memory, a wave of the smaller blocks has in flight; K: the
+// layer's input width.  With PF in flight PF - 1 - n % PF loads of n steps are past the end and waited for with the others, so
+// six only where they save two of those.  A layer-step of H units from H, 16 x 16 blocks, us with four / six: n = 1 (64) 5.8 / 6.7,
+// 4 (256) 7.8 / 6.8, 5 (320) 8.0 / 7.2, 6 (384) 8.1 / 9.8, 7 (448) 8.5 / 9.8, 10 (640) 9.8 / 10.0, 12 (768) 11.8 / 12.7, 14 (896) 11.9 /
+// 12.8, 16 (1024) 14.0 / 13.2, 17 (1088) 14.1 / 13.3, 20 (1280) 16.3 / 16.4, 22 (1408) 16.2 / 16.2; 16 x 32 blocks, 8 (512) 10.8 / 11.1,
+// 14 13.4 / 15.0, 16 16.0 / 15.6.  (Eight: 4 x 1024 units x 128 sentences 75.4, six 68.5.)
+int ls_row_steps_in_flight(int K, int H) {
+  constexpr int KST = LsGeom<uint16_t>::kKStep;
+  const int n = ((H + KST - 1) / KST + (K + KST - 1) / KST + LS_KS - 1) / LS_KS;
+  return 5 - n % 6 + 2 <= 3 - n % 4 ? 6 : 4;
+}
+
 template <typename TE, int NI, int NJ, int PF, int PF_ROWS = PF>
 static hipError_t ls_fwd_shape(const LsFwd& p, int d, int l_lo, int nl, hipStream_t st) {
   const unsigned grid = ls_grid((int64_t)nl * ((p.H + 4 * NI - 1) / (4 * NI)), (p.B + 16 * NJ - 1) / (16 * NJ));
@@ -933,18 +945,18 @@ template <typename TE> hipError_t launch_ls_wave_fwd(const LsFwd& p, int d, hipS
   const int nl = l_hi - l_lo + 1;
   if (nl < 1) return hipErrorInvalidValue;
   const int64_t b64 = (p.B + 63) / 64, b32 = (p.B + 31) / 32;
-  // The caller's rows come from memory, not from the caches: more steps in flight (one step, 4 x 1024 units x 128
-  // sentences, with the other changes to the cells: 72.1 us with four, 68.5 with six, 75.4 with eight).  Six take the
-  // registers of a second block, so not where compute units get one.
   // The largest block that still gives most compute units one: larger blocks load less per output (128 gate rows x 64
   // sentences: 512 bytes per reduction index for 8192 outputs).  1024 units x 128 sentences, 64 x 32 blocks against 128 x 64:
   // three layers 27.5 us (768 blocks) and 28.0 (192), four 34.0 (1024) and 29.4 (256).
   if constexpr (LsMma<TE>::kPair) {
     if (nl * ((p.H + 31) / 32) * b64 >= 192) return ls_fwd_shape<TE, 8, 4, 3>(p, d, l_lo, nl, st);
     const int64_t blocks = nl * ((p.H + 15) / 16) * b32;
-    if (blocks > 256) return ls_fwd_shape<TE, 4, 2, 4>(p, d, l_lo, nl, st);
-    if (blocks >= 192) return ls_fwd_shape<TE, 4, 2, 4, 6>(p, d, l_lo, nl, st);
-    return ls_fwd_shape<TE, 4, 1, 4, 6>(p, d, l_lo, nl, st);
+    const bool six = p.w_rows && ls_row_steps_in_flight(l_lo == 0 ? p.I : p.H, p.H) == 6;   // (one step: one layer)
+    // (six take the registers of a second block of 16 x 32: not where compute units get one)
+    if (blocks >= 192 && six && blocks <= 256) return ls_fwd_shape<TE, 4, 2, 4, 6>(p, d, l_lo, nl, st);
+    if (blocks >= 192) return ls_fwd_shape<TE, 4, 2, 4>(p, d, l_lo, nl, st);
+    if (six) return ls_fwd_shape<TE, 4, 1, 4, 6>(p, d, l_lo, nl, st);
+    return ls_fwd_shape<TE, 4, 1, 4>(p, d, l_lo, nl, st);
   } else {
     if (nl * ((p.H + 15) / 16) * b32 >= 512) return ls_fwd_shape<TE, 4, 2, 4>(p, d, l_lo, nl, st);
     return ls_fwd_shape<TE, 4, 1, 4>(p, d, l_lo, nl, st);

@@ -148,6 +148,15 @@ def test_workspace_of_one_lstm_step():
     assert bd.load_library().lstm_stack_workspace_bytes(ctypes.byref(shape)) <= 64 << 20
 
 
+@pytest.mark.parametrize("K, H, six", [
+    (256, 256, True), (256, 320, True), (320, 320, True), (256, 384, True), (1024, 1024, True), (1088, 1088, True),
+    (64, 64, False), (128, 128, False), (384, 384, False), (256, 448, False), (448, 448, False), (256, 512, False),
+    (640, 640, False), (704, 704, False), (768, 768, False), (896, 896, False), (256, 1024, False), (1280, 1280, False)])
+def test_lstm_one_step_has_six_steps_of_weight_rows_in_flight_where_that_was_faster(K, H, six):
+    """Four or six steps ahead, both measured at these widths: no layer-step may be slower than with four."""
+    assert _rule("_ZN3asx22ls_row_steps_in_flightEii", ctypes.c_int, I32, I32)(K, H) == (6 if six else 4)
+
+
 def test_lstm_workspace_has_no_partial_sums_for_products_that_are_not_split():
     """12800 rows, four layers of 1024 units: alone each weight gradient would be split in four (67 MB of partial sums); in
     one launch for all layers none is, and those of dx (64 wide, 13 MB) are the largest left."""

@@ -62,7 +62,8 @@ def test_lstm_one_step_in_blocks_of_16_units_and_32_sentences(shape):
     import test_gpu_lstm as tl
     from synth_inputs import make_lstm_inputs
     T, B, I, H, L = shape
-    for units in (H, H - 8 * 33):                              # (768: 192 blocks, one per compute unit at most)
+    # (1024 and 768: 256 and 192 blocks, one per compute unit at most, with six and four steps of the weight rows in flight)
+    for units in (H, H - 8, H - 8 * 33):
         inp = make_lstm_inputs(T, B, I, units, L, seed=units, dtype="bf16")
         f, g, _ = tl.run_gpu(inp)
         fo, go = tl.run_oracle(inp)

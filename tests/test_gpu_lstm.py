@@ -161,6 +161,8 @@ def test_cell_functions_at_special_arguments():
                                    (3, 97, 72, 1032, 2),      # 16 units x 32 sentences at one step
                                    (2, 225, 24, 648, 1),      # the same, more blocks than compute units
                                    (2, 385, 72, 1032, 1),     # 32 x 64
+                                   (2, 97, 1000, 1024, 2),    # 16 x 32, six steps of the weight rows in flight
+                                   (3, 21, 264, 328, 2),      # 16 x 16, six in layer 0, four in layer 1
                                    (4, 16, 256, 512, 2)])     # 16 x 16
 def test_lstm_one_step_at_a_time_gives_the_bits_of_the_sequence(shape, dtype):
     """A decoder that advances the stack word by word from the states it got back follows the training pass exactly: one
