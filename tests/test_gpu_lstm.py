@@ -290,6 +290,17 @@ def test_lstm_dropout_between_layers(shape, dtype):
     assert np.array_equal(fz["y"], fp["y"])
 
 
+@pytest.mark.parametrize("shape", [(5, 7, 10, 219, 3), (4, 33, 9, 50, 2), (2, 3, 5, 3, 2)])
+def test_lstm_dropout_of_widths_that_are_no_whole_vectors(shape):
+    """fp32 rows of odd length: the masks of both passes are drawn an element at a time."""
+    T, B, I, H, L = shape
+    inp = make_lstm_inputs(T, B, I, H, L, seed=900 + T + H, dtype="f32")
+    inp.dropout_p, inp.dropout_seed = 0.3, 20190900562 + T
+    f, g, _ = run_gpu(inp)
+    fo, go = run_oracle(inp)
+    compare(inp, f, g, fo, go)
+
+
 def test_lstm_dropout_paper_size_sixteen_sentences():
     inp = make_lstm_inputs(50, 16, 512, 1024, 4, seed=1910, dtype="bf16", min_len=20)
     inp.dropout_p, inp.dropout_seed = 0.3, 5
