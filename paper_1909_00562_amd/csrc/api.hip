@@ -544,25 +544,24 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
   {  // dW_c = dz^T [ctx ; h_dec]: the two halves as one launch of two products that share dz; the second operand
      // of half 1 is the caller's h_dec, reached from ctx through a "batch stride" that is just the distance
      // between the two buffers (both 16-byte aligned, so it is a whole number of 8-element vectors)
-    GemmArgs g;
+    GemmArgs g[2];
     const int64_t h_dec_from_ctx = (hd - (w + L.ctx)) / (int64_t)L.e;
-    g.seg(w + L.dz, H, 0, w + L.ctx, H, h_dec_from_ctx, N);
-    g.a_kc = false; g.b_kc = false;
-    g.M = H; g.N = H; g.batch = 2;
-    g.C = dW_c; g.ldc = 2 * H; g.sC = H; g.c_bf16 = false;
-    g.splits = L.p_dwc.splits; g.partial = partial;
-    AS_TRY(AS_STAGE_GEMM_DWC, launch_gemm(g, bf, L.p_dwc.tile, st));
-  }
-  if (L.dch_pair) {   // both of the next two as one launch: half W_c's columns each
-    GemmArgs g;
-    g.seg(w + L.dz, H, 0, wc, 2 * H, H, H);
-    g.seg(w + L.dz_lo, H, 0, wc, 2 * H, H, H);
-    g.a_kc = true; g.b_kc = false;
-    g.M = N; g.N = H; g.batch = 2;
-    g.C = w + L.dC; g.ldc = H; g.c_bf16 = bf;
-    g.C_lo = w + L.dC_lo;
-    g.C_second = d_h_dec;
-    AS_TRY(AS_STAGE_GEMM_DCH, launch_gemm(g, bf, kTile64, st));
+    g[0].seg(w + L.dz, H, 0, w + L.ctx, H, h_dec_from_ctx, N);
+    g[0].a_kc = false; g[0].b_kc = false;
+    g[0].M = H; g[0].N = H; g[0].batch = 2;
+    g[0].C = dW_c; g[0].ldc = 2 * H; g[0].sC = H; g[0].c_bf16 = false;
+    g[0].splits = L.p_dwc.splits; g[0].partial = partial;
+    if (L.dch_pair) {   // the next two as one product: half W_c's columns each
+      g[1].seg(w + L.dz, H, 0, wc, 2 * H, H, H);
+      g[1].seg(w + L.dz_lo, H, 0, wc, 2 * H, H, H);
+      g[1].a_kc = true; g[1].b_kc = false;
+      g[1].M = N; g[1].N = H; g[1].batch = 2;
+      g[1].C = w + L.dC; g[1].ldc = H; g[1].c_bf16 = bf;
+      g[1].C_lo = w + L.dC_lo;
+      g[1].C_second = d_h_dec;
+    }
+    const GemmTile tiles[2] = {L.p_dwc.tile, kTile64};
+    AS_TRY(AS_STAGE_GEMM_DWC, launch_gemm_together(g, tiles, L.dch_pair ? 2 : 1, bf, st));
   }
   if (!L.dch_pair) {  // dC = dz W_c[:, :H]
     GemmArgs g;
@@ -618,38 +617,38 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
       AS_TRY(AS_STAGE_ATTN_BWD, launch_gemm(g, bf, L.p_dq.tile, st));
     }
   }
-  if (!one_step) {  // d_h_enc_b = alpha_b^T dC_b + dscore_b^T Q_b  (rows s >= src_len[b]: alpha = dscore = 0)
-    GemmArgs g;
-    const int64_t sAl = (int64_t)T * L.ldS;
-    g.seg(w + L.alphaE, L.ldS, sAl, w + L.dC, BH, H, T);
-    g.seg(w + L.dscoreE, L.ldS, sAl, w + L.q, BH, H, T);
-    // first-order remainder terms of the two products
-    g.seg(w + L.alphaE_lo, L.ldS, sAl, w + L.dC, BH, H, T);
-    g.seg(w + L.alphaE, L.ldS, sAl, w + L.dC_lo, BH, H, T);
-    g.seg(w + L.dscoreE_lo, L.ldS, sAl, w + L.q, BH, H, T);
-    g.seg(w + L.dscoreE, L.ldS, sAl, w + L.q_lo, BH, H, T);
-    g.a_kc = false; g.b_kc = false;
-    g.M = S; g.N = H; g.batch = B;
-    g.C = d_h_enc; g.ldc = BH; g.sC = H; g.c_bf16 = false;
-    AS_TRY(AS_STAGE_ATTN_BWD, launch_gemm(g, bf, L.p_ds.tile, st));
-  }
+  // The last three products: one launch where dW_a and d_h_enc are for 64 x 64 tiles, d_h_dec with them whatever its own plan
+  // is (6400 x 1024 alone: 33 us in 128 x 128, 31 in 64 x 64; 128 x 1024: 6.5 by the kernel for few rows, 7.8).
+  GemmArgs g[3];
   {  // dW_a = h_dec^T dQ
-    GemmArgs g;
-    g.seg(hd, H, 0, w + L.dQ, H, 0, N);
-    g.a_kc = false; g.b_kc = false;
-    g.M = H; g.N = H;
-    g.C = dW_a; g.ldc = H; g.c_bf16 = false;
-    g.splits = L.p_dwa.splits; g.partial = partial;
-    AS_TRY(AS_STAGE_GEMM_DWA, launch_gemm(g, bf, L.p_dwa.tile, st));
+    g[0].seg(hd, H, 0, w + L.dQ, H, 0, N);
+    g[0].a_kc = false; g[0].b_kc = false;
+    g[0].M = H; g[0].N = H;
+    g[0].C = dW_a; g[0].ldc = H; g[0].c_bf16 = false;
+    g[0].splits = L.p_dwa.splits; g[0].partial = partial;
   }
   {  // d_h_dec += dQ W_a^T
-    GemmArgs g;
-    g.seg(w + L.dQ, H, 0, W_a, H, 0, H);
-    g.a_kc = true; g.b_kc = true;
-    g.M = N; g.N = H;
-    g.C = d_h_dec; g.ldc = H; g.c_bf16 = false; g.accumulate = 1;
-    AS_TRY(AS_STAGE_GEMM_DH, launch_gemm(g, bf, L.p_dh.tile, st));
+    g[1].seg(w + L.dQ, H, 0, W_a, H, 0, H);
+    g[1].a_kc = true; g[1].b_kc = true;
+    g[1].M = N; g[1].N = H;
+    g[1].C = d_h_dec; g[1].ldc = H; g[1].c_bf16 = false; g[1].accumulate = 1;
   }
+  if (!one_step) {  // d_h_enc_b = alpha_b^T dC_b + dscore_b^T Q_b  (rows s >= src_len[b]: alpha = dscore = 0)
+    const int64_t sAl = (int64_t)T * L.ldS;
+    g[2].seg(w + L.alphaE, L.ldS, sAl, w + L.dC, BH, H, T);
+    g[2].seg(w + L.dscoreE, L.ldS, sAl, w + L.q, BH, H, T);
+    // first-order remainder terms of the two products
+    g[2].seg(w + L.alphaE_lo, L.ldS, sAl, w + L.dC, BH, H, T);
+    g[2].seg(w + L.alphaE, L.ldS, sAl, w + L.dC_lo, BH, H, T);
+    g[2].seg(w + L.dscoreE_lo, L.ldS, sAl, w + L.q, BH, H, T);
+    g[2].seg(w + L.dscoreE, L.ldS, sAl, w + L.q_lo, BH, H, T);
+    g[2].a_kc = false; g[2].b_kc = false;
+    g[2].M = S; g[2].N = H; g[2].batch = B;
+    g[2].C = d_h_enc; g[2].ldc = BH; g[2].sC = H; g[2].c_bf16 = false;
+  }
+  GemmTile tiles[3] = {L.p_dwa.tile, L.p_dh.tile, L.p_ds.tile};
+  if (L.p_dwa.tile == kTile64 && (one_step || L.p_ds.tile == kTile64)) tiles[1] = kTile64;
+  AS_TRY(AS_STAGE_GEMM_DWA, launch_gemm_together(g, tiles, one_step ? 2 : 3, bf, st));
   return AS_OK;
 }
 

@@ -994,14 +994,14 @@ static hipError_t launch_oriented(const GemmArgs& g, const GemmDev& d, hipStream
 
 static bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
-hipError_t launch_gemm_bf16(const GemmArgs& g, GemmTile tile, hipStream_t st) {
+// checks of a product and its description for the kernels
+static hipError_t gemm_describe(const GemmArgs& g, GemmTile tile, GemmDev& d) {
   const bool big_tile = tile == kTile256;
   if (g.M < 1 || g.N < 1 || g.batch < 1 || g.splits < 1) return hipErrorInvalidValue;
   // split-K: the combine step applies the epilogue; the persistent kernel splits a single segment only
   if (g.splits > 1 && (g.partial == nullptr || (big_tile && g.K[1] != 0))) return hipErrorInvalidValue;
   if (g.drop_thr && g.batch != 1) return hipErrorInvalidValue;   // flat element index = m * N + n
   if ((g.C_lo || g.C_dact) && !g.c_bf16) return hipErrorInvalidValue;
-  GemmDev d;
   for (int s = 0; s < kMaxSeg; ++s) {
     d.A[s] = reinterpret_cast<const uint16_t*>(g.A[s]);
     d.B[s] = reinterpret_cast<const uint16_t*>(g.B[s]);
@@ -1074,6 +1074,25 @@ hipError_t launch_gemm_bf16(const GemmArgs& g, GemmTile tile, hipStream_t st) {
   d.kper = ((ktiles + g.splits - 1) / g.splits) * BK;
   if (g.splits > 1 && !g.dyn_split && (int64_t)(d.kper / BK) * (g.splits - 1) >= ktiles)
     return hipErrorInvalidValue;   // an empty split
+  return hipSuccess;
+}
+
+hipError_t launch_gemm_bf16_together(const GemmArgs* g, int n, hipStream_t st) {
+  if (n < 1 || n > kMaxTogether) return hipErrorInvalidValue;
+  GemmDev d[kMaxTogether];
+  TileForm f[kMaxTogether];
+  for (int i = 0; i < n; ++i) {
+    const hipError_t e = gemm_describe(g[i], kTile64, d[i]);
+    if (e != hipSuccess) return e;
+    f[i] = {g[i].a_kc, g[i].b_kc, g[i].c_bf16 && g[i].splits <= 1};
+  }
+  return launch_gemm_bf16_tiles_together(d, f, n, st);
+}
+
+hipError_t launch_gemm_bf16(const GemmArgs& g, GemmTile tile, hipStream_t st) {
+  GemmDev d;
+  const hipError_t e = gemm_describe(g, tile, d);
+  if (e != hipSuccess) return e;
   if (tile == kTileFew) {
     if (!g.a_kc || !g.b_kc || d.nz != 1 || g.M_dev || g.K_dev || d.n_out != g.N) return hipErrorInvalidValue;
     return launch_gemm_bf16_few(d, g.c_bf16, st);

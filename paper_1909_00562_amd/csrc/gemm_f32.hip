@@ -724,4 +724,19 @@ hipError_t launch_gemm(const GemmArgs& g, bool in_bf16, GemmTile tile, hipStream
   return e;
 }
 
+hipError_t launch_gemm_together(const GemmArgs* g, const GemmTile* tile, int n, bool in_bf16, hipStream_t st) {
+  hipError_t e = hipErrorNotSupported;
+  bool small = in_bf16;
+  for (int i = 0; i < n; ++i) small = small && tile[i] == kTile64 && !(g[i].row_pos && g[i].splits <= 1);
+  if (small) e = launch_gemm_bf16_together(g, n, st);
+  if (e == hipErrorNotSupported) {
+    for (int i = 0; i < n; ++i)
+      if ((e = launch_gemm(g[i], in_bf16, tile[i], st)) != hipSuccess) return e;
+    return e;
+  }
+  for (int i = 0; i < n && e == hipSuccess; ++i)
+    if (g[i].splits > 1) e = launch_splitk_combine(g[i], in_bf16, st);
+  return e;
+}
+
 }  // namespace asx

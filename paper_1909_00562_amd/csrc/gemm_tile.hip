@@ -152,18 +152,17 @@ __device__ __forceinline__ void gs_finish_ragged(const GemmDev& p, int out_bf16,
   }
 }
 
+// Block `pid` of product z (batch and split) of a launch, NST * 2 * 32 TW * ROWB bytes of LDS at smem.
 template <int TW, bool AKC, bool BKC, int NST, bool LACED, bool SECOND>
-__global__ __launch_bounds__(256, LACED ? 2 : 1) void gemm_bf16_tile_kernel(GemmDev p, int out_bf16) {
+__device__ __forceinline__ void gemm_bf16_tile_block(const GemmDev& p, int out_bf16, int pid, int z, unsigned char* smem) {
   constexpr int BM = 32 * TW, TILE = BM * ROWB, STAGE = 2 * TILE;   // square block tile; bytes of an operand tile, a stage
   constexpr int NL = TW, LD = BM + 4;                               // loads per wave, operand and tile; staging row (floats)
   static_assert((NST & (NST - 1)) == 0 && NST * STAGE >= 64 * LD * 4, "ring of a power of two; write-out staging");
-  extern __shared__ __align__(1024) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = (wave >> 1) * 16 * TW, wn = (wave & 1) * 16 * TW;
   const int Mv = dev_bound(p.M_dev, p.M), K0 = dev_bound(p.K_dev, p.K[0]);
   const int tiles_m = (Mv + BM - 1) / BM, nt = tiles_m * p.tiles_n;   // the grid was sized for p.M
-  int pid = blockIdx.x;
   if (pid >= nt) return;                                          // the whole block, before any barrier
   {  // each XCD gets a contiguous run of tiles, walked in groups of 8 tile rows
     const int xcd = pid & 7, idx = pid >> 3, per = nt >> 3, rem = nt & 7;
@@ -173,7 +172,7 @@ __global__ __launch_bounds__(256, LACED ? 2 : 1) void gemm_bf16_tile_kernel(Gemm
   const int gm = tiles_m - first_m < 8 ? tiles_m - first_m : 8;
   const int in_g = pid - gid * 8 * p.tiles_n;
   const int m0 = (first_m + in_g % gm) * BM, n0 = (in_g / gm) * BM;
-  const int z = blockIdx.z, batch = z / p.splits, split = z - batch * p.splits;
+  const int batch = z / p.splits, split = z - batch * p.splits;
   const bool second = SECOND && batch == 1;                      // segment 0 alone, to C_second
   const int nseg = second ? 1 : kMaxSeg;
 
@@ -397,6 +396,12 @@ __global__ __launch_bounds__(256, LACED ? 2 : 1) void gemm_bf16_tile_kernel(Gemm
   }
 }
 
+template <int TW, bool AKC, bool BKC, int NST, bool LACED, bool SECOND>
+__global__ __launch_bounds__(256, LACED ? 2 : 1) void gemm_bf16_tile_kernel(GemmDev p, int out_bf16) {
+  extern __shared__ __align__(1024) unsigned char smem[];
+  gemm_bf16_tile_block<TW, AKC, BKC, NST, LACED, SECOND>(p, out_bf16, blockIdx.x, blockIdx.z, smem);
+}
+
 template <int TW, bool AKC, bool BKC, int NST, bool LACED, bool SECOND = false>
 static hipError_t launch_tile_shape(const GemmDev& d, int out_bf16, hipStream_t st) {
   constexpr int BM = 32 * TW, smem = NST * 2 * BM * ROWB;
@@ -435,6 +440,91 @@ static hipError_t launch_tile_form(const GemmDev& d, GemmTile tile, int out_bf16
   if (blocks <= 256) return launch_tile_shape<4, AKC, BKC, 4, true>(d, out_bf16, st);
   if constexpr (AKC) return launch_tile_shape<4, AKC, BKC, 2, true>(d, out_bf16, st);
   return hipErrorInvalidValue;   // (not reached)
+}
+
+// ---- several products in one launch ------------------------------------------------
+// Independent products of one pass that each leave the chip half empty, or are over before a launch is: their blocks one
+// product behind the other in one grid, 64 x 64 tiles (64 KiB of LDS, two blocks on a compute unit).  The product whose blocks
+// walk the longest reduction comes first; the short blocks of the others fill in behind it.  A training step, apart / together
+// (dW_c with dC and dH1; dW_a with the last product of d_h_dec and d_h_enc): 1920 x 512 271 / 252 us, one step of 128 x 1024
+// 200 / 193, 6400 x 1024 (the latter three, 104 us of it apart) 1387 / 1377.
+template <int TW, bool AKC, bool BKC, int NST, bool LACED, bool SECOND = false>
+struct TileMember {
+  GemmDev d;
+  int out_bf16, tiles, blocks;   // blocks: of the grid, a multiple of 8 so that a product's blocks keep their XCDs
+  static constexpr int kSmem = NST * 2 * 32 * TW * ROWB;
+  void set(const GemmDev& dev, bool obf) {
+    d = dev;
+    out_bf16 = obf;
+    tiles = d.tiles_m * d.tiles_n;
+    blocks = (tiles * d.nz + 7) / 8 * 8;
+  }
+  __device__ __forceinline__ void run(int id, unsigned char* smem) const {
+    const int z = id / tiles;
+    if (z < d.nz) gemm_bf16_tile_block<TW, AKC, BKC, NST, LACED, SECOND>(d, out_bf16, id - z * tiles, z, smem);
+  }
+};
+template <typename F, typename... R>
+__device__ __forceinline__ void run_member(int id, unsigned char* smem, const F& f, const R&... rest) {
+  if constexpr (sizeof...(R) > 0) {
+    if (id >= f.blocks) return run_member(id - f.blocks, smem, rest...);
+  }
+  f.run(id, smem);
+}
+// last_first: the blocks of the last product come first
+template <typename... M> __global__ __launch_bounds__(256, 2) void gemm_bf16_together_kernel(int last_first, M... m) {
+  extern __shared__ __align__(1024) unsigned char smem[];
+  run_member(last_first ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x, smem, m...);
+}
+template <typename... M> static hipError_t launch_members(bool last_first, hipStream_t st, const M&... m) {
+  constexpr int sizes[] = {M::kSmem...};
+  int smem = 0;
+  for (int v : sizes) smem = v > smem ? v : smem;
+  auto kfn = gemm_bf16_together_kernel<M...>;
+  static LdsLimit limit;
+  const hipError_t e = limit.raise(reinterpret_cast<const void*>(kfn), smem);
+  if (e != hipSuccess) return e;
+  int64_t blocks = 0;
+  for (int64_t b : {(int64_t)m.blocks...}) blocks += b;
+  if (blocks > (1 << 24)) return hipErrorNotSupported;
+  hipLaunchKernelGGL(kfn, dim3((unsigned)blocks), dim3(256), smem, st, (int)last_first, m...);
+  return hipGetLastError();
+}
+using MemberTN = TileMember<2, false, false, 4, false>;
+using MemberTNLaced = TileMember<2, false, false, 4, true>;
+using MemberNNSecond = TileMember<2, true, false, 4, true, true>;
+using MemberNT = TileMember<2, true, true, 4, true>;
+
+static int tile_ktiles(const GemmDev& d) {   // reduction tiles of a block
+  int n = 0;
+  for (int s = 0; s < kMaxSeg; ++s) n += (d.K[s] + BK - 1) / BK;
+  return (n + d.splits - 1) / d.splits;
+}
+template <typename TN>
+static hipError_t launch_together_with(const GemmDev* d, const TileForm* f, int n, hipStream_t st) {
+  TN tn;
+  tn.set(d[0], f[0].out_bf16);
+  if (n == 2 && f[1].a_kc && !f[1].b_kc && d[1].C_second) {
+    MemberNNSecond nn;
+    nn.set(d[1], f[1].out_bf16);
+    return launch_members(tile_ktiles(d[1]) > tile_ktiles(d[0]), st, tn, nn);
+  }
+  if (n >= 2 && f[1].a_kc && f[1].b_kc) {
+    MemberNT nt;
+    nt.set(d[1], f[1].out_bf16);
+    if (n == 2) return launch_members(false, st, tn, nt);
+    TN last;
+    last.set(d[2], f[2].out_bf16);
+    if (!f[2].a_kc && !f[2].b_kc) return launch_members(false, st, tn, nt, last);
+  }
+  return hipErrorNotSupported;
+}
+hipError_t launch_gemm_bf16_tiles_together(const GemmDev* d, const TileForm* f, int n, hipStream_t st) {
+  if (n < 2 || f[0].a_kc || f[0].b_kc) return hipErrorNotSupported;
+  int64_t blocks = 0;
+  for (int i = 0; i < n; ++i) blocks += (int64_t)d[i].tiles_m * d[i].tiles_n * d[i].nz;
+  return gemm_tile_laced(false, blocks) ? launch_together_with<MemberTNLaced>(d, f, n, st)
+                                        : launch_together_with<MemberTN>(d, f, n, st);
 }
 
 // ---- few rows ----------------------------------------------------------------------

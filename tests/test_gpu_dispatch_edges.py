@@ -278,3 +278,13 @@ def test_bf16_products_with_several_blocks_per_compute_unit(shape):
     attention products and dW_a of the last)."""
     T, S, B, H, V = shape
     _parity(make_custom(T=T, S=S, B=B, H=H, V=V, seed=V + H, dtype="bf16", min_len=1, pad_prob=0.1))
+
+
+@pytest.mark.parametrize("shape", [(1, 9, 3, 72, 2003),        # two products behind dQ, fewer blocks than the XCDs share evenly
+                                   (5, 6, 7, 136, 2003),       # three, 9 + 3 + 21 blocks of ragged tiles
+                                   (30, 7, 61, 264, 2003),     # more than 256 blocks; dW_c the one with the longer reduction
+                                   (2, 7, 61, 520, 2003)])     # dC and dH1 the one
+def test_bf16_products_of_a_pass_in_one_launch(shape):
+    """dW_c with dC and dH1, and dW_a with d_h_dec and d_h_enc, blocks of one product behind those of another."""
+    T, S, B, H, V = shape
+    _parity(make_custom(T=T, S=S, B=B, H=H, V=V, seed=V + H, dtype="bf16", min_len=1, pad_prob=0.1))
