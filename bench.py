@@ -443,6 +443,8 @@ def main():
         gemm_ms = {k: step_ms_by_stage.get(k, 0.0) for k in GEMM_STAGES}
         dom = max(gemm_ms, key=gemm_ms.get)
         flops = GEMM_STAGES[dom](N, R, H, V)
+        if dom == "gemm_dwout" and not gemm_ms["gemm_dhc"]:   # small sizes: both products in one launch
+            flops += GEMM_STAGES["gemm_dhc"](N, R, H, V)
         avg_ms = per_stage[dom]
         ach = flops / (avg_ms * 1e-3) / 1e12 if avg_ms > 0 else 0.0
         bf = inp.dtype == "bf16"

@@ -95,13 +95,14 @@ struct Layout {
   int64_t N, ldS, ldV;
   size_t e;  // bytes per stored element
   size_t q, scores, alpha32, alphaE, ctx, hc, logits, lse, tokloss;
-  size_t partial_hc, dz, dC, dalpha, dscoreE, dQ, dbpart, partial, total;
+  size_t partial_hc, dz, dC, dalpha, dscoreE, dQ, dbpart, partial, partial_dz, total;
   // rounding remainders (value - stored(value)) of operands made inside the attention core,
   // and the tanh derivative 1 - h_c^2 taken before h_c is rounded
   size_t q_lo, alphaE_lo, dC_lo, dscoreE_lo, dact, dz_lo, ctx_lo;
   // row compaction (skip_pad_rows): position <-> compacted row, the count, and the gathered / to-be-scattered blocks
   bool compact;
-  bool dch_pair;   // dC and dH1 in one launch
+  bool dch_pair;   // dC and dH1 as one product
+  bool out_pair;   // dW_out and dz in one launch where they have the tiles for it
   bool dz_scatter;   // compacted rows of dz go back to their places in a pass of their own (a split product's combine does it)
   bool dhc_dyn;   // the product with W_out in the backward pass picks its reduction split on the device
   size_t row_pos, rows, n_act, hc_c, dact_c, dz_c, dz_lo_c;
@@ -213,11 +214,15 @@ Layout make_layout(const as_shape* s) {
   }
   size_t pb = 0;
   auto mx = [&](size_t v) { if (v > pb) pb = v; };
-  mx(gemm_partial_bytes(V, H, 1, L.p_dwout.splits));
-  mx(gemm_partial_bytes(N, H, 1, L.p_dhc.splits));
+  const size_t pb_out = up(gemm_partial_bytes(V, H, 1, L.p_dwout.splits), kAlign);
+  L.out_pair = !bf && gemm_f32_small(V, H, L.p_dwout.splits) && gemm_f32_small(N, H, L.p_dhc.splits);
+  const size_t before_dz = L.out_pair ? pb_out : 0;   // in one launch the partial sums of both are alive together
+  mx(pb_out);
+  mx(before_dz + gemm_partial_bytes(N, H, 1, L.p_dhc.splits));
   mx(gemm_partial_bytes(H, H, 2, L.p_dwc.splits));
   mx(gemm_partial_bytes(H, H, 1, L.p_dwa.splits));
   L.partial = take(pb);
+  L.partial_dz = L.partial + before_dz;
   if (off < end) off = end;
   L.total = off;
   return L;
@@ -515,28 +520,31 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
                              reinterpret_cast<float*>(w + L.dbpart), rows, n_act, st));
   AS_TRY(AS_STAGE_MISC, launch_db_reduce(reinterpret_cast<const float*>(w + L.dbpart), L.nrb, V, db_out, n_act, L.rb, st));
   {  // dW_out = dlogits^T h_c
-    GemmArgs g;
-    g.seg(w + L.logits, L.ldV, 0, L.compact ? w + L.hc_c : w + L.hc, H, 0, N);
-    g.a_kc = false; g.b_kc = false;
-    g.M = V; g.N = H;
-    g.K_dev = n_act;     // compacted: the reduction runs over the non-pad rows only
-    g.C = dW_out; g.ldc = H; g.c_bf16 = false;
-    g.splits = L.p_dwout.splits; g.partial = partial;
-    AS_TRY(AS_STAGE_GEMM_DWOUT, launch_gemm(g, bf, L.p_dwout.tile, st));
-  }
-  {  // dz = (dlogits W_out) * (1 - h_c^2), the factor saved by the forward pass
-    GemmArgs g;
-    g.seg(w + L.logits, L.ldV, 0, W_out, H, 0, V);
-    g.a_kc = true; g.b_kc = false;
-    g.M = N; g.N = H;
-    g.gate = reinterpret_cast<const float*>(w + (L.compact ? L.dact_c : L.dact)); g.ldg = H;
-    g.C = w + (L.dz_scatter ? L.dz_c : L.dz); g.ldc = H; g.c_bf16 = bf;
-    g.C_lo = w + (L.dz_scatter ? L.dz_lo_c : L.dz_lo);
-    if (L.compact && !L.dz_scatter) g.row_pos = reinterpret_cast<const int32_t*>(w + L.row_pos);
-    g.M_dev = n_act;
-    g.dyn_split = L.dhc_dyn;
-    g.splits = L.p_dhc.splits; g.partial = partial;
-    AS_TRY(AS_STAGE_GEMM_DHC, launch_gemm(g, bf, L.p_dhc.tile, st));
+    GemmArgs g[2];
+    g[0].seg(w + L.logits, L.ldV, 0, L.compact ? w + L.hc_c : w + L.hc, H, 0, N);
+    g[0].a_kc = false; g[0].b_kc = false;
+    g[0].M = V; g[0].N = H;
+    g[0].K_dev = n_act;     // compacted: the reduction runs over the non-pad rows only
+    g[0].C = dW_out; g[0].ldc = H; g[0].c_bf16 = false;
+    g[0].splits = L.p_dwout.splits; g[0].partial = partial;
+    // dz = (dlogits W_out) * (1 - h_c^2), the factor saved by the forward pass
+    g[1].seg(w + L.logits, L.ldV, 0, W_out, H, 0, V);
+    g[1].a_kc = true; g[1].b_kc = false;
+    g[1].M = N; g[1].N = H;
+    g[1].gate = reinterpret_cast<const float*>(w + (L.compact ? L.dact_c : L.dact)); g[1].ldg = H;
+    g[1].C = w + (L.dz_scatter ? L.dz_c : L.dz); g[1].ldc = H; g[1].c_bf16 = bf;
+    g[1].C_lo = w + (L.dz_scatter ? L.dz_lo_c : L.dz_lo);
+    if (L.compact && !L.dz_scatter) g[1].row_pos = reinterpret_cast<const int32_t*>(w + L.row_pos);
+    g[1].M_dev = n_act;
+    g[1].dyn_split = L.dhc_dyn;
+    g[1].splits = L.p_dhc.splits; g[1].partial = reinterpret_cast<float*>(w + L.partial_dz);
+    const GemmTile tiles[2] = {L.p_dwout.tile, L.p_dhc.tile};
+    if (L.out_pair) {
+      AS_TRY(AS_STAGE_GEMM_DWOUT, launch_gemm_together(g, tiles, 2, bf, st));
+    } else {
+      AS_TRY(AS_STAGE_GEMM_DWOUT, launch_gemm(g[0], bf, tiles[0], st));
+      AS_TRY(AS_STAGE_GEMM_DHC, launch_gemm(g[1], bf, tiles[1], st));
+    }
   }
   if (L.dz_scatter)   // dz back to its time-major rows, zeros at the padding rows: the rest of the pass is per sentence
     AS_TRY(AS_STAGE_COMPACT, launch_scatter_rows(reinterpret_cast<const int32_t*>(w + L.row_pos), N, w + L.dz_c,
@@ -544,7 +552,7 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
   {  // dW_c = dz^T [ctx ; h_dec]: the two halves as one launch of two products that share dz; the second operand
      // of half 1 is the caller's h_dec, reached from ctx through a "batch stride" that is just the distance
      // between the two buffers (both 16-byte aligned, so it is a whole number of 8-element vectors)
-    GemmArgs g[2];
+    GemmArgs g[3];
     const int64_t h_dec_from_ctx = (hd - (w + L.ctx)) / (int64_t)L.e;
     g[0].seg(w + L.dz, H, 0, w + L.ctx, H, h_dec_from_ctx, N);
     g[0].a_kc = false; g[0].b_kc = false;
@@ -560,26 +568,22 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
       g[1].C_lo = w + L.dC_lo;
       g[1].C_second = d_h_dec;
     }
-    const GemmTile tiles[2] = {L.p_dwc.tile, kTile64};
-    AS_TRY(AS_STAGE_GEMM_DWC, launch_gemm_together(g, tiles, L.dch_pair ? 2 : 1, bf, st));
-  }
-  if (!L.dch_pair) {  // dC = dz W_c[:, :H]
-    GemmArgs g;
-    g.seg(w + L.dz, H, 0, wc, 2 * H, 0, H);
-    g.seg(w + L.dz_lo, H, 0, wc, 2 * H, 0, H);
-    g.a_kc = true; g.b_kc = false;
-    g.M = N; g.N = H;
-    g.C = w + L.dC; g.ldc = H; g.c_bf16 = bf;
-    g.C_lo = w + L.dC_lo;
-    AS_TRY(AS_STAGE_GEMM_DCH, launch_gemm(g, bf, L.p_dch.tile, st));
-  }
-  if (!L.dch_pair) {  // dH1 = dz W_c[:, H:]  -> d_h_dec
-    GemmArgs g;
-    g.seg(w + L.dz, H, 0, wc + (size_t)H * L.e, 2 * H, 0, H);
-    g.a_kc = true; g.b_kc = false;
-    g.M = N; g.N = H;
-    g.C = d_h_dec; g.ldc = H; g.c_bf16 = false;
-    AS_TRY(AS_STAGE_GEMM_DCH, launch_gemm(g, bf, L.p_dch.tile, st));
+    if (!L.dch_pair) {
+      // dC = dz W_c[:, :H]
+      g[1].seg(w + L.dz, H, 0, wc, 2 * H, 0, H);
+      g[1].seg(w + L.dz_lo, H, 0, wc, 2 * H, 0, H);
+      g[1].a_kc = true; g[1].b_kc = false;
+      g[1].M = N; g[1].N = H;
+      g[1].C = w + L.dC; g[1].ldc = H; g[1].c_bf16 = bf;
+      g[1].C_lo = w + L.dC_lo;
+      // dH1 = dz W_c[:, H:]  -> d_h_dec
+      g[2].seg(w + L.dz, H, 0, wc + (size_t)H * L.e, 2 * H, 0, H);
+      g[2].a_kc = true; g[2].b_kc = false;
+      g[2].M = N; g[2].N = H;
+      g[2].C = d_h_dec; g[2].ldc = H; g[2].c_bf16 = false;
+    }
+    const GemmTile tiles[3] = {L.p_dwc.tile, L.p_dch.tile, L.p_dch.tile};
+    AS_TRY(AS_STAGE_GEMM_DWC, launch_gemm_together(g, tiles, L.dch_pair ? 2 : 3, bf, st));
   }
   const bool one_step = bf && attn_one_step_bwd_supported(T, S, H);
   if (one_step) {

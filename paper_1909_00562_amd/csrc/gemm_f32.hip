@@ -118,12 +118,13 @@ struct F32Loader {
   }
 };
 
+// Block `pid` of product z (batch and split) of a launch; smem: f32_smem_floats<BM, BN>.
+template <int BM, int BN> constexpr int f32_smem_floats = 2 * (BM + BN) * FLD;
 template <int BM, int BN, int PF, bool AKC, bool BKC, bool AVEC, bool BVEC>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmDevF p) {
+__device__ __forceinline__ void gemm_f32_block(const GemmDevF& p, int pid, int z, float* smem) {
   static_assert(PF % 2 == 0, "a step's LDS stage is its slot's parity");
   constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 16, TN = WN / 16;
   constexpr int STAGE = (BM + BN) * FLD;   // floats
-  __shared__ __align__(16) float smem[2 * STAGE];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = (wave >> 1) * WM, wn = (wave & 1) * WN;
 
@@ -132,7 +133,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmDevF p) {
   const int Mv = dev_bound_f(p.M_dev, p.M);
   const int K0 = dev_bound_f(p.K_dev, p.K[0]);
   const int tiles_m = (Mv + BM - 1) / BM, nt = tiles_m * p.tiles_n;   // the grid was sized for p.M
-  int pid = blockIdx.x;
   if (pid >= nt) return;   // the whole block, before any barrier
   {
     const int xcd = pid & 7, idx = pid >> 3, per = nt >> 3, rem = nt & 7;
@@ -143,7 +143,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmDevF p) {
   const int in_g = pid - gid * 8 * p.tiles_n;
   const int m0 = (first_m + in_g % gm) * BM, n0 = (in_g / gm) * BN;
   const int kper = p.K_dev ? (((K0 + FK - 1) / FK + p.splits - 1) / p.splits) * FK : p.kper;
-  const int z = blockIdx.z;
   const int batch = z / p.splits, split = z - batch * p.splits;
 
   f64x4_t acc[TM][TN];
@@ -288,6 +287,12 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmDevF p) {
     }
 }
 
+template <int BM, int BN, int PF, bool AKC, bool BKC, bool AVEC, bool BVEC>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmDevF p) {
+  __shared__ __align__(16) float smem[f32_smem_floats<BM, BN>];
+  gemm_f32_block<BM, BN, PF, AKC, BKC, AVEC, BVEC>(p, blockIdx.x, blockIdx.z, smem);
+}
+
 // Block tile edge (64 or 32) for nz products of M x N.  With four blocks and more on every compute unit the 64 x 64 tile
 // is the faster one (4096^3: 2.25 ms = 61 TFLOP/s against 2.43 ms with 32 x 32); below that there are too few waves to
 // cover the loads, and the four times as many blocks of 32 x 32 win by far: 1286 x 512 x 16000 0.70 -> 0.53 ms,
@@ -295,6 +300,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmDevF p) {
 static int f32_tile(int M, int N, int nz) {
   return (int64_t)((M + 63) / 64) * ((N + 63) / 64) * nz >= 1024 ? 64 : 32;
 }
+
+bool gemm_f32_small(int M, int N, int nz) { return f32_tile(M, N, nz) == 32; }
 
 template <int BM, int BN, int PF, bool AKC, bool BKC>
 static hipError_t launch_f32_tile(GemmDevF& d, int batch, bool avec, bool bvec, hipStream_t st) {
@@ -314,13 +321,13 @@ static hipError_t launch_f32_oriented(GemmDevF& d, int batch, bool avec, bool bv
                                                     : launch_f32_tile<32, 32, 4, AKC, BKC>(d, batch, avec, bvec, st);
 }
 
-hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t st) {
+// checks of a product and its description for the kernels; avec, bvec: 16-byte loads of the operand
+static hipError_t f32_describe(const GemmArgs& g, GemmDevF& d, bool& avec, bool& bvec) {
   if (g.M < 1 || g.N < 1 || g.batch < 1 || g.splits < 1 || g.c_bf16) return hipErrorInvalidValue;
   if (g.splits > 1 && (g.K[1] != 0 || g.partial == nullptr)) return hipErrorInvalidValue;
   if (g.splits > 1 && (g.C_dact || g.drop_thr)) return hipErrorInvalidValue;
   if (g.drop_thr && g.batch != 1) return hipErrorInvalidValue;
-  GemmDevF d;
-  bool avec = true, bvec = true;
+  avec = bvec = true;
   for (int s = 0; s < kMaxSeg; ++s) {
     d.A[s] = reinterpret_cast<const float*>(g.A[s]);
     d.B[s] = reinterpret_cast<const float*>(g.B[s]);
@@ -363,10 +370,91 @@ hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t st) {
   const int ktiles = (g.K[0] + FK - 1) / FK;
   d.kper = ((ktiles + g.splits - 1) / g.splits) * FK;
   if (g.splits > 1 && (int64_t)d.kper * (g.splits - 1) >= g.K[0]) return hipErrorInvalidValue;
+  return hipSuccess;
+}
+
+hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t st) {
+  GemmDevF d;
+  bool avec, bvec;
+  const hipError_t e = f32_describe(g, d, avec, bvec);
+  if (e != hipSuccess) return e;
   if (g.a_kc && g.b_kc) return launch_f32_oriented<true, true>(d, g.batch, avec, bvec, st);
   if (g.a_kc && !g.b_kc) return launch_f32_oriented<true, false>(d, g.batch, avec, bvec, st);
   if (!g.a_kc && !g.b_kc) return launch_f32_oriented<false, false>(d, g.batch, avec, bvec, st);
   return hipErrorInvalidValue;  // (A strided, B contiguous) is not used by the path
+}
+
+// ---- several products in one launch: their blocks of 32 x 32 one product behind the other ----
+template <bool AKC, bool BKC, bool AVEC, bool BVEC = AVEC> struct F32Member {
+  GemmDevF d;
+  int tiles, blocks;   // blocks: of the grid, a multiple of 8 so that a product's blocks keep their XCDs
+  void set(const GemmDevF& dev, int batch) {
+    d = dev;
+    d.tiles_n = (d.N + 31) / 32;
+    tiles = (d.M + 31) / 32 * d.tiles_n;
+    blocks = (tiles * batch * d.splits + 7) / 8 * 8;
+  }
+  __device__ __forceinline__ void run(int id, int nz, float* smem) const {
+    const int z = id / tiles;
+    if (z < nz) gemm_f32_block<32, 32, 4, AKC, BKC, AVEC, BVEC>(d, id - z * tiles, z, smem);
+  }
+};
+struct F32Counts {
+  int nz[kMaxTogether];
+};
+template <int I, typename F, typename... R>
+__device__ __forceinline__ void run_f32_member(int id, const F32Counts& n, float* smem, const F& f, const R&... rest) {
+  if constexpr (sizeof...(R) > 0) {
+    if (id >= f.blocks) return run_f32_member<I + 1>(id - f.blocks, n, smem, rest...);
+  }
+  f.run(id, n.nz[I], smem);
+}
+template <typename... M> __global__ __launch_bounds__(256) void gemm_f32_together_kernel(F32Counts n, M... m) {
+  __shared__ __align__(16) float smem[f32_smem_floats<32, 32>];
+  run_f32_member<0>(blockIdx.x, n, smem, m...);
+}
+template <typename... M> static hipError_t launch_f32_members(const GemmArgs* g, const GemmDevF* d, hipStream_t st, M... m) {
+  F32Counts n{};
+  int i = 0;
+  ((m.set(d[i], g[i].batch), n.nz[i] = g[i].batch * g[i].splits, ++i), ...);
+  int64_t blocks = 0;
+  for (int64_t b : {(int64_t)m.blocks...}) blocks += b;
+  if (blocks > (1 << 24)) return hipErrorNotSupported;
+  hipLaunchKernelGGL(gemm_f32_together_kernel<M...>, dim3((unsigned)blocks), dim3(256), 0, st, n, m...);
+  return hipGetLastError();
+}
+// VEC: 16-byte loads of every operand but, without VEC_LAST, the A of the last of three
+template <bool VEC, bool VEC_LAST>
+static hipError_t launch_f32_together_with(const GemmArgs* g, const GemmDevF* d, int n, hipStream_t st) {
+  using TN = F32Member<false, false, VEC>;
+  using NN = F32Member<true, false, VEC>;
+  using NT = F32Member<true, true, VEC>;
+  const bool nn = g[1].a_kc && !g[1].b_kc, nt = g[1].a_kc && g[1].b_kc;
+  if constexpr (VEC == VEC_LAST) {
+    if (n == 2 && nn) return launch_f32_members(g, d, st, TN(), NN());
+    if (n == 3 && nn && g[2].a_kc && !g[2].b_kc) return launch_f32_members(g, d, st, TN(), NN(), NN());
+  }
+  if (n == 3 && nt && !g[2].a_kc && !g[2].b_kc)
+    return launch_f32_members(g, d, st, TN(), NT(), F32Member<false, false, VEC_LAST, VEC>());
+  return hipErrorNotSupported;
+}
+// Products that all go to 32 x 32 tiles; hipErrorNotSupported for the other combinations.  A training step of 32 rows x 64 units x
+// 1000 words, a launch each / the four groups: 105 / 87 us; of 1920 x 512 x 16000, whose products fill the chip: 1656 / 1650.
+static hipError_t launch_gemm_f32_together(const GemmArgs* g, int n, hipStream_t st) {
+  if (n < 2 || n > kMaxTogether || g[0].a_kc || g[0].b_kc) return hipErrorNotSupported;
+  GemmDevF d[kMaxTogether];
+  bool vec = true, vec_last = true;
+  for (int i = 0; i < n; ++i) {
+    bool avec, bvec;
+    const hipError_t e = f32_describe(g[i], d[i], avec, bvec);
+    if (e != hipSuccess) return e;
+    if (!gemm_f32_small(g[i].M, g[i].N, g[i].batch * g[i].splits)) return hipErrorNotSupported;
+    vec = vec && bvec && (avec || i == 2);   // (source positions, the rows of the last A, are rarely a multiple of four)
+    vec_last = vec_last && avec && bvec;
+  }
+  if (vec_last) return launch_f32_together_with<true, true>(g, d, n, st);
+  if (vec && n == 3 && g[1].b_kc) return launch_f32_together_with<true, false>(g, d, n, st);
+  return launch_f32_together_with<false, false>(g, d, n, st);
 }
 
 // ---- split-K combine: C = epilogue(sum_s partial[b*splits+s]) in fixed order --
@@ -727,8 +815,12 @@ hipError_t launch_gemm(const GemmArgs& g, bool in_bf16, GemmTile tile, hipStream
 hipError_t launch_gemm_together(const GemmArgs* g, const GemmTile* tile, int n, bool in_bf16, hipStream_t st) {
   hipError_t e = hipErrorNotSupported;
   bool small = in_bf16;
-  for (int i = 0; i < n; ++i) small = small && tile[i] == kTile64 && !(g[i].row_pos && g[i].splits <= 1);
+  for (int i = 0; i < n; ++i) {
+    if (g[i].row_pos && g[i].splits <= 1) return hipErrorInvalidValue;
+    small = small && tile[i] == kTile64;
+  }
   if (small) e = launch_gemm_bf16_together(g, n, st);
+  else if (!in_bf16) e = launch_gemm_f32_together(g, n, st);
   if (e == hipErrorNotSupported) {
     for (int i = 0; i < n; ++i)
       if ((e = launch_gemm(g[i], in_bf16, tile[i], st)) != hipSuccess) return e;
