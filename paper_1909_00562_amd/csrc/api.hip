@@ -89,6 +89,7 @@ struct StageTimer {
 
 // ---- workspace layout ------------------------------------------------------------
 constexpr size_t kAlign = 256;
+constexpr size_t kStaticScratchBytes = (size_t)64 << 20;   // of attn_softmax_fwd_static
 size_t up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 struct Layout {
@@ -123,6 +124,12 @@ bool shape_ok(const as_shape* s) {
   return true;
 }
 
+bool out_pair_bf16(int N, GemmPlan dwout, GemmPlan dz) {
+  if (dz.tile != kTile64 && dz.tile != kTile128) return false;
+  if (dz.tile == kTile128 && dwout.tile == kTile64) return false;
+  return dwout.tile != kTile256 || (N <= 512 && dwout.splits == 1);
+}
+
 Layout make_layout(const as_shape* s) {
   Layout L;
   const bool bf = s->dtype == AS_BF16;
@@ -148,6 +155,7 @@ Layout make_layout(const as_shape* s) {
   L.dhc_dyn = s->skip_pad_rows != 0 && bf && L.p_dhc.tile == kTile256;
   if (L.dhc_dyn && L.p_dhc.splits < 8) L.p_dhc.splits = 8;
   L.dz_scatter = s->skip_pad_rows != 0 && L.p_dhc.splits == 1;
+  L.out_pair = bf ? out_pair_bf16(N, L.p_dwout, L.p_dhc) : gemm_f32_small(V, H, L.p_dwout.splits) && gemm_f32_small(N, H, L.p_dhc.splits);
   L.p_dwc = gemm_plan(H, H, N, 2, bf, true);          // both halves of dW_c in one launch
   L.p_dch = gemm_plan(N, H, H, 1, bf, false);
   // dC and dH1 as one launch where both are for 64 x 64 tiles, i.e. small.  A training step, apart / together: one step of 128
@@ -214,15 +222,24 @@ Layout make_layout(const as_shape* s) {
   }
   size_t pb = 0;
   auto mx = [&](size_t v) { if (v > pb) pb = v; };
-  const size_t pb_out = up(gemm_partial_bytes(V, H, 1, L.p_dwout.splits), kAlign);
-  L.out_pair = !bf && gemm_f32_small(V, H, L.p_dwout.splits) && gemm_f32_small(N, H, L.p_dhc.splits);
-  const size_t before_dz = L.out_pair ? pb_out : 0;   // in one launch the partial sums of both are alive together
-  mx(pb_out);
-  mx(before_dz + gemm_partial_bytes(N, H, 1, L.p_dhc.splits));
+  mx(gemm_partial_bytes(V, H, 1, L.p_dwout.splits));
+  mx(gemm_partial_bytes(N, H, 1, L.p_dhc.splits));
   mx(gemm_partial_bytes(H, H, 2, L.p_dwc.splits));
   mx(gemm_partial_bytes(H, H, 1, L.p_dwa.splits));
-  L.partial = take(pb);
-  L.partial_dz = L.partial + before_dz;
+  L.partial = L.partial_dz = take(pb);
+  if (L.out_pair) {
+    // read while dz and the partial sums are written: places of their own, unless that alone would put the shape past the
+    // library's static scratch
+    const size_t apart = off < end ? end : off, apart_dbpart = L.dbpart;
+    L.dbpart = take((size_t)L.nrb * V * 4);
+    if (L.p_dwout.splits > 1 && L.p_dhc.splits > 1) L.partial_dz = take(gemm_partial_bytes(N, H, 1, L.p_dhc.splits));
+    if (apart <= kStaticScratchBytes && off > kStaticScratchBytes) {
+      L.out_pair = false;
+      L.dbpart = apart_dbpart;
+      L.partial_dz = L.partial;
+      off = apart;
+    }
+  }
   if (off < end) off = end;
   L.total = off;
   return L;
@@ -266,7 +283,6 @@ as_status check_common(const as_shape* s, const void* h_dec, const void* h_enc, 
 // The workspace of callers that cannot allocate: one array in the code object, so every GPU the library runs on
 // holds its own copy from module load until the process ends.  Host code never uses the array's name as an
 // address: the device address is looked up once per device and kept.
-constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace {
@@ -518,7 +534,8 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
          launch_xent_dlogits(w + L.logits, L.ldV, bf, N, V, targets, s->pad_id,
                              reinterpret_cast<const float*>(w + L.lse), s->grad_scale,
                              reinterpret_cast<float*>(w + L.dbpart), rows, n_act, st));
-  AS_TRY(AS_STAGE_MISC, launch_db_reduce(reinterpret_cast<const float*>(w + L.dbpart), L.nrb, V, db_out, n_act, L.rb, st));
+  const DbReduce sums = {reinterpret_cast<const float*>(w + L.dbpart), L.nrb, V, db_out, n_act, L.rb};
+  if (!L.out_pair) AS_TRY(AS_STAGE_MISC, launch_db_reduce(sums, st));
   {  // dW_out = dlogits^T h_c
     GemmArgs g[2];
     g[0].seg(w + L.logits, L.ldV, 0, L.compact ? w + L.hc_c : w + L.hc, H, 0, N);
@@ -538,12 +555,12 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
     g[1].M_dev = n_act;
     g[1].dyn_split = L.dhc_dyn;
     g[1].splits = L.p_dhc.splits; g[1].partial = reinterpret_cast<float*>(w + L.partial_dz);
-    const GemmTile tiles[2] = {L.p_dwout.tile, L.p_dhc.tile};
     if (L.out_pair) {
-      AS_TRY(AS_STAGE_GEMM_DWOUT, launch_gemm_together(g, tiles, 2, bf, st));
+      const GemmTile tiles[2] = {L.p_dwout.tile == kTile256 ? kTile128 : L.p_dwout.tile, L.p_dhc.tile};
+      AS_TRY(AS_STAGE_GEMM_DWOUT, launch_gemm_together(g, tiles, 2, bf, st, &sums));
     } else {
-      AS_TRY(AS_STAGE_GEMM_DWOUT, launch_gemm(g[0], bf, tiles[0], st));
-      AS_TRY(AS_STAGE_GEMM_DHC, launch_gemm(g[1], bf, tiles[1], st));
+      AS_TRY(AS_STAGE_GEMM_DWOUT, launch_gemm(g[0], bf, L.p_dwout.tile, st));
+      AS_TRY(AS_STAGE_GEMM_DHC, launch_gemm(g[1], bf, L.p_dhc.tile, st));
     }
   }
   if (L.dz_scatter)   // dz back to its time-major rows, zeros at the padding rows: the rest of the pass is per sentence

@@ -128,12 +128,15 @@ inline size_t gemm_partial_bytes(int M, int N, int batch, int splits) {
 
 // Enqueue; return hipSuccess or the launch error.  `in_bf16` selects the kernel family.
 hipError_t launch_gemm(const GemmArgs& g, bool in_bf16, GemmTile tile, hipStream_t st);
-// Products that do not depend on each other, in one launch where there is a kernel for the combination and all go to the
-// smallest tiles (bf16: kTile64; fp32: 32 x 32), else one after the other; splits are combined afterwards.
+// Products that do not depend on each other, in one launch where there is a kernel for the combination and its tiles (bf16:
+// kTile64, two of them also kTile128; fp32: 32 x 32), else one after the other; splits are combined afterwards.  sums: column
+// sums of dlogits beside {dW_out, dz}.
 constexpr int kMaxTogether = 3;
-hipError_t launch_gemm_together(const GemmArgs* g, const GemmTile* tile, int n, bool in_bf16, hipStream_t st);
+struct DbReduce;
+hipError_t launch_gemm_together(const GemmArgs* g, const GemmTile* tile, int n, bool in_bf16, hipStream_t st,
+                                const DbReduce* sums = nullptr);
 hipError_t launch_gemm_bf16(const GemmArgs& g, GemmTile tile, hipStream_t st);
-hipError_t launch_gemm_bf16_together(const GemmArgs* g, int n, hipStream_t st);   // 64 x 64 tiles, without the combines
+hipError_t launch_gemm_bf16_together(const GemmArgs* g, const GemmTile* tile, int n, const DbReduce* sums, hipStream_t st);   // without the combines
 hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t st);
 bool gemm_f32_small(int M, int N, int nz);   // nz products (batch and splits) of M x N go to tiles of 32 x 32
 // partial[batch*splits][M][N] -> C with the epilogue of g

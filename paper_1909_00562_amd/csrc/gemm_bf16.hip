@@ -1077,16 +1077,17 @@ static hipError_t gemm_describe(const GemmArgs& g, GemmTile tile, GemmDev& d) {
   return hipSuccess;
 }
 
-hipError_t launch_gemm_bf16_together(const GemmArgs* g, int n, hipStream_t st) {
+hipError_t launch_gemm_bf16_together(const GemmArgs* g, const GemmTile* tile, int n, const DbReduce* sums, hipStream_t st) {
   if (n < 1 || n > kMaxTogether) return hipErrorInvalidValue;
   GemmDev d[kMaxTogether];
   TileForm f[kMaxTogether];
   for (int i = 0; i < n; ++i) {
-    const hipError_t e = gemm_describe(g[i], kTile64, d[i]);
+    if (tile[i] != kTile64 && tile[i] != kTile128) return hipErrorNotSupported;
+    const hipError_t e = gemm_describe(g[i], tile[i], d[i]);
     if (e != hipSuccess) return e;
-    f[i] = {g[i].a_kc, g[i].b_kc, g[i].c_bf16 && g[i].splits <= 1};
+    f[i] = {g[i].a_kc, g[i].b_kc, g[i].c_bf16 && g[i].splits <= 1, tile[i]};
   }
-  return launch_gemm_bf16_tiles_together(d, f, n, st);
+  return launch_gemm_bf16_tiles_together(d, f, n, sums, st);
 }
 
 hipError_t launch_gemm_bf16(const GemmArgs& g, GemmTile tile, hipStream_t st) {

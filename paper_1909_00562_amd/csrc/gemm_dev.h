@@ -105,12 +105,14 @@ struct DirectLoader {
 
 // the 64 x 64 and 128 x 128 kernel (gemm_tile.hip); d as launch_gemm_bf16 has filled it in
 hipError_t launch_gemm_bf16_tile(const GemmDev& d, GemmTile tile, bool a_kc, bool b_kc, bool out_bf16, hipStream_t st);
-// Several products in 64 x 64 tiles in one launch; hipErrorNotSupported where there is no kernel for the combination:
-// {both strided, A contiguous with C_second}, {both strided, both contiguous}, the latter with another of both strided
+// Several products in one launch; hipErrorNotSupported where there is no kernel for the combination.  64 x 64 tiles: {both
+// strided, A contiguous with C_second}, {both strided, both contiguous}, the latter with another of both strided.  64 x 64 or
+// 128 x 128: {both strided, A contiguous}, sums beside them.
 struct TileForm {
   bool a_kc, b_kc, out_bf16;
+  GemmTile tile;
 };
-hipError_t launch_gemm_bf16_tiles_together(const GemmDev* d, const TileForm* f, int n, hipStream_t st);
+hipError_t launch_gemm_bf16_tiles_together(const GemmDev* d, const TileForm* f, int n, const DbReduce* sums, hipStream_t st);
 // whether that kernel's fragment reads run between its matrix instructions
 bool gemm_tile_laced(bool a_kc, int64_t blocks);
 // the kernel for few rows: both operands reduction-contiguous, up to three segments of the same length, no split, no batch

@@ -4,6 +4,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "db_reduce_dev.h"
 #include "gemm.h"
 
 namespace asx {
@@ -399,6 +400,13 @@ template <bool AKC, bool BKC, bool AVEC, bool BVEC = AVEC> struct F32Member {
     if (z < nz) gemm_f32_block<32, 32, 4, AKC, BKC, AVEC, BVEC>(d, id - z * tiles, z, smem);
   }
 };
+struct F32Sums {   // column sums of dlogits beside the products that read it
+  DbReduce d;
+  int blocks;
+  __device__ __forceinline__ void run(int id, int, float* smem) const {
+    if (id * kDbColumns < d.V) db_reduce_block<256>(d, id, smem);
+  }
+};
 struct F32Counts {
   int nz[kMaxTogether];
 };
@@ -411,36 +419,44 @@ __device__ __forceinline__ void run_f32_member(int id, const F32Counts& n, float
 }
 template <typename... M> __global__ __launch_bounds__(256) void gemm_f32_together_kernel(F32Counts n, M... m) {
   __shared__ __align__(16) float smem[f32_smem_floats<32, 32>];
+  static_assert(sizeof(smem) >= kDbSmem, "the column sums' share");
   run_f32_member<0>(blockIdx.x, n, smem, m...);
 }
-template <typename... M> static hipError_t launch_f32_members(const GemmArgs* g, const GemmDevF* d, hipStream_t st, M... m) {
-  F32Counts n{};
-  int i = 0;
-  ((m.set(d[i], g[i].batch), n.nz[i] = g[i].batch * g[i].splits, ++i), ...);
+template <typename... M> static hipError_t launch_f32_grid(const F32Counts& n, hipStream_t st, const M&... m) {
   int64_t blocks = 0;
   for (int64_t b : {(int64_t)m.blocks...}) blocks += b;
   if (blocks > (1 << 24)) return hipErrorNotSupported;
   hipLaunchKernelGGL(gemm_f32_together_kernel<M...>, dim3((unsigned)blocks), dim3(256), 0, st, n, m...);
   return hipGetLastError();
 }
+template <typename... M>
+static hipError_t launch_f32_members(const GemmArgs* g, const GemmDevF* d, const DbReduce* sums, hipStream_t st, M... m) {
+  F32Counts n{};
+  int i = 0;
+  ((m.set(d[i], g[i].batch), n.nz[i] = g[i].batch * g[i].splits, ++i), ...);
+  if constexpr (sizeof...(M) == 2) {
+    if (sums) return launch_f32_grid(n, st, m..., F32Sums{*sums, (sums->V + kDbColumns - 1) / kDbColumns});
+  }
+  return sums ? hipErrorNotSupported : launch_f32_grid(n, st, m...);
+}
 // VEC: 16-byte loads of every operand but, without VEC_LAST, the A of the last of three
 template <bool VEC, bool VEC_LAST>
-static hipError_t launch_f32_together_with(const GemmArgs* g, const GemmDevF* d, int n, hipStream_t st) {
+static hipError_t launch_f32_together_with(const GemmArgs* g, const GemmDevF* d, int n, const DbReduce* sums, hipStream_t st) {
   using TN = F32Member<false, false, VEC>;
   using NN = F32Member<true, false, VEC>;
   using NT = F32Member<true, true, VEC>;
   const bool nn = g[1].a_kc && !g[1].b_kc, nt = g[1].a_kc && g[1].b_kc;
   if constexpr (VEC == VEC_LAST) {
-    if (n == 2 && nn) return launch_f32_members(g, d, st, TN(), NN());
-    if (n == 3 && nn && g[2].a_kc && !g[2].b_kc) return launch_f32_members(g, d, st, TN(), NN(), NN());
+    if (n == 2 && nn) return launch_f32_members(g, d, sums, st, TN(), NN());
+    if (n == 3 && nn && g[2].a_kc && !g[2].b_kc) return launch_f32_members(g, d, sums, st, TN(), NN(), NN());
   }
   if (n == 3 && nt && !g[2].a_kc && !g[2].b_kc)
-    return launch_f32_members(g, d, st, TN(), NT(), F32Member<false, false, VEC_LAST, VEC>());
+    return launch_f32_members(g, d, sums, st, TN(), NT(), F32Member<false, false, VEC_LAST, VEC>());
   return hipErrorNotSupported;
 }
 // Products that all go to 32 x 32 tiles; hipErrorNotSupported for the other combinations.  A training step of 32 rows x 64 units x
 // 1000 words, a launch each / the four groups: 105 / 87 us; of 1920 x 512 x 16000, whose products fill the chip: 1656 / 1650.
-static hipError_t launch_gemm_f32_together(const GemmArgs* g, int n, hipStream_t st) {
+static hipError_t launch_gemm_f32_together(const GemmArgs* g, int n, const DbReduce* sums, hipStream_t st) {
   if (n < 2 || n > kMaxTogether || g[0].a_kc || g[0].b_kc) return hipErrorNotSupported;
   GemmDevF d[kMaxTogether];
   bool vec = true, vec_last = true;
@@ -452,9 +468,9 @@ static hipError_t launch_gemm_f32_together(const GemmArgs* g, int n, hipStream_t
     vec = vec && bvec && (avec || i == 2);   // (source positions, the rows of the last A, are rarely a multiple of four)
     vec_last = vec_last && avec && bvec;
   }
-  if (vec_last) return launch_f32_together_with<true, true>(g, d, n, st);
-  if (vec && n == 3 && g[1].b_kc) return launch_f32_together_with<true, false>(g, d, n, st);
-  return launch_f32_together_with<false, false>(g, d, n, st);
+  if (vec_last) return launch_f32_together_with<true, true>(g, d, n, sums, st);
+  if (vec && n == 3 && g[1].b_kc) return launch_f32_together_with<true, false>(g, d, n, sums, st);
+  return launch_f32_together_with<false, false>(g, d, n, sums, st);
 }
 
 // ---- split-K combine: C = epilogue(sum_s partial[b*splits+s]) in fixed order --
@@ -812,16 +828,13 @@ hipError_t launch_gemm(const GemmArgs& g, bool in_bf16, GemmTile tile, hipStream
   return e;
 }
 
-hipError_t launch_gemm_together(const GemmArgs* g, const GemmTile* tile, int n, bool in_bf16, hipStream_t st) {
-  hipError_t e = hipErrorNotSupported;
-  bool small = in_bf16;
-  for (int i = 0; i < n; ++i) {
+hipError_t launch_gemm_together(const GemmArgs* g, const GemmTile* tile, int n, bool in_bf16, hipStream_t st,
+                                const DbReduce* sums) {
+  for (int i = 0; i < n; ++i)
     if (g[i].row_pos && g[i].splits <= 1) return hipErrorInvalidValue;
-    small = small && tile[i] == kTile64;
-  }
-  if (small) e = launch_gemm_bf16_together(g, n, st);
-  else if (!in_bf16) e = launch_gemm_f32_together(g, n, st);
+  hipError_t e = in_bf16 ? launch_gemm_bf16_together(g, tile, n, sums, st) : launch_gemm_f32_together(g, n, sums, st);
   if (e == hipErrorNotSupported) {
+    if (sums && (e = launch_db_reduce(*sums, st)) != hipSuccess) return e;
     for (int i = 0; i < n; ++i)
       if ((e = launch_gemm(g[i], in_bf16, tile[i], st)) != hipSuccess) return e;
     return e;

@@ -21,6 +21,7 @@
 //   * strided operand: LDS [64 k][columns] as in memory, fragments by transposing reads.  A 16-lane group reads four
 //     k-rows x 32 bytes; the 32-byte segments of a row are XOR-swizzled so that the four land in different banks.
 #include "common.h"
+#include "db_reduce_dev.h"
 #include "gemm.h"
 #include "gemm_dev.h"
 #include "lds_limit.h"
@@ -490,8 +491,24 @@ template <typename... M> static hipError_t launch_members(bool last_first, hipSt
   hipLaunchKernelGGL(kfn, dim3((unsigned)blocks), dim3(256), smem, st, (int)last_first, m...);
   return hipGetLastError();
 }
+// column sums of dlogits beside the products that read it
+struct SumsMember {
+  DbReduce d;
+  int blocks;
+  static constexpr int kSmem = kDbSmem;
+  void set(const DbReduce& sums) {
+    d = sums;
+    blocks = ((d.V + kDbColumns - 1) / kDbColumns + 7) / 8 * 8;
+  }
+  __device__ __forceinline__ void run(int id, unsigned char* smem) const {
+    if (id * kDbColumns < d.V) db_reduce_block<256>(d, id, reinterpret_cast<float*>(smem));
+  }
+};
 using MemberTN = TileMember<2, false, false, 4, false>;
 using MemberTNLaced = TileMember<2, false, false, 4, true>;
+using MemberTN128 = TileMember<4, false, false, 2, false>;
+using MemberNN = TileMember<2, true, false, 4, true>;
+using MemberNN128 = TileMember<4, true, false, 2, true>;
 using MemberNNSecond = TileMember<2, true, false, 4, true, true>;
 using MemberNT = TileMember<2, true, true, 4, true>;
 
@@ -499,6 +516,16 @@ static int tile_ktiles(const GemmDev& d) {   // reduction tiles of a block
   int n = 0;
   for (int s = 0; s < kMaxSeg; ++s) n += (d.K[s] + BK - 1) / BK;
   return (n + d.splits - 1) / d.splits;
+}
+template <typename TN, typename NN>
+static hipError_t launch_with_sums(const GemmDev* d, const TileForm* f, const DbReduce& sums, hipStream_t st) {
+  TN tn;
+  NN nn;
+  SumsMember s;
+  tn.set(d[0], f[0].out_bf16);
+  nn.set(d[1], f[1].out_bf16);
+  s.set(sums);
+  return launch_members(false, st, nn, tn, s);
 }
 template <typename TN>
 static hipError_t launch_together_with(const GemmDev* d, const TileForm* f, int n, hipStream_t st) {
@@ -519,10 +546,19 @@ static hipError_t launch_together_with(const GemmDev* d, const TileForm* f, int 
   }
   return hipErrorNotSupported;
 }
-hipError_t launch_gemm_bf16_tiles_together(const GemmDev* d, const TileForm* f, int n, hipStream_t st) {
+hipError_t launch_gemm_bf16_tiles_together(const GemmDev* d, const TileForm* f, int n, const DbReduce* sums, hipStream_t st) {
   if (n < 2 || f[0].a_kc || f[0].b_kc) return hipErrorNotSupported;
+  if (sums) {
+    if (n != 2 || !f[1].a_kc || f[1].b_kc || d[1].C_second) return hipErrorNotSupported;
+    if (f[1].tile == kTile128) return f[0].tile == kTile128 ? launch_with_sums<MemberTN128, MemberNN128>(d, f, *sums, st) : hipErrorNotSupported;
+    return f[0].tile == kTile128 ? launch_with_sums<MemberTN128, MemberNN>(d, f, *sums, st)
+                                 : launch_with_sums<MemberTN, MemberNN>(d, f, *sums, st);
+  }
   int64_t blocks = 0;
-  for (int i = 0; i < n; ++i) blocks += (int64_t)d[i].tiles_m * d[i].tiles_n * d[i].nz;
+  for (int i = 0; i < n; ++i) {
+    if (f[i].tile != kTile64) return hipErrorNotSupported;
+    blocks += (int64_t)d[i].tiles_m * d[i].tiles_n * d[i].nz;
+  }
   return gemm_tile_laced(false, blocks) ? launch_together_with<MemberTNLaced>(d, f, n, st)
                                         : launch_together_with<MemberTN>(d, f, n, st);
 }

@@ -65,8 +65,14 @@ hipError_t launch_xent_dlogits(void* logits, int64_t ldV, bool e_bf16, int N, in
                                const int32_t* n_act, hipStream_t st);
 // db_out[v] = sum_rb db_partial[rb][v], rb < nrb; with n_act (and rb_rows rows per block) only over the row blocks that
 // hold compacted rows (the others are not written)
-hipError_t launch_db_reduce(const float* db_partial, int nrb, int V, float* db_out, const int32_t* n_act, int rb_rows,
-                            hipStream_t st);
+struct DbReduce {
+  const float* db_partial;
+  int nrb, V;
+  float* db_out;
+  const int32_t* n_act;
+  int rb_rows;
+};
+hipError_t launch_db_reduce(const DbReduce& d, hipStream_t st);
 
 // One decoder step of attention, fused (Eq. 1-3 with T = 1): kprime [S,B,H] float = W_a h_enc, h_t [B,H],
 // h_enc [S,B,H]; writes alpha [B,S] float, ctx [B,H] (+ optional rounding remainder ctx_lo), optional attn_mask.

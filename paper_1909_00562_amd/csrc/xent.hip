@@ -6,6 +6,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "db_reduce_dev.h"
 #include "kernels.h"
 
 namespace asx {
@@ -290,31 +291,9 @@ __global__ __launch_bounds__(256) void xent_dlogits_kernel(TE* __restrict__ logi
     if (c0 + i < V) db_partial[(int64_t)blockIdx.y * V + c0 + i] = cs[i];
 }
 
-// 64 columns x 16 phases per block: phase p adds the row blocks p, p+16, ... of its column, eight loads in flight, and
-// the sixteen sums meet in LDS; the order of the additions is fixed.  (Four phases with a load at a time took 17 us for
-// 240 row blocks of 16000 columns, 160 of them with rows.)
-__global__ __launch_bounds__(1024) void db_reduce_kernel(const float* __restrict__ db_partial, int nrb, int V,
-                                                        float* __restrict__ db_out, const int32_t* __restrict__ n_act,
-                                                        int rb_rows) {
-  __shared__ float red[16][64];
-  const int c = threadIdx.x & 63, phase = threadIdx.x >> 6;
-  const int v = blockIdx.x * 64 + c;
-  if (n_act) {
-    const int used = (*n_act + rb_rows - 1) / rb_rows;
-    nrb = used < nrb ? used : nrb;
-  }
-  float s = 0.f;
-  if (v < V) {
-#pragma unroll 8
-    for (int r = phase; r < nrb; r += 16) s += db_partial[(int64_t)r * V + v];
-  }
-  red[phase][c] = s;
-  __syncthreads();
-  if (phase == 0 && v < V) {
-#pragma unroll
-    for (int p = 1; p < 16; ++p) s += red[p][c];
-    db_out[v] = s;
-  }
+__global__ __launch_bounds__(1024) void db_reduce_kernel(DbReduce p) {
+  __shared__ float red[kDbSmem / sizeof(float)];
+  db_reduce_block<1024>(p, blockIdx.x, red);
 }
 
 // ---- launchers ----------------------------------------------------------------
@@ -371,9 +350,8 @@ hipError_t launch_xent_dlogits(void* logits, int64_t ldV, bool e_bf16, int N, in
   return hipGetLastError();
 }
 
-hipError_t launch_db_reduce(const float* db_partial, int nrb, int V, float* db_out, const int32_t* n_act, int rb_rows,
-                            hipStream_t st) {
-  hipLaunchKernelGGL(db_reduce_kernel, dim3((V + 63) / 64), dim3(1024), 0, st, db_partial, nrb, V, db_out, n_act, rb_rows);
+hipError_t launch_db_reduce(const DbReduce& d, hipStream_t st) {
+  hipLaunchKernelGGL(db_reduce_kernel, dim3((d.V + kDbColumns - 1) / kDbColumns), dim3(1024), 0, st, d);
   return hipGetLastError();
 }
 
