@@ -153,9 +153,9 @@ __device__ __forceinline__ void gs_finish_ragged(const GemmDev& p, int out_bf16,
   }
 }
 
-// Block `pid` of product z (batch and split) of a launch, NST * 2 * 32 TW * ROWB bytes of LDS at smem.
+// Block `id` of a launch's tiles of all batches and splits, NST * 2 * 32 TW * ROWB bytes of LDS at smem.
 template <int TW, bool AKC, bool BKC, int NST, bool LACED, bool SECOND>
-__device__ __forceinline__ void gemm_bf16_tile_block(const GemmDev& p, int out_bf16, int pid, int z, unsigned char* smem) {
+__device__ __forceinline__ void gemm_bf16_tile_block(const GemmDev& p, int out_bf16, int id, unsigned char* smem) {
   constexpr int BM = 32 * TW, TILE = BM * ROWB, STAGE = 2 * TILE;   // square block tile; bytes of an operand tile, a stage
   constexpr int NL = TW, LD = BM + 4;                               // loads per wave, operand and tile; staging row (floats)
   static_assert((NST & (NST - 1)) == 0 && NST * STAGE >= 64 * LD * 4, "ring of a power of two; write-out staging");
@@ -164,10 +164,14 @@ __device__ __forceinline__ void gemm_bf16_tile_block(const GemmDev& p, int out_b
   const int wm = (wave >> 1) * 16 * TW, wn = (wave & 1) * 16 * TW;
   const int Mv = dev_bound(p.M_dev, p.M), K0 = dev_bound(p.K_dev, p.K[0]);
   const int tiles_m = (Mv + BM - 1) / BM, nt = tiles_m * p.tiles_n;   // the grid was sized for p.M
-  if (pid >= nt) return;                                          // the whole block, before any barrier
-  {  // each XCD gets a contiguous run of tiles, walked in groups of 8 tile rows
-    const int xcd = pid & 7, idx = pid >> 3, per = nt >> 3, rem = nt & 7;
-    pid = xcd * per + (xcd < rem ? xcd : rem) + idx;
+  // Each XCD gets a contiguous run of the tiles of all products (batches, splits), a product's walked in groups of 8 tile rows: its
+  // L2 then brings an operand of a batch, or a split's part of both operands, from memory once.
+  const int total = nt * p.nz, xcd = id & 7, per = total >> 3, rem = total & 7;
+  if ((id >> 3) >= per + (xcd < rem)) return;                     // the whole block, before any barrier
+  int pid = xcd * per + (xcd < rem ? xcd : rem) + (id >> 3), z = 0;
+  if (p.nz > 1) {
+    z = pid / nt;
+    pid -= z * nt;
   }
   const int gid = pid / (8 * p.tiles_n), first_m = gid * 8;
   const int gm = tiles_m - first_m < 8 ? tiles_m - first_m : 8;
@@ -400,7 +404,7 @@ __device__ __forceinline__ void gemm_bf16_tile_block(const GemmDev& p, int out_b
 template <int TW, bool AKC, bool BKC, int NST, bool LACED, bool SECOND>
 __global__ __launch_bounds__(256, LACED ? 2 : 1) void gemm_bf16_tile_kernel(GemmDev p, int out_bf16) {
   extern __shared__ __align__(1024) unsigned char smem[];
-  gemm_bf16_tile_block<TW, AKC, BKC, NST, LACED, SECOND>(p, out_bf16, blockIdx.x, blockIdx.z, smem);
+  gemm_bf16_tile_block<TW, AKC, BKC, NST, LACED, SECOND>(p, out_bf16, blockIdx.x, smem);
 }
 
 template <int TW, bool AKC, bool BKC, int NST, bool LACED, bool SECOND = false>
@@ -410,7 +414,9 @@ static hipError_t launch_tile_shape(const GemmDev& d, int out_bf16, hipStream_t 
   static LdsLimit limit;
   const hipError_t e = limit.raise(reinterpret_cast<const void*>(kfn), smem);
   if (e != hipSuccess) return e;
-  const dim3 grid((d.M + BM - 1) / BM * d.tiles_n, 1, d.nz);
+  const int64_t blocks = (int64_t)d.tiles_m * d.tiles_n * d.nz;
+  if (blocks > (1 << 24)) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks);
   hipLaunchKernelGGL(kfn, grid, dim3(256), smem, st, d, out_bf16);
   return hipGetLastError();
 }
@@ -452,17 +458,15 @@ static hipError_t launch_tile_form(const GemmDev& d, GemmTile tile, int out_bf16
 template <int TW, bool AKC, bool BKC, int NST, bool LACED, bool SECOND = false>
 struct TileMember {
   GemmDev d;
-  int out_bf16, tiles, blocks;   // blocks: of the grid, a multiple of 8 so that a product's blocks keep their XCDs
+  int out_bf16, blocks;   // blocks: of the grid, a multiple of 8 so that a product's blocks keep their XCDs
   static constexpr int kSmem = NST * 2 * 32 * TW * ROWB;
   void set(const GemmDev& dev, bool obf) {
     d = dev;
     out_bf16 = obf;
-    tiles = d.tiles_m * d.tiles_n;
-    blocks = (tiles * d.nz + 7) / 8 * 8;
+    blocks = (d.tiles_m * d.tiles_n * d.nz + 7) / 8 * 8;
   }
   __device__ __forceinline__ void run(int id, unsigned char* smem) const {
-    const int z = id / tiles;
-    if (z < d.nz) gemm_bf16_tile_block<TW, AKC, BKC, NST, LACED, SECOND>(d, out_bf16, id - z * tiles, z, smem);
+    gemm_bf16_tile_block<TW, AKC, BKC, NST, LACED, SECOND>(d, out_bf16, id, smem);
   }
 };
 template <typename F, typename... R>
