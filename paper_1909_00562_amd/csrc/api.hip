@@ -104,6 +104,7 @@ struct Layout {
   bool compact;
   bool dch_pair;   // dC and dH1 as one product
   bool out_pair;   // dW_out and dz in one launch where they have the tiles for it
+  bool hc_gather;    // the product does not write h_c to its compacted rows: a pass of its own does
   bool dz_scatter;   // compacted rows of dz go back to their places in a pass of their own (a split product's combine does it)
   bool dhc_dyn;   // the product with W_out in the backward pass picks its reduction split on the device
   size_t row_pos, rows, n_act, hc_c, dact_c, dz_c, dz_lo_c;
@@ -146,6 +147,7 @@ Layout make_layout(const as_shape* s) {
   L.p_score = gemm_plan(T, S, H, B, bf, false);
   L.p_ctx = gemm_plan(T, H, S, B, bf, false);
   L.p_hc = plan_hc(N, H, bf);
+  L.hc_gather = L.p_hc.tile == kTile256 && L.p_hc.splits == 1;
   L.p_logits = gemm_plan(N, V, H, 1, bf, false);
   const bool counted = s->skip_pad_rows != 0;
   L.p_dwout = gemm_plan(V, H, N, 1, bf, true, false, counted);
@@ -324,6 +326,11 @@ static as_status fwd_from_ctx(const as_shape* s, const Layout& L, char* w, const
     g.M = N; g.N = H; g.act_tanh = 1;
     g.C = w + L.hc; g.ldc = H; g.c_bf16 = bf;
     g.C_dact = reinterpret_cast<float*>(w + L.dact);
+    if (L.compact && !L.hc_gather) {   // padding rows drop out of Eq. 5-6 here
+      g.copy_pos = reinterpret_cast<const int32_t*>(w + L.row_pos);
+      g.C_copy = w + L.hc_c;
+      g.C_dact = reinterpret_cast<float*>(w + L.dact_c);
+    }
     g.splits = L.p_hc.splits; g.partial = reinterpret_cast<float*>(w + L.partial_hc);
     if (s->dropout_p > 0.f) {   // section 4.2: dropout, here on the attentional state; the mask rides on dact into bwd
       g.drop_thr = (uint32_t)((double)s->dropout_p * 4294967296.0);   // floor: the product is exact in double
@@ -332,18 +339,16 @@ static as_status fwd_from_ctx(const as_shape* s, const Layout& L, char* w, const
     }
     AS_TRY(AS_STAGE_GEMM_HC, launch_gemm(g, bf, L.p_hc.tile, st));
   }
-  // Padding rows drop out of Eq. 5-6 here: the rows of h_c (and of its saved derivative) whose target is a
-  // word are gathered into a dense block, and everything over the vocabulary runs on that block alone.
+  // The rows of h_c (and of its saved derivative) whose target is a word lie in a dense block, and everything over the
+  // vocabulary runs on that block alone.
   const int32_t* rows = nullptr;
   const int32_t* n_act = nullptr;
   if (L.compact) {
     rows = reinterpret_cast<const int32_t*>(w + L.rows);
     n_act = reinterpret_cast<const int32_t*>(w + L.n_act);
-    AS_TRY(AS_STAGE_COMPACT, launch_row_compact(targets, N, V, s->pad_id, reinterpret_cast<int32_t*>(w + L.row_pos),
-                                                reinterpret_cast<int32_t*>(w + L.rows),
-                                                reinterpret_cast<int32_t*>(w + L.n_act), tgt_mask, tok_loss, argmax, st));
-    AS_TRY(AS_STAGE_COMPACT, launch_gather_rows(rows, n_act, N, w + L.hc, w + L.hc_c, (int64_t)H * L.e, w + L.dact,
-                                                w + L.dact_c, (int64_t)H * 4, st));
+    if (L.hc_gather)
+      AS_TRY(AS_STAGE_COMPACT, launch_gather_rows(rows, n_act, N, w + L.hc, w + L.hc_c, (int64_t)H * L.e, w + L.dact,
+                                                  w + L.dact_c, (int64_t)H * 4, st));
   }
   {  // logits = h_c W_out^T + b_out                                        (Eq. 5)
     GemmArgs g;
@@ -468,11 +473,15 @@ static as_status fwd_impl(const as_shape* s, const void* h_dec, const void* h_en
   // (T = 1 too: from the same Q, alpha and ctx of a step by itself are the same bits as in a batch of steps, which the row
   // sums of attn_step.hip would not give.  Whole calls are where Q and h_c have the same plan at both row counts, as small
   // models do; else h_c, split by the row count, adds in another order.)
+  RowList list{};
+  if (L.compact)
+    list = {targets, N, V, s->pad_id, reinterpret_cast<int32_t*>(w + L.row_pos), reinterpret_cast<int32_t*>(w + L.rows),
+            reinterpret_cast<int32_t*>(w + L.n_act), tgt_mask, tok_loss, argmax};
   if (bf && attn_fwd_fused_supported(S, H)) {
     // Eq. 2 (second half), 1 and 3 in one kernel per (sentence, 16 or 32 decoder steps): the scores stay on chip
     AS_TRY(AS_STAGE_ATTN_SCORE,
            launch_attn_fwd_fused(w + L.q, w + L.q_lo, he, src_len, B, T, S, H, reinterpret_cast<float*>(w + L.alpha32),
-                                 w + L.alphaE, w + L.alphaE_lo, L.ldS, w + L.ctx, w + L.ctx_lo, attn_mask, st));
+                                 w + L.alphaE, w + L.alphaE_lo, L.ldS, w + L.ctx, w + L.ctx_lo, attn_mask, list, st));
   } else {
     {  // score[b] = Q_b h_enc_b^T, one product per sentence                  (Eq. 2)
       GemmArgs g;
@@ -486,7 +495,7 @@ static as_status fwd_impl(const as_shape* s, const void* h_dec, const void* h_en
     AS_TRY(AS_STAGE_ATTN_SOFTMAX,                                        // Eq. 1
            launch_attn_softmax_rows(reinterpret_cast<const float*>(w + L.scores), src_len, B, T, S,
                                     reinterpret_cast<float*>(w + L.alpha32), w + L.alphaE,
-                                    w + L.alphaE_lo, L.ldS, bf, attn_mask, st));
+                                    w + L.alphaE_lo, L.ldS, bf, attn_mask, list, st));
     {  // ctx_b = alpha_b h_enc_b                                            (Eq. 3)
       GemmArgs g;
       g.seg(w + L.alphaE, L.ldS, (int64_t)T * L.ldS, he, BH, H, S);

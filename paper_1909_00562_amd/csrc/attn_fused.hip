@@ -29,6 +29,7 @@
 #include "kernels.h"
 #include "lds_limit.h"
 #include "gemm_dev.h"
+#include "row_list_dev.h"
 
 namespace asx {
 
@@ -55,6 +56,7 @@ struct AttnFwdArgs {
   int T, S, B, H;
   int64_t ldS;
   int y0;                                // first block of decoder steps of this launch
+  RowList list;                          // forward: made by the blocks x = B, y = 0 of the first launch, if wanted
 };
 
 // LDS of a workgroup of 16 RT decoder steps x 16 ST source positions: a slot of NT x 16 columns of encoder states per wave;
@@ -80,6 +82,12 @@ __global__ __launch_bounds__(64 * AF_NW) void attn_fused_kernel(AttnFwdArgs p) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c16 = lane & 15, q4 = lane >> 4;
+  if constexpr (!BWD) {
+    if (blockIdx.x == (unsigned)p.B) {
+      if (blockIdx.y == 0) row_list_block<64 * AF_NW>(p.list, reinterpret_cast<int*>(smem));
+      return;
+    }
+  }
   const int b = blockIdx.x, t0 = (p.y0 + blockIdx.y) * ROWS;
   const int T = p.T, S = p.S, H = p.H;
   const int64_t BH = (int64_t)p.B * H;
@@ -350,7 +358,8 @@ template <bool BWD, int RT, int ST> static hipError_t launch_attn_shape(AttnFwdA
   if (e != hipSuccess) return e;
   const int ny = (p.T + 16 * RT - 1) / (16 * RT);
   for (p.y0 = 0; p.y0 < ny; p.y0 += kGridY) {   // (more than a million decoder steps: several launches)
-    hipLaunchKernelGGL(k, dim3(p.B, ny - p.y0 < kGridY ? ny - p.y0 : kGridY), dim3(64 * AF_NW), smem, st, p);
+    const int list = p.y0 == 0 && p.list.targets ? 1 : 0;
+    hipLaunchKernelGGL(k, dim3(p.B + list, ny - p.y0 < kGridY ? ny - p.y0 : kGridY), dim3(64 * AF_NW), smem, st, p);
     const hipError_t launched = hipGetLastError();
     if (launched != hipSuccess) return launched;
   }
@@ -367,8 +376,9 @@ template <bool BWD> static hipError_t launch_attn_fused(const AttnFwdArgs& p, hi
 
 hipError_t launch_attn_fwd_fused(const void* q_hi, const void* q_lo, const void* h_enc, const int32_t* src_len, int B,
                                  int T, int S, int H, float* alpha32, void* alphaE, void* alphaE_lo, int64_t ldS,
-                                 void* ctx, void* ctx_lo, uint8_t* attn_mask, hipStream_t st) {
+                                 void* ctx, void* ctx_lo, uint8_t* attn_mask, const RowList& list, hipStream_t st) {
   AttnFwdArgs p{};
+  p.list = list;
   p.q_hi = reinterpret_cast<const uint16_t*>(q_hi);
   p.q_lo = reinterpret_cast<const uint16_t*>(q_lo);
   p.h_enc = reinterpret_cast<const uint16_t*>(h_enc);

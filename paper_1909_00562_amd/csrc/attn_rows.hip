@@ -3,6 +3,7 @@
 // wavefront shuffles, no LDS.
 #include "common.h"
 #include "kernels.h"
+#include "row_list_dev.h"
 
 namespace asx {
 
@@ -12,7 +13,12 @@ __global__ __launch_bounds__(256) void attn_softmax_rows_kernel(const float* __r
                                                                int S, float* __restrict__ alpha32,
                                                                TE* __restrict__ alphaE,
                                                                TE* __restrict__ alphaE_lo, int64_t ldS,
-                                                               uint8_t* __restrict__ attn_mask) {
+                                                               uint8_t* __restrict__ attn_mask, RowList list) {
+  if (list.targets && blockIdx.x == gridDim.x - 1) {   // one block more than the rows need
+    __shared__ int counts[kRowListSmem / sizeof(int)];
+    row_list_block<256>(list, counts);
+    return;
+  }
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);   // row = b*T + t
   if (row >= B * T) return;
@@ -62,16 +68,16 @@ __global__ __launch_bounds__(256) void attn_softmax_rows_bwd_kernel(const float*
 
 hipError_t launch_attn_softmax_rows(const float* score, const int32_t* src_len, int B, int T, int S,
                                     float* alpha32, void* alphaE, void* alphaE_lo, int64_t ldS, bool e_bf16,
-                                    uint8_t* attn_mask, hipStream_t st) {
+                                    uint8_t* attn_mask, const RowList& list, hipStream_t st) {
   const int rows = B * T;
-  dim3 grid((rows + 3) / 4);
+  dim3 grid((rows + 3) / 4 + (list.targets ? 1 : 0));
   if (e_bf16)
     hipLaunchKernelGGL(attn_softmax_rows_kernel<uint16_t>, grid, dim3(256), 0, st, score, src_len, B, T, S,
                        alpha32, reinterpret_cast<uint16_t*>(alphaE), reinterpret_cast<uint16_t*>(alphaE_lo), ldS,
-                       attn_mask);
+                       attn_mask, list);
   else
     hipLaunchKernelGGL(attn_softmax_rows_kernel<float>, grid, dim3(256), 0, st, score, src_len, B, T, S, alpha32,
-                       reinterpret_cast<float*>(alphaE), reinterpret_cast<float*>(alphaE_lo), ldS, attn_mask);
+                       reinterpret_cast<float*>(alphaE), reinterpret_cast<float*>(alphaE_lo), ldS, attn_mask, list);
   return hipGetLastError();
 }
 

@@ -1,59 +1,15 @@
 // Row compaction for the vocabulary part of the path (Eq. 5-6 and its backward).
 // A target position that is padding contributes nothing to the loss or to any
 // gradient, so the three products over the vocabulary and the two cross-entropy
-// passes need only the rows n = t*B + b whose target is a word.  These kernels
-// number those rows in increasing n (the list is made on the device: nothing is
-// copied to the host and the stream is never synchronised), gather the rows of
-// h_c and of the saved tanh derivative into a dense [n_act, H] block, and scatter
-// the rows of dz back to their time-major places with zeros at the padding rows.
+// passes need only the rows n = t*B + b whose target is a word.  The list of them is made beside the attention of the forward pass
+// (row_list_dev.h), on the device: nothing is copied to the host and the stream is never synchronised.  The products write the
+// rows of h_c, of the saved tanh derivative and of dz to their places themselves; the 256 x 256 kernels do not, for them these
+// kernels gather the rows into a dense [n_act, H] block and scatter the rows of dz back to their time-major places with
+// zeros at the padding rows.
 #include "common.h"
 #include "kernels.h"
 
 namespace asx {
-
-// One block walks the N targets in slices of 1024 and counts the non-pad ones before each
-// position (ballot + popcount inside a wave, 16 wave totals through LDS): fixed order, no atomics.
-__global__ __launch_bounds__(1024) void row_compact_kernel(const int32_t* __restrict__ targets, int N, int V,
-                                                          int pad_id, int32_t* __restrict__ row_pos,
-                                                          int32_t* __restrict__ rows, int32_t* __restrict__ n_act,
-                                                          uint8_t* __restrict__ tgt_mask, float* __restrict__ tok_loss,
-                                                          int32_t* __restrict__ argmax) {
-  __shared__ int wave_total[16];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  int base = 0;
-  for (int n0 = 0; n0 < N; n0 += 1024) {
-    const int n = n0 + tid;
-    bool live = false;
-    if (n < N) {
-      const int y = targets[n];
-      live = (y != pad_id) && (y >= 0) && (y < V);
-    }
-    const unsigned long long votes = __ballot(live);
-    const int before = __popcll(votes & ((1ull << lane) - 1ull));
-    if (lane == 0) wave_total[wave] = __popcll(votes);
-    __syncthreads();
-    int woff = 0, total = 0;
-#pragma unroll
-    for (int w = 0; w < 16; ++w) {
-      const int c = wave_total[w];
-      woff += w < wave ? c : 0;
-      total += c;
-    }
-    if (n < N) {
-      const int pos = base + woff + before;
-      row_pos[n] = live ? pos : -1;
-      if (live) rows[pos] = n;
-      if (tgt_mask) tgt_mask[n] = live ? 1 : 0;
-      if (!live) {
-        if (tok_loss) tok_loss[n] = 0.f;
-        if (argmax) argmax[n] = pad_id;
-      }
-    }
-    base += total;
-    __syncthreads();   // wave_total is rewritten by the next slice
-  }
-  if (tid == 0) *n_act = base;
-}
 
 // bytes of one row are a multiple of 4; 16-byte vectors when they are a multiple of 16 (row starts are then aligned)
 __device__ __forceinline__ void copy_row(const unsigned char* __restrict__ src, unsigned char* __restrict__ dst,
@@ -105,13 +61,6 @@ __global__ __launch_bounds__(256) void scatter_rows_kernel(const int32_t* __rest
     zero_row(dst0 + n * bytes, bytes, threadIdx.x, 256);
     if (src1) zero_row(dst1 + n * bytes, bytes, threadIdx.x, 256);
   }
-}
-
-hipError_t launch_row_compact(const int32_t* targets, int N, int V, int pad_id, int32_t* row_pos, int32_t* rows,
-                              int32_t* n_act, uint8_t* tgt_mask, float* tok_loss, int32_t* argmax, hipStream_t st) {
-  hipLaunchKernelGGL(row_compact_kernel, dim3(1), dim3(1024), 0, st, targets, N, V, pad_id, row_pos, rows, n_act,
-                     tgt_mask, tok_loss, argmax);
-  return hipGetLastError();
 }
 
 hipError_t launch_gather_rows(const int32_t* rows, const int32_t* n_act, int N, const void* src0, void* dst0,

@@ -82,6 +82,10 @@ struct GemmArgs {
   // Split products only, applied by the combine step: row n < M of C (and C_lo) is the product's row row_pos[n], zeros where
   // that is negative (row compaction undone on the way out).  The gate's rows are the product's.
   const int32_t* row_pos = nullptr;
+  // Row n of C is written a second time, to row copy_pos[n] of C_copy (C's layout and type) where that is not negative, and
+  // row n of C_dact there alone, not at n.  Not by the 256 x 256 kernels; batch == 1.
+  const int32_t* copy_pos = nullptr;
+  void* C_copy = nullptr;
 };
 
 // Blocks of a persistent launch (one per compute unit, a multiple of the 8 XCDs).

@@ -558,7 +558,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(GemmDev p, int work_t
   // ---- load stream: cursor over (item, segment, reduction tile) --------------------
   PpLoader<AKC> la;
   PpLoader<BKC> lb;
-  const int64_t stepA = AKC ? BK : (int64_t)BK * p.lda[0], stepB = BKC ? BK : (int64_t)BK * p.ldb[0];
+  const int64_t stepA = AKC ? BK : (int64_t)BK * p.lda, stepB = BKC ? BK : (int64_t)BK * p.ldb;
   int lw = wbeg + bidx;        // work item the cursor is in
   bool lvalid = lw < wend;     // false once every tile of this block has been issued
   int cseg = 0, ck_left = 0;
@@ -567,15 +567,15 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(GemmDev p, int work_t
   int lbatch = 0;
   auto enter_item = [&]() {    // cursor to the first reduction tile of item lw
     const Item it = get_item(lw);
-    la.init(p.lda[0], Mv - it.m0, wave, lane);
-    lb.init(p.ldb[0], p.N - it.n0, wave, lane);
-    offA = AKC ? (int64_t)it.m0 * p.lda[0] : it.m0;
-    offB = BKC ? (int64_t)it.n0 * p.ldb[0] : it.n0;
+    la.init(p.lda, Mv - it.m0, wave, lane);
+    lb.init(p.ldb, p.N - it.n0, wave, lane);
+    offA = AKC ? (int64_t)it.m0 * p.lda : it.m0;
+    offB = BKC ? (int64_t)it.n0 * p.ldb : it.n0;
     lbatch = it.batch;
     cseg = 0;
     ck_left = it.kend - it.kbeg;
-    cA = p.A[0] + (int64_t)lbatch * p.sA[0] + offA + (AKC ? it.kbeg : (int64_t)it.kbeg * p.lda[0]);
-    cB = p.B[0] + (int64_t)lbatch * p.sB[0] + offB + (BKC ? it.kbeg : (int64_t)it.kbeg * p.ldb[0]);
+    cA = p.A[0] + (int64_t)lbatch * p.sA[0] + offA + (AKC ? it.kbeg : (int64_t)it.kbeg * p.lda);
+    cB = p.B[0] + (int64_t)lbatch * p.sB[0] + offB + (BKC ? it.kbeg : (int64_t)it.kbeg * p.ldb);
   };
   auto advance = [&]() {
     cA += stepA;
@@ -816,7 +816,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring_kernel(
   // ---- load stream: cursor over (item, segment, reduction tile) --------------------
   RingLoader<AKC> la;
   RingLoader<BKC> lb;
-  const int64_t stepA = AKC ? RK : (int64_t)RK * p.lda[0], stepB = BKC ? RK : (int64_t)RK * p.ldb[0];
+  const int64_t stepA = AKC ? RK : (int64_t)RK * p.lda, stepB = BKC ? RK : (int64_t)RK * p.ldb;
   int lw = wbeg + bidx;        // work item the cursor is in
   bool lvalid = lw < wend;     // false once every tile of this block has been issued
   int cseg = 0, ck_left = 0;
@@ -825,15 +825,15 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring_kernel(
   int lbatch = 0;
   auto enter_item = [&]() {    // cursor to the first reduction tile of item lw
     const Item it = get_item(lw);
-    la.init(p.lda[0], Mv - it.m0, wave, lane);
-    lb.init(p.ldb[0], p.N - it.n0, wave, lane);
-    offA = AKC ? (int64_t)it.m0 * p.lda[0] : it.m0;
-    offB = BKC ? (int64_t)it.n0 * p.ldb[0] : it.n0;
+    la.init(p.lda, Mv - it.m0, wave, lane);
+    lb.init(p.ldb, p.N - it.n0, wave, lane);
+    offA = AKC ? (int64_t)it.m0 * p.lda : it.m0;
+    offB = BKC ? (int64_t)it.n0 * p.ldb : it.n0;
     lbatch = it.batch;
     cseg = 0;
     ck_left = it.kend - it.kbeg;
-    cA = p.A[0] + (int64_t)lbatch * p.sA[0] + offA + (AKC ? it.kbeg : (int64_t)it.kbeg * p.lda[0]);
-    cB = p.B[0] + (int64_t)lbatch * p.sB[0] + offB + (BKC ? it.kbeg : (int64_t)it.kbeg * p.ldb[0]);
+    cA = p.A[0] + (int64_t)lbatch * p.sA[0] + offA + (AKC ? it.kbeg : (int64_t)it.kbeg * p.lda);
+    cB = p.B[0] + (int64_t)lbatch * p.sB[0] + offB + (BKC ? it.kbeg : (int64_t)it.kbeg * p.ldb);
   };
   auto advance = [&]() {
     cA += stepA;
@@ -1005,8 +1005,6 @@ static hipError_t gemm_describe(const GemmArgs& g, GemmTile tile, GemmDev& d) {
   for (int s = 0; s < kMaxSeg; ++s) {
     d.A[s] = reinterpret_cast<const uint16_t*>(g.A[s]);
     d.B[s] = reinterpret_cast<const uint16_t*>(g.B[s]);
-    d.lda[s] = g.lda[s];
-    d.ldb[s] = g.ldb[s];
     d.sA[s] = g.sA[s];
     d.sB[s] = g.sB[s];
     d.K[s] = g.K[s];
@@ -1019,6 +1017,8 @@ static hipError_t gemm_describe(const GemmArgs& g, GemmTile tile, GemmDev& d) {
       if (!al16(g.A[s]) || !al16(g.B[s])) return hipErrorInvalidValue;
     }
   }
+  d.lda = g.lda[0];
+  d.ldb = g.ldb[0];
   d.M = g.M;
   d.N = g.N;
   d.C = g.C;
@@ -1031,6 +1031,10 @@ static hipError_t gemm_describe(const GemmArgs& g, GemmTile tile, GemmDev& d) {
                      g.gate || g.drop_thr || g.accumulate || g.C_dact))
     return hipErrorInvalidValue;
   d.C_second = g.C_second;
+  // (a split's combine writes the copies)
+  if (g.copy_pos && (!g.C_copy || g.batch != 1 || (big_tile && g.splits == 1) || g.M_dev || g.accumulate)) return hipErrorInvalidValue;
+  d.copy_pos = g.splits > 1 ? nullptr : g.copy_pos;
+  d.C_copy = g.C_copy;
   bool apart_al16 = !g.C_second || al16(g.C_second);
   for (int b = 0; g.C_of && b < g.batch; ++b) apart_al16 = apart_al16 && al16(g.C_of[b]);
   d.bias = reinterpret_cast<const uint16_t*>(g.bias);
@@ -1054,12 +1058,12 @@ static hipError_t gemm_describe(const GemmArgs& g, GemmTile tile, GemmDev& d) {
   // Rows with padding behind column N: the write-out may cover whole groups of four columns (the product is zero there,
   // operand rows >= N read as zero).  2257 x 32003 x 1000 with its rows of 32008: 228 us element by element.
   const bool padded = g.pad_out && g.splits == 1 && g.batch == 1 && !g.drop_thr && !g.gate && !g.accumulate && !g.C_lo &&
-                      !g.C_dact && ((g.N + 3) & ~3) <= g.ldc;
+                      !g.C_dact && !g.copy_pos && ((g.N + 3) & ~3) <= g.ldc;
   d.n_out = padded ? (g.N + 3) & ~3 : g.N;
   // vector epilogue: every row of C / C_lo / C_dact / gate starts 16-byte aligned
   // (ldc % 4 == 0 gives 8-byte alignment for bf16 rows, which their 8-byte stores need)
   d.vec_ok = ((g.ldc & 3) == 0) && ((g.sC & 3) == 0) && al16(g.C) && apart_al16 && (!g.C_lo || al16(g.C_lo)) &&
-             (!g.C_dact || al16(g.C_dact)) && (!g.gate || (al16(g.gate) && (g.ldg & 3) == 0)) &&
+             (!g.C_dact || al16(g.C_dact)) && al16(g.C_copy) && (!g.gate || (al16(g.gate) && (g.ldg & 3) == 0)) &&
              (d.n_out & 3) == 0 &&                                        // a 4-column group is all in or all out
              g.ldc < (1 << 21) && g.ldg < (1 << 21) && g.N < (1 << 21);   // 32-bit byte offsets inside a 128-row window
   if (g.C_second && !d.vec_ok) return hipErrorInvalidValue;

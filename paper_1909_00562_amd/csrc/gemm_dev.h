@@ -11,7 +11,7 @@ typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 struct GemmDev {
   const uint16_t* A[kMaxSeg];
   const uint16_t* B[kMaxSeg];
-  int64_t lda[kMaxSeg], ldb[kMaxSeg], sA[kMaxSeg], sB[kMaxSeg];
+  int64_t lda, ldb, sA[kMaxSeg], sB[kMaxSeg];
   int K[kMaxSeg];
   int M, N;
   int n_out;   // columns the vector write-out covers: N, or N rounded up to 4 where C's rows have padding
@@ -19,6 +19,8 @@ struct GemmDev {
   uint16_t* C_lo;
   float* C_dact;
   int64_t ldc, sC;
+  const int32_t* copy_pos; // row n of C also goes to row copy_pos[n] of C_copy, and of C_dact there alone (or null)
+  void* C_copy;
   float* C_second;         // batch of two: where the product of segment 0 alone goes (or null)
   const uint16_t* bias;
   const float* gate;

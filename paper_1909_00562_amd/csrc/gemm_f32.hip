@@ -19,6 +19,8 @@ struct GemmDevF {
   float* C;
   float* C_lo;
   float* C_dact;
+  const int32_t* copy_pos;   // row n of C also goes to row copy_pos[n] of C_copy, and of C_dact there alone (or null)
+  float* C_copy;
   int64_t ldc, sC;
   const float* bias;
   const float* gate;
@@ -283,7 +285,15 @@ __device__ __forceinline__ void gemm_f32_block(const GemmDevF& p, int pid, int z
         const float vf = (float)v;
         p.C[ci] = vf;
         if (p.C_lo) p.C_lo[ci] = (float)(v - (double)vf);
-        if (p.C_dact) p.C_dact[ci] = (float)dact;
+        if (p.copy_pos) {
+          const int copy = p.copy_pos[row];
+          if (copy < 0) continue;
+          const int64_t cc = (int64_t)copy * p.ldc + col;
+          p.C_copy[cc] = vf;
+          if (p.C_dact) p.C_dact[cc] = (float)dact;
+        } else if (p.C_dact) {
+          p.C_dact[ci] = (float)dact;
+        }
       }
     }
 }
@@ -328,6 +338,7 @@ static hipError_t f32_describe(const GemmArgs& g, GemmDevF& d, bool& avec, bool&
   if (g.splits > 1 && (g.K[1] != 0 || g.partial == nullptr)) return hipErrorInvalidValue;
   if (g.splits > 1 && (g.C_dact || g.drop_thr)) return hipErrorInvalidValue;
   if (g.drop_thr && g.batch != 1) return hipErrorInvalidValue;
+  if (g.copy_pos && (!g.C_copy || g.batch != 1 || g.splits != 1 || g.M_dev || g.accumulate)) return hipErrorInvalidValue;
   avec = bvec = true;
   for (int s = 0; s < kMaxSeg; ++s) {
     d.A[s] = reinterpret_cast<const float*>(g.A[s]);
@@ -352,6 +363,8 @@ static hipError_t f32_describe(const GemmArgs& g, GemmDevF& d, bool& avec, bool&
   d.C = reinterpret_cast<float*>(g.C);
   d.C_lo = reinterpret_cast<float*>(g.C_lo);
   d.C_dact = g.C_dact;
+  d.copy_pos = g.copy_pos;
+  d.C_copy = reinterpret_cast<float*>(g.C_copy);
   d.ldc = g.ldc;
   d.sC = g.sC;
   d.bias = reinterpret_cast<const float*>(g.bias);
@@ -489,6 +502,8 @@ struct CombineDev {
   uint64_t drop_seed;
   const int32_t* M_dev;
   const int32_t* row_pos;   // row n of C is row row_pos[n] of the product, zeros where that is negative
+  const int32_t* copy_pos;  // row n of C also goes to row copy_pos[n] of C_copy, and of C_dact there alone (or null)
+  void* C_copy;
   int dyn_ktiles, dyn_blocks;
 };
 
@@ -576,16 +591,18 @@ __global__ __launch_bounds__(256) void splitk_combine_kernel(CombineDev p) {
 #pragma unroll
         for (int e = 0; e < V; ++e) v[e] *= gate[e];
     }
-    auto put = [&](void* dst, const float (&x)[V]) {   // floats
+    const int copy = p.copy_pos ? p.copy_pos[row] : -1;
+    const int64_t cc = (int64_t)copy * p.ldc + col;
+    auto put = [&](void* dst, int64_t at, const float (&x)[V]) {   // floats
 #pragma unroll
       for (int k = 0; k < V / Q; ++k) {
         vec_t o;
 #pragma unroll
         for (int e = 0; e < Q; ++e) o[e] = x[k * Q + e];
-        *reinterpret_cast<vec_t*>(reinterpret_cast<float*>(dst) + ci + k * Q) = o;
+        *reinterpret_cast<vec_t*>(reinterpret_cast<float*>(dst) + at + k * Q) = o;
       }
     };
-    if (p.C_dact) put(p.C_dact, dact);
+    if (p.C_dact && (copy >= 0 || !p.copy_pos)) put(p.C_dact, p.copy_pos ? cc : ci, dact);
     if constexpr (OUT_BF16) {
       uint32_t hi[V], lo[V];
 #pragma unroll
@@ -593,13 +610,14 @@ __global__ __launch_bounds__(256) void splitk_combine_kernel(CombineDev p) {
         hi[e] = f32_to_bf16_bits(v[e]);
         lo[e] = f32_to_bf16_bits(v[e] - bf16_bits_to_f32(hi[e]));
       }
-      auto put16 = [&](void* dst, const uint32_t (&x)[V]) {
-        uint16_t* d = reinterpret_cast<uint16_t*>(dst) + ci;
+      auto put16 = [&](void* dst, int64_t at, const uint32_t (&x)[V]) {
+        uint16_t* d = reinterpret_cast<uint16_t*>(dst) + at;
         static_assert(V == 8, "16-byte stores");
         *reinterpret_cast<uint4*>(d) = make_uint4(x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16), x[6] | (x[7] << 16));
       };
-      put16(p.C, hi);
-      if (p.C_lo) put16(p.C_lo, lo);
+      put16(p.C, ci, hi);
+      if (copy >= 0) put16(p.C_copy, cc, hi);
+      if (p.C_lo) put16(p.C_lo, ci, lo);
     } else {
       if (p.accumulate) {
         float x[V];
@@ -607,10 +625,11 @@ __global__ __launch_bounds__(256) void splitk_combine_kernel(CombineDev p) {
 #pragma unroll
         for (int e = 0; e < V; ++e) v[e] += x[e];
       }
-      put(p.C, v);
+      put(p.C, ci, v);
+      if (copy >= 0) put(p.C_copy, cc, v);
       if (p.C_lo) {   // partial sums were already rounded to fp32
         const float z[V] = {};
-        put(p.C_lo, z);
+        put(p.C_lo, ci, z);
       }
     }
   }
@@ -618,6 +637,7 @@ __global__ __launch_bounds__(256) void splitk_combine_kernel(CombineDev p) {
 
 hipError_t launch_splitk_combine(const GemmArgs& g, bool in_bf16, hipStream_t st) {
   if (g.row_pos && (g.batch != 1 || g.accumulate || g.drop_thr || g.C_dact)) return hipErrorInvalidValue;
+  if (g.copy_pos && (!g.C_copy || g.batch != 1 || g.accumulate || g.row_pos)) return hipErrorInvalidValue;
   CombineDev d;
   d.partial = g.partial;
   d.splits = g.splits;
@@ -638,6 +658,8 @@ hipError_t launch_splitk_combine(const GemmArgs& g, bool in_bf16, hipStream_t st
   d.drop_seed = g.drop_seed;
   d.M_dev = g.M_dev;
   d.row_pos = g.row_pos;
+  d.copy_pos = g.copy_pos;
+  d.C_copy = g.C_copy;
   // a split chosen by the persistent kernel (dyn_split): its reduction tiles and its grid, as that launch had them
   d.dyn_ktiles = g.dyn_split ? (g.K[0] + 63) / 64 : 0;
   d.dyn_blocks = g.dyn_split ? pp_grid_blocks(((g.M + 255) / 256) * ((g.N + 255) / 256) * g.splits) : 0;
@@ -645,7 +667,7 @@ hipError_t launch_splitk_combine(const GemmArgs& g, bool in_bf16, hipStream_t st
   // for the division.  bf16 widths are multiples of 8.
   const int V = g.c_bf16 ? 8 : 4;
   auto al = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
-  const bool vec = g.N % V == 0 && g.ldc % V == 0 && g.sC % V == 0 && al(g.partial) && al(g.C) && al(g.C_lo) && al(g.C_dact) &&
+  const bool vec = g.N % V == 0 && g.ldc % V == 0 && g.sC % V == 0 && al(g.partial) && al(g.C) && al(g.C_lo) && al(g.C_dact) && al(g.C_copy) &&
                    (!g.gate || (g.ldg % 4 == 0 && al(g.gate))) && (int64_t)g.M * g.N / V < (int64_t)1 << 32;
   int64_t blocks = ((int64_t)g.M * g.N / (vec ? V : 1) + 255) / 256;
   if (blocks > 1 << 17) blocks = 1 << 17;

@@ -77,7 +77,11 @@ template <bool KC, int COLS> __device__ __forceinline__ bf16x8_t gs_frag(const u
   }
 }
 
+// What sets an instance of a tile kernel apart (with the choices made in the kernel its other products were 1 to 8 % slower)
+enum TileExtra { kNoExtra, kSecond, kCopy };   // C_second; copy_pos
+
 // Epilogue of four consecutive columns of a row, in whole vectors
+template <bool COPY>
 __device__ __forceinline__ void gs_finish4(const GemmDev& p, int out_bf16, int batch, int row, int col, f32x4_t v,
                                            const f32x4_t& bias4) {
   const int64_t ci = (int64_t)batch * p.sC + (int64_t)row * p.ldc + col;
@@ -98,7 +102,9 @@ __device__ __forceinline__ void gs_finish4(const GemmDev& p, int out_bf16, int b
     }
   }
   if (p.gate) v *= *reinterpret_cast<const f32x4_t*>(p.gate + (int64_t)row * p.ldg + col);
-  if (p.C_dact) *reinterpret_cast<f32x4_t*>(p.C_dact + ci) = dact;
+  const int copy = COPY ? p.copy_pos[row] : -1;
+  const int64_t cc = (int64_t)copy * p.ldc + col;
+  if (p.C_dact && (copy >= 0 || !COPY)) *reinterpret_cast<f32x4_t*>(p.C_dact + (COPY ? cc : ci)) = dact;
   if (out_bf16) {
     uint32_t hb[4];
     float lo[4];
@@ -109,6 +115,7 @@ __device__ __forceinline__ void gs_finish4(const GemmDev& p, int out_bf16, int b
     }
     const u32x2_t o = {hb[0] | (hb[1] << 16), hb[2] | (hb[3] << 16)};
     *reinterpret_cast<u32x2_t*>(reinterpret_cast<uint16_t*>(p.C) + ci) = o;
+    if (COPY && copy >= 0) *reinterpret_cast<u32x2_t*>(reinterpret_cast<uint16_t*>(p.C_copy) + cc) = o;
     if (p.C_lo) {
       const u32x2_t ol = {pack_bf16(lo[0], lo[1]), pack_bf16(lo[2], lo[3])};
       *reinterpret_cast<u32x2_t*>(p.C_lo + ci) = ol;
@@ -117,9 +124,11 @@ __device__ __forceinline__ void gs_finish4(const GemmDev& p, int out_bf16, int b
     float* C = reinterpret_cast<float*>(p.C) + ci;
     if (p.accumulate) v += *reinterpret_cast<const f32x4_t*>(C);
     *reinterpret_cast<f32x4_t*>(C) = v;
+    if (COPY && copy >= 0) *reinterpret_cast<f32x4_t*>(reinterpret_cast<float*>(p.C_copy) + cc) = v;
   }
 }
 // The same element by element: nc columns inside, nothing aligned
+template <bool COPY>
 __device__ __forceinline__ void gs_finish_ragged(const GemmDev& p, int out_bf16, int batch, int z, int row, int col,
                                                  const f32x4_t& v) {
   const int nc = p.N - col < 4 ? p.N - col : 4;
@@ -141,21 +150,27 @@ __device__ __forceinline__ void gs_finish_ragged(const GemmDev& p, int out_bf16,
     }
     if (p.gate) x *= p.gate[(int64_t)row * p.ldg + col + e];
     const int64_t ci = (int64_t)batch * p.sC + (int64_t)row * p.ldc + col + e;
-    if (p.C_dact) p.C_dact[ci] = dact;
+    const int copy = COPY ? p.copy_pos[row] : -1;
+    const int64_t cc = (int64_t)copy * p.ldc + col + e;
+    if (p.C_dact && (copy >= 0 || !COPY)) p.C_dact[COPY ? cc : ci] = dact;
     if (out_bf16) {
       const uint32_t hb = f32_to_bf16_bits(x);
       reinterpret_cast<uint16_t*>(p.C)[ci] = (uint16_t)hb;
+      if (COPY && copy >= 0) reinterpret_cast<uint16_t*>(p.C_copy)[cc] = (uint16_t)hb;
       if (p.C_lo) p.C_lo[ci] = (uint16_t)f32_to_bf16_bits(x - bf16_bits_to_f32(hb));
     } else {
       float* C = reinterpret_cast<float*>(p.C);
       C[ci] = p.accumulate ? x + C[ci] : x;
+      if (COPY && copy >= 0) reinterpret_cast<float*>(p.C_copy)[cc] = x;
     }
   }
 }
 
-// Block `id` of a launch's tiles of all batches and splits, NST * 2 * 32 TW * ROWB bytes of LDS at smem.
-template <int TW, bool AKC, bool BKC, int NST, bool LACED, bool SECOND>
-__device__ __forceinline__ void gemm_bf16_tile_block(const GemmDev& p, int out_bf16, int id, unsigned char* smem) {
+// Block `id` of a launch's tiles of all batches and splits; dynamic LDS: NST * 2 * 32 TW * ROWB bytes.  (p by value: by reference the
+// instances take five registers more and 182 x 51130 x 128 18.7 us for 17.2.)
+template <int TW, bool AKC, bool BKC, int NST, bool LACED, TileExtra EXTRA>
+__device__ __forceinline__ void gemm_bf16_tile_block(GemmDev p, int out_bf16, int id) {
+  extern __shared__ __align__(1024) unsigned char smem[];
   constexpr int BM = 32 * TW, TILE = BM * ROWB, STAGE = 2 * TILE;   // square block tile; bytes of an operand tile, a stage
   constexpr int NL = TW, LD = BM + 4;                               // loads per wave, operand and tile; staging row (floats)
   static_assert((NST & (NST - 1)) == 0 && NST * STAGE >= 64 * LD * 4, "ring of a power of two; write-out staging");
@@ -170,7 +185,7 @@ __device__ __forceinline__ void gemm_bf16_tile_block(const GemmDev& p, int out_b
   if ((id >> 3) >= per + (xcd < rem)) return;                     // the whole block, before any barrier
   int pid = xcd * per + (xcd < rem ? xcd : rem) + (id >> 3), z = 0;
   if (p.nz > 1) {
-    z = pid / nt;
+    z = __builtin_amdgcn_readfirstlane(pid / nt);
     pid -= z * nt;
   }
   const int gid = pid / (8 * p.tiles_n), first_m = gid * 8;
@@ -178,7 +193,7 @@ __device__ __forceinline__ void gemm_bf16_tile_block(const GemmDev& p, int out_b
   const int in_g = pid - gid * 8 * p.tiles_n;
   const int m0 = (first_m + in_g % gm) * BM, n0 = (in_g / gm) * BM;
   const int batch = z / p.splits, split = z - batch * p.splits;
-  const bool second = SECOND && batch == 1;                      // segment 0 alone, to C_second
+  const bool second = EXTRA == kSecond && batch == 1;                      // segment 0 alone, to C_second
   const int nseg = second ? 1 : kMaxSeg;
 
   // reduction tiles of this block: [t0, t1) of the sequence that runs through the segments one after the other
@@ -196,10 +211,10 @@ __device__ __forceinline__ void gemm_bf16_tile_block(const GemmDev& p, int out_b
   }
   typename std::conditional<AKC, DirectLoader<BM, 4>, StridedLoader<BM>>::type la;
   typename std::conditional<BKC, DirectLoader<BM, 4>, StridedLoader<BM>>::type lb;
-  la.init(p.lda[0], Mv - m0, wave, lane);
-  lb.init(p.ldb[0], p.N - n0, wave, lane);
-  const int64_t stepA = AKC ? BK : BK * p.lda[0], stepB = BKC ? BK : BK * p.ldb[0];
-  const int64_t offA = AKC ? (int64_t)m0 * p.lda[0] : m0, offB = BKC ? (int64_t)n0 * p.ldb[0] : n0;
+  la.init(p.lda, Mv - m0, wave, lane);
+  lb.init(p.ldb, p.N - n0, wave, lane);
+  const int64_t stepA = AKC ? BK : BK * p.lda, stepB = BKC ? BK : BK * p.ldb;
+  const int64_t offA = AKC ? (int64_t)m0 * p.lda : m0, offB = BKC ? (int64_t)n0 * p.ldb : n0;
   int k_left = (seg == 0 ? K0 : p.K[seg]) - skip * BK;
   const uint16_t* cA = p.A[seg] + (int64_t)batch * p.sA[seg] + offA + skip * stepA;
   const uint16_t* cB = p.B[seg] + (int64_t)batch * p.sB[seg] + offB + skip * stepB;
@@ -342,7 +357,7 @@ __device__ __forceinline__ void gemm_bf16_tile_block(const GemmDev& p, int out_b
   const int col = n0 + (tid % VPR) * 4;
   const bool fuse = p.splits <= 1;
   if (second) out_bf16 = 0;
-  const bool plain = p.vec_ok && (!fuse || second || (!p.act_tanh && !p.drop_thr && !p.gate && !p.C_lo && !p.C_dact));
+  const bool plain = p.vec_ok && (!fuse || second || (EXTRA != kCopy && !p.act_tanh && !p.drop_thr && !p.gate && !p.C_lo && !p.C_dact));
   f32x4_t bias4 = {0.f, 0.f, 0.f, 0.f};
   if (fuse && p.bias)
 #pragma unroll
@@ -393,24 +408,23 @@ __device__ __forceinline__ void gemm_bf16_tile_block(const GemmDev& p, int out_b
       for (int r0 = tid / VPR; r0 < left; r0 += RP) {
         const int row = m0 + half * 64 + r0;
         const f32x4_t v = *reinterpret_cast<const f32x4_t*>(stage + r0 * LD + (tid % VPR) * 4);
-        if (p.vec_ok) gs_finish4(p, out_bf16, batch, row, col, v, bias4);
-        else gs_finish_ragged(p, out_bf16, batch, z, row, col, v);
+        if (p.vec_ok) gs_finish4<EXTRA == kCopy>(p, out_bf16, batch, row, col, v, bias4);
+        else gs_finish_ragged<EXTRA == kCopy>(p, out_bf16, batch, z, row, col, v);
       }
     }
     if (half + 1 < BM / 64) __syncthreads();
   }
 }
 
-template <int TW, bool AKC, bool BKC, int NST, bool LACED, bool SECOND>
+template <int TW, bool AKC, bool BKC, int NST, bool LACED, TileExtra EXTRA>
 __global__ __launch_bounds__(256, LACED ? 2 : 1) void gemm_bf16_tile_kernel(GemmDev p, int out_bf16) {
-  extern __shared__ __align__(1024) unsigned char smem[];
-  gemm_bf16_tile_block<TW, AKC, BKC, NST, LACED, SECOND>(p, out_bf16, blockIdx.x, smem);
+  gemm_bf16_tile_block<TW, AKC, BKC, NST, LACED, EXTRA>(p, out_bf16, blockIdx.x);
 }
 
-template <int TW, bool AKC, bool BKC, int NST, bool LACED, bool SECOND = false>
+template <int TW, bool AKC, bool BKC, int NST, bool LACED, TileExtra EXTRA = kNoExtra>
 static hipError_t launch_tile_shape(const GemmDev& d, int out_bf16, hipStream_t st) {
   constexpr int BM = 32 * TW, smem = NST * 2 * BM * ROWB;
-  auto kfn = gemm_bf16_tile_kernel<TW, AKC, BKC, NST, LACED, SECOND>;
+  auto kfn = gemm_bf16_tile_kernel<TW, AKC, BKC, NST, LACED, EXTRA>;
   static LdsLimit limit;
   const hipError_t e = limit.raise(reinterpret_cast<const void*>(kfn), smem);
   if (e != hipSuccess) return e;
@@ -437,11 +451,18 @@ static hipError_t launch_tile_form(const GemmDev& d, GemmTile tile, int out_bf16
       return tile == kTile64 ? launch_tile_shape<2, AKC, BKC, 4, false>(d, out_bf16, st)
                              : launch_tile_shape<4, AKC, BKC, 2, false>(d, out_bf16, st);
   }
-  // (an instance of its own: with the choice made in the kernel its other products were 1 to 8 % slower.  launch_gemm_bf16:
-  // 64 x 64 only)
+  // (launch_gemm_bf16: 64 x 64 only)
   if constexpr (AKC && !BKC) {
-    if (d.C_second) return launch_tile_shape<2, AKC, BKC, 4, true, true>(d, out_bf16, st);
+    if (d.C_second) return launch_tile_shape<2, AKC, BKC, 4, true, kSecond>(d, out_bf16, st);
   }
+  if constexpr (AKC && BKC) {
+    if (d.copy_pos) {
+      if (tile == kTile64) return launch_tile_shape<2, AKC, BKC, 4, true, kCopy>(d, out_bf16, st);
+      return blocks <= 256 ? launch_tile_shape<4, AKC, BKC, 4, true, kCopy>(d, out_bf16, st)
+                           : launch_tile_shape<4, AKC, BKC, 2, true, kCopy>(d, out_bf16, st);
+    }
+  }
+  if (d.copy_pos) return hipErrorInvalidValue;
   if (tile == kTile64) return launch_tile_shape<2, AKC, BKC, 4, true>(d, out_bf16, st);
   // 128 KiB of LDS where no compute unit gets a second block anyway
   if (blocks <= 256) return launch_tile_shape<4, AKC, BKC, 4, true>(d, out_bf16, st);
@@ -455,7 +476,7 @@ static hipError_t launch_tile_form(const GemmDev& d, GemmTile tile, int out_bf16
 // walk the longest reduction comes first; the short blocks of the others fill in behind it.  A training step, apart / together
 // (dW_c with dC and dH1; dW_a with the last product of d_h_dec and d_h_enc): 1920 x 512 271 / 252 us, one step of 128 x 1024
 // 200 / 193, 6400 x 1024 (the latter three, 104 us of it apart) 1387 / 1377.
-template <int TW, bool AKC, bool BKC, int NST, bool LACED, bool SECOND = false>
+template <int TW, bool AKC, bool BKC, int NST, bool LACED, TileExtra EXTRA = kNoExtra>
 struct TileMember {
   GemmDev d;
   int out_bf16, blocks;   // blocks: of the grid, a multiple of 8 so that a product's blocks keep their XCDs
@@ -465,21 +486,20 @@ struct TileMember {
     out_bf16 = obf;
     blocks = (d.tiles_m * d.tiles_n * d.nz + 7) / 8 * 8;
   }
-  __device__ __forceinline__ void run(int id, unsigned char* smem) const {
-    gemm_bf16_tile_block<TW, AKC, BKC, NST, LACED, SECOND>(d, out_bf16, id, smem);
+  __device__ __forceinline__ void run(int id) const {
+    gemm_bf16_tile_block<TW, AKC, BKC, NST, LACED, EXTRA>(d, out_bf16, id);
   }
 };
 template <typename F, typename... R>
-__device__ __forceinline__ void run_member(int id, unsigned char* smem, const F& f, const R&... rest) {
+__device__ __forceinline__ void run_member(int id, const F& f, const R&... rest) {
   if constexpr (sizeof...(R) > 0) {
-    if (id >= f.blocks) return run_member(id - f.blocks, smem, rest...);
+    if (id >= f.blocks) return run_member(id - f.blocks, rest...);
   }
-  f.run(id, smem);
+  f.run(id);
 }
 // last_first: the blocks of the last product come first
 template <typename... M> __global__ __launch_bounds__(256, 2) void gemm_bf16_together_kernel(int last_first, M... m) {
-  extern __shared__ __align__(1024) unsigned char smem[];
-  run_member(last_first ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x, smem, m...);
+  run_member(last_first ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x, m...);
 }
 template <typename... M> static hipError_t launch_members(bool last_first, hipStream_t st, const M&... m) {
   constexpr int sizes[] = {M::kSmem...};
@@ -504,7 +524,8 @@ struct SumsMember {
     d = sums;
     blocks = ((d.V + kDbColumns - 1) / kDbColumns + 7) / 8 * 8;
   }
-  __device__ __forceinline__ void run(int id, unsigned char* smem) const {
+  __device__ __forceinline__ void run(int id) const {
+    extern __shared__ __align__(1024) unsigned char smem[];
     if (id * kDbColumns < d.V) db_reduce_block<256>(d, id, reinterpret_cast<float*>(smem));
   }
 };
@@ -513,7 +534,7 @@ using MemberTNLaced = TileMember<2, false, false, 4, true>;
 using MemberTN128 = TileMember<4, false, false, 2, false>;
 using MemberNN = TileMember<2, true, false, 4, true>;
 using MemberNN128 = TileMember<4, true, false, 2, true>;
-using MemberNNSecond = TileMember<2, true, false, 4, true, true>;
+using MemberNNSecond = TileMember<2, true, false, 4, true, kSecond>;
 using MemberNT = TileMember<2, true, true, 4, true>;
 
 static int tile_ktiles(const GemmDev& d) {   // reduction tiles of a block
@@ -579,7 +600,7 @@ constexpr int kFewWaves = 8;
 __device__ __forceinline__ const uint16_t* few_pick(int seg, const uint16_t* a, const uint16_t* b, const uint16_t* c) {
   return seg == 0 ? a : seg == 1 ? b : c;
 }
-template <int NJ>
+template <int NJ, bool COPY>
 __global__ __launch_bounds__(64 * kFewWaves) void gemm_bf16_few_kernel(GemmDev p, int out_bf16, int nseg) {
   constexpr int PF = 4;
   __shared__ f32x4_t red[kFewWaves * NJ * 64];   // [wave][row tile][lane]
@@ -591,10 +612,10 @@ __global__ __launch_bounds__(64 * kFewWaves) void gemm_bf16_few_kernel(GemmDev p
   if (bn >= nbn) return;
   const int n0 = bn * 16, m0 = (idx % nbm) * 16 * NJ, K = p.K[0], nk = (K + 63) / 64;
   const int col = n0 + c < p.N ? n0 + c : p.N - 1;   // columns and rows outside repeat the last one; not stored
-  const int64_t boff = (int64_t)col * p.ldb[0];
+  const int64_t boff = (int64_t)col * p.ldb;
   int64_t aoff[NJ];
 #pragma unroll
-  for (int j = 0; j < NJ; ++j) aoff[j] = (int64_t)(m0 + 16 * j + c < p.M ? m0 + 16 * j + c : p.M - 1) * p.lda[0];
+  for (int j = 0; j < NJ; ++j) aoff[j] = (int64_t)(m0 + 16 * j + c < p.M ? m0 + 16 * j + c : p.M - 1) * p.lda;
   const uint16_t *A0 = p.A[0], *A1 = p.A[1], *A2 = p.A[2], *B0 = p.B[0], *B1 = p.B[1], *B2 = p.B[2];
   f32x4_t acc[NJ];
 #pragma unroll
@@ -643,14 +664,14 @@ __global__ __launch_bounds__(64 * kFewWaves) void gemm_bf16_few_kernel(GemmDev p
   const int row = m0 + 16 * wave + c, ccol = n0 + 4 * q;
   if (row >= p.M || ccol >= p.N) return;
   if (!p.vec_ok) {
-    gs_finish_ragged(p, out_bf16, 0, 0, row, ccol, v);
+    gs_finish_ragged<COPY>(p, out_bf16, 0, 0, row, ccol, v);
     return;
   }
   f32x4_t bias4 = {0.f, 0.f, 0.f, 0.f};
   if (p.bias)
 #pragma unroll
     for (int e = 0; e < 4; ++e) bias4[e] = bf16_bits_to_f32(p.bias[ccol + e]);
-  gs_finish4(p, out_bf16, 0, row, ccol, v, bias4);
+  gs_finish4<COPY>(p, out_bf16, 0, row, ccol, v, bias4);
 }
 hipError_t launch_gemm_bf16_few(const GemmDev& d, bool out_bf16, hipStream_t st) {
   int nseg = 0;
@@ -661,8 +682,9 @@ hipError_t launch_gemm_bf16_few(const GemmDev& d, bool out_bf16, hipStream_t st)
   const int nj = d.M > 16 ? 2 : 1;
   const int64_t nbm = (d.M + 16 * nj - 1) / (16 * nj), per = ((d.N + 15) / 16 + 7) / 8;
   const dim3 grid((unsigned)(8 * per * nbm));
-  if (nj == 2) hipLaunchKernelGGL(gemm_bf16_few_kernel<2>, grid, dim3(64 * kFewWaves), 0, st, d, (int)out_bf16, nseg);
-  else hipLaunchKernelGGL(gemm_bf16_few_kernel<1>, grid, dim3(64 * kFewWaves), 0, st, d, (int)out_bf16, nseg);
+  auto kfn = nj == 2 ? (d.copy_pos ? gemm_bf16_few_kernel<2, true> : gemm_bf16_few_kernel<2, false>)
+                     : (d.copy_pos ? gemm_bf16_few_kernel<1, true> : gemm_bf16_few_kernel<1, false>);
+  hipLaunchKernelGGL(kfn, grid, dim3(64 * kFewWaves), 0, st, d, (int)out_bf16, nseg);
   return hipGetLastError();
 }
 

@@ -7,13 +7,27 @@
 
 namespace asx {
 
+// Row compaction (rows / n_act below, both null = off): logits, lse and tok_loss_ws hold only the *n_act rows
+// whose target is not padding, row r being position rows[r]; N stays the bound the launch is sized for.
+// Position n -> row_pos[n] (its compacted row, -1 at padding), the list rows[0 .. *n_act) of positions in
+// increasing order, *n_act; optional per-position outputs: tgt_mask everywhere, tok_loss = 0 and
+// argmax = pad_id at padding (the statistics kernel fills the other positions).  Made by an extra block of the attention.
+struct RowList {
+  const int32_t* targets;   // null: no list wanted
+  int N, V, pad_id;
+  int32_t *row_pos, *rows, *n_act;
+  uint8_t* tgt_mask;
+  float* tok_loss;
+  int32_t* argmax;
+};
+
 // Eq. 1: alpha[b,t,:] = softmax(score[b,t,:]) over s < clamp(src_len[b],0,S),
 // exactly 0 elsewhere.  Writes alpha32 [B,T,S], a copy in the storage type
 // alphaE [B,T,ldS] (columns S..ldS-1 zero), if non-null the rounding remainder
 // alphaE_lo = alpha - alphaE in the storage type, and, if non-null, attn_mask [B,S].
 hipError_t launch_attn_softmax_rows(const float* score, const int32_t* src_len, int B, int T, int S,
                                     float* alpha32, void* alphaE, void* alphaE_lo, int64_t ldS, bool e_bf16,
-                                    uint8_t* attn_mask, hipStream_t st);
+                                    uint8_t* attn_mask, const RowList& list, hipStream_t st);
 // Softmax Jacobian: dscore = alpha * (dalpha - sum_s alpha*dalpha), storage type, [B,T,ldS] zero
 // padded; dscoreE_lo (optional) receives the rounding remainder.
 hipError_t launch_attn_softmax_rows_bwd(const float* alpha32, const float* dalpha, int B, int T, int S,
@@ -26,20 +40,13 @@ hipError_t launch_attn_softmax_rows_bwd(const float* alpha32, const float* dalph
 bool attn_fwd_fused_supported(int S, int H);
 hipError_t launch_attn_fwd_fused(const void* q_hi, const void* q_lo, const void* h_enc, const int32_t* src_len, int B,
                                  int T, int S, int H, float* alpha32, void* alphaE, void* alphaE_lo, int64_t ldS,
-                                 void* ctx, void* ctx_lo, uint8_t* attn_mask, hipStream_t st);
+                                 void* ctx, void* ctx_lo, uint8_t* attn_mask, const RowList& list, hipStream_t st);
 // First half of the attention backward pass with the same kernel: dC_hi / dC_lo [T,B,H], alpha32 [B,T,S] (read) ->
 // dscoreE / dscoreE_lo [B,T,ldS] (softmax Jacobian, zero padded) and dQ [T,B,H] = dscore . h_enc (value only).
 hipError_t launch_attn_bwd_fused(const void* dC_hi, const void* dC_lo, const void* h_enc, const int32_t* src_len,
                                  int B, int T, int S, int H, const float* alpha32, void* dscoreE, void* dscoreE_lo,
                                  int64_t ldS, void* dQ, hipStream_t st);
 
-// Row compaction (rows / n_act below, both null = off): logits, lse and tok_loss_ws hold only the *n_act rows
-// whose target is not padding, row r being position rows[r]; N stays the bound the launch is sized for.
-// Position n -> row_pos[n] (its compacted row, -1 at padding), the list rows[0 .. *n_act) of positions in
-// increasing order, *n_act; optional per-position outputs: tgt_mask everywhere, tok_loss = 0 and
-// argmax = pad_id at padding (the statistics kernel fills the other positions).
-hipError_t launch_row_compact(const int32_t* targets, int N, int V, int pad_id, int32_t* row_pos, int32_t* rows,
-                              int32_t* n_act, uint8_t* tgt_mask, float* tok_loss, int32_t* argmax, hipStream_t st);
 // dst_x[r] = src_x[rows[r]], r < *n_act; rows of bytes_x bytes (multiples of 4); the second array is optional
 hipError_t launch_gather_rows(const int32_t* rows, const int32_t* n_act, int N, const void* src0, void* dst0,
                               int64_t bytes0, const void* src1, void* dst1, int64_t bytes1, hipStream_t st);

@@ -302,3 +302,14 @@ def test_f32_products_of_a_pass_in_one_launch(shape, skip):
     """dW_out with dz, dW_c with dC and dH1, dW_a with d_h_dec and d_h_enc, blocks of one product behind those of another."""
     T, S, B, H, V = shape
     _parity(make_custom(T=T, S=S, B=B, H=H, V=V, seed=V + H, dtype="f32", min_len=1, pad_prob=0.2), skip)
+
+
+@pytest.mark.parametrize("dtype, S", [("bf16", 5), ("bf16", 129), ("f32", 5)])     # beside either form of the attention
+@pytest.mark.parametrize("T, B", [(1, 1), (3, 171), (64, 64), (241, 17), (723, 17)])   # 4096 positions at a time: 4096, 4097, 12291
+def test_list_of_word_positions(T, B, dtype, S):
+    """Row compaction: words numbered in increasing position, -1 at padding (compared by fwd), and the outputs at padding."""
+    inp = make_custom(T=T, S=S, B=B, H=8, V=11, seed=T, dtype=dtype, min_len=1, pad_prob=0.4)
+    f = pu.GpuRun(inp, skip_pad_rows=True).fwd()
+    pad = inp.targets == inp.pad_id
+    assert np.array_equal(f["tgt_mask"].astype(bool), ~pad) and f["n_tok"] == int((~pad).sum())
+    assert np.all(f["tok_loss"][pad] == 0.0) and np.all(f["argmax"][pad] == inp.pad_id)
