@@ -30,6 +30,7 @@ struct LsLayout {
   int64_t x_stride, h_stride, g_stride;   // bytes of one step's operand as fragment tiles
   size_t gates, cs, hE, out, dG;          // [L] (out: [L - 1]) blocks each
   size_t hf, dcs, dbacc, partial, total;
+  size_t h0_copy;                         // T = 1: h0 and c0 where an output lies on top of them
   size_t xF, zeros, hF[2], oF[2], dGF;    // fragment tiles; [0] value, [1] remainder (bf16 storage)
   std::vector<size_t> Wf_hh, Wf_ih, Wb_hh, Wb_up;   // weights as tiles, per layer
   std::vector<GemmPlan> p_dwi;
@@ -37,6 +38,7 @@ struct LsLayout {
   bool dwh_batched, dwi_batched;   // dW_hh of all layers, dW_ih of all but the first, in one launch
   bool x_apart;   // the input product of layer 0 ahead of the wavefronts
   bool w_rows;    // forward wavefronts read the caller's weight rows
+  bool direct;    // and layer 0 his initial state and input
   int group;      // T = 1, backward: wavefronts whose weights are tiles at the same time
 };
 
@@ -66,10 +68,12 @@ template <typename TE, typename Take> void ls_fwd_tiles(const ls_shape* s, LsLay
   const int copies = sizeof(TE) == 2 ? 2 : 1;
   L.x_apart = ls_input_apart<TE>(T, I, H, NL);
   L.w_rows = ls_reads_weight_rows<TE>(T, I, H);
+  L.direct = L.w_rows && ls_reads_states<TE>(H, s->B);
   L.x_stride = L.x_apart ? 0 : (int64_t)(ls_ksteps<TE>(I) * nct * kLsTile);
   L.h_stride = (int64_t)(ls_ksteps<TE>(H) * nct * kLsTile);
   L.xF = take((size_t)L.x_stride * T);
   L.zeros = take(nct * kLsTile);
+  L.h0_copy = take(L.direct ? 2 * (size_t)NL * s->B * H * 4 : 0);
   for (int k = 0; k < copies; ++k) {
     L.hF[k] = take((size_t)L.h_stride * 2 * NL);
     L.oF[k] = take((size_t)L.h_stride * 2 * (NL - 1));
@@ -194,6 +198,11 @@ as_status check_ls(const ls_shape* s, void* ws, size_t ws_bytes, LsLayout* L) {
     if (e_ != hipSuccess) return set_error(AS_ERR_HIP, "%s: %s", #expr, hipGetErrorString(e_)); \
   } while (0)
 
+bool ranges_meet(const void* a, int64_t na, const void* b, int64_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + (uintptr_t)nb && y < x + (uintptr_t)na;
+}
+
 template <typename TE>
 as_status ls_fwd(const ls_shape* s, const LsLayout& L, const char* x, const int32_t* lengths,
                  const void* const* W_ih, const void* const* W_hh, const void* const* b, const float* h0,
@@ -210,7 +219,7 @@ as_status ls_fwd(const ls_shape* s, const LsLayout& L, const char* x, const int3
     f.W_ih[l] = f.w_rows ? W_ih[l] : w + L.Wf_ih[l];
     f.bias[l] = b[l];
   }
-  q.x = x; q.h0 = h0; q.c0 = c0;
+  f.x = x; f.h0 = h0; f.c0 = c0;
   f.xF = w + L.xF; f.zeros = w + L.zeros; f.x_stride = L.x_stride;
   f.hF_hi = w + L.hF[0]; f.hF_lo = w + L.hF[1];
   f.oF_hi = w + L.oF[0]; f.oF_lo = w + L.oF[1];
@@ -225,7 +234,32 @@ as_status ls_fwd(const ls_shape* s, const LsLayout& L, const char* x, const int3
   f.drop_thr = s->dropout_p > 0.f ? (uint32_t)((double)s->dropout_p * 4294967296.0) : 0u;
   f.drop_scale = 1.f / (1.f - s->dropout_p);
   f.drop_seed = s->dropout_seed;
-  LS_TRY(launch_ls_prep_fwd<TE>(f, q, st));
+  f.direct = L.direct;
+  if (f.direct) {
+    // Read by every block of a layer while others of its launch write the outputs: where the caller has an output on top of an
+    // input, from a copy.
+    const int64_t states = s->L * L.BH * 4, xbytes = L.TB * s->I * (int64_t)sizeof(TE);
+    const void* outs[] = {y, hT, cT};
+    const int64_t sizes[] = {L.TB * s->H * (int64_t)sizeof(TE), states, states};
+    auto overwritten = [&](const void* in, int64_t bytes) {
+      bool hit = false;
+      for (int k = 0; in && k < 3; ++k) hit = hit || (outs[k] && ranges_meet(in, bytes, outs[k], sizes[k]));
+      return hit;
+    };
+    LsCopy c{};
+    auto safe = [&](const void* in, int64_t bytes, char* place) -> const void* {
+      if (!overwritten(in, bytes)) return in;
+      c.add(in, place, bytes);
+      return place;
+    };
+    f.x = safe(x, xbytes, w + L.xF);
+    f.h0 = static_cast<const float*>(safe(h0, states, w + L.h0_copy));
+    if (c0 != cT)   // (a cell's state is read and written by the same lane)
+      f.c0 = static_cast<const float*>(safe(c0, states, w + L.h0_copy + states));
+    if (c.n) LS_TRY(launch_ls_copy(c, st));
+  } else {
+    LS_TRY(launch_ls_prep_fwd<TE>(f, q, st));
+  }
   if (L.x_apart) {   // x W_ih^T + b of layer 0, all steps
     GemmArgs g;
     g.seg(x, s->I, 0, W_ih[0], s->I, 0, s->I);

@@ -47,7 +47,10 @@ struct LsFwd {
   float *hf, *cT;                  // [L][B,H] final h: h0 from the prepare launch, overwritten at a sentence's last step; final c (or null)
   const int32_t* lengths;
   int T, B, I, H, L;
-  int w_rows;
+  int w_rows;                      // one step: the caller's weight rows are read
+  int direct;                      // one step: layer 0 reads x, h0 and c0, and prepares the states of the other layers
+  const void* x;                   // the caller's
+  const float *h0, *c0;            // the caller's initial states (null: zeros)
   int x_apart;                     // layer 0: gates hold x W_ih^T + b when a wavefront starts (x and W_ih are not read)
   uint32_t drop_thr;               // dropout on the outputs below the top layer; 0: none
   float drop_scale;
@@ -70,13 +73,20 @@ struct LsBwd {
   uint64_t drop_seed;
 };
 
-// Before the first wavefront: states of step 0 (h0, c0 may be null = zeros), x and, unless p.w_rows, the weights as
-// tiles (W_hh, W_ih: the caller's rows; p.W_*: where the tiles go).
+// Before the first wavefront, unless p.direct: states of step 0 (h0, c0 may be null = zeros), x and, unless p.w_rows, the
+// weights as tiles (W_hh, W_ih: the caller's rows; p.W_*: where the tiles go).
 struct LsPrepFwd {
   const void *W_hh[kLsMaxLayers], *W_ih[kLsMaxLayers];
-  const void* x;
-  const float *h0, *c0;
 };
+// up to three arrays of 4-byte words
+struct LsCopy {
+  const void* src[3];
+  void* dst[3];
+  int64_t words[3];
+  int n;
+  void add(const void* s, void* d, int64_t bytes) { src[n] = s; dst[n] = d; words[n++] = bytes / 4; }
+};
+hipError_t launch_ls_copy(const LsCopy& c, hipStream_t st);
 template <typename TE> hipError_t launch_ls_prep_fwd(const LsFwd& p, const LsPrepFwd& q, hipStream_t st);
 // tiles of n transposed [4H,H] weights (W_hh[l], W_ih[l + 1]) into the places p.WT_* point to
 struct LsPrepBwd {
@@ -99,6 +109,8 @@ hipError_t launch_ls_bias_reduce(const float* dbacc, const LsBiasOut& o, int L, 
 template <typename TE> bool ls_input_apart(int T, int I, int H, int L);
 // Whether forward wavefronts read the caller's weight rows instead of tiles made from them.
 template <typename TE> bool ls_reads_weight_rows(int T, int I, int H);
+// Whether layer 0 of one step reads the caller's initial state and input instead of tiles made from them.
+template <typename TE> bool ls_reads_states(int H, int B);
 // Reduction steps of those rows that a wave has in flight in the smaller blocks (bf16; K: input width of the layer).
 int ls_row_steps_in_flight(int K, int H);
 

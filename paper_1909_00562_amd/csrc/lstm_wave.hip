@@ -212,15 +212,95 @@ __device__ __forceinline__ bool ls_block_of(int nslices, int nbt, int& slice, in
 }
 static inline unsigned ls_grid(int64_t nslices, int64_t nbt) { return (unsigned)((nslices + 7) / 8 * 8 * nbt); }
 
+// ---- operands as tiles -------------------------------------------------------------
+template <typename TE>
+__device__ __forceinline__ void ls_copy_chunk(char* dst, const TE* src, int n) {
+  constexpr int V = LsGeom<TE>::kVec;
+  if (n >= V && (reinterpret_cast<uintptr_t>(src) & 15) == 0) {
+    *reinterpret_cast<ls_u32x4_t*>(dst) = *reinterpret_cast<const ls_u32x4_t*>(src);
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < V; ++e) reinterpret_cast<TE*>(dst)[e] = e < n ? src[e] : (TE)0;
+}
+
+// Initial state of layer l: as tiles, and where the backward pass looks for it.  padding: only the zeros behind the reduction.
+template <typename TE>
+__device__ __forceinline__ void ls_prep_state(const LsFwd& p, int l, int64_t first, int64_t stride, bool padding) {
+  typedef LsMma<TE> M;
+  constexpr int V = LsGeom<TE>::kVec, KST = LsGeom<TE>::kKStep;
+  const int H = p.H, B = p.B, L = p.L, nct = (B + 15) >> 4;
+  const int64_t BH = (int64_t)B * H;
+  const int64_t n = (int64_t)((H + KST - 1) / KST) * nct * 64;
+  TE* hE = reinterpret_cast<TE*>(p.hE) + (int64_t)l * (p.T + 1) * BH;
+  float* cs = p.cs + (int64_t)l * (p.T + 1) * BH;
+  for (int64_t i = first; i < n; i += stride) {
+    const int lane = (int)(i & 63), k = (int)((i >> 6) / nct) * KST + (lane >> 4) * V;
+    const int64_t tile = i >> 6;
+    const int b = (int)(tile % nct) * 16 + (lane & 15);
+    if (padding && k < H) continue;
+    alignas(16) TE hi[V], lo[V];
+    // a chunk of V units inside, its rows aligned: whole vectors (one step of 4 x 1024 units x 128 sentences: 8.6 -> 5.3 us)
+    const bool whole = H % V == 0 && b < B && k < H;
+    if (whole) {
+      const int64_t row = (int64_t)b * H + k, idx = (int64_t)l * BH + row;
+      f32x4_t h[V / 4], c[V / 4];
+#pragma unroll
+      for (int v = 0; v < V / 4; ++v) {
+        h[v] = p.h0 ? *reinterpret_cast<const f32x4_t*>(p.h0 + idx + 4 * v) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+        c[v] = p.c0 ? *reinterpret_cast<const f32x4_t*>(p.c0 + idx + 4 * v) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+      for (int v = 0; v < V / 4; ++v) {
+        ls_st4<true>(p.hf + idx + 4 * v, h[v], 4);
+        ls_st4<true>(cs + row + 4 * v, c[v], 4);
+        ls_st4<true>(hE + row + 4 * v, h[v], 4);
+        ls_st4<true>(hi + 4 * v, h[v], 4);
+        ls_st4<true>(lo + 4 * v, ls_rest<TE>(h[v]), 4);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      if (whole) break;
+      const bool in = b < B && k + e < H;
+      const int64_t idx = (int64_t)l * BH + (int64_t)(in ? b : 0) * H + (in ? k + e : 0);
+      const float h = in && p.h0 ? p.h0[idx] : 0.f;
+      st_elem<TE>(hi, e, h);
+      st_elem<TE>(lo, e, h - round_elem<TE>(h));
+      if (in) {
+        const float c = p.c0 ? p.c0[idx] : 0.f;
+        p.hf[idx] = h;
+        cs[idx - (int64_t)l * BH] = c;
+        st_elem<TE>(hE, idx - (int64_t)l * BH, h);
+      }
+    }
+    auto put = [&](char* base, const TE (&v)[V]) {
+      *reinterpret_cast<ls_u32x4_t*>(base + i * 16) = *reinterpret_cast<const ls_u32x4_t*>(v);
+    };
+    put(p.hF_hi + 2 * l * p.h_stride, hi);
+    if constexpr (M::kPair) put(p.hF_lo + 2 * l * p.h_stride, lo);
+    if (k >= H) {   // reduction padding: zero in every slot
+      alignas(16) const TE z[V] = {};
+      put(p.hF_hi + (2 * l + 1) * p.h_stride, z);
+      if constexpr (M::kPair) put(p.hF_lo + (2 * l + 1) * p.h_stride, z);
+      if (l + 1 < L)
+        for (int sl = 0; sl < 2; ++sl) {
+          put(p.oF_hi + (2 * l + sl) * p.h_stride, z);
+          if constexpr (M::kPair) put(p.oF_lo + (2 * l + sl) * p.h_stride, z);
+        }
+    }
+  }
+}
+
 // ---- forward ---------------------------------------------------------------------
 // Block: 16 * NI gate rows (4 * NI hidden units) x 16 * NJ sentences.  Tile 4 g + ii of a block, row rho: unit
 // u0 + 16 g + 4 q + ii, gate r, (q, r) = the lane group and register that hold row rho.  ROWS: weights are read as the
 // caller's rows (64 bytes of a row per load), each used once by the call; steps of the reduction, their waves and the order
 // inside a step are those of the tiles, so that a step by itself gives the bits it has in a sequence (whole lines of a row
 // per step: 4 x 1024 units x 128 sentences 114.7 us for 116.9, 4 x 192 units x 116 sentences 75.5 for 73.8, and other bits).
-// APART: layer 0 finds the input product and the
+// ROWS = 2: layer 0 of ls_reads_states.  APART: layer 0 finds the input product and the
 // bias in the gates' place.
-template <typename TE, int NI, int NJ, int PF, bool ROWS, bool VEC, bool APART>
+template <typename TE, int NI, int NJ, int PF, int ROWS, bool VEC, bool APART>
 __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d, int l_lo, int n_layers) {
   typedef LsMma<TE> M;
   typedef typename M::acc_t acc_t;
@@ -233,6 +313,15 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
   const uint32_t lane16 = lane * 16u;
   const int H = p.H, B = p.B, nct = (B + 15) >> 4;
   const int nut = (H + 4 * NI - 1) / (4 * NI), nbt = (B + 16 * NJ - 1) / (16 * NJ);
+  constexpr bool DIRECT = ROWS == 2;
+  if constexpr (DIRECT) {   // blocks past the layer's: the states of the others as tiles
+    const int own = (n_layers * nut + 7) / 8 * 8 * nbt, extra = (int)blockIdx.x - own;
+    if (extra >= 0) {
+      const int per = ((int)gridDim.x - own) / p.L, job = extra / per;
+      ls_prep_state<TE>(p, job, (int64_t)(extra - job * per) * blockDim.x + threadIdx.x, (int64_t)per * blockDim.x, job == 0);
+      return;
+    }
+  }
   int slice, bt;
   if (!ls_block_of(n_layers * nut, nbt, slice, bt)) return;
   const int l = l_lo + slice / nut, u0 = (slice % nut) * 4 * NI, b0 = bt * 16 * NJ;
@@ -243,9 +332,10 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
   // what the cells need from memory is requested ahead of the product
   constexpr int NTASK = (NG * NJ + LS_KS - 1) / LS_KS;   // (g, j) pairs, dealt out to the waves
   // (lanes and tasks without a cell read the last one: no branch around a load that is to stay in flight)
-  f32x4_t cp[NTASK];
+  f32x4_t cp[NTASK], hp[NTASK];   // hp (DIRECT): the initial state itself
   typename M::raw4_t bias[NTASK][4];
-  const float* c_prev = p.cs + ((int64_t)l * (p.T + 1) + t) * BH;
+  const float* c_prev = DIRECT && p.c0 ? p.c0 + l * BH : p.cs + ((int64_t)l * (p.T + 1) + t) * BH;
+  const float* h_prev = p.h0 ? p.h0 + l * BH : c_prev;
   const TE* bl = reinterpret_cast<const TE*>(p.bias[l]);
 #pragma unroll
   for (int k = 0; k < NTASK; ++k) {
@@ -253,6 +343,7 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
     const int b = b0 + 16 * j + c, unit0 = u0 + 16 * g + 4 * q;
     const int bs = b < B ? b : B - 1, us = unit0 < H ? unit0 : (H - 1) & ~3;
     cp[k] = ls_ld4<VEC>(c_prev + (int64_t)bs * H + us, H - us);
+    if constexpr (DIRECT) hp[k] = ls_ld4<VEC>(h_prev + (int64_t)bs * H + us, H - us);
 #pragma unroll
     for (int e = 0; e < 4; ++e) bias[k][e] = ls_ldraw4<VEC>(bl + (int64_t)e * H + us, H - us);
   }
@@ -277,9 +368,9 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
   const int64_t cstep = (int64_t)nct * kLsTile;
   const char* h_hi = p.hF_hi + (2 * l + (t & 1)) * p.h_stride;
   const char* h_lo = M::kPair ? p.hF_lo + (2 * l + (t & 1)) * p.h_stride : nullptr;
-  const char* i_hi = l == 0 ? p.xF + t * p.x_stride : p.oF_hi + (2 * (l - 1) + (t & 1)) * p.h_stride;
-  const bool no_rest = !TWO && !APART && l == 0;   // the input's remainder: zeroed tiles
-  const char* i_lo = !M::kPair ? nullptr : no_rest ? p.zeros : p.oF_lo + (2 * (l - 1) + (t & 1)) * p.h_stride;
+  const char* i_hi = DIRECT ? reinterpret_cast<const char*>(p.x) : l == 0 ? p.xF + t * p.x_stride : p.oF_hi + (2 * (l - 1) + (t & 1)) * p.h_stride;
+  const bool no_rest = !TWO && !APART && l == 0;   // the input's remainder: zeroed tiles (DIRECT: the input again)
+  const char* i_lo = !M::kPair ? nullptr : DIRECT ? i_hi : no_rest ? p.zeros : p.oF_lo + (2 * (l - 1) + (t & 1)) * p.h_stride;
   const int64_t lstep1 = no_rest ? 0 : cstep;
   int64_t ctoff[NJ];
 #pragma unroll
@@ -289,7 +380,18 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
   }
   const char* w0 = reinterpret_cast<const char*>(p.W_hh[l]) + (ROWS ? 0 : (int64_t)(u0 / 16) * n0 * 4 * kLsTile);
   const char* w1 = reinterpret_cast<const char*>(p.W_ih[l]) + (ROWS ? 0 : (int64_t)(u0 / 16) * n1 * 4 * kLsTile);
+  // DIRECT: the caller's initial state as float, split into value and remainder after the load, and his input's rows
   int wrow[NI];
+  int64_t hrow[NJ], xrow[NJ];
+  const char* h_f32 = reinterpret_cast<const char*>(h_prev);
+  if constexpr (DIRECT) {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int b = b0 + 16 * j + c, bs = b < B ? b : B - 1;
+      hrow[j] = (int64_t)bs * H * 4;
+      xrow[j] = (int64_t)bs * p.I * sizeof(TE);
+    }
+  }
   if constexpr (ROWS) {
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
@@ -315,6 +417,17 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
       for (int i = 0; i < NI; ++i)
         wf[slot][i] = ls_frag(wb + (i / 4) * group + (i % 4) * kLsTile, lane16);
     }
+    if constexpr (DIRECT) {
+      const int K = in ? Kin : H, kk = k * KST + q * V, kc = kk < K ? kk : 0;
+      const char *hb = in ? i_hi : h_f32, *lb = in ? i_lo : h_f32 + 16;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int64_t off = in ? xrow[j] + kc * (int)sizeof(TE) : hrow[j] + kc * 4;
+        hf[slot][j] = *reinterpret_cast<const ls_u32x4_t*>(hb + off);
+        if constexpr (M::kPair) lf[slot][j] = *reinterpret_cast<const ls_u32x4_t*>(lb + off);
+      }
+      return;
+    }
     const char* hb = (in ? i_hi : h_hi) + k * cstep;
 #pragma unroll
     for (int j = 0; j < NJ; ++j) hf[slot][j] = ls_frag(hb + ctoff[j], lane16);
@@ -326,12 +439,30 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
   };
   auto mul = [&](int slot, int step, bool rest = true) {
     const int s = wave + step * LS_KS;
-    if constexpr (ROWS) {   // chunks past a row's end were read from its start
+    if constexpr (ROWS) {   // chunks past a row's end were read from its start (DIRECT: both operands cleared, 0 * inf)
       const int K = s >= n0 ? Kin : H, kk = (s >= n0 ? s - n0 : s) * KST + q * V;
 #pragma unroll
       for (int i = 0; i < NI; ++i)
 #pragma unroll
         for (int e = 0; e < 4; ++e) wf[slot][i][e] = kk < K ? wf[slot][i][e] : 0u;
+      const bool state = s < n0, live = kk < K && (!state || p.h0);
+#pragma unroll
+      for (int j = 0; j < (DIRECT ? NJ : 0); ++j) {
+        if constexpr (M::kPair) {
+          const f32x4_t h0 = __builtin_bit_cast(f32x4_t, hf[slot][j]), h1 = __builtin_bit_cast(f32x4_t, lf[slot][j]);
+          const f32x4_t r0 = ls_rest<TE>(h0), r1 = ls_rest<TE>(h1);
+          const ls_u32x4_t hi = {pack_bf16(h0[0], h0[1]), pack_bf16(h0[2], h0[3]), pack_bf16(h1[0], h1[1]), pack_bf16(h1[2], h1[3])};
+          const ls_u32x4_t lo = {pack_bf16(r0[0], r0[1]), pack_bf16(r0[2], r0[3]), pack_bf16(r1[0], r1[1]), pack_bf16(r1[2], r1[3])};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            hf[slot][j][e] = live ? state ? hi[e] : hf[slot][j][e] : 0u;
+            lf[slot][j][e] = live ? state ? lo[e] : lf[slot][j][e] : 0u;
+          }
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) hf[slot][j][e] = live ? hf[slot][j][e] : 0u;
+        }
+      }
     }
 #pragma unroll
     for (int i = 0; i < NI; ++i)
@@ -396,6 +527,10 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
     const int n = H - unit0;
     float* G = p.gates + ((int64_t)l * p.T + t) * 4 * BH + (int64_t)b * 4 * H + unit0;
     f32x4_t gi, gf, gg, go, cn, hn, bias4[4];
+    if constexpr (DIRECT) {
+      if (!p.c0) cp[k] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      if (!p.h0) hp[k] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
     if (apart) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) bias4[e] = ls_ld4<VEC>(G + (int64_t)e * H, n);
@@ -420,6 +555,10 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
       hn[ii] = go[ii] * ls_tanh(cn[ii]);
     }
     const int64_t idx = (int64_t)b * H + unit0;
+    if constexpr (DIRECT) {   // what the preparation leaves elsewhere
+      ls_st4<VEC>(p.cs + (int64_t)l * (p.T + 1) * BH + idx, cp[k], n);
+      ls_st4<VEC>(reinterpret_cast<TE*>(p.hE) + (int64_t)l * (p.T + 1) * BH + idx, hp[k], n);
+    }
     ls_st4_away<VEC>(G, gi, n);
     ls_st4_away<VEC>(G + H, gf, n);
     ls_st4_away<VEC>(G + 2 * (int64_t)H, gg, n);
@@ -443,8 +582,14 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
       }
       hv = hn;
       if (t + 1 == len) ls_st4<VEC>(p.hf + l * BH + idx, hn, n);   // the final state
-      ls_st4<true>(hFn_hi, hn, 4);
-      if constexpr (M::kPair) ls_st4<true>(hFn_lo, ls_rest<TE>(hn), 4);
+      if constexpr (!DIRECT) {
+        ls_st4<true>(hFn_hi, hn, 4);
+        if constexpr (M::kPair) ls_st4<true>(hFn_lo, ls_rest<TE>(hn), 4);
+      }
+    } else if constexpr (DIRECT) {
+      cn = cp[k];
+      hv = hp[k];
+      ls_st4<VEC>(p.hf + l * BH + idx, hv, n);
     } else {       // padded step: the state passes through, the output is 0
       cn = cp[k];
       hv = ls_widen4(ls_ldraw4<true>(reinterpret_cast<const TE*>(h_hi) + foff, 4));
@@ -702,18 +847,6 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_bwd_kernel(LsBwd p, int d,
   }
 }
 
-// ---- operands as tiles -------------------------------------------------------------
-template <typename TE>
-__device__ __forceinline__ void ls_copy_chunk(char* dst, const TE* src, int n) {
-  constexpr int V = LsGeom<TE>::kVec;
-  if (n >= V && (reinterpret_cast<uintptr_t>(src) & 15) == 0) {
-    *reinterpret_cast<ls_u32x4_t*>(dst) = *reinterpret_cast<const ls_u32x4_t*>(src);
-    return;
-  }
-#pragma unroll
-  for (int e = 0; e < V; ++e) reinterpret_cast<TE*>(dst)[e] = e < n ? src[e] : (TE)0;
-}
-
 // Jobs (blockIdx.y): 0 .. L-1 states of a layer, L the input x, then (unless w_rows) W_hh and W_ih of each layer.
 template <typename TE>
 __global__ __launch_bounds__(256) void ls_prep_fwd_kernel(LsFwd p, LsPrepFwd s) {
@@ -723,70 +856,12 @@ __global__ __launch_bounds__(256) void ls_prep_fwd_kernel(LsFwd p, LsPrepFwd s) 
   const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x, stride = (int64_t)gridDim.x * 256;
   const int64_t BH = (int64_t)B * H;
   if (job < L) {
-    const int l = job;
-    const int64_t n = (int64_t)((H + KST - 1) / KST) * nct * 64;
-    TE* hE = reinterpret_cast<TE*>(p.hE) + (int64_t)l * (p.T + 1) * BH;
-    float* cs = p.cs + (int64_t)l * (p.T + 1) * BH;
-    for (int64_t i = first; i < n; i += stride) {
-      const int lane = (int)(i & 63), k = (int)((i >> 6) / nct) * KST + (lane >> 4) * V;
-      const int64_t tile = i >> 6;
-      const int b = (int)(tile % nct) * 16 + (lane & 15);
-      alignas(16) TE hi[V], lo[V];
-      // a chunk of V units inside, its rows aligned: whole vectors (one step of 4 x 1024 units x 128 sentences: 8.6 -> 5.3 us)
-      const bool whole = H % V == 0 && b < B && k < H;
-      if (whole) {
-        const int64_t row = (int64_t)b * H + k, idx = (int64_t)l * BH + row;
-        f32x4_t h[V / 4], c[V / 4];
-#pragma unroll
-        for (int v = 0; v < V / 4; ++v) {
-          h[v] = s.h0 ? *reinterpret_cast<const f32x4_t*>(s.h0 + idx + 4 * v) : f32x4_t{0.f, 0.f, 0.f, 0.f};
-          c[v] = s.c0 ? *reinterpret_cast<const f32x4_t*>(s.c0 + idx + 4 * v) : f32x4_t{0.f, 0.f, 0.f, 0.f};
-        }
-#pragma unroll
-        for (int v = 0; v < V / 4; ++v) {
-          ls_st4<true>(p.hf + idx + 4 * v, h[v], 4);
-          ls_st4<true>(cs + row + 4 * v, c[v], 4);
-          ls_st4<true>(hE + row + 4 * v, h[v], 4);
-          ls_st4<true>(hi + 4 * v, h[v], 4);
-          ls_st4<true>(lo + 4 * v, ls_rest<TE>(h[v]), 4);
-        }
-      }
-#pragma unroll
-      for (int e = 0; e < V; ++e) {
-        if (whole) break;
-        const bool in = b < B && k + e < H;
-        const int64_t idx = (int64_t)l * BH + (int64_t)(in ? b : 0) * H + (in ? k + e : 0);
-        const float h = in && s.h0 ? s.h0[idx] : 0.f;
-        st_elem<TE>(hi, e, h);
-        st_elem<TE>(lo, e, h - round_elem<TE>(h));
-        if (in) {
-          const float c = s.c0 ? s.c0[idx] : 0.f;
-          p.hf[idx] = h;
-          cs[idx - (int64_t)l * BH] = c;
-          st_elem<TE>(hE, idx - (int64_t)l * BH, h);
-        }
-      }
-      auto put = [&](char* base, const TE (&v)[V]) {
-        *reinterpret_cast<ls_u32x4_t*>(base + i * 16) = *reinterpret_cast<const ls_u32x4_t*>(v);
-      };
-      put(p.hF_hi + 2 * l * p.h_stride, hi);
-      if constexpr (M::kPair) put(p.hF_lo + 2 * l * p.h_stride, lo);
-      if (k >= H) {   // reduction padding: zero in every slot
-        alignas(16) const TE z[V] = {};
-        put(p.hF_hi + (2 * l + 1) * p.h_stride, z);
-        if constexpr (M::kPair) put(p.hF_lo + (2 * l + 1) * p.h_stride, z);
-        if (l + 1 < L)
-          for (int sl = 0; sl < 2; ++sl) {
-            put(p.oF_hi + (2 * l + sl) * p.h_stride, z);
-            if constexpr (M::kPair) put(p.oF_lo + (2 * l + sl) * p.h_stride, z);
-          }
-      }
-    }
+    ls_prep_state<TE>(p, job, first, stride, false);
   } else if (job == L) {
     if (p.x_apart) return;
     const int nks = (p.I + KST - 1) / KST;
     const int64_t per = (int64_t)nks * nct * 64, n = per * p.T;
-    const TE* x = reinterpret_cast<const TE*>(s.x);
+    const TE* x = reinterpret_cast<const TE*>(p.x);
     for (int64_t i = first; i < n; i += stride) {
       const int t = (int)(i / per);
       const int64_t r = i - t * per, tile = r >> 6;
@@ -862,6 +937,15 @@ template <typename TE> bool ls_reads_weight_rows(int T, int I, int H) {
   return T == 1 && I % LsGeom<TE>::kVec == 0 && H % LsGeom<TE>::kVec == 0;
 }
 
+// One step in blocks of 16 sentences: layer 0 reads x and the initial state where they are, a lane's 32 bytes of the state split
+// into value and remainder after the load, and blocks behind its own make the tiles of the other layers' states.  That costs a
+// layer-step 1 to 4 us, the more bytes a block reads, and saves a launch: a decoder step of 2 x 512 units, 16 sentences 49.8 -> 47.5
+// us, 2 x 128 units, 182 sentences 56.4 -> 53.6; blocks of 32 sentences, 4 x 1024 units, 128 sentences 138.6 / 140.0 (all
+// layers from their rows 154).
+template <typename TE> bool ls_reads_states(int H, int B) {
+  return (int64_t)((H + 15) / 16) * ((B + 31) / 32) < (LsMma<TE>::kPair ? 192 : 512);
+}
+
 // Folded into the wavefronts, the input product of layer 0 lengthens a chain of T dependent launches by what I reduction
 // indices take (0.7 us a launch at I = 512); as one product ahead of them it costs a launch and the round trip of the gates.
 // With more than one layer a launch has reductions of 2 H in it anyway.  The number of sentences has no part in the rule: the
@@ -903,6 +987,16 @@ template <typename TE> hipError_t launch_ls_prep_bwd(const LsPrepBwd& q, hipStre
   hipLaunchKernelGGL(ls_prep_bwd_kernel<TE>, dim3((unsigned)gx, q.n), dim3(256), 0, st, q);
   return hipGetLastError();
 }
+__global__ __launch_bounds__(256) void ls_copy_kernel(LsCopy c) {
+  const int j = blockIdx.y;
+  const uint32_t* src = reinterpret_cast<const uint32_t*>(c.src[j]);
+  uint32_t* dst = reinterpret_cast<uint32_t*>(c.dst[j]);
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < c.words[j]; i += (int64_t)gridDim.x * 256) dst[i] = src[i];
+}
+hipError_t launch_ls_copy(const LsCopy& c, hipStream_t st) {
+  hipLaunchKernelGGL(ls_copy_kernel, dim3(256, c.n), dim3(256), 0, st, c);
+  return hipGetLastError();
+}
 hipError_t launch_ls_bias_reduce(const float* dbacc, const LsBiasOut& o, int L, int nct, int cols, hipStream_t st) {
   hipLaunchKernelGGL(ls_bias_reduce_kernel, dim3((cols + 255) / 256, L), dim3(256), 0, st, dbacc, o, nct, cols);
   return hipGetLastError();
@@ -923,14 +1017,23 @@ int ls_row_steps_in_flight(int K, int H) {
 template <typename TE, int NI, int NJ, int PF, int PF_ROWS = PF>
 static hipError_t ls_fwd_shape(const LsFwd& p, int d, int l_lo, int nl, hipStream_t st) {
   const unsigned grid = ls_grid((int64_t)nl * ((p.H + 4 * NI - 1) / (4 * NI)), (p.B + 16 * NJ - 1) / (16 * NJ));
+  // one step, layer 0: blocks behind its own prepare the states of the other layers
+  const int64_t chunks = (int64_t)ls_ksteps<TE>(p.H) * ls_batch_tiles(p.B) * 64, per = (chunks + 64 * LS_KS - 1) / (64 * LS_KS);
+  const unsigned others = p.direct && l_lo == 0 && p.L > 1 ? (unsigned)(p.L * (per < 64 ? per : 64)) : 0;
 #define ASX_FWD(ROWS, VEC, APART)                                                                                    \
-  hipLaunchKernelGGL((ls_wave_fwd_kernel<TE, NI, NJ, ROWS ? PF_ROWS : PF, ROWS, VEC, APART>), dim3(grid), dim3(64 * LS_KS), 0, st, p, \
+  hipLaunchKernelGGL((ls_wave_fwd_kernel<TE, NI, NJ, ROWS ? PF_ROWS : PF, ROWS, VEC, APART>), dim3(grid + others), dim3(64 * LS_KS), 0, st, p, \
                      d, l_lo, nl)
   if (p.x_apart && p.w_rows) return hipErrorInvalidValue;   // (ls_input_apart: not with one step)
-  if (p.w_rows) ASX_FWD(true, true, false);   // widths are multiples of 4
-  else if (LsMma<TE>::kPair && p.x_apart && l_lo == 0) ASX_FWD(false, true, LsMma<TE>::kPair);
-  else if (LsMma<TE>::kPair || p.H % 4 == 0) ASX_FWD(false, true, false);
-  else ASX_FWD(false, LsMma<TE>::kPair, false);
+  if constexpr (NJ == 1) {
+    if (p.direct && l_lo == 0) {
+      ASX_FWD(2, true, false);   // (widths are whole vectors)
+      return hipGetLastError();
+    }
+  }
+  if (p.w_rows) ASX_FWD(1, true, false);
+  else if (LsMma<TE>::kPair && p.x_apart && l_lo == 0) ASX_FWD(0, true, LsMma<TE>::kPair);
+  else if (LsMma<TE>::kPair || p.H % 4 == 0) ASX_FWD(0, true, false);
+  else ASX_FWD(0, LsMma<TE>::kPair, false);
 #undef ASX_FWD
   return hipGetLastError();
 }
@@ -955,14 +1058,14 @@ template <typename TE> hipError_t launch_ls_wave_fwd(const LsFwd& p, int d, hipS
   // three layers 27.5 us (768 blocks) and 28.0 (192), four 34.0 (1024) and 29.4 (256).
   if constexpr (LsMma<TE>::kPair) {
     if (nl * ((p.H + 31) / 32) * b64 >= 192) return ls_fwd_shape<TE, 8, 4, 3>(p, d, l_lo, nl, st);
-    const int64_t blocks = nl * ((p.H + 15) / 16) * b32;
+    const int64_t blocks = nl * ((p.H + 15) / 16) * b32;   // (ls_reads_states: the same line)
     const bool six = p.w_rows && ls_row_steps_in_flight(l_lo == 0 ? p.I : p.H, p.H) == 6;   // (one step: one layer)
     // (six take the registers of a second block of 16 x 32: not where compute units get one)
     if (blocks >= 192 && six && blocks <= 256) return ls_fwd_shape<TE, 4, 2, 4, 6>(p, d, l_lo, nl, st);
     if (blocks >= 192) return ls_fwd_shape<TE, 4, 2, 4>(p, d, l_lo, nl, st);
     if (six) return ls_fwd_shape<TE, 4, 1, 4, 6>(p, d, l_lo, nl, st);
     return ls_fwd_shape<TE, 4, 1, 4>(p, d, l_lo, nl, st);
-  } else {
+  } else {   // (ls_reads_states: the same line)
     if (nl * ((p.H + 15) / 16) * b32 >= 512) return ls_fwd_shape<TE, 4, 2, 4>(p, d, l_lo, nl, st);
     return ls_fwd_shape<TE, 4, 1, 4>(p, d, l_lo, nl, st);
   }
@@ -989,6 +1092,7 @@ template <typename TE> hipError_t launch_ls_wave_bwd(const LsBwd& p, int d, hipS
 
 #define ASX_LS(TE)                                                                                  \
   template bool ls_reads_weight_rows<TE>(int, int, int);                                            \
+  template bool ls_reads_states<TE>(int, int);                                                      \
   template bool ls_input_apart<TE>(int, int, int, int);                                             \
   template hipError_t launch_ls_prep_fwd<TE>(const LsFwd&, const LsPrepFwd&, hipStream_t);          \
   template hipError_t launch_ls_prep_bwd<TE>(const LsPrepBwd&, hipStream_t);                        \

@@ -324,3 +324,42 @@ def test_infinite_input_weight_saturates_its_gate(dtype, T):
     for key in ("y", "hT", "cT"):
         assert np.isfinite(fo[key]).all()
         pu.assert_close(f[key], fo[key], dtype, key)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("over", ["hT on h0", "y on x", "cT on c0", "hT past c0"])
+def test_one_step_with_outputs_on_top_of_inputs(dtype, over):
+    """A step in place gives the bits it gives into buffers of its own, whatever the order its blocks run in."""
+    import torch
+    import paper_1909_00562_amd as lib
+    B, H, L = 37, 72, 3
+    tdt, code = (torch.bfloat16, lib.AS_BF16) if dtype == "bf16" else (torch.float32, lib.AS_F32)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    new = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    W_ih, W_hh = [[(new(4 * H, H) * 0.1).to(tdt) for _ in range(L)] for _ in range(2)]
+    b = [new(4 * H).to(tdt) for _ in range(L)]
+    x, h0, c0 = new(1, B, H).to(tdt), new(L, B, H), new(L, B, H)
+    lengths = torch.randint(0, 2, (B,), generator=g, device="cuda", dtype=torch.int32)
+    s = lib.LsShape(1, B, H, H, L, code, 0.0, 0)
+    n = lib.lstm_stack_workspace_bytes(s)
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+
+    def run(x, h0, c0, y, hT, cT):
+        lib.lstm_stack_fwd(s, x, lengths, W_ih, W_hh, b, h0, c0, y, hT, cT, ws, n)
+        torch.cuda.synchronize()
+        return [v.clone() for v in (y, hT, cT)]
+
+    want = run(x, h0, c0, torch.empty_like(x), torch.empty_like(h0), torch.empty_like(c0))
+    y, hT, cT = torch.empty_like(x), torch.empty_like(h0), torch.empty_like(c0)
+    if over == "hT on h0":
+        hT = h0
+    elif over == "y on x":
+        y = x
+    elif over == "cT on c0":
+        cT = c0
+    else:
+        both = torch.empty(L + 1, B, H, device="cuda")
+        both[:L] = c0
+        c0, hT = both[:L], both[1:]
+    for got, w in zip(run(x, h0, c0, y, hT, cT), want):
+        assert torch.equal(got, w)
