@@ -104,6 +104,9 @@ struct Layout {
   bool compact;
   bool dch_pair;   // dC and dH1 as one product
   bool out_pair;   // dW_out and dz in one launch where they have the tiles for it
+  bool tile_stats;   // the projection leaves softmax statistics of its tiles
+  int stat_parts;
+  size_t stats, ticket;
   bool hc_gather;    // the product does not write h_c to its compacted rows: a pass of its own does
   bool dz_scatter;   // compacted rows of dz go back to their places in a pass of their own (a split product's combine does it)
   bool dhc_dyn;   // the product with W_out in the backward pass picks its reduction split on the device
@@ -244,6 +247,20 @@ Layout make_layout(const as_shape* s) {
   }
   if (off < end) off = end;
   L.total = off;
+  // The statistics of the softmax from the projection itself, where its tiles are small: the passes over the logits and over
+  // the losses become one over the tiles' statistics.  us, projection + statistics + loss / projection + this: 64 x 64 tiles, 16 x
+  // 16000 x 512 14.5 + a launch / 11.8, 179 x 2054 x 128 12.4 / 11.5; 128 x 128, a block per compute unit, 128 x 32000 x 1024 29.5 /
+  // 26.9; several blocks per unit, 182 x 51130 x 128 30.9 / 30.3, and slower as a call, so not there.  Their place: that of the
+  // backward pass and of the partial sums of h_c, if it has the room.
+  const int edge = L.p_logits.tile == kTile64 ? 64 : 128;
+  L.stat_parts = (V + edge - 1) / edge;
+  L.stats = area;
+  L.tile_stats = bf && N <= 1024 &&
+                 (L.p_logits.tile == kTile64 || (L.p_logits.tile == kTile128 && (int64_t)((N + 127) / 128) * L.stat_parts <= 256)) &&
+                 area + (size_t)N * L.stat_parts * sizeof(TileStat) <= L.total &&
+                 (L.total > kStaticScratchBytes || L.total + kAlign <= kStaticScratchBytes);
+  L.ticket = L.total;
+  if (L.tile_stats) L.total += kAlign;
   return L;
 }
 
@@ -358,7 +375,21 @@ static as_status fwd_from_ctx(const as_shape* s, const Layout& L, char* w, const
     g.M_dev = n_act;
     g.C = w + L.logits; g.ldc = L.ldV; g.c_bf16 = bf;
     g.pad_out = true;
+    if (L.tile_stats) g.row_stats = reinterpret_cast<TileStat*>(w + L.stats);
     AS_TRY(AS_STAGE_GEMM_LOGITS, launch_gemm(g, bf, L.p_logits.tile, st));
+  }
+  if (L.tile_stats) {                                                  // Eq. 5-6
+    XentFinish f{};
+    f.stats = reinterpret_cast<const TileStat*>(w + L.stats);
+    f.logits = w + L.logits; f.ldV = L.ldV;
+    f.parts = L.stat_parts; f.N = N; f.V = V;
+    f.targets = targets; f.pad_id = s->pad_id;
+    f.lse = reinterpret_cast<float*>(w + L.lse); f.tok_loss_ws = reinterpret_cast<float*>(w + L.tokloss); f.tok_loss = tok_loss;
+    f.argmax = argmax; f.tgt_mask = L.compact ? nullptr : tgt_mask;
+    f.rows = rows; f.n_act = n_act;
+    f.loss_sum = loss_sum; f.n_tok = n_tok; f.ticket = reinterpret_cast<int32_t*>(w + L.ticket);
+    AS_TRY(AS_STAGE_XENT_STATS, launch_xent_finish(f, st));
+    return AS_OK;
   }
   AS_TRY(AS_STAGE_XENT_STATS,                                          // Eq. 5-6
          launch_xent_stats(w + L.logits, L.ldV, bf, N, V, targets, s->pad_id, reinterpret_cast<float*>(w + L.lse),
@@ -473,6 +504,7 @@ static as_status fwd_impl(const as_shape* s, const void* h_dec, const void* h_en
   // (T = 1 too: from the same Q, alpha and ctx of a step by itself are the same bits as in a batch of steps, which the row
   // sums of attn_step.hip would not give.  Whole calls are where Q and h_c have the same plan at both row counts, as small
   // models do; else h_c, split by the row count, adds in another order.)
+  int32_t* ticket = L.tile_stats ? reinterpret_cast<int32_t*>(w + L.ticket) : nullptr;
   RowList list{};
   if (L.compact)
     list = {targets, N, V, s->pad_id, reinterpret_cast<int32_t*>(w + L.row_pos), reinterpret_cast<int32_t*>(w + L.rows),
@@ -481,7 +513,7 @@ static as_status fwd_impl(const as_shape* s, const void* h_dec, const void* h_en
     // Eq. 2 (second half), 1 and 3 in one kernel per (sentence, 16 or 32 decoder steps): the scores stay on chip
     AS_TRY(AS_STAGE_ATTN_SCORE,
            launch_attn_fwd_fused(w + L.q, w + L.q_lo, he, src_len, B, T, S, H, reinterpret_cast<float*>(w + L.alpha32),
-                                 w + L.alphaE, w + L.alphaE_lo, L.ldS, w + L.ctx, w + L.ctx_lo, attn_mask, list, st));
+                                 w + L.alphaE, w + L.alphaE_lo, L.ldS, w + L.ctx, w + L.ctx_lo, attn_mask, list, ticket, st));
   } else {
     {  // score[b] = Q_b h_enc_b^T, one product per sentence                  (Eq. 2)
       GemmArgs g;
@@ -495,7 +527,7 @@ static as_status fwd_impl(const as_shape* s, const void* h_dec, const void* h_en
     AS_TRY(AS_STAGE_ATTN_SOFTMAX,                                        // Eq. 1
            launch_attn_softmax_rows(reinterpret_cast<const float*>(w + L.scores), src_len, B, T, S,
                                     reinterpret_cast<float*>(w + L.alpha32), w + L.alphaE,
-                                    w + L.alphaE_lo, L.ldS, bf, attn_mask, list, st));
+                                    w + L.alphaE_lo, L.ldS, bf, attn_mask, list, ticket, st));
     {  // ctx_b = alpha_b h_enc_b                                            (Eq. 3)
       GemmArgs g;
       g.seg(w + L.alphaE, L.ldS, (int64_t)T * L.ldS, he, BH, H, S);
@@ -761,7 +793,8 @@ as_status attn_softmax_step_fwd(const as_shape* shape, const void* h_t, const vo
   char* w = reinterpret_cast<char*>(workspace);
   AS_TRY(AS_STAGE_ATTN_SCORE,                                           // Eq. 1-3 for one step, fused
          launch_attn_step(h_t, reinterpret_cast<const float*>(w + sl.kprime), h_enc, src_len, s1.B, s1.S, s1.H,
-                          reinterpret_cast<float*>(w + L.alpha32), w + L.ctx, w + L.ctx_lo, bf, nullptr, st));
+                          reinterpret_cast<float*>(w + L.alpha32), w + L.ctx, w + L.ctx_lo, bf, nullptr,
+                          L.tile_stats ? reinterpret_cast<int32_t*>(w + L.ticket) : nullptr, st));
   return fwd_from_ctx(&s1, L, w, reinterpret_cast<const char*>(h_t), reinterpret_cast<const char*>(W_c), W_out, b_out,
                       targets, loss_sum, n_tok, tok_loss, argmax, nullptr, st);
 }

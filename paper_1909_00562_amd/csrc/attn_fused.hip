@@ -56,6 +56,7 @@ struct AttnFwdArgs {
   int T, S, B, H;
   int64_t ldS;
   int y0;                                // first block of decoder steps of this launch
+  int32_t* zero;                         // forward: cleared, if not null
   RowList list;                          // forward: made by the blocks x = B, y = 0 of the first launch, if wanted
 };
 
@@ -83,6 +84,7 @@ __global__ __launch_bounds__(64 * AF_NW) void attn_fused_kernel(AttnFwdArgs p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c16 = lane & 15, q4 = lane >> 4;
   if constexpr (!BWD) {
+    if (p.zero && blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) *p.zero = 0;
     if (blockIdx.x == (unsigned)p.B) {
       if (blockIdx.y == 0) row_list_block<64 * AF_NW>(p.list, reinterpret_cast<int*>(smem));
       return;
@@ -376,8 +378,9 @@ template <bool BWD> static hipError_t launch_attn_fused(const AttnFwdArgs& p, hi
 
 hipError_t launch_attn_fwd_fused(const void* q_hi, const void* q_lo, const void* h_enc, const int32_t* src_len, int B,
                                  int T, int S, int H, float* alpha32, void* alphaE, void* alphaE_lo, int64_t ldS,
-                                 void* ctx, void* ctx_lo, uint8_t* attn_mask, const RowList& list, hipStream_t st) {
+                                 void* ctx, void* ctx_lo, uint8_t* attn_mask, const RowList& list, int32_t* zero, hipStream_t st) {
   AttnFwdArgs p{};
+  p.zero = zero;
   p.list = list;
   p.q_hi = reinterpret_cast<const uint16_t*>(q_hi);
   p.q_lo = reinterpret_cast<const uint16_t*>(q_lo);

@@ -7,17 +7,20 @@
 
 namespace asx {
 
-template <typename TE>
+template <typename TE, bool LIST>
 __global__ __launch_bounds__(256) void attn_softmax_rows_kernel(const float* __restrict__ score,
                                                                const int32_t* __restrict__ src_len, int B, int T,
                                                                int S, float* __restrict__ alpha32,
                                                                TE* __restrict__ alphaE,
                                                                TE* __restrict__ alphaE_lo, int64_t ldS,
-                                                               uint8_t* __restrict__ attn_mask, RowList list) {
-  if (list.targets && blockIdx.x == gridDim.x - 1) {   // one block more than the rows need
-    __shared__ int counts[kRowListSmem / sizeof(int)];
-    row_list_block<256>(list, counts);
-    return;
+                                                               uint8_t* __restrict__ attn_mask, RowList list, int32_t* zero) {
+  if (zero && blockIdx.x == 0 && threadIdx.x == 0) *zero = 0;
+  if constexpr (LIST) {
+    if (blockIdx.x == gridDim.x - 1) {   // one block more than the rows need
+      __shared__ int counts[kRowListSmem / sizeof(int)];
+      row_list_block<256>(list, counts);
+      return;
+    }
   }
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);   // row = b*T + t
@@ -68,16 +71,18 @@ __global__ __launch_bounds__(256) void attn_softmax_rows_bwd_kernel(const float*
 
 hipError_t launch_attn_softmax_rows(const float* score, const int32_t* src_len, int B, int T, int S,
                                     float* alpha32, void* alphaE, void* alphaE_lo, int64_t ldS, bool e_bf16,
-                                    uint8_t* attn_mask, const RowList& list, hipStream_t st) {
+                                    uint8_t* attn_mask, const RowList& list, int32_t* zero, hipStream_t st) {
   const int rows = B * T;
   dim3 grid((rows + 3) / 4 + (list.targets ? 1 : 0));
-  if (e_bf16)
-    hipLaunchKernelGGL(attn_softmax_rows_kernel<uint16_t>, grid, dim3(256), 0, st, score, src_len, B, T, S,
-                       alpha32, reinterpret_cast<uint16_t*>(alphaE), reinterpret_cast<uint16_t*>(alphaE_lo), ldS,
-                       attn_mask, list);
-  else
-    hipLaunchKernelGGL(attn_softmax_rows_kernel<float>, grid, dim3(256), 0, st, score, src_len, B, T, S, alpha32,
-                       reinterpret_cast<float*>(alphaE), reinterpret_cast<float*>(alphaE_lo), ldS, attn_mask, list);
+  auto launch = [&](auto kernel, auto* hi, auto* lo) {
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, score, src_len, B, T, S, alpha32, hi, lo, ldS, attn_mask, list, zero);
+  };
+  uint16_t *hi16 = reinterpret_cast<uint16_t*>(alphaE), *lo16 = reinterpret_cast<uint16_t*>(alphaE_lo);
+  float *hi32 = reinterpret_cast<float*>(alphaE), *lo32 = reinterpret_cast<float*>(alphaE_lo);
+  if (e_bf16 && list.targets) launch(attn_softmax_rows_kernel<uint16_t, true>, hi16, lo16);
+  else if (e_bf16) launch(attn_softmax_rows_kernel<uint16_t, false>, hi16, lo16);
+  else if (list.targets) launch(attn_softmax_rows_kernel<float, true>, hi32, lo32);
+  else launch(attn_softmax_rows_kernel<float, false>, hi32, lo32);
   return hipGetLastError();
 }
 

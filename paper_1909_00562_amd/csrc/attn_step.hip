@@ -42,6 +42,7 @@ struct AttnStep {
   float* alpha;                   // [B,S]: written; BWD: read
   void *ctx, *ctx_lo;             // [B,H] storage type: ctx and optional remainder; BWD: dQ
   uint8_t* attn_mask;             // optional
+  int32_t* zero;                  // cleared, if not null
   const void *q, *q_lo;           // BWD: Q [B,H] as value and remainder
   float* d_h_enc;                 // BWD: [S,B,H]
 };
@@ -56,6 +57,7 @@ __global__ __launch_bounds__(kStepThreads) void attn_step_kernel(AttnStep p) {
   float* part = BWD ? al + S : al;
   __shared__ float red[2 * kStepWaves];
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (!BWD && p.zero && b == 0 && tid == 0) *p.zero = 0;
   int L = p.src_len[b];
   L = L < 0 ? 0 : (L > S ? S : L);
   const TE* query = reinterpret_cast<const TE*>(p.query) + (int64_t)b * H;
@@ -245,8 +247,9 @@ static hipError_t launch_step(AttnStep p, hipStream_t st) {
 
 hipError_t launch_attn_step(const void* h_t, const float* kprime, const void* h_enc, const int32_t* src_len, int B,
                             int S, int H, float* alpha, void* ctx, void* ctx_lo, bool e_bf16, uint8_t* attn_mask,
-                            hipStream_t st) {
+                            int32_t* zero, hipStream_t st) {
   AttnStep p{};
+  p.zero = zero;
   p.query = h_t;
   p.key = kprime;
   p.h_enc = h_enc;

@@ -86,7 +86,16 @@ struct GemmArgs {
   // row n of C_dact there alone, not at n.  Not by the 256 x 256 kernels; batch == 1.
   const int32_t* copy_pos = nullptr;
   void* C_copy = nullptr;
+  // Softmax statistics of each row's part of a tile, over the values as stored (64x64 and 128x128 kernels, both operands
+  // contiguous, bf16 C, bias alone): row_stats[row * tile columns + tile column]
+  struct TileStat* row_stats = nullptr;
 };
+// maximum, sum of exp relative to it, lowest column that attains it (INT_MAX: none, all values are -inf or NaN)
+struct alignas(16) TileStat {
+  float m, s;
+  int idx, unused;
+};
+
 
 // Blocks of a persistent launch (one per compute unit, a multiple of the 8 XCDs).
 inline int pp_grid_blocks(int work_total) { return work_total < 256 ? (work_total + 7) / 8 * 8 : 256; }

@@ -1035,6 +1035,10 @@ static hipError_t gemm_describe(const GemmArgs& g, GemmTile tile, GemmDev& d) {
   if (g.copy_pos && (!g.C_copy || g.batch != 1 || (big_tile && g.splits == 1) || g.M_dev || g.accumulate)) return hipErrorInvalidValue;
   d.copy_pos = g.splits > 1 ? nullptr : g.copy_pos;
   d.C_copy = g.C_copy;
+  if (g.row_stats && ((tile != kTile64 && tile != kTile128) || !g.a_kc || !g.b_kc || !g.c_bf16 || g.splits != 1 || g.batch != 1 || g.copy_pos ||
+                      g.act_tanh || g.drop_thr || g.gate || g.accumulate || g.C_lo || g.C_dact))
+    return hipErrorInvalidValue;
+  d.row_stats = g.row_stats;
   bool apart_al16 = !g.C_second || al16(g.C_second);
   for (int b = 0; g.C_of && b < g.batch; ++b) apart_al16 = apart_al16 && al16(g.C_of[b]);
   d.bias = reinterpret_cast<const uint16_t*>(g.bias);
@@ -1066,7 +1070,7 @@ static hipError_t gemm_describe(const GemmArgs& g, GemmTile tile, GemmDev& d) {
              (!g.C_dact || al16(g.C_dact)) && al16(g.C_copy) && (!g.gate || (al16(g.gate) && (g.ldg & 3) == 0)) &&
              (d.n_out & 3) == 0 &&                                        // a 4-column group is all in or all out
              g.ldc < (1 << 21) && g.ldg < (1 << 21) && g.N < (1 << 21);   // 32-bit byte offsets inside a 128-row window
-  if (g.C_second && !d.vec_ok) return hipErrorInvalidValue;
+  if ((g.C_second || g.row_stats) && !d.vec_ok) return hipErrorInvalidValue;
   const int bm = tile == kTile256 ? 256 : tile == kTile128 ? 128 : 64;
   d.tiles_m = (g.M + bm - 1) / bm;
   d.tiles_n = (g.N + bm - 1) / bm;

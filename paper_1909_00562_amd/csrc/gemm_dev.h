@@ -21,6 +21,7 @@ struct GemmDev {
   int64_t ldc, sC;
   const int32_t* copy_pos; // row n of C also goes to row copy_pos[n] of C_copy, and of C_dact there alone (or null)
   void* C_copy;
+  TileStat* row_stats;     // softmax statistics of a row's part of a tile (or null)
   float* C_second;         // batch of two: where the product of segment 0 alone goes (or null)
   const uint16_t* bias;
   const float* gate;

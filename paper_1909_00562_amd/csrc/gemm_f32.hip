@@ -12,7 +12,7 @@ namespace asx {
 struct GemmDevF {
   const float* A[kMaxSeg];
   const float* B[kMaxSeg];
-  int64_t lda[kMaxSeg], ldb[kMaxSeg];
+  int64_t lda, ldb;   // the same for all segments
   int64_t sA[kMaxSeg], sB[kMaxSeg];
   int K[kMaxSeg];
   int M, N;
@@ -121,187 +121,19 @@ struct F32Loader {
   }
 };
 
-// Block `pid` of product z (batch and split) of a launch; smem: f32_smem_floats<BM, BN>.
 template <int BM, int BN> constexpr int f32_smem_floats = 2 * (BM + BN) * FLD;
 template <int BM, int BN, int PF, bool AKC, bool BKC, bool AVEC, bool BVEC>
-__device__ __forceinline__ void gemm_f32_block(const GemmDevF& p, int pid, int z, float* smem) {
-  static_assert(PF % 2 == 0, "a step's LDS stage is its slot's parity");
-  constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 16, TN = WN / 16;
-  constexpr int STAGE = (BM + BN) * FLD;   // floats
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave >> 1) * WM, wn = (wave & 1) * WN;
-
-  // consecutive blocks go round-robin to the 8 XCDs: each XCD gets a contiguous run of tiles, walked in groups of 8
-  // tile rows, so that co-resident blocks share operand panels in its L2
-  const int Mv = dev_bound_f(p.M_dev, p.M);
-  const int K0 = dev_bound_f(p.K_dev, p.K[0]);
-  const int tiles_m = (Mv + BM - 1) / BM, nt = tiles_m * p.tiles_n;   // the grid was sized for p.M
-  if (pid >= nt) return;   // the whole block, before any barrier
-  {
-    const int xcd = pid & 7, idx = pid >> 3, per = nt >> 3, rem = nt & 7;
-    pid = xcd * per + (xcd < rem ? xcd : rem) + idx;
-  }
-  const int gid = pid / (8 * p.tiles_n), first_m = gid * 8;
-  const int gm = tiles_m - first_m < 8 ? tiles_m - first_m : 8;
-  const int in_g = pid - gid * 8 * p.tiles_n;
-  const int m0 = (first_m + in_g % gm) * BM, n0 = (in_g / gm) * BN;
-  const int kper = p.K_dev ? (((K0 + FK - 1) / FK + p.splits - 1) / p.splits) * FK : p.kper;
-  const int batch = z / p.splits, split = z - batch * p.splits;
-
-  f64x4_t acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.0;
-
-  // cursor over the reduction tiles of all segments (a split covers part of segment 0, the only one then)
-  int seg = 0, k_left = K0;
-  const float* cA = p.A[0] + (int64_t)batch * p.sA[0] + (AKC ? (int64_t)m0 * p.lda[0] : m0);
-  const float* cB = p.B[0] + (int64_t)batch * p.sB[0] + (BKC ? (int64_t)n0 * p.ldb[0] : n0);
-  if (p.splits > 1) {
-    const int kbeg = split * kper;
-    k_left = K0 - kbeg < kper ? K0 - kbeg : kper;
-    cA += AKC ? kbeg : (int64_t)kbeg * p.lda[0];
-    cB += BKC ? kbeg : (int64_t)kbeg * p.ldb[0];
-  }
-  int nk = k_left > 0 ? (k_left + FK - 1) / FK : 0, last_seg = 0;   // tiles of this block, last segment in use
-  if (p.splits <= 1) {
-#pragma unroll
-    for (int s = 1; s < kMaxSeg; ++s)
-      if (p.K[s] > 0) {
-        nk += (p.K[s] + FK - 1) / FK;
-        last_seg = s;
-      }
-  }
-  // tiles on their way: slot t % PF of the registers holds tile t + 1 at the top of step t
-  using LA = F32Loader<BM, AKC, AVEC>;
-  using LB = F32Loader<BN, BKC, BVEC>;
-  LA la;
-  LB lb;
-  f32x4_t ra[PF][LA::NV], rb[PF][LB::NV];
-  int kin[PF];
-  la.init(cA, p.lda[0], Mv - m0, tid);
-  lb.init(cB, p.ldb[0], p.N - n0, tid);
-  const float *safeA = p.A[0], *safeB = p.B[0];
-  // The tile under the cursor into registers.  Past the last tile the loads are issued all the same (of `safe`): the
-  // number in flight is then the same on every path, and the wait before a store to LDS covers just the tile it stores.
-  auto fetch = [&](int slot) {
-    if (k_left <= 0 && seg < last_seg) {   // on to the next segment
-      do { ++seg; } while (p.K[seg] <= 0);
-      k_left = p.K[seg];
-      la.init(p.A[seg] + (int64_t)batch * p.sA[seg] + (AKC ? (int64_t)m0 * p.lda[seg] : m0), p.lda[seg], Mv - m0, tid);
-      lb.init(p.B[seg] + (int64_t)batch * p.sB[seg] + (BKC ? (int64_t)n0 * p.ldb[seg] : n0), p.ldb[seg], p.N - n0, tid);
-    }
-    kin[slot] = k_left;
-    la.load(ra[slot], safeA, k_left, AKC ? FK : (int64_t)FK * p.lda[seg], tid);
-    lb.load(rb[slot], safeB, k_left, BKC ? FK : (int64_t)FK * p.ldb[seg], tid);
-    k_left -= FK;
-  };
-  auto put = [&](int slot, int st) {   // registers -> LDS stage st
-    LA::store(ra[slot], smem + st * STAGE, kin[slot], tid);
-    LB::store(rb[slot], smem + st * STAGE + BM * FLD, kin[slot], tid);
-  };
-  auto compute = [&](int st) {
-    const float* as = smem + st * STAGE;
-    const float* bs = as + BM * FLD;
-#pragma unroll
-    for (int ks = 0; ks < FK / 16; ++ks) {
-      f32x4_t af[TM], bf[TN];
-      const int kof = ks * 16 + (lane >> 4) * 4;
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-        af[i] = *reinterpret_cast<const f32x4_t*>(as + (wm + i * 16 + (lane & 15)) * FLD + kof);
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        bf[j] = *reinterpret_cast<const f32x4_t*>(bs + (wn + j * 16 + (lane & 15)) * FLD + kof);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        double b[TN];
-#pragma unroll
-        for (int j = 0; j < TN; ++j) b[j] = (double)bf[j][e];
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const double a = (double)af[i][e];
-#pragma unroll
-          for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b[j], acc[i][j], 0, 0, 0);
-        }
-      }
-    }
-  };
-
-  fetch(PF - 1);
-#pragma unroll
-  for (int u = 0; u + 1 < PF; ++u) fetch(u);
-  put(PF - 1, 0);
-  fetch(PF - 1);
-  __syncthreads();
-  int t = 0;
-  for (; t + PF <= nk; t += PF) {   // no exit inside: it would meet the loop's other paths with other counts in flight
-#pragma unroll
-    for (int u = 0; u < PF; ++u) {
-      put(u, (u + 1) & 1);
-      fetch(u);
-      compute(u & 1);
-      __syncthreads();        // tile t + u has been read everywhere, the next one is in place
-    }
-  }
-#pragma unroll
-  for (int u = 0; u + 1 < PF; ++u) {
-    if (t + u < nk) {
-      put(u, (u + 1) & 1);
-      compute(u & 1);
-      __syncthreads();
-    }
-  }
-
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = m0 + wm + i * 16 + 4 * r + (lane >> 4);
-      if (row >= Mv) continue;
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int col = n0 + wn + j * 16 + (lane & 15);
-        if (col >= p.N) continue;
-        double v = acc[i][j][r];
-        if (p.splits > 1) {
-          p.partial[((int64_t)z * p.M + row) * p.N + col] = (float)v;
-          continue;
-        }
-        if (p.bias) v += (double)p.bias[col];
-        if (p.act_tanh) v = tanh(v);
-        double dact = 1.0 - v * v;
-        if (p.drop_thr) {
-          const double s = (double)dropout_mult((uint64_t)row * p.N + col, p.drop_seed, p.drop_thr, p.drop_scale);
-          v *= s;
-          dact *= s;
-        }
-        if (p.gate) v *= (double)p.gate[(int64_t)row * p.ldg + col];
-        const int64_t ci = (int64_t)batch * p.sC + (int64_t)row * p.ldc + col;
-        if (p.accumulate) v += (double)p.C[ci];
-        const float vf = (float)v;
-        p.C[ci] = vf;
-        if (p.C_lo) p.C_lo[ci] = (float)(v - (double)vf);
-        if (p.copy_pos) {
-          const int copy = p.copy_pos[row];
-          if (copy < 0) continue;
-          const int64_t cc = (int64_t)copy * p.ldc + col;
-          p.C_copy[cc] = vf;
-          if (p.C_dact) p.C_dact[cc] = (float)dact;
-        } else if (p.C_dact) {
-          p.C_dact[ci] = (float)dact;
-        }
-      }
-    }
+__device__ __forceinline__ void gemm_f32_block(GemmDevF p, int pid, int z, float* smem) {
+  constexpr bool COPY = false;
+#include "gemm_f32_block.inc"
 }
-
-template <int BM, int BN, int PF, bool AKC, bool BKC, bool AVEC, bool BVEC>
+// (COPY: an instance of its own; as a branch of all of them it cost every product half a microsecond)
+template <int BM, int BN, int PF, bool AKC, bool BKC, bool AVEC, bool BVEC, bool COPY>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmDevF p) {
   __shared__ __align__(16) float smem[f32_smem_floats<BM, BN>];
-  gemm_f32_block<BM, BN, PF, AKC, BKC, AVEC, BVEC>(p, blockIdx.x, blockIdx.z, smem);
+  int pid = blockIdx.x;
+  const int z = blockIdx.z;
+#include "gemm_f32_block.inc"
 }
 
 // Block tile edge (64 or 32) for nz products of M x N.  With four blocks and more on every compute unit the 64 x 64 tile
@@ -318,11 +150,18 @@ template <int BM, int BN, int PF, bool AKC, bool BKC>
 static hipError_t launch_f32_tile(GemmDevF& d, int batch, bool avec, bool bvec, hipStream_t st) {
   d.tiles_n = (d.N + BN - 1) / BN;
   dim3 grid((d.M + BM - 1) / BM * d.tiles_n, 1, batch * d.splits);
-#define ASX_F32(AV, BV) hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, PF, AKC, BKC, AV, BV>), grid, dim3(256), 0, st, d)
+#define ASX_F32_C(AV, BV, CP) hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, PF, AKC, BKC, AV, BV, CP>), grid, dim3(256), 0, st, d)
+#define ASX_F32(AV, BV)                                   \
+  do {                                                    \
+    if (AKC && BKC && d.copy_pos) ASX_F32_C(AV, BV, (AKC && BKC)); \
+    else ASX_F32_C(AV, BV, false);                        \
+  } while (0)
+  if (d.copy_pos && !(AKC && BKC)) return hipErrorInvalidValue;
   if (avec && bvec) ASX_F32(true, true);
   else if (avec) ASX_F32(true, false);
   else if (bvec) ASX_F32(false, true);
   else ASX_F32(false, false);
+#undef ASX_F32_C
 #undef ASX_F32
   return hipGetLastError();
 }
@@ -343,12 +182,11 @@ static hipError_t f32_describe(const GemmArgs& g, GemmDevF& d, bool& avec, bool&
   for (int s = 0; s < kMaxSeg; ++s) {
     d.A[s] = reinterpret_cast<const float*>(g.A[s]);
     d.B[s] = reinterpret_cast<const float*>(g.B[s]);
-    d.lda[s] = g.lda[s];
-    d.ldb[s] = g.ldb[s];
     d.sA[s] = g.sA[s];
     d.sB[s] = g.sB[s];
     d.K[s] = g.K[s];
     if (g.K[s] > 0) {
+      if (g.lda[s] != g.lda[0] || g.ldb[s] != g.ldb[0]) return hipErrorInvalidValue;
       // 16-byte loads: groups of four start aligned and do not straddle the operand's edge (a reduction length or row
       // count read on the device counts rows, which are the other index of the operands that use it)
       auto vec_ok = [&](const void* X, int64_t ld, int64_t stride, bool kc, int rows) {
@@ -358,6 +196,8 @@ static hipError_t f32_describe(const GemmArgs& g, GemmDevF& d, bool& avec, bool&
       bvec = bvec && vec_ok(g.B[s], g.ldb[s], g.sB[s], g.b_kc, g.N) && !(g.b_kc && g.K_dev);
     }
   }
+  d.lda = g.lda[0];
+  d.ldb = g.ldb[0];
   d.M = g.M;
   d.N = g.N;
   d.C = reinterpret_cast<float*>(g.C);
@@ -477,7 +317,7 @@ static hipError_t launch_gemm_f32_together(const GemmArgs* g, int n, const DbRed
     bool avec, bvec;
     const hipError_t e = f32_describe(g[i], d[i], avec, bvec);
     if (e != hipSuccess) return e;
-    if (!gemm_f32_small(g[i].M, g[i].N, g[i].batch * g[i].splits)) return hipErrorNotSupported;
+    if (g[i].copy_pos || !gemm_f32_small(g[i].M, g[i].N, g[i].batch * g[i].splits)) return hipErrorNotSupported;
     vec = vec && bvec && (avec || i == 2);   // (source positions, the rows of the last A, are rarely a multiple of four)
     vec_last = vec_last && avec && bvec;
   }

@@ -78,7 +78,7 @@ template <bool KC, int COLS> __device__ __forceinline__ bf16x8_t gs_frag(const u
 }
 
 // What sets an instance of a tile kernel apart (with the choices made in the kernel its other products were 1 to 8 % slower)
-enum TileExtra { kNoExtra, kSecond, kCopy };   // C_second; copy_pos
+enum TileExtra { kNoExtra, kSecond, kCopy, kStats };   // C_second; copy_pos; row_stats
 
 // Epilogue of four consecutive columns of a row, in whole vectors
 template <bool COPY>
@@ -168,6 +168,53 @@ __device__ __forceinline__ void gs_finish_ragged(const GemmDev& p, int out_bf16,
 
 // Block `id` of a launch's tiles of all batches and splits; dynamic LDS: NST * 2 * 32 TW * ROWB bytes.  (p by value: by reference the
 // instances take five registers more and 182 x 51130 x 128 18.7 us for 17.2.)
+// Softmax statistics of a staged row's BM columns by four lanes, which take every fourth vector: few steps across lanes, which
+// is what the time goes to (16 and 32 lanes with a vector each, 128 x 32000 x 1024: 17.9 -> 22.4 us).
+template <int CTRL> __device__ __forceinline__ float gs_quad(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
+}
+constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E;
+template <int BM> __device__ __forceinline__ TileStat gs_stats(const float* row, int part, int col0, int ncols) {
+  constexpr float L2E = 1.4426950408889634f;
+  constexpr int NV = BM / 16;
+  f32x4_t x[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) x[i] = *reinterpret_cast<const f32x4_t*>(row + (part + 4 * i) * 4);
+  float m = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      x[i][e] = (part + 4 * i) * 4 + e < ncols ? bf16_bits_to_f32(f32_to_bf16_bits(x[i][e])) : -INFINITY;
+    m = fmaxf(fmaxf(m, x[i][0]), x[i][1]);
+    m = fmaxf(fmaxf(m, x[i][2]), x[i][3]);
+  }
+  m = fmaxf(m, gs_quad<kQuadXor1>(m));
+  m = fmaxf(m, gs_quad<kQuadXor2>(m));
+  const bool any = m > -INFINITY;   // (a part of a row without a finite value adds nothing, unless NaN makes it so)
+  const float mb = any ? -m * L2E : 0.f;
+  float s0 = 0.f, s1 = 0.f;
+  int idx = 0x7fffffff;
+#pragma unroll
+  for (int i = NV - 1; i >= 0; --i)
+#pragma unroll
+    for (int e = 3; e >= 0; --e) {
+      const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(x[i][e], L2E, mb));
+      if (e & 1) s1 += p;
+      else s0 += p;
+      idx = x[i][e] == m ? (part + 4 * i) * 4 + e : idx;
+    }
+  float s = s0 + s1;
+  s += gs_quad<kQuadXor1>(s);
+  s += gs_quad<kQuadXor2>(s);
+  idx = any && idx != 0x7fffffff ? col0 + idx : 0x7fffffff;
+  int o = __builtin_amdgcn_update_dpp(0, idx, kQuadXor1, 0xf, 0xf, false);
+  idx = o < idx ? o : idx;
+  o = __builtin_amdgcn_update_dpp(0, idx, kQuadXor2, 0xf, 0xf, false);
+  idx = o < idx ? o : idx;
+  return TileStat{m, s, idx, 0};
+}
+
 template <int TW, bool AKC, bool BKC, int NST, bool LACED, TileExtra EXTRA>
 __device__ __forceinline__ void gemm_bf16_tile_block(GemmDev p, int out_bf16, int id) {
   extern __shared__ __align__(1024) unsigned char smem[];
@@ -359,7 +406,12 @@ __device__ __forceinline__ void gemm_bf16_tile_block(GemmDev p, int out_bf16, in
   if (second) out_bf16 = 0;
   const bool plain = p.vec_ok && (!fuse || second || (EXTRA != kCopy && !p.act_tanh && !p.drop_thr && !p.gate && !p.C_lo && !p.C_dact));
   f32x4_t bias4 = {0.f, 0.f, 0.f, 0.f};
-  if (fuse && p.bias)
+  float bias1[TW];   // kStats: added on the way into LDS
+  if constexpr (EXTRA == kStats) {
+#pragma unroll
+    for (int j = 0; j < TW; ++j) bias1[j] = p.bias && n0 + wn + 16 * j + c < p.N ? bf16_bits_to_f32(p.bias[n0 + wn + 16 * j + c]) : 0.f;
+  }
+  if (EXTRA != kStats && fuse && p.bias)
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       if (col + e < p.N) bias4[e] = bf16_bits_to_f32(p.bias[col + e]);
@@ -372,10 +424,15 @@ __device__ __forceinline__ void gemm_bf16_tile_block(GemmDev p, int out_bf16, in
 #pragma unroll
         for (int j = 0; j < TW; ++j)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) stage[(wm % 64 + 16 * i + 4 * q + r) * LD + wn + 16 * j + c] = acc[i][j][r];
+          for (int r = 0; r < 4; ++r)
+            stage[(wm % 64 + 16 * i + 4 * q + r) * LD + wn + 16 * j + c] = EXTRA == kStats ? acc[i][j][r] + bias1[j] : acc[i][j][r];
     }
     __syncthreads();
     const int left = Mv - m0 - half * 64 < 64 ? Mv - m0 - half * 64 : 64;   // rows inside (may be none)
+    if constexpr (EXTRA == kStats) {
+      const TileStat t = gs_stats<BM>(stage + (tid >> 2) * LD, tid & 3, n0, p.N - n0);
+      if ((tid & 3) == 0 && (tid >> 2) < left) p.row_stats[(int64_t)(m0 + half * 64 + (tid >> 2)) * p.tiles_n + n0 / BM] = t;
+    }
     if (plain) {   // bias and accumulation only: nothing tested per row but the bounds
 #pragma unroll
       for (int r0 = 0; r0 < 64; r0 += RU * RP) {
@@ -456,6 +513,10 @@ static hipError_t launch_tile_form(const GemmDev& d, GemmTile tile, int out_bf16
     if (d.C_second) return launch_tile_shape<2, AKC, BKC, 4, true, kSecond>(d, out_bf16, st);
   }
   if constexpr (AKC && BKC) {
+    if (d.row_stats) {
+      if (tile == kTile64) return launch_tile_shape<2, AKC, BKC, 4, true, kStats>(d, out_bf16, st);
+      return blocks <= 256 ? launch_tile_shape<4, AKC, BKC, 4, true, kStats>(d, out_bf16, st) : hipErrorInvalidValue;
+    }
     if (d.copy_pos) {
       if (tile == kTile64) return launch_tile_shape<2, AKC, BKC, 4, true, kCopy>(d, out_bf16, st);
       return blocks <= 256 ? launch_tile_shape<4, AKC, BKC, 4, true, kCopy>(d, out_bf16, st)

@@ -12,6 +12,7 @@ namespace asx {
 // Position n -> row_pos[n] (its compacted row, -1 at padding), the list rows[0 .. *n_act) of positions in
 // increasing order, *n_act; optional per-position outputs: tgt_mask everywhere, tok_loss = 0 and
 // argmax = pad_id at padding (the statistics kernel fills the other positions).  Made by an extra block of the attention.
+// (zero, in the launchers of the attention: a word they clear for a later kernel of the pass, or null)
 struct RowList {
   const int32_t* targets;   // null: no list wanted
   int N, V, pad_id;
@@ -27,7 +28,7 @@ struct RowList {
 // alphaE_lo = alpha - alphaE in the storage type, and, if non-null, attn_mask [B,S].
 hipError_t launch_attn_softmax_rows(const float* score, const int32_t* src_len, int B, int T, int S,
                                     float* alpha32, void* alphaE, void* alphaE_lo, int64_t ldS, bool e_bf16,
-                                    uint8_t* attn_mask, const RowList& list, hipStream_t st);
+                                    uint8_t* attn_mask, const RowList& list, int32_t* zero, hipStream_t st);
 // Softmax Jacobian: dscore = alpha * (dalpha - sum_s alpha*dalpha), storage type, [B,T,ldS] zero
 // padded; dscoreE_lo (optional) receives the rounding remainder.
 hipError_t launch_attn_softmax_rows_bwd(const float* alpha32, const float* dalpha, int B, int T, int S,
@@ -40,7 +41,7 @@ hipError_t launch_attn_softmax_rows_bwd(const float* alpha32, const float* dalph
 bool attn_fwd_fused_supported(int S, int H);
 hipError_t launch_attn_fwd_fused(const void* q_hi, const void* q_lo, const void* h_enc, const int32_t* src_len, int B,
                                  int T, int S, int H, float* alpha32, void* alphaE, void* alphaE_lo, int64_t ldS,
-                                 void* ctx, void* ctx_lo, uint8_t* attn_mask, const RowList& list, hipStream_t st);
+                                 void* ctx, void* ctx_lo, uint8_t* attn_mask, const RowList& list, int32_t* zero, hipStream_t st);
 // First half of the attention backward pass with the same kernel: dC_hi / dC_lo [T,B,H], alpha32 [B,T,S] (read) ->
 // dscoreE / dscoreE_lo [B,T,ldS] (softmax Jacobian, zero padded) and dQ [T,B,H] = dscore . h_enc (value only).
 hipError_t launch_attn_bwd_fused(const void* dC_hi, const void* dC_lo, const void* h_enc, const int32_t* src_len,
@@ -59,6 +60,23 @@ hipError_t launch_xent_stats(const void* logits, int64_t ldV, bool e_bf16, int N
                              const int32_t* targets, int pad_id, float* lse, float* tok_loss_ws,
                              float* tok_loss, int32_t* argmax, uint8_t* tgt_mask, const int32_t* rows,
                              const int32_t* n_act, hipStream_t st);
+// The same and the loss from the statistics of the projection's tiles (GemmArgs::row_stats, `parts` per row).  ticket: zero
+// when the kernel starts (any more blocks than one).
+struct XentFinish {
+  const struct TileStat* stats;
+  const void* logits;
+  int64_t ldV;
+  int parts, N, V;
+  const int32_t* targets;
+  int pad_id;
+  float *lse, *tok_loss_ws, *tok_loss;
+  int32_t* argmax;
+  uint8_t* tgt_mask;
+  const int32_t *rows, *n_act;
+  float* loss_sum;
+  int32_t *n_tok, *ticket;
+};
+hipError_t launch_xent_finish(const XentFinish& p, hipStream_t st);
 // loss_sum = sum(tok_loss_ws) in double, n_tok = number of non-pad targets (= *n_act when given); fixed order.
 hipError_t launch_loss_reduce(const float* tok_loss_ws, const int32_t* targets, int N, int V, int pad_id,
                               float* loss_sum, int32_t* n_tok, const int32_t* n_act, hipStream_t st);
@@ -85,7 +103,7 @@ hipError_t launch_db_reduce(const DbReduce& d, hipStream_t st);
 // h_enc [S,B,H]; writes alpha [B,S] float, ctx [B,H] (+ optional rounding remainder ctx_lo), optional attn_mask.
 hipError_t launch_attn_step(const void* h_t, const float* kprime, const void* h_enc, const int32_t* src_len, int B,
                             int S, int H, float* alpha, void* ctx, void* ctx_lo, bool e_bf16, uint8_t* attn_mask,
-                            hipStream_t st);
+                            int32_t* zero, hipStream_t st);
 // Backward pass of attention for a training step with T = 1, bf16 storage: alpha as saved by the forward pass, dC [B,H] and
 // Q = h_dec W_a [B,H] as value and remainder -> dQ [B,H] and d_h_enc [S,B,H] (all of it).
 bool attn_one_step_bwd_supported(int T, int S, int H);

@@ -7,6 +7,7 @@
 
 #include "common.h"
 #include "db_reduce_dev.h"
+#include "gemm.h"
 #include "kernels.h"
 
 namespace asx {
@@ -190,22 +191,20 @@ __global__ __launch_bounds__(256) void xent_stats_kernel(const TE* __restrict__ 
   }
 }
 
-__global__ __launch_bounds__(1024) void loss_reduce_kernel(const float* __restrict__ tok_loss_ws,
-                                                          const int32_t* __restrict__ targets, int N, int V,
-                                                          int pad_id, float* loss_sum, int32_t* n_tok,
-                                                          const int32_t* __restrict__ n_act) {
-  __shared__ double sd[1024];
-  __shared__ int sc[1024];
+// loss_sum and n_tok by one block of 1024 threads; order fixed
+template <typename Load>
+__device__ __forceinline__ void loss_reduce_block(Load loss, const int32_t* targets, int N, int V, int pad_id, float* loss_sum,
+                                                  int32_t* n_tok, const int32_t* n_act, double* sd, int* sc) {
   const int tid = threadIdx.x;
   double acc = 0.0;
   int cnt = 0;
   if (n_act) {   // compacted rows: the first *n_act entries are the non-pad positions
     const int na = *n_act;
-    for (int i = tid; i < na; i += 1024) acc += (double)tok_loss_ws[i];
+    for (int i = tid; i < na; i += 1024) acc += (double)loss(i);
     cnt = tid == 0 ? na : 0;
   } else {
     for (int i = tid; i < N; i += 1024) {
-      acc += (double)tok_loss_ws[i];
+      acc += (double)loss(i);
       const int y = targets[i];
       cnt += ((y != pad_id) && (y >= 0) && (y < V)) ? 1 : 0;
     }
@@ -226,6 +225,69 @@ __global__ __launch_bounds__(1024) void loss_reduce_kernel(const float* __restri
     cnt += __shfl_down(cnt, o, 64);
   }
   if (tid == 0) { *loss_sum = (float)acc; *n_tok = cnt; }
+}
+__global__ __launch_bounds__(1024) void loss_reduce_kernel(const float* __restrict__ tok_loss_ws,
+                                                          const int32_t* __restrict__ targets, int N, int V,
+                                                          int pad_id, float* loss_sum, int32_t* n_tok,
+                                                          const int32_t* __restrict__ n_act) {
+  __shared__ double sd[1024];
+  __shared__ int sc[1024];
+  loss_reduce_block([&](int i) { return tok_loss_ws[i]; }, targets, N, V, pad_id, loss_sum, n_tok, n_act, sd, sc);
+}
+
+// Few rows: the statistics of the projection's tiles instead of the logits themselves, a wavefront per row, and the loss by the
+// block that is through last.
+constexpr int kFinishRows = 16;
+__global__ __launch_bounds__(1024) void xent_finish_kernel(XentFinish p) {
+  __shared__ double sd[1024];
+  __shared__ int sc[1024];
+  __shared__ int last;
+  const int tid = threadIdx.x, lane = tid & 63, n = blockIdx.x * kFinishRows + (tid >> 6);
+  const int rows = p.rows ? (*p.n_act < p.N ? *p.n_act : p.N) : p.N;
+  if (n < rows) {
+    const int pos = p.rows ? p.rows[n] : n;
+    const int y = p.targets[pos];
+    const bool nonpad = (y != p.pad_id) && (y >= 0) && (y < p.V);
+    const float at = nonpad ? ld_elem<uint16_t>(reinterpret_cast<const uint16_t*>(p.logits) + (int64_t)n * p.ldV, y) : 0.f;
+    RowStat st{-INFINITY, 0.f, 0x7fffffff};
+    const TileStat* t = p.stats + (int64_t)n * p.parts;
+    for (int i = lane; i < p.parts; i += 256) {
+      TileStat q[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) q[u] = t[i + 64 * u < p.parts ? i + 64 * u : i];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (i + 64 * u < p.parts) st = combine(st, RowStat{q[u].m, q[u].s, q[u].idx});
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      RowStat other;
+      other.m = __shfl_xor(st.m, o, 64);
+      other.s = __shfl_xor(st.s, o, 64);
+      other.idx = __shfl_xor(st.idx, o, 64);
+      st = combine(st, other);
+    }
+    if (lane == 0) {
+      const float l = st.m + logf(st.s), loss = nonpad ? l - at : 0.f;
+      p.lse[n] = l;
+      __hip_atomic_store(p.tok_loss_ws + n, loss, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (p.tok_loss) p.tok_loss[pos] = loss;
+      if (p.argmax) p.argmax[pos] = st.idx < p.V ? st.idx : 0;
+      if (p.tgt_mask) p.tgt_mask[pos] = nonpad ? 1 : 0;
+    }
+  }
+  if (gridDim.x > 1) {
+    __builtin_amdgcn_s_waitcnt(0);   // the wave's losses are where every XCD sees them (stored past the caches)
+    __syncthreads();
+    if (tid == 0)
+      last = __hip_atomic_fetch_add(p.ticket, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+    __syncthreads();
+    if (!last) return;
+  } else {
+    __syncthreads();
+  }
+  loss_reduce_block([&](int i) { return __hip_atomic_load(p.tok_loss_ws + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); },
+                    p.targets, p.N, p.V, p.pad_id, p.loss_sum, p.n_tok, p.n_act, sd, sc);
 }
 
 // RU rows in flight per thread; NT: 1 = streaming loads, 2 = streaming stores, 3 = both.  Measured on
@@ -309,6 +371,11 @@ hipError_t launch_xent_stats(const void* logits, int64_t ldV, bool e_bf16, int N
     hipLaunchKernelGGL(xent_stats_kernel<float>, dim3(N), dim3(256), 0, st,
                        reinterpret_cast<const float*>(logits), ldV, V, targets, pad_id, lse, tok_loss_ws, tok_loss,
                        argmax, tgt_mask, rows, n_act);
+  return hipGetLastError();
+}
+
+hipError_t launch_xent_finish(const XentFinish& p, hipStream_t st) {
+  hipLaunchKernelGGL(xent_finish_kernel, dim3((p.N + kFinishRows - 1) / kFinishRows), dim3(1024), 0, st, p);
   return hipGetLastError();
 }
 

@@ -313,3 +313,40 @@ def test_list_of_word_positions(T, B, dtype, S):
     pad = inp.targets == inp.pad_id
     assert np.array_equal(f["tgt_mask"].astype(bool), ~pad) and f["n_tok"] == int((~pad).sum())
     assert np.all(f["tok_loss"][pad] == 0.0) and np.all(f["argmax"][pad] == inp.pad_id)
+
+
+@pytest.mark.parametrize("skip", [False, True])
+@pytest.mark.parametrize("N, H, V", [(1, 64, 67), (16, 64, 643), (17, 64, 643), (130, 72, 2003),     # 64 x 64 tiles
+                                     (70, 520, 16003), (128, 1024, 20005)])                          # 128 x 128
+def test_statistics_from_the_projection(N, H, V, skip):
+    """lse, argmax and loss of few rows against those of the logits as stored, in double.  Words that the bias rules out (-inf):
+    more than a tile of them, and the last.  Bound of lse: the sum of V terms, 32 and then 4, 64 and V / 4096 at a time, has a
+    relative error below 105 * 2^-24, every exponential one of 2^-23 and its argument's rounding, below |x - m| log2(e) 2^-24 for
+    terms of that weight: 1.2e-5, and 2e-6 for rounding lse itself; the loss the same again for its rounding."""
+    import torch
+    inp = make_custom(T=1, S=5, B=N, H=H, V=V, seed=V + N, dtype="bf16", min_len=1, pad_prob=0.2)
+    inp.b_out = inp.b_out.copy()
+    inp.b_out[1:min(V // 2, 150)] = -np.inf
+    inp.b_out[V - 1] = -np.inf
+    inp.targets[inp.targets != inp.pad_id] = V - 2
+    import paper_1909_00562_amd as lib
+    from paper_1909_00562_amd import binding as bd
+    db = lib.DeviceBatch(inp, skip_pad_rows=skip)
+    db.fwd(), db.sync()
+    live = (db.targets.reshape(-1) != inp.pad_id)
+    rows = int(live.sum()) if skip else N
+    x = db.view(bd.AS_VIEW_LOGITS).reshape(N, -1)[:rows].double()
+    assert bool(torch.isneginf(x[:, V - 1]).all())
+    lse = torch.logsumexp(x, 1)
+    assert torch.allclose(db.view(bd.AS_VIEW_LSE).reshape(-1)[:rows].double(), lse, rtol=0, atol=1.4e-5)
+    best = torch.argmax((x == x.max(1, keepdim=True).values).int(), 1).int()      # the lowest that attains it
+    arg, loss = db.argmax.reshape(-1), db.tok_loss.reshape(-1).double()
+    want = lse - x[:, V - 2]
+    if skip:
+        assert torch.equal(arg[live], best) and torch.allclose(loss[live], want, rtol=0, atol=1.6e-5)
+        want_sum = want.sum()
+    else:
+        assert torch.equal(arg, best) and torch.allclose(loss[live], want[live], rtol=0, atol=1.6e-5)
+        want_sum = want[live].sum()
+    assert bool((loss[~live] == 0).all()) and int(db.n_tok.item()) == int(live.sum())
+    assert abs(float(db.loss_sum.item()) - float(want_sum)) <= 1.6e-5 * max(1, int(live.sum())) + 2 ** -23 * abs(float(want_sum))
