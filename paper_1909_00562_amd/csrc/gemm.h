@@ -38,8 +38,8 @@ struct GemmArgs {
   const void* B[kMaxSeg] = {};
   int64_t lda[kMaxSeg] = {}, ldb[kMaxSeg] = {};
   int64_t sA[kMaxSeg] = {}, sB[kMaxSeg] = {};  // batch strides
-  int K[kMaxSeg] = {};                         // K[s] = 0: segment unused
-  int nseg = 0;
+  int K[kMaxSeg] = {};
+  int nseg = 0;   // leading dimensions, batch strides and lengths are the same for all segments
   void seg(const void* a, int64_t lda_, int64_t sa_, const void* b, int64_t ldb_, int64_t sb_, int k) {
     A[nseg] = a; lda[nseg] = lda_; sA[nseg] = sa_;
     B[nseg] = b; ldb[nseg] = ldb_; sB[nseg] = sb_;

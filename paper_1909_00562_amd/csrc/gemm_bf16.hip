@@ -504,7 +504,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(GemmDev p, int work_t
   // share operand panels in their XCD's L2.
   // Sizes read on the device shrink the work list: the grid and work_total were sized for p.M.
   const int Mv = dev_bound(p.M_dev, p.M);
-  const int K0 = dev_bound(p.K_dev, p.K[0]);
+  const int K0 = dev_bound(p.K_dev, p.K);
   const int tiles_m = p.M_dev ? (Mv + BM - 1) / BM : p.tiles_m;
   const int splits = p.dyn_split ? pp_dyn_splits(tiles_m * p.tiles_n, (K0 + BK - 1) / BK, p.splits, gridDim.x) : p.splits;
   if (p.M_dev) work_total = tiles_m * p.tiles_n * (p.dyn_split ? splits : p.nz);
@@ -540,9 +540,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(GemmDev p, int work_t
     }
     return it;
   };
-  int nk_rest = 0;   // reduction tiles of all segments but the first
-#pragma unroll
-  for (int s = 1; s < kMaxSeg; ++s) nk_rest += (p.K[s] + BK - 1) / BK;
+  const int nk_rest = (p.nseg - 1) * ((p.K + BK - 1) / BK);   // reduction tiles of all segments but the first
 
   acc_t acc[TM][TN];
   auto zero_acc = [&]() {
@@ -574,19 +572,18 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(GemmDev p, int work_t
     lbatch = it.batch;
     cseg = 0;
     ck_left = it.kend - it.kbeg;
-    cA = p.A[0] + (int64_t)lbatch * p.sA[0] + offA + (AKC ? it.kbeg : (int64_t)it.kbeg * p.lda);
-    cB = p.B[0] + (int64_t)lbatch * p.sB[0] + offB + (BKC ? it.kbeg : (int64_t)it.kbeg * p.ldb);
+    cA = p.A[0] + (int64_t)lbatch * p.sA + offA + (AKC ? it.kbeg : (int64_t)it.kbeg * p.lda);
+    cB = p.B[0] + (int64_t)lbatch * p.sB + offB + (BKC ? it.kbeg : (int64_t)it.kbeg * p.ldb);
   };
   auto advance = [&]() {
     cA += stepA;
     cB += stepB;
     ck_left -= BK;
     if (ck_left <= 0) {
-      do { ++cseg; } while (cseg < kMaxSeg && p.K[cseg] <= 0);
-      if (cseg < kMaxSeg) {
-        cA = p.A[cseg] + (int64_t)lbatch * p.sA[cseg] + offA;
-        cB = p.B[cseg] + (int64_t)lbatch * p.sB[cseg] + offB;
-        ck_left = p.K[cseg];
+      if (++cseg < p.nseg) {
+        cA = p.A[cseg] + (int64_t)lbatch * p.sA + offA;
+        cB = p.B[cseg] + (int64_t)lbatch * p.sB + offB;
+        ck_left = p.K;
       } else {
         lw += nbx;
         lvalid = lw < wend;
@@ -763,7 +760,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring_kernel(
   // share operand panels in their XCD's L2.
   // Sizes read on the device shrink the work list: the grid and work_total were sized for p.M.
   const int Mv = dev_bound(p.M_dev, p.M);
-  const int K0 = dev_bound(p.K_dev, p.K[0]);
+  const int K0 = dev_bound(p.K_dev, p.K);
   const int tiles_m = p.M_dev ? (Mv + BM - 1) / BM : p.tiles_m;
   if (p.M_dev) work_total = tiles_m * p.tiles_n * p.nz;
   const int kper = p.K_dev ? (((K0 + BK - 1) / BK + p.splits - 1) / p.splits) * BK : p.kper;
@@ -798,9 +795,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring_kernel(
     }
     return it;
   };
-  int nk_rest = 0;   // reduction tiles of all segments but the first
-#pragma unroll
-  for (int s = 1; s < kMaxSeg; ++s) nk_rest += (p.K[s] + RK - 1) / RK;
+  const int nk_rest = (p.nseg - 1) * ((p.K + RK - 1) / RK);   // reduction tiles of all segments but the first
 
   f32x16_t acc[TM][TN];
   auto zero_acc = [&]() {
@@ -832,19 +827,18 @@ __global__ __launch_bounds__(512) void gemm_bf16_ring_kernel(
     lbatch = it.batch;
     cseg = 0;
     ck_left = it.kend - it.kbeg;
-    cA = p.A[0] + (int64_t)lbatch * p.sA[0] + offA + (AKC ? it.kbeg : (int64_t)it.kbeg * p.lda);
-    cB = p.B[0] + (int64_t)lbatch * p.sB[0] + offB + (BKC ? it.kbeg : (int64_t)it.kbeg * p.ldb);
+    cA = p.A[0] + (int64_t)lbatch * p.sA + offA + (AKC ? it.kbeg : (int64_t)it.kbeg * p.lda);
+    cB = p.B[0] + (int64_t)lbatch * p.sB + offB + (BKC ? it.kbeg : (int64_t)it.kbeg * p.ldb);
   };
   auto advance = [&]() {
     cA += stepA;
     cB += stepB;
     ck_left -= RK;
     if (ck_left <= 0) {
-      do { ++cseg; } while (cseg < kMaxSeg && p.K[cseg] <= 0);
-      if (cseg < kMaxSeg) {
-        cA = p.A[cseg] + (int64_t)lbatch * p.sA[cseg] + offA;
-        cB = p.B[cseg] + (int64_t)lbatch * p.sB[cseg] + offB;
-        ck_left = p.K[cseg];
+      if (++cseg < p.nseg) {
+        cA = p.A[cseg] + (int64_t)lbatch * p.sA + offA;
+        cB = p.B[cseg] + (int64_t)lbatch * p.sB + offB;
+        ck_left = p.K;
       } else {
         lw += nbx;
         lvalid = lw < wend;
@@ -997,7 +991,7 @@ static bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) =
 // checks of a product and its description for the kernels
 static hipError_t gemm_describe(const GemmArgs& g, GemmTile tile, GemmDev& d) {
   const bool big_tile = tile == kTile256;
-  if (g.M < 1 || g.N < 1 || g.batch < 1 || g.splits < 1) return hipErrorInvalidValue;
+  if (g.M < 1 || g.N < 1 || g.batch < 1 || g.splits < 1 || g.nseg < 1 || g.K[g.nseg - 1] < 1) return hipErrorInvalidValue;
   // split-K: the combine step applies the epilogue; the persistent kernel splits a single segment only
   if (g.splits > 1 && (g.partial == nullptr || (big_tile && g.K[1] != 0))) return hipErrorInvalidValue;
   if (g.drop_thr && g.batch != 1) return hipErrorInvalidValue;   // flat element index = m * N + n
@@ -1005,20 +999,22 @@ static hipError_t gemm_describe(const GemmArgs& g, GemmTile tile, GemmDev& d) {
   for (int s = 0; s < kMaxSeg; ++s) {
     d.A[s] = reinterpret_cast<const uint16_t*>(g.A[s]);
     d.B[s] = reinterpret_cast<const uint16_t*>(g.B[s]);
-    d.sA[s] = g.sA[s];
-    d.sB[s] = g.sB[s];
-    d.K[s] = g.K[s];
     if (g.K[s] > 0) {
       // 16-byte vector loads: leading dimensions and batch strides in units of 8 elements;
       // 32-bit byte offsets inside one 256-row (or 64-reduction-row) tile
       if ((g.lda[s] & 7) || (g.ldb[s] & 7) || (g.sA[s] & 7) || (g.sB[s] & 7)) return hipErrorInvalidValue;
       if (g.lda[s] >= (1 << 22) || g.ldb[s] >= (1 << 22)) return hipErrorInvalidValue;
-      if (g.lda[s] != g.lda[0] || g.ldb[s] != g.ldb[0]) return hipErrorInvalidValue;  // one set of lane offsets
+      if (g.lda[s] != g.lda[0] || g.ldb[s] != g.ldb[0] || g.sA[s] != g.sA[0] || g.sB[s] != g.sB[0] || g.K[s] != g.K[0] || s >= g.nseg)
+        return hipErrorInvalidValue;
       if (!al16(g.A[s]) || !al16(g.B[s])) return hipErrorInvalidValue;
     }
   }
   d.lda = g.lda[0];
   d.ldb = g.ldb[0];
+  d.sA = g.sA[0];
+  d.sB = g.sB[0];
+  d.K = g.K[0];
+  d.nseg = g.nseg;
   d.M = g.M;
   d.N = g.N;
   d.C = g.C;
@@ -1077,8 +1073,7 @@ static hipError_t gemm_describe(const GemmArgs& g, GemmTile tile, GemmDev& d) {
   // many column tiles: 8 rows x 4 columns of co-resident tiles per XCD share 12 operand panels; few column
   // tiles (long-reduction products): whole tile rows, so a row panel is consumed in one go (measured 2-3 % faster)
   d.group = d.tiles_n >= 16 ? 8 : (16 / d.tiles_n < 2 ? 2 : (16 / d.tiles_n > 8 ? 8 : 16 / d.tiles_n));
-  int ktiles = 0;   // reduction tiles of all segments (the persistent kernel splits segment 0 alone, checked above)
-  for (int s = 0; s < kMaxSeg; ++s) ktiles += (g.K[s] + BK - 1) / BK;
+  const int ktiles = g.nseg * ((g.K[0] + BK - 1) / BK);   // of all segments (the persistent kernel splits segment 0 alone, checked above)
   d.kper = ((ktiles + g.splits - 1) / g.splits) * BK;
   if (g.splits > 1 && !g.dyn_split && (int64_t)(d.kper / BK) * (g.splits - 1) >= ktiles)
     return hipErrorInvalidValue;   // an empty split

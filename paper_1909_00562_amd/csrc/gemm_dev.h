@@ -11,8 +11,8 @@ typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 struct GemmDev {
   const uint16_t* A[kMaxSeg];
   const uint16_t* B[kMaxSeg];
-  int64_t lda, ldb, sA[kMaxSeg], sB[kMaxSeg];
-  int K[kMaxSeg];
+  int64_t lda, ldb, sA, sB;   // the same for all segments, like K: every byte of the arguments costs a launch time (80 of them
+  int K, nseg;                // 0.2 us a product of the smallest sizes)
   int M, N;
   int n_out;   // columns the vector write-out covers: N, or N rounded up to 4 where C's rows have padding
   void* C;

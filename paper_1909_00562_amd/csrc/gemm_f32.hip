@@ -12,9 +12,8 @@ namespace asx {
 struct GemmDevF {
   const float* A[kMaxSeg];
   const float* B[kMaxSeg];
-  int64_t lda, ldb;   // the same for all segments
-  int64_t sA[kMaxSeg], sB[kMaxSeg];
-  int K[kMaxSeg];
+  int64_t lda, ldb, sA, sB;   // the same for all segments, like K
+  int K, nseg;
   int M, N;
   float* C;
   float* C_lo;
@@ -173,7 +172,7 @@ static hipError_t launch_f32_oriented(GemmDevF& d, int batch, bool avec, bool bv
 
 // checks of a product and its description for the kernels; avec, bvec: 16-byte loads of the operand
 static hipError_t f32_describe(const GemmArgs& g, GemmDevF& d, bool& avec, bool& bvec) {
-  if (g.M < 1 || g.N < 1 || g.batch < 1 || g.splits < 1 || g.c_bf16) return hipErrorInvalidValue;
+  if (g.M < 1 || g.N < 1 || g.batch < 1 || g.splits < 1 || g.c_bf16 || g.nseg < 1 || g.K[g.nseg - 1] < 1) return hipErrorInvalidValue;
   if (g.splits > 1 && (g.K[1] != 0 || g.partial == nullptr)) return hipErrorInvalidValue;
   if (g.splits > 1 && (g.C_dact || g.drop_thr)) return hipErrorInvalidValue;
   if (g.drop_thr && g.batch != 1) return hipErrorInvalidValue;
@@ -182,11 +181,9 @@ static hipError_t f32_describe(const GemmArgs& g, GemmDevF& d, bool& avec, bool&
   for (int s = 0; s < kMaxSeg; ++s) {
     d.A[s] = reinterpret_cast<const float*>(g.A[s]);
     d.B[s] = reinterpret_cast<const float*>(g.B[s]);
-    d.sA[s] = g.sA[s];
-    d.sB[s] = g.sB[s];
-    d.K[s] = g.K[s];
     if (g.K[s] > 0) {
-      if (g.lda[s] != g.lda[0] || g.ldb[s] != g.ldb[0]) return hipErrorInvalidValue;
+      if (g.lda[s] != g.lda[0] || g.ldb[s] != g.ldb[0] || g.sA[s] != g.sA[0] || g.sB[s] != g.sB[0] || g.K[s] != g.K[0] || s >= g.nseg)
+        return hipErrorInvalidValue;
       // 16-byte loads: groups of four start aligned and do not straddle the operand's edge (a reduction length or row
       // count read on the device counts rows, which are the other index of the operands that use it)
       auto vec_ok = [&](const void* X, int64_t ld, int64_t stride, bool kc, int rows) {
@@ -198,6 +195,10 @@ static hipError_t f32_describe(const GemmArgs& g, GemmDevF& d, bool& avec, bool&
   }
   d.lda = g.lda[0];
   d.ldb = g.ldb[0];
+  d.sA = g.sA[0];
+  d.sB = g.sB[0];
+  d.K = g.K[0];
+  d.nseg = g.nseg;
   d.M = g.M;
   d.N = g.N;
   d.C = reinterpret_cast<float*>(g.C);

@@ -224,7 +224,7 @@ __device__ __forceinline__ void gemm_bf16_tile_block(GemmDev p, int out_bf16, in
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = (wave >> 1) * 16 * TW, wn = (wave & 1) * 16 * TW;
-  const int Mv = dev_bound(p.M_dev, p.M), K0 = dev_bound(p.K_dev, p.K[0]);
+  const int Mv = dev_bound(p.M_dev, p.M), K0 = dev_bound(p.K_dev, p.K);
   const int tiles_m = (Mv + BM - 1) / BM, nt = tiles_m * p.tiles_n;   // the grid was sized for p.M
   // Each XCD gets a contiguous run of the tiles of all products (batches, splits), a product's walked in groups of 8 tile rows: its
   // L2 then brings an operand of a batch, or a split's part of both operands, from memory once.
@@ -241,20 +241,16 @@ __device__ __forceinline__ void gemm_bf16_tile_block(GemmDev p, int out_bf16, in
   const int m0 = (first_m + in_g % gm) * BM, n0 = (in_g / gm) * BM;
   const int batch = z / p.splits, split = z - batch * p.splits;
   const bool second = EXTRA == kSecond && batch == 1;                      // segment 0 alone, to C_second
-  const int nseg = second ? 1 : kMaxSeg;
+  const int nseg = second ? 1 : p.nseg;
 
   // reduction tiles of this block: [t0, t1) of the sequence that runs through the segments one after the other
-  int nk = 0, seg = 0, skip = 0;
-#pragma unroll
-  for (int s = 0; s < kMaxSeg; ++s) nk += s < nseg ? ((s == 0 ? K0 : p.K[s]) + BK - 1) / BK : 0;
+  const int ks = (p.K + BK - 1) / BK;
+  int nk = (K0 + BK - 1) / BK + (nseg - 1) * ks, seg = 0, skip = 0;
   if (p.splits > 1) {
     const int per = p.K_dev ? (nk + p.splits - 1) / p.splits : p.kper / BK;
     skip = split * per;
     nk = nk - skip < per ? nk - skip : per;
-    for (int left = (K0 + BK - 1) / BK; seg < kMaxSeg - 1 && skip >= left; left = (p.K[seg] + BK - 1) / BK) {
-      skip -= left;
-      ++seg;
-    }
+    for (; seg < nseg - 1 && skip >= ks; ++seg) skip -= ks;   // (K0 = K where there are more segments than one)
   }
   typename std::conditional<AKC, DirectLoader<BM, 4>, StridedLoader<BM>>::type la;
   typename std::conditional<BKC, DirectLoader<BM, 4>, StridedLoader<BM>>::type lb;
@@ -262,16 +258,15 @@ __device__ __forceinline__ void gemm_bf16_tile_block(GemmDev p, int out_bf16, in
   lb.init(p.ldb, p.N - n0, wave, lane);
   const int64_t stepA = AKC ? BK : BK * p.lda, stepB = BKC ? BK : BK * p.ldb;
   const int64_t offA = AKC ? (int64_t)m0 * p.lda : m0, offB = BKC ? (int64_t)n0 * p.ldb : n0;
-  int k_left = (seg == 0 ? K0 : p.K[seg]) - skip * BK;
-  const uint16_t* cA = p.A[seg] + (int64_t)batch * p.sA[seg] + offA + skip * stepA;
-  const uint16_t* cB = p.B[seg] + (int64_t)batch * p.sB[seg] + offB + skip * stepB;
+  int k_left = K0 - skip * BK;
+  const uint16_t* cA = p.A[seg] + (int64_t)batch * p.sA + offA + skip * stepA;
+  const uint16_t* cB = p.B[seg] + (int64_t)batch * p.sB + offB + skip * stepB;
   auto issue = [&](int stage) {   // the tile under the cursor
     if (k_left <= 0) {            // on to the next segment, if there is one
-      do { ++seg; } while (seg < nseg && p.K[seg] <= 0);
-      if (seg < nseg) {
-        cA = p.A[seg] + (int64_t)batch * p.sA[seg] + offA;
-        cB = p.B[seg] + (int64_t)batch * p.sB[seg] + offB;
-        k_left = p.K[seg];
+      if (++seg < nseg) {
+        cA = p.A[seg] + (int64_t)batch * p.sA + offA;
+        cB = p.B[seg] + (int64_t)batch * p.sB + offB;
+        k_left = p.K;
       } else {
         seg = nseg - 1;           // all loads below are out of range
       }
@@ -599,9 +594,7 @@ using MemberNNSecond = TileMember<2, true, false, 4, true, kSecond>;
 using MemberNT = TileMember<2, true, true, 4, true>;
 
 static int tile_ktiles(const GemmDev& d) {   // reduction tiles of a block
-  int n = 0;
-  for (int s = 0; s < kMaxSeg; ++s) n += (d.K[s] + BK - 1) / BK;
-  return (n + d.splits - 1) / d.splits;
+  return (d.nseg * ((d.K + BK - 1) / BK) + d.splits - 1) / d.splits;
 }
 template <typename TN, typename NN>
 static hipError_t launch_with_sums(const GemmDev* d, const TileForm* f, const DbReduce& sums, hipStream_t st) {
@@ -671,7 +664,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void gemm_bf16_few_kernel(GemmDev p
   const int nbm = (p.M + 16 * NJ - 1) / (16 * NJ), nbn = (p.N + 15) / 16, per = (nbn + 7) / 8;
   const int idx = blockIdx.x >> 3, bn = (blockIdx.x & 7) * per + idx / nbm;
   if (bn >= nbn) return;
-  const int n0 = bn * 16, m0 = (idx % nbm) * 16 * NJ, K = p.K[0], nk = (K + 63) / 64;
+  const int n0 = bn * 16, m0 = (idx % nbm) * 16 * NJ, K = p.K, nk = (K + 63) / 64;
   const int col = n0 + c < p.N ? n0 + c : p.N - 1;   // columns and rows outside repeat the last one; not stored
   const int64_t boff = (int64_t)col * p.ldb;
   int64_t aoff[NJ];
@@ -735,11 +728,8 @@ __global__ __launch_bounds__(64 * kFewWaves) void gemm_bf16_few_kernel(GemmDev p
   gs_finish4<COPY>(p, out_bf16, 0, row, ccol, v, bias4);
 }
 hipError_t launch_gemm_bf16_few(const GemmDev& d, bool out_bf16, hipStream_t st) {
-  int nseg = 0;
-  while (nseg < kMaxSeg && d.K[nseg] > 0) ++nseg;
-  if (nseg < 1 || nseg > 3 || d.splits != 1) return hipErrorInvalidValue;
-  for (int s = 1; s < nseg; ++s)
-    if (d.K[s] != d.K[0]) return hipErrorInvalidValue;
+  const int nseg = d.nseg;
+  if (nseg > 3 || d.splits != 1) return hipErrorInvalidValue;
   const int nj = d.M > 16 ? 2 : 1;
   const int64_t nbm = (d.M + 16 * nj - 1) / (16 * nj), per = ((d.N + 15) / 16 + 7) / 8;
   const dim3 grid((unsigned)(8 * per * nbm));
