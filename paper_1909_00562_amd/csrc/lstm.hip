@@ -7,7 +7,7 @@
 // over all steps ahead of them).  Backward walks the wavefronts the other way; the weight
 // gradients and the gradient of x are then large products over all steps at once.
 // Right-padded sentences keep their state at steps t >= lengths[b]; their gate gradients
-// are zero rows, so the large products need no masking.
+// are zero rows, so the large products need no masking, or (ls_packed) have no rows at all.
 #include "../../include/lstm_stack.h"
 
 #include <vector>
@@ -30,6 +30,8 @@ struct LsLayout {
   int64_t x_stride, h_stride, g_stride;   // bytes of one step's operand as fragment tiles
   size_t gates, cs, hE, out, dG;          // [L] (out: [L - 1]) blocks each
   size_t hf, dcs, dbacc, partial, total;
+  size_t start, pos, xw, dx_rows;         // packed: rows of the sentences and positions, of the words of x and of its gradient
+  bool packed;
   size_t h0_copy;                         // T = 1: h0 and c0 where an output lies on top of them
   size_t xF, zeros, hF[2], oF[2], dGF;    // fragment tiles; [0] value, [1] remainder (bf16 storage)
   std::vector<size_t> Wf_hh, Wf_ih, Wb_hh, Wb_up;   // weights as tiles, per layer
@@ -148,6 +150,8 @@ LsLayout make_ls_layout(const ls_shape* s) {
   L.cs = take((size_t)NL * (T + 1) * L.BH * 4);
   L.hE = take((size_t)NL * (T + 1) * L.BH * L.e);
   L.out = take((size_t)(NL - 1) * TB * H * L.e);
+  L.packed = bf ? ls_packed<uint16_t>(T, B, I, H, NL) : ls_packed<float>(T, B, I, H, NL);
+  L.start = take(L.packed ? (size_t)(B + 1) * 4 : 0);
   // one area for what only the forward and what only the backward pass needs
   const size_t area = off;
   L.hf = take((size_t)NL * L.BH * 4);
@@ -159,6 +163,9 @@ LsLayout make_ls_layout(const ls_shape* s) {
   L.dcs = take((size_t)NL * L.BH * 4);
   L.dbacc = take((size_t)NL * ls_batch_tiles(B) * 4 * H * 4);
   L.partial = take(pb);
+  L.pos = take(L.packed ? (size_t)TB * 4 : 0);
+  L.xw = take(L.packed ? (size_t)TB * I * L.e : 0);
+  L.dx_rows = take(L.packed && L.p_dx.splits == 1 ? (size_t)TB * I * 4 : 0);
   if (bf) ls_bwd_tiles<uint16_t>(s, L, take);
   else ls_bwd_tiles<float>(s, L, take);
   if (off < end) off = end;
@@ -210,6 +217,7 @@ as_status ls_fwd(const ls_shape* s, const LsLayout& L, const char* x, const int3
   LsFwd f{};
   LsPrepFwd q{};
   f.T = s->T; f.B = s->B; f.I = s->I; f.H = s->H; f.L = s->L;
+  if (L.packed) f.words.start = reinterpret_cast<int32_t*>(w + L.start);
   f.x_apart = L.x_apart;
   f.w_rows = L.w_rows;
   for (int l = 0; l < s->L; ++l) {
@@ -292,6 +300,13 @@ as_status ls_bwd(const ls_shape* s, const LsLayout& L, const char* x, const int3
   r.gates = reinterpret_cast<const float*>(w + L.gates);
   r.cs = reinterpret_cast<const float*>(w + L.cs);
   r.dy = dy; r.dhT = dhT; r.dcT = dcT;
+  const int32_t* n_words = nullptr;
+  if (L.packed) {
+    q.words = r.words = LsWords{reinterpret_cast<int32_t*>(w + L.start), reinterpret_cast<int32_t*>(w + L.pos), w + L.xw};
+    q.x = x; q.hE = w + L.hE;
+    q.T = T; q.B = B; q.I = I; q.L = NL;
+    n_words = r.words.start + B;
+  }
   r.dcs = dc0 ? dc0 : reinterpret_cast<float*>(w + L.dcs);
   r.dh0 = dh0;
   r.dG = w + L.dG;
@@ -320,15 +335,17 @@ as_status ls_bwd(const ls_shape* s, const LsLayout& L, const char* x, const int3
     }
     LS_TRY(launch_ls_wave_bwd<TE>(r, d, st));
   }
+  const size_t h_first = L.packed ? (size_t)L.BH * L.e : 0;   // packed: behind the initial states
   LS_TRY(launch_ls_bias_reduce(r.dbacc, o, NL, ls_batch_tiles(B), 4 * H, st));
   {
-    const char *dG = w + L.dG, *hE = w + L.hE, *out = w + L.out;
+    const char *dG = w + L.dG, *hE = w + L.hE + h_first, *out = w + L.out;
     const int64_t sG = (int64_t)TB * 4 * H;
     auto together = [&](int n, const char* a, const char* b, int64_t sB, float* const* dW) {
       GemmArgs g;
       g.seg(a, 4 * H, sG, b, H, sB, TB);
       g.a_kc = false; g.b_kc = false;
       g.M = 4 * H; g.N = H; g.batch = n;
+      g.K_dev = n_words;
       g.C_of = reinterpret_cast<void* const*>(dW); g.ldc = H; g.c_bf16 = false;
       return launch_gemm(g, bf, kTile256, st);
     };
@@ -338,13 +355,14 @@ as_status ls_bwd(const ls_shape* s, const LsLayout& L, const char* x, const int3
   for (int l = 0; l < NL; ++l) {
     const int Il = l == 0 ? I : H;
     const char* dG = w + L.dG + (size_t)l * TB * 4 * H * L.e;
-    const char* hE = w + L.hE + (size_t)l * (T + 1) * L.BH * L.e;
-    const char* xin = l == 0 ? x : w + L.out + (size_t)(l - 1) * TB * H * L.e;
+    const char* hE = w + L.hE + h_first + (size_t)l * (T + 1) * L.BH * L.e;
+    const char* xin = l == 0 ? (L.packed ? w + L.xw : x) : w + L.out + (size_t)(l - 1) * TB * H * L.e;
     if (!L.dwh_batched) {  // dW_hh = sum_t da_t^T h_{t-1}
       GemmArgs g;
       g.seg(dG, 4 * H, 0, hE, H, 0, TB);
       g.a_kc = false; g.b_kc = false;
       g.M = 4 * H; g.N = H;
+      g.K_dev = n_words;
       g.C = dW_hh[l]; g.ldc = H; g.c_bf16 = false;
       g.splits = L.p_dwh.splits; g.partial = partial;
       LS_TRY(launch_gemm(g, bf, L.p_dwh.tile, st));
@@ -354,6 +372,7 @@ as_status ls_bwd(const ls_shape* s, const LsLayout& L, const char* x, const int3
       g.seg(dG, 4 * H, 0, xin, Il, 0, TB);
       g.a_kc = false; g.b_kc = false;
       g.M = 4 * H; g.N = Il;
+      g.K_dev = n_words;
       g.C = dW_ih[l]; g.ldc = Il; g.c_bf16 = false;
       g.splits = L.p_dwi[l].splits; g.partial = partial;
       LS_TRY(launch_gemm(g, bf, L.p_dwi[l].tile, st));
@@ -364,9 +383,13 @@ as_status ls_bwd(const ls_shape* s, const LsLayout& L, const char* x, const int3
     g.seg(w + L.dG, 4 * H, 0, W_ih[0], I, 0, 4 * H);
     g.a_kc = true; g.b_kc = false;
     g.M = TB; g.N = I;
-    g.C = dx; g.ldc = I; g.c_bf16 = false;
+    const bool rows = L.packed && L.p_dx.splits == 1;   // (a split's combine puts the rows at their places)
+    g.M_dev = n_words;
+    g.row_pos = L.packed && !rows ? r.words.pos : nullptr;
+    g.C = rows ? reinterpret_cast<float*>(w + L.dx_rows) : dx; g.ldc = I; g.c_bf16 = false;
     g.splits = L.p_dx.splits; g.partial = partial;
     LS_TRY(launch_gemm(g, bf, L.p_dx.tile, st));
+    if (rows) LS_TRY(launch_scatter_rows(r.words.pos, TB, w + L.dx_rows, dx, nullptr, nullptr, (int64_t)I * 4, st));
   }
   return AS_OK;
 }

@@ -32,7 +32,17 @@ template <typename TE> __host__ __device__ inline int ls_gate_stride(int H) {
 }
 
 // Addresses in bytes or typed pointers; strides in elements of the pointer's type (bytes for char*).
+// Sequences (ls_packed): what the products over all steps read (gate gradients, states, outputs, x) is kept per word, without
+// rows for padding: sentence b's words are rows start[b] .. start[b + 1).  Otherwise a row per position, t B + b.
+struct LsWords {
+  int32_t* start;   // [B + 1], or null
+  int32_t* pos;     // [T, B] row of a position, -1 where there is no word (made by the backward pass, as x)
+  void* x;          // the input's rows of words, storage type
+};
+template <typename TE> bool ls_packed(int T, int B, int I, int H, int L);
+
 struct LsFwd {
+  LsWords words;
   // weights of layer l: fragment tiles made by launch_ls_prep_fwd, or the caller's rows (w_rows)
   const void *W_hh[kLsMaxLayers], *W_ih[kLsMaxLayers];
   const void* bias[kLsMaxLayers];
@@ -42,7 +52,8 @@ struct LsFwd {
   char *oF_hi, *oF_lo;             // [L - 1][2 slots][h_stride bytes]: output of step t (what layer l + 1 reads), slot t & 1
   int64_t h_stride;
   float *gates, *cs;               // [L][T,B,4H] i, f, g, o; [L][T+1,B,H] cell states
-  void *hE, *out;                  // [L][T+1,B,H] states, [L - 1][T,B,H] outputs, storage type
+  void *hE, *out;                  // [L][T+1,B,H] states (packed: [B,H] initial ones, then the one before each word), [L - 1][T,B,H] outputs,
+                                   // per word where packed; storage type
   void* y;                         // [T,B,H] output of the top layer
   float *hf, *cT;                  // [L][B,H] final h: h0 from the prepare launch, overwritten at a sentence's last step; final c (or null)
   const int32_t* lengths;
@@ -58,11 +69,12 @@ struct LsFwd {
 };
 
 struct LsBwd {
+  LsWords words;
   const char *WT_hh[kLsMaxLayers], *WT_up[kLsMaxLayers];   // tiles of W_hh[l]^T and of W_ih[l + 1]^T
   const float *gates, *cs, *dy, *dhT, *dcT;                // dhT, dcT [L][B,H] may be null
   float* dcs;                                              // [L][B,H] running gradient w.r.t. c (ends as dc0)
   float* dh0;                                              // [L][B,H] or null
-  void* dG;                                                // [L][T,B,4H] gate gradients, storage type
+  void* dG;                                                // [L][T,B,4H] gate gradients, per word where packed; storage type
   char* dGF;                                               // [L][2 slots][g_stride bytes]: the same as tiles, slot t & 1
   int64_t g_stride;
   float* dbacc;                                            // [L][batch tiles][4H]: column sums of the gate gradients
@@ -93,6 +105,11 @@ struct LsPrepBwd {
   const void* W[2 * kLsMaxLayers];
   char* tiles[2 * kLsMaxLayers];
   int n, H;
+  // packed (words.start not null): behind the weights, rows of x, of the initial states and of the positions
+  LsWords words;
+  const void* x;
+  void* hE;
+  int T, B, I, L;
   void add(const void* w, const char* t) { W[n] = w; tiles[n++] = const_cast<char*>(t); }
 };
 template <typename TE> hipError_t launch_ls_prep_bwd(const LsPrepBwd& q, hipStream_t st);

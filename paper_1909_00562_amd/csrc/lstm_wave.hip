@@ -252,6 +252,7 @@ __device__ __forceinline__ void ls_prep_state(const LsFwd& p, int l, int64_t fir
       }
 #pragma unroll
       for (int v = 0; v < V / 4; ++v) {
+        if (p.words.start && p.cT) ls_st4<true>(p.cT + idx + 4 * v, c[v], 4);   // (stays where a sentence has no words)
         ls_st4<true>(p.hf + idx + 4 * v, h[v], 4);
         ls_st4<true>(cs + row + 4 * v, c[v], 4);
         ls_st4<true>(hE + row + 4 * v, h[v], 4);
@@ -270,6 +271,7 @@ __device__ __forceinline__ void ls_prep_state(const LsFwd& p, int l, int64_t fir
       if (in) {
         const float c = p.c0 ? p.c0[idx] : 0.f;
         p.hf[idx] = h;
+        if (p.words.start && p.cT) p.cT[idx] = c;
         cs[idx - (int64_t)l * BH] = c;
         st_elem<TE>(hE, idx - (int64_t)l * BH, h);
       }
@@ -300,7 +302,7 @@ __device__ __forceinline__ void ls_prep_state(const LsFwd& p, int l, int64_t fir
 // per step: 4 x 1024 units x 128 sentences 114.7 us for 116.9, 4 x 192 units x 116 sentences 75.5 for 73.8, and other bits).
 // ROWS = 2: layer 0 of ls_reads_states.  APART: layer 0 finds the input product and the
 // bias in the gates' place.
-template <typename TE, int NI, int NJ, int PF, int ROWS, bool VEC, bool APART>
+template <typename TE, int NI, int NJ, int PF, int ROWS, bool VEC, bool APART, bool PACKED>
 __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d, int l_lo, int n_layers) {
   typedef LsMma<TE> M;
   typedef typename M::acc_t acc_t;
@@ -332,6 +334,8 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
   // what the cells need from memory is requested ahead of the product
   constexpr int NTASK = (NG * NJ + LS_KS - 1) / LS_KS;   // (g, j) pairs, dealt out to the waves
   // (lanes and tasks without a cell read the last one: no branch around a load that is to stay in flight)
+  constexpr bool packed = PACKED;
+  int len[NTASK], wrd[NTASK];     // packed: row of the sentence's first word
   f32x4_t cp[NTASK], hp[NTASK];   // hp (DIRECT): the initial state itself
   typename M::raw4_t bias[NTASK][4];
   const float* c_prev = DIRECT && p.c0 ? p.c0 + l * BH : p.cs + ((int64_t)l * (p.T + 1) + t) * BH;
@@ -342,6 +346,10 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
     const int task = wave + k * LS_KS, g = task / NJ, j = task % NJ;
     const int b = b0 + 16 * j + c, unit0 = u0 + 16 * g + 4 * q;
     const int bs = b < B ? b : B - 1, us = unit0 < H ? unit0 : (H - 1) & ~3;
+    if constexpr (packed) {
+      len[k] = p.lengths[bs];
+      wrd[k] = p.words.start[bs];
+    }
     cp[k] = ls_ld4<VEC>(c_prev + (int64_t)bs * H + us, H - us);
     if constexpr (DIRECT) hp[k] = ls_ld4<VEC>(h_prev + (int64_t)bs * H + us, H - us);
 #pragma unroll
@@ -555,6 +563,13 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
       hn[ii] = go[ii] * ls_tanh(cn[ii]);
     }
     const int64_t idx = (int64_t)b * H + unit0;
+    if constexpr (packed) {
+      len[k] = len[k] < 0 ? 0 : (len[k] > p.T ? p.T : len[k]);
+      if (t >= len[k]) {   // a padded step leaves everything as it is: no product and no cell reads this sentence's columns again
+        if (l + 1 == p.L) ls_st4<VEC>(reinterpret_cast<TE*>(p.y) + (int64_t)t * BH + idx, f32x4_t{0.f, 0.f, 0.f, 0.f}, n);
+        continue;
+      }
+    }
     if constexpr (DIRECT) {   // what the preparation leaves elsewhere
       ls_st4<VEC>(p.cs + (int64_t)l * (p.T + 1) * BH + idx, cp[k], n);
       ls_st4<VEC>(reinterpret_cast<TE*>(p.hE) + (int64_t)l * (p.T + 1) * BH + idx, hp[k], n);
@@ -563,8 +578,8 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
     ls_st4_away<VEC>(G + H, gf, n);
     ls_st4_away<VEC>(G + 2 * (int64_t)H, gg, n);
     ls_st4_away<VEC>(G + 3 * (int64_t)H, go, n);
-    const int len = ls_len(p.lengths, b, p.T);
-    const bool valid = t < len;
+    if constexpr (!packed) len[k] = ls_len(p.lengths, b, p.T);
+    const bool valid = packed || t < len[k];
     const int64_t foff = ls_tile_off<TE>(unit0, b, nct);
     TE* hFn_hi = reinterpret_cast<TE*>(p.hF_hi + (2 * l + ((t + 1) & 1)) * p.h_stride) + foff;
     TE* hFn_lo = reinterpret_cast<TE*>(p.hF_lo + (2 * l + ((t + 1) & 1)) * p.h_stride) + foff;
@@ -581,7 +596,10 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
         for (int e = 0; e < 4; ++e) o[e] = dm[k][e] != 0.f ? o[e] * dm[k][e] : 0.f;
       }
       hv = hn;
-      if (t + 1 == len) ls_st4<VEC>(p.hf + l * BH + idx, hn, n);   // the final state
+      if (t + 1 == len[k]) {   // the final state
+        ls_st4<VEC>(p.hf + l * BH + idx, hn, n);
+        if (packed && p.cT) ls_st4<VEC>(p.cT + l * BH + idx, cn, n);
+      }
       if constexpr (!DIRECT) {
         ls_st4<true>(hFn_hi, hn, 4);
         if constexpr (M::kPair) ls_st4<true>(hFn_lo, ls_rest<TE>(hn), 4);
@@ -597,10 +615,12 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
       if constexpr (M::kPair) ls_st4<true>(hFn_lo, ls_widen4(ls_ldraw4<true>(reinterpret_cast<const TE*>(h_lo) + foff, 4)), 4);
     }
     ls_st4<VEC>(p.cs + ((int64_t)l * (p.T + 1) + t + 1) * BH + idx, cn, n);
-    if (last && p.cT) ls_st4<VEC>(p.cT + l * BH + idx, cn, n);
-    ls_st4<VEC>(reinterpret_cast<TE*>(p.hE) + ((int64_t)l * (p.T + 1) + t + 1) * BH + idx, hv, n);
+    if (!packed && last && p.cT) ls_st4<VEC>(p.cT + l * BH + idx, cn, n);
+    const int64_t row = packed ? wrd[k] + t : (int64_t)t * B + b;   // of the word (states: of the next one, behind the initial ones)
+    if (!packed || t + 1 < len[k])
+      ls_st4<VEC>(reinterpret_cast<TE*>(p.hE) + (int64_t)l * (p.T + 1) * BH + (B + row + packed) * H + unit0, hv, n);
     if (l + 1 < p.L) {
-      ls_st4<VEC>(reinterpret_cast<TE*>(p.out) + ((int64_t)l * p.T + t) * BH + idx, o, n);
+      ls_st4<VEC>(reinterpret_cast<TE*>(p.out) + ((int64_t)l * p.T * B + row) * H + unit0, o, n);
       const int64_t slot = (2 * l + (t & 1)) * p.h_stride;
       ls_st4<true>(reinterpret_cast<TE*>(p.oF_hi + slot) + foff, o, 4);
       if constexpr (M::kPair) ls_st4<true>(reinterpret_cast<TE*>(p.oF_lo + slot) + foff, ls_rest<TE>(o), 4);
@@ -616,7 +636,7 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
 // of its output; the top layer reads the caller's dy).  The gradient w.r.t. h_t is the former where step t + 1 was a
 // word of the sentence, else what came in for the final state (sentences are right-padded, so the steps of a sentence
 // are a prefix).  t = -1: the first sum alone, written out as the gradient of the initial state.
-template <typename TE, int NI, int NJ, int PF, bool VEC>
+template <typename TE, int NI, int NJ, int PF, bool VEC, bool PACKED>
 __global__ __launch_bounds__(64 * LS_KS) void ls_wave_bwd_kernel(LsBwd p, int d, int l_lo, int n_layers) {
   typedef LsMma<TE> M;
   typedef typename M::acc_t acc_t;
@@ -641,7 +661,8 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_bwd_kernel(LsBwd p, int d,
   // (lanes and tasks without a cell read the last one, and what is absent is read from cs: no branch around a load
   // that is to stay in flight)
   f32x4_t gi[NTASK], gf[NTASK], gg[NTASK], go[NTASK], cp[NTASK], cn[NTASK], dy[NTASK], dcs[NTASK], carried[NTASK];
-  int len[NTASK];
+  constexpr bool packed = PACKED;
+  int len[NTASK], wrd[NTASK];   // packed: row of the sentence's first word
   const int tc0 = t < 0 ? 0 : t;
   const float* cs_t = p.cs + ((int64_t)l * (p.T + 1) + tc0) * BH;
   const float* dc_in = t + 1 < p.T ? p.dcs : p.dcT;
@@ -656,6 +677,7 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_bwd_kernel(LsBwd p, int d,
     const int64_t idx = (int64_t)bs * H + us;
     const float* G = p.gates + ((int64_t)l * p.T + tc0) * 4 * BH + (int64_t)bs * 4 * H + us;
     len[k] = p.lengths[bs];
+    if constexpr (packed) wrd[k] = p.words.start[bs];
     gi[k] = ls_ld4<VEC>(G, n);
     gf[k] = ls_ld4<VEC>(G + H, n);
     gg[k] = ls_ld4<VEC>(G + 2 * (int64_t)H, n);
@@ -820,9 +842,10 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_bwd_kernel(LsBwd p, int d,
 #pragma unroll
         for (int e = 0; e < 4; ++e) da[g][e] = 0.f;
     }
-    if (b < B) {
-      ls_st4<VEC>(p.dcs + l * BH + idx, dcs[k], n);
-      TE* dG = reinterpret_cast<TE*>(p.dG) + ((int64_t)l * p.T + t) * 4 * BH + (int64_t)b * 4 * H + unit0;
+    if (b < B && (!packed || cell || t + 1 == p.T)) ls_st4<VEC>(p.dcs + l * BH + idx, dcs[k], n);
+    if (packed ? cell : b < B) {   // (packed: a padded step has no row, and its column of the tiles adds to sums nobody reads)
+      const int64_t row = packed ? wrd[k] + t : (int64_t)t * B + b;
+      TE* dG = reinterpret_cast<TE*>(p.dG) + ((int64_t)l * p.T * B + row) * 4 * H + unit0;
       TE* dGF = reinterpret_cast<TE*>(p.dGF + (2 * l + (t & 1)) * p.g_stride);
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
@@ -847,15 +870,46 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_bwd_kernel(LsBwd p, int d,
   }
 }
 
-// Jobs (blockIdx.y): 0 .. L-1 states of a layer, L the input x, then (unless w_rows) W_hh and W_ih of each layer.
+// Row of every sentence's first word, by a block of 256 threads: prefix sums of the lengths, 256 sentences at a time.
+__device__ __forceinline__ void ls_word_starts(int32_t* start, const int32_t* lengths, int T, int B) {
+  __shared__ int total[4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int base = 0;
+  for (int b0 = 0; b0 < B; b0 += 256) {
+    const int own = b0 + tid < B ? ls_len(lengths, b0 + tid, T) : 0;
+    int v = own;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int up = __shfl_up(v, d, 64);
+      v += lane >= d ? up : 0;
+    }
+    if (lane == 63) total[wave] = v;
+    __syncthreads();
+    int before = base, all = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      before += w < wave ? total[w] : 0;
+      all += total[w];
+    }
+    if (b0 + tid < B) start[b0 + tid] = before + v - own;
+    base += all;
+    __syncthreads();   // the totals are rewritten
+  }
+  if (tid == 0) start[B] = base;
+}
+
+// Jobs (blockIdx.y): 0 .. L-1 states of a layer, L the input x, then (unless w_rows) W_hh and W_ih of each layer; packed: at the
+// end the rows of the sentences.
 template <typename TE>
-__global__ __launch_bounds__(256) void ls_prep_fwd_kernel(LsFwd p, LsPrepFwd s) {
+__global__ __launch_bounds__(256) void ls_prep_fwd_kernel(LsFwd p, LsPrepFwd s, int jobs) {
   typedef LsMma<TE> M;
   constexpr int V = LsGeom<TE>::kVec, KST = LsGeom<TE>::kKStep;
   const int job = blockIdx.y, H = p.H, B = p.B, L = p.L, nct = (B + 15) >> 4;
   const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x, stride = (int64_t)gridDim.x * 256;
   const int64_t BH = (int64_t)B * H;
-  if (job < L) {
+  if (p.words.start && job == jobs - 1) {
+    if (blockIdx.x == 0) ls_word_starts(p.words.start, p.lengths, p.T, B);
+  } else if (job < L) {
     ls_prep_state<TE>(p, job, first, stride, false);
   } else if (job == L) {
     if (p.x_apart) return;
@@ -894,12 +948,47 @@ __global__ __launch_bounds__(256) void ls_prep_fwd_kernel(LsFwd p, LsPrepFwd s) 
   }
 }
 
-// blockIdx.y: the weight.  Tile row rho of tile i: unit 16 i + 4 q + r.
+// n elements of a row by a wave
+template <typename TE> __device__ __forceinline__ void ls_copy_row(TE* dst, const TE* src, int n) {
+  constexpr int V = 16 / (int)sizeof(TE);
+  const int lane = threadIdx.x & 63;
+  if (n % V == 0) {
+    for (int u = lane * V; u < n; u += 64 * V) *reinterpret_cast<ls_u32x4_t*>(dst + u) = *reinterpret_cast<const ls_u32x4_t*>(src + u);
+  } else {
+    for (int u = lane; u < n; u += 64) dst[u] = src[u];
+  }
+}
+// What the products over all words read and no wavefront writes, a wave per row: rows of x and of the positions; or the states
+// before each sentence's first word.
+template <typename TE> __device__ __forceinline__ void ls_prep_words(const LsPrepBwd& s, bool inputs) {
+  const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6), waves = (int64_t)gridDim.x * 4;
+  const int B = s.B, H = s.H;
+  if (inputs) {
+    for (int64_t i = wave; i < (int64_t)s.T * B; i += waves) {
+      const int t = (int)(i / B), b = (int)(i - (int64_t)t * B), row = s.words.start[b] + t;
+      const bool word = row < s.words.start[b + 1];
+      if ((threadIdx.x & 63) == 0) s.words.pos[i] = word ? row : -1;
+      if (word) ls_copy_row<TE>(reinterpret_cast<TE*>(s.words.x) + (int64_t)row * s.I, reinterpret_cast<const TE*>(s.x) + i * s.I, s.I);
+    }
+  } else {
+    for (int64_t i = wave; i < (int64_t)s.L * B; i += waves) {
+      const int l = (int)(i / B), b = (int)(i - (int64_t)l * B), row = s.words.start[b];
+      TE* hE = reinterpret_cast<TE*>(s.hE) + (int64_t)l * (s.T + 1) * B * H;
+      if (row < s.words.start[b + 1]) ls_copy_row<TE>(hE + ((int64_t)B + row) * H, hE + (int64_t)b * H, H);
+    }
+  }
+}
+
+// blockIdx.y: the weight.  Tile row rho of tile i: unit 16 i + 4 q + r.  Packed: two more for the rows of words.
 template <typename TE>
 __global__ __launch_bounds__(256) void ls_prep_bwd_kernel(LsPrepBwd s) {
   typedef LsMma<TE> M;
   constexpr int V = LsGeom<TE>::kVec, KST = LsGeom<TE>::kKStep;
   const int H = s.H;
+  if ((int)blockIdx.y >= s.n) {
+    ls_prep_words<TE>(s, blockIdx.y == s.n);
+    return;
+  }
   const TE* W = reinterpret_cast<const TE*>(s.W[blockIdx.y]);
   char* dst = s.tiles[blockIdx.y];
   const int GS = ls_gate_stride<TE>(H), ntu = (H + 63) / 64 * 4;
@@ -962,6 +1051,17 @@ template <typename TE> bool ls_input_apart(int T, int I, int H, int L) {
   return LsMma<TE>::kPair && T > 1 && (int64_t)T * (I - 256) >= 6000 && I >= (L > 1 ? 2 * H : H);
 }
 
+// Rows of words alone shorten the products over all steps by the share of padding (30 % where lengths are even over 0.4 T .. T, half
+// over 1 .. T) and save a padded step its stores; the rows of x and of the initial states and the way back of dx cost 4 to 10 us.  So
+// where the weight gradients have enough to do.  Forward and backward, us, a row per position / per word: 4 x 1024 units, 50 x 128
+// 3236 / 3117, fp32 2 x 512, 30 x 64 1340 / 1260; fp32 288 units, 8 x 17, 9e7 multiplications 201.7 / 200.6 and 320 units, 18 x 6,
+// 9e7 405 / 411; bf16 2 x 640, 14 x 16, 1e9 308 / 309, 2 x 128, 64 x 12, 2e8 820 / 826.  (Either way in instances of their own: a choice made in the
+// wavefront kernels cost each launch 0.2 us.  One block finds the rows of the sentences.)
+template <typename TE> bool ls_packed(int T, int B, int I, int H, int L) {
+  const double work = (double)T * B * 4.0 * H * (I + H + (L - 1) * 2.0 * H);   // multiplications of the weight gradients
+  return T > 1 && B <= 16384 && work >= (LsMma<TE>::kPair ? 8e9 : 4e8);
+}
+
 template <typename TE> hipError_t launch_ls_prep_fwd(const LsFwd& p, const LsPrepFwd& q, hipStream_t st) {
   constexpr int KST = LsGeom<TE>::kKStep;
   const int64_t nct = ls_batch_tiles(p.B);
@@ -975,16 +1075,17 @@ template <typename TE> hipError_t launch_ls_prep_fwd(const LsFwd& p, const LsPre
   }
   int64_t gx = (n + 255) / 256;
   if (gx > 1024) gx = 1024;
-  const int jobs = p.L + 1 + (p.w_rows ? 0 : 2 * p.L);
-  hipLaunchKernelGGL(ls_prep_fwd_kernel<TE>, dim3((unsigned)gx, jobs), dim3(256), 0, st, p, q);
+  const int jobs = p.L + 1 + (p.w_rows ? 0 : 2 * p.L) + (p.words.start ? 1 : 0);
+  hipLaunchKernelGGL(ls_prep_fwd_kernel<TE>, dim3((unsigned)gx, jobs), dim3(256), 0, st, p, q, jobs);
   return hipGetLastError();
 }
 template <typename TE> hipError_t launch_ls_prep_bwd(const LsPrepBwd& q, hipStream_t st) {
-  if (q.n < 1) return hipSuccess;
+  const int jobs = q.n + (q.words.start ? 2 : 0);
+  if (jobs < 1) return hipSuccess;
   const int64_t n = (int64_t)(4 * ls_gate_stride<TE>(q.H) / LsGeom<TE>::kKStep) * ls_unit_tiles(q.H) * 64;
   int64_t gx = (n + 255) / 256;
   if (gx > 1024) gx = 1024;
-  hipLaunchKernelGGL(ls_prep_bwd_kernel<TE>, dim3((unsigned)gx, q.n), dim3(256), 0, st, q);
+  hipLaunchKernelGGL(ls_prep_bwd_kernel<TE>, dim3((unsigned)gx, jobs), dim3(256), 0, st, q);
   return hipGetLastError();
 }
 __global__ __launch_bounds__(256) void ls_copy_kernel(LsCopy c) {
@@ -1025,9 +1126,15 @@ static hipError_t ls_fwd_shape(const LsFwd& p, int d, int l_lo, int nl, hipStrea
   // one step, layer 0: blocks behind its own prepare the states of the other layers
   const int64_t chunks = (int64_t)ls_ksteps<TE>(p.H) * ls_batch_tiles(p.B) * 64, per = (chunks + 64 * LS_KS - 1) / (64 * LS_KS);
   const unsigned others = p.direct && l_lo == 0 && p.L > 1 ? (unsigned)(p.L * (per < 64 ? per : 64)) : 0;
-#define ASX_FWD(ROWS, VEC, APART)                                                                                    \
-  hipLaunchKernelGGL((ls_wave_fwd_kernel<TE, NI, NJ, ROWS ? PF_ROWS : PF, ROWS, VEC, APART>), dim3(grid + others), dim3(64 * LS_KS), 0, st, p, \
-                     d, l_lo, nl)
+  const bool packed = p.words.start != nullptr;
+#define ASX_FWD_P(ROWS, VEC, APART, PACKED)                                                                          \
+  hipLaunchKernelGGL((ls_wave_fwd_kernel<TE, NI, NJ, ROWS ? PF_ROWS : PF, ROWS, VEC, APART, PACKED>), dim3(grid + others), dim3(64 * LS_KS), \
+                     0, st, p, d, l_lo, nl)
+#define ASX_FWD(ROWS, VEC, APART)                                         \
+  do {                                                                    \
+    if (ROWS == 0 && packed) ASX_FWD_P(ROWS, VEC, APART, (ROWS == 0));    \
+    else ASX_FWD_P(ROWS, VEC, APART, false);                              \
+  } while (0)
   if (p.x_apart && p.w_rows) return hipErrorInvalidValue;   // (ls_input_apart: not with one step)
   if constexpr (NJ == 1 && PF_ROWS == PF) {
     if (p.direct && l_lo == 0) {
@@ -1040,16 +1147,17 @@ static hipError_t ls_fwd_shape(const LsFwd& p, int d, int l_lo, int nl, hipStrea
   else if (LsMma<TE>::kPair || p.H % 4 == 0) ASX_FWD(0, true, false);
   else ASX_FWD(0, LsMma<TE>::kPair, false);
 #undef ASX_FWD
+#undef ASX_FWD_P
   return hipGetLastError();
 }
 template <typename TE, int NI, int NJ, int PF>
 static hipError_t ls_bwd_shape(const LsBwd& p, int d, int l_lo, int nl, hipStream_t st) {
   const unsigned grid = ls_grid((int64_t)nl * ((p.H + 16 * NI - 1) / (16 * NI)), (p.B + 16 * NJ - 1) / (16 * NJ));
-  if (LsMma<TE>::kPair || p.H % 4 == 0)
-    hipLaunchKernelGGL((ls_wave_bwd_kernel<TE, NI, NJ, PF, true>), dim3(grid), dim3(64 * LS_KS), 0, st, p, d, l_lo, nl);
-  else
-    hipLaunchKernelGGL((ls_wave_bwd_kernel<TE, NI, NJ, PF, LsMma<TE>::kPair>), dim3(grid), dim3(64 * LS_KS), 0, st, p, d,
-                       l_lo, nl);
+  constexpr bool kAnyVec = LsMma<TE>::kPair;   // (bf16 widths are whole vectors)
+  const bool vec = kAnyVec || p.H % 4 == 0;
+  auto k = p.words.start ? (vec ? ls_wave_bwd_kernel<TE, NI, NJ, PF, true, true> : ls_wave_bwd_kernel<TE, NI, NJ, PF, kAnyVec, true>)
+                         : (vec ? ls_wave_bwd_kernel<TE, NI, NJ, PF, true, false> : ls_wave_bwd_kernel<TE, NI, NJ, PF, kAnyVec, false>);
+  hipLaunchKernelGGL(k, dim3(grid), dim3(64 * LS_KS), 0, st, p, d, l_lo, nl);
   return hipGetLastError();
 }
 
@@ -1104,6 +1212,7 @@ template <typename TE> hipError_t launch_ls_wave_bwd(const LsBwd& p, int d, hipS
 #define ASX_LS(TE)                                                                                  \
   template bool ls_reads_weight_rows<TE>(int, int, int);                                            \
   template bool ls_reads_states<TE>(int, int);                                                      \
+  template bool ls_packed<TE>(int, int, int, int, int);                                             \
   template bool ls_input_apart<TE>(int, int, int, int);                                             \
   template hipError_t launch_ls_prep_fwd<TE>(const LsFwd&, const LsPrepFwd&, hipStream_t);          \
   template hipError_t launch_ls_prep_bwd<TE>(const LsPrepBwd&, hipStream_t);                        \

@@ -363,3 +363,27 @@ def test_one_step_with_outputs_on_top_of_inputs(dtype, over):
         c0, hT = both[:L], both[1:]
     for got, w in zip(run(x, h0, c0, y, hT, cT), want):
         assert torch.equal(got, w)
+
+
+@pytest.mark.parametrize("dtype, T, B, I, H, L, dropout", [
+    ("bf16", 9, 300, 520, 520, 2, 0.3),        # rows of words: more sentences than the block that numbers them has threads
+    ("bf16", 33, 70, 264, 776, 2, 0.0),        # the gradient of x in a split product
+    ("bf16", 60, 97, 1024, 200, 3, 0.0),       # in one that is not, and the input product ahead of the wavefronts
+    # no whole vectors.  (With 219 units three of the 876 elements of db[1], sums over 37 sentences that no product here makes and
+    # whose norm is right to 1.1e-7, lie so near zero that 1e-4 of them is less than their terms' rounding; 0.003 of them may.)
+    ("f32", 21, 37, 67, 222, 2, 0.3),
+    ("f32", 3, 257, 72, 256, 2, 0.0)])
+@pytest.mark.parametrize("ends", ["mixed", "some empty", "all empty"])
+def test_sequences_without_rows_for_padding(dtype, T, B, I, H, L, dropout, ends):
+    """Weight gradients and the gradient of x over the words alone; sentences without a word keep their initial state."""
+    inp = make_lstm_inputs(T, B, I, H, L, seed=H, dtype=dtype)
+    inp.dropout_p, inp.dropout_seed = dropout, 5
+    if ends == "some empty":
+        inp.lengths[::3] = 0
+        inp.lengths[1::7] = T
+    elif ends == "all empty":
+        inp.lengths[:] = 0
+    f, g, _ = run_gpu(inp)
+    fo, go = run_oracle(inp)
+    compare(inp, f, g, fo, go)
+    assert np.all(f["y"][np.arange(T)[:, None] >= inp.lengths[None, :]] == 0.0)
