@@ -144,7 +144,7 @@ hipError_t launch_gemm(const GemmArgs& g, bool in_bf16, GemmTile tile, hipStream
 // Products that do not depend on each other, in one launch where there is a kernel for the combination and its tiles (bf16:
 // kTile64, two of them also kTile128; fp32: 32 x 32), else one after the other; splits are combined afterwards.  sums: column
 // sums of dlogits beside {dW_out, dz}.
-constexpr int kMaxTogether = 3;
+constexpr int kMaxTogether = 4;
 struct DbReduce;
 hipError_t launch_gemm_together(const GemmArgs* g, const GemmTile* tile, int n, bool in_bf16, hipStream_t st,
                                 const DbReduce* sums = nullptr);

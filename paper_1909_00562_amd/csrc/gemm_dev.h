@@ -109,7 +109,8 @@ struct DirectLoader {
 // the 64 x 64 and 128 x 128 kernel (gemm_tile.hip); d as launch_gemm_bf16 has filled it in
 hipError_t launch_gemm_bf16_tile(const GemmDev& d, GemmTile tile, bool a_kc, bool b_kc, bool out_bf16, hipStream_t st);
 // Several products in one launch; hipErrorNotSupported where there is no kernel for the combination.  64 x 64 tiles: {both
-// strided, A contiguous with C_second}, {both strided, both contiguous}, the latter with another of both strided.  64 x 64 or
+// strided, A contiguous with C_second}, {both strided, both contiguous}, the latter with another of both strided,
+// two to four of both strided.  64 x 64 or
 // 128 x 128: {both strided, A contiguous}, sums beside them.
 struct TileForm {
   bool a_kc, b_kc, out_bf16;

@@ -301,6 +301,11 @@ static hipError_t launch_f32_together_with(const GemmArgs* g, const GemmDevF* d,
   using NT = F32Member<true, true, VEC>;
   const bool nn = g[1].a_kc && !g[1].b_kc, nt = g[1].a_kc && g[1].b_kc;
   if constexpr (VEC == VEC_LAST) {
+    bool tn = true;
+    for (int i = 1; i < n; ++i) tn = tn && !g[i].a_kc && !g[i].b_kc;
+    if (tn && n == 2) return launch_f32_members(g, d, sums, st, TN(), TN());
+    if (tn && n == 3) return launch_f32_members(g, d, sums, st, TN(), TN(), TN());
+    if (tn && n == 4) return launch_f32_members(g, d, sums, st, TN(), TN(), TN(), TN());
     if (n == 2 && nn) return launch_f32_members(g, d, sums, st, TN(), NN());
     if (n == 3 && nn && g[2].a_kc && !g[2].b_kc) return launch_f32_members(g, d, sums, st, TN(), NN(), NN());
   }
@@ -319,7 +324,7 @@ static hipError_t launch_gemm_f32_together(const GemmArgs* g, int n, const DbRed
     const hipError_t e = f32_describe(g[i], d[i], avec, bvec);
     if (e != hipSuccess) return e;
     if (g[i].copy_pos || !gemm_f32_small(g[i].M, g[i].N, g[i].batch * g[i].splits)) return hipErrorNotSupported;
-    vec = vec && bvec && (avec || i == 2);   // (source positions, the rows of the last A, are rarely a multiple of four)
+    vec = vec && bvec && (avec || (i == 2 && n == 3));   // (source positions, the rows of the last A, are rarely a multiple of four)
     vec_last = vec_last && avec && bvec;
   }
   if (vec_last) return launch_f32_together_with<true, true>(g, d, n, sums, st);

@@ -621,8 +621,15 @@ static hipError_t launch_together_with(const GemmDev* d, const TileForm* f, int 
     if (n == 2) return launch_members(false, st, tn, nt);
     TN last;
     last.set(d[2], f[2].out_bf16);
-    if (!f[2].a_kc && !f[2].b_kc) return launch_members(false, st, tn, nt, last);
+    if (n == 3 && !f[2].a_kc && !f[2].b_kc) return launch_members(false, st, tn, nt, last);
   }
+  for (int i = 1; i < n; ++i)
+    if (f[i].a_kc || f[i].b_kc) return hipErrorNotSupported;
+  TN more[kMaxTogether - 1];
+  for (int i = 1; i < n; ++i) more[i - 1].set(d[i], f[i].out_bf16);
+  if (n == 2) return launch_members(false, st, tn, more[0]);
+  if (n == 3) return launch_members(false, st, tn, more[0], more[1]);
+  if (n == 4) return launch_members(false, st, tn, more[0], more[1], more[2]);
   return hipErrorNotSupported;
 }
 hipError_t launch_gemm_bf16_tiles_together(const GemmDev* d, const TileForm* f, int n, const DbReduce* sums, hipStream_t st) {
