@@ -55,6 +55,14 @@ hipError_t launch_gather_rows(const int32_t* rows, const int32_t* n_act, int N, 
 hipError_t launch_scatter_rows(const int32_t* row_pos, int N, const void* src0, void* dst0, const void* src1,
                                void* dst1, int64_t bytes, hipStream_t st);
 
+// The same two for fp32 storage, S <= 128.
+bool attn_f32_fused_supported(int S);
+hipError_t launch_attn_f32_fwd(const float* q, const float* q_lo, const float* h_enc, const int32_t* src_len, int B, int T, int S,
+                               int H, float* alpha32, float* alphaE, float* alphaE_lo, int64_t ldS, float* ctx, float* ctx_lo,
+                               uint8_t* attn_mask, const RowList& list, int32_t* zero, hipStream_t st);
+hipError_t launch_attn_f32_bwd(const float* dC, const float* dC_lo, const float* h_enc, const int32_t* src_len, int B, int T, int S,
+                               int H, const float* alpha32, float* dscore, float* dscore_lo, int64_t ldS, float* dQ, hipStream_t st);
+
 // Eq. 5-6 per row n of logits [N,ldV]: lse, loss, argmax, target mask.
 hipError_t launch_xent_stats(const void* logits, int64_t ldV, bool e_bf16, int N, int V,
                              const int32_t* targets, int pad_id, float* lse, float* tok_loss_ws,

@@ -350,3 +350,20 @@ def test_statistics_from_the_projection(N, H, V, skip):
         want_sum = want[live].sum()
     assert bool((loss[~live] == 0).all()) and int(db.n_tok.item()) == int(live.sum())
     assert abs(float(db.loss_sum.item()) - float(want_sum)) <= 1.6e-5 * max(1, int(live.sum())) + 2 ** -23 * abs(float(want_sum))
+
+
+@pytest.mark.parametrize("skip", [False, True])
+@pytest.mark.parametrize("shape", [(1, 1, 3, 4, 67),          # one step, one source position, a quarter of a reduction step
+                                   (16, 16, 4, 64, 131),      # whole tiles; a reduction step per wave
+                                   (17, 17, 3, 260, 131),     # one past them; a remainder of columns
+                                   (5, 33, 6, 67, 131),       # no whole vectors
+                                   (35, 64, 2, 141, 131),
+                                   (3, 65, 5, 36, 131),
+                                   (18, 128, 2, 1028, 131),   # the longest source, several sweeps over the columns
+                                   (4, 129, 3, 36, 131)])     # one more: separate launches
+def test_f32_fused_attention_at_tile_edges(shape, skip):
+    """fp32, S <= 128: 16 decoder steps and 16 to 128 source positions per workgroup; one sentence of length 0."""
+    T, S, B, H, V = shape
+    inp = make_custom(T=T, S=S, B=B, H=H, V=V, seed=S + H, dtype="f32", min_len=1, pad_prob=0.1, w=0.05 if H > 1000 else 0.1)
+    inp.src_len[B // 2] = 0
+    _parity(inp, skip)
