@@ -451,7 +451,10 @@ __device__ __forceinline__ void gemm_bf16_tile_block(GemmDev p, int out_bf16, in
           } else {
             float* C = (second ? p.C_second : reinterpret_cast<float*>(p.C)) + ci;
             if (p.accumulate) v[u] += *reinterpret_cast<const f32x4_t*>(C);
-            *reinterpret_cast<f32x4_t*>(C) = v[u];
+            // (weight gradients, which nothing here reads again, past the caches: they push out what the blocks share.  One step of
+            // 128 x 1024, 32000 words, dW_out 131 MB: 178.4 -> 165.4 us)
+            if (!AKC && !BKC) __builtin_nontemporal_store(v[u], reinterpret_cast<f32x4_t*>(C));
+            else *reinterpret_cast<f32x4_t*>(C) = v[u];
           }
         }
       }
