@@ -166,8 +166,6 @@ __device__ __forceinline__ void gs_finish_ragged(const GemmDev& p, int out_bf16,
   }
 }
 
-// Block `id` of a launch's tiles of all batches and splits; dynamic LDS: NST * 2 * 32 TW * ROWB bytes.  (p by value: by reference the
-// instances take five registers more and 182 x 51130 x 128 18.7 us for 17.2.)
 // Softmax statistics of a staged row's BM columns by four lanes, which take every fourth vector: few steps across lanes, which
 // is what the time goes to (16 and 32 lanes with a vector each, 128 x 32000 x 1024: 17.9 -> 22.4 us).
 template <int CTRL> __device__ __forceinline__ float gs_quad(float v) {
@@ -215,6 +213,8 @@ template <int BM> __device__ __forceinline__ TileStat gs_stats(const float* row,
   return TileStat{m, s, idx, 0};
 }
 
+// Block `id` of a launch's tiles of all batches and splits; dynamic LDS: NST * 2 * 32 TW * ROWB bytes.  (p by value: by reference the
+// instances take five registers more and 182 x 51130 x 128 18.7 us for 17.2.)
 template <int TW, bool AKC, bool BKC, int NST, bool LACED, TileExtra EXTRA>
 __device__ __forceinline__ void gemm_bf16_tile_block(GemmDev p, int out_bf16, int id) {
   extern __shared__ __align__(1024) unsigned char smem[];
