@@ -41,6 +41,19 @@ as_status set_error(as_status code, const char* fmt, ...) {
 }
 }  // namespace asx
 
+namespace asx {
+// bf16: the statistics of the softmax from the projection itself, where its tiles are small: the passes over the logits and over
+// the losses become one over the tiles' statistics.  us, projection + statistics + loss / projection + this: 64 x 64 tiles, 16 x
+// 16000 x 512 14.5 + a launch / 11.8, 179 x 2054 x 128 12.4 / 11.5; 128 x 128, a block per compute unit, 128 x 32000 x 1024 29.5 /
+// 26.9; several blocks per unit, 182 x 51130 x 128 30.9 / 30.3, and slower as a call, so not there.  They come from whole
+// vectors of the logits alone: rows past the reach of those stay with the passes.
+bool projection_leaves_stats(int N, int V, int H) {
+  const GemmTile tile = gemm_plan(N, V, H, 1, true, false).tile;
+  if (N > 1024 || !gemm_vector_reach(V, (V + 7) / 8 * 8)) return false;
+  return tile == kTile64 || (tile == kTile128 && (int64_t)((N + 127) / 128) * ((V + 127) / 128) <= 256);
+}
+}  // namespace asx
+
 namespace {
 using namespace asx;
 
@@ -247,16 +260,11 @@ Layout make_layout(const as_shape* s) {
   }
   if (off < end) off = end;
   L.total = off;
-  // The statistics of the softmax from the projection itself, where its tiles are small: the passes over the logits and over
-  // the losses become one over the tiles' statistics.  us, projection + statistics + loss / projection + this: 64 x 64 tiles, 16 x
-  // 16000 x 512 14.5 + a launch / 11.8, 179 x 2054 x 128 12.4 / 11.5; 128 x 128, a block per compute unit, 128 x 32000 x 1024 29.5 /
-  // 26.9; several blocks per unit, 182 x 51130 x 128 30.9 / 30.3, and slower as a call, so not there.  Their place: that of the
-  // backward pass and of the partial sums of h_c, if it has the room.
+  // Their place: that of the backward pass and of the partial sums of h_c, if it has the room.
   const int edge = L.p_logits.tile == kTile64 ? 64 : 128;
   L.stat_parts = (V + edge - 1) / edge;
   L.stats = area;
-  L.tile_stats = bf && N <= 1024 &&
-                 (L.p_logits.tile == kTile64 || (L.p_logits.tile == kTile128 && (int64_t)((N + 127) / 128) * L.stat_parts <= 256)) &&
+  L.tile_stats = bf && projection_leaves_stats(N, V, H) &&
                  area + (size_t)N * L.stat_parts * sizeof(TileStat) <= L.total &&
                  (L.total > kStaticScratchBytes || L.total + kAlign <= kStaticScratchBytes);
   L.ticket = L.total;

@@ -96,6 +96,9 @@ struct alignas(16) TileStat {
   int idx, unused;
 };
 
+// bf16 kernels: whether rows of N columns, ld apart, are in reach of the vector write-out (32-bit byte offsets inside a 128-row
+// window); other results are written element by element, and statistics are not made of them
+inline bool gemm_vector_reach(int N, int64_t ld) { return N < (1 << 21) && ld < (1 << 21); }
 
 // Blocks of a persistent launch (one per compute unit, a multiple of the 8 XCDs).
 inline int pp_grid_blocks(int work_total) { return work_total < 256 ? (work_total + 7) / 8 * 8 : 256; }

@@ -1065,7 +1065,7 @@ static hipError_t gemm_describe(const GemmArgs& g, GemmTile tile, GemmDev& d) {
   d.vec_ok = ((g.ldc & 3) == 0) && ((g.sC & 3) == 0) && al16(g.C) && apart_al16 && (!g.C_lo || al16(g.C_lo)) &&
              (!g.C_dact || al16(g.C_dact)) && al16(g.C_copy) && (!g.gate || (al16(g.gate) && (g.ldg & 3) == 0)) &&
              (d.n_out & 3) == 0 &&                                        // a 4-column group is all in or all out
-             g.ldc < (1 << 21) && g.ldg < (1 << 21) && g.N < (1 << 21);   // 32-bit byte offsets inside a 128-row window
+             gemm_vector_reach(g.N, g.ldc) && gemm_vector_reach(g.N, g.ldg);
   if ((g.C_second || g.row_stats) && !d.vec_ok) return hipErrorInvalidValue;
   const int bm = tile == kTile256 ? 256 : tile == kTile128 ? 128 : 64;
   d.tiles_m = (g.M + bm - 1) / bm;

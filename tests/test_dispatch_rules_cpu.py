@@ -111,6 +111,15 @@ def test_bf16_tile_where_the_device_counts_the_size(M, N, K, plan):
     assert _plan(M, N, K, 1, bf16=True, counted=True) == plan
 
 
+@pytest.mark.parametrize("N, V, H, leaves", [
+    (16, 16000, 512, True), (179, 2054, 128, True), (128, 32000, 1024, True), (1024, 2003, 64, True), (1025, 2003, 64, False),
+    (182, 51130, 128, False),
+    (16, 2097144, 1280, True), (16, 2097145, 1280, False),     # rows of 2^21 and more: past the vector write-out
+    (16, 2200000, 640, False), (1, 4000000, 512, False), (64, 4000000, 1024, False)])
+def test_softmax_statistics_from_the_projection_where_its_kernels_make_them(N, V, H, leaves):
+    assert _rule("_ZN3asx23projection_leaves_statsEiii", ctypes.c_bool, *[I32] * 3)(N, V, H) == leaves
+
+
 @pytest.mark.parametrize("edge, form, M, N, laced", [
     (128, "TN", 1024, 1024, True), (128, "NN", 2257, 1000, True), (64, "NT", 128, 1024, True), (64, "TN", 1024, 1024, True),
     (128, "NT", 6400, 1024, True), (128, "NT", 600, 8000, True), (128, "NN", 6400, 1024, True), (64, "NT", 6400, 1024, True),

@@ -352,6 +352,57 @@ def test_statistics_from_the_projection(N, H, V, skip):
     assert abs(float(db.loss_sum.item()) - float(want_sum)) <= 1.6e-5 * max(1, int(live.sum())) + 2 ** -23 * abs(float(want_sum))
 
 
+@pytest.mark.parametrize("step", [False, True])
+def test_more_words_than_whole_vectors_reach(step):
+    """2200000 words, 640 units: a projection in 64 x 64 tiles that writes its logits element by element.  Logits against double
+    products at some words, the last among them, as rounded to bf16; lse against that of the logits as stored.  Bound of lse: a
+    thread adds at most V / 256 terms one after the other, 8594 * 2^-24 = 5.2e-4 relative, and then a few hundred sums and
+    roundings of single terms, below 3e-5."""
+    import torch
+    import paper_1909_00562_amd as lib
+    from paper_1909_00562_amd import binding as bd
+    N, S, H, V, pad = 16, 5, 640, 2200000, 0
+    g = torch.Generator(device="cuda").manual_seed(21)
+    new = lambda *s: torch.rand(*s, generator=g, device="cuda").mul_(0.2).sub_(0.1).bfloat16()
+    out = lambda *s, dtype=torch.float32: torch.zeros(*s, dtype=dtype, device="cuda")
+    h, he, W_a, W_c, W_out, b_out = new(N, H), new(S, N, H), new(H, H), new(H, 2 * H), new(V, H), new(V)
+    src_len = torch.full((N,), S, dtype=torch.int32, device="cuda")
+    targets = torch.randint(1, V, (N,), generator=g, device="cuda", dtype=torch.int32)
+    targets[0], targets[1] = V - 1, pad
+    loss_sum, n_tok, tok_loss, argmax = out(1), out(1, dtype=torch.int32), out(N), out(N, dtype=torch.int32)
+    attn_mask, tgt_mask = out(N, S, dtype=torch.uint8), out(N, dtype=torch.uint8)
+    shape = lib.AsShape(1, S, N, H, V, pad, lib.AS_BF16, 1.0)
+    n = (lib.attn_softmax_step_workspace_bytes if step else lib.attn_softmax_workspace_bytes)(shape)
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    if step:
+        lib.attn_softmax_step_prepare(shape, he, W_a, ws, n)
+        lib.attn_softmax_step_fwd(shape, h, he, src_len, W_c, W_out, b_out, targets, loss_sum, n_tok, tok_loss, argmax, ws, n)
+    else:
+        lib.attn_softmax_fwd(shape, h, he, src_len, W_a, W_c, W_out, b_out, targets, loss_sum, n_tok, tok_loss, argmax,
+                             attn_mask, tgt_mask, ws, n)
+    torch.cuda.synchronize()
+
+    def view(which):
+        addr, nbytes, ld = lib.attn_softmax_view(shape, ws, which)
+        return ws[addr - ws.data_ptr():addr - ws.data_ptr() + nbytes], ld
+
+    raw, ld = view(bd.AS_VIEW_LOGITS)
+    logits = raw.view(torch.bfloat16).view(N, ld)[:, :V]
+    h_c = view(bd.AS_VIEW_HC)[0].view(torch.bfloat16).view(N, H)
+    words = torch.cat([torch.arange(130, device="cuda"), torch.arange(V - 130, V, device="cuda"),
+                       torch.randint(0, V, (4096,), generator=g, device="cuda")])
+    want = h_c.double() @ W_out[words].double().T + b_out[words].double()
+    assert torch.allclose(logits[:, words].double(), want, rtol=2 ** -8, atol=1e-5)
+    x = logits.double()
+    lse = torch.logsumexp(x, 1)
+    assert torch.allclose(view(bd.AS_VIEW_LSE)[0].view(torch.float32).double(), lse, rtol=0, atol=6e-4)
+    assert torch.equal(argmax.long(), torch.argmax((x == x.max(1, keepdim=True).values).int(), 1))
+    live = targets != pad
+    loss = (lse - x[torch.arange(N, device="cuda"), targets.long()])[live]
+    assert torch.allclose(tok_loss[live].double(), loss, rtol=0, atol=6e-4) and float(tok_loss[1]) == 0.0
+    assert int(n_tok.item()) == N - 1 and abs(float(loss_sum.item()) - float(loss.sum())) <= 6e-4 * N
+
+
 @pytest.mark.parametrize("skip", [False, True])
 @pytest.mark.parametrize("shape", [(1, 1, 3, 4, 67),          # one step, one source position, a quarter of a reduction step
                                    (16, 16, 4, 64, 131),      # whole tiles; a reduction step per wave
