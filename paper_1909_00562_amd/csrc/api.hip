@@ -52,6 +52,14 @@ bool projection_leaves_stats(int N, int V, int H) {
   if (N > 1024 || !gemm_vector_reach(V, (V + 7) / 8 * 8)) return false;
   return tile == kTile64 || (tile == kTile128 && (int64_t)((N + 127) / 128) * ((V + 127) / 128) <= 256);
 }
+// The gradients of weights past the caches, in products of one launch: where dW_out is larger than the L2s together (32 MiB) they
+// push out the operands that the blocks share, and most of them are gone from there anyway when they are read.  Who reads it next decides what that is worth, us, plain / past: 128 x 1024,
+// 32000 words (131 MB) the step alone 178.4 / 165.0; the backward pass of one LSTM step behind it and every gradient added
+// to a running sum 532.8 / 521.6, one layer 365.6 / 356.1; the backward pass of an LSTM layer over 50 steps and Adam 1049.5 /
+// 1040.5; but Adam alone at once behind it 354.0 / 363.1.  64 x 512, 32000 words (66 MB), with the sums 239.3 / 236.4.  Below the
+// line 1920 x 512, 16000 words (33 MB), alone 221.7 / 219.5, with Adam 276.2 / 279.4, with an LSTM layer and Adam 573.8 / 575.9: plain there,
+// and d_h_enc, which the backward pass of the encoder reads at once, everywhere.
+bool gradients_past_caches(int V, int H) { return (int64_t)V * H * (int64_t)sizeof(float) > (int64_t)32 << 20; }
 }  // namespace asx
 
 namespace {
@@ -597,6 +605,7 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
     g[0].M = V; g[0].N = H;
     g[0].K_dev = n_act;     // compacted: the reduction runs over the non-pad rows only
     g[0].C = dW_out; g[0].ldc = H; g[0].c_bf16 = false;
+    g[0].past_caches = gradients_past_caches(V, H);
     g[0].splits = L.p_dwout.splits; g[0].partial = partial;
     // dz = (dlogits W_out) * (1 - h_c^2), the factor saved by the forward pass
     g[1].seg(w + L.logits, L.ldV, 0, W_out, H, 0, V);
@@ -629,6 +638,7 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
     g[0].a_kc = false; g[0].b_kc = false;
     g[0].M = H; g[0].N = H; g[0].batch = 2;
     g[0].C = dW_c; g[0].ldc = 2 * H; g[0].sC = H; g[0].c_bf16 = false;
+    g[0].past_caches = gradients_past_caches(V, H);
     g[0].splits = L.p_dwc.splits; g[0].partial = partial;
     if (L.dch_pair) {   // the next two as one product: half W_c's columns each
       g[1].seg(w + L.dz, H, 0, wc, 2 * H, H, H);
@@ -705,6 +715,7 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
     g[0].a_kc = false; g[0].b_kc = false;
     g[0].M = H; g[0].N = H;
     g[0].C = dW_a; g[0].ldc = H; g[0].c_bf16 = false;
+    g[0].past_caches = gradients_past_caches(V, H);
     g[0].splits = L.p_dwa.splits; g[0].partial = partial;
   }
   {  // d_h_dec += dQ W_a^T

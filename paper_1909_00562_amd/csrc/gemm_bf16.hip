@@ -1015,6 +1015,7 @@ static hipError_t gemm_describe(const GemmArgs& g, GemmTile tile, GemmDev& d) {
   d.sB = g.sB[0];
   d.K = g.K[0];
   d.nseg = g.nseg;
+  d.past_caches = g.past_caches;
   d.M = g.M;
   d.N = g.N;
   d.C = g.C;

@@ -15,6 +15,7 @@ struct GemmDev {
   int K, nseg;                // 0.2 us a product of the smallest sizes)
   int M, N;
   int n_out;   // columns the vector write-out covers: N, or N rounded up to 4 where C's rows have padding
+  int past_caches;
   void* C;
   uint16_t* C_lo;
   float* C_dact;

@@ -78,7 +78,7 @@ template <bool KC, int COLS> __device__ __forceinline__ bf16x8_t gs_frag(const u
 }
 
 // What sets an instance of a tile kernel apart (with the choices made in the kernel its other products were 1 to 8 % slower)
-enum TileExtra { kNoExtra, kSecond, kCopy, kStats };   // C_second; copy_pos; row_stats
+enum TileExtra { kNoExtra, kSecond, kCopy, kStats, kPast };   // C_second; copy_pos; row_stats; past_caches
 
 // Epilogue of four consecutive columns of a row, in whole vectors
 template <bool COPY>
@@ -451,9 +451,7 @@ __device__ __forceinline__ void gemm_bf16_tile_block(GemmDev p, int out_bf16, in
           } else {
             float* C = (second ? p.C_second : reinterpret_cast<float*>(p.C)) + ci;
             if (p.accumulate) v[u] += *reinterpret_cast<const f32x4_t*>(C);
-            // (weight gradients, which nothing here reads again, past the caches: they push out what the blocks share.  One step of
-            // 128 x 1024, 32000 words, dW_out 131 MB: 178.4 -> 165.4 us)
-            if (!AKC && !BKC) __builtin_nontemporal_store(v[u], reinterpret_cast<f32x4_t*>(C));
+            if (EXTRA == kPast) __builtin_nontemporal_store(v[u], reinterpret_cast<f32x4_t*>(C));
             else *reinterpret_cast<f32x4_t*>(C) = v[u];
           }
         }
@@ -591,6 +589,9 @@ struct SumsMember {
 using MemberTN = TileMember<2, false, false, 4, false>;
 using MemberTNLaced = TileMember<2, false, false, 4, true>;
 using MemberTN128 = TileMember<4, false, false, 2, false>;
+using MemberTNPast = TileMember<2, false, false, 4, false, kPast>;
+using MemberTNLacedPast = TileMember<2, false, false, 4, true, kPast>;
+using MemberTN128Past = TileMember<4, false, false, 2, false, kPast>;
 using MemberNN = TileMember<2, true, false, 4, true>;
 using MemberNN128 = TileMember<4, true, false, 2, true>;
 using MemberNNSecond = TileMember<2, true, false, 4, true, kSecond>;
@@ -599,8 +600,11 @@ using MemberNT = TileMember<2, true, true, 4, true>;
 static int tile_ktiles(const GemmDev& d) {   // reduction tiles of a block
   return (d.nseg * ((d.K + BK - 1) / BK) + d.splits - 1) / d.splits;
 }
-template <typename TN, typename NN>
+template <typename TN, typename NN, typename TNPast>
 static hipError_t launch_with_sums(const GemmDev* d, const TileForm* f, const DbReduce& sums, hipStream_t st) {
+  if constexpr (!std::is_same<TN, TNPast>::value) {
+    if (d[0].past_caches) return launch_with_sums<TNPast, NN, TNPast>(d, f, sums, st);
+  }
   TN tn;
   NN nn;
   SumsMember s;
@@ -609,9 +613,9 @@ static hipError_t launch_with_sums(const GemmDev* d, const TileForm* f, const Db
   s.set(sums);
   return launch_members(false, st, nn, tn, s);
 }
-template <typename TN>
+template <typename First, typename TN>
 static hipError_t launch_together_with(const GemmDev* d, const TileForm* f, int n, hipStream_t st) {
-  TN tn;
+  First tn;
   tn.set(d[0], f[0].out_bf16);
   if (n == 2 && f[1].a_kc && !f[1].b_kc && d[1].C_second) {
     MemberNNSecond nn;
@@ -639,17 +643,19 @@ hipError_t launch_gemm_bf16_tiles_together(const GemmDev* d, const TileForm* f, 
   if (n < 2 || f[0].a_kc || f[0].b_kc) return hipErrorNotSupported;
   if (sums) {
     if (n != 2 || !f[1].a_kc || f[1].b_kc || d[1].C_second) return hipErrorNotSupported;
-    if (f[1].tile == kTile128) return f[0].tile == kTile128 ? launch_with_sums<MemberTN128, MemberNN128>(d, f, *sums, st) : hipErrorNotSupported;
-    return f[0].tile == kTile128 ? launch_with_sums<MemberTN128, MemberNN>(d, f, *sums, st)
-                                 : launch_with_sums<MemberTN, MemberNN>(d, f, *sums, st);
+    if (f[1].tile == kTile128) return f[0].tile == kTile128 ? launch_with_sums<MemberTN128, MemberNN128, MemberTN128Past>(d, f, *sums, st) : hipErrorNotSupported;
+    return f[0].tile == kTile128 ? launch_with_sums<MemberTN128, MemberNN, MemberTN128Past>(d, f, *sums, st)
+                                 : launch_with_sums<MemberTN, MemberNN, MemberTNPast>(d, f, *sums, st);
   }
   int64_t blocks = 0;
   for (int i = 0; i < n; ++i) {
     if (f[i].tile != kTile64) return hipErrorNotSupported;
     blocks += (int64_t)d[i].tiles_m * d[i].tiles_n * d[i].nz;
   }
-  return gemm_tile_laced(false, blocks) ? launch_together_with<MemberTNLaced>(d, f, n, st)
-                                        : launch_together_with<MemberTN>(d, f, n, st);
+  if (!gemm_tile_laced(false, blocks))
+    return d[0].past_caches ? launch_together_with<MemberTNPast, MemberTN>(d, f, n, st) : launch_together_with<MemberTN, MemberTN>(d, f, n, st);
+  return d[0].past_caches ? launch_together_with<MemberTNLacedPast, MemberTNLaced>(d, f, n, st)
+                          : launch_together_with<MemberTNLaced, MemberTNLaced>(d, f, n, st);
 }
 
 // ---- few rows ----------------------------------------------------------------------

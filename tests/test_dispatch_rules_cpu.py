@@ -120,6 +120,12 @@ def test_softmax_statistics_from_the_projection_where_its_kernels_make_them(N, V
     assert _rule("_ZN3asx23projection_leaves_statsEiii", ctypes.c_bool, *[I32] * 3)(N, V, H) == leaves
 
 
+@pytest.mark.parametrize("V, H, past", [(32000, 1024, True), (32000, 512, True), (131073, 64, True), (131072, 64, False),
+                                        (16000, 512, False), (1000, 64, False)])
+def test_gradients_past_the_caches_where_dw_out_is_larger_than_they_are(V, H, past):
+    assert _rule("_ZN3asx21gradients_past_cachesEii", ctypes.c_bool, I32, I32)(V, H) == past
+
+
 @pytest.mark.parametrize("edge, form, M, N, laced", [
     (128, "TN", 1024, 1024, True), (128, "NN", 2257, 1000, True), (64, "NT", 128, 1024, True), (64, "TN", 1024, 1024, True),
     (128, "NT", 6400, 1024, True), (128, "NT", 600, 8000, True), (128, "NN", 6400, 1024, True), (64, "NT", 6400, 1024, True),

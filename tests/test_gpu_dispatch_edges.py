@@ -293,6 +293,14 @@ def test_bf16_products_of_a_pass_in_one_launch(shape):
     _parity(make_custom(T=T, S=S, B=B, H=H, V=V, seed=V + H, dtype="bf16", min_len=1, pad_prob=0.1))
 
 
+@pytest.mark.parametrize("shape", [(1, 7, 20, 64, 131101), (3, 7, 100, 136, 70003), (9, 7, 100, 136, 70003)])
+def test_bf16_gradients_past_the_caches(shape):
+    """dW_out of more than 32 MiB in 64 x 64 tiles with dz, in 128 x 128 with dz in either; dW_c and dW_a of the same calls,
+    in launches of up to 256 blocks and of more, d_h_enc beside the latter."""
+    T, S, B, H, V = shape
+    _parity(make_custom(T=T, S=S, B=B, H=H, V=V, seed=V + H, dtype="bf16", min_len=1, pad_prob=0.1))
+
+
 @pytest.mark.parametrize("skip", [False, True])
 @pytest.mark.parametrize("shape", [(3, 8, 5, 36, 517),         # whole vectors in every product; tiles of a few rows
                                    (5, 7, 6, 68, 517),         # but in the source positions
