@@ -252,7 +252,6 @@ __device__ __forceinline__ void ls_prep_state(const LsFwd& p, int l, int64_t fir
       }
 #pragma unroll
       for (int v = 0; v < V / 4; ++v) {
-        if (p.words.start && p.cT) ls_st4<true>(p.cT + idx + 4 * v, c[v], 4);   // (stays where a sentence has no words)
         ls_st4<true>(p.hf + idx + 4 * v, h[v], 4);
         ls_st4<true>(cs + row + 4 * v, c[v], 4);
         ls_st4<true>(hE + row + 4 * v, h[v], 4);
@@ -271,7 +270,6 @@ __device__ __forceinline__ void ls_prep_state(const LsFwd& p, int l, int64_t fir
       if (in) {
         const float c = p.c0 ? p.c0[idx] : 0.f;
         p.hf[idx] = h;
-        if (p.words.start && p.cT) p.cT[idx] = c;
         cs[idx - (int64_t)l * BH] = c;
         st_elem<TE>(hE, idx - (int64_t)l * BH, h);
       }
@@ -567,6 +565,7 @@ __global__ __launch_bounds__(64 * LS_KS) void ls_wave_fwd_kernel(LsFwd p, int d,
       len[k] = len[k] < 0 ? 0 : (len[k] > p.T ? p.T : len[k]);
       if (t >= len[k]) {   // a padded step leaves everything as it is: no product and no cell reads this sentence's columns again
         if (l + 1 == p.L) ls_st4<VEC>(reinterpret_cast<TE*>(p.y) + (int64_t)t * BH + idx, f32x4_t{0.f, 0.f, 0.f, 0.f}, n);
+        if (len[k] == 0 && t == 0 && p.cT) ls_st4<VEC>(p.cT + l * BH + idx, cp[k], n);   // (not by the preparation, which reads c0)
         continue;
       }
     }

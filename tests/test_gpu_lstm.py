@@ -365,6 +365,41 @@ def test_one_step_with_outputs_on_top_of_inputs(dtype, over):
         assert torch.equal(got, w)
 
 
+@pytest.mark.parametrize("dtype, T, B, I, H, L", [("bf16", 9, 300, 520, 520, 2), ("f32", 3, 257, 72, 256, 2), ("f32", 9, 64, 67, 222, 2),
+                                                  ("bf16", 3, 37, 24, 72, 3)])     # the last two: rows per position
+@pytest.mark.parametrize("over", ["cT on c0", "cT past c0", "cT before c0", "cT past h0"])
+def test_sequences_with_final_cells_on_top_of_initial_states(dtype, T, B, I, H, L, over):
+    """cT anywhere over h0 and c0 gives the bits it gives in a buffer of its own; sentences without words among the others."""
+    import torch
+    import paper_1909_00562_amd as lib
+    tdt, code = (torch.bfloat16, lib.AS_BF16) if dtype == "bf16" else (torch.float32, lib.AS_F32)
+    g = torch.Generator(device="cuda").manual_seed(6)
+    new = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    W_ih = [(new(4 * H, I if l == 0 else H) * 0.1).to(tdt) for l in range(L)]
+    W_hh, b = [(new(4 * H, H) * 0.1).to(tdt) for _ in range(L)], [new(4 * H).to(tdt) for _ in range(L)]
+    x, states = new(T, B, I).to(tdt), new(2, L, B, H)
+    lengths = torch.randint(0, T + 1, (B,), generator=g, device="cuda", dtype=torch.int32)
+    lengths[::5] = 0
+    s = lib.LsShape(T, B, I, H, L, code, 0.0, 0)
+    n = lib.lstm_stack_workspace_bytes(s)
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    y, hT = torch.empty(T, B, H, dtype=tdt, device="cuda"), torch.empty(L, B, H, device="cuda")
+
+    def run(h0, c0, cT):
+        lib.lstm_stack_fwd(s, x, lengths, W_ih, W_hh, b, h0, c0, y, hT, cT, ws, n)
+        torch.cuda.synchronize()
+        return [v.clone() for v in (y, hT, cT)]
+
+    want = run(states[0], states[1], torch.empty(L, B, H, device="cuda"))
+    block = torch.empty(L + 1, B, H, device="cuda")
+    first = over in ("cT before c0", "cT on c0")
+    block[1 if first else 0:][:L] = states[0] if over == "cT past h0" else states[1]
+    given, cT = block[1 if first else 0:][:L], block[1 if over == "cT on c0" or not first else 0:][:L]
+    got = run(given, states[1], cT) if over == "cT past h0" else run(states[0], given, cT)
+    for v, w in zip(got, want):
+        assert torch.equal(v, w)
+
+
 @pytest.mark.parametrize("dtype, T, B, I, H, L, dropout", [
     ("bf16", 9, 300, 520, 520, 2, 0.3),        # rows of words: more sentences than the block that numbers them has threads
     ("bf16", 33, 70, 264, 776, 2, 0.0),        # the gradient of x in a split product
