@@ -1051,14 +1051,24 @@ template <typename TE> bool ls_input_apart(int T, int I, int H, int L) {
 }
 
 // Rows of words alone shorten the products over all steps by the share of padding (30 % where lengths are even over 0.4 T .. T, half
-// over 1 .. T) and save a padded step its stores; the rows of x and of the initial states and the way back of dx cost 4 to 10 us.  So
-// where the weight gradients have enough to do.  Forward and backward, us, a row per position / per word: 4 x 1024 units, 50 x 128
-// 3236 / 3117, fp32 2 x 512, 30 x 64 1340 / 1260; fp32 288 units, 8 x 17, 9e7 multiplications 201.7 / 200.6 and 320 units, 18 x 6,
-// 9e7 405 / 411; bf16 2 x 640, 14 x 16, 1e9 308 / 309, 2 x 128, 64 x 12, 2e8 820 / 826.  (Either way in instances of their own: a choice made in the
-// wavefront kernels cost each launch 0.2 us.  One block finds the rows of the sentences.)
+// over 1 .. T) and save a padded step its stores; the rows of x and of the initial states, the way back of dx and rows of a wavefront
+// that lie apart cost 4 to 60 us, the more words there are.  So where the weight gradients have enough to do, and enough per word.
+// Forward and backward, us, a row per position / per word with lengths over 1 .. T, then over 0.4 T .. T; multiplications of the weight
+// gradients, of them per word:
+//   bf16  64 x 192, 64 -> 2 x 128      3e9, 2.3e5   896 / 962      891 / 960      60 x 128, 256 -> 2 x 256   8e9, 1.0e6    952 / 962    945 / 965
+//         60 x 64, 128 -> 4 x 256      7e9, 2.0e6   992 / 999      987 / 998      64 x 192, 256 -> 4 x 256   3e10, 2.1e6   1473 / 1411  1467 / 1439
+//         32 x 64, 512 -> 512          4e9, 2.1e6   506 / 504      503 / 506      32 x 128, 512 -> 512       9e9, 2.1e6    565 / 558    562 / 563
+//         50 x 32, 512 -> 4 x 512      1e10, 8.4e6  982 / 979      978 / 986      60 x 64, 512 -> 2 x 512    2e10, 4.2e6   1120 / 1114  1114 / 1118
+//         64 x 12, 64 -> 1024          3e9, 4.5e6   1028 / 1029    1020 / 1023    64 x 48, 64 -> 1024        1e10, 4.5e6   1175 / 1167  1168 / 1168
+//         40 x 64, 512 -> 2 x 640      2e10, 6.4e6  908 / 892      905 / 904      50 x 64, 512 -> 4 x 1024   1e11, 3.1e7   2234 / 2116  2231 / 2164
+//   fp32  60 x 128, 64 -> 2 x 128      2e9, 2.3e5   1109 / 1096    1107 / 1133    30 x 64, 192 -> 192        6e8, 2.9e5    549 / 550    548 / 552
+//         24 x 16, 256 -> 384          4e8, 9.8e5   541 / 545      541 / 546      10 x 64, 256 -> 384        6e8, 9.8e5    287 / 281    286 / 284
+//         24 x 64, 512 -> 2 x 128      7e8, 4.6e5   543 / 539      542 / 548      24 x 48, 256 -> 2 x 384    2e9, 2.2e6    819 / 770    819 / 788
+// (Either way in instances of their own: a choice made in the wavefront kernels cost each launch 0.2 us.  One block finds the rows of
+// the sentences.)
 template <typename TE> bool ls_packed(int T, int B, int I, int H, int L) {
-  const double work = (double)T * B * 4.0 * H * (I + H + (L - 1) * 2.0 * H);   // multiplications of the weight gradients
-  return T > 1 && B <= 16384 && work >= (LsMma<TE>::kPair ? 8e9 : 4e8);
+  const double word = 4.0 * H * (I + H + (L - 1) * 2.0 * H), work = (double)T * B * word;   // multiplications of the weight gradients
+  return T > 1 && B <= 16384 && work >= (LsMma<TE>::kPair ? 8e9 : 4e8) && word >= (LsMma<TE>::kPair ? 2e6 : 3e5);
 }
 
 template <typename TE> hipError_t launch_ls_prep_fwd(const LsFwd& p, const LsPrepFwd& q, hipStream_t st) {

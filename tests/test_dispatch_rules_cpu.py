@@ -33,6 +33,16 @@ def test_input_product_of_layer_0_where_it_was_faster(T, I, H, L, apart):
     assert not _rule("_ZN3asx14ls_input_apartIfEEbiiii", ctypes.c_bool, *[I32] * 4)(T, I, H, L)
 
 
+@pytest.mark.parametrize("dtype, T, B, I, H, L, packed", [
+    ("t", 50, 64, 512, 1024, 4, True), ("t", 64, 192, 256, 256, 4, True), ("t", 40, 64, 512, 640, 2, True), ("t", 32, 128, 512, 512, 1, True),
+    ("t", 64, 192, 64, 128, 2, False), ("t", 60, 128, 256, 256, 2, False), ("t", 32, 64, 512, 512, 1, False),
+    ("t", 64, 12, 64, 1024, 1, False), ("t", 1, 16384, 512, 1024, 4, False), ("t", 50, 16385, 512, 1024, 4, False),
+    ("f", 30, 64, 256, 512, 2, True), ("f", 24, 48, 256, 384, 2, True), ("f", 10, 64, 256, 384, 1, True),
+    ("f", 60, 128, 64, 128, 2, False), ("f", 30, 64, 192, 192, 1, False), ("f", 24, 16, 256, 384, 1, False)])
+def test_rows_of_words_where_they_were_faster(dtype, T, B, I, H, L, packed):
+    assert _rule(f"_ZN3asx9ls_packedI{dtype}EEbiiiii", ctypes.c_bool, *[I32] * 5)(T, B, I, H, L) == packed
+
+
 def _plan(M, N, K, batch, bf16, allow_split=True, multi_segment=False, counted=False):
     """(tile, splits) of a product: tile 0 = 128 x 128, 1 = 256 x 256, 2 = 64 x 64 (bf16)."""
     f = _rule("_ZN3asx9gemm_planEiiiibbbb", ctypes.c_uint64, *[I32] * 4, *[ctypes.c_bool] * 4)
