@@ -62,8 +62,7 @@ struct GemmArgs {
   bool pad_out = false;         // columns N .. ldc - 1 of C's rows are padding: they may be written (with anything finite)
   int act_tanh = 0;
   int accumulate = 0;
-  // a float result past the caches (the first of products in one launch, both operands strided, no split)
-  bool past_caches = false;
+  bool past_caches = false;     // a float result past the caches (64x64 and 128x128 kernels of strided operands, no split)
   uint32_t drop_thr = 0;        // 0 = no dropout
   float drop_scale = 1.f;       // 1 / (1 - p)
   uint64_t drop_seed = 0;

@@ -496,19 +496,24 @@ static hipError_t launch_tile_shape(const GemmDev& d, int out_bf16, hipStream_t 
 // 36.2; 64: 2048 x 768 x 1500 13.8 / 14.5, 4096 x 1024 x 6400 84.8 / 91.1.
 bool gemm_tile_laced(bool a_kc, int64_t blocks) { return a_kc || blocks <= 256; }
 
-template <bool AKC, bool BKC>
+// both operands strided
+template <TileExtra EXTRA> static hipError_t launch_tile_tn(const GemmDev& d, GemmTile tile, int out_bf16, hipStream_t st) {
+  if (!gemm_tile_laced(false, (int64_t)d.tiles_m * d.tiles_n * d.nz))
+    return tile == kTile64 ? launch_tile_shape<2, false, false, 4, false, EXTRA>(d, out_bf16, st)
+                           : launch_tile_shape<4, false, false, 2, false, EXTRA>(d, out_bf16, st);
+  return tile == kTile64 ? launch_tile_shape<2, false, false, 4, true, EXTRA>(d, out_bf16, st)
+                         : launch_tile_shape<4, false, false, 4, true, EXTRA>(d, out_bf16, st);   // (a block per compute unit)
+}
+// A contiguous
+template <bool BKC>
 static hipError_t launch_tile_form(const GemmDev& d, GemmTile tile, int out_bf16, hipStream_t st) {
+  constexpr bool AKC = true;
   const int64_t blocks = (int64_t)d.tiles_m * d.tiles_n * d.nz;
-  if constexpr (!AKC) {
-    if (!gemm_tile_laced(AKC, blocks))
-      return tile == kTile64 ? launch_tile_shape<2, AKC, BKC, 4, false>(d, out_bf16, st)
-                             : launch_tile_shape<4, AKC, BKC, 2, false>(d, out_bf16, st);
-  }
   // (launch_gemm_bf16: 64 x 64 only)
-  if constexpr (AKC && !BKC) {
+  if constexpr (!BKC) {
     if (d.C_second) return launch_tile_shape<2, AKC, BKC, 4, true, kSecond>(d, out_bf16, st);
   }
-  if constexpr (AKC && BKC) {
+  if constexpr (BKC) {
     if (d.row_stats) {
       if (tile == kTile64) return launch_tile_shape<2, AKC, BKC, 4, true, kStats>(d, out_bf16, st);
       return blocks <= 256 ? launch_tile_shape<4, AKC, BKC, 4, true, kStats>(d, out_bf16, st) : hipErrorInvalidValue;
@@ -523,8 +528,7 @@ static hipError_t launch_tile_form(const GemmDev& d, GemmTile tile, int out_bf16
   if (tile == kTile64) return launch_tile_shape<2, AKC, BKC, 4, true>(d, out_bf16, st);
   // 128 KiB of LDS where no compute unit gets a second block anyway
   if (blocks <= 256) return launch_tile_shape<4, AKC, BKC, 4, true>(d, out_bf16, st);
-  if constexpr (AKC) return launch_tile_shape<4, AKC, BKC, 2, true>(d, out_bf16, st);
-  return hipErrorInvalidValue;   // (not reached)
+  return launch_tile_shape<4, AKC, BKC, 2, true>(d, out_bf16, st);
 }
 
 // ---- several products in one launch ------------------------------------------------
@@ -639,6 +643,14 @@ static hipError_t launch_together_with(const GemmDev* d, const TileForm* f, int 
   if (n == 4) return launch_members(false, st, tn, more[0], more[1], more[2]);
   return hipErrorNotSupported;
 }
+// past the caches: all of them, the first alone, or none
+template <typename TN, typename TNPast>
+static hipError_t launch_together_any(const GemmDev* d, const TileForm* f, int n, hipStream_t st) {
+  int past = 0;
+  for (int i = 0; i < n; ++i) past += d[i].past_caches ? 1 : 0;
+  if (past == n) return launch_together_with<TNPast, TNPast>(d, f, n, st);
+  return d[0].past_caches ? launch_together_with<TNPast, TN>(d, f, n, st) : launch_together_with<TN, TN>(d, f, n, st);
+}
 hipError_t launch_gemm_bf16_tiles_together(const GemmDev* d, const TileForm* f, int n, const DbReduce* sums, hipStream_t st) {
   if (n < 2 || f[0].a_kc || f[0].b_kc) return hipErrorNotSupported;
   if (sums) {
@@ -652,10 +664,8 @@ hipError_t launch_gemm_bf16_tiles_together(const GemmDev* d, const TileForm* f, 
     if (f[i].tile != kTile64) return hipErrorNotSupported;
     blocks += (int64_t)d[i].tiles_m * d[i].tiles_n * d[i].nz;
   }
-  if (!gemm_tile_laced(false, blocks))
-    return d[0].past_caches ? launch_together_with<MemberTNPast, MemberTN>(d, f, n, st) : launch_together_with<MemberTN, MemberTN>(d, f, n, st);
-  return d[0].past_caches ? launch_together_with<MemberTNLacedPast, MemberTNLaced>(d, f, n, st)
-                          : launch_together_with<MemberTNLaced, MemberTNLaced>(d, f, n, st);
+  return gemm_tile_laced(false, blocks) ? launch_together_any<MemberTNLaced, MemberTNLacedPast>(d, f, n, st)
+                                        : launch_together_any<MemberTN, MemberTNPast>(d, f, n, st);
 }
 
 // ---- few rows ----------------------------------------------------------------------
@@ -756,9 +766,10 @@ hipError_t launch_gemm_bf16_few(const GemmDev& d, bool out_bf16, hipStream_t st)
 }
 
 hipError_t launch_gemm_bf16_tile(const GemmDev& d, GemmTile tile, bool a_kc, bool b_kc, bool out_bf16, hipStream_t st) {
-  if (a_kc && b_kc) return launch_tile_form<true, true>(d, tile, out_bf16, st);
-  if (a_kc && !b_kc) return launch_tile_form<true, false>(d, tile, out_bf16, st);
-  if (!a_kc && !b_kc) return launch_tile_form<false, false>(d, tile, out_bf16, st);
+  if (a_kc && b_kc) return launch_tile_form<true>(d, tile, out_bf16, st);
+  if (a_kc && !b_kc) return launch_tile_form<false>(d, tile, out_bf16, st);
+  if (!a_kc && !b_kc && !d.copy_pos)
+    return d.past_caches ? launch_tile_tn<kPast>(d, tile, out_bf16, st) : launch_tile_tn<kNoExtra>(d, tile, out_bf16, st);
   return hipErrorInvalidValue;  // (A strided, B contiguous) is not used by the path
 }
 

@@ -38,6 +38,7 @@ struct LsLayout {
   std::vector<GemmPlan> p_dwi;
   std::vector<size_t> dw_at;               // partial sums of the weight gradients that are not batched, behind `partial`
   GemmPlan p_dwh, p_dx, p_gx;
+  bool dw_past;   // the weight gradients that are not batched past the caches
   bool dwh_batched, dwi_batched;   // dW_hh of all layers, dW_ih of all but the first, in one launch
   bool x_apart;   // the input product of layer 0 ahead of the wavefronts
   bool w_rows;    // forward wavefronts read the caller's weight rows
@@ -142,10 +143,19 @@ LsLayout make_ls_layout(const ls_shape* s) {
     beside += upl(gemm_partial_bytes(4 * H, cols, 1, p.splits), kAlignL);
     mx(beside);
   };
+  size_t dw_bytes = 0;
   for (int l = 0; l < NL; ++l) {
+    const int Il = l == 0 ? I : H;
     if (!L.dwh_batched) one(H, L.p_dwh);
-    if (!L.dwi_batched || l == 0) one(l == 0 ? I : H, L.p_dwi[l]);
+    if (!L.dwi_batched || l == 0) one(Il, L.p_dwi[l]);
+    dw_bytes += (L.dwh_batched ? 0 : (size_t)16 * H * H) + (L.dwi_batched && l > 0 ? 0 : (size_t)16 * H * Il);
   }
+  // From a quarter of the L2s together on; smaller ones are the same either way.  Forward and backward, us, plain / past, alone; with a
+  // running sum; with Adam behind it: 256 -> 2 x 256, 30 x 16 (4 MB) 417.9 / 417.7; 431.3 / 431.2; 431.9 / 432.1; 512 -> 512, 32 x 64 (8
+  // MB) 507 / 506; 535 / 526; 545.7 / 545.9; 256 -> 2 x 512, 24 x 16 (15 MB) 416.8 / 415.6; 433.7 / 432.9; 460.7 / 462.4; 512 -> 1024, 32
+  // x 32 (25 MB) 638 / 613; 656 / 654; 677.5 / 676.3; 512 -> 2 x 768, 20 x 32 (35 MB) 496 / 473; 523.6 / 522.2; 551.7 / 549.9; 512 -> 2 x
+  // 1024, 20 x 16 (59 MB) 542 / 516; 580.5 / 576.9; 629 / 632.
+  L.dw_past = dw_bytes >= (size_t)8 << 20;
   // The reduction split of the gradient of x is a function of the widths alone: with a split chosen from the row
   // count, a sentence's gradients would depend (in the last fp32 bit) on how many sentences share its batch.
   L.p_dx = gemm_plan(TB, I, 4 * H, 1, bf, false);
@@ -375,6 +385,7 @@ as_status ls_bwd(const ls_shape* s, const LsLayout& L, const char* x, const int3
     g[n].M = 4 * H; g[n].N = Il;
     g[n].K_dev = n_words;
     g[n].C = dW; g[n].ldc = Il; g[n].c_bf16 = false;
+    g[n].past_caches = L.dw_past;
     g[n].splits = p.splits; g[n].partial = partial + L.dw_at[made++] / sizeof(float);
     tiles[n++] = p.tile;
     if (n < kMaxTogether && made < (int)L.dw_at.size()) return hipSuccess;
