@@ -530,7 +530,7 @@ static as_status fwd_impl(const as_shape* s, const void* h_dec, const void* h_en
     AS_TRY(AS_STAGE_ATTN_SCORE,
            launch_attn_fwd_fused(w + L.q, w + L.q_lo, he, src_len, B, T, S, H, reinterpret_cast<float*>(w + L.alpha32),
                                  w + L.alphaE, w + L.alphaE_lo, L.ldS, w + L.ctx, w + L.ctx_lo, attn_mask, list, ticket, st));
-  } else if (!bf && attn_f32_fused_supported(S)) {
+  } else if (!bf && attn_f32_fused_supported(S, H)) {
     auto f = [&](size_t at) { return reinterpret_cast<float*>(w + at); };
     AS_TRY(AS_STAGE_ATTN_SCORE,
            launch_attn_f32_fwd(f(L.q), f(L.q_lo), reinterpret_cast<const float*>(he), src_len, B, T, S, H, f(L.alpha32), f(L.alphaE),
@@ -678,7 +678,7 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
            launch_attn_bwd_fused(w + L.dC, w + L.dC_lo, he, src_len, B, T, S, H,
                                  reinterpret_cast<const float*>(w + L.alpha32), w + L.dscoreE, w + L.dscoreE_lo, L.ldS,
                                  w + L.dQ, st));
-  } else if (!bf && attn_f32_fused_supported(S)) {
+  } else if (!bf && attn_f32_fused_supported(S, H)) {
     auto f = [&](size_t at) { return reinterpret_cast<float*>(w + at); };
     AS_TRY(AS_STAGE_ATTN_BWD,
            launch_attn_f32_bwd(f(L.dC), f(L.dC_lo), reinterpret_cast<const float*>(he), src_len, B, T, S, H, f(L.alpha32), f(L.dscoreE),

@@ -251,7 +251,7 @@ template <bool BWD, int ST> hipError_t launch_shape(const AttnF32Args& p, hipStr
   return hipGetLastError();
 }
 template <bool BWD> hipError_t launch_any(const AttnF32Args& p, hipStream_t st) {
-  if (!attn_f32_fused_supported(p.S) || p.B < 1 || p.T < 1 || p.ldS < p.S || p.ldS > kMaxS) return hipErrorInvalidValue;
+  if (!attn_f32_fused_supported(p.S, p.H) || p.B < 1 || p.T < 1 || p.ldS < p.S || p.ldS > kMaxS) return hipErrorInvalidValue;
   if (p.S <= 16) return launch_shape<BWD, 1>(p, st);
   if (p.S <= 32) return launch_shape<BWD, 2>(p, st);
   if (p.S <= 64) return launch_shape<BWD, 4>(p, st);
@@ -259,7 +259,13 @@ template <bool BWD> hipError_t launch_any(const AttnF32Args& p, hipStream_t st) 
 }
 }  // namespace
 
-bool attn_f32_fused_supported(int S) { return S >= 1 && S <= kMaxS; }
+// More than 64 source positions: a wave's eight tiles a step and each row's sweeps over the columns are one chain per workgroup, longer
+// than three launches where there is more than one sweep (256 columns) and few workgroups.  A training step, us, separate / fused, 16
+// steps of S 128: H 256, 1 sentence 119.6 / 112.2, 32 156.9 / 151.9; H 320, 1 131.5 / 133.7, 16 148.3 / 155.4; 512, 16 193.1 / 197.6; 1024, 4
+// 274.0 / 295.4; 2048, 4 549.9 / 603.8.  With 64 and more workgroups it would win there too (43 sentences x 48 steps, H 512 of 72
+// positions 446 / 416), but a sentence's attention must not depend on how many share its batch.  S 64: H 2048, 1 524.0 / 496.3, 16
+// 806.7 / 778.5, 4096, 4 1075.6 / 1024.9.
+bool attn_f32_fused_supported(int S, int H) { return S >= 1 && (S <= 64 || (S <= kMaxS && H <= 256)); }
 
 hipError_t launch_attn_f32_fwd(const float* q, const float* q_lo, const float* h_enc, const int32_t* src_len, int B, int T, int S,
                                int H, float* alpha32, float* alphaE, float* alphaE_lo, int64_t ldS, float* ctx, float* ctx_lo,

@@ -55,8 +55,8 @@ hipError_t launch_gather_rows(const int32_t* rows, const int32_t* n_act, int N, 
 hipError_t launch_scatter_rows(const int32_t* row_pos, int N, const void* src0, void* dst0, const void* src1,
                                void* dst1, int64_t bytes, hipStream_t st);
 
-// The same two for fp32 storage, S <= 128.
-bool attn_f32_fused_supported(int S);
+// The same two for fp32 storage.
+bool attn_f32_fused_supported(int S, int H);
 hipError_t launch_attn_f32_fwd(const float* q, const float* q_lo, const float* h_enc, const int32_t* src_len, int B, int T, int S,
                                int H, float* alpha32, float* alphaE, float* alphaE_lo, int64_t ldS, float* ctx, float* ctx_lo,
                                uint8_t* attn_mask, const RowList& list, int32_t* zero, hipStream_t st);

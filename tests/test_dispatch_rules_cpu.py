@@ -43,6 +43,12 @@ def test_rows_of_words_where_they_were_faster(dtype, T, B, I, H, L, packed):
     assert _rule(f"_ZN3asx9ls_packedI{dtype}EEbiiiii", ctypes.c_bool, *[I32] * 5)(T, B, I, H, L) == packed
 
 
+@pytest.mark.parametrize("S, H, fused", [(1, 1, True), (64, 4096, True), (65, 256, True), (128, 256, True), (65, 257, False), (128, 2048, False),
+                                         (129, 64, False)])
+def test_f32_attention_in_one_launch_where_it_was_faster(S, H, fused):
+    assert _rule("_ZN3asx24attn_f32_fused_supportedEii", ctypes.c_bool, I32, I32)(S, H) == fused
+
+
 def _plan(M, N, K, batch, bf16, allow_split=True, multi_segment=False, counted=False):
     """(tile, splits) of a product: tile 0 = 128 x 128, 1 = 256 x 256, 2 = 64 x 64 (bf16)."""
     f = _rule("_ZN3asx9gemm_planEiiiibbbb", ctypes.c_uint64, *[I32] * 4, *[ctypes.c_bool] * 4)

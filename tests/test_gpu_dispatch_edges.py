@@ -418,10 +418,12 @@ def test_more_words_than_whole_vectors_reach(step):
                                    (5, 33, 6, 67, 131),       # no whole vectors
                                    (35, 64, 2, 141, 131),
                                    (3, 65, 5, 36, 131),
-                                   (18, 128, 2, 1028, 131),   # the longest source, several sweeps over the columns
+                                   (18, 64, 2, 1028, 131),    # several sweeps over the columns
+                                   (18, 128, 2, 256, 131),    # the longest source, one whole sweep
+                                   (18, 128, 2, 1028, 131), (3, 65, 2, 257, 131),   # more of both: separate launches
                                    (4, 129, 3, 36, 131)])     # one more: separate launches
 def test_f32_fused_attention_at_tile_edges(shape, skip):
-    """fp32, S <= 128: 16 decoder steps and 16 to 128 source positions per workgroup; one sentence of length 0."""
+    """fp32, S <= 64, or S <= 128 and H <= 256: 16 decoder steps and 16 to 128 source positions per workgroup; one sentence of length 0."""
     T, S, B, H, V = shape
     inp = make_custom(T=T, S=S, B=B, H=H, V=V, seed=S + H, dtype="f32", min_len=1, pad_prob=0.1, w=0.05 if H > 1000 else 0.1)
     inp.src_len[B // 2] = 0
