@@ -1113,13 +1113,14 @@ hipError_t launch_ls_bias_reduce(const float* dbacc, const LsBiasOut& o, int L, 
 }
 
 // One step: how many steps of the weight rows, which come from memory, a wave of the smaller blocks has in flight; K: the
-// layer's input width.  With PF in flight PF - 1 - n % PF loads of n steps are past the end and waited for with the others, so
-// six only where they save two of those; with PF = n + 1 all are requested at once and none is past the end.  A layer-step of H
-// units from H, 16 x 16 blocks, us with four / six / n + 1: n = 1 (64) 5.8 / 6.7, 4 (256) 7.8 / 7.1 / 6.8, 5 (320) 8.0 / 7.5 / 7.6, 6
-// (384) 8.1 / 9.8 / 8.0, 7 (448) 8.2 / 9.8 / 8.8, 8 (512) 10.1 / - / 9.2, 10 (640) 9.8 / 10.0, 12 (768) 11.8 / 12.7, 14 (896) 11.9 / 12.8,
-// 16 (1024) 14.0 / 13.2, 17 (1088) 14.1 / 13.3, 20 (1280) 16.3 / 16.4, 22 (1408) 16.2 / 16.2; 16 x 32 blocks, 8 (512) 10.8 / 11.1,
-// 14 13.4 / 15.0, 16 16.0 / 15.6.  (Eight: 4 x 1024 units x 128 sentences 75.4, six 68.5.  Layer 0 of ls_reads_states, which splits
-// the states it loads: four, 256 -> 512 units 9.9, all at once 11.4.)
+// layer's input width.  With PF in flight PF - 1 - n % PF loads of n steps are past the end and waited for with the others: three of
+// four in flight where four divides n.  There, up to eight steps (what registers hold of 16 x 16 blocks), all are requested at once and
+// none is past the end; else six in flight where they save two such loads.  A layer-step of H units from H, 16 x 16 blocks, us
+// with four / six / all: n = 1 (64) 5.8 / 6.7, 4 (256) 7.8 / 7.1 / 6.8, 5 (320) 8.0 / 7.5 / 7.6, 6 (384) 8.1 / 9.8 / 8.0, 7 (448) 8.2 / 9.8 /
+// 8.8, 8 (512) 10.1 / - / 9.2, 10 (640) 9.8 / 10.0, 12 (768) 11.8 / 12.7, 14 (896) 11.9 / 12.8, 16 (1024) 14.0 / 13.2, 17 (1088) 14.1 / 13.3,
+// 20 (1280) 16.3 / 16.4, 22 (1408) 16.2 / 16.2; 16 x 32 blocks, 8 (512) 10.8 / 11.1, 14 13.4 / 15.0, 16 16.0 / 15.6.  (Eight: 4 x 1024
+// units x 128 sentences 75.4, six 68.5.  Layer 0 of ls_reads_states, which splits the states it loads: four, 256 -> 512 units 9.9,
+// all at once 11.4.)
 static int ls_row_steps(int K, int H) {   // of a wave
   constexpr int KST = LsGeom<uint16_t>::kKStep;
   return ((H + KST - 1) / KST + (K + KST - 1) / KST + LS_KS - 1) / LS_KS;
@@ -1187,9 +1188,8 @@ template <typename TE> hipError_t launch_ls_wave_fwd(const LsFwd& p, int d, hipS
     if (blocks >= 192) return ls_fwd_shape<TE, 4, 2, 4>(p, d, l_lo, nl, st);
     if (p.direct && l_lo == 0) return ls_fwd_shape<TE, 4, 1, 4>(p, d, l_lo, nl, st);
     if (p.w_rows) {
-      const int n = ls_row_steps(K, p.H);
+      const int n = ls_row_steps(K, p.H);   // all at once: a slot more than steps
       if (n == 4) return ls_fwd_shape<TE, 4, 1, 4, 5>(p, d, l_lo, nl, st);
-      if (n == 6) return ls_fwd_shape<TE, 4, 1, 4, 7>(p, d, l_lo, nl, st);
       if (n == 8) return ls_fwd_shape<TE, 4, 1, 4, 9>(p, d, l_lo, nl, st);
     }
     return pf == 6 ? ls_fwd_shape<TE, 4, 1, 4, 6>(p, d, l_lo, nl, st) : ls_fwd_shape<TE, 4, 1, 4>(p, d, l_lo, nl, st);
