@@ -61,6 +61,8 @@ GEMM_STAGES = {  # stage -> flops per launch; N = all positions, R = rows of the
     "gemm_dwa": lambda N, R, H, V: 2.0 * N * H * H,
     "gemm_dh": lambda N, R, H, V: 2.0 * N * H * H,
 }
+# small sizes: products that share the launch, and with it the stage, of another (d_h_enc with gemm_dwa apart)
+SAME_LAUNCH = {"gemm_dwout": ["gemm_dhc"], "gemm_dwc": ["gemm_dch", "gemm_dch"], "gemm_dwa": ["gemm_dh"]}
 
 
 def _source_digest(names):
@@ -443,8 +445,9 @@ def main():
         gemm_ms = {k: step_ms_by_stage.get(k, 0.0) for k in GEMM_STAGES}
         dom = max(gemm_ms, key=gemm_ms.get)
         flops = GEMM_STAGES[dom](N, R, H, V)
-        if dom == "gemm_dwout" and not gemm_ms["gemm_dhc"]:   # small sizes: both products in one launch
-            flops += GEMM_STAGES["gemm_dhc"](N, R, H, V)
+        flops += sum(GEMM_STAGES[k](N, R, H, V) for k in SAME_LAUNCH.get(dom, []) if not gemm_ms[k])
+        if dom == "gemm_dwa" and not gemm_ms["gemm_dh"] and T > 1:
+            flops += 4.0 * N * S * H
         avg_ms = per_stage[dom]
         ach = flops / (avg_ms * 1e-3) / 1e12 if avg_ms > 0 else 0.0
         bf = inp.dtype == "bf16"

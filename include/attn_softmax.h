@@ -186,12 +186,15 @@ const char* attn_softmax_last_error(void);
  * Per-kernel timing for benchmarks.  While enabled, every kernel the library
  * enqueues is bracketed by HIP events on the caller's stream.
  * attn_softmax_profile_read synchronises those events, adds the elapsed times
- * into per-stage totals and returns them; stage ids are as_stage.  Enabling
+ * into per-stage totals and returns them; stage ids are as_stage.  Small sizes
+ * have {DWOUT, DHC, the column sums}, {DWC, DCH} and {DWA, DH, the last product
+ * of ATTN_BWD} in one launch each, which is the first one's.  Enabling
  * clears the totals.  Not thread-safe; meant for one benchmarking thread.
  */
 typedef enum {
   AS_STAGE_GEMM_Q = 0,        /* Q = h_dec W_a                      (Eq. 2)  */
-  AS_STAGE_ATTN_SCORE = 1,    /* batched Q_b h_enc_b^T              (Eq. 2)  */
+  AS_STAGE_ATTN_SCORE = 1,    /* batched Q_b h_enc_b^T              (Eq. 2), or
+                                 all of attention and the list of words' rows */
   AS_STAGE_ATTN_SOFTMAX = 2,  /* masked softmax rows                (Eq. 1)  */
   AS_STAGE_ATTN_CTX = 3,      /* batched alpha_b h_enc_b            (Eq. 3)  */
   AS_STAGE_GEMM_HC = 4,       /* tanh(W_c[c;h])                     (Eq. 4)  */
@@ -208,7 +211,7 @@ typedef enum {
   AS_STAGE_GEMM_DH = 15,      /* d_h_dec = dH1 + dQ W_a^T                    */
   AS_STAGE_MISC = 16,         /* small reductions, split-K combine           */
   AS_STAGE_ADAM = 17,         /* attn_softmax_adam_step                      */
-  AS_STAGE_COMPACT = 18,      /* row list, gather of h_c rows, scatter of dz */
+  AS_STAGE_COMPACT = 18,      /* gather of h_c rows, scatter of dz           */
   AS_STAGE_COUNT = 19
 } as_stage;
 

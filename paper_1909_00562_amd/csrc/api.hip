@@ -102,11 +102,39 @@ struct StageTimer {
     if (!rec.a || !rec.b) return;
     live = hipEventRecord(rec.a, st) == hipSuccess;
   }
+  void drop() {   // nothing was enqueued
+    if (!live) return;
+    live = false;
+    g_prof.pool.push_back(rec.a);
+    g_prof.pool.push_back(rec.b);
+  }
   ~StageTimer() {
     if (!live) return;
     if (hipEventRecord(rec.b, st) == hipSuccess) g_prof.pending.push_back(rec);
   }
 };
+
+// Products that wait for the same thing: one launch, timed as stage[0], or a launch and a stage each.
+hipError_t gemm_group(const as_stage* stage, const GemmArgs* g, const GemmTile* tiles, int n, bool bf, hipStream_t st,
+                      const DbReduce* sums = nullptr) {
+  {
+    StageTimer timer(stage[0], st);
+    const hipError_t e = launch_gemm_joint(g, tiles, n, bf, st, sums);
+    if (e != hipErrorNotSupported) return e;
+    timer.drop();
+  }
+  if (sums) {
+    StageTimer timer(AS_STAGE_MISC, st);
+    const hipError_t e = launch_db_reduce(*sums, st);
+    if (e != hipSuccess) return e;
+  }
+  for (int i = 0; i < n; ++i) {
+    StageTimer timer(stage[i], st);
+    const hipError_t e = launch_gemm(g[i], bf, tiles[i], st);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
 
 // ---- workspace layout ------------------------------------------------------------
 constexpr size_t kAlign = 256;
@@ -309,6 +337,11 @@ as_status check_common(const as_shape* s, const void* h_dec, const void* h_enc, 
       StageTimer timer_(stage, st);                                                      \
       e_ = (expr);                                                                       \
     }                                                                                    \
+    if (e_ != hipSuccess) return fail(AS_ERR_HIP, "%s: %s", #expr, hipGetErrorString(e_)); \
+  } while (0)
+#define AS_TRY_TIMED(expr)   /* expr times its own stages */                             \
+  do {                                                                                   \
+    const hipError_t e_ = (expr);                                                        \
     if (e_ != hipSuccess) return fail(AS_ERR_HIP, "%s: %s", #expr, hipGetErrorString(e_)); \
   } while (0)
 
@@ -620,7 +653,8 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
     g[1].splits = L.p_dhc.splits; g[1].partial = reinterpret_cast<float*>(w + L.partial_dz);
     if (L.out_pair) {
       const GemmTile tiles[2] = {L.p_dwout.tile == kTile256 ? kTile128 : L.p_dwout.tile, L.p_dhc.tile};
-      AS_TRY(AS_STAGE_GEMM_DWOUT, launch_gemm_together(g, tiles, 2, bf, st, &sums));
+      const as_stage stages[2] = {AS_STAGE_GEMM_DWOUT, AS_STAGE_GEMM_DHC};
+      AS_TRY_TIMED(gemm_group(stages, g, tiles, 2, bf, st, &sums));
     } else {
       AS_TRY(AS_STAGE_GEMM_DWOUT, launch_gemm(g[0], bf, L.p_dwout.tile, st));
       AS_TRY(AS_STAGE_GEMM_DHC, launch_gemm(g[1], bf, L.p_dhc.tile, st));
@@ -664,7 +698,8 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
       g[2].C = d_h_dec; g[2].ldc = H; g[2].c_bf16 = false;
     }
     const GemmTile tiles[3] = {L.p_dwc.tile, L.p_dch.tile, L.p_dch.tile};
-    AS_TRY(AS_STAGE_GEMM_DWC, launch_gemm_together(g, tiles, L.dch_pair ? 2 : 3, bf, st));
+    const as_stage stages[3] = {AS_STAGE_GEMM_DWC, AS_STAGE_GEMM_DCH, AS_STAGE_GEMM_DCH};
+    AS_TRY_TIMED(gemm_group(stages, g, tiles, L.dch_pair ? 2 : 3, bf, st));
   }
   const bool one_step = bf && attn_one_step_bwd_supported(T, S, H);
   if (one_step) {
@@ -739,7 +774,8 @@ as_status attn_softmax_bwd(const as_shape* s, const void* h_dec, const void* h_e
   }
   GemmTile tiles[3] = {L.p_dwa.tile, L.p_dh.tile, L.p_ds.tile};
   if (L.p_dwa.tile == kTile64 && (one_step || L.p_ds.tile == kTile64)) tiles[1] = kTile64;
-  AS_TRY(AS_STAGE_GEMM_DWA, launch_gemm_together(g, tiles, one_step ? 2 : 3, bf, st));
+  const as_stage stages[3] = {AS_STAGE_GEMM_DWA, AS_STAGE_GEMM_DH, AS_STAGE_ATTN_BWD};
+  AS_TRY_TIMED(gemm_group(stages, g, tiles, one_step ? 2 : 3, bf, st));
   return AS_OK;
 }
 

@@ -146,12 +146,13 @@ inline size_t gemm_partial_bytes(int M, int N, int batch, int splits) {
 // Enqueue; return hipSuccess or the launch error.  `in_bf16` selects the kernel family.
 hipError_t launch_gemm(const GemmArgs& g, bool in_bf16, GemmTile tile, hipStream_t st);
 // Products that do not depend on each other, in one launch where there is a kernel for the combination and its tiles (bf16:
-// kTile64, two of them also kTile128; fp32: 32 x 32), else one after the other; splits are combined afterwards.  sums: column
-// sums of dlogits beside {dW_out, dz}.
+// kTile64, two of them also kTile128; fp32: 32 x 32), else hipErrorNotSupported and nothing is enqueued; splits are combined
+// afterwards.  sums: column sums of dlogits beside {dW_out, dz}.  launch_gemm_together: one after the other there instead.
 constexpr int kMaxTogether = 4;
 struct DbReduce;
-hipError_t launch_gemm_together(const GemmArgs* g, const GemmTile* tile, int n, bool in_bf16, hipStream_t st,
-                                const DbReduce* sums = nullptr);
+hipError_t launch_gemm_joint(const GemmArgs* g, const GemmTile* tile, int n, bool in_bf16, hipStream_t st,
+                             const DbReduce* sums = nullptr);
+hipError_t launch_gemm_together(const GemmArgs* g, const GemmTile* tile, int n, bool in_bf16, hipStream_t st);
 hipError_t launch_gemm_bf16(const GemmArgs& g, GemmTile tile, hipStream_t st);
 hipError_t launch_gemm_bf16_together(const GemmArgs* g, const GemmTile* tile, int n, const DbReduce* sums, hipStream_t st);   // without the combines
 hipError_t launch_gemm_f32(const GemmArgs& g, hipStream_t st);

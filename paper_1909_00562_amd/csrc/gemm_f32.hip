@@ -696,19 +696,19 @@ hipError_t launch_gemm(const GemmArgs& g, bool in_bf16, GemmTile tile, hipStream
   return e;
 }
 
-hipError_t launch_gemm_together(const GemmArgs* g, const GemmTile* tile, int n, bool in_bf16, hipStream_t st,
-                                const DbReduce* sums) {
+hipError_t launch_gemm_joint(const GemmArgs* g, const GemmTile* tile, int n, bool in_bf16, hipStream_t st, const DbReduce* sums) {
   for (int i = 0; i < n; ++i)
     if (g[i].row_pos && g[i].splits <= 1) return hipErrorInvalidValue;
   hipError_t e = in_bf16 ? launch_gemm_bf16_together(g, tile, n, sums, st) : launch_gemm_f32_together(g, n, sums, st);
-  if (e == hipErrorNotSupported) {
-    if (sums && (e = launch_db_reduce(*sums, st)) != hipSuccess) return e;
-    for (int i = 0; i < n; ++i)
-      if ((e = launch_gemm(g[i], in_bf16, tile[i], st)) != hipSuccess) return e;
-    return e;
-  }
   for (int i = 0; i < n && e == hipSuccess; ++i)
     if (g[i].splits > 1) e = launch_splitk_combine(g[i], in_bf16, st);
+  return e;
+}
+hipError_t launch_gemm_together(const GemmArgs* g, const GemmTile* tile, int n, bool in_bf16, hipStream_t st) {
+  hipError_t e = launch_gemm_joint(g, tile, n, in_bf16, st);
+  if (e != hipErrorNotSupported) return e;
+  e = hipSuccess;
+  for (int i = 0; i < n && e == hipSuccess; ++i) e = launch_gemm(g[i], in_bf16, tile[i], st);
   return e;
 }
 

@@ -428,3 +428,21 @@ def test_f32_fused_attention_at_tile_edges(shape, skip):
     inp = make_custom(T=T, S=S, B=B, H=H, V=V, seed=S + H, dtype="f32", min_len=1, pad_prob=0.1, w=0.05 if H > 1000 else 0.1)
     inp.src_len[B // 2] = 0
     _parity(inp, skip)
+
+
+@pytest.mark.parametrize("shape, alone", [((5, 6, 7, 136, 2003), False), ((64, 64, 256, 2048, 1003), True)])
+def test_stage_times_of_products_with_and_without_a_launch_of_their_own(shape, alone):
+    """A product in a launch of its own is timed under its own stage, products that share one under the first one's."""
+    import paper_1909_00562_amd as lib
+    T, S, B, H, V = shape
+    db = lib.DeviceBatch(make_custom(T=T, S=S, B=B, H=H, V=V, seed=1, dtype="bf16", min_len=1, w=0.05))
+    lib.attn_softmax_profile_enable(True)
+    try:
+        db.fwd(), db.bwd(), db.sync()
+        launches = {k: v["launches"] for k, v in lib.attn_softmax_profile_read().items()}
+    finally:
+        lib.attn_softmax_profile_enable(False)
+    got = {k: launches[k] for k in ("gemm_dwout", "gemm_dhc", "gemm_dwc", "gemm_dch", "gemm_dwa", "gemm_dh", "attn_bwd", "misc")}
+    # attn_bwd: the first half in one kernel, and d_h_enc; misc: the sum of the losses, and the column sums of dlogits
+    assert got == dict(gemm_dwout=1, gemm_dhc=int(alone), gemm_dwc=1, gemm_dch=2 * alone, gemm_dwa=1, gemm_dh=int(alone),
+                       attn_bwd=1 + alone, misc=2 * alone)
