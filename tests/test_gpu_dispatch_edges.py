@@ -430,6 +430,39 @@ def test_f32_fused_attention_at_tile_edges(shape, skip):
     _parity(inp, skip)
 
 
+@pytest.mark.parametrize("entry, S", [("fwd", 5), ("fwd", 129), ("step", 5)])     # the three kernels ahead of the statistics
+@pytest.mark.parametrize("skip", [False, True])
+def test_loss_sum_of_further_calls_on_a_workspace(entry, S, skip):
+    """Rows in several blocks, of which the last adds up the losses: every call finds one.  The sum is of floats in double, rounded once."""
+    import torch
+    import paper_1909_00562_amd as lib
+    N, H, V, pad = 130, 72, 2003, 0
+    g = torch.Generator(device="cuda").manual_seed(3)
+    new = lambda *s: torch.rand(*s, generator=g, device="cuda").mul_(0.2).sub_(0.1).bfloat16()
+    h, he, W_a, W_c, W_out, b_out = new(N, H), new(S, N, H), new(H, H), new(H, 2 * H), new(V, H), new(V)
+    src_len = torch.full((N,), S, dtype=torch.int32, device="cuda")
+    loss_sum, n_tok = torch.empty(1, device="cuda"), torch.empty(1, dtype=torch.int32, device="cuda")
+    tok_loss, argmax = torch.empty(N, device="cuda"), torch.empty(N, dtype=torch.int32, device="cuda")
+    shape = lib.AsShape(1, S, N, H, V, pad, lib.AS_BF16, 1.0, 0.0, 0, 1 if skip else 0)
+    n = (lib.attn_softmax_step_workspace_bytes if entry == "step" else lib.attn_softmax_workspace_bytes)(shape)
+    ws = torch.full((n,), 0x5a, dtype=torch.uint8, device="cuda")
+    if entry == "step":
+        lib.attn_softmax_step_prepare(shape, he, W_a, ws, n)
+    for words in (N, 77, 0, 129):
+        targets = torch.randint(1, V, (N,), generator=g, device="cuda", dtype=torch.int32)
+        targets[words:] = pad
+        loss_sum.fill_(float("nan")), n_tok.fill_(-1), tok_loss.fill_(float("nan"))
+        if entry == "step":
+            lib.attn_softmax_step_fwd(shape, h, he, src_len, W_c, W_out, b_out, targets, loss_sum, n_tok, tok_loss, argmax, ws, n)
+        else:
+            lib.attn_softmax_fwd(shape, h, he, src_len, W_a, W_c, W_out, b_out, targets, loss_sum, n_tok, tok_loss, argmax,
+                                 None, None, ws, n)
+        torch.cuda.synchronize()
+        want = float(tok_loss.double().sum())
+        assert int(n_tok.item()) == words and bool((tok_loss[words:] == 0).all())
+        assert abs(float(loss_sum.item()) - want) <= 2 ** -23 * abs(want) and (want > words or words == 0)
+
+
 @pytest.mark.parametrize("shape, alone", [((5, 6, 7, 136, 2003), False), ((64, 64, 256, 2048, 1003), True)])
 def test_stage_times_of_products_with_and_without_a_launch_of_their_own(shape, alone):
     """A product in a launch of its own is timed under its own stage, products that share one under the first one's."""
