@@ -405,6 +405,7 @@ def test_sequences_with_final_cells_on_top_of_initial_states(dtype, T, B, I, H, 
     ("bf16", 33, 70, 264, 776, 2, 0.0),        # the gradient of x in a split product
     ("bf16", 60, 97, 1024, 208, 4, 0.0),       # in one that is not, and the input product ahead of the wavefronts
     ("bf16", 60, 97, 1024, 200, 3, 0.0),       # too little per word: rows per position
+    ("bf16", 9, 37, 64, 1024, 4, 0.3),         # weight gradients of a kind of all layers in one launch
     # no whole vectors.  (With 219 units three of the 876 elements of db[1], sums over 37 sentences that no product here makes and
     # whose norm is right to 1.1e-7, lie so near zero that 1e-4 of them is less than their terms' rounding; 0.003 of them may.)
     ("f32", 21, 37, 67, 222, 2, 0.3),
