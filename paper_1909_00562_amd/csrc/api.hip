@@ -241,9 +241,9 @@ Layout make_layout(const as_shape* s) {
   L.tokloss = take((size_t)N * 4);
   L.q_lo = take(NH * L.e);
   L.alphaE_lo = take(BTSl * L.e);
-  L.dact = take(NH * 4);
-  L.ctx_lo = take(NH * L.e);
   L.compact = s->skip_pad_rows != 0;
+  L.dact = take(L.compact && !L.hc_gather ? 0 : NH * 4);   // (else the product writes it to its compacted rows alone)
+  L.ctx_lo = take(NH * L.e);
   L.row_pos = L.rows = L.n_act = L.hc_c = L.dact_c = L.dz_c = L.dz_lo_c = 0;
   if (L.compact) {
     L.row_pos = take((size_t)N * 4);

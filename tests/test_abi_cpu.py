@@ -52,6 +52,17 @@ def test_workspace_bytes():
     assert 4.19e9 < bd.attn_softmax_workspace_bytes(s) < 6e9
 
 
+@pytest.mark.parametrize("kw, elem", [(dict(T=9, S=7, B=100, H=136, V=4001, dtype=bd.AS_BF16), 2), (dict(T=30, S=30, B=64, H=512, V=16000), 4)])
+def test_row_compaction_keeps_one_tanh_derivative(kw, elem):
+    """Where no pass of its own gathers rows, skip_pad_rows adds a dense block of h_c and two lists of rows: the derivative is in its
+    dense block alone."""
+    s = _shape(**kw)
+    all_rows = bd.attn_softmax_workspace_bytes(s)
+    s.skip_pad_rows = 1
+    dense = s.T * s.B * (s.H * elem + 8)
+    assert dense <= bd.attn_softmax_workspace_bytes(s) - all_rows <= dense + 4096
+
+
 def _call_fwd(shape, ptrs=None, ws_bytes=1 << 40, **over):
     # fake, 16-byte aligned, never dereferenced addresses: every check below fails before a launch
     a = dict(h_dec=0x1000, h_enc=0x2000, src_len=0x3000, W_a=0x4000, W_c=0x5000, W_out=0x6000, b_out=0x7000,
