@@ -25,6 +25,8 @@
 // unit: 8.4, 13.8, 23.3, 107.  The kernel this replaced, four waves that brought both operands through LDS a tile ahead in
 // registers: 20.6, 32.8, 36.4, 104 forward and 17.3, -, 33.5, 108 backward (now 6.2, -, 18.1, 91); T 80 S 80 B 128 H 1024
 // 69 and 66, now 43 and 43; T 1 S 50 B 128 H 1024 29, now 9.5.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 #include "lds_limit.h"
@@ -56,8 +58,10 @@ struct AttnFwdArgs {
   int T, S, B, H;
   int64_t ldS;
   int y0;                                // first block of decoder steps of this launch
-  int32_t* zero;                         // forward: cleared, if not null
-  RowList list;                          // forward: made by the blocks x = B, y = 0 of the first launch, if wanted
+};
+struct AttnFwdMore : AttnFwdArgs {
+  int32_t* zero;                         // cleared, if not null
+  RowList list;                          // made by the blocks x = B, y = 0 of the first launch, if wanted
 };
 
 // LDS of a workgroup of 16 RT decoder steps x 16 ST source positions: a slot of NT x 16 columns of encoder states per wave;
@@ -75,15 +79,17 @@ template <int RT, int ST> struct AttnLds {
 // 16-byte piece c of slot row k is kept at c ^ slot_swizzle(k): the four rows of a transposing read lie in different banks
 template <int NT> __device__ __forceinline__ int slot_swizzle(int k) { return NT == 4 ? (k & 2) << 1 : 0; }
 
-template <bool BWD, int RT, int ST>
-__global__ __launch_bounds__(64 * AF_NW) void attn_fused_kernel(AttnFwdArgs p) {
+// Args: AttnFwdMore where the forward pass has either to do, an instance of its own: its arguments and tests cost the others 0.3 us (53 x
+// 52, H 256 7.2 / 6.9, 29 x 7, H 192 6.1 / 5.8).
+template <bool BWD, int RT, int ST, typename Args>
+__global__ __launch_bounds__(64 * AF_NW) void attn_fused_kernel(Args p) {
   typedef AttnLds<RT, ST> Lds;
   constexpr int NW = AF_NW, ROWS = Lds::kRows, SLD = Lds::kSld, KB = Lds::kKB, NT = Lds::kNT, RB = Lds::kRB;
   extern __shared__ __align__(1024) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c16 = lane & 15, q4 = lane >> 4;
-  if constexpr (!BWD) {
+  if constexpr (std::is_same<Args, AttnFwdMore>::value) {
     if (p.zero && blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) *p.zero = 0;
     if (blockIdx.x == (unsigned)p.B) {
       if (blockIdx.y == 0) row_list_block<64 * AF_NW>(p.list, reinterpret_cast<int*>(smem));
@@ -352,22 +358,23 @@ __global__ __launch_bounds__(64 * AF_NW) void attn_fused_kernel(AttnFwdArgs p) {
 
 bool attn_fwd_fused_supported(int S, int H) { return S >= 1 && S <= 128 && (H % 8) == 0; }
 
-template <bool BWD, int RT, int ST> static hipError_t launch_attn_shape(AttnFwdArgs p, hipStream_t st) {
-  auto k = attn_fused_kernel<BWD, RT, ST>;
+template <bool BWD, int RT, int ST, typename Args> static hipError_t launch_attn_shape(Args p, hipStream_t st) {
+  auto k = attn_fused_kernel<BWD, RT, ST, Args>;
   constexpr int smem = AttnLds<RT, ST>::kBytes;
   static LdsLimit limit;
   const hipError_t e = limit.raise(reinterpret_cast<const void*>(k), smem);
   if (e != hipSuccess) return e;
   const int ny = (p.T + 16 * RT - 1) / (16 * RT);
   for (p.y0 = 0; p.y0 < ny; p.y0 += kGridY) {   // (more than a million decoder steps: several launches)
-    const int list = p.y0 == 0 && p.list.targets ? 1 : 0;
+    int list = 0;
+    if constexpr (std::is_same<Args, AttnFwdMore>::value) list = p.y0 == 0 && p.list.targets ? 1 : 0;
     hipLaunchKernelGGL(k, dim3(p.B + list, ny - p.y0 < kGridY ? ny - p.y0 : kGridY), dim3(64 * AF_NW), smem, st, p);
     const hipError_t launched = hipGetLastError();
     if (launched != hipSuccess) return launched;
   }
   return hipSuccess;
 }
-template <bool BWD> static hipError_t launch_attn_fused(const AttnFwdArgs& p, hipStream_t st) {
+template <bool BWD, typename Args> static hipError_t launch_attn_fused(const Args& p, hipStream_t st) {
   if (!attn_fwd_fused_supported(p.S, p.H) || p.B < 1 || p.T < 1 || p.ldS < p.S || p.ldS > 128) return hipErrorInvalidValue;
   // (the order of every sum is the same in all of them; the figures are at the head of this file)
   if (p.S > 64) return launch_attn_shape<BWD, 1, 8>(p, st);
@@ -379,7 +386,7 @@ template <bool BWD> static hipError_t launch_attn_fused(const AttnFwdArgs& p, hi
 hipError_t launch_attn_fwd_fused(const void* q_hi, const void* q_lo, const void* h_enc, const int32_t* src_len, int B,
                                  int T, int S, int H, float* alpha32, void* alphaE, void* alphaE_lo, int64_t ldS,
                                  void* ctx, void* ctx_lo, uint8_t* attn_mask, const RowList& list, int32_t* zero, hipStream_t st) {
-  AttnFwdArgs p{};
+  AttnFwdMore p{};
   p.zero = zero;
   p.list = list;
   p.q_hi = reinterpret_cast<const uint16_t*>(q_hi);
@@ -394,7 +401,7 @@ hipError_t launch_attn_fwd_fused(const void* q_hi, const void* q_lo, const void*
   p.attn_mask = attn_mask;
   p.T = T; p.S = S; p.B = B; p.H = H;
   p.ldS = ldS;
-  return launch_attn_fused<false>(p, st);
+  return zero || list.targets ? launch_attn_fused<false>(p, st) : launch_attn_fused<false>(static_cast<const AttnFwdArgs&>(p), st);
 }
 
 hipError_t launch_attn_bwd_fused(const void* dC_hi, const void* dC_lo, const void* h_enc, const int32_t* src_len,

@@ -121,6 +121,12 @@ def test_fused_attention_of_wide_states_with_large_weights(shape):
     _parity(make_custom(T=T, S=S, B=B, H=H, V=V, seed=S, dtype="bf16", min_len=1, pad_prob=0.1, w=0.1))
 
 
+@pytest.mark.parametrize("T, S, B", [(9, 5, 120), (33, 5, 97), (9, 40, 120), (33, 40, 97), (9, 100, 120)])   # 16 steps a workgroup, 32
+def test_fused_attention_without_a_list_or_a_count_to_clear(T, S, B):
+    """More than 1024 rows, padding rows not left out: the forward pass has nothing but the attention to do."""
+    _parity(make_custom(T=T, S=S, B=B, H=72, V=8011, seed=S, dtype="bf16", min_len=1, pad_prob=0.1))
+
+
 def test_fused_attention_of_more_steps_than_a_grid_has_blocks():
     """S > 64 takes 16 decoder steps per workgroup: 16 * 65536 + 64 steps need more workgroups than a grid may have in one
     direction.  Every step repeats the one 64 before it, so its results do too, bit for bit."""
