@@ -52,16 +52,22 @@ bool projection_leaves_stats(int N, int V, int H) {
   if (N > 1024 || !gemm_vector_reach(V, (V + 7) / 8 * 8)) return false;
   return tile == kTile64 || (tile == kTile128 && (int64_t)((N + 127) / 128) * ((V + 127) / 128) <= 256);
 }
-// The gradients of weights past the caches, in products of one launch: where dW_out is larger than the L2s together (32 MiB) they
-// push out the operands that the blocks share, and most of them are gone from there anyway when they are read.  Who reads it next
-// decides what that is worth, us, plain / past: 128 x 1024, 32000 words (131 MB) the step alone 178.4 / 165.0; the backward pass of
-// one LSTM step behind it and every gradient added to a running sum 532.8 / 521.6, one layer 365.6 / 356.1; the backward pass of an
-// LSTM layer over 50 steps and Adam 1049.5 / 1040.5; but Adam alone at once behind it 354.0 / 363.1.  64 x 512, 32000 words (66 MB),
-// with the sums 239.3 / 236.4.  Below the line plain, since whoever reads them gains more than the step alone loses; alone, with Adam,
-// with the sums: 294 x 1024, 2292 words (9 MB) 138.4 / 136.6, 168.1 / 169.7, 152.5 / 159.4; 325 x 704, 4363 (12 MB) 101.4 / 100.1, 127.8 /
-// 129.1, 115.7 / 123.1; 2604 x 832, 6666 (22 MB) 259.8 / 258.9, 303.5 / 305.7, 274.6 / 284.0; 1920 x 512, 16000 words (33 MB) 221.7 / 219.5
-// and with Adam 276.2 / 279.4.  d_h_enc, which the backward pass of the encoder reads at once, is plain everywhere.
-bool gradients_past_caches(int V, int H) { return (int64_t)V * H * (int64_t)sizeof(float) > (int64_t)32 << 20; }
+// The gradients of weights past the caches, in products of one launch: where dW_out is larger than the L2s together (32 MiB), or
+// all of them than one and a half times that, they push out the operands that the blocks share, and most of them are gone from there
+// anyway when they are read.  Who reads it next decides what that is worth, us, plain / past: 128 x 1024, 32000 words (dW_out 131 MB)
+// the step alone 178.4 / 165.0; the backward pass of one LSTM step behind it and every gradient added to a running sum 532.8 /
+// 521.6, one layer 365.6 / 356.1; the backward pass of an LSTM layer over 50 steps and Adam 1049.5 / 1040.5; but Adam alone at once
+// behind it 354.0 / 363.1.  64 x 512, 32000 words (66 MB), with the sums 239.3 / 236.4.  Rows x units, words (dW_out, all in MB), alone,
+// with Adam, with the sums: above the line 40 x 2048, 1000 (8, 59) 138.8 / 136.7, 226.0 / 218.5, 164.4 / 166.3; 80 x 1536, 4000 (25, 53)
+// 138.0 / 134.3, 213.8 / 208.4, 160.6 / 162.6; 800 x 1280, 6000 (31, 50) 199.2 / 198.0, 281.8 / 279.4, 221.9 / 226.2.  Below it plain, since
+// whoever reads them gains what the step alone loses, or more: 60 x 1728, 1200 (8, 44) 135.9 / 132.8, 190.9 / 189.3, 154.4 / 160.8; 294 x
+// 1024, 2292 (9, 22) 138.4 / 136.6, 168.1 / 169.7, 152.5 / 159.4; 325 x 704, 4363 (12, 18) 101.4 / 100.1, 127.8 / 129.1, 115.7 / 123.1; 2604 x
+// 832, 6666 (22, 30) 259.8 / 258.9, 303.5 / 305.7, 274.6 / 284.0; 1920 x 512, 16000 (33, 36) 221.7 / 219.5, 276.2 / 279.4.  d_h_enc, which the
+// backward pass of the encoder reads at once, is plain everywhere.
+bool gradients_past_caches(int V, int H) {
+  const int64_t dw_out = (int64_t)V * H * (int64_t)sizeof(float), all = dw_out + 3 * (int64_t)H * H * (int64_t)sizeof(float);
+  return dw_out > (int64_t)32 << 20 || all > (int64_t)48 << 20;
+}
 }  // namespace asx
 
 namespace {

@@ -142,6 +142,11 @@ def test_gradients_past_the_caches_where_dw_out_is_larger_than_they_are(V, H, pa
     assert _rule("_ZN3asx21gradients_past_cachesEii", ctypes.c_bool, I32, I32)(V, H) == past
 
 
+@pytest.mark.parametrize("V, H, past", [(6000, 1280, True), (4000, 1536, True), (1, 2048, True), (2, 2047, False), (1200, 1728, False), (2292, 1024, False)])
+def test_gradients_past_the_caches_where_all_of_them_are_larger_still(V, H, past):
+    assert _rule("_ZN3asx21gradients_past_cachesEii", ctypes.c_bool, I32, I32)(V, H) == past
+
+
 @pytest.mark.parametrize("edge, form, M, N, laced", [
     (128, "TN", 1024, 1024, True), (128, "NN", 2257, 1000, True), (64, "NT", 128, 1024, True), (64, "TN", 1024, 1024, True),
     (128, "NT", 6400, 1024, True), (128, "NT", 600, 8000, True), (128, "NN", 6400, 1024, True), (64, "NT", 6400, 1024, True),
